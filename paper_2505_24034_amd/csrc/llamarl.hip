@@ -94,7 +94,6 @@ struct BwdWs {
 // Most workgroups a persistent grid has (one per CU of an MI355X); also the most split items the last round of a
 // store contraction can hold, each leaving one BM x BN fp32 block in the workspace.
 constexpr int MAX_GRID = 256;
-constexpr int STORE_MAX_SPLITS = 8;
 BwdWs bwd_ws(int64_t N, int64_t d, int64_t V, llamarl_dtype dt, int64_t max_rows_per_pass) {
   BwdWs w;
   const size_t es = esize(dt);
@@ -178,7 +177,7 @@ llamarl_status launch_store_mode(const StoreArgs& a, int64_t work_items, int til
     // the split tiles of the last round, if the device-side sizes left any: fewer than `grid` of them
     const int tail = std::min(grid - 1, tiles_worst);
     if (tail > 0) {
-      k_reduce_tail<MODE><<<dim3((unsigned)tail, BM / TAIL_STRIPE_ROWS), dim3(256), 0, st>>>(a);
+      k_reduce_tail<MODE><<<dim3((unsigned)std::min(tail * TAIL_UNITS, TAIL_MAX_BLOCKS)), dim3(256), 0, st>>>(a);
       HIP_TRY(hipGetLastError());
     }
   }
