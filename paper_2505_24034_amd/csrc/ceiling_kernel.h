@@ -65,7 +65,7 @@ __global__ __launch_bounds__(NTHREADS) void k_mfma_ceiling(int iters, float* sin
 // loads wraps inside a row.  Values computed are meaningless (slabs are overwritten while they are read); every
 // access is in bounds and every wavefront runs the same `iters` iterations.
 constexpr int CEILING_PANEL_K = 4096;                                        // elements per panel row (8 KB)
-constexpr size_t CEILING_PANEL_BYTES = (size_t)2 * BM * CEILING_PANEL_K * 2;   // both panels
+constexpr size_t CEILING_PANEL_BYTES = (size_t)2 * Shape256::BM * CEILING_PANEL_K * 2;   // both panels
 
 __device__ __forceinline__ void ceiling_k_step(bf16x8_t (&a)[MB], const bf16x8_t (&bc)[NB], bf16x8_t (&bn)[NB],
                                                f32x4_t (&acc)[MB][NB], const char* pa_cur, const char* pa_nxt,
@@ -101,10 +101,10 @@ __device__ __forceinline__ void ceiling_k_step(bf16x8_t (&a)[MB], const bf16x8_t
 __device__ __forceinline__ void ceiling_traffic_loop(int iters, float* sink, const void* panels, char* smem,
                                                      const bool READS, const bool LOADS) {
   const int lane = threadIdx.x & 63, wave = wave_id();
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const int wm = wave / Shape256::WAVES_N, wn = wave % Shape256::WAVES_N;
   SlabLoader<BF16> la, lb;
-  la.init(panels, CEILING_PANEL_K, BM, wave, lane);
-  lb.init(reinterpret_cast<const char*>(panels) + (size_t)BM * CEILING_PANEL_K * 2, CEILING_PANEL_K, BN, wave, lane);
+  la.init(panels, CEILING_PANEL_K, Shape256::BM, wave, lane);
+  lb.init(reinterpret_cast<const char*>(panels) + (size_t)Shape256::BM * CEILING_PANEL_K * 2, CEILING_PANEL_K, Shape256::BN, wave, lane);
   // both stages start with panel data (every variant: the registers then hold the caller's operand values)
 #pragma unroll
   for (int s = 0; s < 2; ++s)
@@ -120,7 +120,7 @@ __device__ __forceinline__ void ceiling_traffic_loop(int iters, float* sink, con
   int a_addr[2], b_addr[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
-    a_addr[ks] = (wm * WAVE_M + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
+    a_addr[ks] = (wm * Shape256::WAVE_M + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
     b_addr[ks] = SLAB_A_BYTES + (wn * WAVE_N + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
   }
   bf16x8_t a[MB], b0[NB], b1[NB];

@@ -1,9 +1,11 @@
-// gemm_nt.h -- the one MFMA main loop every contraction of the path runs on.
+// gemm_nt.h -- the MFMA main loop of the large bf16 contractions, and the pieces (tile shapes, schedule, slab loads,
+// fragment layout) that the other loops share with it.
 //
 // C[m,n] = sum_k A[m,k] * B[n,k]   ("NT": both operands are K-contiguous), fp32 accumulate.
 //   forward / recompute : A = W [V,d] tile       B = H rows (gathered)   K = d
 //   dW = dz^T H         : A = dz^T [V,N]         B = H^T [d,N]           K = N
 //   (fp32 only) dH      : A = dz [N,V]           B = W^T [d,V]           K = V
+// fp32 runs on the loop of gemm_small.h; the k-major dH contraction of bf16 on that of gemm_tn.h.
 //
 // gfx950 mapping
 //   - one workgroup = 8 wavefronts (2 x 4) = one 256 x 256 output tile; a wavefront owns 128 x 64 of it as
@@ -31,20 +33,31 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
-constexpr int BM = 256;       // tile rows (A rows)
-constexpr int BN = 256;       // tile cols (B rows)
-constexpr int NTHREADS = 512;
-constexpr int WAVES_N = 4;    // wave grid 2 (M) x 4 (N)
-constexpr int MB = 8;         // 16 x 16 MFMA blocks per wave along M  (128 rows)
-constexpr int NB = 4;         // ... along N                            (64 cols)
-constexpr int WAVE_M = MB * 16;
+constexpr int NB = 4;         // 16 x 16 MFMA blocks per wave along N (64 cols), in every tile shape
 constexpr int WAVE_N = NB * 16;
 constexpr int SLAB_ROW_BYTES = 128;
 constexpr int BLOCK_BYTES = 16 * SLAB_ROW_BYTES;                  // 16 slab rows: one MFMA block of an operand
-constexpr int SLAB_A_BYTES = BM * SLAB_ROW_BYTES;                 // 32 KB
-constexpr int STAGE_BYTES = (BM + BN) * SLAB_ROW_BYTES;           // 64 KB
-constexpr int MAINLOOP_LDS_BYTES = 2 * STAGE_BYTES;               // 128 KB
 constexpr uint32_t OOB_OFFSET = 0x80000000u;                      // beyond any descriptor range used here
+
+// A workgroup's output tile: WM x WN wavefronts, each MB_ x NB MFMA blocks.
+template <int WM, int WN, int MB_>
+struct TileShape {
+  static constexpr int WAVES_M = WM, WAVES_N = WN, WAVES = WM * WN, THREADS = 64 * WM * WN;
+  static constexpr int MB = MB_, WAVE_M = MB_ * 16;
+  static constexpr int BM = WM * WAVE_M, BN = WN * WAVE_N;        // tile rows (A rows), tile columns (B rows)
+  static constexpr int SLAB_A_BYTES = BM * SLAB_ROW_BYTES;
+  static constexpr int STAGE_BYTES = (BM + BN) * SLAB_ROW_BYTES;  // one K slab of both operands
+};
+typedef TileShape<2, 4, 8> Shape256;   // 256 x 256, 8 wavefronts of 128 x 64
+typedef TileShape<2, 2, 4> Shape128;   // 128 x 128, 4 wavefronts of  64 x 64
+typedef TileShape<4, 1, 1> Shape64;    //  64 x  64, 4 wavefronts of  16 x 64
+
+// the 256 x 256 loop's own constants
+constexpr int MB = Shape256::MB;
+constexpr int NTHREADS = Shape256::THREADS;
+constexpr int SLAB_A_BYTES = Shape256::SLAB_A_BYTES;              // 32 KB
+constexpr int STAGE_BYTES = Shape256::STAGE_BYTES;                // 64 KB
+constexpr int MAINLOOP_LDS_BYTES = 2 * STAGE_BYTES;               // 128 KB
 
 struct BF16 {
   typedef uint16_t store_t;
@@ -81,11 +94,14 @@ __device__ __forceinline__ uint16_t float_to_bf16_bits(float f) {  // round to n
   return (uint16_t)(u >> 16);
 }
 
-// Where the accumulator element (ib, jb, r) of this lane sits inside the 256 x 256 tile.
+// Where the accumulator element (ib, jb, r) of this lane sits inside the tile.
 // MFMA 16x16 output layout: register r of lane l holds row 4 (l / 16) + r, column l % 16.
+template <typename S>
 struct LanePos {
   int wm, wn, lane;
-  __device__ __forceinline__ int row(int ib, int r) const { return wm * WAVE_M + ib * 16 + (lane >> 4) * 4 + r; }
+  __device__ __forceinline__ explicit LanePos(int tid)
+      : wm((tid >> 6) / S::WAVES_N), wn((tid >> 6) % S::WAVES_N), lane(tid & 63) {}
+  __device__ __forceinline__ int row(int ib, int r) const { return wm * S::WAVE_M + ib * 16 + (lane >> 4) * 4 + r; }
   __device__ __forceinline__ int col(int jb) const { return wn * WAVE_N + jb * 16 + (lane & 15); }
   // Quad-interleaved columns (see tile_row_of): the lane's four column blocks hold NEIGHBOURING columns
   // col_quad() + jb, so 16 lanes own 64 consecutive columns of one row.
@@ -154,18 +170,32 @@ struct TileSchedule {
   }
 };
 
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+// buffer_load_dwordx4 ... lds, written out by hand.  The compiler's wait-count pass cannot tell which LDS bytes
+// an LDS-direct load will fill: with the builtin, transposing reads (ds_read_b64_tr_b16 carries no memory operand) and
+// reads through a computed stage address wait for ALL loads in flight, which serialises the loop.  Issued from inline
+// asm the loads are invisible to that pass; the loop's own s_waitcnt vmcnt + barrier order them against the reads.
+__device__ __forceinline__ void lds_dma16(uint32_t lds_addr, uint32_t voff, i32x4_t rsrc, uint32_t soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
+               : "memory", "m0");
+}
+
 __device__ __forceinline__ int swizzle(int row) { return (row >> 1) & 7; }
 
-// One operand slab stream: 256 rows x 128 bytes per step; this thread moves four 16-byte chunks of it.
-// Wave-instruction `it` of wave w fills rows (it*8 + w)*8 .. +7 of the slab; lane l takes row +l/8 and the
-// physical 16-byte slot l%8.  Because it*64 rows is a multiple of 16, the swizzle (and so the logical chunk this
-// lane fetches) is the same for all four instructions.
-template <typename TT>
+// One operand slab stream: ROWS rows x 128 bytes per step; this thread moves ITERS 16-byte chunks of it.
+// Wave-instruction `it` of wave w fills rows (it*WAVES + w)*8 .. +7 of the slab; lane l takes row +l/8 and the
+// physical 16-byte slot l%8.  Because it*WAVES*8 rows is a multiple of 16, the swizzle (and so the logical chunk this
+// lane fetches) is the same for all instructions.
+template <typename TT, int ROWS = Shape256::BM, int WAVES = Shape256::WAVES>
 struct SlabLoader {
+  static constexpr int ITERS = ROWS / (8 * WAVES);
+  static_assert(ITERS * 8 * WAVES == ROWS && (8 * WAVES) % 16 == 0, "whole wave-instructions, one swizzle for all");
   // The buffer descriptor is rebuilt from these at every use; readfirstlane pins them to scalar registers, so
   // the compiler never has to guess that the descriptor is wave-uniform (a guess it loses across loops).
   uint32_t base_lo, base_hi, records;
-  uint32_t voff[4];       // per-lane byte offset of (row, logical chunk) inside the panel at k = 0
+  uint32_t voff[ITERS];   // per-lane byte offset of (row, logical chunk) inside the panel at k = 0
 
   __device__ __forceinline__ void set_base(const void* base, uint32_t bytes) {
     const uint64_t p = reinterpret_cast<uint64_t>(base);
@@ -181,48 +211,36 @@ struct SlabLoader {
   __device__ __forceinline__ static int lane_chunk(int wave, int lane) {
     return (lane & 7) ^ swizzle(wave * 8 + (lane >> 3));
   }
-  // base: first row of the tile; ld in elements; rows_valid <= 256 rows exist from base on.
+  // base: first row of the tile; ld in elements; rows_valid <= ROWS rows exist from base on.
   template <bool QUAD = false>
   __device__ __forceinline__ void init(const void* base, int64_t ld, int rows_valid, int wave, int lane) {
     const uint32_t row_bytes = (uint32_t)(ld * (int64_t)sizeof(typename TT::store_t));
     set_base(base, row_bytes * (uint32_t)rows_valid);
     const uint32_t c16 = (uint32_t)lane_chunk(wave, lane) * 16u;
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int row = tile_row_of<QUAD>((it * 8 + wave) * 8 + (lane >> 3));
+    for (int it = 0; it < ITERS; ++it) {
+      const int row = lane_tile_row<QUAD>(it, wave, lane);
       voff[it] = (row < rows_valid) ? (uint32_t)row * row_bytes + c16 : OOB_OFFSET;
     }
   }
-  // Gathered panel: tile row r is row rows[r] of the whole matrix `base` (total_rows rows, < 2^31 bytes).
-  // Free with per-lane buffer offsets: this is how masked tokens are skipped without a packed copy of H.
-  template <bool QUAD = false>
-  __device__ __forceinline__ void init_gather(const void* base, int64_t ld, int64_t total_rows, const int32_t* rows,
-                                              int rows_valid, int wave, int lane) {
-    const uint32_t row_bytes = (uint32_t)(ld * (int64_t)sizeof(typename TT::store_t));
-    set_base(base, (uint32_t)total_rows * row_bytes);
-    const uint32_t c16 = (uint32_t)lane_chunk(wave, lane) * 16u;
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int row = tile_row_of<QUAD>((it * 8 + wave) * 8 + (lane >> 3));
-      voff[it] = (row < rows_valid) ? (uint32_t)rows[row] * row_bytes + c16 : OOB_OFFSET;
-    }
-  }
-  // The four tile rows this lane fetches (one per wave-instruction), for callers that load the gather list
-  // themselves -- in one batch, ahead of time -- and hand the result to init_gathered().
+  // The tile rows this lane fetches (one per wave-instruction).
   template <bool QUAD = false>
   __device__ __forceinline__ static int lane_tile_row(int it, int wave, int lane) {
-    return tile_row_of<QUAD>((it * 8 + wave) * 8 + (lane >> 3));
+    return tile_row_of<QUAD>((it * WAVES + wave) * 8 + (lane >> 3));
   }
+  // Gathered panel: tile row r is a row of the whole matrix `base` (total_rows rows, < 2^31 bytes).  Free with per-lane
+  // buffer offsets: this is how masked tokens are skipped without a packed copy of H.  The caller loads the gather
+  // list entries itself, in one batch and ahead of time.
   // grow[it] = row of the whole matrix that tile row lane_tile_row(it) maps to (any valid row where the tile row
   // is >= rows_valid: it is not fetched).
   template <bool QUAD = false>
-  __device__ __forceinline__ void init_gathered(const void* base, int64_t ld, int64_t total_rows, const int (&grow)[4],
+  __device__ __forceinline__ void init_gathered(const void* base, int64_t ld, int64_t total_rows, const int (&grow)[ITERS],
                                                 int rows_valid, int wave, int lane) {
     const uint32_t row_bytes = (uint32_t)(ld * (int64_t)sizeof(typename TT::store_t));
     set_base(base, (uint32_t)total_rows * row_bytes);
     const uint32_t c16 = (uint32_t)lane_chunk(wave, lane) * 16u;
 #pragma unroll
-    for (int it = 0; it < 4; ++it)
+    for (int it = 0; it < ITERS; ++it)
       voff[it] = (lane_tile_row<QUAD>(it, wave, lane) < rows_valid) ? (uint32_t)grow[it] * row_bytes + c16 : OOB_OFFSET;
   }
   // k0: first k of the slab (elements); K: contraction length.  lds: start of this operand's slab in LDS.
@@ -232,12 +250,22 @@ struct SlabLoader {
     const int soff = k0 * (int)sizeof(typename TT::store_t);
     uint32_t v = voff[it];
     if (tail) v = (k0 + lane_chunk(wave, lane) * TT::EPC >= K) ? OOB_OFFSET : v;   // `tail` is a constant once inlined
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc(), (lds_void_ptr)(lds + (it * 8 + wave) * 8 * SLAB_ROW_BYTES), 16,
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc(), (lds_void_ptr)(lds + (it * WAVES + wave) * 8 * SLAB_ROW_BYTES), 16,
                                              (int)v, soff, 0, 0);
+  }
+  // all of a slab's loads, hidden from the compiler's wait-count pass (lds_dma16)
+  __device__ __forceinline__ void issue_opaque(char* lds, int k0, int K, int wave, int lane) const {
+    const i32x4_t rs = {(int)base_lo, (int)(base_hi & 0xffffu), (int)records, 0x00020000};
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+    const bool past = k0 + lane_chunk(wave, lane) * TT::EPC >= K;
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it)
+      lds_dma16(lds0 + (uint32_t)((it * WAVES + wave) * 8 * SLAB_ROW_BYTES), past ? OOB_OFFSET : voff[it], rs,
+                (uint32_t)k0 * (uint32_t)sizeof(typename TT::store_t));
   }
   __device__ __forceinline__ void issue(char* lds, int k0, int K, int wave, int lane) const {
 #pragma unroll
-    for (int it = 0; it < 4; ++it) issue_one(lds, it, k0, K, wave, lane, true);
+    for (int it = 0; it < ITERS; ++it) issue_one(lds, it, k0, K, wave, lane, true);
   }
 };
 
@@ -324,25 +352,27 @@ __device__ __forceinline__ void k_step(typename TT::frag_t (&a)[MB], const typen
 //   run():      the K loop.  Waves leave it at different times: __syncthreads() before reusing LDS.
 // smem must hold MAINLOOP_LDS_BYTES.
 //
-// GATHER_B: the B panel is gathered -- B_tile is then the base of the whole matrix with b_total rows and
-// tile row r is its row b_rows[r].  QUAD_B: output columns are quad-interleaved over the lane's four column blocks
+// QUAD_B: output columns are quad-interleaved over the lane's four column blocks
 // (tile_row_of); the epilogue must then take its columns from LanePos::col_quad().
 template <typename TT, int LOAD_SLOT = 11>
 struct TileGemm {
+  typedef TT Type;
+  typedef Shape256 Shape;
   typedef typename TT::frag_t frag_t;
+  static constexpr bool KMAJOR = false;
   static constexpr int BK = 8 * TT::EPC;
+  static constexpr int LDS_BYTES = MAINLOOP_LDS_BYTES;
+  static constexpr int GROUPS_PER_CU = 1;      // workgroups of a persistent grid per CU
   SlabLoader<TT> la, lb;
   int K;
 
-  template <bool GATHER_B, bool QUAD_B = false>
+  template <bool QUAD_B>
   __device__ __forceinline__ void prefetch(const void* A_tile, int64_t lda, int rowsA, const void* B_tile, int64_t ldb,
-                                           int rowsB, int64_t K_, char* smem, const int32_t* b_rows = nullptr,
-                                           int64_t b_total = 0) {
+                                           int rowsB, int64_t K_, char* smem) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
     la.init(A_tile, lda, rowsA, wave, lane);
-    if constexpr (GATHER_B) lb.template init_gather<QUAD_B>(B_tile, ldb, b_total, b_rows, rowsB, wave, lane);
-    else lb.template init<QUAD_B>(B_tile, ldb, rowsB, wave, lane);
+    lb.template init<QUAD_B>(B_tile, ldb, rowsB, wave, lane);
     la.issue(smem, 0, K, wave, lane);
     lb.issue(smem + SLAB_A_BYTES, 0, K, wave, lane);
     if (K > BK) {
@@ -351,8 +381,9 @@ struct TileGemm {
     }
   }
 
-  // as prefetch<true, QUAD_B>, with the gather list entries of this lane already in registers (SlabLoader::
-  // init_gathered): no global load stands between the caller's barrier and the first slab request
+  // as prefetch, the B panel gathered: B_base is the base of the whole matrix with b_total rows, grow the gather list
+  // entries of this lane (SlabLoader::init_gathered), already in registers: no global load stands between the
+  // caller's barrier and the first slab request
   template <bool QUAD_B>
   __device__ __forceinline__ void prefetch_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
                                                     int64_t ldb, int rowsB, int64_t K_, char* smem, const int (&grow)[4],
@@ -371,7 +402,7 @@ struct TileGemm {
 
   __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[MB][NB]) {
     const int lane = threadIdx.x & 63, wave = wave_id();
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    const int wm = wave / Shape::WAVES_N, wn = wave % Shape::WAVES_N;
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -387,7 +418,7 @@ struct TileGemm {
     int a_addr[2], b_addr[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-      a_addr[ks] = (wm * WAVE_M + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
+      a_addr[ks] = (wm * Shape::WAVE_M + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
       b_addr[ks] = SLAB_A_BYTES + (wn * WAVE_N + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
     }
     // Slabs 0 and 1 were issued by prefetch(); stores of a previous epilogue may sit between them and now in the

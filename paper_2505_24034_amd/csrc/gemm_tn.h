@@ -18,25 +18,13 @@
 // two groups in different bank halves.  As in gemm_nt.h the permutation is applied on the global-address side of
 // the LDS-direct loads.
 #pragma once
-#include "gemm_nt.h"
+#include "gemm_small.h"
 
 namespace llamarl {
 
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4_t;
 typedef __attribute__((address_space(3))) s16x4_t* lds_s16x4_ptr;
 constexpr int KM_ROW_BYTES = 512;        // one k-row of a slab: 256 columns of bf16
-
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
-// buffer_load_dwordx4 ... lds, written out by hand.  The compiler's wait-count pass cannot tell which LDS bytes
-// an LDS-direct load will fill, and ds_read_b64_tr_b16 carries no memory operand, so with the builtin it makes
-// every transposing read wait for ALL loads in flight -- which serialises the loop.  Issued from inline asm the
-// loads are invisible to that pass; the loop's own s_waitcnt vmcnt(0) + barrier order them against the reads.
-__device__ __forceinline__ void lds_dma16(uint32_t lds_addr, uint32_t voff, i32x4_t rsrc, uint32_t soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
-               : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
-               : "memory", "m0");
-}
 
 // XOR applied to the 16-byte chunk index of k-row k (see the header)
 __device__ __forceinline__ int km_swz(int k) { return 2 * (k & 3) | 8 * ((k >> 3) & 1); }
@@ -89,8 +77,12 @@ struct KMajorLoader {
 };
 
 struct TileGemmTN {
-  typedef BF16 TT;
+  typedef BF16 Type;
+  typedef Shape256 Shape;
   typedef bf16x8_t frag_t;
+  static constexpr bool KMAJOR = true;
+  static constexpr int LDS_BYTES = MAINLOOP_LDS_BYTES;
+  static constexpr int GROUPS_PER_CU = 1;
   KMajorLoader la, lb;
   int k_len;
 
@@ -183,7 +175,7 @@ struct TileGemmTN {
 
   __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[MB][NB]) {
     const int lane = threadIdx.x & 63, wave = wave_id();
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    const int wm = wave / Shape::WAVES_N, wn = wave % Shape::WAVES_N;
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -198,7 +190,7 @@ struct TileGemmTN {
     const int krow = 8 * g + jrow;
     const int fx = km_swz(krow) * 16;                  // same for krow + 4; bit 3 of the k-row is g & 1 in both k-steps
     // block 0 of this wave: chunk (column / 8) before the swizzle, + the 8-byte half the lane's 4 columns sit in
-    const int a_off = krow * KM_ROW_BYTES + (wm * WAVE_M / 8 + (q4 >> 1)) * 16 + (q4 & 1) * 8;
+    const int a_off = krow * KM_ROW_BYTES + (wm * Shape::WAVE_M / 8 + (q4 >> 1)) * 16 + (q4 & 1) * 8;
     const int fxb = fx & 0x60;
     const int b_off = SLAB_A_BYTES + krow * KM_ROW_BYTES + ((wn * WAVE_N * 2) ^ (fx & 0x80)) + (q4 >> 1) * 16 + (q4 & 1) * 8;
     constexpr int KS = 32 * KM_ROW_BYTES;              // bytes between the two k-steps of a slab

@@ -13,11 +13,13 @@
 // accumulator lane then holds ONE token per column block (column = lane % 16) and 4 vocab entries per 16x16
 // block, 32 per token over the wave's 8 row blocks, so the softmax reductions over the vocabulary run inside the
 // lane's own registers and finish with two cross-lane steps (lane groups l/16 hold different rows).
+//
+// Every kernel is a template over its main loop G (TileGemm, TileGemmSmall, TileGemmTN), which brings element type,
+// tile shape and LDS size; llamarl.hip picks the loop.
 #pragma once
 #include "gemm_nt.h"
+#include "gemm_small.h"
 #include "gemm_tn.h"
-
-#include <type_traits>
 
 namespace llamarl {
 
@@ -41,17 +43,10 @@ constexpr int PATCH_ROWS_STORE = 8;
 // patches (8 x 4: +0.8 %, 4 x 8: +1.7 %).  Wider outputs (d = 8192, 16384) keep 8 x 4 (16 x 2: +2 - 3 % there).
 constexpr int PATCH_ROWS_KMAJOR = 16;
 
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 // v_exp_f32 without the denormal-range fix-up of exp2f(): arguments here are <= 0 up to rounding, results that
 // underflow are exact zeros in the sums they feed.
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {   // v_cvt_pk_bf16_f32: round to nearest even
-  f32x2_t v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-}
-
 // Combine a value over the four lane groups l/16 (lanes l, l^16, l^32, l^48) without going through the LDS pipe:
 // v_permlane16_swap / v_permlane32_swap of a register with a copy of itself leave "my 16-lane row's partner" and
 // "my half's partner" next to the own value.
@@ -67,6 +62,10 @@ __device__ __forceinline__ float rows_sum(float x) {
   const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
+
+// second launch bound: wavefronts per SIMD that the register allocation has to leave room for
+template <typename G>
+constexpr int MIN_WAVES = G::GROUPS_PER_CU * G::Shape::WAVES / 4;
 
 struct FwdArgs {
   const void* H;
@@ -87,22 +86,24 @@ struct FwdArgs {
 // needs for a tile are loaded in ONE batch, branch-free (indices clamped into the list), before the barrier that
 // ends the previous tile; the compiler otherwise serialises them, each behind its own s_waitcnt, and puts them
 // between the barrier and the slab requests.
-template <bool QUAD, typename Args>
-__device__ __forceinline__ void gather_rows(const TileSchedule& sch, const Args& a, int id, int n_act, int (&grow)[4]) {
+template <bool QUAD, typename G, typename Args>
+__device__ __forceinline__ void gather_rows(const TileSchedule& sch, const Args& a, int id, int n_act,
+                                            int (&grow)[decltype(G::lb)::ITERS]) {
   int tv, tt;
   sch.coords(id, tv, tt);
   const int lane = threadIdx.x & 63, wave = wave_id();
 #pragma unroll
-  for (int it = 0; it < 4; ++it) {
-    const int p = tt * BN + SlabLoader<BF16>::lane_tile_row<QUAD>(it, wave, lane);
+  for (int it = 0; it < decltype(G::lb)::ITERS; ++it) {
+    const int p = tt * G::Shape::BN + decltype(G::lb)::template lane_tile_row<QUAD>(it, wave, lane);
     grow[it] = a.rows[min(p, n_act - 1)];
   }
 }
-// both operand streams of tile `id` (rows = W tile, columns = gathered H rows), first two slabs
-template <typename TT, bool QUAD, typename Args>
-__device__ __forceinline__ void logits_fetch(TileGemm<TT>& g, const TileSchedule& sch, const Args& a, int id, int n_act,
-                                             const int (&grow)[4], char* smem) {
-  typedef typename TT::store_t st;
+// both operand streams of tile `id` (rows = W tile, columns = gathered H rows), first slabs
+template <bool QUAD, typename G, typename Args>
+__device__ __forceinline__ void logits_fetch(G& g, const TileSchedule& sch, const Args& a, int id, int n_act,
+                                             const int (&grow)[decltype(G::lb)::ITERS], char* smem) {
+  typedef typename G::Type::store_t st;
+  constexpr int BM = G::Shape::BM, BN = G::Shape::BN;
   int tv, tt;
   sch.coords(id, tv, tt);
   g.template prefetch_gathered<QUAD>((const st*)a.W + (int64_t)tv * BM * a.d, a.d,
@@ -110,24 +111,27 @@ __device__ __forceinline__ void logits_fetch(TileGemm<TT>& g, const TileSchedule
                                      (int)min((int64_t)BN, (int64_t)n_act - (int64_t)tt * BN), a.d, smem, grow, a.N);
 }
 
-constexpr int FWD_LDS_BYTES = MAINLOOP_LDS_BYTES + 2 * 2 * BN * 4;   // + per-token (max, sum) of the two wave rows
+// + per-token (max, sum) of the wave rows
+template <typename G>
+constexpr int fwd_lds_bytes = G::LDS_BYTES + 2 * G::Shape::WAVES_M * G::Shape::BN * 4;
 
-template <typename TT>
-__global__ __launch_bounds__(NTHREADS) void k_fwd_partials(FwdArgs a) {
+template <typename G>
+__global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partials(FwdArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  typedef typename TT::store_t st;
+  typedef typename G::Shape S;
+  constexpr int BM = S::BM, BN = S::BN, MB = S::MB;
   const int n_act = *a.n_act;
   TileSchedule sch;
   sch.init(a.tiles_v, (n_act + BN - 1) / BN, PATCH_ROWS_LOGITS);        // token tiles that hold active rows only
   if (!sch.has_tile()) return;                       // block-uniform
-  float* s_m = reinterpret_cast<float*>(smem + MAINLOOP_LDS_BYTES);   // [2 waves along the vocabulary][256 tokens]
-  float* s_s = s_m + 2 * BN;                                          // outside the slab buffers: see prefetch below
+  float* s_m = reinterpret_cast<float*>(smem + G::LDS_BYTES);   // [waves along the vocabulary][tokens of the tile]
+  float* s_s = s_m + S::WAVES_M * BN;                           // outside the slab buffers: see prefetch below
 
-  TileGemm<TT> g;
+  G g;
   int id = sch.take();
-  int grow[4];
-  gather_rows<false>(sch, a, id, n_act, grow);
-  logits_fetch<TT, false>(g, sch, a, id, n_act, grow, smem);
+  int grow[decltype(g.lb)::ITERS];
+  gather_rows<false, G>(sch, a, id, n_act, grow);
+  logits_fetch<false>(g, sch, a, id, n_act, grow, smem);
   while (true) {
     f32x4_t acc[MB][NB];
     g.run(smem, acc);
@@ -136,7 +140,7 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_partials(FwdArgs a) {
     // the slab requests of the next tile as well.
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
-    const LanePos lp{(tid >> 6) / WAVES_N, (tid >> 6) % WAVES_N, tid & 63};
+    const LanePos<S> lp(tid);
     int tv, tt;
     sch.coords(id, tv, tt);
     const int64_t v0 = (int64_t)tv * BM, t0 = (int64_t)tt * BN;
@@ -147,7 +151,7 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_partials(FwdArgs a) {
     // gather rows), then the targets they point to -- all issued before the slab requests below, so that waiting
     // for them later does not mean waiting for those
     const int nid = more ? sch.take() : id;
-    gather_rows<false>(sch, a, nid, n_act, grow);
+    gather_rows<false, G>(sch, a, nid, n_act, grow);
     int ytok[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) ytok[j] = a.rows[min((int)t0 + lp.col(j), n_act - 1)];
@@ -158,7 +162,7 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_partials(FwdArgs a) {
     __syncthreads();                                 // every wave is done reading the slab buffers
     if (more) {                                      // start the next tile's first slabs; the epilogue hides them
       id = nid;
-      logits_fetch<TT, false>(g, sch, a, id, n_act, grow, smem);
+      logits_fetch<false>(g, sch, a, id, n_act, grow, smem);
     }
     // From here to the next main loop nothing may wait on vmcnt: the counter is in order, so a wait for any load
     // (or spill reload) issued before the slab requests turns into a wait for the requests themselves, and the
@@ -195,7 +199,7 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_partials(FwdArgs a) {
         for (int r = 0; r < 4; ++r) s += fast_exp2(fmaf(acc[i][j][r], LOG2E, -mb));   // exp2(-inf) = 0
       s = rows_sum(s);
       // target logit: one lane of one wave of one vocab tile owns row y_t of a token; most waves own none
-      const bool mine = y >= 0 && yrow < rowsV && tok < rowsT && yrel >= 0 && yrel < WAVE_M && (yrel & 12) == 0;
+      const bool mine = y >= 0 && yrow < rowsV && tok < rowsT && yrel >= 0 && yrel < S::WAVE_M && (yrel & 12) == 0;
       if (__any(mine)) {                             // wave-uniform
         float zy = 0.f;
 #pragma unroll
@@ -211,12 +215,15 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_partials(FwdArgs a) {
     }
     __syncthreads();
     if (tid < rowsT) {
-      const float m0 = s_m[tid], m1 = s_m[BN + tid];
-      const float M = fmaxf(m0, m1);
+      float M = s_m[tid];
+#pragma unroll
+      for (int w = 1; w < S::WAVES_M; ++w) M = fmaxf(M, s_m[w * BN + tid]);
       const float Mb = (M == -INFINITY) ? 0.f : M;
-      const float S = s_s[tid] * __expf(m0 - Mb) + s_s[BN + tid] * __expf(m1 - Mb);
+      float sum = s_s[tid] * __expf(s_m[tid] - Mb);
+#pragma unroll
+      for (int w = 1; w < S::WAVES_M; ++w) sum += s_s[w * BN + tid] * __expf(s_m[w * BN + tid] - Mb);
       a.part_m[(int64_t)tv * a.n_pad + t0 + tid] = M;
-      a.part_s[(int64_t)tv * a.n_pad + t0 + tid] = S;
+      a.part_s[(int64_t)tv * a.n_pad + t0 + tid] = sum;
     }
     if (!more) break;
   }
@@ -277,9 +284,10 @@ __global__ __launch_bounds__(MERGE_TOKENS * MERGE_SLICES) void k_merge_logp(Merg
       a.out1[t] = Sx;
       a.out2[t] = (y >= 0 && y < a.V) ? a.zt[p] : 0.f;
     } else {
-      const float l = Mx + logf(Sx);
-      a.out1[t] = l;
-      a.out0[t] = a.zt[p] - l;
+      // in double: lse and logp each carry one fp32 rounding, at the size of the result
+      const double l = (double)Mx + log((double)Sx);
+      a.out1[t] = (float)l;
+      a.out0[t] = (float)((double)a.zt[p] - l);
     }
   }
 }
@@ -403,29 +411,29 @@ struct DzArgs {
   const int32_t* n_act;
 };
 
-template <typename TT>
-__global__ __launch_bounds__(NTHREADS) void k_bwd_dz(DzArgs a) {
+template <typename G>
+__global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  typedef typename TT::store_t st;
+  typedef typename G::Shape S;
+  constexpr int BM = S::BM, BN = S::BN, MB = S::MB;
   const int n_act = *a.n_act;
   const int64_t ldzt = packed_pitch(n_act);
   TileSchedule sch;
   sch.init(a.tiles_v, (n_act + BN - 1) / BN, PATCH_ROWS_LOGITS);
   if (!sch.has_tile()) return;                       // block-uniform: no active token at all
-  // bf16: token columns are fetched quad-interleaved (a lane's four column blocks are neighbouring tokens), so the
-  // vocab-major dz^T leaves straight from registers, 8 bytes per lane and whole 128-byte lines per 16 lanes.
-  constexpr bool QUAD = sizeof(st) == 2;
-  TileGemm<TT> g;
+  // token columns are fetched quad-interleaved (a lane's four column blocks are neighbouring tokens), so the
+  // vocab-major dz^T leaves straight from registers, 8 (bf16) or 16 bytes per lane and whole lines per 16 lanes.
+  G g;
   int id = sch.take();
-  int grow[4];
-  gather_rows<QUAD>(sch, a, id, n_act, grow);
-  logits_fetch<TT, QUAD>(g, sch, a, id, n_act, grow, smem);
+  int grow[decltype(g.lb)::ITERS];
+  gather_rows<true, G>(sch, a, id, n_act, grow);
+  logits_fetch<true>(g, sch, a, id, n_act, grow, smem);
   while (true) {
     f32x4_t acc[MB][NB];
     g.run(smem, acc);
     int tid = threadIdx.x;                           // opaque per tile: see k_fwd_partials
     asm volatile("" : "+v"(tid));
-    const LanePos lp{(tid >> 6) / WAVES_N, (tid >> 6) % WAVES_N, tid & 63};
+    const LanePos<S> lp(tid);
     int tv, tt;
     sch.coords(id, tv, tt);
     const bool more = sch.has_tile();
@@ -435,12 +443,12 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_dz(DzArgs a) {
     // every global load of the tile boundary in two batches (list entries, then what they point to), all issued
     // before the slab requests below
     const int nid = more ? sch.take() : id;
-    gather_rows<QUAD>(sch, a, nid, n_act, grow);
+    gather_rows<true, G>(sch, a, nid, n_act, grow);
     int trow[NB];
     float tcoef[NB], tlse[NB];
     int ttgt[NB];
 #pragma unroll
-    for (int j = 0; j < NB; ++j) trow[j] = a.rows[min((int)t0 + (QUAD ? lp.col_quad() + j : lp.col(j)), n_act - 1)];
+    for (int j = 0; j < NB; ++j) trow[j] = a.rows[min((int)t0 + lp.col_quad() + j, n_act - 1)];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       tcoef[j] = a.coef[trow[j]];
@@ -452,7 +460,7 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_dz(DzArgs a) {
     __syncthreads();                                 // every wave is done reading the slab buffers
     if (more) {                                      // the epilogue uses no LDS: fetch the next tile under it
       id = nid;
-      logits_fetch<TT, QUAD>(g, sch, a, id, n_act, grow, smem);
+      logits_fetch<true>(g, sch, a, id, n_act, grow, smem);
     }
     LLAMARL_FENCE();
 
@@ -460,7 +468,7 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_dz(DzArgs a) {
     const int lane_row0 = lp.row(0, 0);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      const int tok = QUAD ? lp.col_quad() + j : lp.col(j);
+      const int tok = lp.col_quad() + j;
       const bool in = tok < rowsT;
       const float c = in ? a.g * tcoef[j] : 0.f;
       const float lb = (c != 0.f) ? tlse[j] * LOG2E : 0.f;
@@ -474,7 +482,7 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_dz(DzArgs a) {
           acc[i][j][r] = live ? -c * p : 0.f;
         }
       // + coef at the target's own vocab row: one lane of one wave of one vocab tile per token
-      const bool mine = live && yrel >= 0 && yrel < WAVE_M && (yrel & 12) == 0;
+      const bool mine = live && yrel >= 0 && yrel < S::WAVE_M && (yrel & 12) == 0;
       if (__any(mine)) {                                     // wave-uniform
 #pragma unroll
         for (int i = 0; i < MB; ++i)
@@ -485,7 +493,7 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_dz(DzArgs a) {
 
     // how far the zero padding of each orientation reaches inside this tile
     const int dzt_cols = (int)min((int64_t)BN, ldzt - t0);   // dzt[vocab][token]: vocab < V, token < ldzt
-    if constexpr (QUAD) {
+    if constexpr (sizeof(typename G::Type::store_t) == 2) {
       // bf16: only the vocab-major orientation exists (both gradient contractions read it).  ldzt is a multiple
       // of 64, so a token quad is never cut by the padding limit.
       // Uniform 64-bit tile base + 32-bit lane offset, made opaque once per tile so that the 32 row offsets are
@@ -511,20 +519,32 @@ __global__ __launch_bounds__(NTHREADS) void k_bwd_dz(DzArgs a) {
         }
       }
     } else {
+      // fp32: both orientations.  A lane holds four neighbouring vocabulary rows (r) of four neighbouring tokens (j):
+      // 16-byte stores along either.  ldz and ldzt are multiples of 64, so no group of four is cut.
       const int dz_cols = (int)min((int64_t)BM, a.ldz - v0);   // dz[token][vocab]:  token < N, vocab < ldz
       float* dz = reinterpret_cast<float*>(a.dz);
       float* dzt = reinterpret_cast<float*>(a.dzt);
+      const int tok0 = lp.col_quad();
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
+      for (int i = 0; i < MB; ++i) {
+        LLAMARL_FENCE();
+        const int vr0 = lp.row(i, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (vr0 + r >= rowsV) {                              // padded vocab rows of the token-major copy are 0
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[i][j][r] = 0.f;
+          }
 #pragma unroll
         for (int j = 0; j < NB; ++j)
+          if (tok0 + j < rowsT && vr0 < dz_cols)
+            *reinterpret_cast<f32x4_t*>(dz + (t0 + tok0 + j) * a.ldz + v0 + vr0) = acc[i][j];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int vr = lp.row(i, r), tok = lp.col(j);
-            const float v = (vr < rowsV) ? acc[i][j][r] : 0.f;   // padded vocab rows of the token-major copy are 0
-            if (tok < rowsT && vr < dz_cols) dz[(t0 + tok) * a.ldz + v0 + vr] = v;
-            if (vr < rowsV && tok < dzt_cols) dzt[(v0 + vr) * ldzt + t0 + tok] = v;
-          }
+        for (int r = 0; r < 4; ++r)
+          if (vr0 + r < rowsV && tok0 < dzt_cols)
+            *reinterpret_cast<float4*>(dzt + (v0 + vr0 + r) * ldzt + t0 + tok0) =
+                make_float4(acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]);
+      }
     }
     if (!more) break;
   }
@@ -548,7 +568,7 @@ struct StoreArgs {
   int packed_a, packed_b;   // A / B is such a panel (lda / ldb are then ignored)
   int group_m;              // rows of a 32-tile patch (see TileSchedule)
   int max_splits;           // the tiles of the last, partial round may be split this many ways along K (1: never)
-  float* part;              // [splits][tail tiles][BM x BN] fp32 partial products of split tiles
+  float* part;              // [splits][tail tiles][tile] fp32 partial products of split tiles
   int32_t* plan_out;        // [4] {whole, rem, splits, tiles_m}: what k_reduce_tail has to finish
 };
 
@@ -623,12 +643,12 @@ struct StorePlan {
   }
 };
 
-template <typename TT>
+template <typename G>
 struct StoreTile {     // what one work item of k_gemm_store contracts and where it goes
   int64_t row0, col0, k_lo, k_len;
   int rowsA, rowsB, split, nsplit, tail_index;
   __device__ __forceinline__ void set(const StoreArgs& a, const StorePlan& plan, int64_t M, int64_t K, int item) {
-    constexpr int BK = 8 * TT::EPC;
+    constexpr int BK = 8 * G::Type::EPC, BM = G::Shape::BM, BN = G::Shape::BN;
     int tile, tm, tn;
     plan.decode(item, tile, split, nsplit);
     plan.coords(tile, tm, tn);
@@ -643,29 +663,25 @@ struct StoreTile {     // what one work item of k_gemm_store contracts and where
   }
 };
 
-template <typename TT>
-__device__ __forceinline__ StoreTile<TT> store_tile_of(const StorePlan& plan, const StoreArgs& a, int item, int64_t M,
-                                                       int64_t K) {
-  StoreTile<TT> t;
+template <typename G>
+__device__ __forceinline__ StoreTile<G> store_tile_of(const StorePlan& plan, const StoreArgs& a, int item, int64_t M,
+                                                      int64_t K) {
+  StoreTile<G> t;
   t.set(a, plan, M, K, item);
   return t;
 }
-template <typename TT>
-__device__ __forceinline__ void store_fetch(TileGemm<TT, STORE_LOAD_SLOT>& g, const StorePlan& plan, const StoreArgs& a,
-                                            int item, int64_t M, int64_t K, char* smem) {
-  typedef typename TT::store_t st;
-  const StoreTile<TT> t = store_tile_of<TT>(plan, a, item, M, K);
-  if (t.k_len > 0)
-    g.template prefetch<false, true>((const st*)a.A + t.row0 * a.lda + t.k_lo, a.lda, t.rowsA,
-                               (const st*)a.B + t.col0 * a.ldb + t.k_lo, a.ldb, t.rowsB, t.k_len, smem);
-}
-// k-major operands: A is At [K][lda] (output rows are its columns), B is Bt [K][ldb]
-__device__ __forceinline__ void store_fetch(TileGemmTN& g, const StorePlan& plan, const StoreArgs& a, int item, int64_t M,
+template <typename G>
+__device__ __forceinline__ void store_fetch(G& g, const StorePlan& plan, const StoreArgs& a, int item, int64_t M,
                                             int64_t K, char* smem) {
-  const StoreTile<BF16> t = store_tile_of<BF16>(plan, a, item, M, K);
-  if (t.k_len > 0)
+  typedef typename G::Type::store_t st;
+  const StoreTile<G> t = store_tile_of<G>(plan, a, item, M, K);
+  if (t.k_len <= 0) return;
+  if constexpr (G::KMAJOR)   // A is At [K][lda] (output rows are its columns), B is Bt [K][ldb]
     g.prefetch((const uint16_t*)a.A + t.k_lo * a.lda + t.row0, a.lda, t.row0,
                (const uint16_t*)a.B + t.k_lo * a.ldb + t.col0, a.ldb, t.col0, (int)t.k_len, smem);
+  else
+    g.template prefetch<true>((const st*)a.A + t.row0 * a.lda + t.k_lo, a.lda, t.rowsA,
+                              (const st*)a.B + t.col0 * a.ldb + t.k_lo, a.ldb, t.rowsB, t.k_len, smem);
 }
 
 // One output element group in its final form.  MODE: 1 fp32, 2 fp32 accumulate, 3 bf16, 4 bf16 accumulate.
@@ -708,11 +724,12 @@ __device__ __forceinline__ void store_final1(char* q, float v) {
 
 // MODE (compile time): the final form of the output, see store_final4.  Split tiles of the last round leave fp32
 // partial products instead (k_reduce_tail finishes them in the same MODE).
-template <typename TT, bool KMAJOR, int MODE>
-__global__ __launch_bounds__(NTHREADS) void k_gemm_store(StoreArgs a) {
+template <typename G, int MODE>
+__global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(StoreArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  typedef typename TT::store_t st;
-  constexpr int BK = 8 * TT::EPC;
+  typedef typename G::Shape S;
+  constexpr bool KMAJOR = G::KMAJOR;
+  constexpr int BK = 8 * G::Type::EPC, BM = S::BM, BN = S::BN, MB = S::MB;
   const int64_t M = a.m_count ? (int64_t)*a.m_count : a.M;
   const int64_t K = a.k_count ? ((int64_t)*a.k_count + 63) / 64 * 64 : a.K;
   // a later pass of a chunked backward that found no active rows: nothing to add to what the output holds
@@ -734,13 +751,13 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_store(StoreArgs a) {
     a.plan_out[0] = plan.whole; a.plan_out[1] = plan.rem; a.plan_out[2] = plan.splits; a.plan_out[3] = tiles_m;
   }
   if (!plan.has_item()) return;                      // block-uniform
-  typename std::conditional<KMAJOR, TileGemmTN, TileGemm<TT, STORE_LOAD_SLOT>>::type g;
+  G g;
   int id = plan.take();
   store_fetch(g, plan, a, id, M, K, smem);
   while (true) {
     f32x4_t acc[MB][NB];
     const int cur_id = id;
-    if (store_tile_of<TT>(plan, a, cur_id, M, K).k_len > 0) {
+    if (store_tile_of<G>(plan, a, cur_id, M, K).k_len > 0) {
       g.run(smem, acc);
     } else {                                         // nothing to contract: the product is zero
 #pragma unroll
@@ -759,17 +776,17 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_store(StoreArgs a) {
     }
     LLAMARL_FENCE();
 
-    const StoreTile<TT> cur = store_tile_of<TT>(plan, a, cur_id, M, K);
+    const StoreTile<G> cur = store_tile_of<G>(plan, a, cur_id, M, K);
     int tid = threadIdx.x;                           // opaque per tile: see k_fwd_partials (a spilled per-lane constant
     asm volatile("" : "+v"(tid));                    // reloaded here would wait for the slab requests above)
-    const LanePos lp{(tid >> 6) / WAVES_N, (tid >> 6) % WAVES_N, tid & 63};
+    const LanePos<S> lp(tid);
     // Store epilogue, one 16-row block at a time (fences keep the unrolled blocks from piling up address registers).
     // Addresses are a uniform 64-bit tile base plus a 32-bit per-lane byte offset (a 256-row panel is < 2 GiB).
     // The offset passes through an empty asm once per tile: otherwise the 32 row offsets of a lane, which do not
     // depend on the tile, are hoisted out of the persistent loop and live in scratch memory.
     const int row_l = lp.row(0, 0);                                // lane's first row; (ib, r) adds 16 ib + r
     if (cur.nsplit > 1) {
-      // a split tile of the last round (block-uniform): the whole 256 x 256 fp32 block goes to the workspace,
+      // a split tile of the last round (block-uniform): the whole BM x BN fp32 block goes to the workspace,
       // rows and columns past the matrix edge included (they hold zeros or values nobody reads)
       char* blk = reinterpret_cast<char*>(a.part + ((int64_t)cur.split * plan.rem + cur.tail_index) * (BM * BN));
       uint32_t lane_off = (uint32_t)row_l * (BN * 4) + (uint32_t)(KMAJOR ? lp.col(0) : lp.col_quad()) * 4u;
@@ -845,17 +862,20 @@ __global__ __launch_bounds__(NTHREADS) void k_gemm_store(StoreArgs a) {
 
 // Finishes the split tiles of a store contraction's last round: C tile = sum over splits (ascending) of the fp32
 // partial blocks, stored in the contraction's MODE (dtype, accumulate, row scatter); the plan is the one k_gemm_store
-// wrote.  Bound by memory latency: a work unit is four rows of one tail tile (one float4 per thread and split), all
+// wrote.  Bound by memory latency: a work unit is a few rows of one tail tile (one float4 per thread and split), all
 // of a thread's loads are in flight before the first is added, and the units of all tail tiles are dealt to a bounded
 // grid -- bounded because the number of tail tiles is only known on the device and a launch that finds none must
 // stay cheap.  Against one block per 32-row stripe, whose threads walked eight rows and their splits one dependent
 // load after the other: 18.0 -> 5.4 us for one tile in eight parts, 19.5 -> 5.4 us for 15, 52.8 -> 32 us for the dW
 // of a 33001 x 1032 head (~200 MB of partial blocks, now near copy rate).
-constexpr int TAIL_UNIT_ROWS = 4;
-constexpr int TAIL_UNITS = BM / TAIL_UNIT_ROWS;      // per tile
+template <typename S>
+struct TailUnit {
+  static constexpr int THREADS_PER_ROW = S::BN / 4, ROWS = 256 / THREADS_PER_ROW;   // 256 threads, one float4 each
+  static constexpr int PER_TILE = S::BM / ROWS;
+};
 constexpr int TAIL_MAX_BLOCKS = 2048;
 constexpr int STORE_MAX_SPLITS = 8;                  // most parts a tail tile is cut into
-template <int MODE>
+template <typename S, int MODE>
 __global__ __launch_bounds__(256) void k_reduce_tail(StoreArgs a) {
   const int whole = a.plan_out[0], rem = a.plan_out[1], splits = a.plan_out[2], tiles_m = a.plan_out[3];
   if (splits <= 1) return;                           // block-uniform
@@ -864,13 +884,14 @@ __global__ __launch_bounds__(256) void k_reduce_tail(StoreArgs a) {
   plan.tiles_m = tiles_m;
   plan.tiles_n = a.tiles_n;
   plan.group_m = a.group_m;
-  constexpr int esz = (MODE >= 3) ? 2 : 4;
+  constexpr int esz = (MODE >= 3) ? 2 : 4, BM = S::BM, BN = S::BN;
+  typedef TailUnit<S> U;
   char* Cb = reinterpret_cast<char*>(a.C);
-  const int c = (threadIdx.x & 63) * 4;              // 64 threads x 4 columns = one 256-column row
+  const int c = (int)(threadIdx.x % U::THREADS_PER_ROW) * 4;
   const int64_t plane = (int64_t)rem * (BM * BN);
-  for (int u = blockIdx.x; u < rem * TAIL_UNITS; u += gridDim.x) {
-    const int j = u / TAIL_UNITS;
-    const int row = (u - j * TAIL_UNITS) * TAIL_UNIT_ROWS + (threadIdx.x >> 6);
+  for (int u = blockIdx.x; u < rem * U::PER_TILE; u += gridDim.x) {
+    const int j = u / U::PER_TILE;
+    const int row = (u - j * U::PER_TILE) * U::ROWS + (int)(threadIdx.x / U::THREADS_PER_ROW);
     int tm, tn;
     plan.coords(whole + j, tm, tn);
     const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * BN;

@@ -33,17 +33,47 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t esize(llamarl_dtype dt) { return dt == LLAMARL_BF16 ? 2 : 4; }
 
+// ---- which main loop a contraction runs on ---------------------------------------------------------------
+// The choice depends on host-side sizes only (workspace sizes follow from it).
+enum Tile { TILE_256, TILE_128, TILE_64 };
+inline int tile_edge(Tile t) { return t == TILE_256 ? 256 : t == TILE_128 ? 128 : 64; }
+inline int64_t tile_count(int64_t rows, int64_t cols, int64_t edge) {
+  return ((rows + edge - 1) / edge) * ((cols + edge - 1) / edge);
+}
+// Logits kernels (forward, recompute): N x V outputs.  fp32: 64 x 64 tiles while 128 x 128 ones would leave CUs empty.
+// Forward at (N, V, d), 128- / 64-tiles: (512, 2048, 512) 39 / 26 us, (512, 4096, 512) 39 / 33, (1024, 4096, 512)
+// 40 / 53, (2048, 8192, 512) 105 / 180.
+Tile logits_tile(int64_t N, int64_t V, llamarl_dtype dt) {
+  if (dt == LLAMARL_BF16) return TILE_256;
+  return tile_count(N, V, 128) >= 192 ? TILE_128 : TILE_64;
+}
+// Store contractions: M x Nn outputs over K, split along K where tiles are few; counted in parts of 16 slabs (512 k),
+// which still pay for their partial blocks.  fp32, 128- / 64-tiles: dH of (N, V, d) = (512, 4096, 512) 39 / 32 us,
+// (1024, 4096, 512) 42 / 50, (300, 16400, 260) 113 / 59; dW of (512, 4096, 512) 32 / 28, (1024, 4096, 512) 43 / 46,
+// (300, 16400, 260) 40 / 48, (2048, 8192, 512) 107 / 158.
+Tile store_tile(int64_t M, int64_t Nn, int64_t K, llamarl_dtype dt) {
+  if (dt == LLAMARL_BF16) return TILE_256;
+  const int64_t parts = std::min<int64_t>(STORE_MAX_SPLITS, std::max<int64_t>(1, K / 512));
+  return tile_count(M, Nn, 128) * parts >= 256 ? TILE_128 : TILE_64;
+}
+
+typedef TileGemm<BF16> Logits256;
+typedef TileGemm<BF16, STORE_LOAD_SLOT> Store256;
+typedef TileGemmSmall<F32, Shape128, 2, 2> F32Loop128;
+typedef TileGemmSmall<F32, Shape64, 4, 2> F32Loop64;
+
 // ---- workspace layouts (every block 256-byte aligned) ----------------------------------------------------
 struct FwdWs {
   int tiles_v, tiles_t;
   int64_t n_pad;
   size_t off_m, off_s, off_zt, off_rows, off_nact, total;
 };
-FwdWs fwd_ws(int64_t N, int64_t V) {
+FwdWs fwd_ws(int64_t N, int64_t V, llamarl_dtype dt) {
   FwdWs w;
-  w.tiles_v = (int)((V + BM - 1) / BM);
-  w.tiles_t = (int)((N + BN - 1) / BN);
-  w.n_pad = round_up(N, BN);
+  const int tile = tile_edge(logits_tile(N, V, dt));
+  w.tiles_v = (int)((V + tile - 1) / tile);
+  w.tiles_t = (int)((N + tile - 1) / tile);
+  w.n_pad = round_up(N, 256);
   const size_t plane = (size_t)w.tiles_v * (size_t)w.n_pad * sizeof(float);
   w.off_m = 0;
   w.off_s = round_up((int64_t)plane, 256);
@@ -97,7 +127,7 @@ constexpr int MAX_GRID = 256;
 BwdWs bwd_ws(int64_t N, int64_t d, int64_t V, llamarl_dtype dt, int64_t max_rows_per_pass) {
   BwdWs w;
   const size_t es = esize(dt);
-  w.R = (max_rows_per_pass <= 0 || max_rows_per_pass >= N) ? N : std::min(N, round_up(max_rows_per_pass, BN));
+  w.R = (max_rows_per_pass <= 0 || max_rows_per_pass >= N) ? N : std::min(N, round_up(max_rows_per_pass, 256));
   w.n_pass = (int)((N + w.R - 1) / w.R);
   w.ldz = round_up(V, 64);
   w.ldzt = packed_pitch(w.R);        // the kernels use packed_pitch(active rows of the pass) <= this
@@ -114,9 +144,15 @@ BwdWs bwd_ws(int64_t N, int64_t d, int64_t V, llamarl_dtype dt, int64_t max_rows
   w.off_part = w.off_plan + 256;
   // fp32 partial blocks of the split tiles at the end of a store contraction (see StorePlan): at most
   // STORE_TAIL_ROUNDS per workgroup of the grid, and never more than eight per tile
-  const int64_t tiles_dh = ((w.R + BM - 1) / BM) * ((d + BN - 1) / BN), tiles_dw = ((V + BM - 1) / BM) * ((d + BN - 1) / BN);
-  const int64_t blocks = std::min<int64_t>((int64_t)STORE_TAIL_ROUNDS * MAX_GRID, std::max(tiles_dh, tiles_dw) * STORE_MAX_SPLITS);
-  w.total = w.off_part + (size_t)(blocks * BM * BN * 4);
+  auto part_bytes = [&](int64_t M, int64_t edge) {
+    const int64_t grid = (int64_t)MAX_GRID * (edge == 256 ? 1 : 2);
+    return std::min(STORE_TAIL_ROUNDS * grid, tile_count(M, d, edge) * STORE_MAX_SPLITS) * edge * edge * 4;
+  };
+  // fp32 passes of different lengths may run on different tiles: room for either
+  w.total = w.off_part;
+  for (const int64_t M : {w.R, V})
+    w.total = std::max(w.total, w.off_part + (size_t)(dt == LLAMARL_BF16 ? part_bytes(M, 256)
+                                                                          : std::max(part_bytes(M, 128), part_bytes(M, 64))));
   return w;
 }
 
@@ -135,7 +171,7 @@ llamarl_status check_head_shape(int64_t N, int64_t d, int64_t V, llamarl_dtype d
     return fail(LLAMARL_ERR_UNSUPPORTED, "a 256-row panel of %lld elements per row exceeds 2 GiB", (long long)widest);
   if (N * d * (int64_t)esize(dt) >= (int64_t)1 << 31)
     return fail(LLAMARL_ERR_UNSUPPORTED, "H must be smaller than 2 GiB (its rows are gathered with 32-bit offsets)");
-  if ((N + BM - 1) / BM * ((V + BN - 1) / BN) >= (int64_t)1 << 31 || V >= (int64_t)1 << 31)
+  if (tile_count(N, V, tile_edge(logits_tile(N, V, dt))) >= (int64_t)1 << 31 || V >= (int64_t)1 << 31)
     return fail(LLAMARL_ERR_UNSUPPORTED, "too many tiles");
   return LLAMARL_OK;
 }
@@ -146,8 +182,8 @@ hipError_t set_lds(K kernel, int bytes) {
                              bytes);
 }
 
-// One persistent workgroup per CU (256 on MI355X); a smaller problem gets one workgroup per tile.
-int persistent_grid(int64_t tiles) {
+// `per_cu` persistent workgroups per CU (256 on MI355X); a smaller problem gets one workgroup per tile.
+int persistent_grid(int64_t tiles, int per_cu = 1) {
   static int cus = 0;   // a device property, not call state: read once
   if (cus == 0) {
     int dev = 0, n = 0;
@@ -158,7 +194,7 @@ int persistent_grid(int64_t tiles) {
       cus = MAX_GRID;
     if (cus > MAX_GRID) cus = MAX_GRID;
   }
-  return (int)(tiles < (int64_t)cus ? tiles : (int64_t)cus);
+  return (int)std::min<int64_t>(tiles, (int64_t)cus * per_cu);
 }
 
 #define HIP_TRY(expr)                                                                              \
@@ -167,17 +203,24 @@ int persistent_grid(int64_t tiles) {
     if (e_ != hipSuccess) return fail(LLAMARL_ERR_HIP, "%s failed: %s", #expr, hipGetErrorString(e_)); \
   } while (0)
 
-template <typename TT, bool KMAJOR, int MODE>
+// Dynamic LDS beyond 64 KB has to be asked for.
+template <typename K>
+hipError_t set_lds_if_large(K kernel, int bytes) {
+  return bytes > 65536 ? set_lds(kernel, bytes) : hipSuccess;
+}
+
+template <typename G, int MODE>
 llamarl_status launch_store_mode(const StoreArgs& a, int64_t work_items, int tiles_worst, hipStream_t st) {
-  HIP_TRY(set_lds(k_gemm_store<TT, KMAJOR, MODE>, MAINLOOP_LDS_BYTES));
-  const int grid = persistent_grid(work_items);
-  k_gemm_store<TT, KMAJOR, MODE><<<dim3((unsigned)grid), dim3(NTHREADS), MAINLOOP_LDS_BYTES, st>>>(a);
+  HIP_TRY(set_lds_if_large(k_gemm_store<G, MODE>, G::LDS_BYTES));
+  const int grid = persistent_grid(work_items, G::GROUPS_PER_CU);
+  k_gemm_store<G, MODE><<<dim3((unsigned)grid), dim3(G::Shape::THREADS), G::LDS_BYTES, st>>>(a);
   HIP_TRY(hipGetLastError());
   if (a.max_splits > 1) {
     // the split tiles of the last round, if the device-side sizes left any: fewer than `grid` of them
     const int tail = std::min(grid - 1, tiles_worst);
     if (tail > 0) {
-      k_reduce_tail<MODE><<<dim3((unsigned)std::min(tail * TAIL_UNITS, TAIL_MAX_BLOCKS)), dim3(256), 0, st>>>(a);
+      const int units = tail * TailUnit<typename G::Shape>::PER_TILE;
+      k_reduce_tail<typename G::Shape, MODE><<<dim3((unsigned)std::min(units, TAIL_MAX_BLOCKS)), dim3(256), 0, st>>>(a);
       HIP_TRY(hipGetLastError());
     }
   }
@@ -185,7 +228,7 @@ llamarl_status launch_store_mode(const StoreArgs& a, int64_t work_items, int til
 }
 
 // C [M,Nn] (+)= A B^T on the persistent grid; ws_part / ws_plan: workspace of the last round's split tiles
-template <typename TT, bool KMAJOR = false>
+template <typename G>
 llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t M, int64_t Nn,
                                  int64_t K, void* C, int64_t ldc, int c_is_f32, int accumulate, const int32_t* m_count,
                                  const int32_t* k_count, const int32_t* c_rows, float* ws_part, int32_t* ws_plan,
@@ -200,20 +243,38 @@ llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int6
 
   a.pitch_count = pitch_count; a.packed_a = packed_a; a.packed_b = packed_b;
   a.A = A; a.lda = lda; a.B = B; a.ldb = ldb; a.M = M; a.Nn = Nn; a.K = K;
+  constexpr int BM = G::Shape::BM, BN = G::Shape::BN;
   const int tiles_m = (int)((M + BM - 1) / BM);      // worst case: every row active
   a.tiles_n = (int)((Nn + BN - 1) / BN);
-  a.group_m = (KMAJOR && a.tiles_n <= 16) ? PATCH_ROWS_KMAJOR : PATCH_ROWS_STORE;
+  a.group_m = (G::KMAJOR && a.tiles_n <= 16) ? PATCH_ROWS_KMAJOR : PATCH_ROWS_STORE;
   a.C = C; a.ldc = ldc; a.c_is_f32 = c_is_f32; a.accumulate = accumulate;
   const int tiles = tiles_m * a.tiles_n;
   const int64_t items = (int64_t)tiles * STORE_MAX_SPLITS;   // a small contraction still gets a workgroup per split
-  if (c_is_f32) return accumulate ? launch_store_mode<TT, KMAJOR, 2>(a, items, tiles, st)
-                                  : launch_store_mode<TT, KMAJOR, 1>(a, items, tiles, st);
-  if constexpr (sizeof(typename TT::store_t) == 2) {
-    return accumulate ? launch_store_mode<TT, KMAJOR, 4>(a, items, tiles, st)
-                      : launch_store_mode<TT, KMAJOR, 3>(a, items, tiles, st);
+  if (c_is_f32) return accumulate ? launch_store_mode<G, 2>(a, items, tiles, st) : launch_store_mode<G, 1>(a, items, tiles, st);
+  if constexpr (sizeof(typename G::Type::store_t) == 2) {
+    return accumulate ? launch_store_mode<G, 4>(a, items, tiles, st) : launch_store_mode<G, 3>(a, items, tiles, st);
   } else {
     return fail(LLAMARL_ERR_INVALID_ARG, "a 16-bit output needs a 16-bit input type");
   }
+}
+
+template <typename G>
+llamarl_status launch_fwd_partials(const FwdArgs& a, hipStream_t st) {
+  HIP_TRY(set_lds_if_large(k_fwd_partials<G>, fwd_lds_bytes<G>));
+  k_fwd_partials<G><<<dim3((unsigned)persistent_grid((int64_t)a.tiles_v * a.tiles_t, G::GROUPS_PER_CU)),
+                      dim3(G::Shape::THREADS), fwd_lds_bytes<G>, st>>>(a);
+  HIP_TRY(hipGetLastError());
+  return LLAMARL_OK;
+}
+template <typename G>
+llamarl_status launch_bwd_dz(DzArgs a, int64_t rows, hipStream_t st) {
+  a.tiles_v = (int)((a.V + G::Shape::BM - 1) / G::Shape::BM);
+  a.tiles_t = (int)((rows + G::Shape::BN - 1) / G::Shape::BN);
+  HIP_TRY(set_lds_if_large(k_bwd_dz<G>, G::LDS_BYTES));
+  k_bwd_dz<G><<<dim3((unsigned)persistent_grid((int64_t)a.tiles_v * a.tiles_t, G::GROUPS_PER_CU)),
+                dim3(G::Shape::THREADS), G::LDS_BYTES, st>>>(a);
+  HIP_TRY(hipGetLastError());
+  return LLAMARL_OK;
 }
 
 // W holds the vocabulary rows [v_off, v_off + V) of a head with V_total rows (the whole head: v_off = 0, V = V_total).
@@ -222,7 +283,8 @@ template <typename TT>
 llamarl_status run_logprobs(const void* H, const void* W, const int32_t* targets, const uint8_t* mask, int64_t N,
                             int64_t d, int64_t V, int64_t v_off, int64_t V_total, int partial, float* out0,
                             float* out1, float* out2, char* ws, hipStream_t st) {
-  const FwdWs w = fwd_ws(N, V);
+  constexpr llamarl_dtype dt = sizeof(typename TT::store_t) == 2 ? LLAMARL_BF16 : LLAMARL_F32;
+  const FwdWs w = fwd_ws(N, V, dt);
   FwdArgs a;
   a.H = H; a.W = W; a.targets = targets; a.N = N; a.d = d; a.V = V; a.v_off = v_off;
   a.tiles_v = w.tiles_v; a.tiles_t = w.tiles_t; a.n_pad = w.n_pad;
@@ -236,10 +298,11 @@ llamarl_status run_logprobs(const void* H, const void* W, const int32_t* targets
   k_compact_rows<<<dim3((unsigned)((N + COMPACT_BLOCK_ROWS - 1) / COMPACT_BLOCK_ROWS)), dim3(COMPACT_THREADS), 0, st>>>(
       partial ? 2 : 0, mask, targets, V_total, nullptr, N, rows, n_act, out0, out1, out2);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(set_lds(k_fwd_partials<TT>, FWD_LDS_BYTES));
-  k_fwd_partials<TT><<<dim3((unsigned)persistent_grid((int64_t)w.tiles_v * w.tiles_t)), dim3(NTHREADS), FWD_LDS_BYTES,
-                       st>>>(a);
-  HIP_TRY(hipGetLastError());
+  llamarl_status s;
+  if constexpr (dt == LLAMARL_BF16) s = launch_fwd_partials<Logits256>(a, st);
+  else if (logits_tile(N, V, dt) == TILE_128) s = launch_fwd_partials<F32Loop128>(a, st);
+  else s = launch_fwd_partials<F32Loop64>(a, st);
+  if (s != LLAMARL_OK) return s;
   MergeArgs m;
   m.part_m = a.part_m; m.part_s = a.part_s; m.zt = a.zt; m.rows = rows; m.n_act = n_act; m.tiles_v = w.tiles_v;
   m.n_pad = w.n_pad; m.out0 = out0; m.out1 = out1; m.out2 = out2; m.targets = targets; m.v_off = v_off; m.V = V;
@@ -309,35 +372,37 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     DzArgs a;
     a.H = H; a.W = W; a.targets = targets; a.lse = lse; a.coef = coef; a.g = g; a.N = N; a.d = d; a.V = V;
     a.v_off = v_off;
-    a.tiles_v = (int)((V + BM - 1) / BM);
-    a.tiles_t = (int)((Rc + BN - 1) / BN);
     a.dz = dz; a.ldz = w.ldz; a.dzt = dzt; a.rows = rows; a.n_act = n_act;
-    const int dz_lds = MAINLOOP_LDS_BYTES;
-    HIP_TRY(set_lds(k_bwd_dz<TT>, dz_lds));
-    k_bwd_dz<TT><<<dim3((unsigned)persistent_grid((int64_t)a.tiles_v * a.tiles_t)), dim3(NTHREADS), dz_lds, st>>>(a);
-    HIP_TRY(hipGetLastError());
+    llamarl_status s;
+    if constexpr (kBf16) s = launch_bwd_dz<Logits256>(a, Rc, st);
+    else if (logits_tile(Rc, V, dt) == TILE_128) s = launch_bwd_dz<F32Loop128>(a, Rc, st);
+    else s = launch_bwd_dz<F32Loop64>(a, Rc, st);
+    if (s != LLAMARL_OK) return s;
     if (c == 0) PHASE_EVENT(2);
 
     // dH [active rows, d] = dz [n_act,V] . W [V,d], scattered to the token rows.
     //   bf16: k-major operands dz^T [V][n_act] and W [V][d], K = V exactly
     //   fp32: K-contiguous operands dz [n_act][ldz] and W^T [d][ldz], K zero-padded to ldz
-    llamarl_status s;
     float* part = reinterpret_cast<float*>(ws + w.off_part);
     int32_t* plan = reinterpret_cast<int32_t*>(ws + w.off_plan);
     if constexpr (kBf16) {
-      s = launch_store_gemm<TT, true>(dzt, w.ldzt, W, d, Rc, d, V, dH, d, 0, 0, n_act, nullptr, rows, part, plan, n_act,
-                                      1, 0, st);
+      s = launch_store_gemm<TileGemmTN>(dzt, w.ldzt, W, d, Rc, d, V, dH, d, 0, 0, n_act, nullptr, rows, part, plan,
+                                        n_act, 1, 0, st);
     } else {
-      s = launch_store_gemm<TT>(dz, w.ldz, wt, w.ldz, Rc, d, w.ldz, dH, d, 1, 0, n_act, nullptr, rows, part, plan,
-                                nullptr, 0, 0, st);
+      const auto launch = store_tile(Rc, d, V, dt) == TILE_128 ? launch_store_gemm<F32Loop128> : launch_store_gemm<F32Loop64>;
+      s = launch(dz, w.ldz, wt, w.ldz, Rc, d, w.ldz, dH, d, 1, 0, n_act, nullptr, rows, part, plan, nullptr, 0, 0, st);
     }
     if (s != LLAMARL_OK) return s;
     if (c == 0) PHASE_EVENT(3);
     if (c == 0) PHASE_EVENT(4);
     // dW [V,d] (+)= dz^T [V,n_act] . H^T[d,n_act]^T      (K = n_act, zero-padded to a multiple of 64); passes after
     // the first add to what the earlier ones stored
-    s = launch_store_gemm<TT>(dzt, w.ldzt, ht, w.ldzt, V, d, w.ldzt, dW, d, dW_dt == LLAMARL_F32,
-                              c == 0 ? accumulate_dW : 1, nullptr, n_act, nullptr, part, plan, n_act, 1, 1, st);
+    auto launch_dw = [&] {
+      if constexpr (kBf16) return launch_store_gemm<Store256>;
+      else return store_tile(V, d, Rc, dt) == TILE_128 ? launch_store_gemm<F32Loop128> : launch_store_gemm<F32Loop64>;
+    }();
+    s = launch_dw(dzt, w.ldzt, ht, w.ldzt, V, d, w.ldzt, dW, d, dW_dt == LLAMARL_F32, c == 0 ? accumulate_dW : 1, nullptr,
+                  n_act, nullptr, part, plan, n_act, 1, 1, st);
     if (s != LLAMARL_OK) return s;
     if (c == 0) PHASE_EVENT(5);
   }
@@ -366,7 +431,7 @@ size_t llamarl_workspace_bytes(int64_t N, int64_t d, int64_t V, llamarl_dtype dt
   switch (pass) {
     case LLAMARL_PASS_LOGPROBS:
       if (V <= 0) return 0;
-      return fwd_ws(N, V).total;
+      return fwd_ws(N, V, dt).total;
     case LLAMARL_PASS_LOSS_FWD:
       return loss_ws(N, N).total;     // sized for the worst case B = N
     case LLAMARL_PASS_LOSS_BWD:
@@ -388,7 +453,7 @@ static llamarl_status logprobs_entry(const void* H, const void* W, const int32_t
     return fail(LLAMARL_ERR_INVALID_ARG, "vocabulary slice [%lld, %lld) does not lie inside [0, %lld)", (long long)v_off,
                 (long long)(v_off + V), (long long)V_total);
   if (!aligned16(H) || !aligned16(W)) return fail(LLAMARL_ERR_INVALID_ARG, "H and W must be 16-byte aligned");
-  const size_t need = fwd_ws(N, V).total;
+  const size_t need = fwd_ws(N, V, dt).total;
   if (!ws || ws_bytes < need)
     return fail(LLAMARL_ERR_WORKSPACE, "workspace of %zu bytes given, %zu needed", ws ? ws_bytes : (size_t)0, need);
   if (!aligned16(ws)) return fail(LLAMARL_ERR_INVALID_ARG, "workspace must be 16-byte aligned");

@@ -1,0 +1,75 @@
+"""fp32 contractions on 128 x 128 and 64 x 64 tiles with operands split into three bf16 parts: sizes at the edges of
+the tiles, of a K slab (32) and of the rule that picks the tile, against float64; values that cannot be split."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(N, V, d, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    H = torch.randn(N, d, generator=g, device="cuda")
+    W = torch.randn(V, d, generator=g, device="cuda") * d ** -0.5
+    t = torch.randint(0, V, (N,), generator=g, device="cuda").int()
+    coef = torch.randn(N, generator=g, device="cuda") / N
+    return H, W, t, coef
+
+
+def _reference(H, W, t, coef):
+    z = H.double() @ W.double().T
+    lse = torch.logsumexp(z, dim=1)
+    logp = z.gather(1, t.long()[:, None])[:, 0] - lse
+    dz = -torch.exp(z - lse[:, None])
+    dz[torch.arange(t.numel(), device="cuda"), t.long()] += 1.0
+    dz *= coef.double()[:, None]
+    return logp, lse, dz @ W.double(), dz.T @ H.double()
+
+
+def _rel(a, b):
+    return float((a.double() - b).norm() / b.norm())
+
+
+# a sum of K products, each rounded to 2^-24 of a partial sum no larger than sqrt(K) standard products, in any order:
+# relative error of the result's norm below sqrt(K) 2^-24; the logits feed dz through exp(z - lse), |z| <= 8 here
+@pytest.mark.parametrize("N,V,d", [
+    (1, 64, 4), (64, 64, 32), (65, 63, 36), (63, 129, 28), (127, 1025, 64), (128, 128, 256), (129, 257, 260),
+    (384, 8064, 68), (385, 8193, 100),          # 189 and 260 tiles of 128: either side of the logits rule
+    (500, 512, 512), (512, 3000, 480),          # dH on 64-tiles, split along K
+    (700, 4100, 516), (1100, 4097, 516),        # dW and dH on either tile
+])
+def test_tile_edges(lib, N, V, d):
+    H, W, t, coef = _inputs(N, V, d, 7 * N + V + d)
+    logp, lse = lib.token_logprobs(H, W, t)
+    rlogp, rlse, rdH, rdW = _reference(H, W, t, coef)
+    bound = 2.0 ** -24 * d ** 0.5
+    assert float((lse.double() - rlse).abs().max()) <= 8 * bound + 2e-6
+    assert float((logp.double() - rlogp).abs().max()) <= 16 * bound + 2e-6
+    dH, dW = lib.offpolicy_loss_bwd(H, W, t, lse, coef)
+    tol = 2.0 ** -24 * (max(V, N, d) ** 0.5 + 16)
+    assert _rel(dH, rdH) <= tol and _rel(dW, rdW) <= tol
+
+
+@pytest.mark.parametrize("N,V,d", [(130, 300, 40), (400, 9000, 40)])      # 64- and 128-tiles
+def test_values_that_cannot_be_split(lib, N, V, d):
+    # a constant-one column makes W[:, 0] a bias; -inf there bans a token, and 3.4e38 (infinity in bf16) times
+    # 1e-38 is an ordinary number: both are what fp32 arithmetic gives
+    H, W, t, _ = _inputs(N, V, d, 5)
+    H[:, 0] = 1.0
+    H[:, 1] = 3.4e38
+    W[:, 1] = 1e-38 * W[:, 2]
+    banned = torch.tensor([3, V - 1], device="cuda")
+    W[banned, 0] = -float("inf")
+    t = torch.where((t == 3) | (t == V - 1), torch.zeros_like(t), t)
+    logp, lse = lib.token_logprobs(H, W, t)
+    z = H.double() @ torch.where(torch.isinf(W), torch.zeros_like(W), W).double().T
+    z[:, banned] = -float("inf")
+    rlse = torch.logsumexp(z, dim=1)
+    rlogp = z.gather(1, t.long()[:, None])[:, 0] - rlse
+    assert float((lse.double() - rlse).abs().max()) <= 2e-5
+    assert float((logp.double() - rlogp).abs().max()) <= 2e-5
+    # a NaN row stays in its own row (its maximum ignores NaN, so lse is -inf rather than NaN: fmax semantics)
+    H[17, 4] = float("nan")
+    logp2, lse2 = lib.token_logprobs(H, W, t)
+    assert not bool(torch.isfinite(lse2[17])) and bool(torch.isnan(logp2[17]))
+    ok = torch.arange(N, device="cuda") != 17
+    assert float((lse2[ok].double() - rlse[ok]).abs().max()) <= 2e-5
