@@ -229,4 +229,138 @@ struct TileGemmTN {
   }
 };
 
+// The same contraction on 128 x 128 or 64 x 64 tiles, for outputs too small to give every CU a 256 x 256 tile: the
+// pipeline of TileGemmSmall (several workgroups per CU, counted waits, compiler-scheduled fragments) on k-major slabs.
+//
+// A k-row of a slab has COLS columns.  128 columns = 256 bytes: all rows start at the same bank, as with 256 columns,
+// and the same chunk permutation applies.  64 columns = 128 bytes: odd rows sit in the upper bank half already, so the
+// permutation separates rows 0 and 2 of a lane group (bit 1 of the row) and the two groups (bit 3).
+template <int COLS>
+__device__ __forceinline__ int km_swz_of(int k) {
+  static_assert(COLS == 128 || COLS == 64, "");
+  return COLS == 128 ? km_swz(k) : (2 * ((k >> 1) & 1) | 4 * ((k >> 3) & 1));
+}
+
+template <int COLS, int WAVES>
+struct KMajorLoaderSmall {
+  static constexpr int ROW_BYTES = COLS * 2, LANES_PER_ROW = COLS / 8, ROWS_PER_LOAD = 64 / LANES_PER_ROW;
+  static constexpr int ITERS = 64 / (ROWS_PER_LOAD * WAVES);       // loads of one thread per slab
+  static_assert(ITERS * ROWS_PER_LOAD * WAVES == 64 && (ROWS_PER_LOAD * WAVES) % 16 == 0,
+                "whole wave-instructions, one permutation for all");
+  uint32_t base_lo, base_hi, row_bytes, col0_bytes, voff;
+
+  // as KMajorLoader::init
+  __device__ __forceinline__ void init(const void* origin, int64_t ld, int64_t col0, int wave, int lane) {
+    const uint64_t p = reinterpret_cast<uint64_t>(origin);
+    base_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+    base_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32));
+    row_bytes = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(ld * 2));
+    col0_bytes = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(col0 * 2));
+    const int r = wave * ROWS_PER_LOAD + lane / LANES_PER_ROW;
+    voff = (uint32_t)r * row_bytes + (uint32_t)((lane % LANES_PER_ROW) ^ km_swz_of<COLS>(r)) * 16u;
+  }
+  // slab kt of a K range of k_len rows; past the range every lane is out of the descriptor's range (zeros, no traffic)
+  __device__ __forceinline__ void issue(char* lds, int kt, int k_len, int wave) const {
+    const int rows_left = k_len - kt * 64;
+    const uint32_t rows = (uint32_t)(rows_left <= 0 ? 0 : (rows_left < 64 ? rows_left : 64));
+    const uint32_t records = rows ? rows * row_bytes - col0_bytes : 0u;
+    const uint64_t b = (((uint64_t)base_hi << 32) | base_lo) + (rows ? (uint64_t)kt * 64u * row_bytes : 0u);
+    const i32x4_t rs = {(int)(uint32_t)b, (int)((uint32_t)(b >> 32) & 0xffffu), (int)records, 0x00020000};
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it)
+      lds_dma16(lds0 + (uint32_t)((it * WAVES + wave) * ROWS_PER_LOAD * ROW_BYTES), voff, rs,
+                (uint32_t)(it * WAVES * ROWS_PER_LOAD) * row_bytes);
+  }
+};
+
+template <typename S, int NSTAGE, int GROUPS_PER_CU_>
+struct TileGemmTNSmall {
+  typedef BF16 Type;
+  typedef S Shape;
+  typedef bf16x8_t frag_t;
+  typedef KMajorLoaderSmall<S::BM, S::WAVES> LoaderA;
+  typedef KMajorLoaderSmall<S::BN, S::WAVES> LoaderB;
+  static constexpr bool KMAJOR = true;
+  static constexpr int LDS_BYTES = NSTAGE * S::STAGE_BYTES;
+  static constexpr int GROUPS_PER_CU = GROUPS_PER_CU_;
+  static constexpr int LOADS = LoaderA::ITERS + LoaderB::ITERS;
+  LoaderA la;
+  LoaderB lb;
+  int k_len;
+
+  __device__ __forceinline__ void issue(char* stage, int kt) const {
+    const int wave = wave_id();
+    la.issue(stage, kt, k_len, wave);
+    lb.issue(stage + S::SLAB_A_BYTES, kt, k_len, wave);
+  }
+  __device__ __forceinline__ void prefetch(const uint16_t* At_origin, int64_t lda, int64_t a_col0,
+                                           const uint16_t* Bt_origin, int64_t ldb, int64_t b_col0, int k_len_,
+                                           char* smem) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    k_len = k_len_;
+    la.init(At_origin, lda, a_col0, wave, lane);
+    lb.init(Bt_origin, ldb, b_col0, wave, lane);
+#pragma unroll
+    for (int i = 0; i < NSTAGE - 1; ++i) issue(smem + i * S::STAGE_BYTES, i);
+  }
+
+  // two transposing reads, 4 k-rows apart (TileGemmTN::read_frag)
+  template <int ROW_BYTES>
+  __device__ __forceinline__ static frag_t read_frag(const char* p) {
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (lds_s16x4_ptr)(__attribute__((address_space(3))) void*)const_cast<char*>(p));
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (lds_s16x4_ptr)(__attribute__((address_space(3))) void*)const_cast<char*>(p + 4 * ROW_BYTES));
+    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
+    const s16x8_t v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(frag_t, v);
+  }
+
+  __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[S::MB][NB]) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int wm = wave / S::WAVES_N, wn = wave % S::WAVES_N;
+    // lane -> k-row and 8-byte piece it loads for the transposing reads: see TileGemmTN::run
+    const int g = lane >> 4, jrow = (lane >> 2) & 3, q4 = lane & 3, krow = 8 * g + jrow;
+    int a_off[S::MB], b_off[NB];
+#pragma unroll
+    for (int i = 0; i < S::MB; ++i)
+      a_off[i] = krow * LoaderA::ROW_BYTES + (((wm * S::WAVE_M / 8 + 2 * i) ^ km_swz_of<S::BM>(krow)) + (q4 >> 1)) * 16 +
+                 (q4 & 1) * 8;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      b_off[j] = S::SLAB_A_BYTES + krow * LoaderB::ROW_BYTES +
+                 (((wn * WAVE_N / 8 + 2 * j) ^ km_swz_of<S::BN>(krow)) + (q4 >> 1)) * 16 + (q4 & 1) * 8;
+#pragma unroll
+    for (int i = 0; i < S::MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const int nk = (k_len + 63) / 64;
+    wait_vmcnt0();
+    __syncthreads();
+    int st = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+      if (kt > 0) {
+        wait_vmcnt<LOADS * (NSTAGE - 2)>();
+        __syncthreads();
+      }
+      issue(smem + (st == 0 ? NSTAGE - 1 : st - 1) * S::STAGE_BYTES, kt + NSTAGE - 1);
+      const char* cur = smem + st * S::STAGE_BYTES;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        frag_t a[S::MB], b[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) b[j] = read_frag<LoaderB::ROW_BYTES>(cur + b_off[j] + ks * 32 * LoaderB::ROW_BYTES);
+#pragma unroll
+        for (int i = 0; i < S::MB; ++i) a[i] = read_frag<LoaderA::ROW_BYTES>(cur + a_off[i] + ks * 32 * LoaderA::ROW_BYTES);
+#pragma unroll
+        for (int i = 0; i < S::MB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j) mma(a[i], b[j], acc[i][j]);
+      }
+      st = st == NSTAGE - 1 ? 0 : st + 1;
+    }
+  }
+};
+
 }  // namespace llamarl

@@ -34,31 +34,43 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 inline size_t esize(llamarl_dtype dt) { return dt == LLAMARL_BF16 ? 2 : 4; }
 
 // ---- which main loop a contraction runs on ---------------------------------------------------------------
-// The choice depends on host-side sizes only (workspace sizes follow from it).
+// The choice depends on host-side sizes only (workspace sizes follow from it).  A large contraction runs fastest on the
+// largest tiles (bf16: 256 x 256, 1.2 - 1.3 times as fast as 128 x 128 when both fill the chip), a small one on the
+// tiles that give most CUs something to do.
 enum Tile { TILE_256, TILE_128, TILE_64 };
 inline int tile_edge(Tile t) { return t == TILE_256 ? 256 : t == TILE_128 ? 128 : 64; }
 inline int64_t tile_count(int64_t rows, int64_t cols, int64_t edge) {
   return ((rows + edge - 1) / edge) * ((cols + edge - 1) / edge);
 }
-// Logits kernels (forward, recompute): N x V outputs.  fp32: 64 x 64 tiles while 128 x 128 ones would leave CUs empty.
-// Forward at (N, V, d), 128- / 64-tiles: (512, 2048, 512) 39 / 26 us, (512, 4096, 512) 39 / 33, (1024, 4096, 512)
-// 40 / 53, (2048, 8192, 512) 105 / 180.
+// Logits kernels (forward, recompute): N x V outputs.
+//   bf16, dz at (N, V, d) on 256- / 128- / 64-tiles: (512, 2048, 512) 22 / 16 / 12 us, (512, 8192, 1024) 30 / 18 / 22,
+//   (1041, 5003, 520) 26 / 18 / 26, (1024, 8192, 1024) 30 / 24 / 39, (1024, 16032, 2048) 58 / 70 / 115.
+//   fp32, forward on 128- / 64-tiles: (512, 2048, 512) 39 / 26 us, (512, 4096, 512) 39 / 33, (1024, 4096, 512) 40 / 53,
+//   (2048, 8192, 512) 105 / 180.
 Tile logits_tile(int64_t N, int64_t V, llamarl_dtype dt) {
-  if (dt == LLAMARL_BF16) return TILE_256;
-  return tile_count(N, V, 128) >= 192 ? TILE_128 : TILE_64;
+  if (dt == LLAMARL_BF16 && tile_count(N, V, 256) >= 192) return TILE_256;
+  return tile_count(N, V, 128) >= (dt == LLAMARL_BF16 ? 128 : 192) ? TILE_128 : TILE_64;
 }
-// Store contractions: M x Nn outputs over K, split along K where tiles are few; counted in parts of 16 slabs (512 k),
-// which still pay for their partial blocks.  fp32, 128- / 64-tiles: dH of (N, V, d) = (512, 4096, 512) 39 / 32 us,
-// (1024, 4096, 512) 42 / 50, (300, 16400, 260) 113 / 59; dW of (512, 4096, 512) 32 / 28, (1024, 4096, 512) 43 / 46,
-// (300, 16400, 260) 40 / 48, (2048, 8192, 512) 107 / 158.
+// Store contractions: M x Nn outputs over K, split along K where tiles are few; counted in parts of 16 slabs, which
+// still pay for their partial blocks.
+//   bf16, dH at (N, V, d) on 256- / 128- / 64-tiles: (512, 2048, 512) 23 / 17.5 / 17 us, (1041, 5003, 520) 33 / 26 / 29,
+//   (1024, 8192, 1024) 42 / 36 / 43, (64, 128256, 4096) 337 / 236 / 229, (1024, 16032, 2048) 77 / 79 / 125;
+//   dW: (512, 2048, 512) 23 / 19 / 16, (512, 8192, 1024) 38 / 17 / 25, (1024, 16032, 2048) 67 / 73 / 131.
+//   fp32 on 128- / 64-tiles, dH: (512, 4096, 512) 39 / 32, (1024, 4096, 512) 42 / 50, (300, 16400, 260) 113 / 59;
+//   dW: (512, 4096, 512) 32 / 28, (1024, 4096, 512) 43 / 46, (300, 16400, 260) 40 / 48.
 Tile store_tile(int64_t M, int64_t Nn, int64_t K, llamarl_dtype dt) {
-  if (dt == LLAMARL_BF16) return TILE_256;
-  const int64_t parts = std::min<int64_t>(STORE_MAX_SPLITS, std::max<int64_t>(1, K / 512));
-  return tile_count(M, Nn, 128) * parts >= 256 ? TILE_128 : TILE_64;
+  const int64_t slab_k = dt == LLAMARL_BF16 ? 64 : 32;
+  const int64_t parts = std::min<int64_t>(STORE_MAX_SPLITS, std::max<int64_t>(1, K / (16 * slab_k)));
+  if (dt == LLAMARL_BF16 && tile_count(M, Nn, 256) * parts >= 256) return TILE_256;
+  return tile_count(M, Nn, 128) * parts >= (dt == LLAMARL_BF16 ? 128 : 256) ? TILE_128 : TILE_64;
 }
 
 typedef TileGemm<BF16> Logits256;
 typedef TileGemm<BF16, STORE_LOAD_SLOT> Store256;
+typedef TileGemmSmall<BF16, Shape128, 2, 2> Bf16Loop128;
+typedef TileGemmSmall<BF16, Shape64, 4, 2> Bf16Loop64;
+typedef TileGemmTNSmall<Shape128, 2, 2> Bf16LoopTN128;
+typedef TileGemmTNSmall<Shape64, 4, 2> Bf16LoopTN64;
 typedef TileGemmSmall<F32, Shape128, 2, 2> F32Loop128;
 typedef TileGemmSmall<F32, Shape64, 4, 2> F32Loop64;
 
@@ -148,11 +160,12 @@ BwdWs bwd_ws(int64_t N, int64_t d, int64_t V, llamarl_dtype dt, int64_t max_rows
     const int64_t grid = (int64_t)MAX_GRID * (edge == 256 ? 1 : 2);
     return std::min(STORE_TAIL_ROUNDS * grid, tile_count(M, d, edge) * STORE_MAX_SPLITS) * edge * edge * 4;
   };
-  // fp32 passes of different lengths may run on different tiles: room for either
-  w.total = w.off_part;
+  // passes of different lengths may run on different tiles: room for any
+  int64_t part = 0;
   for (const int64_t M : {w.R, V})
-    w.total = std::max(w.total, w.off_part + (size_t)(dt == LLAMARL_BF16 ? part_bytes(M, 256)
-                                                                          : std::max(part_bytes(M, 128), part_bytes(M, 64))));
+    for (const int64_t edge : {256, 128, 64})
+      if (edge != 256 || dt == LLAMARL_BF16) part = std::max(part, part_bytes(M, edge));
+  w.total = w.off_part + (size_t)part;
   return w;
 }
 
@@ -299,9 +312,13 @@ llamarl_status run_logprobs(const void* H, const void* W, const int32_t* targets
       partial ? 2 : 0, mask, targets, V_total, nullptr, N, rows, n_act, out0, out1, out2);
   HIP_TRY(hipGetLastError());
   llamarl_status s;
-  if constexpr (dt == LLAMARL_BF16) s = launch_fwd_partials<Logits256>(a, st);
-  else if (logits_tile(N, V, dt) == TILE_128) s = launch_fwd_partials<F32Loop128>(a, st);
-  else s = launch_fwd_partials<F32Loop64>(a, st);
+  const Tile tile = logits_tile(N, V, dt);
+  if constexpr (dt == LLAMARL_BF16)
+    s = (tile == TILE_256   ? launch_fwd_partials<Logits256>
+         : tile == TILE_128 ? launch_fwd_partials<Bf16Loop128>
+                            : launch_fwd_partials<Bf16Loop64>)(a, st);
+  else
+    s = (tile == TILE_128 ? launch_fwd_partials<F32Loop128> : launch_fwd_partials<F32Loop64>)(a, st);
   if (s != LLAMARL_OK) return s;
   MergeArgs m;
   m.part_m = a.part_m; m.part_s = a.part_s; m.zt = a.zt; m.rows = rows; m.n_act = n_act; m.tiles_v = w.tiles_v;
@@ -374,9 +391,13 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     a.v_off = v_off;
     a.dz = dz; a.ldz = w.ldz; a.dzt = dzt; a.rows = rows; a.n_act = n_act;
     llamarl_status s;
-    if constexpr (kBf16) s = launch_bwd_dz<Logits256>(a, Rc, st);
-    else if (logits_tile(Rc, V, dt) == TILE_128) s = launch_bwd_dz<F32Loop128>(a, Rc, st);
-    else s = launch_bwd_dz<F32Loop64>(a, Rc, st);
+    const Tile logits = logits_tile(Rc, V, dt);
+    if constexpr (kBf16)
+      s = (logits == TILE_256   ? launch_bwd_dz<Logits256>
+           : logits == TILE_128 ? launch_bwd_dz<Bf16Loop128>
+                                : launch_bwd_dz<Bf16Loop64>)(a, Rc, st);
+    else
+      s = (logits == TILE_128 ? launch_bwd_dz<F32Loop128> : launch_bwd_dz<F32Loop64>)(a, Rc, st);
     if (s != LLAMARL_OK) return s;
     if (c == 0) PHASE_EVENT(2);
 
@@ -385,11 +406,14 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     //   fp32: K-contiguous operands dz [n_act][ldz] and W^T [d][ldz], K zero-padded to ldz
     float* part = reinterpret_cast<float*>(ws + w.off_part);
     int32_t* plan = reinterpret_cast<int32_t*>(ws + w.off_plan);
+    const Tile dh_tile = store_tile(Rc, d, V, dt), dw_tile = store_tile(V, d, Rc, dt);
     if constexpr (kBf16) {
-      s = launch_store_gemm<TileGemmTN>(dzt, w.ldzt, W, d, Rc, d, V, dH, d, 0, 0, n_act, nullptr, rows, part, plan,
-                                        n_act, 1, 0, st);
+      const auto launch = dh_tile == TILE_256   ? launch_store_gemm<TileGemmTN>
+                          : dh_tile == TILE_128 ? launch_store_gemm<Bf16LoopTN128>
+                                                : launch_store_gemm<Bf16LoopTN64>;
+      s = launch(dzt, w.ldzt, W, d, Rc, d, V, dH, d, 0, 0, n_act, nullptr, rows, part, plan, n_act, 1, 0, st);
     } else {
-      const auto launch = store_tile(Rc, d, V, dt) == TILE_128 ? launch_store_gemm<F32Loop128> : launch_store_gemm<F32Loop64>;
+      const auto launch = dh_tile == TILE_128 ? launch_store_gemm<F32Loop128> : launch_store_gemm<F32Loop64>;
       s = launch(dz, w.ldz, wt, w.ldz, Rc, d, w.ldz, dH, d, 1, 0, n_act, nullptr, rows, part, plan, nullptr, 0, 0, st);
     }
     if (s != LLAMARL_OK) return s;
@@ -398,8 +422,12 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     // dW [V,d] (+)= dz^T [V,n_act] . H^T[d,n_act]^T      (K = n_act, zero-padded to a multiple of 64); passes after
     // the first add to what the earlier ones stored
     auto launch_dw = [&] {
-      if constexpr (kBf16) return launch_store_gemm<Store256>;
-      else return store_tile(V, d, Rc, dt) == TILE_128 ? launch_store_gemm<F32Loop128> : launch_store_gemm<F32Loop64>;
+      if constexpr (kBf16)
+        return dw_tile == TILE_256   ? launch_store_gemm<Store256>
+               : dw_tile == TILE_128 ? launch_store_gemm<Bf16Loop128>
+                                     : launch_store_gemm<Bf16Loop64>;
+      else
+        return dw_tile == TILE_128 ? launch_store_gemm<F32Loop128> : launch_store_gemm<F32Loop64>;
     }();
     s = launch_dw(dzt, w.ldzt, ht, w.ldzt, V, d, w.ldzt, dW, d, dW_dt == LLAMARL_F32, c == 0 ? accumulate_dW : 1, nullptr,
                   n_act, nullptr, part, plan, n_act, 1, 1, st);

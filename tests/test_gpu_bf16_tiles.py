@@ -1,0 +1,37 @@
+"""bf16 contractions on the three tile sizes: sizes at the edges of the tiles, of a K slab (64) and of the rule that
+picks the tile, and the 256 x 256 loops at one, two and three slabs, against float64."""
+import pytest
+import torch
+
+from test_gpu_f32_tiles import _inputs, _reference, _rel
+
+pytestmark = pytest.mark.gpu
+
+
+# logits: bf16 products are exact in fp32, see the fp32 bound; gradients: dz and the results are rounded to bf16 once
+# each, 2^-9 relative at most and independent per entry: 2 x 2^-9 bounds either result's relative error
+@pytest.mark.parametrize("N,V,d", [
+    (1, 64, 8), (64, 63, 64), (65, 129, 72), (127, 1025, 136), (129, 257, 200),       # 64-tiles
+    (256, 8065, 64), (383, 5300, 136), (500, 24000, 72),                               # 128-tiles
+    (300, 24577, 64), (257, 33001, 128), (400, 32700, 136),                            # 256-tiles, K of 1, 2, 3 slabs
+    (40, 33000, 1032), (70, 33000, 1032), (130, 33000, 520),                           # dW on 256-tiles, K of 1, 2, 3 slabs
+    (260, 16384, 520), (520, 16400, 2056),                                             # dH on 128- and 256-tiles, split along K
+])
+@pytest.mark.parametrize("masked", [False, True])
+def test_tile_edges(lib, N, V, d, masked):
+    H, W, t, coef = _inputs(N, V, d, 3 * N + V + d)
+    H, W = H.bfloat16(), W.bfloat16()
+    if masked:
+        coef[1::3] = 0
+    logp, lse = lib.token_logprobs(H, W, t)
+    rlogp, rlse, rdH, rdW = _reference(H, W, t, coef)
+    bound = 2.0 ** -24 * d ** 0.5
+    assert float((lse.double() - rlse).abs().max()) <= 8 * bound + 2e-6
+    assert float((logp.double() - rlogp).abs().max()) <= 16 * bound + 2e-6
+    dH, dW = lib.offpolicy_loss_bwd(H, W, t, lse, coef)
+    assert _rel(dH, rdH) <= 2.0 ** -8 and _rel(dW, rdW) <= 2.0 ** -8
+    _, dW32 = lib.offpolicy_loss_bwd(H, W, t, lse, coef, dW_dtype=torch.float32)
+    assert _rel(dW32, rdW) <= 2.0 ** -8
+    total = dW32.clone()
+    lib.offpolicy_loss_bwd(H, W, t, lse, coef, dW=total, accumulate_dW=True)
+    assert torch.equal(total, 2 * dW32)
