@@ -97,12 +97,13 @@ FwdWs fwd_ws(int64_t N, int64_t V, llamarl_dtype dt) {
 }
 
 struct LossWs {
-  int nblocks;
+  int threads, nblocks;     // of k_loss_tokens
   size_t off_len, off_bad, off_part, off_ticket, total;
 };
 LossWs loss_ws(int64_t N, int64_t B) {  // B generations, N = B * T tokens
   LossWs w;
-  w.nblocks = (int)std::min<int64_t>((N + LOSS_BLOCK_TOKENS - 1) / LOSS_BLOCK_TOKENS, LOSS_MAX_BLOCKS);
+  w.threads = N > (int64_t)LOSS_MAX_BLOCKS * 256 * LOSS_ITEMS ? 1024 : 256;
+  w.nblocks = (int)std::min<int64_t>((N + w.threads * LOSS_ITEMS - 1) / (w.threads * LOSS_ITEMS), LOSS_MAX_BLOCKS);
   w.off_len = 0;
   w.off_bad = (size_t)round_up(B * 4, 256);
   w.off_part = w.off_bad + (size_t)round_up(B * 4, 256);
@@ -540,7 +541,7 @@ static llamarl_status check_loss_args(const float* logp, const float* mu_logp, c
   return LLAMARL_OK;
 }
 
-// the two launches of the loss forward; wsb holds a LossWs layout for (B*T, B)
+// the launches of the loss forward; wsb holds a LossWs layout for (B*T, B)
 static llamarl_status launch_loss_fwd(const float* logp, const float* mu_logp, const float* adv, int adv_per_token,
                                       const uint8_t* mask, const int32_t* targets, int64_t V, int64_t B, int64_t T,
                                       const llamarl_loss_params* p, float* loss, float* coef, float* stats, char* wsb,
@@ -554,9 +555,17 @@ static llamarl_status launch_loss_fwd(const float* logp, const float* mu_logp, c
   a.partials = reinterpret_cast<double*>(wsb + w.off_part);
   a.ticket = reinterpret_cast<unsigned int*>(wsb + w.off_ticket);
   a.nblocks = w.nblocks; a.coef = coef; a.loss = loss; a.stats = stats;
-  k_seq_lengths<<<dim3((unsigned)B), dim3(SEQ_THREADS), 0, st>>>(a);          // also clears the ticket
+  if (B <= LOSS_SMALL_GENERATIONS && B * T <= LOSS_SMALL_TOKENS) {
+    k_loss_small<<<dim3(1), dim3(LOSS_SMALL_THREADS), 0, st>>>(a);
+    HIP_TRY(hipGetLastError());
+    return LLAMARL_OK;
+  }
+  const int seq_threads = T > 4096 ? 1024 : 256;
+  (seq_threads == 1024 ? k_seq_lengths<1024> : k_seq_lengths<256>)<<<dim3((unsigned)B), dim3((unsigned)seq_threads), 0, st>>>(
+      a);                                                                     // also clears the ticket
   HIP_TRY(hipGetLastError());
-  k_loss_tokens<<<dim3((unsigned)w.nblocks), dim3(LOSS_THREADS), 0, st>>>(a);   // its last block writes loss, stats
+  (w.threads == 1024 ? k_loss_tokens<1024> : k_loss_tokens<256>)<<<dim3((unsigned)w.nblocks), dim3((unsigned)w.threads), 0,
+                                                                   st>>>(a);   // its last block writes loss, stats
   HIP_TRY(hipGetLastError());
   return LLAMARL_OK;
 }
@@ -731,7 +740,7 @@ llamarl_status llamarl_kl_shaped_rewards(const float* rewards, const float* logp
   if (B <= 0 || T <= 0) return fail(LLAMARL_ERR_INVALID_ARG, "B and T must be positive");
   if (B >= (int64_t)1 << 31) return fail(LLAMARL_ERR_UNSUPPORTED, "too many generations");
   if (!(lambda_kl == lambda_kl)) return fail(LLAMARL_ERR_INVALID_ARG, "lambda_kl is NaN");
-  k_kl_shaped_rewards<<<dim3((unsigned)B), dim3(LOSS_THREADS), 0, reinterpret_cast<hipStream_t>(stream)>>>(
+  k_kl_shaped_rewards<<<dim3((unsigned)B), dim3(KL_THREADS), 0, reinterpret_cast<hipStream_t>(stream)>>>(
       rewards, logp, base_logp, mask, T, lambda_kl, shaped, kl);
   HIP_TRY(hipGetLastError());
   return LLAMARL_OK;
