@@ -233,7 +233,7 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
 // already wrote 0 for masked / bad-target rows).  HBM-bound (8 bytes per token and vocab tile): a block of 1024
 // threads takes 32 list positions x 32 slices of the vocab tiles, so a row of 32 lanes reads one 128-byte line and
 // there are enough loads in flight to stream.
-constexpr int MERGE_TOKENS = 32, MERGE_SLICES = 32;
+constexpr int MERGE_TOKENS = 32, MERGE_SLICES = 32, MERGE_BATCH = 8;
 struct MergeArgs {
   const float* part_m;
   const float* part_s;
@@ -259,13 +259,25 @@ __global__ __launch_bounds__(MERGE_TOKENS * MERGE_SLICES) void k_merge_logp(Merg
   if ((int64_t)blockIdx.x * MERGE_TOKENS >= n) return;        // block-uniform
   float M = -INFINITY, S = 0.f;
   if (p < n) {
-    for (int j = sl; j < a.tiles_v; j += MERGE_SLICES) {
-      const float m = a.part_m[(int64_t)j * a.n_pad + p], s = a.part_s[(int64_t)j * a.n_pad + p];
-      if (m > M) {
-        S = S * __expf(M - m) + s;      // exp(-inf) = 0 on the first tile
-        M = m;
-      } else if (m != -INFINITY) {
-        S += s * __expf(m - M);
+    // MERGE_BATCH tiles' loads in flight at a time: the running (M, S) is a serial chain, the loads need not be
+    for (int j0 = sl; j0 < a.tiles_v; j0 += MERGE_SLICES * MERGE_BATCH) {
+      float mb[MERGE_BATCH], sb[MERGE_BATCH];
+#pragma unroll
+      for (int q = 0; q < MERGE_BATCH; ++q) {
+        const int64_t at = (int64_t)min(j0 + q * MERGE_SLICES, a.tiles_v - 1) * a.n_pad + p;
+        mb[q] = a.part_m[at];
+        sb[q] = a.part_s[at];
+      }
+#pragma unroll
+      for (int q = 0; q < MERGE_BATCH; ++q) {
+        if (j0 + q * MERGE_SLICES >= a.tiles_v) break;
+        const float m = mb[q], s = sb[q];
+        if (m > M) {
+          S = S * __expf(M - m) + s;      // exp(-inf) = 0 on the first tile
+          M = m;
+        } else if (m != -INFINITY) {
+          S += s * __expf(m - M);
+        }
       }
     }
   }
@@ -321,67 +333,105 @@ __global__ __launch_bounds__(256) void k_merge_shards(const float* m, const floa
 // is inside [0,V); inactive rows get out0 = out1 = 0 (logp, lse) here.  mode 2 (forward of a shard): the same
 // list, inactive rows get (out0, out1, out2) = (-inf, 0, 0), the shard's (m, s, zt).  mode 1 (backward): active
 // if coef[t] != 0.
-// The list is ascending, so every later kernel is deterministic.  Block b owns rows [b, b+1) * COMPACT_BLOCK_ROWS:
-// it first counts the active rows in front of its range by evaluating the predicate over them (5 bytes a row,
-// served by L2 -- cheaper than a second launch or a cross-block wait for the batch sizes of a trainer step), then
-// scans its own rows in order.  The last block stores the total.
+// The list is ascending, so every later kernel is deterministic.  Block b owns rows [b, b+1) * COMPACT_BLOCK_ROWS, four
+// neighbouring rows a thread (16-byte loads of targets / coef, 4 bytes of mask; token by token where the arrays are
+// not aligned for that or the batch ends inside the group).  It first counts the active rows in front of its range by
+// evaluating the predicate over them (5 bytes a row, served by L2 -- cheaper than a second launch or a cross-block
+// wait for the batch sizes of a trainer step), then places its own in one scan.  The last block stores the total.
+// Bound by latency; with four scans of one row a thread and its list walked a row at a time the log-prob call on a tiny
+// head took 18 us at 4097 rows and 29 us at 40000, now 12 and 18 (partial merge included, see MERGE_BATCH).
 constexpr int COMPACT_THREADS = 1024;
 constexpr int COMPACT_BLOCK_ROWS = 4 * COMPACT_THREADS;
 
-__device__ __forceinline__ bool row_active(int mode, const uint8_t* mask, const int32_t* targets, int64_t V,
-                                           const float* coef, int64_t t) {
-  if (mode == 1) return coef[t] != 0.f;
-  const int y = targets[t];
-  return (mask == nullptr || mask[t] != 0) && y >= 0 && (int64_t)y < V;
+struct CompactArgs {
+  int mode;
+  const uint8_t* mask;
+  const int32_t* targets;
+  const float* coef;
+  int64_t V, N;
+  int aligned;               // targets / coef 16-byte, mask 4-byte aligned
+  int32_t* rows;
+  int32_t* n_act;
+  float* out0;
+  float* out1;
+  float* out2;
+};
+
+// bit i: row t0 + i is active (t0 a multiple of 4)
+__device__ __forceinline__ uint32_t active_rows4(const CompactArgs& a, int64_t t0) {
+  uint32_t bits = 0;
+  if (a.aligned && t0 + 4 <= a.N) {
+    if (a.mode == 1) {
+      const float4 c = *reinterpret_cast<const float4*>(a.coef + t0);
+      return (c.x != 0.f ? 1u : 0u) | (c.y != 0.f ? 2u : 0u) | (c.z != 0.f ? 4u : 0u) | (c.w != 0.f ? 8u : 0u);
+    }
+    const int4 y = *reinterpret_cast<const int4*>(a.targets + t0);
+    const uchar4 k = a.mask != nullptr ? *reinterpret_cast<const uchar4*>(a.mask + t0) : make_uchar4(1, 1, 1, 1);
+    bits |= (k.x != 0 && y.x >= 0 && (int64_t)y.x < a.V) ? 1u : 0u;
+    bits |= (k.y != 0 && y.y >= 0 && (int64_t)y.y < a.V) ? 2u : 0u;
+    bits |= (k.z != 0 && y.z >= 0 && (int64_t)y.z < a.V) ? 4u : 0u;
+    bits |= (k.w != 0 && y.w >= 0 && (int64_t)y.w < a.V) ? 8u : 0u;
+    return bits;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int64_t t = t0 + i;
+    if (t >= a.N) continue;
+    bool on;
+    if (a.mode == 1) {
+      on = a.coef[t] != 0.f;
+    } else {
+      const int y = a.targets[t];
+      on = (a.mask == nullptr || a.mask[t] != 0) && y >= 0 && (int64_t)y < a.V;
+    }
+    bits |= on ? 1u << i : 0u;
+  }
+  return bits;
 }
 
-__global__ __launch_bounds__(COMPACT_THREADS) void k_compact_rows(int mode, const uint8_t* mask, const int32_t* targets,
-                                                                   int64_t V, const float* coef, int64_t N,
-                                                                   int32_t* rows, int32_t* n_act, float* out0,
-                                                                   float* out1, float* out2) {
-  __shared__ int s_wave[COMPACT_THREADS / 64];
-  __shared__ int s_base;
+__global__ __launch_bounds__(COMPACT_THREADS) void k_compact_rows(CompactArgs a) {
+  constexpr int WAVES = COMPACT_THREADS / 64;
+  __shared__ int s_front[WAVES], s_own[WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t first = (int64_t)blockIdx.x * COMPACT_BLOCK_ROWS;
-  int before_block = 0;
-  for (int64_t t = tid; t < first; t += COMPACT_THREADS) before_block += row_active(mode, mask, targets, V, coef, t) ? 1 : 0;
+  const int64_t first = (int64_t)blockIdx.x * COMPACT_BLOCK_ROWS, t0 = first + 4 * tid;
+  const uint32_t act = t0 < a.N ? active_rows4(a, t0) : 0u;
+  int front = 0;
+#pragma unroll 4
+  for (int64_t t = 4 * tid; t < first; t += COMPACT_BLOCK_ROWS) front += __popc(active_rows4(a, t));
+  if (a.mode != 1) {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) before_block += __shfl_xor(before_block, o);
-  if (lane == 0) s_wave[wave] = before_block;
-  __syncthreads();
-  if (tid == 0) {
-    int tot = 0;
-    for (int w = 0; w < COMPACT_THREADS / 64; ++w) tot += s_wave[w];
-    s_base = tot;
-  }
-  __syncthreads();
-  for (int64_t start = first; start < min(N, first + COMPACT_BLOCK_ROWS); start += COMPACT_THREADS) {
-    const int64_t t = start + tid;
-    bool act = false;
-    if (t < N) {
-      act = row_active(mode, mask, targets, V, coef, t);
-      if (mode != 1 && !act) {
-        out0[t] = (mode == 2) ? -INFINITY : 0.f;
-        out1[t] = 0.f;
-        if (mode == 2) out2[t] = 0.f;
+    for (int i = 0; i < 4; ++i) {
+      const int64_t t = t0 + i;
+      if (t < a.N && !(act >> i & 1u)) {
+        a.out0[t] = (a.mode == 2) ? -INFINITY : 0.f;
+        a.out1[t] = 0.f;
+        if (a.mode == 2) a.out2[t] = 0.f;
       }
     }
-    const unsigned long long b = __ballot(act);
-    const int before = __popcll(b & ((1ull << lane) - 1ull));
-    if (lane == 0) s_wave[wave] = __popcll(b);
-    __syncthreads();
-    int off = s_base;
-    for (int w = 0; w < wave; ++w) off += s_wave[w];
-    if (act) rows[off + before] = (int32_t)t;
-    __syncthreads();
-    if (tid == 0) {
-      int tot = 0;
-      for (int w = 0; w < COMPACT_THREADS / 64; ++w) tot += s_wave[w];
-      s_base += tot;
-    }
-    __syncthreads();
   }
-  if (tid == 0 && blockIdx.x == gridDim.x - 1) *n_act = s_base;
+  const int own = __popc(act);
+  int upto = own;                                   // active rows of lanes 0 .. lane of this wavefront
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(upto, o);
+    upto += lane >= o ? v : 0;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) front += __shfl_xor(front, o);
+  if (lane == 63) s_own[wave] = upto;
+  if (lane == 0) s_front[wave] = front;
+  __syncthreads();
+  int base = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) {
+    base += s_front[w] + (w < wave ? s_own[w] : 0);
+    total += s_front[w] + s_own[w];
+  }
+  int at = base + upto - own;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (act >> i & 1u) a.rows[at++] = (int32_t)(t0 + i);
+  if (tid == 0 && blockIdx.x == gridDim.x - 1) *a.n_act = total;
 }
 
 // dH rows of inactive tokens (coef == 0) are exactly zero; the dH contraction only writes the active ones.

@@ -272,6 +272,13 @@ llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int6
   }
 }
 
+llamarl_status launch_compact(CompactArgs a, hipStream_t st) {
+  a.aligned = aligned16(a.targets) && aligned16(a.coef) && (reinterpret_cast<uintptr_t>(a.mask) & 3u) == 0;
+  k_compact_rows<<<dim3((unsigned)((a.N + COMPACT_BLOCK_ROWS - 1) / COMPACT_BLOCK_ROWS)), dim3(COMPACT_THREADS), 0, st>>>(a);
+  HIP_TRY(hipGetLastError());
+  return LLAMARL_OK;
+}
+
 template <typename G>
 llamarl_status launch_fwd_partials(const FwdArgs& a, hipStream_t st) {
   HIP_TRY(set_lds_if_large(k_fwd_partials<G>, fwd_lds_bytes<G>));
@@ -309,10 +316,8 @@ llamarl_status run_logprobs(const void* H, const void* W, const int32_t* targets
   int32_t* n_act = reinterpret_cast<int32_t*>(ws + w.off_nact);
   a.rows = rows; a.n_act = n_act;
   // active-token list (mask and target range); inactive rows get their outputs here
-  k_compact_rows<<<dim3((unsigned)((N + COMPACT_BLOCK_ROWS - 1) / COMPACT_BLOCK_ROWS)), dim3(COMPACT_THREADS), 0, st>>>(
-      partial ? 2 : 0, mask, targets, V_total, nullptr, N, rows, n_act, out0, out1, out2);
-  HIP_TRY(hipGetLastError());
-  llamarl_status s;
+  llamarl_status s = launch_compact({partial ? 2 : 0, mask, targets, nullptr, V_total, N, 0, rows, n_act, out0, out1, out2}, st);
+  if (s != LLAMARL_OK) return s;
   const Tile tile = logits_tile(N, V, dt);
   if constexpr (dt == LLAMARL_BF16)
     s = (tile == TILE_256   ? launch_fwd_partials<Logits256>
@@ -359,9 +364,8 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
   int32_t* pass_cnt = n_act_all + 1;
 
   // tokens that carry gradient (coef != 0), and exact zeros for the dH rows of all the others
-  k_compact_rows<<<dim3((unsigned)((N + COMPACT_BLOCK_ROWS - 1) / COMPACT_BLOCK_ROWS)), dim3(COMPACT_THREADS), 0, st>>>(
-      1, nullptr, nullptr, V, coef, N, all_rows, n_act_all, nullptr, nullptr, nullptr);
-  HIP_TRY(hipGetLastError());
+  llamarl_status s = launch_compact({1, nullptr, nullptr, coef, V, N, 0, all_rows, n_act_all, nullptr, nullptr, nullptr}, st);
+  if (s != LLAMARL_OK) return s;
   k_zero_inactive_rows<stt><<<dim3((unsigned)N), dim3(256), 0, st>>>(reinterpret_cast<stt*>(dH), coef, N, d);
   HIP_TRY(hipGetLastError());
   if (w.n_pass > 1) {
@@ -391,7 +395,6 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     a.H = H; a.W = W; a.targets = targets; a.lse = lse; a.coef = coef; a.g = g; a.N = N; a.d = d; a.V = V;
     a.v_off = v_off;
     a.dz = dz; a.ldz = w.ldz; a.dzt = dzt; a.rows = rows; a.n_act = n_act;
-    llamarl_status s;
     const Tile logits = logits_tile(Rc, V, dt);
     if constexpr (kBf16)
       s = (logits == TILE_256   ? launch_bwd_dz<Logits256>

@@ -13,6 +13,34 @@ def _shifted(t, by):
     return out.copy_(t)
 
 
+@pytest.mark.parametrize("N", [1, 3, 4, 5, 255, 257, 4095, 4096, 4097, 8191, 12289])
+def test_compaction_at_any_alignment(lib, N):
+    g = torch.Generator(device="cuda").manual_seed(N)
+    H = torch.randn(N, 8, generator=g, device="cuda").bfloat16()
+    W = torch.randn(20, 8, generator=g, device="cuda").bfloat16()
+    t = torch.randint(-1, 21, (N,), generator=g, device="cuda").int()          # some out of range
+    m = (torch.rand(N, generator=g, device="cuda") < 0.6).to(torch.uint8)
+    logp, lse = lib.token_logprobs(H, W, t, m)
+    ok = (m != 0) & (t >= 0) & (t < 20)
+    z = H.double() @ W.double().T
+    rlse = torch.logsumexp(z, dim=1)
+    rlogp = z.gather(1, t.long().clamp(0, 19)[:, None])[:, 0] - rlse
+    zero = torch.zeros_like(rlse)
+    assert float((lse.double() - torch.where(ok, rlse, zero)).abs().max()) <= 1e-5
+    assert float((logp.double() - torch.where(ok, rlogp, zero)).abs().max()) <= 1e-5
+    l2, s2 = lib.token_logprobs(H, W, _shifted(t, 1), _shifted(m, 3))
+    assert torch.equal(logp, l2) and torch.equal(lse, s2)
+    a = lib.token_logprobs_partial(H, W, t, 0, 20, m)
+    b = lib.token_logprobs_partial(H, W, _shifted(t, 3), 0, 20, _shifted(m, 1))
+    assert all(torch.equal(x, y) for x, y in zip(a, b))
+    assert bool((a[0][~ok] == -float("inf")).all()) and not bool(a[1][~ok].any())
+    coef = torch.where(ok, torch.randn(N, generator=g, device="cuda"), torch.zeros(N, device="cuda"))
+    tc = t.clamp(0, 19)
+    dH, dW = lib.offpolicy_loss_bwd(H, W, tc, lse, coef)
+    dH2, dW2 = lib.offpolicy_loss_bwd(H, W, _shifted(tc, 1), lse, _shifted(coef, 1))
+    assert torch.equal(dH, dH2) and torch.equal(dW, dW2) and not bool(dH[~ok].any())
+
+
 @pytest.mark.parametrize("B,T", [(1, 1), (3, 2), (5, 7), (2, 1023), (3, 2049), (2, 16385)])
 @pytest.mark.parametrize("with_mask", [True, False])
 def test_kl_sums_at_any_alignment(lib, B, T, with_mask):
