@@ -6,8 +6,9 @@
 //   k_bwd_dz         recomputed logits tile -> dz = g * coef * (onehot - softmax), written in both orientations
 //   k_gemm_store     plain contraction with a store epilogue: dW = dz^T H (K-contiguous operands) and
 //                    dH = dz W (k-major operands: dz^T as written, W as the caller holds it; bf16)
-//   k_transpose      [R,C] -> [C,R] with zero padding and row gather (H^T panel of the active tokens; fp32: W^T too)
-//   k_compact_rows   ascending list of active token rows; k_zero_inactive_rows, k_reduce_tail: small helpers
+//   k_transpose      [R,C] -> [C,R] with zero padding and row gather (H^T panel of the active tokens)
+//   k_compact_rows   ascending list of active token rows (the backward's is part of k_bwd_setup)
+//   k_bwd_setup      the backward's list, zeroed inactive dH rows, fp32: W^T;  k_reduce_tail: sums of split tiles
 //
 // In the two logits kernels the MFMA "row" operand is W (vocab) and the "column" operand is H (tokens): an
 // accumulator lane then holds ONE token per column block (column = lane % 16) and 4 vocab entries per 16x16
@@ -389,11 +390,11 @@ __device__ __forceinline__ uint32_t active_rows4(const CompactArgs& a, int64_t t
   return bits;
 }
 
-__global__ __launch_bounds__(COMPACT_THREADS) void k_compact_rows(CompactArgs a) {
+__device__ __forceinline__ void compact_rows(const CompactArgs& a, int block, int nblocks) {
   constexpr int WAVES = COMPACT_THREADS / 64;
   __shared__ int s_front[WAVES], s_own[WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t first = (int64_t)blockIdx.x * COMPACT_BLOCK_ROWS, t0 = first + 4 * tid;
+  const int64_t first = (int64_t)block * COMPACT_BLOCK_ROWS, t0 = first + 4 * tid;
   const uint32_t act = t0 < a.N ? active_rows4(a, t0) : 0u;
   int front = 0;
 #pragma unroll 4
@@ -431,18 +432,9 @@ __global__ __launch_bounds__(COMPACT_THREADS) void k_compact_rows(CompactArgs a)
 #pragma unroll
   for (int i = 0; i < 4; ++i)
     if (act >> i & 1u) a.rows[at++] = (int32_t)(t0 + i);
-  if (tid == 0 && blockIdx.x == gridDim.x - 1) *a.n_act = total;
+  if (tid == 0 && block == nblocks - 1) *a.n_act = total;
 }
-
-// dH rows of inactive tokens (coef == 0) are exactly zero; the dH contraction only writes the active ones.
-template <typename ST>
-__global__ __launch_bounds__(256) void k_zero_inactive_rows(ST* dH, const float* coef, int64_t N, int64_t d) {
-  const int64_t t = blockIdx.x;
-  if (coef[t] != 0.f) return;
-  uint4* p = reinterpret_cast<uint4*>(dH + t * d);
-  const int64_t n16 = d * (int64_t)sizeof(ST) / 16;
-  for (int64_t i = threadIdx.x; i < n16; i += 256) p[i] = make_uint4(0, 0, 0, 0);
-}
+__global__ __launch_bounds__(COMPACT_THREADS) void k_compact_rows(CompactArgs a) { compact_rows(a, blockIdx.x, gridDim.x); }
 
 struct DzArgs {
   const void* H;
@@ -963,64 +955,104 @@ __global__ __launch_bounds__(256) void k_reduce_tail(StoreArgs a) {
   }
 }
 
-// out[c][p] = in[src(p)][c] for p < R, c < C; out[c][p] = 0 for R <= p < ld_out.
-// rows == nullptr: src(p) = p and R is the host value.  Otherwise src(p) = rows[p], R = *r_count, the row pitch of
-// `out` is packed_pitch(R) (ld_out is the pitch the buffer was sized for) and only the first R rounded up to 64
-// columns of `out` are written (the contraction that reads it stops there).
-template <typename ST>
-__global__ __launch_bounds__(256) void k_transpose(const ST* in, int64_t R, int64_t C, int64_t ld_in, ST* out,
-                                                    int64_t ld_out, const int32_t* rows, const int32_t* r_count) {
-  if (rows != nullptr) {
-    R = *r_count;
-    ld_out = packed_pitch(R);
-  }
-  const int64_t r0 = (int64_t)blockIdx.x * 64, c0 = (int64_t)blockIdx.y * 64;
-  if (rows != nullptr && r0 >= R) return;                     // block-uniform
-  if constexpr (sizeof(ST) == 2) {
-    // 16-bit elements, whole 16-byte chunks along both matrices' rows (block-uniform test): 16-byte loads and
-    // stores, eight elements a thread, the transposition through LDS in between
-    if (C % 8 == 0 && ld_in % 8 == 0 && ld_out % 8 == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
-        (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
-      __shared__ __attribute__((aligned(16))) uint16_t t16[64][72];
-      const int q = threadIdx.x & 7, line = threadIdx.x >> 3;   // 8 chunks x 32 lines, two rounds
+// out[c][p] = in[src(p)][c] for p < R, c < C; out[c][p] = 0 for R <= p < ld_out, one 64 x 64 tile (origin r0, c0) by a
+// workgroup of THREADS.  src(p) = p, or rows[p] where a list is given.
+template <typename ST, int THREADS>
+__device__ __forceinline__ void transpose_tile(const ST* in, int64_t R, int64_t C, int64_t ld_in, ST* out, int64_t ld_out,
+                                               const int32_t* rows, int64_t r0, int64_t c0) {
+  constexpr int EPV = 16 / sizeof(ST);                          // elements of a 16-byte chunk
+  constexpr int CHUNKS = 64 / EPV, LINES = THREADS / CHUNKS;    // chunks along a tile row; rows taken at a time
+  // whole 16-byte chunks along both matrices' rows (block-uniform test): 16-byte loads and stores, the transposition
+  // through LDS in between.  The LDS row is padded by one chunk: the columns a wavefront gathers for its stores then
+  // start in different banks.
+  if (C % EPV == 0 && ld_in % EPV == 0 && ld_out % EPV == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
+      (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
+    __shared__ __attribute__((aligned(16))) ST t[64][64 + EPV];
+    const int q = threadIdx.x % CHUNKS, line = threadIdx.x / CHUNKS;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int rr = line + 32 * h;
-        const int64_t r = r0 + rr, c = c0 + q * 8;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (r < R && c < C)
-          v = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(in) +
-                                              (rows ? (int64_t)rows[r] : r) * ld_in + c);
-        *reinterpret_cast<uint4*>(&t16[rr][q * 8]) = v;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int cc = line + 32 * h;
-        const int64_t c = c0 + cc, r = r0 + q * 8;
-        if (c < C && r < ld_out) {
-          uint32_t w[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            w[j] = (uint32_t)t16[q * 8 + 2 * j][cc] | ((uint32_t)t16[q * 8 + 2 * j + 1][cc] << 16);
-          *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(out) + c * ld_out + r) = make_uint4(w[0], w[1], w[2], w[3]);
-        }
-      }
-      return;
+    for (int h = 0; h < 64; h += LINES) {
+      const int rr = line + h;
+      const int64_t r = r0 + rr, c = c0 + q * EPV;
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (rr < 64 && r < R && c < C) v = *reinterpret_cast<const uint4*>(in + (rows ? (int64_t)rows[r] : r) * ld_in + c);
+      if (rr < 64) *reinterpret_cast<uint4*>(&t[rr][q * EPV]) = v;
     }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 64; h += LINES) {
+      const int cc = line + h;
+      const int64_t c = c0 + cc, r = r0 + q * EPV;
+      if (cc < 64 && c < C && r < ld_out) {
+        ST w[EPV];
+#pragma unroll
+        for (int j = 0; j < EPV; ++j) w[j] = t[q * EPV + j][cc];
+        uint4 v;
+        __builtin_memcpy(&v, w, 16);
+        *reinterpret_cast<uint4*>(out + c * ld_out + r) = v;
+      }
+    }
+    return;
   }
   __shared__ ST tile[64][65];
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;     // 256 threads: 64 x 4
-  for (int rr = ty; rr < 64; rr += 4) {
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  for (int rr = ty; rr < 64; rr += THREADS / 64) {
     const int64_t r = r0 + rr, c = c0 + tx;
     ST v = 0;
     if (r < R && c < C) v = in[(rows ? (int64_t)rows[r] : r) * ld_in + c];
     tile[rr][tx] = v;
   }
   __syncthreads();
-  for (int cc = ty; cc < 64; cc += 4) {
+  for (int cc = ty; cc < 64; cc += THREADS / 64) {
     const int64_t c = c0 + cc, r = r0 + tx;
     if (c < C && r < ld_out) out[c * ld_out + r] = tile[tx][cc];
+  }
+}
+
+// H^T panel of a pass's active tokens: R = *r_count, the row pitch of `out` is packed_pitch(R), and only the first R
+// rounded up to 64 columns of `out` are written (the contraction that reads it stops there).
+template <typename ST>
+__global__ __launch_bounds__(256) void k_transpose(const ST* in, int64_t C, int64_t ld_in, ST* out, const int32_t* rows,
+                                                    const int32_t* r_count) {
+  const int64_t R = *r_count, r0 = (int64_t)blockIdx.x * 64;
+  if (r0 >= R) return;                                          // block-uniform
+  transpose_tile<ST, 256>(in, R, C, ld_in, out, packed_pitch(R), rows, r0, (int64_t)blockIdx.y * 64);
+}
+
+// What the backward prepares before it knows the active rows, in one launch: the active-row list (first blocks), zeros
+// in the dH rows of inactive tokens (coef == 0: the dH contraction only writes the active ones; a wavefront takes a
+// row) and, fp32 only, W^T [d][ldz] (64 x 64 tiles).  Three launches of a few microseconds each otherwise.
+template <typename ST>
+struct SetupArgs {
+  CompactArgs compact;
+  int compact_blocks, zero_blocks;
+  ST* dH;
+  int64_t d;
+  const ST* W;               // fp32 only
+  int64_t V, ldz;
+  ST* wt;
+  int64_t wt_tiles_r;        // tiles along V; the tiles along d follow from the grid
+};
+constexpr int SETUP_ROWS = COMPACT_THREADS / 64;       // dH rows of a block
+template <typename ST>
+__global__ __launch_bounds__(COMPACT_THREADS) void k_bwd_setup(SetupArgs<ST> a) {
+  int block = blockIdx.x;
+  if (block < a.compact_blocks) {
+    compact_rows(a.compact, block, a.compact_blocks);
+    return;
+  }
+  block -= a.compact_blocks;
+  if (block < a.zero_blocks) {
+    const int64_t t = (int64_t)block * SETUP_ROWS + (threadIdx.x >> 6);
+    if (t >= a.compact.N || a.compact.coef[t] != 0.f) return;
+    uint4* p = reinterpret_cast<uint4*>(a.dH + t * a.d);
+    const int64_t n16 = a.d * (int64_t)sizeof(ST) / 16;
+    for (int64_t i = threadIdx.x & 63; i < n16; i += 64) p[i] = make_uint4(0, 0, 0, 0);
+    return;
+  }
+  block -= a.zero_blocks;
+  if constexpr (sizeof(ST) == 4) {
+    const int64_t tc = block / a.wt_tiles_r, tr = block - tc * a.wt_tiles_r;
+    transpose_tile<ST, COMPACT_THREADS>(a.W, a.V, a.d, a.d, a.wt, a.ldz, nullptr, tr * 64, tc * 64);
   }
 }
 

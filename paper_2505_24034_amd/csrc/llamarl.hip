@@ -229,8 +229,10 @@ llamarl_status launch_store_mode(const StoreArgs& a, int64_t work_items, int til
   const int grid = persistent_grid(work_items, G::GROUPS_PER_CU);
   k_gemm_store<G, MODE><<<dim3((unsigned)grid), dim3(G::Shape::THREADS), G::LDS_BYTES, st>>>(a);
   HIP_TRY(hipGetLastError());
-  if (a.max_splits > 1) {
-    // the split tiles of the last round, if the device-side sizes left any: fewer than `grid` of them
+  // the split tiles of the last round, if the device-side sizes left any: fewer than `grid` of them.  A contraction
+  // whose longest K leaves no two parts of four slabs is never split (StorePlan::init).
+  constexpr int BK = 8 * G::Type::EPC;
+  if (a.max_splits > 1 && (a.K + BK - 1) / BK >= 8) {
     const int tail = std::min(grid - 1, tiles_worst);
     if (tail > 0) {
       const int units = tail * TailUnit<typename G::Shape>::PER_TILE;
@@ -272,12 +274,11 @@ llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int6
   }
 }
 
-llamarl_status launch_compact(CompactArgs a, hipStream_t st) {
+CompactArgs compact_args(CompactArgs a) {
   a.aligned = aligned16(a.targets) && aligned16(a.coef) && (reinterpret_cast<uintptr_t>(a.mask) & 3u) == 0;
-  k_compact_rows<<<dim3((unsigned)((a.N + COMPACT_BLOCK_ROWS - 1) / COMPACT_BLOCK_ROWS)), dim3(COMPACT_THREADS), 0, st>>>(a);
-  HIP_TRY(hipGetLastError());
-  return LLAMARL_OK;
+  return a;
 }
+int compact_blocks(int64_t N) { return (int)((N + COMPACT_BLOCK_ROWS - 1) / COMPACT_BLOCK_ROWS); }
 
 template <typename G>
 llamarl_status launch_fwd_partials(const FwdArgs& a, hipStream_t st) {
@@ -316,8 +317,10 @@ llamarl_status run_logprobs(const void* H, const void* W, const int32_t* targets
   int32_t* n_act = reinterpret_cast<int32_t*>(ws + w.off_nact);
   a.rows = rows; a.n_act = n_act;
   // active-token list (mask and target range); inactive rows get their outputs here
-  llamarl_status s = launch_compact({partial ? 2 : 0, mask, targets, nullptr, V_total, N, 0, rows, n_act, out0, out1, out2}, st);
-  if (s != LLAMARL_OK) return s;
+  k_compact_rows<<<dim3((unsigned)compact_blocks(N)), dim3(COMPACT_THREADS), 0, st>>>(
+      compact_args({partial ? 2 : 0, mask, targets, nullptr, V_total, N, 0, rows, n_act, out0, out1, out2}));
+  HIP_TRY(hipGetLastError());
+  llamarl_status s;
   const Tile tile = logits_tile(N, V, dt);
   if constexpr (dt == LLAMARL_BF16)
     s = (tile == TILE_256   ? launch_fwd_partials<Logits256>
@@ -363,22 +366,24 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
   int32_t* n_act_all = reinterpret_cast<int32_t*>(ws + w.off_nact);
   int32_t* pass_cnt = n_act_all + 1;
 
-  // tokens that carry gradient (coef != 0), and exact zeros for the dH rows of all the others
-  llamarl_status s = launch_compact({1, nullptr, nullptr, coef, V, N, 0, all_rows, n_act_all, nullptr, nullptr, nullptr}, st);
-  if (s != LLAMARL_OK) return s;
-  k_zero_inactive_rows<stt><<<dim3((unsigned)N), dim3(256), 0, st>>>(reinterpret_cast<stt*>(dH), coef, N, d);
+  constexpr bool kBf16 = sizeof(stt) == 2;
+  // tokens that carry gradient (coef != 0), exact zeros for the dH rows of all the others, fp32: W^T for the
+  // K-contiguous dH contraction
+  SetupArgs<stt> u;
+  u.compact = compact_args({1, nullptr, nullptr, coef, V, N, 0, all_rows, n_act_all, nullptr, nullptr, nullptr});
+  u.compact_blocks = compact_blocks(N);
+  u.zero_blocks = (int)((N + SETUP_ROWS - 1) / SETUP_ROWS);
+  u.dH = reinterpret_cast<stt*>(dH); u.d = d;
+  u.W = reinterpret_cast<const stt*>(W); u.V = V; u.ldz = w.ldz; u.wt = wt;
+  u.wt_tiles_r = w.ldz / 64;
+  const int64_t setup_blocks = u.compact_blocks + u.zero_blocks + (kBf16 ? 0 : u.wt_tiles_r * ((d + 63) / 64));
+  k_bwd_setup<stt><<<dim3((unsigned)setup_blocks), dim3(COMPACT_THREADS), 0, st>>>(u);
   HIP_TRY(hipGetLastError());
   if (w.n_pass > 1) {
     k_pass_counts<<<dim3((unsigned)((w.n_pass + 255) / 256)), dim3(256), 0, st>>>(n_act_all, w.R, w.n_pass, pass_cnt);
     HIP_TRY(hipGetLastError());
   }
-  constexpr bool kBf16 = sizeof(stt) == 2;
-  if (!kBf16) {   // fp32 only: W^T [d][ldz] for the K-contiguous dH contraction
-    k_transpose<stt><<<dim3((unsigned)(w.ldz / 64), (unsigned)((d + 63) / 64)), dim3(256), 0, st>>>(
-        reinterpret_cast<const stt*>(W), V, d, d, wt, w.ldz, nullptr, nullptr);
-    HIP_TRY(hipGetLastError());
-  }
-
+  llamarl_status s;
   for (int c = 0; c < w.n_pass; ++c) {
     // this pass: list positions [c R, c R + n_act), n_act = the pass's own count (device scalar)
     const int32_t* rows = all_rows + (int64_t)c * w.R;
@@ -386,7 +391,7 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     const int64_t Rc = std::min(w.R, N - (int64_t)c * w.R);       // rows the pass can hold at most
     // operand panel H^T [d][pitch] of the pass's tokens (dW contraction)
     k_transpose<stt><<<dim3((unsigned)(w.ldzt / 64), (unsigned)((d + 63) / 64)), dim3(256), 0, st>>>(
-        reinterpret_cast<const stt*>(H), N, d, d, ht, w.ldzt, rows, n_act);
+        reinterpret_cast<const stt*>(H), d, d, ht, rows, n_act);
     HIP_TRY(hipGetLastError());
     if (c == 0) PHASE_EVENT(1);
 
