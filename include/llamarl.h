@@ -180,6 +180,17 @@ llamarl_status llamarl_offpolicy_loss_bwd(const void* H, const void* W, const in
                                           int accumulate_dW, void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * llamarl_offpolicy_loss_bwd with the upstream scalar on the device: grad_loss points to one float that is read when the
+ * kernels run, so a caller whose scalar is itself a result on `stream` need not wait for it.  A non-finite value cannot be
+ * refused here (dz is what it makes of it): the caller checks its own copy.
+ */
+llamarl_status llamarl_offpolicy_loss_bwd_device_scale(const void* H, const void* W, const int32_t* targets,
+                                                       const float* lse, const float* coef, const float* grad_loss,
+                                                       int64_t N, int64_t d, int64_t V, llamarl_dtype dt, void* dH,
+                                                       void* dW, llamarl_dtype dW_dt, int accumulate_dW, void* ws,
+                                                       size_t ws_bytes, void* stream);
+
+/*
  * llamarl_offpolicy_loss_bwd with a bounded workspace.  The backward stages dz for the rows it works on; by default
  * that is every row of the batch (workspace ~ 2 * V * N bytes for bf16).  With max_rows_per_pass = R > 0 (rounded up
  * to a multiple of 256) it takes the active rows (coef != 0) R at a time: the workspace holds dz for R rows only,

@@ -23,7 +23,8 @@ EXPORTS = ("llamarl_workspace_bytes", "llamarl_last_error", "llamarl_version", "
            "llamarl_offpolicy_loss_fwd", "llamarl_offpolicy_loss_bwd", "llamarl_offpolicy_loss_bwd_phases",
            "llamarl_group_advantages", "llamarl_kl_shaped_rewards", "llamarl_mfma_ceiling", "llamarl_mfma_ceiling_traffic",
            "llamarl_offpolicy_loss_fwd_static", "llamarl_token_logprobs_partial", "llamarl_merge_partials",
-           "llamarl_offpolicy_loss_bwd_slice", "llamarl_bwd_workspace_bytes", "llamarl_offpolicy_loss_bwd_chunked")
+           "llamarl_offpolicy_loss_bwd_slice", "llamarl_bwd_workspace_bytes", "llamarl_offpolicy_loss_bwd_chunked",
+           "llamarl_offpolicy_loss_bwd_device_scale")
 
 
 class LlamarlError(RuntimeError):
@@ -65,6 +66,9 @@ def load():
                                                       ctypes.POINTER(LossParams), vp, vp, vp, vp]
     lib.llamarl_offpolicy_loss_bwd.restype = ci
     lib.llamarl_offpolicy_loss_bwd.argtypes = [vp, vp, vp, vp, vp, cf, i64, i64, i64, ci, vp, vp, ci, ci, vp, sz, vp]
+    lib.llamarl_offpolicy_loss_bwd_device_scale.restype = ci
+    lib.llamarl_offpolicy_loss_bwd_device_scale.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i64, ci, vp, vp, ci, ci, vp,
+                                                            sz, vp]
     lib.llamarl_offpolicy_loss_bwd_phases.restype = ci
     lib.llamarl_offpolicy_loss_bwd_phases.argtypes = [vp, vp, vp, vp, vp, cf, i64, i64, i64, ci, vp, vp, ci, ci, vp, sz,
                                                       vp, ctypes.POINTER(vp)]
@@ -98,13 +102,13 @@ def _check(status):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is None:      # the handle itself: building a torch Stream object for it costs 3 us a call
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _dtype_code(t):
@@ -244,6 +248,26 @@ def offpolicy_loss_bwd(H, W, targets, lse, coef, grad_loss=1.0, dW_dtype=None, d
     else:
         ev = (ctypes.c_void_p * 6)(*[ctypes.c_void_p(int(e)) for e in phase_events])
         _check(lib.llamarl_offpolicy_loss_bwd_phases(*args, ev))
+    return dH, dW
+
+
+def offpolicy_loss_bwd_device_scale(H, W, targets, lse, coef, grad_loss, dW_dtype=None, stream=None):
+    """llamarl_offpolicy_loss_bwd_device_scale: offpolicy_loss_bwd with grad_loss a one-element float32 device tensor,
+    read on the device and not checked for being finite."""
+    lib = load()
+    dt = _dtype_code(H)
+    _need(H, H.dtype, "H"); _need(W, H.dtype, "W"); _need(targets, torch.int32, "targets")
+    _need(lse, torch.float32, "lse"); _need(coef, torch.float32, "coef"); _need(grad_loss, torch.float32, "grad_loss")
+    if grad_loss.numel() != 1:
+        raise LlamarlError(ERR_INVALID_ARG, "grad_loss must have one entry")
+    N, d = H.shape
+    V = W.shape[0]
+    dH = torch.empty(N, d, dtype=H.dtype, device=H.device)
+    dW = torch.empty(V, d, dtype=dW_dtype or H.dtype, device=H.device)
+    ws = _workspace(workspace_bytes(N, d, V, dt, PASS_LOSS_BWD), H.device, None)
+    _check(lib.llamarl_offpolicy_loss_bwd_device_scale(
+        _ptr(H), _ptr(W), _ptr(targets), _ptr(lse), _ptr(coef), _ptr(grad_loss), N, d, V, dt, _ptr(dH), _ptr(dW),
+        _dtype_code(dW), 0, _ptr(ws), ws.numel(), _stream(stream)))
     return dH, dW
 
 

@@ -443,6 +443,7 @@ struct DzArgs {
   const float* lse;
   const float* coef;
   float g;
+  const float* g_device;  // non-null: the upstream scalar is *g_device instead of g
   int64_t N, d, V;
   int64_t v_off;          // vocabulary index of row 0 of W (0 unless W is a shard's slice); lse is always global
   int tiles_v, tiles_t;
@@ -463,6 +464,7 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzAr
   TileSchedule sch;
   sch.init(a.tiles_v, (n_act + BN - 1) / BN, PATCH_ROWS_LOGITS);
   if (!sch.has_tile()) return;                       // block-uniform: no active token at all
+  const float upstream = a.g_device != nullptr ? *a.g_device : a.g;
   // token columns are fetched quad-interleaved (a lane's four column blocks are neighbouring tokens), so the
   // vocab-major dz^T leaves straight from registers, 8 (bf16) or 16 bytes per lane and whole lines per 16 lanes.
   G g;
@@ -512,7 +514,7 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzAr
     for (int j = 0; j < NB; ++j) {
       const int tok = lp.col_quad() + j;
       const bool in = tok < rowsT;
-      const float c = in ? a.g * tcoef[j] : 0.f;
+      const float c = in ? upstream * tcoef[j] : 0.f;
       const float lb = (c != 0.f) ? tlse[j] * LOG2E : 0.f;
       const int yrel = (in ? ttgt[j] - (int)a.v_off : -1) - (int)v0 - lane_row0;   // far out of range: another shard's
       const bool live = c != 0.f;                            // select: a masked token's row is exactly 0

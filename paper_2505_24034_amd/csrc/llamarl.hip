@@ -349,8 +349,8 @@ __global__ void k_pass_counts(const int32_t* n_act, int64_t R, int n_pass, int32
 
 template <typename TT>
 llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, const float* lse, const float* coef,
-                       float g, int64_t N, int64_t d, int64_t V, int64_t v_off, llamarl_dtype dt, void* dH, void* dW,
-                       llamarl_dtype dW_dt, int accumulate_dW, int64_t max_rows_per_pass, char* ws, hipStream_t st,
+                       float g, const float* g_device, int64_t N, int64_t d, int64_t V, int64_t v_off,
+                       llamarl_dtype dt, void* dH, void* dW, llamarl_dtype dW_dt, int accumulate_dW, int64_t max_rows_per_pass, char* ws, hipStream_t st,
                        void* const* ev) {
   typedef typename TT::store_t stt;
   const BwdWs w = bwd_ws(N, d, V, dt, max_rows_per_pass);
@@ -397,7 +397,7 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
 
     // recompute logits tile by tile, turn them into dz (rows / columns = list positions of the pass)
     DzArgs a;
-    a.H = H; a.W = W; a.targets = targets; a.lse = lse; a.coef = coef; a.g = g; a.N = N; a.d = d; a.V = V;
+    a.H = H; a.W = W; a.targets = targets; a.lse = lse; a.coef = coef; a.g = g; a.g_device = g_device; a.N = N; a.d = d; a.V = V;
     a.v_off = v_off;
     a.dz = dz; a.ldz = w.ldz; a.dzt = dzt; a.rows = rows; a.n_act = n_act;
     const Tile logits = logits_tile(Rc, V, dt);
@@ -630,8 +630,8 @@ llamarl_status llamarl_offpolicy_loss_fwd_static(const float* logp, const float*
 }
 
 static llamarl_status bwd_entry(const void* H, const void* W, const int32_t* targets, const float* lse,
-                                const float* coef, float grad_loss, int64_t N, int64_t d, int64_t V, int64_t v_off,
-                                llamarl_dtype dt, void* dH, void* dW, llamarl_dtype dW_dt, int accumulate_dW,
+                                const float* coef, float grad_loss, const float* grad_loss_device, int64_t N,
+                                int64_t d, int64_t V, int64_t v_off, llamarl_dtype dt, void* dH, void* dW, llamarl_dtype dW_dt, int accumulate_dW,
                                 int64_t max_rows_per_pass, void* ws, size_t ws_bytes, void* stream, void* const* ev) {
   if (!H || !W || !targets || !lse || !coef || !dH || !dW) return fail(LLAMARL_ERR_INVALID_ARG, "null pointer argument");
   llamarl_status s = check_head_shape(N, d, V, dt);
@@ -649,10 +649,10 @@ static llamarl_status bwd_entry(const void* H, const void* W, const int32_t* tar
   if (!aligned16(ws)) return fail(LLAMARL_ERR_INVALID_ARG, "workspace must be 16-byte aligned");
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (dt == LLAMARL_BF16)
-    return run_bwd<BF16>(H, W, targets, lse, coef, grad_loss, N, d, V, v_off, dt, dH, dW, dW_dt, accumulate_dW,
+    return run_bwd<BF16>(H, W, targets, lse, coef, grad_loss, grad_loss_device, N, d, V, v_off, dt, dH, dW, dW_dt, accumulate_dW,
                          max_rows_per_pass,
                          reinterpret_cast<char*>(ws), st, ev);
-  return run_bwd<F32>(H, W, targets, lse, coef, grad_loss, N, d, V, v_off, dt, dH, dW, dW_dt, accumulate_dW,
+  return run_bwd<F32>(H, W, targets, lse, coef, grad_loss, grad_loss_device, N, d, V, v_off, dt, dH, dW, dW_dt, accumulate_dW,
                       max_rows_per_pass,
                       reinterpret_cast<char*>(ws), st, ev);
 }
@@ -661,8 +661,19 @@ llamarl_status llamarl_offpolicy_loss_bwd(const void* H, const void* W, const in
                                           const float* coef, float grad_loss, int64_t N, int64_t d, int64_t V,
                                           llamarl_dtype dt, void* dH, void* dW, llamarl_dtype dW_dt,
                                           int accumulate_dW, void* ws, size_t ws_bytes, void* stream) {
-  return bwd_entry(H, W, targets, lse, coef, grad_loss, N, d, V, 0, dt, dH, dW, dW_dt, accumulate_dW, 0, ws, ws_bytes,
+  return bwd_entry(H, W, targets, lse, coef, grad_loss, nullptr, N, d, V, 0, dt, dH, dW, dW_dt, accumulate_dW, 0, ws, ws_bytes,
                    stream, nullptr);
+}
+
+llamarl_status llamarl_offpolicy_loss_bwd_device_scale(const void* H, const void* W, const int32_t* targets,
+                                                       const float* lse, const float* coef, const float* grad_loss,
+                                                       int64_t N, int64_t d, int64_t V, llamarl_dtype dt, void* dH,
+                                                       void* dW, llamarl_dtype dW_dt, int accumulate_dW, void* ws,
+                                                       size_t ws_bytes, void* stream) {
+  if (!grad_loss || (reinterpret_cast<uintptr_t>(grad_loss) & 3u) != 0)
+    return fail(LLAMARL_ERR_INVALID_ARG, "grad_loss must be a 4-byte aligned device pointer");
+  return bwd_entry(H, W, targets, lse, coef, 1.f, grad_loss, N, d, V, 0, dt, dH, dW, dW_dt, accumulate_dW, 0, ws,
+                   ws_bytes, stream, nullptr);
 }
 
 size_t llamarl_bwd_workspace_bytes(int64_t N, int64_t d, int64_t V, llamarl_dtype dt, int64_t max_rows_per_pass) {
@@ -675,7 +686,7 @@ llamarl_status llamarl_offpolicy_loss_bwd_chunked(const void* H, const void* W, 
                                                   int64_t d, int64_t V, llamarl_dtype dt, void* dH, void* dW,
                                                   llamarl_dtype dW_dt, int accumulate_dW, int64_t max_rows_per_pass,
                                                   void* ws, size_t ws_bytes, void* stream) {
-  return bwd_entry(H, W, targets, lse, coef, grad_loss, N, d, V, 0, dt, dH, dW, dW_dt, accumulate_dW, max_rows_per_pass,
+  return bwd_entry(H, W, targets, lse, coef, grad_loss, nullptr, N, d, V, 0, dt, dH, dW, dW_dt, accumulate_dW, max_rows_per_pass,
                    ws, ws_bytes, stream, nullptr);
 }
 
@@ -684,7 +695,7 @@ llamarl_status llamarl_offpolicy_loss_bwd_slice(const void* H, const void* W_sli
                                                 int64_t d, int64_t V_slice, int64_t v0, llamarl_dtype dt,
                                                 void* dH_partial, void* dW_slice, llamarl_dtype dW_dt,
                                                 int accumulate_dW, void* ws, size_t ws_bytes, void* stream) {
-  return bwd_entry(H, W_slice, targets, lse, coef, grad_loss, N, d, V_slice, v0, dt, dH_partial, dW_slice, dW_dt,
+  return bwd_entry(H, W_slice, targets, lse, coef, grad_loss, nullptr, N, d, V_slice, v0, dt, dH_partial, dW_slice, dW_dt,
                    accumulate_dW, 0, ws, ws_bytes, stream, nullptr);
 }
 
@@ -696,7 +707,7 @@ llamarl_status llamarl_offpolicy_loss_bwd_phases(const void* H, const void* W, c
   if (!phase_events) return fail(LLAMARL_ERR_INVALID_ARG, "phase_events is null");
   for (int i = 0; i < 6; ++i)
     if (!phase_events[i]) return fail(LLAMARL_ERR_INVALID_ARG, "phase_events[%d] is null", i);
-  return bwd_entry(H, W, targets, lse, coef, grad_loss, N, d, V, 0, dt, dH, dW, dW_dt, accumulate_dW, 0, ws, ws_bytes,
+  return bwd_entry(H, W, targets, lse, coef, grad_loss, nullptr, N, d, V, 0, dt, dH, dW, dW_dt, accumulate_dW, 0, ws, ws_bytes,
                    stream, phase_events);
 }
 

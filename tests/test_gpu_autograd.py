@@ -26,3 +26,31 @@ def test_backward_through_the_wrapper_matches_the_oracle(lib, name, d, V, B, T):
     check_grad("H.grad", f64(H.grad), ref["dH"], base.dtype)
     check_grad("W.grad", f64(W.grad), ref["dW"], base.dtype)
     assert H.grad.dtype == H.dtype and W.grad.dtype == W.dtype
+
+
+@pytest.mark.parametrize("name", ["llama3_8b", "tiny_fp32"])
+@pytest.mark.parametrize("scale", [1.0, -2.5, 0.0, 1e-3])
+def test_upstream_scalar_on_the_device(lib, name, scale):
+    """the scale read on the device gives the bits of the scale passed from the host, through autograd as well; a
+    non-finite one is refused and leaves no gradient"""
+    from paper_2505_24034_amd.autograd import aipo_loss
+    w = synth.scaled(synth.WORKLOADS[name], d=128, V=700, B=2, T=90, len_lo=20, len_hi=90, seed=78)
+    x = synth.make_inputs(w, "cuda")
+    H, W = x["H"].clone().requires_grad_(True), x["W"].clone().requires_grad_(True)
+
+    def loss():
+        return aipo_loss(H, W, x["targets"], x["mu_logp"], x["adv"], x["mask"], rho=1.1)[0]
+
+    logp, lse = lib.token_logprobs(x["H"], x["W"], x["targets"], x["mask"].reshape(-1))
+    _, coef, _ = lib.offpolicy_loss_fwd(logp, x["mu_logp"], x["adv"], x["mask"], 2, 90, rho=1.1, targets=x["targets"], V=700)
+    dH, dW = lib.offpolicy_loss_bwd(x["H"], x["W"], x["targets"], lse, coef, grad_loss=scale)
+    s = torch.tensor(scale, device="cuda")
+    dH2, dW2 = lib.offpolicy_loss_bwd_device_scale(x["H"], x["W"], x["targets"], lse, coef, s)
+    assert torch.equal(dH, dH2) and torch.equal(dW, dW2)
+    loss().backward(gradient=s)
+    assert torch.equal(H.grad, dH) and torch.equal(W.grad, dW)
+    H.grad = W.grad = None
+    for bad in (float("nan"), float("inf")):
+        with pytest.raises(lib.LlamarlError):
+            loss().backward(gradient=torch.tensor(bad, device="cuda"))
+        assert H.grad is None and W.grad is None
