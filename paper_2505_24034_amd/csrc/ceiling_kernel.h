@@ -101,7 +101,7 @@ __device__ __forceinline__ void ceiling_k_step(bf16x8_t (&a)[MB], const bf16x8_t
 __device__ __forceinline__ void ceiling_traffic_loop(int iters, float* sink, const void* panels, char* smem,
                                                      const bool READS, const bool LOADS) {
   const int lane = threadIdx.x & 63, wave = wave_id();
-  const int wm = wave / Shape256::WAVES_N, wn = wave % Shape256::WAVES_N;
+  const int wm = Shape256::wave_row(wave), wn = Shape256::wave_col(wave);
   SlabLoader<BF16> la, lb;
   la.init(panels, CEILING_PANEL_K, Shape256::BM, wave, lane);
   lb.init(reinterpret_cast<const char*>(panels) + (size_t)Shape256::BM * CEILING_PANEL_K * 2, CEILING_PANEL_K, Shape256::BN, wave, lane);

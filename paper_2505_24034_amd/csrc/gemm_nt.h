@@ -39,16 +39,22 @@ constexpr int SLAB_ROW_BYTES = 128;
 constexpr int BLOCK_BYTES = 16 * SLAB_ROW_BYTES;                  // 16 slab rows: one MFMA block of an operand
 constexpr uint32_t OOB_OFFSET = 0x80000000u;                      // beyond any descriptor range used here
 
-// A workgroup's output tile: WM x WN wavefronts, each MB_ x NB MFMA blocks.
-template <int WM, int WN, int MB_>
+// A workgroup's output tile: WM x WN wavefronts, each MB_ x NB MFMA blocks.  Wavefront w runs on SIMD w % 4.  By default
+// wavefronts are numbered along the columns, so the four of an upper half (WM = 2) sit on four SIMDs; COLUMN_MAJOR
+// numbers them along the rows, so the four of a left half (WN = 4) do: whichever edge of the matrix is ragged, the
+// wavefronts that have nothing to do there (see run_idle) then leave every SIMD one that has.
+template <int WM, int WN, int MB_, bool COLUMN_MAJOR = false>
 struct TileShape {
+  __device__ __forceinline__ static int wave_row(int wave) { return COLUMN_MAJOR ? wave % WM : wave / WN; }
+  __device__ __forceinline__ static int wave_col(int wave) { return COLUMN_MAJOR ? wave / WM : wave % WN; }
   static constexpr int WAVES_M = WM, WAVES_N = WN, WAVES = WM * WN, THREADS = 64 * WM * WN;
   static constexpr int MB = MB_, WAVE_M = MB_ * 16;
   static constexpr int BM = WM * WAVE_M, BN = WN * WAVE_N;        // tile rows (A rows), tile columns (B rows)
   static constexpr int SLAB_A_BYTES = BM * SLAB_ROW_BYTES;
   static constexpr int STAGE_BYTES = (BM + BN) * SLAB_ROW_BYTES;  // one K slab of both operands
 };
-typedef TileShape<2, 4, 8> Shape256;   // 256 x 256, 8 wavefronts of 128 x 64
+typedef TileShape<2, 4, 8, true> Shape256;   // 256 x 256, 8 wavefronts of 128 x 64
+typedef TileShape<2, 4, 8> Shape256Rows;     // the same, for outputs with a ragged last row of tiles
 typedef TileShape<2, 2, 4> Shape128;   // 128 x 128, 4 wavefronts of  64 x 64
 typedef TileShape<4, 1, 1> Shape64;    //  64 x  64, 4 wavefronts of  16 x 64
 
@@ -100,7 +106,7 @@ template <typename S>
 struct LanePos {
   int wm, wn, lane;
   __device__ __forceinline__ explicit LanePos(int tid)
-      : wm((tid >> 6) / S::WAVES_N), wn((tid >> 6) % S::WAVES_N), lane(tid & 63) {}
+      : wm(S::wave_row(tid >> 6)), wn(S::wave_col(tid >> 6)), lane(tid & 63) {}
   __device__ __forceinline__ int row(int ib, int r) const { return wm * S::WAVE_M + ib * 16 + (lane >> 4) * 4 + r; }
   __device__ __forceinline__ int col(int jb) const { return wn * WAVE_N + jb * 16 + (lane & 15); }
   // Quad-interleaved columns (see tile_row_of): the lane's four column blocks hold NEIGHBOURING columns
@@ -167,6 +173,11 @@ struct TileSchedule {
     const int in_g = id - g * per_group;
     tm = first_m + in_g % gsize;
     tn = in_g / gsize;
+    // Where a round of the grid is a whole number of groups, a workgroup would get the same column in every round:
+    // turn the columns by one a round, so that nobody is left with all the narrow last columns (two columns, 300
+    // tokens: half of the workgroups had four full tiles, the other half four of 44 tokens).
+    const int nblk = gridDim.x;
+    if (nblk % per_group == 0) tn = (tn + id / nblk) % tiles_n;
   }
 };
 
@@ -360,6 +371,7 @@ struct TileGemm {
   typedef Shape256 Shape;
   typedef typename TT::frag_t frag_t;
   static constexpr bool KMAJOR = false;
+  static constexpr bool HAS_IDLE = true;
   static constexpr int BK = 8 * TT::EPC;
   static constexpr int LDS_BYTES = MAINLOOP_LDS_BYTES;
   static constexpr int GROUPS_PER_CU = 1;      // workgroups of a persistent grid per CU
@@ -400,9 +412,31 @@ struct TileGemm {
     }
   }
 
+  // Instead of run() for a wavefront whose whole part of the tile lies past the matrix (wave-uniform; a last column of
+  // few tokens): its loads and barriers, nothing else.  The SIMD then belongs to the other wavefront.  The forward over
+  // a 128256 x 4096 head: 64 tokens 284 -> 259 us, 300 413 -> 382, 1100 986 -> 939.  Not used by the recompute, whose
+  // epilogue leaves no registers for the branch (4 spilled: +0.8 % at 8576 tokens for -2 % at 300).
+  __device__ __forceinline__ void run_idle(char* smem) const {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int nk = (K + BK - 1) / BK;
+    wait_vmcnt0();
+    __syncthreads();
+    for (int kt = 0; kt < nk - 2; ++kt) {
+      char* cur = smem + (kt & 1) * STAGE_BYTES;
+      wait_vmcnt0();
+      __syncthreads();
+      la.issue(cur, (kt + 2) * BK, K, wave, lane);
+      lb.issue(cur + SLAB_A_BYTES, (kt + 2) * BK, K, wave, lane);
+    }
+    if (nk >= 2) {
+      wait_vmcnt0();
+      __syncthreads();
+    }
+  }
+
   __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[MB][NB]) {
     const int lane = threadIdx.x & 63, wave = wave_id();
-    const int wm = wave / Shape::WAVES_N, wn = wave % Shape::WAVES_N;
+    const int wm = Shape::wave_row(wave), wn = Shape::wave_col(wave);
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll

@@ -64,6 +64,7 @@ struct TileGemmSmall {
   typedef SlabLoader<TT, S::BM, S::WAVES> LoaderA;
   typedef SlabLoader<TT, S::BN, S::WAVES> LoaderB;
   static constexpr bool KMAJOR = false;
+  static constexpr bool HAS_IDLE = false;
   static constexpr int BK = 8 * TT::EPC;
   static constexpr int LDS_BYTES = NSTAGE * S::STAGE_BYTES + 16;     // + a flag (fp32: redo this tile)
   static constexpr int GROUPS_PER_CU = GROUPS_PER_CU_;
@@ -170,7 +171,7 @@ struct TileGemmSmall {
   __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[S::MB][NB]) {
     constexpr bool SPLIT = sizeof(typename TT::store_t) == 4;
     const int lane = threadIdx.x & 63, wave = wave_id();
-    const int wm = wave / S::WAVES_N, wn = wave % S::WAVES_N;
+    const int wm = S::wave_row(wave), wn = S::wave_col(wave);
     const int g = lane >> 4, l16 = lane & 15, sw = swizzle(l16);
     int a_addr[2], b_addr[2];
 #pragma unroll

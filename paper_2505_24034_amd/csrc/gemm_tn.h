@@ -78,9 +78,10 @@ struct KMajorLoader {
 
 struct TileGemmTN {
   typedef BF16 Type;
-  typedef Shape256 Shape;
+  typedef Shape256Rows Shape;
   typedef bf16x8_t frag_t;
   static constexpr bool KMAJOR = true;
+  static constexpr bool HAS_IDLE = true;
   static constexpr int LDS_BYTES = MAINLOOP_LDS_BYTES;
   static constexpr int GROUPS_PER_CU = 1;
   KMajorLoader la, lb;
@@ -173,9 +174,29 @@ struct TileGemmTN {
     }
   }
 
+  // as TileGemm::run_idle, for wavefronts past the last row.  dH over a 128256 x 4096 head: 300 tokens 414 -> 385 us,
+  // 1100 1030 -> 994, 8576 (half a last tile of 34) within noise.
+  __device__ __forceinline__ void run_idle(char* smem) const {
+    const int wave = wave_id();
+    const int nk = (k_len + 63) / 64;
+    wait_vmcnt0();
+    __syncthreads();
+    for (int kt = 0; kt < nk - 2; ++kt) {
+      char* cur = smem + (kt & 1) * STAGE_BYTES;
+      wait_vmcnt0();
+      __syncthreads();
+      la.issue(cur, kt + 2, k_len, wave);
+      lb.issue(cur + SLAB_A_BYTES, kt + 2, k_len, wave);
+    }
+    if (nk >= 2) {
+      wait_vmcnt0();
+      __syncthreads();
+    }
+  }
+
   __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[MB][NB]) {
     const int lane = threadIdx.x & 63, wave = wave_id();
-    const int wm = wave / Shape::WAVES_N, wn = wave % Shape::WAVES_N;
+    const int wm = Shape::wave_row(wave), wn = Shape::wave_col(wave);
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -282,6 +303,7 @@ struct TileGemmTNSmall {
   typedef KMajorLoaderSmall<S::BM, S::WAVES> LoaderA;
   typedef KMajorLoaderSmall<S::BN, S::WAVES> LoaderB;
   static constexpr bool KMAJOR = true;
+  static constexpr bool HAS_IDLE = false;
   static constexpr int LDS_BYTES = NSTAGE * S::STAGE_BYTES;
   static constexpr int GROUPS_PER_CU = GROUPS_PER_CU_;
   static constexpr int LOADS = LoaderA::ITERS + LoaderB::ITERS;
@@ -319,7 +341,7 @@ struct TileGemmTNSmall {
 
   __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[S::MB][NB]) {
     const int lane = threadIdx.x & 63, wave = wave_id();
-    const int wm = wave / S::WAVES_N, wn = wave % S::WAVES_N;
+    const int wm = S::wave_row(wave), wn = S::wave_col(wave);
     // lane -> k-row and 8-byte piece it loads for the transposing reads: see TileGemmTN::run
     const int g = lane >> 4, jrow = (lane >> 2) & 3, q4 = lane & 3, krow = 8 * g + jrow;
     int a_off[S::MB], b_off[NB];

@@ -83,6 +83,29 @@ struct FwdArgs {
   const int32_t* n_act;   // device scalar
 };  // partials and zt are indexed by compacted position, not by token
 
+// One tile's main loop; a wavefront with no part in the tile only takes part in its loads (256 x 256 loops).
+template <typename G>
+__device__ __forceinline__ void run_or_idle(G& g, char* smem, f32x4_t (&acc)[G::Shape::MB][NB], bool idle) {
+  if constexpr (G::HAS_IDLE) {
+    if (idle) {                                      // wave-uniform
+#pragma unroll
+      for (int i = 0; i < G::Shape::MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      g.run_idle(smem);
+      return;
+    }
+  }
+  g.run(smem, acc);
+}
+
+// token columns of tile `id` that hold active rows
+template <typename G>
+__device__ __forceinline__ int columns_left(const TileSchedule& sch, int id, int n_act) {
+  int tv, tt;
+  sch.coords(id, tv, tt);
+  return n_act - tt * G::Shape::BN;
+}
 // The logits kernels gather their column operand (H rows) through the active-row list.  The list entries a lane
 // needs for a tile are loaded in ONE batch, branch-free (indices clamped into the list), before the barrier that
 // ends the previous tile; the compiler otherwise serialises them, each behind its own s_waitcnt, and puts them
@@ -135,7 +158,7 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
   logits_fetch<false>(g, sch, a, id, n_act, grow, smem);
   while (true) {
     f32x4_t acc[MB][NB];
-    g.run(smem, acc);
+    run_or_idle(g, smem, acc, G::Shape::wave_col(wave_id()) * WAVE_N >= columns_left<G>(sch, id, n_act));
     // The lane's position is rebuilt from an opaque copy of the thread id after every main loop: otherwise all the
     // per-lane constants of the epilogue stay live through the loop, are spilled, and every reload waits (vmcnt) for
     // the slab requests of the next tile as well.
@@ -802,7 +825,10 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
     f32x4_t acc[MB][NB];
     const int cur_id = id;
     if (store_tile_of<G>(plan, a, cur_id, M, K).k_len > 0) {
-      g.run(smem, acc);
+      if constexpr (KMAJOR)
+        run_or_idle(g, smem, acc, S::wave_row(wave_id()) * S::WAVE_M >= store_tile_of<G>(plan, a, cur_id, M, K).rowsA);
+      else
+        g.run(smem, acc);
     } else {                                         // nothing to contract: the product is zero
 #pragma unroll
       for (int i = 0; i < MB; ++i)

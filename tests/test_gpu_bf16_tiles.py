@@ -35,3 +35,20 @@ def test_tile_edges(lib, N, V, d, masked):
     total = dW32.clone()
     lib.offpolicy_loss_bwd(H, W, t, lse, coef, dW=total, accumulate_dW=True)
     assert torch.equal(total, 2 * dW32)
+
+
+@pytest.mark.parametrize("N", [1, 64, 127, 128, 129, 255, 256, 257, 320, 384, 385, 640])
+@pytest.mark.parametrize("d", [64, 136, 264])                   # 1, 3 and 5 slabs
+def test_narrow_last_token_column(lib, N, d):
+    # 192 or more tiles of 256 x 256 at every N: the last column holds 1 .. 256 tokens, half of the wavefronts idle up to 128
+    V = 49200
+    H, W, t, coef = _inputs(N, V, d, N + d)
+    H, W = H.bfloat16(), W.bfloat16()
+    t[0] = V - 1
+    logp, lse = lib.token_logprobs(H, W, t)
+    rlogp, rlse, rdH, rdW = _reference(H, W, t, coef)
+    bound = 2.0 ** -24 * d ** 0.5
+    assert float((lse.double() - rlse).abs().max()) <= 8 * bound + 2e-6
+    assert float((logp.double() - rlogp).abs().max()) <= 16 * bound + 2e-6
+    dH, dW = lib.offpolicy_loss_bwd(H, W, t, lse, coef)
+    assert _rel(dH, rdH) <= 2.0 ** -8 and _rel(dW, rdW) <= 2.0 ** -8
