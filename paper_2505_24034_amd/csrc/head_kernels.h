@@ -648,28 +648,37 @@ struct StoreArgs {
 // for every tile, and what trims the last round of dW (8016 tiles on 256 CUs).  The assignment is fixed by the
 // sizes alone: results stay bitwise reproducible.
 constexpr int STORE_TAIL_ROUNDS = 4;      // rounds of split parts at the end of a store contraction, at most
+constexpr int STORE_REDUCE_COST = 3 * 256;    // launch and latency of k_reduce_tail, ~4 us, in 1/256 of a 1.5 us slab
+// A block of BM x BN floats written and read at ~5 TB/s against the time the whole grid takes for a slab: 256 x 256
+// bf16 0.105 of 1.47 us; the 128-tiles' block is a quarter and their slab 0.9 us (bf16) or 2.9 us (fp32).
+template <typename G>
+constexpr int STORE_PART_COST = G::Shape::BM == 256 ? 18 : G::Shape::BM == 128 ? (sizeof(typename G::Type::store_t) == 2 ? 7 : 2) : 1;
 struct StorePlan {
   int tiles_m, tiles_n, group_m;
   int whole, rem, splits, n_items;
   int next, stride;
-  __device__ __forceinline__ void init(int tiles_m_, int tiles_n_, int group_m_, int nk, int max_splits) {
+  // part_cost: what writing one part's fp32 block and reading it back costs, in 1/256 of a slab of the whole grid
+  __device__ __forceinline__ void init(int tiles_m_, int tiles_n_, int group_m_, int nk, int max_splits, int part_cost) {
     tiles_m = tiles_m_;
     tiles_n = tiles_n_;
     group_m = group_m_;
     const int T = tiles_m * tiles_n, G = gridDim.x;
     whole = T / G * G;
     rem = T - whole;
-    // split factor of the tail: the one that makes the tail shortest -- ceil(rem s / G) rounds of 1 / s tile time
-    // each -- among those that keep four K slabs per part and at most STORE_TAIL_ROUNDS rounds of parts (each part
-    // leaves a 256 KB block in the workspace); the smallest such factor on ties
-    int best = 1, best_num = 1, best_den = 1;          // tail time best_num / best_den, in tile times
+    // split factor of the tail: the one that makes the tail shortest -- ceil(rem s / G) rounds of nk / s slabs each, the
+    // traffic of the rem s partial blocks and the reduction's launch -- among those that keep four K slabs per part
+    // and at most STORE_TAIL_ROUNDS rounds of parts; the smallest such factor on ties.  Counting rounds alone cut the
+    // dW of (N, V, d) = (7000, 33001, 1032) into 931 parts (0.5 GB of blocks): 515 us
+    // instead of 487; (3000, 60000, 1504) 545 instead of 485, (4000, 128256, 2560) 2022 instead of 1944.
+    int best = 1;
+    int best_cost = nk * 256;                          // nk < 2^16 (a 256-row panel is < 2 GiB): 32 bits are enough
     for (int sp = 2; sp <= max_splits && rem > 0; ++sp) {
       const int rounds = (rem * sp + G - 1) / G;
       if (nk / sp < 4 || rounds > STORE_TAIL_ROUNDS) break;
-      if (rounds * best_den < best_num * sp) {
+      const int cost = rounds * nk * 256 / sp + rem * sp * part_cost + STORE_REDUCE_COST;
+      if (cost < best_cost) {
         best = sp;
-        best_num = rounds;
-        best_den = sp;
+        best_cost = cost;
       }
     }
     splits = best;
@@ -813,7 +822,7 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
   }
   const int tiles_m = (int)((M + BM - 1) / BM);
   StorePlan plan;
-  plan.init(tiles_m, a.tiles_n, a.group_m, (int)((K + BK - 1) / BK), a.max_splits);
+  plan.init(tiles_m, a.tiles_n, a.group_m, (int)((K + BK - 1) / BK), a.max_splits, STORE_PART_COST<G>);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.plan_out[0] = plan.whole; a.plan_out[1] = plan.rem; a.plan_out[2] = plan.splits; a.plan_out[3] = tiles_m;
   }
