@@ -90,7 +90,12 @@ __device__ __forceinline__ void mma(const f32x4_t& a, const f32x4_t& b, f32x4_t&
   c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], c, 0, 0, 0);
 }
 
-__device__ __forceinline__ void wait_vmcnt0() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {       // at most N vector-memory operations of this wave in flight
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
+}
+
+__device__ __forceinline__ void wait_vmcnt0() { wait_vmcnt<0>(); }
 
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 __device__ __forceinline__ uint16_t float_to_bf16_bits(float f) {  // round to nearest even
@@ -316,7 +321,8 @@ __device__ __forceinline__ constexpr int snake_col(int t) { return ((t >> 2) & 1
 //   LS     : a template parameter although only its value matters: every specialisation of this template must be
 //            called from ONE function instantiation only -- the host pass of hipcc (ROCm 7.2) rejects a second
 //            caller of the same specialisation ("substitution failure", no reason given; the device pass accepts it).
-template <typename TT, bool BAR, bool NEXT, bool FETCH, int LS>
+//   YOUNGER: vector-memory operations issued after the next slab's loads that the barrier need not wait for.
+template <typename TT, bool BAR, bool NEXT, bool FETCH, int LS, int YOUNGER = 0>
 __device__ __forceinline__ void k_step(typename TT::frag_t (&a)[MB], const typename TT::frag_t (&bc)[NB],
                                        typename TT::frag_t (&bn)[NB], f32x4_t (&acc)[MB][NB], const char* pa_cur,
                                        const char* pa_nxt, const char* pb_nxt, const SlabFetch<TT>* sf) {
@@ -327,8 +333,8 @@ __device__ __forceinline__ void k_step(typename TT::frag_t (&a)[MB], const typen
   for (int t = 0; t < MB * NB; ++t) {
     const int ib = t >> 2, jb = snake_col(t);
     if (BAR && t == TB) {
-      wait_vmcnt0();      // this thread's share of the next slab has landed in LDS
-      __syncthreads();    // everyone's has, and everyone is done reading this slab
+      wait_vmcnt<YOUNGER>();      // this thread's share of the next slab has landed in LDS
+      __syncthreads();            // everyone's has, and everyone is done reading this slab
       LLAMARL_FENCE();
     }
     mma(a[ib], bc[jb], acc[ib][jb]);
@@ -434,7 +440,12 @@ struct TileGemm {
     }
   }
 
-  __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[MB][NB]) {
+  // YOUNGER > 0: if `counted` (workgroup-uniform), at least YOUNGER vector-memory operations -- the previous tile's
+  // stores -- were issued after prefetch().  vmcnt counts in order, so slabs 0 and 1 are waited for without them; the
+  // stores then drain under the first slabs.  dW over a 128256 x 4096 head: 64 rows 295 -> 273 us, 300 rows 587 -> 528,
+  // 1100 rows 1183 -> 1124, 8576 rows -0.8 %.  (No gain for the recompute, whose epilogue is longer than its stores.)
+  template <int YOUNGER = 0>
+  __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[MB][NB], bool counted = false) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int wm = Shape::wave_row(wave), wn = Shape::wave_col(wave);
 #pragma unroll
@@ -456,8 +467,9 @@ struct TileGemm {
       b_addr[ks] = SLAB_A_BYTES + (wn * WAVE_N + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
     }
     // Slabs 0 and 1 were issued by prefetch(); stores of a previous epilogue may sit between them and now in the
-    // vmcnt queue, so wait for everything rather than count.
-    wait_vmcnt0();
+    // vmcnt queue.  Where their number is not known, wait for everything.
+    if (YOUNGER > 0 && counted) wait_vmcnt<YOUNGER>();
+    else wait_vmcnt0();
     __syncthreads();
     frag_t a[MB], b0[NB], b1[NB];
     a[0] = *reinterpret_cast<const frag_t*>(smem + a_addr[0]);
@@ -468,7 +480,19 @@ struct TileGemm {
 
     // slabs 0 .. nk-3 fetch slab kt+2 after their barrier; slab nk-2 (nothing left to fetch) and the last slab
     // follow, written out one after the other (a branch inside one loop body makes the compiler copy accumulators)
-    for (int kt = 0; kt < nk - 2; ++kt) {
+    int kt0 = 0;
+    if (YOUNGER > 0 && nk > 2) {       // slab 0 apart: its barrier waits for slab 1, which is older than the stores too
+      char* cur = smem;
+      const char* nxt = smem + STAGE_BYTES;
+      LLAMARL_FENCE();
+      k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, cur + a_addr[0], cur + a_addr[1], cur + b_addr[1],
+                                                nullptr);
+      const SlabFetch<TT> sf{&la, &lb, cur, 2 * BK, K, wave, lane};
+      k_step<TT, true, true, true, LOAD_SLOT, YOUNGER>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0],
+                                                       nxt + b_addr[0], &sf);
+      kt0 = 1;
+    }
+    for (int kt = kt0; kt < nk - 2; ++kt) {
       char* cur = smem + (kt & 1) * STAGE_BYTES;
       const char* nxt = smem + ((kt + 1) & 1) * STAGE_BYTES;
       LLAMARL_FENCE();

@@ -32,11 +32,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {   // v_cvt_p
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {       // at most N vector-memory operations of this wave in flight
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
-}
-
 struct Split3 {
   bf16x8_t h, m, l;
 };

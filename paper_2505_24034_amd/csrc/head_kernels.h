@@ -22,6 +22,8 @@
 #include "gemm_small.h"
 #include "gemm_tn.h"
 
+#include <type_traits>
+
 namespace llamarl {
 
 constexpr float LOG2E = 1.4426950408889634f;
@@ -830,12 +832,17 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
   G g;
   int id = plan.take();
   store_fetch(g, plan, a, id, M, K, smem);
+  // The K-contiguous epilogue stores one unit per row of a lane: STORES_OF_A_TILE, unless the tile is ragged.
+  constexpr int STORES_OF_A_TILE = MB * 4;
+  bool counted = false;
   while (true) {
     f32x4_t acc[MB][NB];
     const int cur_id = id;
     if (store_tile_of<G>(plan, a, cur_id, M, K).k_len > 0) {
       if constexpr (KMAJOR)
         run_or_idle(g, smem, acc, S::wave_row(wave_id()) * S::WAVE_M >= store_tile_of<G>(plan, a, cur_id, M, K).rowsA);
+      else if constexpr (std::is_same<G, TileGemm<BF16, STORE_LOAD_SLOT>>::value)
+        g.template run<STORES_OF_A_TILE>(smem, acc, counted);
       else
         g.run(smem, acc);
     } else {                                         // nothing to contract: the product is zero
@@ -856,6 +863,7 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
     LLAMARL_FENCE();
 
     const StoreTile<G> cur = store_tile_of<G>(plan, a, cur_id, M, K);
+    counted = cur.nsplit > 1 || (cur.rowsA == BM && cur.rowsB == BN);    // no store of a lane is left out
     int tid = threadIdx.x;                           // opaque per tile: see k_fwd_partials (a spilled per-lane constant
     asm volatile("" : "+v"(tid));                    // reloaded here would wait for the slab requests above)
     const LanePos<S> lp(tid);

@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
     (256, 8065, 64), (383, 5300, 136), (500, 24000, 72),                               # 128-tiles
     (300, 24577, 64), (257, 33001, 128), (400, 32700, 136),                            # 256-tiles, K of 1, 2, 3 slabs
     (40, 33000, 1032), (70, 33000, 1032), (130, 33000, 520),                           # dW on 256-tiles, K of 1, 2, 3 slabs
+    (200, 32768, 1024), (330, 33000, 1024),                                            # full dW tiles, K of 4 and 6 slabs
     (260, 16384, 520), (520, 16400, 2056),                                             # dH on 128- and 256-tiles, split along K
 ])
 @pytest.mark.parametrize("masked", [False, True])
