@@ -7,6 +7,8 @@
 // one fp32 addition.  hh is summed apart from the five small terms, whose rounding errors are 2^-8 smaller, so 32 k
 // cost the main accumulator one rounding where eight 16x16x4 fp32 MFMAs cost it eight.  Six 16x16x32 bf16 MFMAs
 // take less than half the time of those eight.
+//   - bf16 has fp32's exponents: only below 2^-109 does a value run out of bits for l (subnormals are not flushed), and
+//     then by at most 2^-134.
 //   - Infinities, NaN and values that round to infinity in bf16 cannot be split (inf - inf): they make the
 //     accumulator non-finite, and so does an honest overflow.  A tile with any non-finite sum is contracted again with
 //     fp32 MFMAs, whose results it keeps.

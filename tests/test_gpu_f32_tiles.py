@@ -73,3 +73,18 @@ def test_values_that_cannot_be_split(lib, N, V, d):
     assert not bool(torch.isfinite(lse2[17])) and bool(torch.isnan(logp2[17]))
     ok = torch.arange(N, device="cuda") != 17
     assert float((lse2[ok].double() - rlse[ok]).abs().max()) <= 2e-5
+
+
+@pytest.mark.parametrize("N,V,d", [(100, 300, 64), (400, 9000, 64)])      # 64- and 128-tiles
+@pytest.mark.parametrize("shift", [-100, -60, 60, 100])
+def test_scaling_by_a_power_of_two_changes_no_bit(lib, N, V, d, shift):
+    # all three parts of a value of 2^-103 .. 2^-99 are bf16 numbers (the smallest is 2^-133): nothing may be lost there
+    H, W, t, _ = _inputs(N, V, d, 9)
+    a = lib.token_logprobs(H, W, t)
+    b = lib.token_logprobs(H * 2.0 ** -shift, W * 2.0 ** shift, t)
+    W_exact = torch.where(W.abs() * 2.0 ** shift < 2.0 ** -109, torch.zeros_like(W), W) if shift < 0 else W
+    H_exact = torch.where(H.abs() * 2.0 ** -shift < 2.0 ** -109, torch.zeros_like(H), H) if shift > 0 else H
+    if torch.equal(W_exact, W) and torch.equal(H_exact, H):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    else:       # a value below 2^-109 loses at most 2^-134, times a partner below 8 x 2^100: nothing beside a sum's rounding
+        assert float((a[0] - b[0]).abs().max()) <= 1e-6
