@@ -256,10 +256,10 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
 }
 
 // lse[t] = log sum over vocab tiles; logp[t] = z[t,y_t] - lse[t], for the active tokens (the compaction pass
-// already wrote 0 for masked / bad-target rows).  HBM-bound (8 bytes per token and vocab tile): a block of 1024
-// threads takes 32 list positions x 32 slices of the vocab tiles, so a row of 32 lanes reads one 128-byte line and
-// there are enough loads in flight to stream.
-constexpr int MERGE_TOKENS = 32, MERGE_SLICES = 32, MERGE_BATCH = 8;
+// already wrote 0 for masked / bad-target rows).  8 bytes per token and vocab tile.  A block of 1024 threads takes
+// TOKENS list positions x 1024 / TOKENS slices of the vocab tiles: 32 tokens read whole 128-byte lines and stream; where
+// that leaves most CUs without a block (few tokens) 8 tokens and 128 slices shorten the chain instead.
+constexpr int MERGE_THREADS = 1024, MERGE_BATCH = 8;
 struct MergeArgs {
   const float* part_m;
   const float* part_s;
@@ -276,27 +276,29 @@ struct MergeArgs {
 };
 // PARTIAL: W is a shard of a vocabulary-parallel head; the per-token (m, s, zt) are what the shards would
 // all-reduce (paper Sec. 8.2, Table 3: trainer model parallelism 8-32), see k_merge_shards.
-template <bool PARTIAL>
-__global__ __launch_bounds__(MERGE_TOKENS * MERGE_SLICES) void k_merge_logp(MergeArgs a) {
-  __shared__ float s_M[MERGE_SLICES][MERGE_TOKENS], s_S[MERGE_SLICES][MERGE_TOKENS];
-  const int tok = threadIdx.x % MERGE_TOKENS, sl = threadIdx.x / MERGE_TOKENS;
-  const int64_t p = (int64_t)blockIdx.x * MERGE_TOKENS + tok;
+template <bool PARTIAL, int TOKENS>
+__global__ __launch_bounds__(MERGE_THREADS) void k_merge_logp(MergeArgs a) {
+  constexpr int SLICES = MERGE_THREADS / TOKENS, WAVES = MERGE_THREADS / 64;
+  static_assert(TOKENS == 32 || TOKENS == 8, "cross-lane steps written for these");
+  __shared__ float s_M[WAVES][TOKENS], s_S[WAVES][TOKENS];
+  const int tok = threadIdx.x % TOKENS, sl = threadIdx.x / TOKENS;
+  const int64_t p = (int64_t)blockIdx.x * TOKENS + tok;
   const int64_t n = *a.n_act;
-  if ((int64_t)blockIdx.x * MERGE_TOKENS >= n) return;        // block-uniform
+  if ((int64_t)blockIdx.x * TOKENS >= n) return;        // block-uniform
   float M = -INFINITY, S = 0.f;
   if (p < n) {
     // MERGE_BATCH tiles' loads in flight at a time: the running (M, S) is a serial chain, the loads need not be
-    for (int j0 = sl; j0 < a.tiles_v; j0 += MERGE_SLICES * MERGE_BATCH) {
+    for (int j0 = sl; j0 < a.tiles_v; j0 += SLICES * MERGE_BATCH) {
       float mb[MERGE_BATCH], sb[MERGE_BATCH];
 #pragma unroll
       for (int q = 0; q < MERGE_BATCH; ++q) {
-        const int64_t at = (int64_t)min(j0 + q * MERGE_SLICES, a.tiles_v - 1) * a.n_pad + p;
+        const int64_t at = (int64_t)min(j0 + q * SLICES, a.tiles_v - 1) * a.n_pad + p;
         mb[q] = a.part_m[at];
         sb[q] = a.part_s[at];
       }
 #pragma unroll
       for (int q = 0; q < MERGE_BATCH; ++q) {
-        if (j0 + q * MERGE_SLICES >= a.tiles_v) break;
+        if (j0 + q * SLICES >= a.tiles_v) break;
         const float m = mb[q], s = sb[q];
         if (m > M) {
           S = S * __expf(M - m) + s;      // exp(-inf) = 0 on the first tile
@@ -307,14 +309,39 @@ __global__ __launch_bounds__(MERGE_TOKENS * MERGE_SLICES) void k_merge_logp(Merg
       }
     }
   }
-  s_M[sl][tok] = M;
-  s_S[sl][tok] = S;
+  // the slices of a wavefront meet across its lanes (the sum is the same in both lanes of a pair), wavefronts in LDS
+  auto merge = [&](float m2, float s2) {
+    const float m = fmaxf(M, m2), b = (m == -INFINITY) ? 0.f : m;
+    S = S * expf(M - b) + s2 * expf(m2 - b);
+    M = m;
+  };
+  if constexpr (TOKENS == 8)
+    merge(__uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(M), 0x128, 0xf, 0xf, true)),   // lane ^ 8
+          __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(S), 0x128, 0xf, 0xf, true)));
+  if constexpr (TOKENS == 8) {
+    const bool up = (threadIdx.x & 16) != 0;                                                                            // lane ^ 16
+    const auto m = __builtin_amdgcn_permlane16_swap(__float_as_uint(M), __float_as_uint(M), false, false);
+    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(S), __float_as_uint(S), false, false);
+    merge(__uint_as_float(up ? m[0] : m[1]), __uint_as_float(up ? t[0] : t[1]));
+  }
+  {
+    const bool up = (threadIdx.x & 32) != 0;                                                                            // lane ^ 32
+    const auto m = __builtin_amdgcn_permlane32_swap(__float_as_uint(M), __float_as_uint(M), false, false);
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(S), __float_as_uint(S), false, false);
+    merge(__uint_as_float(up ? m[0] : m[1]), __uint_as_float(up ? t[0] : t[1]));
+  }
+  if ((threadIdx.x & 63) < TOKENS) {
+    s_M[threadIdx.x >> 6][tok] = M;
+    s_S[threadIdx.x >> 6][tok] = S;
+  }
   __syncthreads();
   if (sl == 0 && p < n) {
     float Mx = s_M[0][tok];
-    for (int q = 1; q < MERGE_SLICES; ++q) Mx = fmaxf(Mx, s_M[q][tok]);
+#pragma unroll
+    for (int q = 1; q < WAVES; ++q) Mx = fmaxf(Mx, s_M[q][tok]);
     float Sx = 0.f;
-    for (int q = 0; q < MERGE_SLICES; ++q) Sx += (s_M[q][tok] == -INFINITY) ? 0.f : s_S[q][tok] * expf(s_M[q][tok] - Mx);
+#pragma unroll
+    for (int q = 0; q < WAVES; ++q) Sx += (s_M[q][tok] == -INFINITY) ? 0.f : s_S[q][tok] * expf(s_M[q][tok] - Mx);
     const int64_t t = a.rows[p];
     if constexpr (PARTIAL) {
       const int64_t y = (int64_t)a.targets[t] - a.v_off;
