@@ -78,6 +78,8 @@ typedef enum { LLAMARL_PASS_LOGPROBS = 0, LLAMARL_PASS_LOSS_FWD = 1, LLAMARL_PAS
 
 /* Bytes of device workspace the given entry point needs for these sizes
  * (for LLAMARL_PASS_LOSS_FWD pass N = B*T; d, V, dt are ignored).
+ * The size does not fall as N or V grows: a workspace sized for the largest
+ * batch serves smaller ones.
  * Returns 0 for invalid sizes.  Host-only computation, no HIP call. */
 size_t llamarl_workspace_bytes(int64_t N, int64_t d, int64_t V, llamarl_dtype dt, llamarl_pass pass);
 

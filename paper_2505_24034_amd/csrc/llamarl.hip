@@ -47,9 +47,10 @@ inline int64_t tile_count(int64_t rows, int64_t cols, int64_t edge) {
 //   (1041, 5003, 520) 26 / 18 / 26, (1024, 8192, 1024) 30 / 24 / 39, (1024, 16032, 2048) 58 / 70 / 115.
 //   fp32, forward on 128- / 64-tiles: (512, 2048, 512) 39 / 26 us, (512, 4096, 512) 39 / 33, (1024, 4096, 512) 40 / 53,
 //   (2048, 8192, 512) 105 / 180.
+constexpr int LOGITS_MIN_TILES = 192, LOGITS_MIN_TILES_BF16_128 = 128;   // of the larger edge; fewer: the next smaller one
 Tile logits_tile(int64_t N, int64_t V, llamarl_dtype dt) {
-  if (dt == LLAMARL_BF16 && tile_count(N, V, 256) >= 192) return TILE_256;
-  return tile_count(N, V, 128) >= (dt == LLAMARL_BF16 ? 128 : 192) ? TILE_128 : TILE_64;
+  if (dt == LLAMARL_BF16 && tile_count(N, V, 256) >= LOGITS_MIN_TILES) return TILE_256;
+  return tile_count(N, V, 128) >= (dt == LLAMARL_BF16 ? LOGITS_MIN_TILES_BF16_128 : LOGITS_MIN_TILES) ? TILE_128 : TILE_64;
 }
 // Store contractions: M x Nn outputs over K, split along K where tiles are few; counted in parts of 16 slabs, which
 // still pay for their partial blocks.
@@ -86,7 +87,14 @@ FwdWs fwd_ws(int64_t N, int64_t V, llamarl_dtype dt) {
   w.tiles_v = (int)((V + tile - 1) / tile);
   w.tiles_t = (int)((N + tile - 1) / tile);
   w.n_pad = round_up(N, 256);
-  const size_t plane = (size_t)w.tiles_v * (size_t)w.n_pad * sizeof(float);
+  // Smaller tiles leave more partials per token, so the planes of a call can be larger than those of a call with more
+  // tokens (or vocabulary rows) on larger tiles.  A workspace sized for the larger call has to serve the smaller one as
+  // well: room for whatever any N' <= N, V' <= V can need.  A call on tiles of edge e has fewer than LOGITS_MIN_TILES
+  // of edge 2e, each of them two rows of partials of at most 256 tokens: at most `small` floats, 0.4 MB.
+  const int64_t largest = dt == LLAMARL_BF16 ? 256 : 128, small = 2 * 256 * (LOGITS_MIN_TILES - 1);
+  static_assert(LOGITS_MIN_TILES_BF16_128 <= LOGITS_MIN_TILES, "`small` covers both edges");
+  const int64_t reserve = std::max((V + largest - 1) / largest * w.n_pad, std::min((V + 63) / 64 * w.n_pad, small));
+  const size_t plane = (size_t)reserve * sizeof(float);
   w.off_m = 0;
   w.off_s = round_up((int64_t)plane, 256);
   w.off_zt = w.off_s + round_up((int64_t)plane, 256);

@@ -44,6 +44,20 @@ def test_workspace_sizes(clib):
     assert wb(1000, 0, 0, 0, binding.PASS_LOSS_FWD) >= 8 * 1000
 
 
+@pytest.mark.parametrize("dt", [binding.F32, binding.BF16])
+def test_logprobs_workspace_of_a_larger_call_serves_a_smaller_one(clib, dt):
+    """a workspace is sized once for the largest micro-batch (or shard) and reused: the size never falls as N or V grows,
+    whatever tiles either size runs on"""
+    rows = sorted({n + o for n in list(range(64, 4200, 64)) + [8192, 16384, 24576] for o in (-1, 0, 1)} | {1, 2, 3})
+    vocabs = sorted({v + o for v in [64, 512, 1024, 3000, 4096, 5003, 8064, 8192, 16032, 20000, 20011, 24576, 32000, 48896,
+                                     64000, 97792, 128256] for o in (-1, 0, 1)})
+    size = {(n, v): binding.workspace_bytes(n, 64, v, dt, binding.PASS_LOGPROBS) for n in rows for v in vocabs}
+    for v in vocabs:
+        assert all(size[a, v] <= size[b, v] for a, b in zip(rows, rows[1:])), v
+    for n in rows:
+        assert all(size[n, a] <= size[n, b] for a, b in zip(vocabs, vocabs[1:])), n
+
+
 def _call_logprobs(clib, H=1 << 20, W=1 << 21, tg=1 << 22, N=16, d=8, V=8, dt=binding.BF16, logp=1 << 23,
                    lse=1 << 24, ws=1 << 25, ws_bytes=1 << 30):
     # fake non-null device addresses: validation must fail before anything is dereferenced or launched
