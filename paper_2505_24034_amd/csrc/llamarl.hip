@@ -115,7 +115,9 @@ LossWs loss_ws(int64_t N, int64_t B) {  // B generations, N = B * T tokens
   w.off_len = 0;
   w.off_bad = (size_t)round_up(B * 4, 256);
   w.off_part = w.off_bad + (size_t)round_up(B * 4, 256);
-  w.off_ticket = w.off_part + (size_t)round_up((int64_t)w.nblocks * LOSS_NSUM * 8, 256);
+  // room for the partial sums of the narrower blocks (more of them): the size does not fall where the width changes
+  const int64_t most = std::min<int64_t>((N + 256 * LOSS_ITEMS - 1) / (256 * LOSS_ITEMS), LOSS_MAX_BLOCKS);
+  w.off_ticket = w.off_part + (size_t)round_up(most * LOSS_NSUM * 8, 256);
   w.total = w.off_ticket + 256;
   return w;
 }

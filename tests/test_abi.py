@@ -58,6 +58,12 @@ def test_logprobs_workspace_of_a_larger_call_serves_a_smaller_one(clib, dt):
         assert all(size[n, a] <= size[n, b] for a, b in zip(vocabs, vocabs[1:])), n
 
 
+def test_loss_workspace_of_a_larger_batch_serves_a_smaller_one(clib):
+    edges = [1 << 10, 1 << 13, 1 << 17, 1 << 19, 1 << 20, 1 << 21, 1 << 22]
+    sizes = [binding.workspace_bytes(n + o, 0, 0, 0, binding.PASS_LOSS_FWD) for n in edges for o in (-1, 0, 1, 4096)]
+    assert sizes == sorted(sizes)
+
+
 def _call_logprobs(clib, H=1 << 20, W=1 << 21, tg=1 << 22, N=16, d=8, V=8, dt=binding.BF16, logp=1 << 23,
                    lse=1 << 24, ws=1 << 25, ws_bytes=1 << 30):
     # fake non-null device addresses: validation must fail before anything is dereferenced or launched
