@@ -104,7 +104,9 @@ const char* llamarl_version(void);
  *                 whatever H holds there.
  *   logp,lse  out float [N]
  *   ws        scratch, >= llamarl_workspace_bytes(N,d,V,dt,LLAMARL_PASS_LOGPROBS)
- * Accumulation is fp32 for both dtypes.
+ * Accumulation is fp32 for both dtypes.  fp32 operands are multiplied as sums
+ * of three bf16 numbers each (no bit of an operand is lost; a product is good
+ * to 2^-30), in the backward as well.
  */
 llamarl_status llamarl_token_logprobs(const void* H, const void* W, const int32_t* targets, const uint8_t* mask,
                                       int64_t N, int64_t d, int64_t V, llamarl_dtype dt, float* logp, float* lse,

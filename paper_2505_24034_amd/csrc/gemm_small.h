@@ -1,14 +1,14 @@
 // gemm_small.h -- K-contiguous contraction loop on 128 x 128 and 64 x 64 tiles, C[m,n] = sum_k A[m,k] * B[n,k].
 //
 // fp32 operands go through the bf16 matrix pipes: every value is written as a sum of three bf16 numbers,
-// x = h + m + l (h = bf16(x), m = bf16(x - h), l = bf16(x - h - m): 3 x 8 significant bits, nothing of a normal fp32
-// number is lost), and a product is taken as  hh + hm + mh + mm + hl + lh  in fp32 accumulators.  bf16 products are
-// exact in fp32; the three terms left out (ml, lm, ll) are below 2^-26 of the product, a quarter of the rounding of
-// one fp32 addition.  hh is summed apart from the five small terms, whose rounding errors are 2^-8 smaller, so 32 k
-// cost the main accumulator one rounding where eight 16x16x4 fp32 MFMAs cost it eight.  Six 16x16x32 bf16 MFMAs
-// take less than half the time of those eight.
-//   - bf16 has fp32's exponents: only below 2^-109 does a value run out of bits for l (subnormals are not flushed), and
-//     then by at most 2^-134.
+// x = h + m + l (h = bf16(x), m = bf16(x - h), l = bf16(x - h - m): 3 x 8 significant bits, so nothing of a normal fp32
+// number is lost), and a product is taken as  hh + hm + mh + mm + hl + lh + ml + lm  in fp32 accumulators.  bf16 products
+// are exact in fp32; the term left out, ll, is below 2^-34 of the product (|l| <= 2^-17 of a number's leading power of
+// two).  hh is summed apart from the seven small terms, whose rounding errors are 2^-8 smaller, so 32 k cost the main
+// accumulator one rounding where eight 16x16x4 fp32 MFMAs cost it eight; a contraction with a single product is within
+// 0.506 ulp of it (without ml and lm, up to 2^-24 of the product together, 0.96 ulp; fp32 MFMAs 0.5).  Eight 16x16x32
+// bf16 MFMAs take half the time of the eight fp32 ones.
+//   - bf16 has fp32's exponents: only below 2^-110 does a value run out of bits for l (subnormals are not flushed).
 //   - Infinities, NaN and values that round to infinity in bf16 cannot be split (inf - inf): they make the
 //     accumulator non-finite, and so does an honest overflow.  A tile with any non-finite sum is contracted again with
 //     fp32 MFMAs, whose results it keeps.
@@ -16,11 +16,11 @@
 // gfx950 mapping: four wavefronts, 128-byte slab rows with the XOR swizzle of gemm_nt.h, slabs fetched straight into
 // LDS.  The tiles are small enough for two or more workgroups per CU, whose main loops, splits and epilogues cover
 // each other's waits: the loop needs no hand-written slot table.  Bound by the VALU work of the splits (44 operations
-// per fragment, 8 fragments per 96 MFMAs of a wavefront) beside the MFMAs.  Measured against a 256 x 256 loop of
-// 16x16x4 fp32 MFMAs, per contraction of (N, V, d): (4096, 20011, 516) 665 - 930 -> 540 - 575 us, (1024, 32000, 2048)
-// 940 - 1020 -> 690 - 725 us; (256, 1024, 256) on 64 x 64 tiles 64 - 86 -> 9 - 13 us.  Relative error against 64 bits
-// over 60 shapes (32 .. 8192 tokens, 300 .. 40000 entries, d 64 .. 2048): logp 7.1e-8 -> 3.2e-8, dH 4.3e-7 -> 1.9e-7,
-// dW 2.2e-7 -> 1.2e-7, and smaller than before at every one of them.
+// per fragment, 8 fragments per 128 MFMAs of a wavefront) beside the MFMAs.  Measured against a 256 x 256 loop of
+// 16x16x4 fp32 MFMAs, per contraction of (N, V, d): (4096, 20011, 516) 690 - 930 -> 620 - 680 us, (1024, 32000, 2048)
+// 940 - 1020 -> 820 - 860 us (without ml and lm 545 - 585 and 705 - 750); (256, 1024, 256) on 64 x 64 tiles 45 - 97 ->
+// 15 - 18 us.  Relative error against 64 bits over 60 shapes (32 .. 8192 tokens, 300 .. 40000 entries, d 64 .. 2048):
+// logp 7.1e-8 -> 3.1e-8, dH 4.3e-7 -> 1.9e-7, dW 2.2e-7 -> 1.2e-7, and smaller than before at every one of them.
 #pragma once
 #include "gemm_nt.h"
 
@@ -110,7 +110,7 @@ struct TileGemmSmall {
   }
 
   // the MFMAs of one slab; a_addr / b_addr: this lane's chunk of block 0 in either half of a slab row.
-  // low: sums of the five small terms of split products
+  // low: sums of the seven small terms of split products
   __device__ __forceinline__ static void slab(const char* st, const int (&a_addr)[2], const int (&b_addr)[2],
                                               f32x4_t (&acc)[S::MB][NB], f32x4_t (&low)[S::MB][NB], bool native) {
     if constexpr (sizeof(typename TT::store_t) == 2) {
@@ -149,6 +149,10 @@ struct TileGemmSmall {
         const Split3 a = split3(*reinterpret_cast<const frag_t*>(st + a_addr[0] + i * BLOCK_BYTES),
                                 *reinterpret_cast<const frag_t*>(st + a_addr[1] + i * BLOCK_BYTES));
         // j innermost: consecutive MFMAs do not wait for each other's accumulator
+#pragma unroll
+        for (int j = 0; j < NB; ++j) mma(a.m, b[j].l, low[i][j]);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) mma(a.l, b[j].m, low[i][j]);
 #pragma unroll
         for (int j = 0; j < NB; ++j) mma(a.l, b[j].h, low[i][j]);
 #pragma unroll

@@ -88,3 +88,39 @@ def test_scaling_by_a_power_of_two_changes_no_bit(lib, N, V, d, shift):
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     else:       # a value below 2^-109 loses at most 2^-134, times a partner below 8 x 2^100: nothing beside a sum's rounding
         assert float((a[0] - b[0]).abs().max()) <= 1e-6
+
+
+def _full_mantissas(g, exponent, *shape):
+    """fp32 numbers in [2^exponent, 2^(exponent+1)) with random 24-bit significands"""
+    x = 1.0 + torch.rand(*shape, generator=g, device="cuda", dtype=torch.float64)
+    return torch.ldexp(x, torch.tensor(exponent, device="cuda")).float()
+
+
+def _ulps(got, exact):
+    """distance in units of the last place of an fp32 number of exact's size"""
+    ulp = torch.ldexp(torch.ones_like(exact), (torch.frexp(exact)[1] - 24).clamp(min=-149))
+    return float(((got.double() - exact).abs() / ulp).max())
+
+
+# Sums with one product that is not zero: the bare arithmetic of a product, in all three contractions.  The five bf16
+# products of orders 2^-8 and 2^-16 and the last two of 2^-25 meet in one fp32 sum below 2^-6 of the factors' leading
+# powers of two: its roundings (2^-32 + 2^-31 and smaller ones) and the product left out (2^-34) are below 2^-7 ulp of the
+# result, the final addition is half an ulp.
+@pytest.mark.parametrize("N,V,d", [(2000, 512, 64), (4096, 8192, 260)])      # 64- and 128-tiles
+@pytest.mark.parametrize("ex,ey", [(0, 0), (40, -70), (-100, 55), (60, -108)])   # sums of 2 ey stay finite
+def test_single_products(lib, N, V, d, ex, ey):
+    g = torch.Generator(device="cuda").manual_seed(N + ex)
+    rows = torch.arange(N, device="cuda")
+    x, W = _full_mantissas(g, ex, N), _full_mantissas(g, ey, V, d)
+    H = torch.zeros(N, d, device="cuda")
+    H[rows, rows % d] = x                                           # one-hot rows: a logit is one product
+    t = (rows * 37 % V).int()
+    _, _, zt = lib.token_logprobs_partial(H, W, t, 0, V)
+    assert _ulps(zt, x.double() * W[t.long(), rows % d].double()) <= 0.5 + 2.0 ** -7
+    # lse = inf: dz is coef at the target and zero elsewhere; distinct targets
+    n = min(N, V)
+    t = torch.randperm(V, generator=g, device="cuda")[:n]
+    H, coef = _full_mantissas(g, ey, n, d), x[:n].contiguous()
+    dH, dW = lib.offpolicy_loss_bwd(H, W, t.int(), torch.full((n,), float("inf"), device="cuda"), coef)
+    assert _ulps(dH, coef.double()[:, None] * W[t].double()) <= 0.5 + 2.0 ** -7
+    assert _ulps(dW[t], coef.double()[:, None] * H.double()) <= 0.5 + 2.0 ** -7
