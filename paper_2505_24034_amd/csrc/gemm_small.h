@@ -8,19 +8,23 @@
 // accumulator one rounding where eight 16x16x4 fp32 MFMAs cost it eight; a contraction with a single product is within
 // 0.506 ulp of it (without ml and lm, up to 2^-24 of the product together, 0.96 ulp; fp32 MFMAs 0.5).  Eight 16x16x32
 // bf16 MFMAs take half the time of the eight fp32 ones.
-//   - bf16 has fp32's exponents: only below 2^-110 does a value run out of bits for l (subnormals are not flushed).
+//   - bf16 has fp32's exponents (subnormals are not flushed), but a value below 2^-110 can have bits below 2^-133, the
+//     last one of l.  (The gradient of a very unlikely vocabulary row would be such a value, 76 nats under its token's: dz
+//     is stored scaled up, dz_scale_for.)
 //   - Infinities, NaN and values that round to infinity in bf16 cannot be split (inf - inf): they make the
-//     accumulator non-finite, and so does an honest overflow.  A tile with any non-finite sum is contracted again with
-//     fp32 MFMAs, whose results it keeps.
+//     accumulator non-finite, and so does an honest overflow.
+// A tile whose operands lost a bit or that has a non-finite sum is contracted again with fp32 MFMAs, whose results it
+// keeps.
 //
 // gfx950 mapping: four wavefronts, 128-byte slab rows with the XOR swizzle of gemm_nt.h, slabs fetched straight into
 // LDS.  The tiles are small enough for two or more workgroups per CU, whose main loops, splits and epilogues cover
-// each other's waits: the loop needs no hand-written slot table.  Bound by the VALU work of the splits (44 operations
+// each other's waits: the loop needs no hand-written slot table.  Bound by the VALU work of the splits (48 operations
 // per fragment, 8 fragments per 128 MFMAs of a wavefront) beside the MFMAs.  Measured against a 256 x 256 loop of
-// 16x16x4 fp32 MFMAs, per contraction of (N, V, d): (4096, 20011, 516) 690 - 930 -> 620 - 680 us, (1024, 32000, 2048)
-// 940 - 1020 -> 820 - 860 us (without ml and lm 545 - 585 and 705 - 750); (256, 1024, 256) on 64 x 64 tiles 45 - 97 ->
-// 15 - 18 us.  Relative error against 64 bits over 60 shapes (32 .. 8192 tokens, 300 .. 40000 entries, d 64 .. 2048):
-// logp 7.1e-8 -> 3.1e-8, dH 4.3e-7 -> 1.9e-7, dW 2.2e-7 -> 1.2e-7, and smaller than before at every one of them.
+// 16x16x4 fp32 MFMAs, per contraction of (N, V, d): (4096, 20011, 516) 690 - 930 -> 630 - 705 us, (1024, 32000, 2048)
+// 940 - 1020 -> 830 - 885 us (without ml and lm 545 - 585 and 705 - 750, with them but without `lost` 620 - 680 and
+// 820 - 865); (256, 1024, 256) on 64 x 64 tiles 45 - 97 -> 15 - 18 us.  Relative error against 64 bits over 60 shapes
+// (32 .. 8192 tokens, 300 .. 40000 entries, d 64 .. 2048): logp 7.1e-8 -> 3.1e-8, dH 4.3e-7 -> 1.9e-7, dW 2.2e-7 ->
+// 1.2e-7, and smaller than before at every one of them.
 #pragma once
 #include "gemm_nt.h"
 
@@ -37,7 +41,8 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {   // v_cvt_p
 struct Split3 {
   bf16x8_t h, m, l;
 };
-__device__ __forceinline__ Split3 split3(const f32x4_t& x0, const f32x4_t& x1) {
+// lost: bits that l has no room for are collected in its low half (0 as long as every split is exact)
+__device__ __forceinline__ Split3 split3(const f32x4_t& x0, const f32x4_t& x1, uint32_t& lost) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   u32x4 h, m, l;
 #pragma unroll
@@ -46,7 +51,10 @@ __device__ __forceinline__ Split3 split3(const f32x4_t& x0, const f32x4_t& x1) {
     h[i] = pack_bf16(a, b);
     const float ra = a - __uint_as_float(h[i] << 16), rb = b - __uint_as_float(h[i] & 0xffff0000u);
     m[i] = pack_bf16(ra, rb);
-    l[i] = pack_bf16(ra - __uint_as_float(m[i] << 16), rb - __uint_as_float(m[i] & 0xffff0000u));
+    const float sa = ra - __uint_as_float(m[i] << 16), sb = rb - __uint_as_float(m[i] & 0xffff0000u);
+    l[i] = pack_bf16(sa, sb);
+    // one instruction, here: left to itself the compiler gathers the 64 parts of a slab first, and spills
+    asm("v_or3_b32 %0, %0, %1, %2" : "+v"(lost) : "v"(sa), "v"(sb));
   }
   return Split3{__builtin_bit_cast(bf16x8_t, h), __builtin_bit_cast(bf16x8_t, m), __builtin_bit_cast(bf16x8_t, l)};
 }
@@ -69,6 +77,7 @@ struct TileGemmSmall {
   LoaderA la;
   LoaderB lb;
   int K;
+  float unscale;     // run<true> only
 
   // A slab past K fetches nothing (every lane out of the descriptor's range: zeros land in LDS), so the number of
   // loads in flight is the same in every iteration and the waits can count them.
@@ -110,9 +119,12 @@ struct TileGemmSmall {
   }
 
   // the MFMAs of one slab; a_addr / b_addr: this lane's chunk of block 0 in either half of a slab row.
-  // low: sums of the seven small terms of split products
+  // low: sums of the seven small terms of split products; lost: see split3.  SPLIT = false: the operands' own MFMAs, A
+  // times a_factor
+  template <bool SPLIT>
   __device__ __forceinline__ static void slab(const char* st, const int (&a_addr)[2], const int (&b_addr)[2],
-                                              f32x4_t (&acc)[S::MB][NB], f32x4_t (&low)[S::MB][NB], bool native) {
+                                              f32x4_t (&acc)[S::MB][NB], f32x4_t (&low)[S::MB][NB], uint32_t& lost,
+                                              float a_factor) {
     if constexpr (sizeof(typename TT::store_t) == 2) {
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
@@ -126,12 +138,14 @@ struct TileGemmSmall {
 #pragma unroll
           for (int j = 0; j < NB; ++j) mma(a[i], b[j], acc[i][j]);
       }
-    } else if (native) {
+    } else if constexpr (!SPLIT) {
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
         for (int i = 0; i < S::MB; ++i) {
-          const frag_t a = *reinterpret_cast<const frag_t*>(st + a_addr[ks] + i * BLOCK_BYTES);
+          frag_t a = *reinterpret_cast<const frag_t*>(st + a_addr[ks] + i * BLOCK_BYTES);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) a[r] *= a_factor;
 #pragma unroll
           for (int j = 0; j < NB; ++j)
             mma(a, *reinterpret_cast<const frag_t*>(st + b_addr[ks] + j * BLOCK_BYTES), acc[i][j]);
@@ -143,11 +157,11 @@ struct TileGemmSmall {
 #pragma unroll
       for (int j = 0; j < NB; ++j)
         b[j] = split3(*reinterpret_cast<const frag_t*>(st + b_addr[0] + j * BLOCK_BYTES),
-                      *reinterpret_cast<const frag_t*>(st + b_addr[1] + j * BLOCK_BYTES));
+                      *reinterpret_cast<const frag_t*>(st + b_addr[1] + j * BLOCK_BYTES), lost);
 #pragma unroll
       for (int i = 0; i < S::MB; ++i) {
         const Split3 a = split3(*reinterpret_cast<const frag_t*>(st + a_addr[0] + i * BLOCK_BYTES),
-                                *reinterpret_cast<const frag_t*>(st + a_addr[1] + i * BLOCK_BYTES));
+                                *reinterpret_cast<const frag_t*>(st + a_addr[1] + i * BLOCK_BYTES), lost);
         // j innermost: consecutive MFMAs do not wait for each other's accumulator
 #pragma unroll
         for (int j = 0; j < NB; ++j) mma(a.m, b[j].l, low[i][j]);
@@ -169,8 +183,33 @@ struct TileGemmSmall {
     }
   }
 
+  // the K loop; the first slabs are on their way
+  template <bool SPLIT>
+  __device__ __forceinline__ void slabs(char* smem, const int (&a_addr)[2], const int (&b_addr)[2],
+                                        f32x4_t (&acc)[S::MB][NB], f32x4_t (&low)[S::MB][NB], uint32_t& lost,
+                                        float a_factor) const {
+    const int nk = (K + BK - 1) / BK;
+    wait_vmcnt0();                     // the first slabs (and stores of a previous epilogue, which may sit between)
+    __syncthreads();
+    int st = 0;                        // stage of slab kt
+    for (int kt = 0; kt < nk; ++kt) {
+      if (kt > 0) {
+        wait_vmcnt<LOADS * (NSTAGE - 2)>();      // this thread's share of slab kt has landed
+        __syncthreads();                         // everyone's has, and everyone is done with slab kt - 1
+      }
+      // slab kt - 1's stage is free now
+      issue(smem + (st == 0 ? NSTAGE - 1 : st - 1) * S::STAGE_BYTES, kt + NSTAGE - 1);
+      slab<SPLIT>(smem + st * S::STAGE_BYTES, a_addr, b_addr, acc, low, lost, a_factor);
+      st = st == NSTAGE - 1 ? 0 : st + 1;
+    }
+  }
+
+  // A_SCALED (fp32): A holds its values divided by `unscale`, a power of two; the sums come out unscaled.  The native pass
+  // unscales the operand itself: what it is there for may be a sum that only overflows scaled.
+  template <bool A_SCALED = false>
   __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[S::MB][NB]) {
     constexpr bool SPLIT = sizeof(typename TT::store_t) == 4;
+    const float factor = A_SCALED ? unscale : 1.f;
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int wm = S::wave_row(wave), wn = S::wave_col(wave);
     const int g = lane >> 4, l16 = lane & 15, sw = swizzle(l16);
@@ -183,24 +222,12 @@ struct TileGemmSmall {
     int* redo = reinterpret_cast<int*>(smem + NSTAGE * S::STAGE_BYTES);
     if (SPLIT && threadIdx.x == 0) *redo = 0;
     f32x4_t low[S::MB][NB];
+    uint32_t lost = 0;
     clear(acc);
     clear(low);
-    const int nk = (K + BK - 1) / BK;
-    wait_vmcnt0();                     // the first slabs (and stores of a previous epilogue, which may sit between)
-    __syncthreads();
-    int st = 0;                        // stage of slab kt
-    for (int kt = 0; kt < nk; ++kt) {
-      if (kt > 0) {
-        wait_vmcnt<LOADS * (NSTAGE - 2)>();      // this thread's share of slab kt has landed
-        __syncthreads();                         // everyone's has, and everyone is done with slab kt - 1
-      }
-      // slab kt - 1's stage is free now
-      issue(smem + (st == 0 ? NSTAGE - 1 : st - 1) * S::STAGE_BYTES, kt + NSTAGE - 1);
-      slab(smem + st * S::STAGE_BYTES, a_addr, b_addr, acc, low, false);
-      st = st == NSTAGE - 1 ? 0 : st + 1;
-    }
+    slabs<SPLIT>(smem, a_addr, b_addr, acc, low, lost, 1.f);
     if constexpr (SPLIT) {
-      bool bad = false;
+      bool bad = (lost & 0xffffu) != 0;
 #pragma unroll
       for (int i = 0; i < S::MB; ++i)
 #pragma unroll
@@ -209,19 +236,15 @@ struct TileGemmSmall {
           for (int r = 0; r < 4; ++r) {
             acc[i][j][r] += low[i][j][r];
             bad |= !(fabsf(acc[i][j][r]) < INFINITY);
+            if constexpr (A_SCALED) acc[i][j][r] *= factor;
           }
       if (bad) *redo = 1;
       wait_vmcnt0();                   // slabs past K that are still in flight would overwrite the ones fetched below
       __syncthreads();
       if (*redo) {                     // workgroup-uniform
         clear(acc);
-        for (int kt = 0; kt < nk; ++kt) {
-          issue(smem, kt);
-          wait_vmcnt0();
-          __syncthreads();
-          slab(smem, a_addr, b_addr, acc, low, true);
-          __syncthreads();
-        }
+        first_slabs(smem);
+        slabs<false>(smem, a_addr, b_addr, acc, low, lost, factor);
       }
     }
   }

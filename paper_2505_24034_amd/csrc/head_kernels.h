@@ -408,14 +408,18 @@ struct CompactArgs {
   float* out0;
   float* out1;
   float* out2;
+  float g;                   // mode 1, fp32: the upstream scalar (or *g_device) and where the scale of dz goes
+  const float* g_device;
+  float* dz_scale;
 };
 
-// bit i: row t0 + i is active (t0 a multiple of 4)
-__device__ __forceinline__ uint32_t active_rows4(const CompactArgs& a, int64_t t0) {
+// bit i: row t0 + i is active (t0 a multiple of 4); mode 1: top = max(top, |coef|)
+__device__ __forceinline__ uint32_t active_rows4(const CompactArgs& a, int64_t t0, float& top) {
   uint32_t bits = 0;
   if (a.aligned && t0 + 4 <= a.N) {
     if (a.mode == 1) {
       const float4 c = *reinterpret_cast<const float4*>(a.coef + t0);
+      top = fmaxf(fmaxf(top, fmaxf(fabsf(c.x), fabsf(c.y))), fmaxf(fabsf(c.z), fabsf(c.w)));
       return (c.x != 0.f ? 1u : 0u) | (c.y != 0.f ? 2u : 0u) | (c.z != 0.f ? 4u : 0u) | (c.w != 0.f ? 8u : 0u);
     }
     const int4 y = *reinterpret_cast<const int4*>(a.targets + t0);
@@ -433,6 +437,7 @@ __device__ __forceinline__ uint32_t active_rows4(const CompactArgs& a, int64_t t
     bool on;
     if (a.mode == 1) {
       on = a.coef[t] != 0.f;
+      top = fmaxf(top, fabsf(a.coef[t]));
     } else {
       const int y = a.targets[t];
       on = (a.mask == nullptr || a.mask[t] != 0) && y >= 0 && (int64_t)y < a.V;
@@ -442,15 +447,25 @@ __device__ __forceinline__ uint32_t active_rows4(const CompactArgs& a, int64_t t
   return bits;
 }
 
+// fp32 keeps dz multiplied by a power of two that lifts the largest |upstream * coef| to 2^60: the contractions split
+// their operands into bf16 parts that end at 2^-133 (gemm_small.h), and entries c p with p down to 2^-126 then stay clear of
+// that for any coef within 2^-40 of the largest one.  Exact in both directions; large gradients are left alone.
+__device__ __forceinline__ float dz_scale_for(float c) {
+  const int e = (int)(__float_as_uint(c) >> 23 & 0xffu) - 127;      // a subnormal c counts as 2^-127
+  return (c == 0.f || e >= 60) ? 1.f : __uint_as_float((uint32_t)(min(60 - e, 126) + 127) << 23);
+}
+
 __device__ __forceinline__ void compact_rows(const CompactArgs& a, int block, int nblocks) {
   constexpr int WAVES = COMPACT_THREADS / 64;
   __shared__ int s_front[WAVES], s_own[WAVES];
+  __shared__ float s_top[WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t first = (int64_t)block * COMPACT_BLOCK_ROWS, t0 = first + 4 * tid;
-  const uint32_t act = t0 < a.N ? active_rows4(a, t0) : 0u;
+  float top = 0.f;
+  const uint32_t act = t0 < a.N ? active_rows4(a, t0, top) : 0u;
   int front = 0;
 #pragma unroll 4
-  for (int64_t t = 4 * tid; t < first; t += COMPACT_BLOCK_ROWS) front += __popc(active_rows4(a, t));
+  for (int64_t t = 4 * tid; t < first; t += COMPACT_BLOCK_ROWS) front += __popc(active_rows4(a, t, top));
   if (a.mode != 1) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -471,6 +486,12 @@ __device__ __forceinline__ void compact_rows(const CompactArgs& a, int block, in
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) front += __shfl_xor(front, o);
+  const bool last = block == nblocks - 1;           // has seen every row
+  if (last && a.dz_scale != nullptr) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+    if (lane == 0) s_top[wave] = top;
+  }
   if (lane == 63) s_own[wave] = upto;
   if (lane == 0) s_front[wave] = front;
   __syncthreads();
@@ -484,7 +505,13 @@ __device__ __forceinline__ void compact_rows(const CompactArgs& a, int block, in
 #pragma unroll
   for (int i = 0; i < 4; ++i)
     if (act >> i & 1u) a.rows[at++] = (int32_t)(t0 + i);
-  if (tid == 0 && block == nblocks - 1) *a.n_act = total;
+  if (tid == 0 && last) {
+    *a.n_act = total;
+    if (a.dz_scale != nullptr) {
+      for (int w = 0; w < WAVES; ++w) top = fmaxf(top, s_top[w]);
+      *a.dz_scale = dz_scale_for(fabsf((a.g_device != nullptr ? *a.g_device : a.g) * top));
+    }
+  }
 }
 __global__ __launch_bounds__(COMPACT_THREADS) void k_compact_rows(CompactArgs a) { compact_rows(a, blockIdx.x, gridDim.x); }
 
@@ -496,6 +523,7 @@ struct DzArgs {
   const float* coef;
   float g;
   const float* g_device;  // non-null: the upstream scalar is *g_device instead of g
+  const float* dz_scale;  // fp32: dz is stored times this (dz_scale_for)
   int64_t N, d, V;
   int64_t v_off;          // vocabulary index of row 0 of W (0 unless W is a shard's slice); lse is always global
   int tiles_v, tiles_t;
@@ -517,6 +545,8 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzAr
   sch.init(a.tiles_v, (n_act + BN - 1) / BN, PATCH_ROWS_LOGITS);
   if (!sch.has_tile()) return;                       // block-uniform: no active token at all
   const float upstream = a.g_device != nullptr ? *a.g_device : a.g;
+  float scale = 1.f;
+  if constexpr (sizeof(typename G::Type::store_t) == 4) scale = *a.dz_scale;
   // token columns are fetched quad-interleaved (a lane's four column blocks are neighbouring tokens), so the
   // vocab-major dz^T leaves straight from registers, 8 (bf16) or 16 bytes per lane and whole lines per 16 lanes.
   G g;
@@ -566,7 +596,8 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzAr
     for (int j = 0; j < NB; ++j) {
       const int tok = lp.col_quad() + j;
       const bool in = tok < rowsT;
-      const float c = in ? upstream * tcoef[j] : 0.f;
+      float c = in ? upstream * tcoef[j] : 0.f;
+      if constexpr (sizeof(typename G::Type::store_t) == 4) c *= scale;
       const float lb = (c != 0.f) ? tlse[j] * LOG2E : 0.f;
       const int yrel = (in ? ttgt[j] - (int)a.v_off : -1) - (int)v0 - lane_row0;   // far out of range: another shard's
       const bool live = c != 0.f;                            // select: a masked token's row is exactly 0
@@ -648,6 +679,7 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzAr
 
 struct StoreArgs {
   const void* A;
+  const float* a_scale;     // fp32: A holds its values times *a_scale, a power of two
   int64_t lda;
   const void* B;
   int64_t ldb;
@@ -679,7 +711,7 @@ struct StoreArgs {
 constexpr int STORE_TAIL_ROUNDS = 4;      // rounds of split parts at the end of a store contraction, at most
 constexpr int STORE_REDUCE_COST = 3 * 256;    // launch and latency of k_reduce_tail, ~4 us, in 1/256 of a 1.5 us slab
 // A block of BM x BN floats written and read at ~5 TB/s against the time the whole grid takes for a slab: 256 x 256
-// bf16 0.105 of 1.47 us; the 128-tiles' block is a quarter and their slab 0.9 us (bf16) or 2.9 us (fp32).
+// bf16 0.105 of 1.47 us; the 128-tiles' block is a quarter and their slab 0.9 us (bf16) or 3.5 us (fp32).
 template <typename G>
 constexpr int STORE_PART_COST = G::Shape::BM == 256 ? 18 : G::Shape::BM == 128 ? (sizeof(typename G::Type::store_t) == 2 ? 7 : 2) : 1;
 struct StorePlan {
@@ -857,6 +889,8 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
   }
   if (!plan.has_item()) return;                      // block-uniform
   G g;
+  if constexpr (sizeof(typename G::Type::store_t) == 4)
+    g.unscale = __uint_as_float((254u << 23) - __float_as_uint(*a.a_scale));       // 1 / *a.a_scale
   int id = plan.take();
   store_fetch(g, plan, a, id, M, K, smem);
   // The K-contiguous epilogue stores one unit per row of a lane: STORES_OF_A_TILE, unless the tile is ragged.
@@ -870,6 +904,8 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
         run_or_idle(g, smem, acc, S::wave_row(wave_id()) * S::WAVE_M >= store_tile_of<G>(plan, a, cur_id, M, K).rowsA);
       else if constexpr (std::is_same<G, TileGemm<BF16, STORE_LOAD_SLOT>>::value)
         g.template run<STORES_OF_A_TILE>(smem, acc, counted);
+      else if constexpr (sizeof(typename G::Type::store_t) == 4)
+        g.template run<true>(smem, acc);
       else
         g.run(smem, acc);
     } else {                                         // nothing to contract: the product is zero

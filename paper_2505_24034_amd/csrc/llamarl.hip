@@ -258,7 +258,7 @@ template <typename G>
 llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t M, int64_t Nn,
                                  int64_t K, void* C, int64_t ldc, int c_is_f32, int accumulate, const int32_t* m_count,
                                  const int32_t* k_count, const int32_t* c_rows, float* ws_part, int32_t* ws_plan,
-                                 const int32_t* pitch_count, int packed_a, int packed_b, hipStream_t st) {
+                                 const int32_t* pitch_count, int packed_a, int packed_b, const float* a_scale, hipStream_t st) {
   // the store epilogue of the K-contiguous loop writes four neighbouring columns per lane as one unit, and so
   // does the tail reduction
   if (Nn % 4 != 0 || ldc % 4 != 0)
@@ -268,7 +268,7 @@ llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int6
   a.max_splits = STORE_MAX_SPLITS; a.part = ws_part; a.plan_out = ws_plan;
 
   a.pitch_count = pitch_count; a.packed_a = packed_a; a.packed_b = packed_b;
-  a.A = A; a.lda = lda; a.B = B; a.ldb = ldb; a.M = M; a.Nn = Nn; a.K = K;
+  a.A = A; a.a_scale = a_scale; a.lda = lda; a.B = B; a.ldb = ldb; a.M = M; a.Nn = Nn; a.K = K;
   constexpr int BM = G::Shape::BM, BN = G::Shape::BN;
   const int tiles_m = (int)((M + BM - 1) / BM);      // worst case: every row active
   a.tiles_n = (int)((Nn + BN - 1) / BN);
@@ -328,7 +328,8 @@ llamarl_status run_logprobs(const void* H, const void* W, const int32_t* targets
   a.rows = rows; a.n_act = n_act;
   // active-token list (mask and target range); inactive rows get their outputs here
   k_compact_rows<<<dim3((unsigned)compact_blocks(N)), dim3(COMPACT_THREADS), 0, st>>>(
-      compact_args({partial ? 2 : 0, mask, targets, nullptr, V_total, N, 0, rows, n_act, out0, out1, out2}));
+      compact_args({partial ? 2 : 0, mask, targets, nullptr, V_total, N, 0, rows, n_act, out0, out1, out2, 0.f, nullptr,
+                    nullptr}));
   HIP_TRY(hipGetLastError());
   llamarl_status s;
   const Tile tile = logits_tile(N, V, dt);
@@ -383,7 +384,10 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
   // tokens that carry gradient (coef != 0), exact zeros for the dH rows of all the others, fp32: W^T for the
   // K-contiguous dH contraction
   SetupArgs<stt> u;
-  u.compact = compact_args({1, nullptr, nullptr, coef, V, N, 0, all_rows, n_act_all, nullptr, nullptr, nullptr});
+  int32_t* plan = reinterpret_cast<int32_t*>(ws + w.off_plan);
+  float* dz_scale = kBf16 ? nullptr : reinterpret_cast<float*>(plan + 16);     // plan: StoreArgs::plan_out, 4 entries
+  u.compact = compact_args({1, nullptr, nullptr, coef, V, N, 0, all_rows, n_act_all, nullptr, nullptr, nullptr, g, g_device,
+                            dz_scale});
   u.compact_blocks = compact_blocks(N);
   u.zero_blocks = (int)((N + SETUP_ROWS - 1) / SETUP_ROWS);
   u.dH = reinterpret_cast<stt*>(dH); u.d = d;
@@ -411,6 +415,7 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     // recompute logits tile by tile, turn them into dz (rows / columns = list positions of the pass)
     DzArgs a;
     a.H = H; a.W = W; a.targets = targets; a.lse = lse; a.coef = coef; a.g = g; a.g_device = g_device; a.N = N; a.d = d; a.V = V;
+    a.dz_scale = dz_scale;
     a.v_off = v_off;
     a.dz = dz; a.ldz = w.ldz; a.dzt = dzt; a.rows = rows; a.n_act = n_act;
     const Tile logits = logits_tile(Rc, V, dt);
@@ -427,16 +432,16 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     //   bf16: k-major operands dz^T [V][n_act] and W [V][d], K = V exactly
     //   fp32: K-contiguous operands dz [n_act][ldz] and W^T [d][ldz], K zero-padded to ldz
     float* part = reinterpret_cast<float*>(ws + w.off_part);
-    int32_t* plan = reinterpret_cast<int32_t*>(ws + w.off_plan);
     const Tile dh_tile = store_tile(Rc, d, V, dt), dw_tile = store_tile(V, d, Rc, dt);
     if constexpr (kBf16) {
       const auto launch = dh_tile == TILE_256   ? launch_store_gemm<TileGemmTN>
                           : dh_tile == TILE_128 ? launch_store_gemm<Bf16LoopTN128>
                                                 : launch_store_gemm<Bf16LoopTN64>;
-      s = launch(dzt, w.ldzt, W, d, Rc, d, V, dH, d, 0, 0, n_act, nullptr, rows, part, plan, n_act, 1, 0, st);
+      s = launch(dzt, w.ldzt, W, d, Rc, d, V, dH, d, 0, 0, n_act, nullptr, rows, part, plan, n_act, 1, 0, nullptr, st);
     } else {
       const auto launch = dh_tile == TILE_128 ? launch_store_gemm<F32Loop128> : launch_store_gemm<F32Loop64>;
-      s = launch(dz, w.ldz, wt, w.ldz, Rc, d, w.ldz, dH, d, 1, 0, n_act, nullptr, rows, part, plan, nullptr, 0, 0, st);
+      s = launch(dz, w.ldz, wt, w.ldz, Rc, d, w.ldz, dH, d, 1, 0, n_act, nullptr, rows, part, plan, nullptr, 0, 0, dz_scale,
+                 st);
     }
     if (s != LLAMARL_OK) return s;
     if (c == 0) PHASE_EVENT(3);
@@ -452,7 +457,7 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
         return dw_tile == TILE_128 ? launch_store_gemm<F32Loop128> : launch_store_gemm<F32Loop64>;
     }();
     s = launch_dw(dzt, w.ldzt, ht, w.ldzt, V, d, w.ldzt, dW, d, dW_dt == LLAMARL_F32, c == 0 ? accumulate_dW : 1, nullptr,
-                  n_act, nullptr, part, plan, n_act, 1, 1, st);
+                  n_act, nullptr, part, plan, n_act, 1, 1, dz_scale, st);
     if (s != LLAMARL_OK) return s;
     if (c == 0) PHASE_EVENT(5);
   }

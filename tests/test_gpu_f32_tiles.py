@@ -106,8 +106,9 @@ def _ulps(got, exact):
 # products of orders 2^-8 and 2^-16 and the last two of 2^-25 meet in one fp32 sum below 2^-6 of the factors' leading
 # powers of two: its roundings (2^-32 + 2^-31 and smaller ones) and the product left out (2^-34) are below 2^-7 ulp of the
 # result, the final addition is half an ulp.
-@pytest.mark.parametrize("N,V,d", [(2000, 512, 64), (4096, 8192, 260)])      # 64- and 128-tiles
-@pytest.mark.parametrize("ex,ey", [(0, 0), (40, -70), (-100, 55), (60, -108)])   # sums of 2 ey stay finite
+@pytest.mark.parametrize("N,V,d", [(130, 300, 4), (2000, 512, 64), (4096, 8192, 260)])      # 64-, 64- and 128-tiles
+@pytest.mark.parametrize("ex,ey", [(0, 0), (40, -70), (-100, 55), (60, -108),                    # sums of 2 ey stay finite
+                                   (-111, 55), (-114, 55), (-126, 55), (-135, 55), (50, -120), (100, -108)])  # bits below 2^-133
 def test_single_products(lib, N, V, d, ex, ey):
     g = torch.Generator(device="cuda").manual_seed(N + ex)
     rows = torch.arange(N, device="cuda")
@@ -124,3 +125,24 @@ def test_single_products(lib, N, V, d, ex, ey):
     dH, dW = lib.offpolicy_loss_bwd(H, W, t.int(), torch.full((n,), float("inf"), device="cuda"), coef)
     assert _ulps(dH, coef.double()[:, None] * W[t].double()) <= 0.5 + 2.0 ** -7
     assert _ulps(dW[t], coef.double()[:, None] * H.double()) <= 0.5 + 2.0 ** -7
+
+
+@pytest.mark.parametrize("N,V,d", [(100, 300, 64), (2100, 8100, 64)])      # 64- and 128-tiles
+def test_gradient_of_a_very_unlikely_row(lib, N, V, d):
+    # H[:, 0] = 1 makes W[:, 0] a bias: -82 nats on two rows, whose dz is 2^-118 .. 2^-124 and has fp32 numbers' 24 bits
+    H, W, t, _ = _inputs(N, V, d, 11)
+    g = torch.Generator(device="cuda").manual_seed(12)
+    coef = torch.rand(N, generator=g, device="cuda") / 64 + 1.0 / 64
+    rows = torch.tensor([5, V - 3], device="cuda")
+    H[:, 0] = 1.0
+    W[:, 0] = 0.0
+    W[rows] *= 0.125
+    W[rows, 0] = -82.0 + torch.logsumexp(H.double() @ W.double().T, dim=1).float().mean()
+    t = torch.where((t[:, None] == rows).any(1), torch.zeros_like(t), t)
+    _, lse = lib.token_logprobs(H, W, t)
+    _, _, _, rdW = _reference(H, W, t, coef)
+    _, dW = lib.offpolicy_loss_bwd(H, W, t, lse, coef)
+    assert float(rdW[rows].abs().max()) < 2.0 ** -107
+    # z and lse of about 82 are rounded to 2^-18 each, which is the relative error of p = exp(z - lse) they leave
+    for r in rows.tolist():
+        assert _rel(dW[r], rdW[r]) <= 2.0 ** -16
