@@ -778,7 +778,8 @@ llamarl_status llamarl_kl_shaped_rewards(const float* rewards, const float* logp
   if (B >= (int64_t)1 << 31) return fail(LLAMARL_ERR_UNSUPPORTED, "too many generations");
   if (!(lambda_kl == lambda_kl)) return fail(LLAMARL_ERR_INVALID_ARG, "lambda_kl is NaN");
   const int aligned = aligned16(logp) && aligned16(base_logp) && (reinterpret_cast<uintptr_t>(mask) & 3u) == 0;
-  const int threads = T > 2048 ? 1024 : 256;
+  // a grid has fewer than 2^32 threads
+  const int threads = T > 2048 && B * 1024 < (int64_t)1 << 32 ? 1024 : 256;
   (threads == 1024 ? k_kl_shaped_rewards<1024> : k_kl_shaped_rewards<256>)<<<
       dim3((unsigned)B), dim3((unsigned)threads), 0, reinterpret_cast<hipStream_t>(stream)>>>(
       rewards, logp, base_logp, mask, B, T, aligned, lambda_kl, shaped, kl);

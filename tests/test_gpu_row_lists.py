@@ -58,3 +58,17 @@ def test_kl_sums_at_any_alignment(lib, B, T, with_mask):
     for by in (1, 2):
         s2, k2 = lib.kl_shaped_rewards(r, _shifted(dirty, by), base, None if m is None else _shifted(m, by), 0.05)
         assert torch.equal(shaped, s2) and torch.equal(kl, k2)
+
+
+def test_kl_sums_of_a_launch_limit_of_generations(lib):
+    # a grid has fewer than 2^32 threads: 2^22 generations cannot have 1024 each
+    B, T = 1 << 22, 2049
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 70 GB of device memory")
+    lp = torch.full((B, T), 0.25, device="cuda")
+    base = torch.zeros(B, T, device="cuda")
+    r = torch.arange(B, device="cuda", dtype=torch.float32)
+    shaped, kl = lib.kl_shaped_rewards(r, lp, base, None, 0.5)
+    assert bool((kl == 0.25 * T).all()) and torch.equal(shaped.double(), (r.double() - 0.125 * T).float().double())
+    del lp, base
+    torch.cuda.empty_cache()
