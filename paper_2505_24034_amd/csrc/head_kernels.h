@@ -1138,8 +1138,10 @@ struct SetupArgs {
   const ST* W;               // fp32 only
   int64_t V, ldz;
   ST* wt;
-  int64_t wt_tiles_r;        // tiles along V; the tiles along d follow from the grid
+  int64_t wt_tiles, wt_tiles_r;        // tiles of W^T, along V of them
+  int wt_blocks;
 };
+constexpr int SETUP_MAX_WT_BLOCKS = 1 << 20;           // a launch has fewer than 2^32 threads: 2^22 blocks
 constexpr int SETUP_ROWS = COMPACT_THREADS / 64;       // dH rows of a block
 template <typename ST>
 __global__ __launch_bounds__(COMPACT_THREADS) void k_bwd_setup(SetupArgs<ST> a) {
@@ -1159,8 +1161,11 @@ __global__ __launch_bounds__(COMPACT_THREADS) void k_bwd_setup(SetupArgs<ST> a) 
   }
   block -= a.zero_blocks;
   if constexpr (sizeof(ST) == 4) {
-    const int64_t tc = block / a.wt_tiles_r, tr = block - tc * a.wt_tiles_r;
-    transpose_tile<ST, COMPACT_THREADS>(a.W, a.V, a.d, a.d, a.wt, a.ldz, nullptr, tr * 64, tc * 64);
+    for (int64_t tile = block; tile < a.wt_tiles; tile += a.wt_blocks) {
+      const int64_t tc = tile / a.wt_tiles_r, tr = tile - tc * a.wt_tiles_r;
+      if (tile != block) __syncthreads();              // everyone is done with the previous tile's LDS
+      transpose_tile<ST, COMPACT_THREADS>(a.W, a.V, a.d, a.d, a.wt, a.ldz, nullptr, tr * 64, tc * 64);
+    }
   }
 }
 

@@ -393,7 +393,9 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
   u.dH = reinterpret_cast<stt*>(dH); u.d = d;
   u.W = reinterpret_cast<const stt*>(W); u.V = V; u.ldz = w.ldz; u.wt = wt;
   u.wt_tiles_r = w.ldz / 64;
-  const int64_t setup_blocks = u.compact_blocks + u.zero_blocks + (kBf16 ? 0 : u.wt_tiles_r * ((d + 63) / 64));
+  u.wt_tiles = kBf16 ? 0 : u.wt_tiles_r * ((d + 63) / 64);
+  u.wt_blocks = (int)std::min<int64_t>(u.wt_tiles, SETUP_MAX_WT_BLOCKS);
+  const int64_t setup_blocks = (int64_t)u.compact_blocks + u.zero_blocks + u.wt_blocks;
   k_bwd_setup<stt><<<dim3((unsigned)setup_blocks), dim3(COMPACT_THREADS), 0, st>>>(u);
   HIP_TRY(hipGetLastError());
   if (w.n_pass > 1) {

@@ -146,3 +146,21 @@ def test_gradient_of_a_very_unlikely_row(lib, N, V, d):
     # z and lse of about 82 are rounded to 2^-18 each, which is the relative error of p = exp(z - lse) they leave
     for r in rows.tolist():
         assert _rel(dW[r], rdW[r]) <= 2.0 ** -16
+
+
+def test_backward_of_a_head_with_more_transpose_tiles_than_a_launch_holds_blocks(lib):
+    # 16385 x 256 tiles of 64 x 64 for W^T: one 1024-thread block each would be 2^32 threads and more
+    V, d = 1048640, 16384
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 215 << 30:
+        pytest.skip("needs 207 GB of device memory: W, its transpose and dW")
+    W = torch.zeros(V, d, device="cuda")
+    W[-1] = torch.arange(d, device="cuda") % 7
+    H = torch.zeros(1, d, device="cuda")
+    H[0, :64] = torch.arange(64, device="cuda") / 64
+    t = torch.tensor([V - 1], device="cuda").int()
+    dH, dW = lib.offpolicy_loss_bwd(H, W, t, torch.full((1,), float("inf"), device="cuda"), torch.full((1,), 2.0, device="cuda"))
+    assert torch.equal(dH[0], 2.0 * W[-1]) and torch.equal(dW[-1], 2.0 * H[0])        # dz = 2 at the target, 0 elsewhere
+    assert all(not bool(dW[i:i + 65536].any()) for i in range(0, V - 65536, 65536))
+    del W, dW
+    torch.cuda.empty_cache()
