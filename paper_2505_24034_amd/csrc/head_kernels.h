@@ -363,23 +363,23 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_merge_logp(MergeArgs a) {
 // ascending order: deterministic.
 __global__ __launch_bounds__(256) void k_merge_shards(const float* m, const float* s, const float* zt, int shards,
                                                        int64_t N, float* logp, float* lse) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= N) return;
-  float M = -INFINITY;
-  for (int p = 0; p < shards; ++p) M = fmaxf(M, m[(int64_t)p * N + t]);
-  float l = 0.f, lp = 0.f;
-  if (M != -INFINITY) {
-    float S = 0.f, Z = 0.f;
-    for (int p = 0; p < shards; ++p) {
-      const float mp = m[(int64_t)p * N + t];
-      S += (mp == -INFINITY) ? 0.f : s[(int64_t)p * N + t] * expf(mp - M);
-      Z += zt[(int64_t)p * N + t];
+  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < N; t += (int64_t)gridDim.x * 256) {
+    float M = -INFINITY;
+    for (int p = 0; p < shards; ++p) M = fmaxf(M, m[(int64_t)p * N + t]);
+    float l = 0.f, lp = 0.f;
+    if (M != -INFINITY) {
+      float S = 0.f, Z = 0.f;
+      for (int p = 0; p < shards; ++p) {
+        const float mp = m[(int64_t)p * N + t];
+        S += (mp == -INFINITY) ? 0.f : s[(int64_t)p * N + t] * expf(mp - M);
+        Z += zt[(int64_t)p * N + t];
+      }
+      l = M + logf(S);
+      lp = Z - l;
     }
-    l = M + logf(S);
-    lp = Z - l;
+    lse[t] = l;
+    logp[t] = lp;
   }
-  lse[t] = l;
-  logp[t] = lp;
 }
 
 // Active-row list.  mode 0 (forward): row t is active if mask[t] != 0 (mask == nullptr: always) and its target

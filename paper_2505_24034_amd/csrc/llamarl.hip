@@ -221,6 +221,11 @@ int persistent_grid(int64_t tiles, int per_cu = 1) {
   return (int)std::min<int64_t>(tiles, (int64_t)cus * per_cu);
 }
 
+// Blocks of one launch where a block takes one generation or a few prompts (of 256 or 1024 threads): a launch has fewer than
+// 2^32 threads, and HIP gives one that asks for more the count modulo 2^32.  A multiple of 4, so that a later launch's
+// tokens start as aligned as the batch.
+constexpr int64_t LAUNCH_BLOCKS = (int64_t)1 << 20;
+
 #define HIP_TRY(expr)                                                                              \
   do {                                                                                             \
     hipError_t e_ = (expr);                                                                        \
@@ -540,7 +545,7 @@ llamarl_status llamarl_merge_partials(const float* m, const float* s, const floa
   if (!m || !s || !zt || !logp || !lse) return fail(LLAMARL_ERR_INVALID_ARG, "null pointer argument");
   if (shards <= 0 || N <= 0) return fail(LLAMARL_ERR_INVALID_ARG, "shards and N must be positive");
   if (N >= ((int64_t)1 << 39)) return fail(LLAMARL_ERR_UNSUPPORTED, "too many tokens");
-  k_merge_shards<<<dim3((unsigned)((N + 255) / 256)), dim3(256), 0, reinterpret_cast<hipStream_t>(stream)>>>(
+  k_merge_shards<<<dim3((unsigned)std::min((N + 255) / 256, LAUNCH_BLOCKS)), dim3(256), 0, reinterpret_cast<hipStream_t>(stream)>>>(
       m, s, zt, shards, N, logp, lse);
   HIP_TRY(hipGetLastError());
   return LLAMARL_OK;
@@ -589,9 +594,17 @@ static llamarl_status launch_loss_fwd(const float* logp, const float* mu_logp, c
     return LLAMARL_OK;
   }
   const int seq_threads = T > 4096 ? 1024 : 256;
-  (seq_threads == 1024 ? k_seq_lengths<1024> : k_seq_lengths<256>)<<<dim3((unsigned)B), dim3((unsigned)seq_threads), 0, st>>>(
-      a);                                                                     // also clears the ticket
-  HIP_TRY(hipGetLastError());
+  for (int64_t b = 0; b < B; b += LAUNCH_BLOCKS) {
+    LossArgs part = a;
+    part.B = std::min(B - b, LAUNCH_BLOCKS);
+    if (mask) part.mask += b * T;
+    if (targets) part.targets += b * T;
+    part.seq_len += b;
+    part.seq_bad += b;
+    (seq_threads == 1024 ? k_seq_lengths<1024> : k_seq_lengths<256>)<<<dim3((unsigned)part.B), dim3((unsigned)seq_threads), 0,
+                                                                       st>>>(part);   // also clears the ticket
+    HIP_TRY(hipGetLastError());
+  }
   (w.threads == 1024 ? k_loss_tokens<1024> : k_loss_tokens<256>)<<<dim3((unsigned)w.nblocks), dim3((unsigned)w.threads), 0,
                                                                    st>>>(a);   // its last block writes loss, stats
   HIP_TRY(hipGetLastError());
@@ -766,9 +779,12 @@ llamarl_status llamarl_group_advantages(const float* rewards, int64_t P, int64_t
   if (P <= 0 || n <= 0) return fail(LLAMARL_ERR_INVALID_ARG, "P and n must be positive");
   if (P >= ((int64_t)1 << 31) * 4) return fail(LLAMARL_ERR_UNSUPPORTED, "too many prompts");
   if (normalise_std && !(eps >= 0.f)) return fail(LLAMARL_ERR_INVALID_ARG, "eps must be non-negative");
-  k_group_advantages<<<dim3((unsigned)((P + 3) / 4)), dim3(256), 0, reinterpret_cast<hipStream_t>(stream)>>>(
-      rewards, P, n, normalise_std, eps, adv);
-  HIP_TRY(hipGetLastError());
+  for (int64_t p = 0; p < P; p += LAUNCH_BLOCKS * 4) {
+    const int64_t prompts = std::min(P - p, LAUNCH_BLOCKS * 4);
+    k_group_advantages<<<dim3((unsigned)((prompts + 3) / 4)), dim3(256), 0, reinterpret_cast<hipStream_t>(stream)>>>(
+        rewards + p * n, prompts, n, normalise_std, eps, adv + p * n);
+    HIP_TRY(hipGetLastError());
+  }
   return LLAMARL_OK;
 }
 
@@ -780,12 +796,15 @@ llamarl_status llamarl_kl_shaped_rewards(const float* rewards, const float* logp
   if (B >= (int64_t)1 << 31) return fail(LLAMARL_ERR_UNSUPPORTED, "too many generations");
   if (!(lambda_kl == lambda_kl)) return fail(LLAMARL_ERR_INVALID_ARG, "lambda_kl is NaN");
   const int aligned = aligned16(logp) && aligned16(base_logp) && (reinterpret_cast<uintptr_t>(mask) & 3u) == 0;
-  // a grid has fewer than 2^32 threads
-  const int threads = T > 2048 && B * 1024 < (int64_t)1 << 32 ? 1024 : 256;
-  (threads == 1024 ? k_kl_shaped_rewards<1024> : k_kl_shaped_rewards<256>)<<<
-      dim3((unsigned)B), dim3((unsigned)threads), 0, reinterpret_cast<hipStream_t>(stream)>>>(
-      rewards, logp, base_logp, mask, B, T, aligned, lambda_kl, shaped, kl);
-  HIP_TRY(hipGetLastError());
+  const int threads = T > 2048 ? 1024 : 256;
+  for (int64_t b = 0; b < B; b += LAUNCH_BLOCKS) {
+    const int64_t n = std::min(B - b, LAUNCH_BLOCKS), t = b * T;
+    (threads == 1024 ? k_kl_shaped_rewards<1024> : k_kl_shaped_rewards<256>)<<<
+        dim3((unsigned)n), dim3((unsigned)threads), 0, reinterpret_cast<hipStream_t>(stream)>>>(
+        rewards + b, logp + t, base_logp + t, mask ? mask + t : nullptr, n, T, aligned, lambda_kl, shaped + b,
+        kl ? kl + b : nullptr);
+    HIP_TRY(hipGetLastError());
+  }
   return LLAMARL_OK;
 }
 

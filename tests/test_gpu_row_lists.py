@@ -60,15 +60,55 @@ def test_kl_sums_at_any_alignment(lib, B, T, with_mask):
         assert torch.equal(shaped, s2) and torch.equal(kl, k2)
 
 
-def test_kl_sums_of_a_launch_limit_of_generations(lib):
-    # a grid has fewer than 2^32 threads: 2^22 generations cannot have 1024 each
-    B, T = 1 << 22, 2049
-    if torch.cuda.mem_get_info()[0] < 80 << 30:
-        pytest.skip("needs 70 GB of device memory")
+# A launch has fewer than 2^32 threads: larger batches take several.
+def _room(gib):
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < gib << 30:
+        pytest.skip("needs %d GiB of device memory" % gib)
+
+
+@pytest.mark.parametrize("B,T", [(1 << 22, 2049), ((1 << 24) + 5, 3), ((1 << 20) + 7, 2)])
+def test_kl_sums_of_many_generations(lib, B, T):
+    _room(8 * B * T // 2 ** 30 + 4)
     lp = torch.full((B, T), 0.25, device="cuda")
     base = torch.zeros(B, T, device="cuda")
     r = torch.arange(B, device="cuda", dtype=torch.float32)
     shaped, kl = lib.kl_shaped_rewards(r, lp, base, None, 0.5)
-    assert bool((kl == 0.25 * T).all()) and torch.equal(shaped.double(), (r.double() - 0.125 * T).float().double())
+    ok = bool((kl == 0.25 * T).all()), torch.equal(shaped, (r.double() - 0.125 * T).float())
+    assert all(ok)                                                  # (pytest would print the tensors)
     del lp, base
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("B", [(1 << 20) + 7, (1 << 24) + 5])
+def test_loss_of_many_generations(lib, B):
+    T = 2
+    t = torch.arange(B, device="cuda")
+    mask = torch.stack([torch.ones_like(t), t % 3 == 0], dim=1).to(torch.uint8).contiguous()      # lengths 2, 1, 1, 2, ..
+    logp = torch.full((B * T,), -1.0, device="cuda")
+    loss, coef, stats = lib.offpolicy_loss_fwd(logp, logp, torch.ones(B, device="cuda"), mask, B, T, norm_mode=lib.NORM_SEQ_MEAN)
+    per = torch.where(t % 3 == 0, 0.5, 1.0).double()[:, None] / B * mask.double()
+    assert float((coef.double().view(B, T) + per).abs().max()) <= 2.0 ** -22 / B
+    assert abs(float(loss) - 1.0) <= 1e-6 and float(stats[0]) == float(mask.sum().float()) and float(stats[4]) == 0
+
+
+@pytest.mark.parametrize("P", [(1 << 22) + 3, (1 << 26) + 3])
+def test_advantages_of_many_prompts(lib, P):
+    r = torch.arange(2 * P, device="cuda").remainder(1 << 20).float()
+    adv = lib.group_advantages(r, 2)
+    d = (r.view(P, 2)[:, 0] - r.view(P, 2)[:, 1]) / 2
+    ok = torch.equal(adv.view(P, 2), torch.stack([d, -d], dim=1))
+    assert ok
+
+
+@pytest.mark.parametrize("N", [(1 << 28) + 257, (1 << 32) + 257])
+def test_merge_of_many_tokens(lib, N):
+    _room(22 * N // 2 ** 30 + 4)
+    m = torch.full((1, N), -2.0, device="cuda")
+    s = torch.ones(1, N, device="cuda")
+    zt = torch.full((1, N), -3.0, device="cuda")
+    logp, lse = lib.merge_partials(m, s, zt)
+    ok = bool((lse == -2.0).all()), bool((logp == -1.0).all())
+    assert all(ok)
+    del m, s, zt, logp, lse
     torch.cuda.empty_cache()
