@@ -3,13 +3,14 @@ picks the tile, and the 256 x 256 loops at one, two and three slabs, against flo
 import pytest
 import torch
 
-from test_gpu_f32_tiles import _inputs, _reference, _rel
+from test_gpu_f32_tiles import _inputs, _reference, _rel, _worst
 
 pytestmark = pytest.mark.gpu
 
 
 # logits: bf16 products are exact in fp32, see the fp32 bound; gradients: dz and the results are rounded to bf16 once
-# each, 2^-9 relative at most and independent per entry: 2 x 2^-9 bounds either result's relative error
+# each, 2^-9 relative at most and independent per entry: 2 x 2^-9 bounds either result's relative error; twice that for a
+# single row or column, whose sum can cancel to a fraction of its terms
 @pytest.mark.parametrize("N,V,d", [
     (1, 64, 8), (64, 63, 64), (65, 129, 72), (127, 1025, 136), (129, 257, 200),       # 64-tiles
     (256, 8065, 64), (383, 5300, 136), (500, 24000, 72),                               # 128-tiles
@@ -31,8 +32,9 @@ def test_tile_edges(lib, N, V, d, masked):
     assert float((logp.double() - rlogp).abs().max()) <= 16 * bound + 2e-6
     dH, dW = lib.offpolicy_loss_bwd(H, W, t, lse, coef)
     assert _rel(dH, rdH) <= 2.0 ** -8 and _rel(dW, rdW) <= 2.0 ** -8
+    assert _worst(dH, rdH) <= 2.0 ** -7 and _worst(dW, rdW) <= 2.0 ** -7
     _, dW32 = lib.offpolicy_loss_bwd(H, W, t, lse, coef, dW_dtype=torch.float32)
-    assert _rel(dW32, rdW) <= 2.0 ** -8
+    assert _rel(dW32, rdW) <= 2.0 ** -8 and _worst(dW32, rdW) <= 2.0 ** -7
     total = dW32.clone()
     lib.offpolicy_loss_bwd(H, W, t, lse, coef, dW=total, accumulate_dW=True)
     assert torch.equal(total, 2 * dW32)
@@ -53,3 +55,4 @@ def test_narrow_last_token_column(lib, N, d):
     assert float((logp.double() - rlogp).abs().max()) <= 16 * bound + 2e-6
     dH, dW = lib.offpolicy_loss_bwd(H, W, t, lse, coef)
     assert _rel(dH, rdH) <= 2.0 ** -8 and _rel(dW, rdW) <= 2.0 ** -8
+    assert _worst(dH, rdH) <= 2.0 ** -7 and _worst(dW, rdW) <= 2.0 ** -7

@@ -1,5 +1,6 @@
-"""The loss forward at the sizes where its launches change: one workgroup (up to 16384 tokens and 1024 generations)
-against several, generation lengths that no group of four tokens or wavefront lines up with, the grid's stride."""
+"""The loss forward at the sizes where its launches change: one workgroup (up to 8192 tokens and 1024 generations; the
+second half of them in a second group of four a thread) against several, generation lengths that no group of four tokens
+or wavefront lines up with, the grid's stride."""
 import numpy as np
 import pytest
 import torch
@@ -10,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("B,T", [(1, 1), (1, 3), (3, 1), (1024, 1), (1025, 1), (5, 7), (1000, 3), (63, 65), (4, 255), (3, 257),
-                                 (1, 16383), (1, 16384), (16, 1024), (7, 2341), (2, 8193), (1024, 17), (5, 4099),
+                                 (1, 4096), (1, 4097), (3, 2049), (63, 67), (7, 1170), (1000, 8), (1, 8191), (1, 8192),
+                                 (2, 4096), (1024, 8), (1, 8193), (1025, 7), (1, 16383),
+                                 (1, 16384), (16, 1024), (7, 2341), (2, 8193), (1024, 17), (5, 4099),
                                  (2, 1100001)])
 @pytest.mark.parametrize("norm,clip,per_token,with_mask,with_targets",
                          [(0, 0, False, True, True), (1, 1, True, True, False), (2, 0, True, False, False),
