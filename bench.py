@@ -384,8 +384,9 @@ def main():
         "roofline": {"bound": "mfma", "kernel": dom["kernel"], "achieved": dom["achieved"],
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": dom["frac"],
                      "measured_ceiling": ceil_tflops, "frac_of_measured_ceiling": dom["achieved"] / ceil_tflops,
-                     "traffic": measured_traffic(dom["kernel"].split()[0].split("<")[0] +
-                                                 ("<llamarl::BF16, true" if "k-major" in dom["kernel"] else ""))
+                     "traffic": measured_traffic(
+                         "k_gemm_store<llamarl::TileGemmTN" if "k-major" in dom["kernel"] else
+                         "k_gemm_store<llamarl::TileGemm<" if "dW" in dom["kernel"] else dom["kernel"].split()[0])
                      if w.name == "llama3_8b" else None,
                      "traffic_note": "bytes per launch between L2 and fabric, rocprofv3 FETCH_SIZE x2.0 + WRITE_SIZE "
                                      "x1.0 (plain-copy calibration; includes Infinity-Cache hits); read from "

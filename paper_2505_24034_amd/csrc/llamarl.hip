@@ -45,8 +45,8 @@ inline int64_t tile_count(int64_t rows, int64_t cols, int64_t edge) {
 // Logits kernels (forward, recompute): N x V outputs.
 //   bf16, dz at (N, V, d) on 256- / 128- / 64-tiles: (512, 2048, 512) 22 / 16 / 12 us, (512, 8192, 1024) 30 / 18 / 22,
 //   (1041, 5003, 520) 26 / 18 / 26, (1024, 8192, 1024) 30 / 24 / 39, (1024, 16032, 2048) 58 / 70 / 115.
-//   fp32, forward on 128- / 64-tiles: (512, 2048, 512) 39 / 26 us, (512, 4096, 512) 39 / 33, (1024, 4096, 512) 40 / 53,
-//   (2048, 8192, 512) 105 / 180.
+//   fp32, dz on 128- / 64-tiles: (512, 2048, 512) 44 / 26 us, (512, 4096, 512) 45 / 34, (1024, 4096, 512) 48 / 57,
+//   (2048, 8192, 512) 127 / 206.
 constexpr int LOGITS_MIN_TILES = 192, LOGITS_MIN_TILES_BF16_128 = 128;   // of the larger edge; fewer: the next smaller one
 Tile logits_tile(int64_t N, int64_t V, llamarl_dtype dt) {
   if (dt == LLAMARL_BF16 && tile_count(N, V, 256) >= LOGITS_MIN_TILES) return TILE_256;
@@ -57,8 +57,8 @@ Tile logits_tile(int64_t N, int64_t V, llamarl_dtype dt) {
 //   bf16, dH at (N, V, d) on 256- / 128- / 64-tiles: (512, 2048, 512) 23 / 17.5 / 17 us, (1041, 5003, 520) 33 / 26 / 29,
 //   (1024, 8192, 1024) 42 / 36 / 43, (64, 128256, 4096) 337 / 236 / 229, (1024, 16032, 2048) 77 / 79 / 125;
 //   dW: (512, 2048, 512) 23 / 19 / 16, (512, 8192, 1024) 38 / 17 / 25, (1024, 16032, 2048) 67 / 73 / 131.
-//   fp32 on 128- / 64-tiles, dH: (512, 4096, 512) 39 / 32, (1024, 4096, 512) 42 / 50, (300, 16400, 260) 113 / 59;
-//   dW: (512, 4096, 512) 32 / 28, (1024, 4096, 512) 43 / 46, (300, 16400, 260) 40 / 48.
+//   fp32 on 128- / 64-tiles, dH: (512, 4096, 512) 45 / 35, (1024, 4096, 512) 49 / 57, (300, 16400, 260) 137 / 69;
+//   dW: (512, 4096, 512) 35 / 31, (1024, 4096, 512) 48 / 52, (300, 16400, 260) 43 / 54.
 Tile store_tile(int64_t M, int64_t Nn, int64_t K, llamarl_dtype dt) {
   const int64_t slab_k = dt == LLAMARL_BF16 ? 64 : 32;
   const int64_t parts = std::min<int64_t>(STORE_MAX_SPLITS, std::max<int64_t>(1, K / (16 * slab_k)));
