@@ -31,7 +31,6 @@ namespace llamarl {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
-typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
 constexpr int NB = 4;         // 16 x 16 MFMA blocks per wave along N (64 cols), in every tile shape
 constexpr int WAVE_N = NB * 16;
@@ -139,6 +138,7 @@ __device__ __forceinline__ int tile_row_of(int r) {
 struct TileSchedule {
   int tiles_m, tiles_n, group_m;
   int next_id, end_id, stride;
+  bool turn;               // see coords
   // group_m_: rows of a patch.  The 32 workgroups of an XCD work on 32 consecutive ids = group_m x (32 / group_m)
   // tiles, which load group_m A panels and 32 / group_m B panels: a B panel is shared by group_m tiles, an A panel
   // by 32 / group_m.  Give the larger share to the operand that has to come from HBM.
@@ -149,6 +149,7 @@ struct TileSchedule {
     const int ntiles = tiles_m * tiles_n;
     const int bid = blockIdx.x, nblk = gridDim.x;
     const int xcd = bid & 7, local = bid >> 3;
+    turn = nblk % (group_m * tiles_n) == 0;
     if ((nblk & 7) == 0) {
       // Patches dealt round-robin over the XCDs: in round k XCD x works on patch 8 k + x, so the eight patches in
       // flight are neighbours in id order and share operand panels through the Infinity Cache.
@@ -181,8 +182,7 @@ struct TileSchedule {
     // Where a round of the grid is a whole number of groups, a workgroup would get the same column in every round:
     // turn the columns by one a round, so that nobody is left with all the narrow last columns (two columns, 300
     // tokens: half of the workgroups had four full tiles, the other half four of 44 tokens).
-    const int nblk = gridDim.x;
-    if (nblk % per_group == 0) tn = (tn + id / nblk) % tiles_n;
+    if (turn) tn = (tn + id / (int)gridDim.x) % tiles_n;
   }
 };
 
@@ -196,6 +196,17 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds_addr, uint32_t voff, i32x
                :
                : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
                : "memory", "m0");
+}
+
+// as lds_dma16, four bytes a lane: 64 neighbouring words of LDS
+__device__ __forceinline__ void lds_dma4(uint32_t lds_addr, uint32_t voff, i32x4_t rsrc) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+               :
+               : "s"(lds_addr), "v"(voff), "s"(rsrc)
+               : "memory", "m0");
+}
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)(const char*)p;
 }
 
 __device__ __forceinline__ int swizzle(int row) { return (row >> 1) & 7; }
@@ -219,11 +230,6 @@ struct SlabLoader {
     base_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32));
     records = (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes);
   }
-  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc() const {
-    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((uint64_t)base_hi << 32) | base_lo), 0,
-                                             (int)records, 0x00020000);
-  }
-
   __device__ __forceinline__ static int lane_chunk(int wave, int lane) {
     return (lane & 7) ^ swizzle(wave * 8 + (lane >> 3));
   }
@@ -259,29 +265,17 @@ struct SlabLoader {
     for (int it = 0; it < ITERS; ++it)
       voff[it] = (lane_tile_row<QUAD>(it, wave, lane) < rows_valid) ? (uint32_t)grow[it] * row_bytes + c16 : OOB_OFFSET;
   }
-  // k0: first k of the slab (elements); K: contraction length.  lds: start of this operand's slab in LDS.
-  // tail: the slab may reach past K (only the last slab of a contraction whose K is not a multiple of the slab
-  // depth): lanes whose chunk lies past K fetch nothing.
-  __device__ __forceinline__ void issue_one(char* lds, int it, int k0, int K, int wave, int lane, bool tail) const {
-    const int soff = k0 * (int)sizeof(typename TT::store_t);
-    uint32_t v = voff[it];
-    if (tail) v = (k0 + lane_chunk(wave, lane) * TT::EPC >= K) ? OOB_OFFSET : v;   // `tail` is a constant once inlined
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc(), (lds_void_ptr)(lds + (it * WAVES + wave) * 8 * SLAB_ROW_BYTES), 16,
-                                             (int)v, soff, 0, 0);
-  }
-  // all of a slab's loads, hidden from the compiler's wait-count pass (lds_dma16)
-  __device__ __forceinline__ void issue_opaque(char* lds, int k0, int K, int wave, int lane) const {
+  // One request of a slab (lds_dma16).  k0: first k of the slab (elements); K: contraction length; lds: start of this
+  // operand's slab in LDS.  Lanes whose chunk lies past K fetch nothing (zeros); no slab reaches past K if !tail.
+  __device__ __forceinline__ void issue_one(char* lds, int it, int k0, int K, int wave, int lane, bool tail = true) const {
     const i32x4_t rs = {(int)base_lo, (int)(base_hi & 0xffffu), (int)records, 0x00020000};
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-    const bool past = k0 + lane_chunk(wave, lane) * TT::EPC >= K;
-#pragma unroll
-    for (int it = 0; it < ITERS; ++it)
-      lds_dma16(lds0 + (uint32_t)((it * WAVES + wave) * 8 * SLAB_ROW_BYTES), past ? OOB_OFFSET : voff[it], rs,
-                (uint32_t)k0 * (uint32_t)sizeof(typename TT::store_t));
+    lds_dma16(lds_address(lds) + (uint32_t)((it * WAVES + wave) * 8 * SLAB_ROW_BYTES),
+              tail && k0 + lane_chunk(wave, lane) * TT::EPC >= K ? OOB_OFFSET : voff[it], rs,
+              (uint32_t)k0 * (uint32_t)sizeof(typename TT::store_t));
   }
   __device__ __forceinline__ void issue(char* lds, int k0, int K, int wave, int lane) const {
 #pragma unroll
-    for (int it = 0; it < ITERS; ++it) issue_one(lds, it, k0, K, wave, lane, true);
+    for (int it = 0; it < ITERS; ++it) issue_one(lds, it, k0, K, wave, lane);
   }
 };
 
@@ -322,7 +316,8 @@ __device__ __forceinline__ constexpr int snake_col(int t) { return ((t >> 2) & 1
 //            called from ONE function instantiation only -- the host pass of hipcc (ROCm 7.2) rejects a second
 //            caller of the same specialisation ("substitution failure", no reason given; the device pass accepts it).
 //   YOUNGER: vector-memory operations issued after the next slab's loads that the barrier need not wait for.
-template <typename TT, bool BAR, bool NEXT, bool FETCH, int LS, int YOUNGER = 0>
+//   INIT   : a tile's first k-step; the accumulators start here (as zero), so that no pass clears them.
+template <typename TT, bool BAR, bool NEXT, bool FETCH, int LS, int YOUNGER = 0, bool INIT = false>
 __device__ __forceinline__ void k_step(typename TT::frag_t (&a)[MB], const typename TT::frag_t (&bc)[NB],
                                        typename TT::frag_t (&bn)[NB], f32x4_t (&acc)[MB][NB], const char* pa_cur,
                                        const char* pa_nxt, const char* pb_nxt, const SlabFetch<TT>* sf) {
@@ -337,6 +332,7 @@ __device__ __forceinline__ void k_step(typename TT::frag_t (&a)[MB], const typen
       __syncthreads();            // everyone's has, and everyone is done reading this slab
       LLAMARL_FENCE();
     }
+    if (INIT) acc[ib][jb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     mma(a[ib], bc[jb], acc[ib][jb]);
     LLAMARL_FENCE();
     if (t == 0) {
@@ -355,8 +351,8 @@ __device__ __forceinline__ void k_step(typename TT::frag_t (&a)[MB], const typen
     }
     if (FETCH && t >= LS && t <= LS + 14 && ((t - LS) & 1) == 0) {
       const int n = (t - LS) >> 1;
-      if (n < 4) sf->la->issue_one(sf->dst, n, sf->k0, sf->K, sf->wave, sf->lane, true);
-      else sf->lb->issue_one(sf->dst + SLAB_A_BYTES, n - 4, sf->k0, sf->K, sf->wave, sf->lane, true);
+      if (n < 4) sf->la->issue_one(sf->dst, n, sf->k0, sf->K, sf->wave, sf->lane);
+      else sf->lb->issue_one(sf->dst + SLAB_A_BYTES, n - 4, sf->k0, sf->K, sf->wave, sf->lane);
       LLAMARL_FENCE();
     }
   }
@@ -371,7 +367,8 @@ __device__ __forceinline__ void k_step(typename TT::frag_t (&a)[MB], const typen
 //
 // QUAD_B: output columns are quad-interleaved over the lane's four column blocks
 // (tile_row_of); the epilogue must then take its columns from LanePos::col_quad().
-template <typename TT, int LOAD_SLOT = 11>
+// YOUNGER, FIRST_ONLY: see run().
+template <typename TT, int LOAD_SLOT, int YOUNGER, bool FIRST_ONLY>
 struct TileGemm {
   typedef TT Type;
   typedef Shape256 Shape;
@@ -401,21 +398,26 @@ struct TileGemm {
 
   // as prefetch, the B panel gathered: B_base is the base of the whole matrix with b_total rows, grow the gather list
   // entries of this lane (SlabLoader::init_gathered), already in registers: no global load stands between the
-  // caller's barrier and the first slab request
+  // caller's barrier and the first slab request.  The requests are the caller's: issue_first(0) .. (FIRST_PARTS - 1).
   template <bool QUAD_B>
-  __device__ __forceinline__ void prefetch_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
-                                                    int64_t ldb, int rowsB, int64_t K_, char* smem, const int (&grow)[4],
-                                                    int64_t b_total) {
+  __device__ __forceinline__ void setup_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
+                                                 int64_t ldb, int rowsB, int64_t K_, const int (&grow)[4],
+                                                 int64_t b_total) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
     la.init(A_tile, lda, rowsA, wave, lane);
     lb.template init_gathered<QUAD_B>(B_base, ldb, b_total, grow, rowsB, wave, lane);
-    la.issue(smem, 0, K, wave, lane);
-    lb.issue(smem + SLAB_A_BYTES, 0, K, wave, lane);
-    if (K > BK) {
-      la.issue(smem + STAGE_BYTES, BK, K, wave, lane);
-      lb.issue(smem + STAGE_BYTES + SLAB_A_BYTES, BK, K, wave, lane);
-    }
+  }
+  // Four requests a call, so that a logits kernel can spread them over its epilogue: sixteen at once (128 KB for the
+  // workgroup) keep a wavefront from its epilogue for as long as the CU takes to accept them.
+  static constexpr int FIRST_PARTS = 4;
+  __device__ __forceinline__ void issue_first(char* smem, int part) const {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    char* st = smem + (part >> 1) * STAGE_BYTES;
+    const int k0 = (part >> 1) * BK;
+    if (k0 >= K && part > 1) return;
+    if ((part & 1) == 0) la.issue(st, k0, K, wave, lane);
+    else lb.issue(st + SLAB_A_BYTES, k0, K, wave, lane);
   }
 
   // Instead of run() for a wavefront whose whole part of the tile lies past the matrix (wave-uniform; a last column of
@@ -440,21 +442,15 @@ struct TileGemm {
     }
   }
 
-  // YOUNGER > 0: if `counted` (workgroup-uniform), at least YOUNGER vector-memory operations -- the previous tile's
-  // stores -- were issued after prefetch().  vmcnt counts in order, so slabs 0 and 1 are waited for without them; the
-  // stores then drain under the first slabs.  dW over a 128256 x 4096 head: 64 rows 295 -> 273 us, 300 rows 587 -> 528,
-  // 1100 rows 1183 -> 1124, 8576 rows -0.8 %.  (No gain for the recompute, whose epilogue is longer than its stores.)
-  template <int YOUNGER = 0>
+  static constexpr int COUNTED_STORES = YOUNGER;
+  // If `counted` (wave-uniform), at least YOUNGER vector-memory operations -- the previous tile's stores -- were issued
+  // after prefetch().  vmcnt counts in order, so slabs 0 and 1 are waited for without them; the stores then drain under
+  // the first slabs.  dW over a 128256 x 4096 head: 64 rows 295 -> 273 us, 300 rows 587 -> 528, 1100 rows 1183 -> 1124,
+  // 8576 rows -0.8 %.  (No gain for the recompute, whose epilogue is longer than its stores.)
+  // FIRST_ONLY: only the first wait is counted, for a few stores (the forward's).
   __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[MB][NB], bool counted = false) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int wm = Shape::wave_row(wave), wn = Shape::wave_col(wave);
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int j = 0; j < NB; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
-
     const int nk = (K + BK - 1) / BK;
     // per-lane read addresses of block 0: row = lane % 16, chunk 4 ks + lane / 16 of k-step ks, swizzled.  The
     // swizzle depends on the low four row bits only, so block ib is the same address + ib * BLOCK_BYTES.
@@ -468,7 +464,7 @@ struct TileGemm {
     }
     // Slabs 0 and 1 were issued by prefetch(); stores of a previous epilogue may sit between them and now in the
     // vmcnt queue.  Where their number is not known, wait for everything.
-    if (YOUNGER > 0 && counted) wait_vmcnt<YOUNGER>();
+    if (counted) wait_vmcnt<YOUNGER>();
     else wait_vmcnt0();
     __syncthreads();
     frag_t a[MB], b0[NB], b1[NB];
@@ -478,44 +474,40 @@ struct TileGemm {
 #pragma unroll
     for (int i = 1; i < MB - 1; ++i) a[i] = *reinterpret_cast<const frag_t*>(smem + a_addr[0] + i * BLOCK_BYTES);
 
-    // slabs 0 .. nk-3 fetch slab kt+2 after their barrier; slab nk-2 (nothing left to fetch) and the last slab
-    // follow, written out one after the other (a branch inside one loop body makes the compiler copy accumulators)
+    // One turn of the loop: a slab's second k-step, then the next slab's first.  Slabs 0 .. nk-3 fetch slab kt+2 after
+    // their barrier; slab nk-2 (nothing left to fetch) and the last slab follow, written out one after the other (a
+    // branch inside one loop body makes the compiler copy accumulators)
+    LLAMARL_FENCE();
+    k_step<TT, false, true, false, LOAD_SLOT, 0, true>(a, b0, b1, acc, smem + a_addr[0], smem + a_addr[1],
+                                                       smem + b_addr[1], nullptr);
     int kt0 = 0;
-    if (YOUNGER > 0 && nk > 2) {       // slab 0 apart: its barrier waits for slab 1, which is older than the stores too
+    if (!FIRST_ONLY && nk > 2) {       // slab 0 apart: its barrier waits for slab 1, older than the stores too
       char* cur = smem;
       const char* nxt = smem + STAGE_BYTES;
-      LLAMARL_FENCE();
-      k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, cur + a_addr[0], cur + a_addr[1], cur + b_addr[1],
-                                                nullptr);
       const SlabFetch<TT> sf{&la, &lb, cur, 2 * BK, K, wave, lane};
-      k_step<TT, true, true, true, LOAD_SLOT, YOUNGER>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0],
-                                                       nxt + b_addr[0], &sf);
+      k_step<TT, true, true, true, LOAD_SLOT, FIRST_ONLY ? 0 : YOUNGER>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0],
+                                                                        nxt + b_addr[0], &sf);
+      k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
       kt0 = 1;
     }
     for (int kt = kt0; kt < nk - 2; ++kt) {
       char* cur = smem + (kt & 1) * STAGE_BYTES;
       const char* nxt = smem + ((kt + 1) & 1) * STAGE_BYTES;
       LLAMARL_FENCE();
-      k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, cur + a_addr[0], cur + a_addr[1], cur + b_addr[1],
-                                                nullptr);
       const SlabFetch<TT> sf{&la, &lb, cur, (kt + 2) * BK, K, wave, lane};
-      k_step<TT, true, true, true, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0], nxt + b_addr[0],
-                                              &sf);
+      k_step<TT, true, true, true, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0], nxt + b_addr[0], &sf);
+      k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
     }
     if (nk >= 2) {
       const char* cur = smem + ((nk - 2) & 1) * STAGE_BYTES;
       const char* nxt = smem + ((nk - 1) & 1) * STAGE_BYTES;
       LLAMARL_FENCE();
-      k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, cur + a_addr[0], cur + a_addr[1], cur + b_addr[1],
-                                                nullptr);
-      k_step<TT, true, true, false, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0], nxt + b_addr[0],
-                                               nullptr);
+      k_step<TT, true, true, false, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0], nxt + b_addr[0], nullptr);
+      k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
     }
     {
       const char* cur = smem + ((nk - 1) & 1) * STAGE_BYTES;
       LLAMARL_FENCE();
-      k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, cur + a_addr[0], cur + a_addr[1], cur + b_addr[1],
-                                                nullptr);
       k_step<TT, false, false, false, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nullptr, nullptr, nullptr);
     }
   }

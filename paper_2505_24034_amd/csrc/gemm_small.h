@@ -59,7 +59,7 @@ __device__ __forceinline__ Split3 split3(const f32x4_t& x0, const f32x4_t& x1, u
   return Split3{__builtin_bit_cast(bf16x8_t, h), __builtin_bit_cast(bf16x8_t, m), __builtin_bit_cast(bf16x8_t, l)};
 }
 
-// Same interface as TileGemm (prefetch / prefetch_gathered / run).  NSTAGE slabs are resident, NSTAGE - 1 of them in
+// Same interface as TileGemm (prefetch / setup_gathered, issue_first / run).  NSTAGE slabs are resident, NSTAGE - 1 of them in
 // flight; smem must hold LDS_BYTES.
 template <typename TT, typename S, int NSTAGE, int GROUPS_PER_CU_>
 struct TileGemmSmall {
@@ -83,8 +83,8 @@ struct TileGemmSmall {
   // loads in flight is the same in every iteration and the waits can count them.
   __device__ __forceinline__ void issue(char* stage, int kt) const {
     const int lane = threadIdx.x & 63, wave = wave_id();
-    la.issue_opaque(stage, kt * BK, K, wave, lane);
-    lb.issue_opaque(stage + S::SLAB_A_BYTES, kt * BK, K, wave, lane);
+    la.issue(stage, kt * BK, K, wave, lane);
+    lb.issue(stage + S::SLAB_A_BYTES, kt * BK, K, wave, lane);
   }
   __device__ __forceinline__ void first_slabs(char* smem) const {
 #pragma unroll
@@ -101,15 +101,16 @@ struct TileGemmSmall {
     first_slabs(smem);
   }
   template <bool QUAD_B>
-  __device__ __forceinline__ void prefetch_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
-                                                    int64_t ldb, int rowsB, int64_t K_, char* smem,
-                                                    const int (&grow)[LoaderB::ITERS], int64_t b_total) {
+  __device__ __forceinline__ void setup_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
+                                                 int64_t ldb, int rowsB, int64_t K_, const int (&grow)[LoaderB::ITERS],
+                                                 int64_t b_total) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
     la.init(A_tile, lda, rowsA, wave, lane);
     lb.template init_gathered<QUAD_B>(B_base, ldb, b_total, grow, rowsB, wave, lane);
-    first_slabs(smem);
   }
+  static constexpr int FIRST_PARTS = 1;
+  __device__ __forceinline__ void issue_first(char* smem, int) const { first_slabs(smem); }
 
   __device__ __forceinline__ static void clear(f32x4_t (&acc)[S::MB][NB]) {
 #pragma unroll

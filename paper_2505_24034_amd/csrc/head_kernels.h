@@ -82,12 +82,16 @@ struct FwdArgs {
   float* part_s;          // [tiles_v][n_pad] sum of exp(logit - max)
   float* zt;              // [n_pad] target logit, written by the one tile that holds vocab row y_t
   const int32_t* rows;    // [n_act] active token rows, ascending: position p of the compacted list is token rows[p]
+  const int32_t* row_targets;  // [n_act] their targets
   const int32_t* n_act;   // device scalar
 };  // partials and zt are indexed by compacted position, not by token
 
-// One tile's main loop; a wavefront with no part in the tile only takes part in its loads (256 x 256 loops).
+typedef TileGemm<BF16, 11, 2, true> Logits256;      // counted: the two stores of a token's partials
+// One tile's main loop; a wavefront with no part in the tile only takes part in its loads (256 x 256 loops).  counted:
+// the loop's COUNTED_STORES were issued since the tile was fetched (TileGemm::run).
 template <typename G>
-__device__ __forceinline__ void run_or_idle(G& g, char* smem, f32x4_t (&acc)[G::Shape::MB][NB], bool idle) {
+__device__ __forceinline__ void run_or_idle(G& g, char* smem, f32x4_t (&acc)[G::Shape::MB][NB], bool idle,
+                                            bool counted = false) {
   if constexpr (G::HAS_IDLE) {
     if (idle) {                                      // wave-uniform
 #pragma unroll
@@ -98,48 +102,82 @@ __device__ __forceinline__ void run_or_idle(G& g, char* smem, f32x4_t (&acc)[G::
       return;
     }
   }
-  g.run(smem, acc);
+  if constexpr (std::is_same<G, Logits256>::value) g.run(smem, acc, counted);
+  else g.run(smem, acc);
 }
 
-// token columns of tile `id` that hold active rows
-template <typename G>
-__device__ __forceinline__ int columns_left(const TileSchedule& sch, int id, int n_act) {
+// A tile of the logits kernels: rows [256 tv, ..) of W (256: the tile's edge), list positions [256 tt, ..).
+struct LogitsTile {
   int tv, tt;
-  sch.coords(id, tv, tt);
-  return n_act - tt * G::Shape::BN;
-}
-// The logits kernels gather their column operand (H rows) through the active-row list.  The list entries a lane
-// needs for a tile are loaded in ONE batch, branch-free (indices clamped into the list), before the barrier that
-// ends the previous tile; the compiler otherwise serialises them, each behind its own s_waitcnt, and puts them
-// between the barrier and the slab requests.
-template <bool QUAD, typename G, typename Args>
-__device__ __forceinline__ void gather_rows(const TileSchedule& sch, const Args& a, int id, int n_act,
-                                            int (&grow)[decltype(G::lb)::ITERS]) {
-  int tv, tt;
-  sch.coords(id, tv, tt);
+  __device__ __forceinline__ void take(TileSchedule& sch) {
+    sch.coords(sch.take(), tv, tt);
+    asm volatile("" : "+s"(tv), "+s"(tt));           // divided out here, under an epilogue, not where they are used
+  }
+};
+// What a tile of the logits kernels needs per token is in list order in memory (compact_rows) and goes through LDS: the
+// words of the tile's BN list positions from t0 on, of each of LISTS lists, fetched with the tile's first slabs and there
+// when its main loop starts: no global load stands between two tiles.  Loaded at the boundary, through the row list, they
+// were two dependent trips to memory; with accumulators that are not cleared, requests spread over the epilogue and no
+// wait but the loop's own, a tile of 10188 tokens x 128256 entries takes 1.1 - 2 us less (forward / dz: d = 256 900 / 1015
+// -> 817 / 909 us, 696 1945 / 1970 -> 1785 / 1830, 1024 2240 / 2388 -> 2128 / 2277, 4096 -0.7 / -0.4 %).
+// Positions past the list repeat its last word.
+template <typename S, int LISTS>
+struct TokenWords {
+  static constexpr int PIECES = S::BN / 64, BYTES = LISTS * S::BN * 4;     // a wavefront fetches 64 words at a time
+  __device__ __forceinline__ static void fetch(const void* const (&list)[LISTS], const int (&t0)[LISTS], int n_act, char* lds) {
+    const int wave = wave_id(), lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < (LISTS * PIECES + S::WAVES - 1) / S::WAVES; ++i) {
+      const int piece = i * S::WAVES + wave;
+      if (LISTS * PIECES % S::WAVES != 0 && piece >= LISTS * PIECES) break;      // wave-uniform
+      uint64_t base = 0;
+      int first = 0;
+#pragma unroll
+      for (int l = 0; l < LISTS; ++l)
+        if (piece / PIECES == l) {
+          base = reinterpret_cast<uint64_t>(list[l]);
+          first = t0[l];
+        }
+      const i32x4_t rs = {__builtin_amdgcn_readfirstlane((int)(uint32_t)base),
+                          __builtin_amdgcn_readfirstlane((int)((uint32_t)(base >> 32) & 0xffffu)), n_act * 4, 0x00020000};
+      lds_dma4(lds_address(lds) + (uint32_t)piece * 256u, (uint32_t)min(first + piece % PIECES * 64 + lane, n_act - 1) * 4u, rs);
+    }
+  }
+  template <typename V>
+  __device__ __forceinline__ static V word(const char* lds, int list, int pos) {
+    return *reinterpret_cast<const V*>(lds + (list * S::BN + pos) * 4);
+  }
+};
+// The logits kernels gather their column operand (H rows) through the active-row list: the rows a lane fetches.
+template <bool QUAD, typename G>
+__device__ __forceinline__ void gather_rows(const char* words, int (&grow)[decltype(G::lb)::ITERS]) {
   const int lane = threadIdx.x & 63, wave = wave_id();
 #pragma unroll
-  for (int it = 0; it < decltype(G::lb)::ITERS; ++it) {
-    const int p = tt * G::Shape::BN + decltype(G::lb)::template lane_tile_row<QUAD>(it, wave, lane);
-    grow[it] = a.rows[min(p, n_act - 1)];
-  }
+  for (int it = 0; it < decltype(G::lb)::ITERS; ++it)
+    grow[it] = *reinterpret_cast<const int*>(words + decltype(G::lb)::template lane_tile_row<QUAD>(it, wave, lane) * 4);
 }
-// both operand streams of tile `id` (rows = W tile, columns = gathered H rows), first slabs
 template <bool QUAD, typename G, typename Args>
-__device__ __forceinline__ void logits_fetch(G& g, const TileSchedule& sch, const Args& a, int id, int n_act,
-                                             const int (&grow)[decltype(G::lb)::ITERS], char* smem) {
+__device__ __forceinline__ void gather_rows_of_first(const Args& a, const LogitsTile& t, int n_act,
+                                                     int (&grow)[decltype(G::lb)::ITERS]) {
+  const int lane = threadIdx.x & 63, wave = wave_id();
+#pragma unroll
+  for (int it = 0; it < decltype(G::lb)::ITERS; ++it)
+    grow[it] = a.rows[min(t.tt * G::Shape::BN + decltype(G::lb)::template lane_tile_row<QUAD>(it, wave, lane), n_act - 1)];
+}
+// both operand streams of a tile (rows = W tile, columns = gathered H rows); issue_first() requests the first slabs
+template <bool QUAD, typename G, typename Args>
+__device__ __forceinline__ void logits_setup(G& g, const Args& a, const LogitsTile& t, int n_act,
+                                             const int (&grow)[decltype(G::lb)::ITERS]) {
   typedef typename G::Type::store_t st;
   constexpr int BM = G::Shape::BM, BN = G::Shape::BN;
-  int tv, tt;
-  sch.coords(id, tv, tt);
-  g.template prefetch_gathered<QUAD>((const st*)a.W + (int64_t)tv * BM * a.d, a.d,
-                                     (int)min((int64_t)BM, a.V - (int64_t)tv * BM), a.H, a.d,
-                                     (int)min((int64_t)BN, (int64_t)n_act - (int64_t)tt * BN), a.d, smem, grow, a.N);
+  g.template setup_gathered<QUAD>((const st*)a.W + (int64_t)t.tv * BM * a.d, a.d,
+                                     (int)min((int64_t)BM, a.V - (int64_t)t.tv * BM), a.H, a.d,
+                                     (int)min((int64_t)BN, (int64_t)n_act - (int64_t)t.tt * BN), a.d, grow, a.N);
 }
 
-// + per-token (max, sum) of the wave rows
+// + per-token (max, sum) of the wave rows + the next tile's rows and the tile's targets
 template <typename G>
-constexpr int fwd_lds_bytes = G::LDS_BYTES + 2 * G::Shape::WAVES_M * G::Shape::BN * 4;
+constexpr int fwd_lds_bytes = G::LDS_BYTES + 2 * G::Shape::WAVES_M * G::Shape::BN * 4 + TokenWords<typename G::Shape, 2>::BYTES;
 
 template <typename G>
 __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partials(FwdArgs a) {
@@ -153,46 +191,53 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
   float* s_m = reinterpret_cast<float*>(smem + G::LDS_BYTES);   // [waves along the vocabulary][tokens of the tile]
   float* s_s = s_m + S::WAVES_M * BN;                           // outside the slab buffers: see prefetch below
 
+  typedef TokenWords<S, 2> Words;
+  char* words = reinterpret_cast<char*>(s_s + S::WAVES_M * BN);
+
   G g;
-  int id = sch.take();
+  LogitsTile cur, next;
+  cur.take(sch);
   int grow[decltype(g.lb)::ITERS];
-  gather_rows<false, G>(sch, a, id, n_act, grow);
-  logits_fetch<false>(g, sch, a, id, n_act, grow, smem);
+  gather_rows_of_first<false, G>(a, cur, n_act, grow);
+  logits_setup<false>(g, a, cur, n_act, grow);
+#pragma unroll
+  for (int q = 0; q < G::FIRST_PARTS; ++q) g.issue_first(smem, q);
+  bool more = sch.has_tile();
+  next = cur;
+  if (more) next.take(sch);
+  Words::fetch({a.rows, a.row_targets}, {next.tt * BN, cur.tt * BN}, n_act, words);
+  bool counted = false;
   while (true) {
     f32x4_t acc[MB][NB];
-    run_or_idle(g, smem, acc, G::Shape::wave_col(wave_id()) * WAVE_N >= columns_left<G>(sch, id, n_act));
+    run_or_idle(g, smem, acc, S::wave_col(wave_id()) * WAVE_N >= n_act - cur.tt * BN, counted);
     // The lane's position is rebuilt from an opaque copy of the thread id after every main loop: otherwise all the
     // per-lane constants of the epilogue stay live through the loop, are spilled, and every reload waits (vmcnt) for
     // the slab requests of the next tile as well.
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const LanePos<S> lp(tid);
-    int tv, tt;
-    sch.coords(id, tv, tt);
+    const int tv = cur.tv, tt = cur.tt;
     const int64_t v0 = (int64_t)tv * BM, t0 = (int64_t)tt * BN;
     const int rowsV = (int)min((int64_t)BM, a.V - v0);
     const int rowsT = (int)min((int64_t)BN, (int64_t)n_act - t0);
-    const bool more = sch.has_tile();
-    // every global load of the tile boundary in two batches: list entries (this tile's tokens, the next tile's
-    // gather rows), then the targets they point to -- all issued before the slab requests below, so that waiting
-    // for them later does not mean waiting for those
-    const int nid = more ? sch.take() : id;
-    gather_rows<false, G>(sch, a, nid, n_act, grow);
+    const bool last = !more;
+    gather_rows<false, G>(words, grow);
     int ytok[NB];
 #pragma unroll
-    for (int j = 0; j < NB; ++j) ytok[j] = a.rows[min((int)t0 + lp.col(j), n_act - 1)];
-#pragma unroll
-    for (int j = 0; j < NB; ++j) ytok[j] = a.targets[ytok[j]];
+    for (int j = 0; j < NB; ++j) ytok[j] = Words::template word<int>(words, 1, lp.col(j));
+    __syncthreads();                                 // every wave is done reading the slab buffers and the token words
     LLAMARL_FENCE();
-    wait_vmcnt0();                                   // see below
-    __syncthreads();                                 // every wave is done reading the slab buffers
-    if (more) {                                      // start the next tile's first slabs; the epilogue hides them
-      id = nid;
-      logits_fetch<false>(g, sch, a, id, n_act, grow, smem);
+    if (!last) {                                     // start the next tile's first slabs; the epilogue hides them
+      cur = next;
+      logits_setup<false>(g, a, cur, n_act, grow);
+      g.issue_first(smem, 0);
+      more = sch.has_tile();
+      if (more) next.take(sch);
+      Words::fetch({a.rows, a.row_targets}, {next.tt * BN, cur.tt * BN}, n_act, words);
     }
     // From here to the next main loop nothing may wait on vmcnt: the counter is in order, so a wait for any load
     // (or spill reload) issued before the slab requests turns into a wait for the requests themselves, and the
-    // epilogue would start only when the slabs have arrived.  Hence the explicit wait above.
+    // epilogue would start only when the slabs have arrived.
     LLAMARL_FENCE();
 
     if (rowsV < BM) {   // last vocab tile only (block-uniform): rows past V must not enter the softmax
@@ -207,6 +252,7 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
     const int lane_row0 = lp.row(0, 0);              // rows of this lane: lane_row0 + 16 ib + r
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
+      if (j > 0 && j < G::FIRST_PARTS && !last) g.issue_first(smem, j);
       const int tok = lp.col(j);
       const int y = (tok < rowsT) ? ytok[j] - (int)a.v_off : -1;   // row of W that is the target (negative: none)
       const int yrow = y - (int)v0;                  // vocab row of the target inside this tile (if 0 <= . < rowsV)
@@ -251,7 +297,8 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
       a.part_m[(int64_t)tv * a.n_pad + t0 + tid] = M;
       a.part_s[(int64_t)tv * a.n_pad + t0 + tid] = sum;
     }
-    if (!more) break;
+    if (last) break;
+    counted = (wave_id() * 64) < rowsT;              // this wavefront has just issued its two stores
   }
 }
 
@@ -405,6 +452,10 @@ struct CompactArgs {
   int aligned;               // targets / coef 16-byte, mask 4-byte aligned
   int32_t* rows;
   int32_t* n_act;
+  int32_t* row_targets;      // targets of the listed rows
+  const float* lse;          // mode 1: lse and coef of the listed rows as well
+  float* row_lse;
+  float* row_coef;
   float* out0;
   float* out1;
   float* out2;
@@ -463,6 +514,17 @@ __device__ __forceinline__ void compact_rows(const CompactArgs& a, int block, in
   const int64_t first = (int64_t)block * COMPACT_BLOCK_ROWS, t0 = first + 4 * tid;
   float top = 0.f;
   const uint32_t act = t0 < a.N ? active_rows4(a, t0, top) : 0u;
+  int y4[4];                                        // on their way while the rows in front are counted
+  float c4[4], l4[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (act >> i & 1u) {
+      y4[i] = a.targets[t0 + i];
+      if (a.mode == 1) {
+        c4[i] = a.coef[t0 + i];
+        l4[i] = a.lse[t0 + i];
+      }
+    }
   int front = 0;
 #pragma unroll 4
   for (int64_t t = 4 * tid; t < first; t += COMPACT_BLOCK_ROWS) front += __popc(active_rows4(a, t, top));
@@ -504,7 +566,15 @@ __device__ __forceinline__ void compact_rows(const CompactArgs& a, int block, in
   int at = base + upto - own;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
-    if (act >> i & 1u) a.rows[at++] = (int32_t)(t0 + i);
+    if (act >> i & 1u) {
+      a.rows[at] = (int32_t)(t0 + i);
+      a.row_targets[at] = y4[i];
+      if (a.mode == 1) {
+        a.row_coef[at] = c4[i];
+        a.row_lse[at] = l4[i];
+      }
+      ++at;
+    }
   if (tid == 0 && last) {
     *a.n_act = total;
     if (a.dz_scale != nullptr) {
@@ -518,9 +588,6 @@ __global__ __launch_bounds__(COMPACT_THREADS) void k_compact_rows(CompactArgs a)
 struct DzArgs {
   const void* H;
   const void* W;
-  const int32_t* targets;
-  const float* lse;
-  const float* coef;
   float g;
   const float* g_device;  // non-null: the upstream scalar is *g_device instead of g
   const float* dz_scale;  // fp32: dz is stored times this (dz_scale_for)
@@ -531,8 +598,14 @@ struct DzArgs {
   int64_t ldz;
   void* dzt;    // [V][packed_pitch(n_act)] vocab-major; columns past the active rows written as zero
   const int32_t* rows;    // active token rows (coef != 0), ascending; dz / dzt are indexed by list position
+  const float* row_coef;  // their coef, lse and targets
+  const float* row_lse;
+  const int32_t* row_targets;
   const int32_t* n_act;
 };
+// + the next tile's rows, the tile's coef, lse and targets
+template <typename G>
+constexpr int dz_lds_bytes = G::LDS_BYTES + TokenWords<typename G::Shape, 4>::BYTES;
 
 template <typename G>
 __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzArgs a) {
@@ -549,51 +622,53 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzAr
   if constexpr (sizeof(typename G::Type::store_t) == 4) scale = *a.dz_scale;
   // token columns are fetched quad-interleaved (a lane's four column blocks are neighbouring tokens), so the
   // vocab-major dz^T leaves straight from registers, 8 (bf16) or 16 bytes per lane and whole lines per 16 lanes.
+  typedef TokenWords<S, 4> Words;
+  char* words = smem + G::LDS_BYTES;
   G g;
-  int id = sch.take();
+  LogitsTile cur, next;
+  cur.take(sch);
   int grow[decltype(g.lb)::ITERS];
-  gather_rows<true, G>(sch, a, id, n_act, grow);
-  logits_fetch<true>(g, sch, a, id, n_act, grow, smem);
+  gather_rows_of_first<true, G>(a, cur, n_act, grow);
+  logits_setup<true>(g, a, cur, n_act, grow);
+#pragma unroll
+  for (int q = 0; q < G::FIRST_PARTS; ++q) g.issue_first(smem, q);
+  bool more = sch.has_tile();
+  next = cur;
+  if (more) next.take(sch);
+  Words::fetch({a.rows, a.row_coef, a.row_lse, a.row_targets}, {next.tt * BN, cur.tt * BN, cur.tt * BN, cur.tt * BN}, n_act, words);
   while (true) {
     f32x4_t acc[MB][NB];
     g.run(smem, acc);
     int tid = threadIdx.x;                           // opaque per tile: see k_fwd_partials
     asm volatile("" : "+v"(tid));
     const LanePos<S> lp(tid);
-    int tv, tt;
-    sch.coords(id, tv, tt);
-    const bool more = sch.has_tile();
+    const int tv = cur.tv, tt = cur.tt;
     const int64_t v0 = (int64_t)tv * BM, t0 = (int64_t)tt * BN;
     const int rowsV = (int)min((int64_t)BM, a.V - v0);
     const int rowsT = (int)min((int64_t)BN, (int64_t)n_act - t0);
-    // every global load of the tile boundary in two batches (list entries, then what they point to), all issued
-    // before the slab requests below
-    const int nid = more ? sch.take() : id;
-    gather_rows<true, G>(sch, a, nid, n_act, grow);
-    int trow[NB];
-    float tcoef[NB], tlse[NB];
-    int ttgt[NB];
-#pragma unroll
-    for (int j = 0; j < NB; ++j) trow[j] = a.rows[min((int)t0 + lp.col_quad() + j, n_act - 1)];
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      tcoef[j] = a.coef[trow[j]];
-      tlse[j] = a.lse[trow[j]];
-      ttgt[j] = a.targets[trow[j]];
-    }
+    const bool last = !more;
+    gather_rows<true, G>(words, grow);
+    const f32x4_t tcoef = Words::template word<f32x4_t>(words, 1, lp.col_quad());
+    const f32x4_t tlse = Words::template word<f32x4_t>(words, 2, lp.col_quad());
+    const i32x4_t ttgt = Words::template word<i32x4_t>(words, 3, lp.col_quad());
+    __syncthreads();                                 // every wave is done reading the slab buffers and the token words
     LLAMARL_FENCE();
-    wait_vmcnt0();                                   // nothing may wait on vmcnt after the slab requests: see k_fwd_partials
-    __syncthreads();                                 // every wave is done reading the slab buffers
-    if (more) {                                      // the epilogue uses no LDS: fetch the next tile under it
-      id = nid;
-      logits_fetch<true>(g, sch, a, id, n_act, grow, smem);
+    if (!last) {                                     // the epilogue uses no LDS: fetch the next tile under it
+      cur = next;
+      logits_setup<true>(g, a, cur, n_act, grow);
+      g.issue_first(smem, 0);
+      more = sch.has_tile();
+      if (more) next.take(sch);
+      Words::fetch({a.rows, a.row_coef, a.row_lse, a.row_targets}, {next.tt * BN, cur.tt * BN, cur.tt * BN, cur.tt * BN}, n_act,
+                   words);
     }
-    LLAMARL_FENCE();
+    LLAMARL_FENCE();                                 // nothing may wait on vmcnt from here on: see k_fwd_partials
 
     // dz in place of the logits; per-token scalars live in registers (one token per lane and j)
     const int lane_row0 = lp.row(0, 0);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
+      if (j > 0 && j < G::FIRST_PARTS && !last) g.issue_first(smem, j);
       const int tok = lp.col_quad() + j;
       const bool in = tok < rowsT;
       float c = in ? upstream * tcoef[j] : 0.f;
@@ -673,7 +748,7 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzAr
                 make_float4(acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]);
       }
     }
-    if (!more) break;
+    if (last) break;
   }
 }
 
@@ -861,6 +936,7 @@ __device__ __forceinline__ void store_final1(char* q, float v) {
 
 // MODE (compile time): the final form of the output, see store_final4.  Split tiles of the last round leave fp32
 // partial products instead (k_reduce_tail finishes them in the same MODE).
+typedef TileGemm<BF16, STORE_LOAD_SLOT, 32, false> Store256;      // its epilogue's stores: one unit per row of a lane
 template <typename G, int MODE>
 __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(StoreArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -893,8 +969,6 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
     g.unscale = __uint_as_float((254u << 23) - __float_as_uint(*a.a_scale));       // 1 / *a.a_scale
   int id = plan.take();
   store_fetch(g, plan, a, id, M, K, smem);
-  // The K-contiguous epilogue stores one unit per row of a lane: STORES_OF_A_TILE, unless the tile is ragged.
-  constexpr int STORES_OF_A_TILE = MB * 4;
   bool counted = false;
   while (true) {
     f32x4_t acc[MB][NB];
@@ -902,8 +976,8 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
     if (store_tile_of<G>(plan, a, cur_id, M, K).k_len > 0) {
       if constexpr (KMAJOR)
         run_or_idle(g, smem, acc, S::wave_row(wave_id()) * S::WAVE_M >= store_tile_of<G>(plan, a, cur_id, M, K).rowsA);
-      else if constexpr (std::is_same<G, TileGemm<BF16, STORE_LOAD_SLOT>>::value)
-        g.template run<STORES_OF_A_TILE>(smem, acc, counted);
+      else if constexpr (std::is_same<G, Store256>::value)
+        g.run(smem, acc, counted);
       else if constexpr (sizeof(typename G::Type::store_t) == 4)
         g.template run<true>(smem, acc);
       else

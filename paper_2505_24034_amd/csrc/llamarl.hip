@@ -66,8 +66,6 @@ Tile store_tile(int64_t M, int64_t Nn, int64_t K, llamarl_dtype dt) {
   return tile_count(M, Nn, 128) * parts >= (dt == LLAMARL_BF16 ? 128 : 256) ? TILE_128 : TILE_64;
 }
 
-typedef TileGemm<BF16> Logits256;
-typedef TileGemm<BF16, STORE_LOAD_SLOT> Store256;
 typedef TileGemmSmall<BF16, Shape128, 2, 2> Bf16Loop128;
 typedef TileGemmSmall<BF16, Shape64, 4, 2> Bf16Loop64;
 typedef TileGemmTNSmall<Shape128, 2, 2> Bf16LoopTN128;
@@ -79,7 +77,7 @@ typedef TileGemmSmall<F32, Shape64, 4, 2> F32Loop64;
 struct FwdWs {
   int tiles_v, tiles_t;
   int64_t n_pad;
-  size_t off_m, off_s, off_zt, off_rows, off_nact, total;
+  size_t off_m, off_s, off_zt, off_rows, off_tgt, off_nact, total;
 };
 FwdWs fwd_ws(int64_t N, int64_t V, llamarl_dtype dt) {
   FwdWs w;
@@ -99,7 +97,8 @@ FwdWs fwd_ws(int64_t N, int64_t V, llamarl_dtype dt) {
   w.off_s = round_up((int64_t)plane, 256);
   w.off_zt = w.off_s + round_up((int64_t)plane, 256);
   w.off_rows = w.off_zt + (size_t)round_up(w.n_pad * (int64_t)sizeof(float), 256);
-  w.off_nact = w.off_rows + (size_t)round_up(w.n_pad * (int64_t)sizeof(int32_t), 256);
+  w.off_tgt = w.off_rows + (size_t)round_up(w.n_pad * (int64_t)sizeof(int32_t), 256);
+  w.off_nact = w.off_tgt + (size_t)round_up(w.n_pad * (int64_t)sizeof(int32_t), 256);
   w.total = w.off_nact + 256;
   return w;
 }
@@ -142,7 +141,8 @@ struct BwdWs {
                       // partials are sized for R rows; more active rows than that are taken in further passes
   int n_pass;         // passes the host enqueues = ceil(N / R); passes past the active rows find nothing to do
   int64_t ldz, ldzt;  // padded leading dimensions (elements): V rounded up to 64; packed_pitch(R)
-  size_t off_dz, off_dzt, off_wt, off_ht, off_rows, off_nact, off_plan, off_part, total;
+  size_t off_dz, off_dzt, off_wt, off_ht, off_rows, off_words, off_nact, off_plan, off_part, total;
+  int64_t n_list;     // entries of the row list and of each of the three lists of per-row words
 };
 // Most workgroups a persistent grid has (one per CU of an MI355X); also the most split items the last round of a
 // store contraction can hold, each leaving one BM x BN fp32 block in the workspace.
@@ -162,7 +162,9 @@ BwdWs bwd_ws(int64_t N, int64_t d, int64_t V, llamarl_dtype dt, int64_t max_rows
   w.off_wt = w.off_dzt + (size_t)round_up(V * w.ldzt * (int64_t)es, 256);
   w.off_ht = w.off_wt + (both ? (size_t)round_up(d * w.ldz * (int64_t)es, 256) : 0);
   w.off_rows = w.off_ht + (size_t)round_up(d * w.ldzt * (int64_t)es, 256);
-  w.off_nact = w.off_rows + (size_t)round_up(round_up(N, 64) * (int64_t)sizeof(int32_t), 256);
+  w.n_list = round_up(N, 64);
+  w.off_words = w.off_rows + (size_t)(w.n_list * (int64_t)sizeof(int32_t));
+  w.off_nact = w.off_words + (size_t)(3 * w.n_list * (int64_t)sizeof(int32_t));
   w.off_plan = w.off_nact + (size_t)round_up((int64_t)(1 + w.n_pass) * (int64_t)sizeof(int32_t), 256);
   w.off_part = w.off_plan + 256;
   // fp32 partial blocks of the split tiles at the end of a store contraction (see StorePlan): at most
@@ -290,7 +292,7 @@ llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int6
 }
 
 CompactArgs compact_args(CompactArgs a) {
-  a.aligned = aligned16(a.targets) && aligned16(a.coef) && (reinterpret_cast<uintptr_t>(a.mask) & 3u) == 0;
+  a.aligned = (a.mode == 1 || aligned16(a.targets)) && aligned16(a.coef) && (reinterpret_cast<uintptr_t>(a.mask) & 3u) == 0;
   return a;
 }
 int compact_blocks(int64_t N) { return (int)((N + COMPACT_BLOCK_ROWS - 1) / COMPACT_BLOCK_ROWS); }
@@ -307,9 +309,9 @@ template <typename G>
 llamarl_status launch_bwd_dz(DzArgs a, int64_t rows, hipStream_t st) {
   a.tiles_v = (int)((a.V + G::Shape::BM - 1) / G::Shape::BM);
   a.tiles_t = (int)((rows + G::Shape::BN - 1) / G::Shape::BN);
-  HIP_TRY(set_lds_if_large(k_bwd_dz<G>, G::LDS_BYTES));
+  HIP_TRY(set_lds_if_large(k_bwd_dz<G>, dz_lds_bytes<G>));
   k_bwd_dz<G><<<dim3((unsigned)persistent_grid((int64_t)a.tiles_v * a.tiles_t, G::GROUPS_PER_CU)),
-                dim3(G::Shape::THREADS), G::LDS_BYTES, st>>>(a);
+                dim3(G::Shape::THREADS), dz_lds_bytes<G>, st>>>(a);
   HIP_TRY(hipGetLastError());
   return LLAMARL_OK;
 }
@@ -323,18 +325,19 @@ llamarl_status run_logprobs(const void* H, const void* W, const int32_t* targets
   constexpr llamarl_dtype dt = sizeof(typename TT::store_t) == 2 ? LLAMARL_BF16 : LLAMARL_F32;
   const FwdWs w = fwd_ws(N, V, dt);
   FwdArgs a;
-  a.H = H; a.W = W; a.targets = targets; a.N = N; a.d = d; a.V = V; a.v_off = v_off;
+  a.H = H; a.W = W; a.N = N; a.d = d; a.V = V; a.v_off = v_off;
   a.tiles_v = w.tiles_v; a.tiles_t = w.tiles_t; a.n_pad = w.n_pad;
   a.part_m = reinterpret_cast<float*>(ws + w.off_m);
   a.part_s = reinterpret_cast<float*>(ws + w.off_s);
   a.zt = reinterpret_cast<float*>(ws + w.off_zt);
   int32_t* rows = reinterpret_cast<int32_t*>(ws + w.off_rows);
   int32_t* n_act = reinterpret_cast<int32_t*>(ws + w.off_nact);
-  a.rows = rows; a.n_act = n_act;
+  int32_t* row_targets = reinterpret_cast<int32_t*>(ws + w.off_tgt);
+  a.rows = rows; a.row_targets = row_targets; a.n_act = n_act;
   // active-token list (mask and target range); inactive rows get their outputs here
   k_compact_rows<<<dim3((unsigned)compact_blocks(N)), dim3(COMPACT_THREADS), 0, st>>>(
-      compact_args({partial ? 2 : 0, mask, targets, nullptr, V_total, N, 0, rows, n_act, out0, out1, out2, 0.f, nullptr,
-                    nullptr}));
+      compact_args({partial ? 2 : 0, mask, targets, nullptr, V_total, N, 0, rows, n_act, row_targets, nullptr, nullptr,
+                    nullptr, out0, out1, out2, 0.f, nullptr, nullptr}));
   HIP_TRY(hipGetLastError());
   llamarl_status s;
   const Tile tile = logits_tile(N, V, dt);
@@ -391,8 +394,11 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
   SetupArgs<stt> u;
   int32_t* plan = reinterpret_cast<int32_t*>(ws + w.off_plan);
   float* dz_scale = kBf16 ? nullptr : reinterpret_cast<float*>(plan + 16);     // plan: StoreArgs::plan_out, 4 entries
-  u.compact = compact_args({1, nullptr, nullptr, coef, V, N, 0, all_rows, n_act_all, nullptr, nullptr, nullptr, g, g_device,
-                            dz_scale});
+  int32_t* all_targets = reinterpret_cast<int32_t*>(ws + w.off_words);
+  float* all_lse = reinterpret_cast<float*>(all_targets + w.n_list);
+  float* all_coef = all_lse + w.n_list;
+  u.compact = compact_args({1, nullptr, targets, coef, V, N, 0, all_rows, n_act_all, all_targets, lse, all_lse, all_coef,
+                            nullptr, nullptr, nullptr, g, g_device, dz_scale});
   u.compact_blocks = compact_blocks(N);
   u.zero_blocks = (int)((N + SETUP_ROWS - 1) / SETUP_ROWS);
   u.dH = reinterpret_cast<stt*>(dH); u.d = d;
@@ -421,10 +427,11 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
 
     // recompute logits tile by tile, turn them into dz (rows / columns = list positions of the pass)
     DzArgs a;
-    a.H = H; a.W = W; a.targets = targets; a.lse = lse; a.coef = coef; a.g = g; a.g_device = g_device; a.N = N; a.d = d; a.V = V;
+    a.H = H; a.W = W; a.g = g; a.g_device = g_device; a.N = N; a.d = d; a.V = V;
     a.dz_scale = dz_scale;
     a.v_off = v_off;
     a.dz = dz; a.ldz = w.ldz; a.dzt = dzt; a.rows = rows; a.n_act = n_act;
+    a.row_targets = all_targets + (int64_t)c * w.R; a.row_lse = all_lse + (int64_t)c * w.R; a.row_coef = all_coef + (int64_t)c * w.R;
     const Tile logits = logits_tile(Rc, V, dt);
     if constexpr (kBf16)
       s = (logits == TILE_256   ? launch_bwd_dz<Logits256>
