@@ -9,12 +9,15 @@
 
 namespace llamarl {
 
+typedef Shape256 CeilingShape;
+constexpr int CEILING_MB = CeilingShape::MB, CEILING_NB = CeilingShape::NB;
+
 constexpr int CEILING_KSTEPS_PER_ITER = 2;   // two k-steps with alternating operand registers, as in a K slab
 
 __global__ __launch_bounds__(NTHREADS) void k_mfma_ceiling(int iters, float* sink) {
   // operands with random sign and mantissa bits and exponents spread over eight binades (what hidden states and
   // head weights look like to the datapath: its power draw depends on the bits it toggles)
-  bf16x8_t a[2][MB], b[2][NB];
+  bf16x8_t a[2][CEILING_MB], b[2][CEILING_NB];
   uint32_t h = (uint32_t)(blockIdx.x * NTHREADS + threadIdx.x) * 2654435761u + 12345u;
   auto next_bf16 = [&h](int exp_hi) {
     h = h * 1664525u + 1013904223u;
@@ -25,33 +28,33 @@ __global__ __launch_bounds__(NTHREADS) void k_mfma_ceiling(int iters, float* sin
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+    for (int i = 0; i < CEILING_MB; ++i)
 #pragma unroll
       for (int e = 0; e < 8; ++e) a[s][i][e] = next_bf16(127);     // |a| in [2^-7, 2)
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
+    for (int j = 0; j < CEILING_NB; ++j)
 #pragma unroll
       for (int e = 0; e < 8; ++e) b[s][j][e] = next_bf16(121);     // |b| in [2^-13, 2^-5)
   }
-  f32x4_t acc[MB][NB];
+  f32x4_t acc[CEILING_MB][CEILING_NB];
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+  for (int i = 0; i < CEILING_MB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < CEILING_NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
     for (int s = 0; s < CEILING_KSTEPS_PER_ITER; ++s)
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
+      for (int i = 0; i < CEILING_MB; ++i)
 #pragma unroll
-        for (int j = 0; j < NB; ++j) mma(a[s][i], b[s][j], acc[i][j]);
+        for (int j = 0; j < CEILING_NB; ++j) mma(a[s][i], b[s][j], acc[i][j]);
     asm volatile("" ::: "memory");            // keep the loop a loop
   }
   float t = 0.f;
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+  for (int i = 0; i < CEILING_MB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) t += acc[i][j][0] + acc[i][j][1] + acc[i][j][2] + acc[i][j][3];
+    for (int j = 0; j < CEILING_NB; ++j) t += acc[i][j][0] + acc[i][j][1] + acc[i][j][2] + acc[i][j][3];
   if (t == 12345.678f) sink[0] = t;           // never true in practice; keeps the accumulators alive
 }
 
@@ -65,18 +68,18 @@ __global__ __launch_bounds__(NTHREADS) void k_mfma_ceiling(int iters, float* sin
 // loads wraps inside a row.  Values computed are meaningless (slabs are overwritten while they are read); every
 // access is in bounds and every wavefront runs the same `iters` iterations.
 constexpr int CEILING_PANEL_K = 4096;                                        // elements per panel row (8 KB)
-constexpr size_t CEILING_PANEL_BYTES = (size_t)2 * Shape256::BM * CEILING_PANEL_K * 2;   // both panels
+constexpr size_t CEILING_PANEL_BYTES = (size_t)2 * CeilingShape::BM * CEILING_PANEL_K * 2;   // both panels
 
-__device__ __forceinline__ void ceiling_k_step(bf16x8_t (&a)[MB], const bf16x8_t (&bc)[NB], bf16x8_t (&bn)[NB],
-                                               f32x4_t (&acc)[MB][NB], const char* pa_cur, const char* pa_nxt,
+__device__ __forceinline__ void ceiling_k_step(bf16x8_t (&a)[CEILING_MB], const bf16x8_t (&bc)[CEILING_NB], bf16x8_t (&bn)[CEILING_NB],
+                                               f32x4_t (&acc)[CEILING_MB][CEILING_NB], const char* pa_cur, const char* pa_nxt,
                                                const char* pb_nxt, const SlabLoader<BF16>& la,
                                                const SlabLoader<BF16>& lb, char* dst, int k0, int wave, int lane,
                                                const bool READS, const bool LOADS) {   // both flags are constants once inlined
   // slot table of k_step (gemm_nt.h): a[7] of this k-step at slot 0; the next k-step's a[0], a[1] at slots 8, 9,
   // a[2..6] at slots 12, 16, .., 28, its B fragments at slots 10, 14, 18, 22; slab loads at the odd slots 11 .. 25
 #pragma unroll
-  for (int t = 0; t < MB * NB; ++t) {
-    const int ib = t >> 2, jb = snake_col(t);
+  for (int t = 0; t < CEILING_MB * CEILING_NB; ++t) {
+    const int ib = t >> 2, jb = snake(t);
     mma(a[ib], bc[jb], acc[ib][jb]);
     LLAMARL_FENCE();
     if (READS) {
@@ -90,8 +93,8 @@ __device__ __forceinline__ void ceiling_k_step(bf16x8_t (&a)[MB], const bf16x8_t
     }
     if (LOADS && t >= 11 && t <= 25 && (t & 1) == 1) {
       const int n = (t - 11) >> 1;
-      if (n < 4) la.issue_one(dst, n, k0, CEILING_PANEL_K, wave, lane, false);
-      else lb.issue_one(dst + SLAB_A_BYTES, n - 4, k0, CEILING_PANEL_K, wave, lane, false);
+      if (n < 4) la.issue_one(la.rsrc(), dst, n, k0, CEILING_PANEL_K, wave, lane, false);
+      else lb.issue_one(lb.rsrc(), dst + SLAB_A_BYTES, n - 4, k0, CEILING_PANEL_K, wave, lane, false);
       LLAMARL_FENCE();
     }
   }
@@ -101,17 +104,17 @@ __device__ __forceinline__ void ceiling_k_step(bf16x8_t (&a)[MB], const bf16x8_t
 __device__ __forceinline__ void ceiling_traffic_loop(int iters, float* sink, const void* panels, char* smem,
                                                      const bool READS, const bool LOADS) {
   const int lane = threadIdx.x & 63, wave = wave_id();
-  const int wm = Shape256::wave_row(wave), wn = Shape256::wave_col(wave);
+  const int wm = CeilingShape::wave_row(wave), wn = CeilingShape::wave_col(wave);
   SlabLoader<BF16> la, lb;
-  la.init(panels, CEILING_PANEL_K, Shape256::BM, wave, lane);
-  lb.init(reinterpret_cast<const char*>(panels) + (size_t)Shape256::BM * CEILING_PANEL_K * 2, CEILING_PANEL_K, Shape256::BN, wave, lane);
+  la.init(panels, CEILING_PANEL_K, CeilingShape::BM, wave, lane);
+  lb.init(reinterpret_cast<const char*>(panels) + (size_t)CeilingShape::BM * CEILING_PANEL_K * 2, CEILING_PANEL_K, CeilingShape::BN, wave, lane);
   // both stages start with panel data (every variant: the registers then hold the caller's operand values)
 #pragma unroll
   for (int s = 0; s < 2; ++s)
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
-      la.issue_one(smem + s * STAGE_BYTES, n, s * 64, CEILING_PANEL_K, wave, lane, false);
-      lb.issue_one(smem + s * STAGE_BYTES + SLAB_A_BYTES, n, s * 64, CEILING_PANEL_K, wave, lane, false);
+      la.issue_one(la.rsrc(), smem + s * STAGE_BYTES, n, s * 64, CEILING_PANEL_K, wave, lane, false);
+      lb.issue_one(lb.rsrc(), smem + s * STAGE_BYTES + SLAB_A_BYTES, n, s * 64, CEILING_PANEL_K, wave, lane, false);
     }
   wait_vmcnt0();
   __syncthreads();
@@ -120,22 +123,22 @@ __device__ __forceinline__ void ceiling_traffic_loop(int iters, float* sink, con
   int a_addr[2], b_addr[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
-    a_addr[ks] = (wm * Shape256::WAVE_M + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
-    b_addr[ks] = SLAB_A_BYTES + (wn * WAVE_N + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
+    a_addr[ks] = (wm * CeilingShape::WAVE_M + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
+    b_addr[ks] = SLAB_A_BYTES + (wn * CeilingShape::WAVE_N + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
   }
-  bf16x8_t a[MB], b0[NB], b1[NB];
+  bf16x8_t a[CEILING_MB], b0[CEILING_NB], b1[CEILING_NB];
 #pragma unroll
-  for (int i = 0; i < MB; ++i) a[i] = *reinterpret_cast<const bf16x8_t*>(smem + a_addr[0] + i * BLOCK_BYTES);
+  for (int i = 0; i < CEILING_MB; ++i) a[i] = *reinterpret_cast<const bf16x8_t*>(smem + a_addr[0] + i * BLOCK_BYTES);
 #pragma unroll
-  for (int j = 0; j < NB; ++j) {
+  for (int j = 0; j < CEILING_NB; ++j) {
     b0[j] = *reinterpret_cast<const bf16x8_t*>(smem + b_addr[0] + j * BLOCK_BYTES);
     b1[j] = *reinterpret_cast<const bf16x8_t*>(smem + b_addr[1] + j * BLOCK_BYTES);
   }
-  f32x4_t acc[MB][NB];
+  f32x4_t acc[CEILING_MB][CEILING_NB];
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+  for (int i = 0; i < CEILING_MB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < CEILING_NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   for (int it = 0; it < iters; ++it) {
     char* cur = smem + (it & 1) * STAGE_BYTES;
     const char* nxt = smem + ((it + 1) & 1) * STAGE_BYTES;
@@ -150,9 +153,9 @@ __device__ __forceinline__ void ceiling_traffic_loop(int iters, float* sink, con
   __syncthreads();
   float t = 0.f;
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+  for (int i = 0; i < CEILING_MB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) t += acc[i][j][0] + acc[i][j][1] + acc[i][j][2] + acc[i][j][3];
+    for (int j = 0; j < CEILING_NB; ++j) t += acc[i][j][0] + acc[i][j][1] + acc[i][j][2] + acc[i][j][3];
   if (t == 12345.678f) sink[0] = t;           // never true in practice; keeps the accumulators alive
 }
 

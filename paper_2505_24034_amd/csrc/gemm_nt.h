@@ -20,6 +20,7 @@
 //     16 rows that 16 lanes of a ds_read_b128 touch over all 64 LDS banks.
 //   - the loop is software-pipelined by hand (see TileGemm::run): every ds_read_b128 and every slab load is
 //     issued in the shadow of an MFMA, far ahead of its use, and scheduling fences pin that interleave.
+//   - TileGemmNarrow: the same for 128 or 160 columns (few tokens), three slabs resident.
 //   - out-of-range rows and the K tail use the buffer descriptor's bounds check: such lanes read zeros.
 //   - kernels are persistent (one workgroup per CU walks a list of tiles) and fetch the first slabs of their next
 //     tile before the epilogue of the current one, so the epilogue's VALU work overlaps that latency.
@@ -32,37 +33,47 @@ namespace llamarl {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
-constexpr int NB = 4;         // 16 x 16 MFMA blocks per wave along N (64 cols), in every tile shape
-constexpr int WAVE_N = NB * 16;
 constexpr int SLAB_ROW_BYTES = 128;
 constexpr int BLOCK_BYTES = 16 * SLAB_ROW_BYTES;                  // 16 slab rows: one MFMA block of an operand
 constexpr uint32_t OOB_OFFSET = 0x80000000u;                      // beyond any descriptor range used here
 
-// A workgroup's output tile: WM x WN wavefronts, each MB_ x NB MFMA blocks.  Wavefront w runs on SIMD w % 4.  By default
-// wavefronts are numbered along the columns, so the four of an upper half (WM = 2) sit on four SIMDs; COLUMN_MAJOR
-// numbers them along the rows, so the four of a left half (WN = 4) do: whichever edge of the matrix is ragged, the
-// wavefronts that have nothing to do there (see run_idle) then leave every SIMD one that has.
-template <int WM, int WN, int MB_, bool COLUMN_MAJOR = false>
+// A workgroup's output tile: WM x WN wavefronts, each MB_ x NB_ MFMA blocks.  Wavefront w runs on SIMD w % 4.
+template <int WM, int WN, int MB_, int NB_>
 struct TileShape {
-  __device__ __forceinline__ static int wave_row(int wave) { return COLUMN_MAJOR ? wave % WM : wave / WN; }
-  __device__ __forceinline__ static int wave_col(int wave) { return COLUMN_MAJOR ? wave / WM : wave % WN; }
+  __device__ __forceinline__ static int wave_row(int wave) { return wave / WN; }
+  __device__ __forceinline__ static int wave_col(int wave) { return wave % WN; }
   static constexpr int WAVES_M = WM, WAVES_N = WN, WAVES = WM * WN, THREADS = 64 * WM * WN;
-  static constexpr int MB = MB_, WAVE_M = MB_ * 16;
+  static constexpr int MB = MB_, NB = NB_, WAVE_M = MB_ * 16, WAVE_N = NB_ * 16;
   static constexpr int BM = WM * WAVE_M, BN = WN * WAVE_N;        // tile rows (A rows), tile columns (B rows)
   static constexpr int SLAB_A_BYTES = BM * SLAB_ROW_BYTES;
   static constexpr int STAGE_BYTES = (BM + BN) * SLAB_ROW_BYTES;  // one K slab of both operands
 };
-typedef TileShape<2, 4, 8, true> Shape256;   // 256 x 256, 8 wavefronts of 128 x 64
-typedef TileShape<2, 4, 8> Shape256Rows;     // the same, for outputs with a ragged last row of tiles
-typedef TileShape<2, 2, 4> Shape128;   // 128 x 128, 4 wavefronts of  64 x 64
-typedef TileShape<4, 1, 1> Shape64;    //  64 x  64, 4 wavefronts of  16 x 64
+// 256 x 256, 8 wavefronts of 128 x 64, numbered down the columns: the four of a left half sit on four SIMDs, so where the
+// last columns are empty the wavefronts with nothing to do (run_idle) leave every SIMD one that has.
+struct Shape256 : TileShape<2, 4, 8, 4> {
+  __device__ __forceinline__ static int wave_row(int wave) { return wave & 1; }
+  __device__ __forceinline__ static int wave_col(int wave) { return wave >> 1; }
+};
+// 256 rows in two halves of up to 128 columns, 8 wavefronts of 64 x (16 nb): the left half's have eight column blocks, the
+// right half's nb1 = 0, 2, .., 8.  A SIMD's two wavefronts (w, w + 4) belong to the two column halves and to row quarters two
+// apart: every SIMD has the same work at any width, and keeps a wavefront with work when either edge cuts the tile in half.
+struct Shape256Halves : TileShape<4, 2, 4, 8> {
+  __device__ __forceinline__ static int wave_row(int wave) { return (wave + 2 * (wave >> 2)) & 3; }
+  __device__ __forceinline__ static int wave_col(int wave) { return wave >> 2; }
+};
+typedef TileShape<2, 2, 4, 4> Shape128;   // 128 x 128, 4 wavefronts of  64 x 64
+typedef TileShape<4, 1, 1, 4> Shape64;    //  64 x  64, 4 wavefronts of  16 x 64
 
 // the 256 x 256 loop's own constants
-constexpr int MB = Shape256::MB;
+constexpr int MB = Shape256::MB, NB = Shape256::NB;
 constexpr int NTHREADS = Shape256::THREADS;
 constexpr int SLAB_A_BYTES = Shape256::SLAB_A_BYTES;              // 32 KB
 constexpr int STAGE_BYTES = Shape256::STAGE_BYTES;                // 64 KB
 constexpr int MAINLOOP_LDS_BYTES = 2 * STAGE_BYTES;               // 128 KB
+// Tiles of at most NARROW_BN columns: three resident slabs instead of two.
+constexpr int NARROW_BN = 160;
+constexpr int NARROW_STAGE_BYTES = (Shape256::BM + NARROW_BN) * SLAB_ROW_BYTES;      // 52 KB
+constexpr int NARROW_LDS_BYTES = 3 * NARROW_STAGE_BYTES;          // 156 KB
 
 struct BF16 {
   typedef uint16_t store_t;
@@ -112,20 +123,22 @@ struct LanePos {
   __device__ __forceinline__ explicit LanePos(int tid)
       : wm(S::wave_row(tid >> 6)), wn(S::wave_col(tid >> 6)), lane(tid & 63) {}
   __device__ __forceinline__ int row(int ib, int r) const { return wm * S::WAVE_M + ib * 16 + (lane >> 4) * 4 + r; }
-  __device__ __forceinline__ int col(int jb) const { return wn * WAVE_N + jb * 16 + (lane & 15); }
-  // Quad-interleaved columns (see tile_row_of): the lane's four column blocks hold NEIGHBOURING columns
-  // col_quad() + jb, so 16 lanes own 64 consecutive columns of one row.
-  __device__ __forceinline__ int col_quad() const { return wn * WAVE_N + 4 * (lane & 15); }
+  __device__ __forceinline__ int col(int jb) const { return wn * S::WAVE_N + jb * 16 + (lane & 15); }
+  // Neighbouring columns (see tile_row_of): the lane's nb column blocks hold columns col_near(nb) + 0 .. nb - 1, so 16
+  // lanes own 16 nb consecutive columns of one row.
+  __device__ __forceinline__ int col_near(int nb) const { return wn * S::WAVE_N + nb * (lane & 15); }
 };
 
-// Which row of an operand tile the loader puts into LDS row `r`.  A wave's 64 LDS rows of the column operand feed
-// its four 16-column MFMA blocks (block jb = bits 5:4, MFMA column n = low 4 bits); with QUAD, block jb / column n
-// is tile row 4 n + jb of those 64, so that acc[.][0..3] of a lane are four neighbouring output columns and an
-// epilogue can store them as one unit.  Only the global side changes: LDS layout, swizzle and fragment reads stay.
-template <bool QUAD>
-__device__ __forceinline__ int tile_row_of(int r) {
-  static_assert(NB == 4 && WAVE_N == 64, "the interleave covers exactly four column blocks");
-  return QUAD ? ((r & ~63) | ((r & 15) << 2) | ((r >> 4) & 3)) : r;
+// Which row of an operand tile the loader puts into LDS row `r`.  The LDS rows of the column operand feed a wavefront's
+// 16-column MFMA blocks, WAVE_N rows a wavefront (block jb, MFMA column n = low 4 bits); with NEAR, block jb / column n of
+// a wavefront with nb blocks is its tile row nb n + jb, so that acc[.][0 .. nb-1] of a lane are neighbouring output
+// columns and an epilogue can store them as one unit.  Rows of blocks it does not have: none.  Only the global side
+// changes: LDS layout, swizzle and fragment reads stay.
+constexpr int NO_ROW = 1 << 30;
+template <bool NEAR, int WAVE_N>
+__device__ __forceinline__ int tile_row_of(int r, int nb) {
+  const int jb = (r & (WAVE_N - 1)) >> 4;
+  return !NEAR ? r : jb < nb ? (r & ~(WAVE_N - 1)) + nb * (r & 15) + jb : NO_ROW;
 }
 
 // Persistent tile schedule.  The grid has one workgroup per CU (any size works); the hardware deals workgroups
@@ -135,21 +148,23 @@ __device__ __forceinline__ int tile_row_of(int r) {
 // they share panels through the Infinity Cache (against giving every XCD a contiguous eighth of the ids: -3.5 %
 // step time, -6.5 % for the dH contraction whose two operands both stream from HBM).  tiles_m x tiles_n is the
 // number of tiles that exist once the device-side active-row count is known.
+template <int GROUP_M>     // rows of a patch
 struct TileSchedule {
-  int tiles_m, tiles_n, group_m;
+  int tiles_m, tiles_n;
   int next_id, end_id, stride;
-  bool turn;               // see coords
-  // group_m_: rows of a patch.  The 32 workgroups of an XCD work on 32 consecutive ids = group_m x (32 / group_m)
-  // tiles, which load group_m A panels and 32 / group_m B panels: a B panel is shared by group_m tiles, an A panel
-  // by 32 / group_m.  Give the larger share to the operand that has to come from HBM.
-  __device__ __forceinline__ void init(int tiles_m_, int tiles_n_, int group_m_ = 8) {
+  bool turn;               // see take
+  int group, in_group;     // of next_id: its group of GROUP_M rows of tiles, and its place there
+  int group_step, in_group_step, round;
+  // The 32 workgroups of an XCD work on 32 consecutive ids = GROUP_M x (32 / GROUP_M)
+  // tiles, which load GROUP_M A panels and 32 / GROUP_M B panels: a B panel is shared by GROUP_M tiles, an A panel
+  // by 32 / GROUP_M.  Give the larger share to the operand that has to come from HBM.
+  __device__ __forceinline__ void init(int tiles_m_, int tiles_n_) {
     tiles_m = tiles_m_;
     tiles_n = tiles_n_;
-    group_m = group_m_;
     const int ntiles = tiles_m * tiles_n;
     const int bid = blockIdx.x, nblk = gridDim.x;
     const int xcd = bid & 7, local = bid >> 3;
-    turn = nblk % (group_m * tiles_n) == 0;
+    turn = nblk % (GROUP_M * tiles_n) == 0;
     if ((nblk & 7) == 0) {
       // Patches dealt round-robin over the XCDs: in round k XCD x works on patch 8 k + x, so the eight patches in
       // flight are neighbours in id order and share operand panels through the Infinity Cache.
@@ -157,32 +172,39 @@ struct TileSchedule {
       next_id = xcd * per + local;
       stride = nblk;
       end_id = ntiles;
-      return;
+    } else {
+      const int base = ntiles >> 3, rem = ntiles & 7;
+      const int start = xcd * base + min(xcd, rem);
+      end_id = start + base + (xcd < rem ? 1 : 0);
+      next_id = start + local;
+      stride = (nblk >> 3) + ((nblk & 7) > xcd ? 1 : 0);    // workgroups of this grid that sit on my XCD
     }
-    const int base = ntiles >> 3, rem = ntiles & 7;
-    const int start = xcd * base + min(xcd, rem);
-    end_id = start + base + (xcd < rem ? 1 : 0);
-    next_id = start + local;
-    stride = (nblk >> 3) + ((nblk & 7) > xcd ? 1 : 0);      // workgroups of this grid that sit on my XCD
+    const int per_group = GROUP_M * tiles_n;
+    group = next_id / per_group;
+    in_group = next_id - group * per_group;
+    group_step = stride / per_group;
+    in_group_step = stride - group_step * per_group;
+    round = 0;
   }
   __device__ __forceinline__ bool has_tile() const { return next_id < end_id; }
-  __device__ __forceinline__ int take() {                   // id of the next tile; advance
-    const int id = next_id;
-    next_id += stride;
-    return id;
-  }
-  __device__ __forceinline__ void coords(int id, int& tm, int& tn) const {
-    const int per_group = group_m * tiles_n;
-    const int g = id / per_group;
-    const int first_m = g * group_m;
-    const int gsize = min(tiles_m - first_m, group_m);
-    const int in_g = id - g * per_group;
-    tm = first_m + in_g % gsize;
-    tn = in_g / gsize;
+  // coordinates of the next tile; advance.  No division while the group is whole: this stands in every tile's epilogue.
+  __device__ __forceinline__ void take(int& tm, int& tn) {
+    const int first_m = group * GROUP_M, gsize = min(tiles_m - first_m, GROUP_M);
+    tn = gsize == GROUP_M ? in_group / GROUP_M : in_group / gsize;
+    tm = first_m + in_group - tn * gsize;
     // Where a round of the grid is a whole number of groups, a workgroup would get the same column in every round:
     // turn the columns by one a round, so that nobody is left with all the narrow last columns (two columns, 300
     // tokens: half of the workgroups had four full tiles, the other half four of 44 tokens).
-    if (turn) tn = (tn + id / (int)gridDim.x) % tiles_n;
+    if (turn) tn = (tn + round) % tiles_n;
+    ++round;
+    next_id += stride;
+    group += group_step;
+    in_group += in_group_step;
+    const int per_group = GROUP_M * tiles_n;
+    if (in_group >= per_group) {
+      in_group -= per_group;
+      ++group;
+    }
   }
 };
 
@@ -215,67 +237,76 @@ __device__ __forceinline__ int swizzle(int row) { return (row >> 1) & 7; }
 // Wave-instruction `it` of wave w fills rows (it*WAVES + w)*8 .. +7 of the slab; lane l takes row +l/8 and the
 // physical 16-byte slot l%8.  Because it*WAVES*8 rows is a multiple of 16, the swizzle (and so the logical chunk this
 // lane fetches) is the same for all instructions.
-template <typename TT, int ROWS = Shape256::BM, int WAVES = Shape256::WAVES>
+// WAVE_ROWS: rows of a wavefront's blocks (column operand; the last wavefront has nb1 blocks, the others all).
+template <typename TT, int ROWS = Shape256::BM, int WAVES = Shape256::WAVES, int WAVE_ROWS = Shape256::WAVE_N>
 struct SlabLoader {
   static constexpr int ITERS = ROWS / (8 * WAVES);
   static_assert(ITERS * 8 * WAVES == ROWS && (8 * WAVES) % 16 == 0, "whole wave-instructions, one swizzle for all");
-  // The buffer descriptor is rebuilt from these at every use; readfirstlane pins them to scalar registers, so
-  // the compiler never has to guess that the descriptor is wave-uniform (a guess it loses across loops).
-  uint32_t base_lo, base_hi, records;
+  i32x4_t desc;           // buffer descriptor
   uint32_t voff[ITERS];   // per-lane byte offset of (row, logical chunk) inside the panel at k = 0
 
   __device__ __forceinline__ void set_base(const void* base, uint32_t bytes) {
     const uint64_t p = reinterpret_cast<uint64_t>(base);
-    base_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
-    base_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32));
-    records = (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes);
+    desc = i32x4_t{__builtin_amdgcn_readfirstlane((int)(uint32_t)p),
+                   __builtin_amdgcn_readfirstlane((int)((uint32_t)(p >> 32) & 0xffffu)),
+                   __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
   }
+  // Built once a tile and used as it is: rebuilt for every slab (a dozen scalar instructions) it cost the long contractions
+  // 1 - 2 %.  readfirstlane is a no-op on scalar registers; where the compiler has lost track of a word being uniform it
+  // is what brings it back.
+  __device__ __forceinline__ i32x4_t rsrc() const {
+    return i32x4_t{__builtin_amdgcn_readfirstlane(desc[0]), __builtin_amdgcn_readfirstlane(desc[1]),
+                   __builtin_amdgcn_readfirstlane(desc[2]), __builtin_amdgcn_readfirstlane(desc[3])};
+  }
+
   __device__ __forceinline__ static int lane_chunk(int wave, int lane) {
     return (lane & 7) ^ swizzle(wave * 8 + (lane >> 3));
   }
   // base: first row of the tile; ld in elements; rows_valid <= ROWS rows exist from base on.
-  template <bool QUAD = false>
-  __device__ __forceinline__ void init(const void* base, int64_t ld, int rows_valid, int wave, int lane) {
+  template <bool NEAR = false>
+  __device__ __forceinline__ void init(const void* base, int64_t ld, int rows_valid, int wave, int lane, int nb1 = WAVE_ROWS / 16) {
     const uint32_t row_bytes = (uint32_t)(ld * (int64_t)sizeof(typename TT::store_t));
     set_base(base, row_bytes * (uint32_t)rows_valid);
     const uint32_t c16 = (uint32_t)lane_chunk(wave, lane) * 16u;
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) {
-      const int row = lane_tile_row<QUAD>(it, wave, lane);
+      const int row = lane_tile_row<NEAR>(it, wave, lane, nb1);
       voff[it] = (row < rows_valid) ? (uint32_t)row * row_bytes + c16 : OOB_OFFSET;
     }
   }
   // The tile rows this lane fetches (one per wave-instruction).
-  template <bool QUAD = false>
-  __device__ __forceinline__ static int lane_tile_row(int it, int wave, int lane) {
-    return tile_row_of<QUAD>((it * WAVES + wave) * 8 + (lane >> 3));
+  template <bool NEAR = false>
+  __device__ __forceinline__ static int lane_tile_row(int it, int wave, int lane, int nb1) {
+    const int r = (it * WAVES + wave) * 8 + (lane >> 3);
+    return tile_row_of<NEAR, WAVE_ROWS>(r, r >= ROWS - WAVE_ROWS ? nb1 : WAVE_ROWS / 16);
   }
   // Gathered panel: tile row r is a row of the whole matrix `base` (total_rows rows, < 2^31 bytes).  Free with per-lane
   // buffer offsets: this is how masked tokens are skipped without a packed copy of H.  The caller loads the gather
   // list entries itself, in one batch and ahead of time.
   // grow[it] = row of the whole matrix that tile row lane_tile_row(it) maps to (any valid row where the tile row
   // is >= rows_valid: it is not fetched).
-  template <bool QUAD = false>
+  template <bool NEAR = false>
   __device__ __forceinline__ void init_gathered(const void* base, int64_t ld, int64_t total_rows, const int (&grow)[ITERS],
-                                                int rows_valid, int wave, int lane) {
+                                                int rows_valid, int wave, int lane, int nb1 = WAVE_ROWS / 16) {
     const uint32_t row_bytes = (uint32_t)(ld * (int64_t)sizeof(typename TT::store_t));
     set_base(base, (uint32_t)total_rows * row_bytes);
     const uint32_t c16 = (uint32_t)lane_chunk(wave, lane) * 16u;
 #pragma unroll
     for (int it = 0; it < ITERS; ++it)
-      voff[it] = (lane_tile_row<QUAD>(it, wave, lane) < rows_valid) ? (uint32_t)grow[it] * row_bytes + c16 : OOB_OFFSET;
+      voff[it] = (lane_tile_row<NEAR>(it, wave, lane, nb1) < rows_valid) ? (uint32_t)grow[it] * row_bytes + c16 : OOB_OFFSET;
   }
   // One request of a slab (lds_dma16).  k0: first k of the slab (elements); K: contraction length; lds: start of this
   // operand's slab in LDS.  Lanes whose chunk lies past K fetch nothing (zeros); no slab reaches past K if !tail.
-  __device__ __forceinline__ void issue_one(char* lds, int it, int k0, int K, int wave, int lane, bool tail = true) const {
-    const i32x4_t rs = {(int)base_lo, (int)(base_hi & 0xffffu), (int)records, 0x00020000};
+  __device__ __forceinline__ void issue_one(const i32x4_t& rs, char* lds, int it, int k0, int K, int wave, int lane,
+                                            bool tail = true) const {
     lds_dma16(lds_address(lds) + (uint32_t)((it * WAVES + wave) * 8 * SLAB_ROW_BYTES),
               tail && k0 + lane_chunk(wave, lane) * TT::EPC >= K ? OOB_OFFSET : voff[it], rs,
               (uint32_t)k0 * (uint32_t)sizeof(typename TT::store_t));
   }
   __device__ __forceinline__ void issue(char* lds, int k0, int K, int wave, int lane) const {
+    const i32x4_t rs = rsrc();
 #pragma unroll
-    for (int it = 0; it < ITERS; ++it) issue_one(lds, it, k0, K, wave, lane);
+    for (int it = 0; it < ITERS; ++it) issue_one(rs, lds, it, k0, K, wave, lane);
   }
 };
 
@@ -284,10 +315,11 @@ __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane
 #define LLAMARL_FENCE() __builtin_amdgcn_sched_barrier(0)
 
 // The loads of one K slab, issued one per MFMA slot after the barrier of a k-step.
-template <typename TT>
+template <typename LA, typename LB>
 struct SlabFetch {
-  const SlabLoader<TT>* la;
-  const SlabLoader<TT>* lb;
+  const LA* la;
+  const LB* lb;
+  i32x4_t ra, rb;
   char* dst;      // stage that receives the slab
   int k0, K, wave, lane;
 };
@@ -296,9 +328,9 @@ struct SlabFetch {
 // operand stays the same across a row change (the row operand changes there).  The chip is power-limited under
 // MFMA load and operand switching costs energy: this order measured 0.5 % faster on every contraction kernel than
 // restarting each row at column block 0.
-__device__ __forceinline__ constexpr int snake_col(int t) { return ((t >> 2) & 1) ? 3 - (t & 3) : (t & 3); }
+__device__ __forceinline__ constexpr int snake(int t) { return ((t >> 2) & 1) ? 3 - (t & 3) : (t & 3); }
 
-// One k-step = one MFMA depth (two per slab): 32 slots, slot t runs block (ib, jb) = (t / 4, snake_col(t)).
+// One k-step = one MFMA depth (two per slab): 32 slots, slot t runs block (ib, jb) = (t / 4, snake(t)).
 //   a[8]   : the A fragments of this k-step, one register set each.  Block ib is done after slot 4 ib + 3 and its
 //            registers take the NEXT k-step's fragment right away (slot 4 ib + 4): 28 slots ahead of its use.
 //            a[7] of a k-step is read at its own slot 0.
@@ -320,13 +352,13 @@ __device__ __forceinline__ constexpr int snake_col(int t) { return ((t >> 2) & 1
 template <typename TT, bool BAR, bool NEXT, bool FETCH, int LS, int YOUNGER = 0, bool INIT = false>
 __device__ __forceinline__ void k_step(typename TT::frag_t (&a)[MB], const typename TT::frag_t (&bc)[NB],
                                        typename TT::frag_t (&bn)[NB], f32x4_t (&acc)[MB][NB], const char* pa_cur,
-                                       const char* pa_nxt, const char* pb_nxt, const SlabFetch<TT>* sf) {
+                                       const char* pa_nxt, const char* pb_nxt, const SlabFetch<SlabLoader<TT>, SlabLoader<TT>>* sf) {
   typedef typename TT::frag_t frag_t;
   constexpr int TB = 8;
   static_assert(MB == 8 && NB == 4, "slot table written for an 8 x 4 wave tile");
 #pragma unroll
   for (int t = 0; t < MB * NB; ++t) {
-    const int ib = t >> 2, jb = snake_col(t);
+    const int ib = t >> 2, jb = snake(t);
     if (BAR && t == TB) {
       wait_vmcnt<YOUNGER>();      // this thread's share of the next slab has landed in LDS
       __syncthreads();            // everyone's has, and everyone is done reading this slab
@@ -351,8 +383,8 @@ __device__ __forceinline__ void k_step(typename TT::frag_t (&a)[MB], const typen
     }
     if (FETCH && t >= LS && t <= LS + 14 && ((t - LS) & 1) == 0) {
       const int n = (t - LS) >> 1;
-      if (n < 4) sf->la->issue_one(sf->dst, n, sf->k0, sf->K, sf->wave, sf->lane);
-      else sf->lb->issue_one(sf->dst + SLAB_A_BYTES, n - 4, sf->k0, sf->K, sf->wave, sf->lane);
+      if (n < 4) sf->la->issue_one(sf->ra, sf->dst, n, sf->k0, sf->K, sf->wave, sf->lane);
+      else sf->lb->issue_one(sf->rb, sf->dst + SLAB_A_BYTES, n - 4, sf->k0, sf->K, sf->wave, sf->lane);
       LLAMARL_FENCE();
     }
   }
@@ -365,8 +397,7 @@ __device__ __forceinline__ void k_step(typename TT::frag_t (&a)[MB], const typen
 //   run():      the K loop.  Waves leave it at different times: __syncthreads() before reusing LDS.
 // smem must hold MAINLOOP_LDS_BYTES.
 //
-// QUAD_B: output columns are quad-interleaved over the lane's four column blocks
-// (tile_row_of); the epilogue must then take its columns from LanePos::col_quad().
+// NEAR: a lane's column blocks hold neighbouring output columns (tile_row_of); the epilogue must then take its columns from LanePos::col_quad().
 // YOUNGER, FIRST_ONLY: see run().
 template <typename TT, int LOAD_SLOT, int YOUNGER, bool FIRST_ONLY>
 struct TileGemm {
@@ -374,20 +405,21 @@ struct TileGemm {
   typedef Shape256 Shape;
   typedef typename TT::frag_t frag_t;
   static constexpr bool KMAJOR = false;
-  static constexpr bool HAS_IDLE = true;
+  static constexpr bool HAS_IDLE = true, HALVES = false;
   static constexpr int BK = 8 * TT::EPC;
   static constexpr int LDS_BYTES = MAINLOOP_LDS_BYTES;
   static constexpr int GROUPS_PER_CU = 1;      // workgroups of a persistent grid per CU
   SlabLoader<TT> la, lb;
   int K;
+  __device__ __forceinline__ static constexpr int width() { return Shape::BN; }
 
-  template <bool QUAD_B>
+  template <bool NEAR>
   __device__ __forceinline__ void prefetch(const void* A_tile, int64_t lda, int rowsA, const void* B_tile, int64_t ldb,
                                            int rowsB, int64_t K_, char* smem) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
     la.init(A_tile, lda, rowsA, wave, lane);
-    lb.template init<QUAD_B>(B_tile, ldb, rowsB, wave, lane);
+    lb.template init<NEAR>(B_tile, ldb, rowsB, wave, lane);
     la.issue(smem, 0, K, wave, lane);
     lb.issue(smem + SLAB_A_BYTES, 0, K, wave, lane);
     if (K > BK) {
@@ -399,14 +431,14 @@ struct TileGemm {
   // as prefetch, the B panel gathered: B_base is the base of the whole matrix with b_total rows, grow the gather list
   // entries of this lane (SlabLoader::init_gathered), already in registers: no global load stands between the
   // caller's barrier and the first slab request.  The requests are the caller's: issue_first(0) .. (FIRST_PARTS - 1).
-  template <bool QUAD_B>
+  template <bool NEAR>
   __device__ __forceinline__ void setup_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
                                                  int64_t ldb, int rowsB, int64_t K_, const int (&grow)[4],
                                                  int64_t b_total) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
     la.init(A_tile, lda, rowsA, wave, lane);
-    lb.template init_gathered<QUAD_B>(B_base, ldb, b_total, grow, rowsB, wave, lane);
+    lb.template init_gathered<NEAR>(B_base, ldb, b_total, grow, rowsB, wave, lane);
   }
   // Four requests a call, so that a logits kernel can spread them over its epilogue: sixteen at once (128 KB for the
   // workgroup) keep a wavefront from its epilogue for as long as the CU takes to accept them.
@@ -421,9 +453,7 @@ struct TileGemm {
   }
 
   // Instead of run() for a wavefront whose whole part of the tile lies past the matrix (wave-uniform; a last column of
-  // few tokens): its loads and barriers, nothing else.  The SIMD then belongs to the other wavefront.  The forward over
-  // a 128256 x 4096 head: 64 tokens 284 -> 259 us, 300 413 -> 382, 1100 986 -> 939.  Not used by the recompute, whose
-  // epilogue leaves no registers for the branch (4 spilled: +0.8 % at 8576 tokens for -2 % at 300).
+  // few tokens): its loads and barriers, nothing else.  The SIMD then belongs to the other wavefront.
   __device__ __forceinline__ void run_idle(char* smem) const {
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int nk = (K + BK - 1) / BK;
@@ -460,7 +490,7 @@ struct TileGemm {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       a_addr[ks] = (wm * Shape::WAVE_M + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
-      b_addr[ks] = SLAB_A_BYTES + (wn * WAVE_N + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
+      b_addr[ks] = SLAB_A_BYTES + (wn * Shape::WAVE_N + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
     }
     // Slabs 0 and 1 were issued by prefetch(); stores of a previous epilogue may sit between them and now in the
     // vmcnt queue.  Where their number is not known, wait for everything.
@@ -484,7 +514,7 @@ struct TileGemm {
     if (!FIRST_ONLY && nk > 2) {       // slab 0 apart: its barrier waits for slab 1, older than the stores too
       char* cur = smem;
       const char* nxt = smem + STAGE_BYTES;
-      const SlabFetch<TT> sf{&la, &lb, cur, 2 * BK, K, wave, lane};
+      const SlabFetch<SlabLoader<TT>, SlabLoader<TT>> sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, 2 * BK, K, wave, lane};
       k_step<TT, true, true, true, LOAD_SLOT, FIRST_ONLY ? 0 : YOUNGER>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0],
                                                                         nxt + b_addr[0], &sf);
       k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
@@ -494,7 +524,7 @@ struct TileGemm {
       char* cur = smem + (kt & 1) * STAGE_BYTES;
       const char* nxt = smem + ((kt + 1) & 1) * STAGE_BYTES;
       LLAMARL_FENCE();
-      const SlabFetch<TT> sf{&la, &lb, cur, (kt + 2) * BK, K, wave, lane};
+      const SlabFetch<SlabLoader<TT>, SlabLoader<TT>> sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, (kt + 2) * BK, K, wave, lane};
       k_step<TT, true, true, true, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0], nxt + b_addr[0], &sf);
       k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
     }
@@ -511,6 +541,181 @@ struct TileGemm {
       k_step<TT, false, false, false, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nullptr, nullptr, nullptr);
     }
   }
+};
+
+// ---- narrow tiles: 256 rows x 128 or 160 columns -----------------------------------------------------------------------
+// For few tokens against a large vocabulary, where W streams from HBM: with two slabs resident a slab took the 1.6 us of a
+// trip to memory whatever its MFMAs; here three are resident and two in flight.  Wavefronts 0 .. 3 are the left half with
+// eight column blocks, 4 .. 7 the right half with nb1 = 2 or none.
+// The slots of a k-step for a wavefront with nb column blocks: 4 nb slots, slot t runs block (snake(t), t / 4).
+struct KSlots {
+  int nb;
+  constexpr int barrier() const { return nb >= 6 ? 8 : 4; }
+  // where the next k-step's fragment of column block j < nb - 1 is read: the block is done after slot 4 j + 3
+  constexpr int column(int j) const { return j == 0 ? barrier() : j == 1 && nb >= 6 ? 9 : 4 * (j + 1); }
+  constexpr int row(int i) const { return nb >= 6 ? 10 + 4 * i : nb == 4 ? 5 + 3 * i : 4 + i; }     // ... of row block i
+  // load n = 0 .. 7 of the slab after next; first: for eight blocks, see k_step
+  constexpr int load(int n, int first) const { return nb == 8 ? first + 2 * n : nb == 6 ? 9 + 2 * n : nb == 4 ? 8 + n : 4 + n / 2; }
+};
+
+// One k-step, as k_step with the operands' roles exchanged: the column fragments b have one register set each, the four row
+// fragments are double-buffered.  LB: loads of the column operand.
+template <typename TT, typename Fetch, int nb, bool BAR, bool NEXT, bool FETCH, int YOUNGER, bool INIT, int LB>
+__device__ __forceinline__ void narrow_k_step(typename TT::frag_t (&b)[nb], const typename TT::frag_t (&ac)[4],
+                                       typename TT::frag_t (&an)[4], f32x4_t (&acc)[4][nb], const char* pb_cur,
+                                       const char* pb_nxt, const char* pa_nxt, const Fetch* sf) {
+  typedef typename TT::frag_t frag_t;
+  constexpr KSlots S{nb};
+#pragma unroll
+  for (int t = 0; t < 4 * nb; ++t) {
+    const int ib = snake(t), jb = t >> 2;
+    if (BAR && t == S.barrier()) {
+      wait_vmcnt<YOUNGER>();      // this thread's share of the next slab has landed in LDS
+      __syncthreads();            // everyone's has, and everyone is done reading this slab
+      LLAMARL_FENCE();
+    }
+    if (INIT) acc[ib][jb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    mma(ac[ib], b[jb], acc[ib][jb]);
+    LLAMARL_FENCE();
+    if (t == 0) {
+      b[nb - 1] = *reinterpret_cast<const frag_t*>(pb_cur + (nb - 1) * BLOCK_BYTES);
+      LLAMARL_FENCE();
+    }
+    if (NEXT) {
+#pragma unroll
+      for (int j = 0; j < nb - 1; ++j)
+        if (t == S.column(j)) b[j] = *reinterpret_cast<const frag_t*>(pb_nxt + j * BLOCK_BYTES);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (t == S.row(i)) an[i] = *reinterpret_cast<const frag_t*>(pa_nxt + i * BLOCK_BYTES);
+      LLAMARL_FENCE();
+    }
+    if (FETCH) {
+#pragma unroll
+      for (int n = 0; n < 4 + LB; ++n)
+        if (t == S.load(n, 11)) {
+          if (n < 4) sf->la->issue_one(sf->ra, sf->dst, n, sf->k0, sf->K, sf->wave, sf->lane);
+          else sf->lb->issue_one(sf->rb, sf->dst + SLAB_A_BYTES, n - 4, sf->k0, sf->K, sf->wave, sf->lane);
+          LLAMARL_FENCE();
+        }
+    }
+  }
+}
+
+template <typename TT>
+struct TileGemmNarrow {
+  typedef TT Type;
+  typedef Shape256Halves Shape;
+  typedef typename TT::frag_t frag_t;
+  typedef SlabLoader<TT> LoaderA;
+  typedef SlabLoader<TT, Shape::BN, Shape::WAVES, Shape::WAVE_N> LoaderB;
+  typedef SlabFetch<LoaderA, LoaderB> Fetch;
+  static constexpr bool KMAJOR = false;
+  static constexpr bool HAS_IDLE = true, HALVES = true;
+  static constexpr int BK = 8 * TT::EPC;
+  static constexpr int LDS_BYTES = NARROW_LDS_BYTES;
+  static constexpr int FIRST_PARTS = 2;        // see TileGemm::issue_first
+  static constexpr int COUNTED_STORES = 2;     // see TileGemm::run
+  LoaderA la;
+  LoaderB lb;
+  int K;
+  int nb1;
+  __device__ __forceinline__ int width() const { return Shape::WAVE_N + 16 * nb1; }
+
+  template <bool NEAR>
+  __device__ __forceinline__ void setup_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
+                                                 int64_t ldb, int rowsB, int64_t K_, const int (&grow)[LoaderB::ITERS],
+                                                 int64_t b_total) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    K = (int)K_;
+    la.init(A_tile, lda, rowsA, wave, lane);
+    lb.template init_gathered<NEAR>(B_base, ldb, b_total, grow, rowsB, wave, lane, nb1);
+  }
+  // per-lane read addresses of block 0: row = lane % 16, chunk 4 ks + lane / 16 of k-step ks, swizzled.  The
+  // swizzle depends on the low four row bits only, so block i is the same address + i * BLOCK_BYTES.
+  __device__ __forceinline__ static void fragment_addresses(int (&a_addr)[2], int (&b_addr)[2]) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int g = lane >> 4, l16 = lane & 15, sw = swizzle(l16);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      a_addr[ks] = (Shape::wave_row(wave) * Shape::WAVE_M + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
+      b_addr[ks] = SLAB_A_BYTES + (Shape::wave_col(wave) * Shape::WAVE_N + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
+    }
+  }
+  template <int nb>
+  __device__ __forceinline__ static void first_fragments(const char* smem, const int (&a_addr)[2], const int (&b_addr)[2],
+                                                         frag_t (&b)[nb], frag_t (&a)[4]) {
+    b[0] = *reinterpret_cast<const frag_t*>(smem + b_addr[0]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const frag_t*>(smem + a_addr[0] + i * BLOCK_BYTES);
+#pragma unroll
+    for (int j = 1; j < nb - 1; ++j) b[j] = *reinterpret_cast<const frag_t*>(smem + b_addr[0] + j * BLOCK_BYTES);
+  }
+
+  // Column rows of a slab: 128 by two loads of everyone, 32 by a third of wavefronts 0 .. 3; slabs past K are requested
+  // like the others (zeros, no traffic), so that the waits can count.
+  template <int nb>
+  static constexpr int LB_LOADS = nb == 8 ? 3 : 2;      // the left half is wavefronts 0 .. 3
+  template <int nb>
+  __device__ __forceinline__ void issue(char* st, int kt) const {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    la.issue(st, kt * BK, K, wave, lane);
+    const i32x4_t rs = lb.rsrc();
+#pragma unroll
+    for (int it = 0; it < LB_LOADS<nb>; ++it) lb.issue_one(rs, st + SLAB_A_BYTES, it, kt * BK, K, wave, lane);
+  }
+  template <int nb>
+  __device__ __forceinline__ void issue_first(char* smem, int part) const {      // as issue_first
+    if (part < 2) issue<nb>(smem + part * NARROW_STAGE_BYTES, part);
+  }
+  __device__ __forceinline__ static char* stage(char* smem, int s) { return smem + s * NARROW_STAGE_BYTES; }
+  template <int nb>
+  __device__ __forceinline__ void run_idle(char* smem) const {
+    const int nk = (K + BK - 1) / BK;
+    wait_vmcnt0();
+    __syncthreads();
+    issue<nb>(stage(smem, 2), 2);
+    int st = 0;
+    for (int kt = 0; kt < nk - 1; ++kt) {
+      wait_vmcnt<4 + LB_LOADS<nb>>();
+      __syncthreads();
+      issue<nb>(stage(smem, st), kt + 3);
+      st = st == 2 ? 0 : st + 1;
+    }
+  }
+  template <int nb>
+  __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[4][nb], bool counted) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int nk = (K + BK - 1) / BK;
+    constexpr int LB = LB_LOADS<nb>;
+    int a_addr[2], b_addr[2];
+    fragment_addresses(a_addr, b_addr);
+    if (counted) wait_vmcnt<COUNTED_STORES>();
+    else wait_vmcnt0();
+    __syncthreads();
+    issue<nb>(stage(smem, 2), 2);      // not earlier: an epilogue may use that stage
+    frag_t b[nb], a0[4], a1[4];
+    first_fragments<nb>(smem, a_addr, b_addr, b, a0);
+    LLAMARL_FENCE();
+    narrow_k_step<TT, Fetch, nb, false, true, false, 0, true, LB>(b, a0, a1, acc, smem + b_addr[0], smem + b_addr[1],
+                                                               smem + a_addr[1], nullptr);
+    int st = 0;
+    for (int kt = 0; kt < nk - 1; ++kt) {
+      char* cur = stage(smem, st);
+      st = st == 2 ? 0 : st + 1;
+      const char* nxt = stage(smem, st);
+      LLAMARL_FENCE();
+      const Fetch sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, (kt + 3) * BK, K, wave, lane};
+      narrow_k_step<TT, Fetch, nb, true, true, true, 4 + LB, false, LB>(b, a1, a0, acc, cur + b_addr[1], nxt + b_addr[0],
+                                                                     nxt + a_addr[0], &sf);
+      narrow_k_step<TT, Fetch, nb, false, true, false, 0, false, LB>(b, a0, a1, acc, nxt + b_addr[0], nxt + b_addr[1],
+                                                                  nxt + a_addr[1], nullptr);
+    }
+    const char* cur = stage(smem, st);
+    LLAMARL_FENCE();
+    narrow_k_step<TT, Fetch, nb, false, false, false, 0, false, LB>(b, a1, a0, acc, cur + b_addr[1], nullptr, nullptr, nullptr);
+  }
+
 };
 
 }  // namespace llamarl

@@ -66,10 +66,10 @@ struct TileGemmSmall {
   typedef TT Type;
   typedef S Shape;
   typedef typename TT::frag_t frag_t;
-  typedef SlabLoader<TT, S::BM, S::WAVES> LoaderA;
-  typedef SlabLoader<TT, S::BN, S::WAVES> LoaderB;
+  typedef SlabLoader<TT, S::BM, S::WAVES, S::WAVE_N> LoaderA;
+  typedef SlabLoader<TT, S::BN, S::WAVES, S::WAVE_N> LoaderB;
   static constexpr bool KMAJOR = false;
-  static constexpr bool HAS_IDLE = false;
+  static constexpr bool HAS_IDLE = false, HALVES = false;
   static constexpr int BK = 8 * TT::EPC;
   static constexpr int LDS_BYTES = NSTAGE * S::STAGE_BYTES + 16;     // + a flag (fp32: redo this tile)
   static constexpr int GROUPS_PER_CU = GROUPS_PER_CU_;
@@ -77,6 +77,7 @@ struct TileGemmSmall {
   LoaderA la;
   LoaderB lb;
   int K;
+  __device__ __forceinline__ static constexpr int width() { return S::BN; }
   float unscale;     // run<true> only
 
   // A slab past K fetches nothing (every lane out of the descriptor's range: zeros land in LDS), so the number of
@@ -91,32 +92,32 @@ struct TileGemmSmall {
     for (int i = 0; i < NSTAGE - 1; ++i) issue(smem + i * S::STAGE_BYTES, i);
   }
 
-  template <bool QUAD_B>
+  template <bool NEAR>
   __device__ __forceinline__ void prefetch(const void* A_tile, int64_t lda, int rowsA, const void* B_tile, int64_t ldb,
                                            int rowsB, int64_t K_, char* smem) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
     la.init(A_tile, lda, rowsA, wave, lane);
-    lb.template init<QUAD_B>(B_tile, ldb, rowsB, wave, lane);
+    lb.template init<NEAR>(B_tile, ldb, rowsB, wave, lane);
     first_slabs(smem);
   }
-  template <bool QUAD_B>
+  template <bool NEAR>
   __device__ __forceinline__ void setup_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
                                                  int64_t ldb, int rowsB, int64_t K_, const int (&grow)[LoaderB::ITERS],
                                                  int64_t b_total) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
     la.init(A_tile, lda, rowsA, wave, lane);
-    lb.template init_gathered<QUAD_B>(B_base, ldb, b_total, grow, rowsB, wave, lane);
+    lb.template init_gathered<NEAR>(B_base, ldb, b_total, grow, rowsB, wave, lane);
   }
   static constexpr int FIRST_PARTS = 1;
   __device__ __forceinline__ void issue_first(char* smem, int) const { first_slabs(smem); }
 
-  __device__ __forceinline__ static void clear(f32x4_t (&acc)[S::MB][NB]) {
+  __device__ __forceinline__ static void clear(f32x4_t (&acc)[S::MB][S::NB]) {
 #pragma unroll
     for (int i = 0; i < S::MB; ++i)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < S::NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
 
   // the MFMAs of one slab; a_addr / b_addr: this lane's chunk of block 0 in either half of a slab row.
@@ -124,20 +125,20 @@ struct TileGemmSmall {
   // times a_factor
   template <bool SPLIT>
   __device__ __forceinline__ static void slab(const char* st, const int (&a_addr)[2], const int (&b_addr)[2],
-                                              f32x4_t (&acc)[S::MB][NB], f32x4_t (&low)[S::MB][NB], uint32_t& lost,
+                                              f32x4_t (&acc)[S::MB][S::NB], f32x4_t (&low)[S::MB][S::NB], uint32_t& lost,
                                               float a_factor) {
     if constexpr (sizeof(typename TT::store_t) == 2) {
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        frag_t b[NB], a[S::MB];
+        frag_t b[S::NB], a[S::MB];
 #pragma unroll
-        for (int j = 0; j < NB; ++j) b[j] = *reinterpret_cast<const frag_t*>(st + b_addr[ks] + j * BLOCK_BYTES);
+        for (int j = 0; j < S::NB; ++j) b[j] = *reinterpret_cast<const frag_t*>(st + b_addr[ks] + j * BLOCK_BYTES);
 #pragma unroll
         for (int i = 0; i < S::MB; ++i) a[i] = *reinterpret_cast<const frag_t*>(st + a_addr[ks] + i * BLOCK_BYTES);
 #pragma unroll
         for (int i = 0; i < S::MB; ++i)
 #pragma unroll
-          for (int j = 0; j < NB; ++j) mma(a[i], b[j], acc[i][j]);
+          for (int j = 0; j < S::NB; ++j) mma(a[i], b[j], acc[i][j]);
       }
     } else if constexpr (!SPLIT) {
 #pragma unroll
@@ -148,15 +149,15 @@ struct TileGemmSmall {
 #pragma unroll
           for (int r = 0; r < 4; ++r) a[r] *= a_factor;
 #pragma unroll
-          for (int j = 0; j < NB; ++j)
+          for (int j = 0; j < S::NB; ++j)
             mma(a, *reinterpret_cast<const frag_t*>(st + b_addr[ks] + j * BLOCK_BYTES), acc[i][j]);
         }
     } else {
       // The 32 k of a slab are one k-step of the 16x16x32 MFMA.  Which k sits at which position of the fragment does
       // not matter as long as both operands agree: a lane takes the chunks of the two conflict-free reads.
-      Split3 b[NB];
+      Split3 b[S::NB];
 #pragma unroll
-      for (int j = 0; j < NB; ++j)
+      for (int j = 0; j < S::NB; ++j)
         b[j] = split3(*reinterpret_cast<const frag_t*>(st + b_addr[0] + j * BLOCK_BYTES),
                       *reinterpret_cast<const frag_t*>(st + b_addr[1] + j * BLOCK_BYTES), lost);
 #pragma unroll
@@ -165,21 +166,21 @@ struct TileGemmSmall {
                                 *reinterpret_cast<const frag_t*>(st + a_addr[1] + i * BLOCK_BYTES), lost);
         // j innermost: consecutive MFMAs do not wait for each other's accumulator
 #pragma unroll
-        for (int j = 0; j < NB; ++j) mma(a.m, b[j].l, low[i][j]);
+        for (int j = 0; j < S::NB; ++j) mma(a.m, b[j].l, low[i][j]);
 #pragma unroll
-        for (int j = 0; j < NB; ++j) mma(a.l, b[j].m, low[i][j]);
+        for (int j = 0; j < S::NB; ++j) mma(a.l, b[j].m, low[i][j]);
 #pragma unroll
-        for (int j = 0; j < NB; ++j) mma(a.l, b[j].h, low[i][j]);
+        for (int j = 0; j < S::NB; ++j) mma(a.l, b[j].h, low[i][j]);
 #pragma unroll
-        for (int j = 0; j < NB; ++j) mma(a.h, b[j].l, low[i][j]);
+        for (int j = 0; j < S::NB; ++j) mma(a.h, b[j].l, low[i][j]);
 #pragma unroll
-        for (int j = 0; j < NB; ++j) mma(a.m, b[j].m, low[i][j]);
+        for (int j = 0; j < S::NB; ++j) mma(a.m, b[j].m, low[i][j]);
 #pragma unroll
-        for (int j = 0; j < NB; ++j) mma(a.m, b[j].h, low[i][j]);
+        for (int j = 0; j < S::NB; ++j) mma(a.m, b[j].h, low[i][j]);
 #pragma unroll
-        for (int j = 0; j < NB; ++j) mma(a.h, b[j].m, low[i][j]);
+        for (int j = 0; j < S::NB; ++j) mma(a.h, b[j].m, low[i][j]);
 #pragma unroll
-        for (int j = 0; j < NB; ++j) mma(a.h, b[j].h, acc[i][j]);
+        for (int j = 0; j < S::NB; ++j) mma(a.h, b[j].h, acc[i][j]);
       }
     }
   }
@@ -187,7 +188,7 @@ struct TileGemmSmall {
   // the K loop; the first slabs are on their way
   template <bool SPLIT>
   __device__ __forceinline__ void slabs(char* smem, const int (&a_addr)[2], const int (&b_addr)[2],
-                                        f32x4_t (&acc)[S::MB][NB], f32x4_t (&low)[S::MB][NB], uint32_t& lost,
+                                        f32x4_t (&acc)[S::MB][S::NB], f32x4_t (&low)[S::MB][S::NB], uint32_t& lost,
                                         float a_factor) const {
     const int nk = (K + BK - 1) / BK;
     wait_vmcnt0();                     // the first slabs (and stores of a previous epilogue, which may sit between)
@@ -208,7 +209,7 @@ struct TileGemmSmall {
   // A_SCALED (fp32): A holds its values divided by `unscale`, a power of two; the sums come out unscaled.  The native pass
   // unscales the operand itself: what it is there for may be a sum that only overflows scaled.
   template <bool A_SCALED = false>
-  __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[S::MB][NB]) {
+  __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[S::MB][S::NB]) {
     constexpr bool SPLIT = sizeof(typename TT::store_t) == 4;
     const float factor = A_SCALED ? unscale : 1.f;
     const int lane = threadIdx.x & 63, wave = wave_id();
@@ -218,11 +219,11 @@ struct TileGemmSmall {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       a_addr[ks] = (wm * S::WAVE_M + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
-      b_addr[ks] = S::SLAB_A_BYTES + (wn * WAVE_N + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
+      b_addr[ks] = S::SLAB_A_BYTES + (wn * S::WAVE_N + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
     }
     int* redo = reinterpret_cast<int*>(smem + NSTAGE * S::STAGE_BYTES);
     if (SPLIT && threadIdx.x == 0) *redo = 0;
-    f32x4_t low[S::MB][NB];
+    f32x4_t low[S::MB][S::NB];
     uint32_t lost = 0;
     clear(acc);
     clear(low);
@@ -232,7 +233,7 @@ struct TileGemmSmall {
 #pragma unroll
       for (int i = 0; i < S::MB; ++i)
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
+        for (int j = 0; j < S::NB; ++j)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             acc[i][j][r] += low[i][j][r];

@@ -36,8 +36,9 @@ struct KMajorLoader {
   uint32_t row_bytes, col0_bytes;
   uint32_t voff;               // this lane's (k-row inside a 16-row group, logical chunk) byte offset
 
-  // origin = element (first k-row of the range, column col0) of a matrix with ld columns
-  __device__ __forceinline__ void init(const void* origin, int64_t ld, int64_t col0, int wave, int lane) {
+  // origin = element (first k-row of the range, column col0) of a matrix with ld columns; the tile's first `width`
+  // columns are fetched
+  __device__ __forceinline__ void init(const void* origin, int64_t ld, int64_t col0, int width, int wave, int lane) {
     const uint64_t p = reinterpret_cast<uint64_t>(origin);
     base_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
     base_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32));
@@ -47,7 +48,7 @@ struct KMajorLoader {
     // Bits 0, 1 and 3 of the row do not depend on `it`, so one offset serves all four instructions.
     const int r = 2 * wave + (lane >> 5);
     const int c = (lane & 31) ^ km_swz(r);
-    voff = (uint32_t)r * row_bytes + (uint32_t)c * 16u;
+    voff = c * 8 < width ? (uint32_t)r * row_bytes + (uint32_t)c * 16u : OOB_OFFSET;
   }
   // slab kt of a K range of k_len rows -> lds: the descriptor (uniform) once, then four loads
   struct Slab {
@@ -78,14 +79,16 @@ struct KMajorLoader {
 
 struct TileGemmTN {
   typedef BF16 Type;
-  typedef Shape256Rows Shape;
+  typedef Shape256Halves Shape;
   typedef bf16x8_t frag_t;
   static constexpr bool KMAJOR = true;
-  static constexpr bool HAS_IDLE = true;
+  static constexpr bool HAS_IDLE = true, HALVES = true;
   static constexpr int LDS_BYTES = MAINLOOP_LDS_BYTES;
   static constexpr int GROUPS_PER_CU = 1;
   KMajorLoader la, lb;
   int k_len;
+  int nb1;                                     // column blocks of the right half: 0, 2, .., 8 (Shape256Halves)
+  __device__ __forceinline__ int width() const { return Shape::WAVE_N + 16 * nb1; }
 
   // At_origin / Bt_origin: element (first k-row of the range, first column of the tile).  Columns past the
   // matrix edge read the neighbouring row's finite values: they only reach output rows / columns nobody stores.
@@ -94,8 +97,8 @@ struct TileGemmTN {
                                            char* smem) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     k_len = k_len_;
-    la.init(At_origin, lda, a_col0, wave, lane);
-    lb.init(Bt_origin, ldb, b_col0, wave, lane);
+    la.init(At_origin, lda, a_col0, Shape::BM, wave, lane);
+    lb.init(Bt_origin, ldb, b_col0, width(), wave, lane);
     la.issue(smem, 0, k_len, wave);
     lb.issue(smem + SLAB_A_BYTES, 0, k_len, wave);
     if (k_len > 64) {
@@ -123,59 +126,67 @@ struct TileGemmTN {
   };
 
   // Address of block b's fragment: blocks are 32 bytes (two chunks) apart before the chunk swizzle, which XORs bits
-  // 1..3 of the chunk index -- bits the block index occupies too -- so it is an XOR, not an add.  A: the 8 blocks
-  // of a wave span bits 1..3 (fx = the whole swizzle).  B: the 4 blocks span bits 1..2 and the wave's position
+  // 1..3 of the chunk index -- bits the block index occupies too -- so it is an XOR, not an add.  B: the 8 blocks
+  // of a wave span bits 1..3 (fx = the whole swizzle).  A: the 4 blocks span bits 1..2 and the wave's position
   // bits 3..4, so bit 3 of the swizzle is folded into the base and fx carries bits 1..2 only.
   __device__ __forceinline__ static const char* blk(const char* base, int b, int fx) { return base + ((b * 32) ^ fx); }
 
-  // One k-step (32 k-rows); the slot table of k_step in gemm_nt.h with the barrier of a slab's last k-step moved up
-  // to slot 4 and the slab loads to the odd slots 5 .. 19.  Every fragment is two LDS instructions here, so the 24
-  // reads of the next slab need the room: barrier at slot 8 / loads from slot 11 measured 3.4 % slower for the dH
-  // contraction, barrier at slot 6: 0.8 % slower, at slot 2: 0.5 % slower; loads on even slots (where the fragment
-  // reads sit): 4 - 6 % slower.  (The K-contiguous loop does not care: +-0.5 % for the same moves.)
-  // pa / pb: slab base + this lane's row and byte offset for the k-step; fx: the lane's chunk swizzle in bytes.
-  template <bool BAR, bool NEXT, bool FETCH>
-  __device__ __forceinline__ static void k_step(frag_t (&a)[MB], const frag_t (&bc)[NB], frag_t (&bn)[NB],
-                                                f32x4_t (&acc)[MB][NB], const char* pa_cur, const char* pa_nxt,
-                                                const char* pb_nxt, int fx, int fxb, const Fetch* f) {
-    constexpr int TB = 4;      // barrier slot: a[7], the last read of the slab, was issued at slot 0
-    constexpr int LS = 5;      // first of the eight load slots (every other slot from here)
-    static_assert(MB == 8 && NB == 4, "slot table written for an 8 x 4 wave tile");
+  // The slots (KSlots) with the barrier of a slab's last k-step moved up to slot 4 and the slab loads to the odd slots
+  // 5 .. 19.  Every fragment is two LDS instructions here, so the 24 reads of the next slab need the room: barrier at slot
+  // 8 / loads from slot 11 measured 3.4 % slower for the dH contraction, barrier at slot 6: 0.8 % slower, at slot 2: 0.5 %
+  // slower; loads on even slots (where the fragment reads sit): 4 - 6 % slower.  (The K-contiguous loop does not care:
+  // +-0.5 % for the same moves.)
+  struct Slots {
+    int nb;
+    constexpr int barrier() const { return 4; }
+    constexpr int column(int j) const { return 4 * (j + 1); }
+    constexpr int row(int i) const { return KSlots{nb}.row(i); }
+    constexpr int load(int n) const { return nb >= 6 ? 5 + 2 * n : KSlots{nb}.load(n, 0); }
+  };
+  // One k-step (32 k-rows), as narrow_k_step in gemm_nt.h.  pa / pb: slab base + this lane's row and byte offset for the k-step;
+  // fx: the lane's chunk swizzle in bytes.
+  template <int nb, bool BAR, bool NEXT, bool FETCH, bool INIT = false>
+  __device__ __forceinline__ static void k_step(frag_t (&b)[nb], const frag_t (&ac)[4], frag_t (&an)[4],
+                                                f32x4_t (&acc)[4][nb], const char* pb_cur, const char* pb_nxt,
+                                                const char* pa_nxt, int fx, int fxa, const Fetch* f) {
+    constexpr Slots S{nb};
 #pragma unroll
-    for (int t = 0; t < MB * NB; ++t) {
-      const int ib = t >> 2, jb = snake_col(t);
-      if (BAR && t == TB) {
+    for (int t = 0; t < 4 * nb; ++t) {
+      const int ib = snake(t), jb = t >> 2;
+      if (BAR && t == S.barrier()) {      // b[nb - 1], the last read of the slab, was issued at slot 0
         wait_vmcnt0();      // this thread's share of the next slab has landed in LDS
         __syncthreads();    // everyone's has, and everyone is done reading this slab
         LLAMARL_FENCE();
       }
-      mma(a[ib], bc[jb], acc[ib][jb]);
+      if (INIT) acc[ib][jb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      mma(ac[ib], b[jb], acc[ib][jb]);
       LLAMARL_FENCE();
       if (t == 0) {
-        a[7] = read_frag(blk(pa_cur, 7, fx));
+        b[nb - 1] = read_frag(blk(pb_cur, nb - 1, fx));
         LLAMARL_FENCE();
       }
       if (NEXT) {
-        if (t == 4) a[0] = read_frag(blk(pa_nxt, 0, fx));        // block 0 is done after slot 3, block 1 after slot 7
-        if (t == 8) a[1] = read_frag(blk(pa_nxt, 1, fx));
-        if (t >= 12 && (t & 3) == 0) a[ib - 1] = read_frag(blk(pa_nxt, ib - 1, fx));
-        if (t == 10) bn[0] = read_frag(blk(pb_nxt, 0, fxb));
-        if (t == 14) bn[1] = read_frag(blk(pb_nxt, 1, fxb));
-        if (t == 18) bn[2] = read_frag(blk(pb_nxt, 2, fxb));
-        if (t == 22) bn[3] = read_frag(blk(pb_nxt, 3, fxb));
+#pragma unroll
+        for (int j = 0; j < nb - 1; ++j)
+          if (t == S.column(j)) b[j] = read_frag(blk(pb_nxt, j, fx));
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (t == S.row(i)) an[i] = read_frag(blk(pa_nxt, i, fxa));
         LLAMARL_FENCE();
       }
-      if (FETCH && t >= LS && t <= LS + 14 && ((t - LS) & 1) == 0) {
-        const int n = (t - LS) >> 1;
-        if (n < 4) f->la->issue_one(f->sa, n, f->wave);
-        else f->lb->issue_one(f->sb, n - 4, f->wave);
-        LLAMARL_FENCE();
+      if (FETCH) {
+#pragma unroll
+        for (int n = 0; n < 8; ++n)
+          if (t == S.load(n)) {
+            if (n < 4) f->la->issue_one(f->sa, n, f->wave);
+            else f->lb->issue_one(f->sb, n - 4, f->wave);
+            LLAMARL_FENCE();
+          }
       }
     }
   }
 
-  // as TileGemm::run_idle, for wavefronts past the last row.  dH over a 128256 x 4096 head: 300 tokens 414 -> 385 us,
-  // 1100 1030 -> 994, 8576 (half a last tile of 34) within noise.
+  // as TileGemm::run_idle
   __device__ __forceinline__ void run_idle(char* smem) const {
     const int wave = wave_id();
     const int nk = (k_len + 63) / 64;
@@ -194,15 +205,10 @@ struct TileGemmTN {
     }
   }
 
-  __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[MB][NB]) {
+  template <int nb>                            // column blocks of this wavefront
+  __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[4][nb]) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int wm = Shape::wave_row(wave), wn = Shape::wave_col(wave);
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int j = 0; j < NB; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
     const int nk = (k_len + 63) / 64;
 
     // lane -> what it LOADS for the transposing read: lane group g = lane / 16 serves k-rows 8g .. 8g+7 of a k-step;
@@ -211,41 +217,42 @@ struct TileGemmTN {
     const int krow = 8 * g + jrow;
     const int fx = km_swz(krow) * 16;                  // same for krow + 4; bit 3 of the k-row is g & 1 in both k-steps
     // block 0 of this wave: chunk (column / 8) before the swizzle, + the 8-byte half the lane's 4 columns sit in
-    const int a_off = krow * KM_ROW_BYTES + (wm * Shape::WAVE_M / 8 + (q4 >> 1)) * 16 + (q4 & 1) * 8;
-    const int fxb = fx & 0x60;
-    const int b_off = SLAB_A_BYTES + krow * KM_ROW_BYTES + ((wn * WAVE_N * 2) ^ (fx & 0x80)) + (q4 >> 1) * 16 + (q4 & 1) * 8;
+    const int b_off = SLAB_A_BYTES + krow * KM_ROW_BYTES + (wn * Shape::WAVE_N / 8 + (q4 >> 1)) * 16 + (q4 & 1) * 8;
+    const int fxa = fx & 0x60;
+    const int a_off = krow * KM_ROW_BYTES + ((wm * Shape::WAVE_M * 2) ^ (fx & 0x80)) + (q4 >> 1) * 16 + (q4 & 1) * 8;
     constexpr int KS = 32 * KM_ROW_BYTES;              // bytes between the two k-steps of a slab
 
     wait_vmcnt0();
     __syncthreads();
-    frag_t a[MB], b0[NB], b1[NB];
-    a[0] = read_frag(blk(smem + a_off, 0, fx));
+    frag_t b[nb], a0[4], a1[4];
+    b[0] = read_frag(blk(smem + b_off, 0, fx));
 #pragma unroll
-    for (int j = 0; j < NB; ++j) b0[j] = read_frag(blk(smem + b_off, j, fxb));
+    for (int i = 0; i < 4; ++i) a0[i] = read_frag(blk(smem + a_off, i, fxa));
 #pragma unroll
-    for (int i = 1; i < MB - 1; ++i) a[i] = read_frag(blk(smem + a_off, i, fx));
+    for (int j = 1; j < nb - 1; ++j) b[j] = read_frag(blk(smem + b_off, j, fx));
 
-    // slabs 0 .. nk-3 fetch slab kt+2 after their barrier; slab nk-2 and the last slab follow, written out
+    // as TileGemm::run
+    LLAMARL_FENCE();
+    k_step<nb, false, true, false, true>(b, a0, a1, acc, smem + b_off, smem + b_off + KS, smem + a_off + KS, fx, fxa, nullptr);
     for (int kt = 0; kt < nk - 2; ++kt) {
       char* cur = smem + (kt & 1) * STAGE_BYTES;
       const char* nxt = smem + ((kt + 1) & 1) * STAGE_BYTES;
       LLAMARL_FENCE();
-      k_step<false, true, false>(a, b0, b1, acc, cur + a_off, cur + a_off + KS, cur + b_off + KS, fx, fxb, nullptr);
       const Fetch f{&la, &lb, la.slab(cur, kt + 2, k_len), lb.slab(cur + SLAB_A_BYTES, kt + 2, k_len), wave};
-      k_step<true, true, true>(a, b1, b0, acc, cur + a_off + KS, nxt + a_off, nxt + b_off, fx, fxb, &f);
+      k_step<nb, true, true, true>(b, a1, a0, acc, cur + b_off + KS, nxt + b_off, nxt + a_off, fx, fxa, &f);
+      k_step<nb, false, true, false>(b, a0, a1, acc, nxt + b_off, nxt + b_off + KS, nxt + a_off + KS, fx, fxa, nullptr);
     }
     if (nk >= 2) {
       const char* cur = smem + ((nk - 2) & 1) * STAGE_BYTES;
       const char* nxt = smem + ((nk - 1) & 1) * STAGE_BYTES;
       LLAMARL_FENCE();
-      k_step<false, true, false>(a, b0, b1, acc, cur + a_off, cur + a_off + KS, cur + b_off + KS, fx, fxb, nullptr);
-      k_step<true, true, false>(a, b1, b0, acc, cur + a_off + KS, nxt + a_off, nxt + b_off, fx, fxb, nullptr);
+      k_step<nb, true, true, false>(b, a1, a0, acc, cur + b_off + KS, nxt + b_off, nxt + a_off, fx, fxa, nullptr);
+      k_step<nb, false, true, false>(b, a0, a1, acc, nxt + b_off, nxt + b_off + KS, nxt + a_off + KS, fx, fxa, nullptr);
     }
     {
       const char* cur = smem + ((nk - 1) & 1) * STAGE_BYTES;
       LLAMARL_FENCE();
-      k_step<false, true, false>(a, b0, b1, acc, cur + a_off, cur + a_off + KS, cur + b_off + KS, fx, fxb, nullptr);
-      k_step<false, false, false>(a, b1, b0, acc, cur + a_off + KS, nullptr, nullptr, fx, fxb, nullptr);
+      k_step<nb, false, false, false>(b, a1, a0, acc, cur + b_off + KS, nullptr, nullptr, fx, fxa, nullptr);
     }
   }
 };
@@ -303,13 +310,14 @@ struct TileGemmTNSmall {
   typedef KMajorLoaderSmall<S::BM, S::WAVES> LoaderA;
   typedef KMajorLoaderSmall<S::BN, S::WAVES> LoaderB;
   static constexpr bool KMAJOR = true;
-  static constexpr bool HAS_IDLE = false;
+  static constexpr bool HAS_IDLE = false, HALVES = false;
   static constexpr int LDS_BYTES = NSTAGE * S::STAGE_BYTES;
   static constexpr int GROUPS_PER_CU = GROUPS_PER_CU_;
   static constexpr int LOADS = LoaderA::ITERS + LoaderB::ITERS;
   LoaderA la;
   LoaderB lb;
   int k_len;
+  __device__ __forceinline__ static constexpr int width() { return S::BN; }
 
   __device__ __forceinline__ void issue(char* stage, int kt) const {
     const int wave = wave_id();
@@ -339,24 +347,24 @@ struct TileGemmTNSmall {
     return __builtin_bit_cast(frag_t, v);
   }
 
-  __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[S::MB][NB]) {
+  __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[S::MB][S::NB]) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int wm = S::wave_row(wave), wn = S::wave_col(wave);
     // lane -> k-row and 8-byte piece it loads for the transposing reads: see TileGemmTN::run
     const int g = lane >> 4, jrow = (lane >> 2) & 3, q4 = lane & 3, krow = 8 * g + jrow;
-    int a_off[S::MB], b_off[NB];
+    int a_off[S::MB], b_off[S::NB];
 #pragma unroll
     for (int i = 0; i < S::MB; ++i)
       a_off[i] = krow * LoaderA::ROW_BYTES + (((wm * S::WAVE_M / 8 + 2 * i) ^ km_swz_of<S::BM>(krow)) + (q4 >> 1)) * 16 +
                  (q4 & 1) * 8;
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
+    for (int j = 0; j < S::NB; ++j)
       b_off[j] = S::SLAB_A_BYTES + krow * LoaderB::ROW_BYTES +
-                 (((wn * WAVE_N / 8 + 2 * j) ^ km_swz_of<S::BN>(krow)) + (q4 >> 1)) * 16 + (q4 & 1) * 8;
+                 (((wn * S::WAVE_N / 8 + 2 * j) ^ km_swz_of<S::BN>(krow)) + (q4 >> 1)) * 16 + (q4 & 1) * 8;
 #pragma unroll
     for (int i = 0; i < S::MB; ++i)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < S::NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int nk = (k_len + 63) / 64;
     wait_vmcnt0();
     __syncthreads();
@@ -370,15 +378,15 @@ struct TileGemmTNSmall {
       const char* cur = smem + st * S::STAGE_BYTES;
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        frag_t a[S::MB], b[NB];
+        frag_t a[S::MB], b[S::NB];
 #pragma unroll
-        for (int j = 0; j < NB; ++j) b[j] = read_frag<LoaderB::ROW_BYTES>(cur + b_off[j] + ks * 32 * LoaderB::ROW_BYTES);
+        for (int j = 0; j < S::NB; ++j) b[j] = read_frag<LoaderB::ROW_BYTES>(cur + b_off[j] + ks * 32 * LoaderB::ROW_BYTES);
 #pragma unroll
         for (int i = 0; i < S::MB; ++i) a[i] = read_frag<LoaderA::ROW_BYTES>(cur + a_off[i] + ks * 32 * LoaderA::ROW_BYTES);
 #pragma unroll
         for (int i = 0; i < S::MB; ++i)
 #pragma unroll
-          for (int j = 0; j < NB; ++j) mma(a[i], b[j], acc[i][j]);
+          for (int j = 0; j < S::NB; ++j) mma(a[i], b[j], acc[i][j]);
       }
       st = st == NSTAGE - 1 ? 0 : st + 1;
     }

@@ -50,20 +50,33 @@ typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 // v_exp_f32 without the denormal-range fix-up of exp2f(): arguments here are <= 0 up to rounding, results that
 // underflow are exact zeros in the sums they feed.
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-// Combine a value over the four lane groups l/16 (lanes l, l^16, l^32, l^48) without going through the LDS pipe:
-// v_permlane16_swap / v_permlane32_swap of a register with a copy of itself leave "my 16-lane row's partner" and
-// "my half's partner" next to the own value.
-__device__ __forceinline__ float rows_max(float x) {
-  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
-  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+// Four values over the four lane groups l / 16, without the LDS pipe.  v_permlane16_swap / v_permlane32_swap exchange the odd
+// 16-lane rows of one register with the even ones of another (the upper half of one with the lower of the other): combining
+// the two registers then combines neighbouring rows of BOTH values in one instruction, and after two such steps row g holds
+// value g over all rows.
+struct Swapped {
+  float a, b;
+};
+__device__ __forceinline__ Swapped swap16(float x, float y) {      // {x0 y0 x2 y2}, {x1 y1 x3 y3}
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return {__uint_as_float(p[0]), __uint_as_float(p[1])};
 }
-__device__ __forceinline__ float rows_sum(float x) {
-  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+__device__ __forceinline__ Swapped swap32(float x, float y) {      // {x0 x1 y0 y1}, {x2 x3 y2 y3}
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return {__uint_as_float(p[0]), __uint_as_float(p[1])};
+}
+template <typename F>
+__device__ __forceinline__ float rows_combine(const float (&v)[4], F f) {
+  const Swapped p = swap16(v[0], v[1]), q = swap16(v[2], v[3]);
+  const Swapped r = swap32(f(p.a, p.b), f(q.a, q.b));
+  return f(r.a, r.b);
+}
+__device__ __forceinline__ void rows_spread(float x, float (&v)[4]) {      // v[g] = row g of x, in every row
+  const Swapped p = swap16(x, x), q = swap32(p.a, p.a), r = swap32(p.b, p.b);
+  v[0] = q.a;
+  v[1] = r.a;
+  v[2] = q.b;
+  v[3] = r.b;
 }
 
 // second launch bound: wavefronts per SIMD that the register allocation has to leave room for
@@ -76,41 +89,69 @@ struct FwdArgs {
   const int32_t* targets;
   int64_t N, d, V;        // V: rows of W as passed (the whole vocabulary, or a shard's slice of it)
   int64_t v_off;          // vocabulary index of row 0 of W (0 unless W is a slice): targets are global indices
-  int tiles_v, tiles_t;   // tiles over the vocabulary (MFMA rows) and over the tokens (MFMA columns)
+  int tiles_v;            // tiles over the vocabulary (MFMA rows)
   int64_t n_pad;          // row stride of the partial arrays
   float* part_m;          // [tiles_v][n_pad] max of the tile's logits of a token
   float* part_s;          // [tiles_v][n_pad] sum of exp(logit - max)
   float* zt;              // [n_pad] target logit, written by the one tile that holds vocab row y_t
   const int32_t* rows;    // [n_act] active token rows, ascending: position p of the compacted list is token rows[p]
-  const int32_t* row_targets;  // [n_act] their targets
+  int64_t list_stride;    // rows + list_stride: their targets
   const int32_t* n_act;   // device scalar
 };  // partials and zt are indexed by compacted position, not by token
 
 typedef TileGemm<BF16, 11, 2, true> Logits256;      // counted: the two stores of a token's partials
-// One tile's main loop; a wavefront with no part in the tile only takes part in its loads (256 x 256 loops).  counted:
-// the loop's COUNTED_STORES were issued since the tile was fetched (TileGemm::run).
-template <typename G>
-__device__ __forceinline__ void run_or_idle(G& g, char* smem, f32x4_t (&acc)[G::Shape::MB][NB], bool idle,
-                                            bool counted = false) {
+// zeros from an opaque register: as constants the compiler sets them ahead of the branch, for every tile
+template <int M, int N>
+__device__ __forceinline__ void clear(f32x4_t (&acc)[M][N]) {
+  float z = 0.f;
+  asm volatile("" : "+v"(z));
+#pragma unroll
+  for (int i = 0; i < M; ++i)
+#pragma unroll
+    for (int j = 0; j < N; ++j) acc[i][j] = f32x4_t{z, z, z, z};
+}
+// One tile's main loop; a wavefront with no part in the tile only takes part in its loads (256-row loops).  nb: its column
+// blocks; counted: the loop's COUNTED_STORES were issued since the tile was fetched (TileGemm::run).
+template <typename G, int nb>
+__device__ __forceinline__ void run_tile(G& g, char* smem, f32x4_t (&acc)[G::Shape::MB][nb > 0 ? nb : 1], bool idle,
+                                         bool counted = false) {
   if constexpr (G::HAS_IDLE) {
-    if (idle) {                                      // wave-uniform
-#pragma unroll
-      for (int i = 0; i < G::Shape::MB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-      g.run_idle(smem);
+    if (nb == 0 || idle) {                           // wave-uniform
+      clear(acc);
+      if constexpr (G::HALVES && !G::KMAJOR) g.template run_idle<nb>(smem);
+      else g.run_idle(smem);
       return;
     }
   }
-  if constexpr (std::is_same<G, Logits256>::value) g.run(smem, acc, counted);
+  if constexpr (nb == 0) {
+  } else if constexpr (std::is_same<G, Logits256>::value) g.run(smem, acc, counted);
+  else if constexpr (G::HALVES && !G::KMAJOR) g.template run<nb>(smem, acc, counted);
+  else if constexpr (G::HALVES) g.template run<nb>(smem, acc);
   else g.run(smem, acc);
 }
+// column blocks of this wavefront
+template <typename G>
+__device__ __forceinline__ int column_blocks(const G& g) {
+  if constexpr (G::HALVES) return G::Shape::wave_col(wave_id()) == 0 ? G::Shape::NB : g.nb1;
+  else return G::Shape::NB;
+}
+template <typename G>
+__device__ __forceinline__ int last_blocks(const G& g) {      // ... of the tile's last column of wavefronts
+  if constexpr (G::HALVES) return g.nb1;
+  else return G::Shape::NB;
+}
 
-// A tile of the logits kernels: rows [256 tv, ..) of W (256: the tile's edge), list positions [256 tt, ..).
+template <typename G, int nb>
+__device__ __forceinline__ void issue_first(const G& g, char* smem, int part) {
+  if constexpr (G::HALVES) g.template issue_first<nb>(smem, part);
+  else g.issue_first(smem, part);
+}
+
+// A tile of the logits kernels: rows [BM tv, ..) of W, list positions [width tt, ..).
 struct LogitsTile {
   int tv, tt;
-  __device__ __forceinline__ void take(TileSchedule& sch) {
-    sch.coords(sch.take(), tv, tt);
+  __device__ __forceinline__ void take(TileSchedule<PATCH_ROWS_LOGITS>& sch) {
+    sch.take(tv, tt);
     asm volatile("" : "+s"(tv), "+s"(tt));           // divided out here, under an epilogue, not where they are used
   }
 };
@@ -124,23 +165,19 @@ struct LogitsTile {
 template <typename S, int LISTS>
 struct TokenWords {
   static constexpr int PIECES = S::BN / 64, BYTES = LISTS * S::BN * 4;     // a wavefront fetches 64 words at a time
-  __device__ __forceinline__ static void fetch(const void* const (&list)[LISTS], const int (&t0)[LISTS], int n_act, char* lds) {
+  // rows: list 0 (the row list), the others `stride` entries after one another; next, cur: first positions of the next
+  // tile, whose rows are fetched, and of this one
+  __device__ __forceinline__ static void fetch(const int32_t* rows, int64_t stride, int next, int cur, int n_act, char* lds) {
     const int wave = wave_id(), lane = threadIdx.x & 63;
 #pragma unroll
     for (int i = 0; i < (LISTS * PIECES + S::WAVES - 1) / S::WAVES; ++i) {
-      const int piece = i * S::WAVES + wave;
+      const int piece = i * S::WAVES + wave, l = piece / PIECES;
       if (LISTS * PIECES % S::WAVES != 0 && piece >= LISTS * PIECES) break;      // wave-uniform
-      uint64_t base = 0;
-      int first = 0;
-#pragma unroll
-      for (int l = 0; l < LISTS; ++l)
-        if (piece / PIECES == l) {
-          base = reinterpret_cast<uint64_t>(list[l]);
-          first = t0[l];
-        }
+      const uint64_t base = reinterpret_cast<uint64_t>(rows + l * stride);
+      const int first = (l == 0 ? next : cur) + piece % PIECES * 64;
       const i32x4_t rs = {__builtin_amdgcn_readfirstlane((int)(uint32_t)base),
                           __builtin_amdgcn_readfirstlane((int)((uint32_t)(base >> 32) & 0xffffu)), n_act * 4, 0x00020000};
-      lds_dma4(lds_address(lds) + (uint32_t)piece * 256u, (uint32_t)min(first + piece % PIECES * 64 + lane, n_act - 1) * 4u, rs);
+      lds_dma4(lds_address(lds) + (uint32_t)piece * 256u, (uint32_t)min(first + lane, n_act - 1) * 4u, rs);
     }
   }
   template <typename V>
@@ -149,67 +186,135 @@ struct TokenWords {
   }
 };
 // The logits kernels gather their column operand (H rows) through the active-row list: the rows a lane fetches.
-template <bool QUAD, typename G>
-__device__ __forceinline__ void gather_rows(const char* words, int (&grow)[decltype(G::lb)::ITERS]) {
+template <bool NEAR, typename G>
+__device__ __forceinline__ void gather_rows(const G& g, const char* words, int (&grow)[decltype(G::lb)::ITERS]) {
   const int lane = threadIdx.x & 63, wave = wave_id();
 #pragma unroll
   for (int it = 0; it < decltype(G::lb)::ITERS; ++it)
-    grow[it] = *reinterpret_cast<const int*>(words + decltype(G::lb)::template lane_tile_row<QUAD>(it, wave, lane) * 4);
+    grow[it] = *reinterpret_cast<const int*>(
+        words + min(decltype(G::lb)::template lane_tile_row<NEAR>(it, wave, lane, last_blocks(g)), G::Shape::BN - 1) * 4);
 }
-template <bool QUAD, typename G, typename Args>
-__device__ __forceinline__ void gather_rows_of_first(const Args& a, const LogitsTile& t, int n_act,
+template <bool NEAR, typename G, typename Args>
+__device__ __forceinline__ void gather_rows_of_first(const G& g, const Args& a, const LogitsTile& t, int n_act,
                                                      int (&grow)[decltype(G::lb)::ITERS]) {
   const int lane = threadIdx.x & 63, wave = wave_id();
 #pragma unroll
   for (int it = 0; it < decltype(G::lb)::ITERS; ++it)
-    grow[it] = a.rows[min(t.tt * G::Shape::BN + decltype(G::lb)::template lane_tile_row<QUAD>(it, wave, lane), n_act - 1)];
+    grow[it] = a.rows[min(t.tt * g.width() + decltype(G::lb)::template lane_tile_row<NEAR>(it, wave, lane, last_blocks(g)),
+                          n_act - 1)];
 }
 // both operand streams of a tile (rows = W tile, columns = gathered H rows); issue_first() requests the first slabs
-template <bool QUAD, typename G, typename Args>
+template <bool NEAR, typename G, typename Args>
 __device__ __forceinline__ void logits_setup(G& g, const Args& a, const LogitsTile& t, int n_act,
                                              const int (&grow)[decltype(G::lb)::ITERS]) {
   typedef typename G::Type::store_t st;
-  constexpr int BM = G::Shape::BM, BN = G::Shape::BN;
-  g.template setup_gathered<QUAD>((const st*)a.W + (int64_t)t.tv * BM * a.d, a.d,
+  constexpr int BM = G::Shape::BM;
+  const int width = g.width();
+  g.template setup_gathered<NEAR>((const st*)a.W + (int64_t)t.tv * BM * a.d, a.d,
                                      (int)min((int64_t)BM, a.V - (int64_t)t.tv * BM), a.H, a.d,
-                                     (int)min((int64_t)BN, (int64_t)n_act - (int64_t)t.tt * BN), a.d, grow, a.N);
+                                     min(width, n_act - t.tt * width), a.d, grow, a.N);
 }
 
-// + per-token (max, sum) of the wave rows + the next tile's rows and the tile's targets
-template <typename G>
-constexpr int fwd_lds_bytes = G::LDS_BYTES + 2 * G::Shape::WAVES_M * G::Shape::BN * 4 + TokenWords<typename G::Shape, 2>::BYTES;
+// f(std::integral_constant<int, column blocks of this wavefront>()): a kernel's walk over its tiles.  The wavefronts of a
+// workgroup may take different branches; all of them meet the same barriers.
+template <typename G, typename F>
+__device__ __forceinline__ void with_blocks(const G& g, F&& f) {
+  if constexpr (!G::HALVES) {
+    f(std::integral_constant<int, G::Shape::NB>());
+  } else {                                           // wave-uniform
+    const int nb = column_blocks(g);
+    constexpr bool ANY = G::KMAJOR;                  // the narrow loop has right halves of two or no blocks
+    if (nb == 8) f(std::integral_constant<int, 8>());
+    else if (ANY && nb == 6) f(std::integral_constant<int, ANY ? 6 : 0>());
+    else if (ANY && nb == 4) f(std::integral_constant<int, ANY ? 4 : 0>());
+    else if (nb == 2) f(std::integral_constant<int, 2>());
+    else f(std::integral_constant<int, 0>());
+  }
+}
+// Which tiles a logits kernel of 256 vocabulary rows takes: 256 columns wide, or 128 or 160 (TileGemmNarrow), by what the
+// rounds of the grid cost.  Costs in 1/256 of the time of a slab of the 256 x 256 forward (1.4 us), for 128, 160 and 256
+// columns, measured over (6720, 128256, 512 .. 2048):
+//   slab, tile      a slab of d; what a tile costs besides (dz stores its tile, in partial lines where it is narrow)
+//   unaligned       rows of d that are no multiple of 128 bytes: a slab row touches two lines, and the requests bound a slab
+//   stream          W comes from HBM: 1 or 2 columns of narrow tiles, 1 or 2 - 4 of wide ones (two resident slabs)
+// Forward at (N, V, d), 256 / 160 / 128 columns: (300, 128256, 4096) 367 / 295 / 347 us, (225, ..) 264 / 266 / 268,
+// (450, ..) 427 / 415 / 455, (600, ..) 551 / 505 / 573, (360, 114156, 8168) 877 / 918 / 997.
+struct WidthCosts {
+  int slab[3], tile[3];
+};
+constexpr WidthCosts FWD_COSTS = {{167, 184, 256}, {328, 474, 765}};
+constexpr WidthCosts DZ_COSTS = {{177, 201, 261}, {440, 640, 1000}};
+constexpr int UNALIGNED_SLAB[3] = {220, 239, 294}, STREAM_NARROW[2] = {320, 200}, STREAM_WIDE[2] = {350, 300};
+struct LogitsWidth {
+  int half_blocks;        // column blocks of the right half of narrow tiles; 8: 256 columns
+  int64_t cost;
+};
+__host__ __device__ __forceinline__ LogitsWidth logits_width(const WidthCosts& c, int tiles_v, int n_act, int64_t d, int grid) {
+  LogitsWidth best = {8, 0};
+  const int nk = (int)((d + 63) / 64);
+#pragma unroll
+  for (int h = 2; h >= 0; --h) {
+    const int width = h == 2 ? 256 : 128 + 32 * h, cols = (int)((uint32_t)(n_act + width - 1) / (uint32_t)width);
+    const int64_t tiles = (int64_t)tiles_v * cols;
+    int slab = c.slab[h];
+    if (d % 64 != 0 && slab < UNALIGNED_SLAB[h]) slab = UNALIGNED_SLAB[h];
+    const int stream = width <= NARROW_BN ? (cols <= 2 ? STREAM_NARROW[cols == 2] : 0) : cols <= 4 ? STREAM_WIDE[cols >= 2] : 0;
+    if (slab < stream) slab = stream;
+    if (tiles + grid >= (1ll << 31)) continue;               // 32-bit division; so many rounds are 256 wide
+    const int64_t cost = (int64_t)((uint32_t)(tiles + grid - 1) / (uint32_t)grid) * (nk * slab + c.tile[h]);
+    if (h == 2 || (best.cost != 0 && cost < best.cost)) best = {h == 2 ? 8 : 2 * h, cost};
+  }
+  return best;
+}
 
+// LDS of the logits kernels: slabs, the token words and, in the forward, per-token (max, sum) of the wave rows.  Narrow
+// tiles have those inside their third slab, which is empty during an epilogue.
 template <typename G>
-__global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partials(FwdArgs a) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
+constexpr int FWD_SUMS_BYTES = 2 * G::Shape::WAVES_M * G::Shape::BN * 4;
+template <typename G>
+constexpr int fwd_sums_at = G::HALVES ? 2 * NARROW_STAGE_BYTES : G::LDS_BYTES;
+static_assert(FWD_SUMS_BYTES<TileGemmNarrow<BF16>> <= NARROW_STAGE_BYTES, "");
+template <typename G>
+constexpr int fwd_words_at = G::LDS_BYTES + (G::HALVES ? 0 : FWD_SUMS_BYTES<G>);
+template <typename G>
+constexpr int fwd_bytes_of = fwd_words_at<G> + TokenWords<typename G::Shape, 2>::BYTES;
+template <typename G>
+constexpr int dz_bytes_of = G::LDS_BYTES + TokenWords<typename G::Shape, 4>::BYTES;
+// a kernel of 256-row tiles holds both loops
+typedef TileGemmNarrow<BF16> LogitsNarrow;
+template <typename G>
+constexpr bool HAS_NARROW = std::is_same<G, Logits256>::value;
+template <typename G>
+constexpr int fwd_lds_bytes = HAS_NARROW<G> ? (fwd_bytes_of<LogitsNarrow> > fwd_bytes_of<G> ? fwd_bytes_of<LogitsNarrow> : fwd_bytes_of<G>) : fwd_bytes_of<G>;
+template <typename G>
+constexpr int dz_lds_bytes = HAS_NARROW<G> ? (dz_bytes_of<LogitsNarrow> > dz_bytes_of<G> ? dz_bytes_of<LogitsNarrow> : dz_bytes_of<G>) : dz_bytes_of<G>;
+
+template <typename G, int nb>
+__device__ __forceinline__ void fwd_tiles(const FwdArgs& a, G& g, TileSchedule<PATCH_ROWS_LOGITS>& sch, int n_act, char* smem) {
   typedef typename G::Shape S;
   constexpr int BM = S::BM, BN = S::BN, MB = S::MB;
-  const int n_act = *a.n_act;
-  TileSchedule sch;
-  sch.init(a.tiles_v, (n_act + BN - 1) / BN, PATCH_ROWS_LOGITS);        // token tiles that hold active rows only
-  if (!sch.has_tile()) return;                       // block-uniform
-  float* s_m = reinterpret_cast<float*>(smem + G::LDS_BYTES);   // [waves along the vocabulary][tokens of the tile]
+  const int width = g.width();
+  float* s_m = reinterpret_cast<float*>(smem + fwd_sums_at<G>);   // [waves along the vocabulary][tokens of the tile]
   float* s_s = s_m + S::WAVES_M * BN;                           // outside the slab buffers: see prefetch below
 
   typedef TokenWords<S, 2> Words;
-  char* words = reinterpret_cast<char*>(s_s + S::WAVES_M * BN);
+  char* words = smem + fwd_words_at<G>;
 
-  G g;
   LogitsTile cur, next;
   cur.take(sch);
   int grow[decltype(g.lb)::ITERS];
-  gather_rows_of_first<false, G>(a, cur, n_act, grow);
+  gather_rows_of_first<false>(g, a, cur, n_act, grow);
   logits_setup<false>(g, a, cur, n_act, grow);
 #pragma unroll
-  for (int q = 0; q < G::FIRST_PARTS; ++q) g.issue_first(smem, q);
+  for (int q = 0; q < G::FIRST_PARTS; ++q) issue_first<G, nb>(g, smem, q);
   bool more = sch.has_tile();
   next = cur;
   if (more) next.take(sch);
-  Words::fetch({a.rows, a.row_targets}, {next.tt * BN, cur.tt * BN}, n_act, words);
+  Words::fetch(a.rows, a.list_stride, next.tt * width, cur.tt * width, n_act, words);
   bool counted = false;
   while (true) {
-    f32x4_t acc[MB][NB];
-    run_or_idle(g, smem, acc, S::wave_col(wave_id()) * WAVE_N >= n_act - cur.tt * BN, counted);
+    f32x4_t acc[MB][nb > 0 ? nb : 1];
+    run_tile<G, nb>(g, smem, acc, S::wave_col(wave_id()) * S::WAVE_N >= n_act - cur.tt * width, counted);
     // The lane's position is rebuilt from an opaque copy of the thread id after every main loop: otherwise all the
     // per-lane constants of the epilogue stay live through the loop, are spilled, and every reload waits (vmcnt) for
     // the slab requests of the next tile as well.
@@ -217,23 +322,24 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
     asm volatile("" : "+v"(tid));
     const LanePos<S> lp(tid);
     const int tv = cur.tv, tt = cur.tt;
-    const int64_t v0 = (int64_t)tv * BM, t0 = (int64_t)tt * BN;
+    const int64_t v0 = (int64_t)tv * BM, t0 = (int64_t)tt * width;
     const int rowsV = (int)min((int64_t)BM, a.V - v0);
-    const int rowsT = (int)min((int64_t)BN, (int64_t)n_act - t0);
+    const int rowsT = min(width, n_act - tt * width);
     const bool last = !more;
-    gather_rows<false, G>(words, grow);
-    int ytok[NB];
+    gather_rows<false>(g, words, grow);
+    int ytok[nb > 0 ? nb : 1];
 #pragma unroll
-    for (int j = 0; j < NB; ++j) ytok[j] = Words::template word<int>(words, 1, lp.col(j));
+    for (int j = 0; j < nb; ++j) ytok[j] = Words::template word<int>(words, 1, lp.col(j));
+    if constexpr (G::HALVES) wait_vmcnt0();             // slabs past K must not land in what is written next
     __syncthreads();                                 // every wave is done reading the slab buffers and the token words
     LLAMARL_FENCE();
     if (!last) {                                     // start the next tile's first slabs; the epilogue hides them
       cur = next;
       logits_setup<false>(g, a, cur, n_act, grow);
-      g.issue_first(smem, 0);
+      issue_first<G, nb>(g, smem, 0);
       more = sch.has_tile();
       if (more) next.take(sch);
-      Words::fetch({a.rows, a.row_targets}, {next.tt * BN, cur.tt * BN}, n_act, words);
+      Words::fetch(a.rows, a.list_stride, next.tt * width, cur.tt * width, n_act, words);
     }
     // From here to the next main loop nothing may wait on vmcnt: the counter is in order, so a wait for any load
     // (or spill reload) issued before the slab requests turns into a wait for the requests themselves, and the
@@ -244,45 +350,75 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
 #pragma unroll
       for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
+        for (int r = 0; r < 4; ++r)
+          if (lp.row(i, r) >= rowsV) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (lp.row(i, r) >= rowsV) acc[i][j][r] = -INFINITY;
+            for (int j = 0; j < nb; ++j) acc[i][j][r] = -INFINITY;
+          }
     }
-    const int lane_row0 = lp.row(0, 0);              // rows of this lane: lane_row0 + 16 ib + r
+    auto issue_part = [&](int part) {
+      if (part > 0 && part < G::FIRST_PARTS && !last) issue_first<G, nb>(g, smem, part);
+    };
+    // Four tokens at a time.  VALU-bound: per logit half a max, an fma, an exponential (two issue cycles) and an add; what a
+    // token costs beyond its logits is shared by the four.
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      if (j > 0 && j < G::FIRST_PARTS && !last) g.issue_first(smem, j);
-      const int tok = lp.col(j);
-      const int y = (tok < rowsT) ? ytok[j] - (int)a.v_off : -1;   // row of W that is the target (negative: none)
-      const int yrow = y - (int)v0;                  // vocab row of the target inside this tile (if 0 <= . < rowsV)
-      const int yrel = yrow - lane_row0;             // ... relative to this lane's first row
-      float m = -INFINITY;
+    for (int j0 = 0; j0 < nb; j0 += 4) {
+      float m[4], s[4];
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
+      for (int q = 0; q < 4; ++q) {
+        m[q] = -INFINITY;
+        if (j0 + q < nb) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) m = fmaxf(m, acc[i][j][r]);
-      m = rows_max(m);                               // the four lane groups hold different rows of the same token
-      const float mb = (m == -INFINITY) ? 0.f : m * LOG2E;
-      float s = 0.f;
+          for (int i = 0; i < MB; ++i)
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) s += fast_exp2(fmaf(acc[i][j][r], LOG2E, -mb));   // exp2(-inf) = 0
-      s = rows_sum(s);
-      // target logit: one lane of one wave of one vocab tile owns row y_t of a token; most waves own none
-      const bool mine = y >= 0 && yrow < rowsV && tok < rowsT && yrel >= 0 && yrel < S::WAVE_M && (yrel & 12) == 0;
-      if (__any(mine)) {                             // wave-uniform
-        float zy = 0.f;
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) zy = (yrel == i * 16 + r) ? acc[i][j][r] : zy;
-        if (mine) a.zt[t0 + tok] = zy;
+            for (int r = 0; r < 4; ++r) m[q] = fmaxf(m[q], acc[i][j0 + q][r]);
+        }
       }
-      if ((lp.lane >> 4) == 0) {
-        s_m[lp.wm * BN + tok] = m;
-        s_s[lp.wm * BN + tok] = s;
+      const float top = rows_combine(m, [](float x, float y) { return fmaxf(x, y); });    // row g: token j0 + g
+      rows_spread(top, m);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        issue_part(j0 + q);
+        s[q] = 0.f;
+        if (j0 + q < nb) {
+          const float mb = (m[q] == -INFINITY) ? 0.f : m[q] * LOG2E;
+#pragma unroll
+          for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s[q] += fast_exp2(fmaf(acc[i][j0 + q][r], LOG2E, -mb));   // exp2(-inf) = 0
+          asm volatile("" : "+v"(s[q]));             // here, between the requests: the compiler sinks it past them all
+        }
+      }
+      const float sum = rows_combine(s, [](float x, float y) { return x + y; });
+      // row g of the wavefront holds token j0 + g: position 16 (j0 + g) + l % 16 = 16 j0 + l of its columns
+      if (nb - j0 >= 4 || lp.lane < 16 * (nb - j0)) {
+        const int at = lp.wm * BN + lp.wn * S::WAVE_N + 16 * j0 + lp.lane;
+        s_m[at] = top;
+        s_s[at] = sum;
+      }
+    }
+#pragma unroll
+    for (int part = (nb + 3) / 4 * 4; part < G::FIRST_PARTS; ++part) issue_part(part);
+    // target logits: a token's is held by one lane of one wavefront of one vocab tile; most wavefronts hold none
+    {
+      const int first = (int)a.v_off + (int)v0 + lp.wm * S::WAVE_M;     // the wavefront's first row (a global index)
+      bool any = false;
+#pragma unroll
+      for (int j = 0; j < nb; ++j) any |= (uint32_t)(ytok[j] - first) < (uint32_t)S::WAVE_M;
+      if (__any(any)) {                              // wave-uniform
+        const int lane_row0 = lp.row(0, 0);          // rows of this lane: lane_row0 + 16 ib + r
+#pragma unroll
+        for (int j = 0; j < nb; ++j) {
+          const int tok = lp.col(j);
+          const int yrow = ytok[j] - (int)a.v_off - (int)v0;      // vocab row of the target inside this tile
+          const int yrel = yrow - lane_row0;                      // ... relative to this lane's first row
+          float zy = 0.f;
+#pragma unroll
+          for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) zy = (yrel == i * 16 + r) ? acc[i][j][r] : zy;
+          if (tok < rowsT && yrow < rowsV && yrel >= 0 && yrel < S::WAVE_M && (yrel & 12) == 0) a.zt[t0 + tok] = zy;
+        }
       }
     }
     __syncthreads();
@@ -300,6 +436,28 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
     if (last) break;
     counted = (wave_id() * 64) < rowsT;              // this wavefront has just issued its two stores
   }
+}
+
+template <typename G>
+__global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partials(FwdArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int n_act = *a.n_act;
+  TileSchedule<PATCH_ROWS_LOGITS> sch;
+  if constexpr (HAS_NARROW<G>) {
+    const int half = logits_width(FWD_COSTS, a.tiles_v, n_act, a.d, gridDim.x).half_blocks;
+    if (half < 8) {
+      LogitsNarrow g;
+      g.nb1 = half;
+      sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width());
+      if (!sch.has_tile()) return;
+      with_blocks(g, [&](auto blocks) { fwd_tiles<LogitsNarrow, decltype(blocks)::value>(a, g, sch, n_act, smem); });
+      return;
+    }
+  }
+  G g;
+  sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width());             // token tiles that hold active rows only
+  if (!sch.has_tile()) return;                       // block-uniform
+  fwd_tiles<G, G::Shape::NB>(a, g, sch, n_act, smem);
 }
 
 // lse[t] = log sum over vocab tiles; logp[t] = z[t,y_t] - lse[t], for the active tokens (the compaction pass
@@ -593,130 +751,161 @@ struct DzArgs {
   const float* dz_scale;  // fp32: dz is stored times this (dz_scale_for)
   int64_t N, d, V;
   int64_t v_off;          // vocabulary index of row 0 of W (0 unless W is a shard's slice); lse is always global
-  int tiles_v, tiles_t;
+  int tiles_v;
   void* dz;     // [N][ldz]  token-major (type of H/W); columns V..ldz-1 written as zero
   int64_t ldz;
   void* dzt;    // [V][packed_pitch(n_act)] vocab-major; columns past the active rows written as zero
   const int32_t* rows;    // active token rows (coef != 0), ascending; dz / dzt are indexed by list position
-  const float* row_coef;  // their coef, lse and targets
-  const float* row_lse;
-  const int32_t* row_targets;
+  int64_t list_stride;    // rows + 1, 2, 3 list_stride: their targets, lse and coef
   const int32_t* n_act;
 };
-// + the next tile's rows, the tile's coef, lse and targets
-template <typename G>
-constexpr int dz_lds_bytes = G::LDS_BYTES + TokenWords<typename G::Shape, 4>::BYTES;
-
-template <typename G>
-__global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzArgs a) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
+template <typename G, int nb>
+__device__ __forceinline__ void dz_tiles(const DzArgs& a, G& g, TileSchedule<PATCH_ROWS_LOGITS>& sch, int n_act, char* smem) {
   typedef typename G::Shape S;
-  constexpr int BM = S::BM, BN = S::BN, MB = S::MB;
-  const int n_act = *a.n_act;
+  constexpr int BM = S::BM, MB = S::MB;
+  const int width = g.width();
   const int64_t ldzt = packed_pitch(n_act);
-  TileSchedule sch;
-  sch.init(a.tiles_v, (n_act + BN - 1) / BN, PATCH_ROWS_LOGITS);
-  if (!sch.has_tile()) return;                       // block-uniform: no active token at all
   const float upstream = a.g_device != nullptr ? *a.g_device : a.g;
   float scale = 1.f;
   if constexpr (sizeof(typename G::Type::store_t) == 4) scale = *a.dz_scale;
-  // token columns are fetched quad-interleaved (a lane's four column blocks are neighbouring tokens), so the
-  // vocab-major dz^T leaves straight from registers, 8 (bf16) or 16 bytes per lane and whole lines per 16 lanes.
+  // a lane's column blocks are neighbouring tokens, so the vocab-major dz^T leaves straight from registers, 16 bytes per
+  // lane and whole lines per 16 lanes
   typedef TokenWords<S, 4> Words;
   char* words = smem + G::LDS_BYTES;
-  G g;
   LogitsTile cur, next;
   cur.take(sch);
   int grow[decltype(g.lb)::ITERS];
-  gather_rows_of_first<true, G>(a, cur, n_act, grow);
+  gather_rows_of_first<true>(g, a, cur, n_act, grow);
   logits_setup<true>(g, a, cur, n_act, grow);
 #pragma unroll
-  for (int q = 0; q < G::FIRST_PARTS; ++q) g.issue_first(smem, q);
+  for (int q = 0; q < G::FIRST_PARTS; ++q) issue_first<G, nb>(g, smem, q);
   bool more = sch.has_tile();
   next = cur;
   if (more) next.take(sch);
-  Words::fetch({a.rows, a.row_coef, a.row_lse, a.row_targets}, {next.tt * BN, cur.tt * BN, cur.tt * BN, cur.tt * BN}, n_act, words);
+  Words::fetch(a.rows, a.list_stride, next.tt * width, cur.tt * width, n_act, words);
   while (true) {
-    f32x4_t acc[MB][NB];
-    g.run(smem, acc);
+    f32x4_t acc[MB][nb > 0 ? nb : 1];
+    run_tile<G, nb>(g, smem, acc, S::wave_col(wave_id()) * S::WAVE_N >= n_act - cur.tt * width);
     int tid = threadIdx.x;                           // opaque per tile: see k_fwd_partials
     asm volatile("" : "+v"(tid));
     const LanePos<S> lp(tid);
     const int tv = cur.tv, tt = cur.tt;
-    const int64_t v0 = (int64_t)tv * BM, t0 = (int64_t)tt * BN;
+    const int64_t v0 = (int64_t)tv * BM, t0 = (int64_t)tt * width;
     const int rowsV = (int)min((int64_t)BM, a.V - v0);
-    const int rowsT = (int)min((int64_t)BN, (int64_t)n_act - t0);
+    const int rowsT = min(width, n_act - tt * width), tok0 = lp.col_near(nb);
     const bool last = !more;
-    gather_rows<true, G>(words, grow);
-    const f32x4_t tcoef = Words::template word<f32x4_t>(words, 1, lp.col_quad());
-    const f32x4_t tlse = Words::template word<f32x4_t>(words, 2, lp.col_quad());
-    const i32x4_t ttgt = Words::template word<i32x4_t>(words, 3, lp.col_quad());
+    gather_rows<true>(g, words, grow);
+    float tcoef[nb > 0 ? nb : 1], tlse[nb > 0 ? nb : 1];
+    int ttgt[nb > 0 ? nb : 1];
+#pragma unroll
+    for (int j = 0; j < nb; ++j) {
+      const int tok = tok0 + j;
+      ttgt[j] = Words::template word<int>(words, 1, tok);
+      tlse[j] = Words::template word<float>(words, 2, tok);
+      tcoef[j] = Words::template word<float>(words, 3, tok);
+    }
+    if constexpr (G::HALVES) wait_vmcnt0();             // slabs past K must not land in what is written next
     __syncthreads();                                 // every wave is done reading the slab buffers and the token words
     LLAMARL_FENCE();
     if (!last) {                                     // the epilogue uses no LDS: fetch the next tile under it
       cur = next;
       logits_setup<true>(g, a, cur, n_act, grow);
-      g.issue_first(smem, 0);
+      issue_first<G, nb>(g, smem, 0);
       more = sch.has_tile();
       if (more) next.take(sch);
-      Words::fetch({a.rows, a.row_coef, a.row_lse, a.row_targets}, {next.tt * BN, cur.tt * BN, cur.tt * BN, cur.tt * BN}, n_act,
-                   words);
+      Words::fetch(a.rows, a.list_stride, next.tt * width, cur.tt * width, n_act, words);
     }
     LLAMARL_FENCE();                                 // nothing may wait on vmcnt from here on: see k_fwd_partials
 
     // dz in place of the logits; per-token scalars live in registers (one token per lane and j)
     const int lane_row0 = lp.row(0, 0);
+    auto issue_part = [&](int part) {
+      if (part > 0 && part < G::FIRST_PARTS && !last) issue_first<G, nb>(g, smem, part);
+    };
+    float nc[nb > 0 ? nb : 1];                               // - upstream * coef; 0 past the active rows, whose logits are 0
+    bool dead = false, any = false;
+    const int first = (int)a.v_off + (int)v0 + lp.wm * S::WAVE_M;       // the wavefront's first row (a global index)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      if (j > 0 && j < G::FIRST_PARTS && !last) g.issue_first(smem, j);
-      const int tok = lp.col_quad() + j;
-      const bool in = tok < rowsT;
+    for (int j = 0; j < nb; ++j) {
+      const bool in = tok0 + j < rowsT;
       float c = in ? upstream * tcoef[j] : 0.f;
       if constexpr (sizeof(typename G::Type::store_t) == 4) c *= scale;
-      const float lb = (c != 0.f) ? tlse[j] * LOG2E : 0.f;
-      const int yrel = (in ? ttgt[j] - (int)a.v_off : -1) - (int)v0 - lane_row0;   // far out of range: another shard's
-      const bool live = c != 0.f;                            // select: a masked token's row is exactly 0
+      nc[j] = -c;
+      dead |= in && c == 0.f;
+      any |= (uint32_t)(ttgt[j] - first) < (uint32_t)S::WAVE_M;
+    }
+    if (__any(dead)) {                                       // wave-uniform
+      // a row whose upstream * coef is 0 is exactly 0, whatever its logits are (they may be infinite or NaN)
+      asm volatile("");                                      // a branch, not 128 selects of every tile
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float p = fast_exp2(fmaf(acc[i][j][r], LOG2E, -lb));
-          acc[i][j][r] = live ? -c * p : 0.f;
-        }
-      // + coef at the target's own vocab row: one lane of one wave of one vocab tile per token
-      const bool mine = live && yrel >= 0 && yrel < S::WAVE_M && (yrel & 12) == 0;
-      if (__any(mine)) {                                     // wave-uniform
+      for (int j = 0; j < nb; ++j)
 #pragma unroll
         for (int i = 0; i < MB; ++i)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) acc[i][j][r] += (mine && yrel == i * 16 + r) ? c : 0.f;
+          for (int r = 0; r < 4; ++r) acc[i][j][r] = nc[j] != 0.f ? acc[i][j][r] : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < nb; ++j) {
+      issue_part(j);
+      const float lb = (nc[j] != 0.f) ? tlse[j] * LOG2E : 0.f;
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[i][j][r] = nc[j] * fast_exp2(fmaf(acc[i][j][r], LOG2E, -lb));
+    }
+#pragma unroll
+    for (int part = nb; part < G::FIRST_PARTS; ++part) issue_part(part);
+    if (__any(any)) {                                        // wave-uniform; most wavefronts hold no token's target
+#pragma unroll
+      for (int j = 0; j < nb; ++j) {
+        // + coef at the target's own vocab row: one lane of one wave of one vocab tile per token
+        const int yrel = ttgt[j] - (int)a.v_off - (int)v0 - lane_row0;          // far out of range: another shard's
+        const bool mine = nc[j] != 0.f && yrel >= 0 && yrel < S::WAVE_M && (yrel & 12) == 0;
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[i][j][r] += (mine && yrel == i * 16 + r) ? -nc[j] : 0.f;
       }
     }
 
     // how far the zero padding of each orientation reaches inside this tile
-    const int dzt_cols = (int)min((int64_t)BN, ldzt - t0);   // dzt[vocab][token]: vocab < V, token < ldzt
-    if constexpr (sizeof(typename G::Type::store_t) == 2) {
-      // bf16: only the vocab-major orientation exists (both gradient contractions read it).  ldzt is a multiple
-      // of 64, so a token quad is never cut by the padding limit.
-      // Uniform 64-bit tile base + 32-bit lane offset, made opaque once per tile so that the 32 row offsets are
+    const int dzt_cols = (int)min((int64_t)width, ldzt - t0);   // dzt[vocab][token]: vocab < V, token < ldzt
+    if constexpr (nb == 0) {
+    } else if constexpr (sizeof(typename G::Type::store_t) == 2) {
+      // bf16: only the vocab-major orientation exists (both gradient contractions read it).
+      // Uniform 64-bit tile base + 32-bit lane offset, made opaque once per tile so that the row offsets are
       // not hoisted out of the persistent loop into scratch memory (a 256-row panel of dz^T is < 2 GiB).
       char* tile_base = reinterpret_cast<char*>(a.dzt) + (v0 * ldzt + t0) * 2;
       const uint32_t ld_b = (uint32_t)ldzt * 2u;
-      uint32_t lane_off = (uint32_t)lane_row0 * ld_b + (uint32_t)lp.col_quad() * 2u;
+      uint32_t lane_off = (uint32_t)lane_row0 * ld_b + (uint32_t)tok0 * 2u;
       asm volatile("" : "+v"(lane_off));
-      const bool in_cols = lp.col_quad() < dzt_cols;
+      // ldzt is a multiple of 64: it cuts no group of 2, 4 or 8 neighbours, but may cut one of 6, which goes pair by pair
+      const int left = dzt_cols - tok0;
+      typedef uint32_t words_t __attribute__((ext_vector_type(nb / 2), aligned(4)));
 #pragma unroll
       for (int i = 0; i < MB; ++i) {
         LLAMARL_FENCE();
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int rel = i * 16 + r;
-          if (lane_row0 + rel < rowsV && in_cols) {
+          if (lane_row0 + rel < rowsV) {
+            words_t v;
+#pragma unroll
+            for (int j = 0; j < nb / 2; ++j) {
+              if constexpr (nb == 2) v = pack_bf16(acc[i][0][r], acc[i][1][r]);
+              else v[j] = pack_bf16(acc[i][2 * j][r], acc[i][2 * j + 1][r]);
+            }
+            char* q = tile_base + (lane_off + (uint32_t)rel * ld_b);
             // non-temporal: dz^T is gigabytes that the gradient contractions stream later; written normally it
             // pushes the H and W panels this kernel re-reads out of the Infinity Cache (-5 % kernel time at
             // 21 k active rows, where the active H rows alone are 174 MB; neutral at 8.6 k)
-            const u32x2_t v = {pack_bf16(acc[i][0][r], acc[i][1][r]), pack_bf16(acc[i][2][r], acc[i][3][r])};
-            __builtin_nontemporal_store(v, reinterpret_cast<u32x2_t*>(tile_base + (lane_off + (uint32_t)rel * ld_b)));
+            if (left >= nb) {
+              __builtin_nontemporal_store(v, reinterpret_cast<words_t*>(q));
+            } else if constexpr (nb == 6) {
+#pragma unroll
+              for (int j = 0; j < 3; ++j)
+                if (left >= 2 * j + 2) reinterpret_cast<uint32_t*>(q)[j] = v[j];
+            }
           }
         }
       }
@@ -726,7 +915,6 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzAr
       const int dz_cols = (int)min((int64_t)BM, a.ldz - v0);   // dz[token][vocab]:  token < N, vocab < ldz
       float* dz = reinterpret_cast<float*>(a.dz);
       float* dzt = reinterpret_cast<float*>(a.dzt);
-      const int tok0 = lp.col_quad();
 #pragma unroll
       for (int i = 0; i < MB; ++i) {
         LLAMARL_FENCE();
@@ -735,10 +923,10 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzAr
         for (int r = 0; r < 4; ++r)
           if (vr0 + r >= rowsV) {                              // padded vocab rows of the token-major copy are 0
 #pragma unroll
-            for (int j = 0; j < NB; ++j) acc[i][j][r] = 0.f;
+            for (int j = 0; j < nb; ++j) acc[i][j][r] = 0.f;
           }
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
+        for (int j = 0; j < nb; ++j)
           if (tok0 + j < rowsT && vr0 < dz_cols)
             *reinterpret_cast<f32x4_t*>(dz + (t0 + tok0 + j) * a.ldz + v0 + vr0) = acc[i][j];
 #pragma unroll
@@ -750,6 +938,29 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzAr
     }
     if (last) break;
   }
+}
+
+template <typename G>
+__global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int n_act = *a.n_act;
+  TileSchedule<PATCH_ROWS_LOGITS> sch;
+  const int n_read = (n_act + 63) / 64 * 64;         // the contractions over dz^T read its columns that far
+  if constexpr (HAS_NARROW<G>) {
+    const int half = logits_width(DZ_COSTS, a.tiles_v, n_act, a.d, gridDim.x).half_blocks;
+    if (half < 8) {
+      LogitsNarrow g;
+      g.nb1 = half;
+      sch.init(a.tiles_v, (n_read + g.width() - 1) / g.width());
+      if (!sch.has_tile()) return;
+      with_blocks(g, [&](auto blocks) { dz_tiles<LogitsNarrow, decltype(blocks)::value>(a, g, sch, n_act, smem); });
+      return;
+    }
+  }
+  G g;
+  sch.init(a.tiles_v, (n_read + g.width() - 1) / g.width());
+  if (!sch.has_tile()) return;                       // block-uniform: no active token at all
+  dz_tiles<G, G::Shape::NB>(a, g, sch, n_act, smem);
 }
 
 struct StoreArgs {
@@ -770,9 +981,14 @@ struct StoreArgs {
   const int32_t* pitch_count;  // non-null: operands flagged below have the row pitch packed_pitch(*pitch_count)
   int packed_a, packed_b;   // A / B is such a panel (lda / ldb are then ignored)
   int group_m;              // rows of a 32-tile patch (see TileSchedule)
+  int width, nb1;           // columns of a tile; column blocks of its right half (TileGemm)
   int max_splits;           // the tiles of the last, partial round may be split this many ways along K (1: never)
   float* part;              // [splits][tail tiles][tile] fp32 partial products of split tiles
   int32_t* plan_out;        // [4] {whole, rem, splits, tiles_m}: what k_reduce_tail has to finish
+};
+
+struct StoreStrides {       // row strides of A and B
+  int64_t a, b;
 };
 
 // Work list of a store contraction.  T tiles on a persistent grid of G workgroups: the first floor(T / G) * G tiles
@@ -866,12 +1082,17 @@ struct StoreTile {     // what one work item of k_gemm_store contracts and where
     plan.coords(tile, tm, tn);
     tail_index = tile - plan.whole;
     row0 = (int64_t)tm * BM;
-    col0 = (int64_t)tn * BN;
+    const int width = G::HALVES ? a.width : BN;
+    col0 = (int64_t)tn * width;
     rowsA = (int)min((int64_t)BM, M - row0);
-    rowsB = (int)min((int64_t)BN, a.Nn - col0);
-    const int nk = (int)((K + BK - 1) / BK);         // 32-bit: slabs per contraction fit an int by far
-    k_lo = (int64_t)(nk * split / nsplit) * BK;
-    k_len = min(K, (int64_t)(nk * (split + 1) / nsplit) * BK) - k_lo;
+    rowsB = (int)min((int64_t)width, a.Nn - col0);
+    k_lo = 0;
+    k_len = K;
+    if (nsplit > 1) {
+      const int nk = (int)((K + BK - 1) / BK);       // 32-bit: slabs per contraction fit an int by far
+      k_lo = (int64_t)(nk * split / nsplit) * BK;
+      k_len = min(K, (int64_t)(nk * (split + 1) / nsplit) * BK) - k_lo;
+    }
   }
 };
 
@@ -882,43 +1103,60 @@ __device__ __forceinline__ StoreTile<G> store_tile_of(const StorePlan& plan, con
   t.set(a, plan, M, K, item);
   return t;
 }
+// (nothing to contract, k_len = 0: every request lies past K)
 template <typename G>
-__device__ __forceinline__ void store_fetch(G& g, const StorePlan& plan, const StoreArgs& a, int item, int64_t M,
-                                            int64_t K, char* smem) {
+__device__ __forceinline__ void store_fetch(G& g, const StorePlan& plan, const StoreArgs& a, const StoreStrides& ld, int item,
+                                            int64_t M, int64_t K, char* smem) {
   typedef typename G::Type::store_t st;
   const StoreTile<G> t = store_tile_of<G>(plan, a, item, M, K);
-  if (t.k_len <= 0) return;
   if constexpr (G::KMAJOR)   // A is At [K][lda] (output rows are its columns), B is Bt [K][ldb]
-    g.prefetch((const uint16_t*)a.A + t.k_lo * a.lda + t.row0, a.lda, t.row0,
-               (const uint16_t*)a.B + t.k_lo * a.ldb + t.col0, a.ldb, t.col0, (int)t.k_len, smem);
+    g.prefetch((const uint16_t*)a.A + t.k_lo * ld.a + t.row0, ld.a, t.row0,
+               (const uint16_t*)a.B + t.k_lo * ld.b + t.col0, ld.b, t.col0, (int)t.k_len, smem);
   else
-    g.template prefetch<true>((const st*)a.A + t.row0 * a.lda + t.k_lo, a.lda, t.rowsA,
-                              (const st*)a.B + t.col0 * a.ldb + t.k_lo, a.ldb, t.rowsB, t.k_len, smem);
+    g.template prefetch<true>((const st*)a.A + t.row0 * ld.a + t.k_lo, ld.a, t.rowsA,
+                              (const st*)a.B + t.col0 * ld.b + t.k_lo, ld.b, t.rowsB, t.k_len, smem);
 }
 
-// One output element group in its final form.  MODE: 1 fp32, 2 fp32 accumulate, 3 bf16, 4 bf16 accumulate.
-template <int MODE>
-__device__ __forceinline__ void store_final4(char* q, float v0, float v1, float v2, float v3) {
-  if (MODE <= 2) {
-    float4* f = reinterpret_cast<float4*>(q);
-    if (MODE == 2) {
-      const float4 old = *f;
-      v0 += old.x; v1 += old.y; v2 += old.z; v3 += old.w;
+// C neighbouring output elements (C even) in their final form.  MODE: 1 fp32, 2 fp32 accumulate, 3 bf16, 4 bf16 accumulate.
+template <int MODE, int C>
+__device__ __forceinline__ void store_final(char* q, const float (&x)[C]) {
+  if constexpr (MODE <= 2) {
+    if constexpr (C > 4) {
+      const float lo[4] = {x[0], x[1], x[2], x[3]};
+      float hi[C - 4];
+#pragma unroll
+      for (int j = 0; j < C - 4; ++j) hi[j] = x[4 + j];
+      store_final<MODE, 4>(q, lo);
+      store_final<MODE, C - 4>(q + 16, hi);
+    } else {
+      typedef float floats_t __attribute__((ext_vector_type(C), aligned(8)));
+      floats_t v;
+#pragma unroll
+      for (int j = 0; j < C; ++j) v[j] = x[j];
+      if (MODE == 2) v += *reinterpret_cast<const floats_t*>(q);
+      *reinterpret_cast<floats_t*>(q) = v;
     }
-    *f = make_float4(v0, v1, v2, v3);
   } else {
-    uint2* h = reinterpret_cast<uint2*>(q);
-    if (MODE == 4) {
-      const uint2 old = *h;
-      v0 += bf16_bits_to_float((uint16_t)(old.x & 0xffffu));
-      v1 += bf16_bits_to_float((uint16_t)(old.x >> 16));
-      v2 += bf16_bits_to_float((uint16_t)(old.y & 0xffffu));
-      v3 += bf16_bits_to_float((uint16_t)(old.y >> 16));
+    uint32_t w[C / 2];
+    if constexpr (MODE == 4) __builtin_memcpy(w, __builtin_assume_aligned(q, 4), C * 2);
+#pragma unroll
+    for (int j = 0; j < C / 2; ++j) {
+      float lo = x[2 * j], hi = x[2 * j + 1];
+      if constexpr (MODE == 4) {
+        lo += bf16_bits_to_float((uint16_t)(w[j] & 0xffffu));
+        hi += bf16_bits_to_float((uint16_t)(w[j] >> 16));
+      }
+      w[j] = pack_bf16(lo, hi);
     }
-    uint2 o;
-    o.x = pack_bf16(v0, v1);
-    o.y = pack_bf16(v2, v3);
-    *h = o;
+    if constexpr (C == 2) {
+      *reinterpret_cast<uint32_t*>(q) = w[0];
+    } else {
+      typedef uint32_t words_t __attribute__((ext_vector_type(C / 2), aligned(4)));
+      words_t v;
+#pragma unroll
+      for (int j = 0; j < C / 2; ++j) v[j] = w[j];
+      *reinterpret_cast<words_t*>(q) = v;
+    }
   }
 }
 template <int MODE>
@@ -934,15 +1172,148 @@ __device__ __forceinline__ void store_final1(char* q, float v) {
   }
 }
 
-// MODE (compile time): the final form of the output, see store_final4.  Split tiles of the last round leave fp32
+// MODE (compile time): the final form of the output, see store_final.  Split tiles of the last round leave fp32
 // partial products instead (k_reduce_tail finishes them in the same MODE).
-typedef TileGemm<BF16, STORE_LOAD_SLOT, 32, false> Store256;      // its epilogue's stores: one unit per row of a lane
-template <typename G, int MODE>
-__global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(StoreArgs a) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
+typedef TileGemm<BF16, STORE_LOAD_SLOT, 32, false> Store256;      // counted: its epilogue's stores, one unit per row of a lane
+template <typename G, int MODE, int nb>
+__device__ __forceinline__ void store_tiles(const StoreArgs a, const StoreStrides ld, G g, StorePlan plan, int64_t M, int64_t K, char* smem) {
   typedef typename G::Shape S;
   constexpr bool KMAJOR = G::KMAJOR;
-  constexpr int BK = 8 * G::Type::EPC, BM = S::BM, BN = S::BN, MB = S::MB;
+  constexpr int BM = S::BM, BN = S::BN, MB = S::MB;
+  int id = plan.take();
+  store_fetch(g, plan, a, ld, id, M, K, smem);
+  bool counted = false;
+  while (true) {
+    f32x4_t acc[MB][nb > 0 ? nb : 1];
+    const int cur_id = id;
+    if (store_tile_of<G>(plan, a, cur_id, M, K).k_len > 0) {
+      const StoreTile<G> t = store_tile_of<G>(plan, a, cur_id, M, K);
+      if constexpr (G::HALVES)
+        run_tile<G, nb>(g, smem, acc,
+                        S::wave_row(wave_id()) * S::WAVE_M >= t.rowsA || S::wave_col(wave_id()) * S::WAVE_N >= t.rowsB, counted);
+      else if constexpr (std::is_same<G, Store256>::value)
+        g.run(smem, acc, counted);
+      else if constexpr (sizeof(typename G::Type::store_t) == 4)
+        g.template run<true>(smem, acc);
+      else
+        g.run(smem, acc);
+    } else {
+      clear(acc);                                    // nothing to contract: the product is zero
+    }
+    const bool more = plan.has_item();
+    wait_vmcnt0();                                   // nothing may wait on vmcnt after the slab requests: see k_fwd_partials
+    __syncthreads();                                 // every wave is done reading the slab buffers
+    if (more) {                                      // the store epilogue uses no LDS: fetch the next tile under it
+      id = plan.take();
+      store_fetch(g, plan, a, ld, id, M, K, smem);
+    }
+    LLAMARL_FENCE();
+
+    const StoreTile<G> t = store_tile_of<G>(plan, a, cur_id, M, K);
+    // no store of a lane is left out (a wavefront without columns has none)
+    counted = nb > 0 && (t.nsplit > 1 || (t.rowsA == BM && t.rowsB == g.width()));
+    if constexpr (nb > 0) {
+      int tid = threadIdx.x;                           // opaque per tile: see k_fwd_partials (a spilled per-lane constant
+      asm volatile("" : "+v"(tid));                    // reloaded here would wait for the slab requests above)
+      const LanePos<S> lp(tid);
+      // Store epilogue, one 16-row block at a time (fences keep the unrolled blocks from piling up address registers).
+      // Addresses are a uniform 64-bit tile base plus a 32-bit per-lane byte offset (a 256-row panel is < 2 GiB).
+      // The offset passes through an empty asm once per tile: otherwise the 32 row offsets of a lane, which do not
+      // depend on the tile, are hoisted out of the persistent loop and live in scratch memory.
+      const int row_l = lp.row(0, 0);                                // lane's first row; (ib, r) adds 16 ib + r
+      if (t.nsplit > 1) {
+        // a split tile of the last round (block-uniform): the whole BM x BN fp32 block goes to the workspace,
+        // rows and columns past the matrix edge included (they hold zeros or values nobody reads)
+        char* blk = reinterpret_cast<char*>(a.part + ((int64_t)t.split * plan.rem + t.tail_index) * (BM * BN));
+        uint32_t lane_off = (uint32_t)row_l * (BN * 4) + (uint32_t)(KMAJOR ? lp.col(0) : lp.col_near(nb)) * 4u;
+        asm volatile("" : "+v"(lane_off));
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+          LLAMARL_FENCE();
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            char* q = blk + (lane_off + (uint32_t)(i * 16 + r) * (BN * 4));
+            float x[nb];
+#pragma unroll
+            for (int j = 0; j < nb; ++j) x[j] = acc[i][j][r];
+            if constexpr (!KMAJOR) {
+              store_final<1>(q, x);
+            } else {
+#pragma unroll
+              for (int j = 0; j < nb; ++j) reinterpret_cast<float*>(q)[j * 16] = x[j];
+            }
+          }
+        }
+      } else {
+        constexpr int esz = (MODE >= 3) ? 2 : 4;
+        char* Cb = reinterpret_cast<char*>(a.C);
+        const bool scatter = a.c_rows != nullptr;
+        const uint32_t ldc_b = (uint32_t)a.ldc * esz;
+        char* tile_base = Cb + (t.row0 * a.ldc + t.col0) * esz;
+        if constexpr (!KMAJOR) {
+          // A lane's column blocks are neighbouring columns c, c + 1, .., stored as one unit: 16 bytes of bf16 from eight
+          // blocks; 16 lanes cover 256 consecutive bytes of a row -- whole 128-byte lines with no cross-lane traffic (stores
+          // that split a line over lanes of different rows measured ~0.5 ms per GB slower).  The number of columns is a
+          // multiple of 4, of 8 for bf16 (checked on the host): only a group of six can be cut, and goes pair by pair.
+          const int c = lp.col_near(nb), left = t.rowsB - c;
+          uint32_t lane_off = (uint32_t)row_l * ldc_b + (uint32_t)c * esz;
+          asm volatile("" : "+v"(lane_off));
+#pragma unroll
+          for (int i = 0; i < MB; ++i) {
+            LLAMARL_FENCE();
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int rel = i * 16 + r;
+              const int rib = row_l + rel;
+              if (rib < t.rowsA && left > 0) {
+                char* q = scatter ? Cb + ((int64_t)a.c_rows[t.row0 + rib] * a.ldc + t.col0 + c) * esz
+                                  : tile_base + (lane_off + (uint32_t)rel * ldc_b);
+                float x[nb];
+#pragma unroll
+                for (int j = 0; j < nb; ++j) x[j] = acc[i][j][r];
+                if (nb != 6 || left >= nb) {
+                  store_final<MODE>(q, x);
+                } else {
+#pragma unroll
+                  for (int j = 0; j < nb; j += 2) {
+                    const float pair[2] = {x[j], x[j + 1]};
+                    if (left >= j + 2) store_final<MODE>(q + j * esz, pair);
+                  }
+                }
+              }
+            }
+          }
+        } else {
+          // k-major operands keep the plain column order: one element per lane and column block
+          uint32_t lane_off = (uint32_t)row_l * ldc_b + (uint32_t)lp.col(0) * esz;
+          asm volatile("" : "+v"(lane_off));
+#pragma unroll
+          for (int i = 0; i < MB; ++i) {
+            LLAMARL_FENCE();
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int rel = i * 16 + r;
+              const int rib = row_l + rel;
+              if (rib < t.rowsA) {
+                char* rowq = scatter ? Cb + ((int64_t)a.c_rows[t.row0 + rib] * a.ldc + t.col0 + lp.col(0)) * esz
+                                     : tile_base + (lane_off + (uint32_t)rel * ldc_b);
+#pragma unroll
+                for (int j = 0; j < nb; ++j)
+                  if (lp.col(j) < t.rowsB) store_final1<MODE>(rowq + j * 16 * esz, acc[i][j][r]);
+              }
+            }
+          }
+        }
+      }
+    }
+    if (!more) break;
+  }
+}
+
+template <typename G, int MODE>
+__global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(const StoreArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  constexpr int BK = 8 * G::Type::EPC, BM = G::Shape::BM;
   const int64_t M = a.m_count ? (int64_t)*a.m_count : a.M;
   const int64_t K = a.k_count ? ((int64_t)*a.k_count + 63) / 64 * 64 : a.K;
   // a later pass of a chunked backward that found no active rows: nothing to add to what the output holds
@@ -952,11 +1323,8 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
     }
     return;
   }
-  if (a.pitch_count != nullptr) {                    // kernel arguments are a private copy
-    const int64_t pp = packed_pitch(*a.pitch_count);
-    if (a.packed_a) a.lda = pp;
-    if (a.packed_b) a.ldb = pp;
-  }
+  const int64_t pitch = a.pitch_count != nullptr ? packed_pitch(*a.pitch_count) : 0;
+  const StoreStrides ld{a.packed_a ? pitch : a.lda, a.packed_b ? pitch : a.ldb};
   const int tiles_m = (int)((M + BM - 1) / BM);
   StorePlan plan;
   plan.init(tiles_m, a.tiles_n, a.group_m, (int)((K + BK - 1) / BK), a.max_splits, STORE_PART_COST<G>);
@@ -965,123 +1333,13 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
   }
   if (!plan.has_item()) return;                      // block-uniform
   G g;
+  if constexpr (G::HALVES) g.nb1 = a.nb1;
   if constexpr (sizeof(typename G::Type::store_t) == 4)
     g.unscale = __uint_as_float((254u << 23) - __float_as_uint(*a.a_scale));       // 1 / *a.a_scale
-  int id = plan.take();
-  store_fetch(g, plan, a, id, M, K, smem);
-  bool counted = false;
-  while (true) {
-    f32x4_t acc[MB][NB];
-    const int cur_id = id;
-    if (store_tile_of<G>(plan, a, cur_id, M, K).k_len > 0) {
-      if constexpr (KMAJOR)
-        run_or_idle(g, smem, acc, S::wave_row(wave_id()) * S::WAVE_M >= store_tile_of<G>(plan, a, cur_id, M, K).rowsA);
-      else if constexpr (std::is_same<G, Store256>::value)
-        g.run(smem, acc, counted);
-      else if constexpr (sizeof(typename G::Type::store_t) == 4)
-        g.template run<true>(smem, acc);
-      else
-        g.run(smem, acc);
-    } else {                                         // nothing to contract: the product is zero
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
-    }
-    const bool more = plan.has_item();
-    wait_vmcnt0();                                   // nothing may wait on vmcnt after the slab requests: see k_fwd_partials
-    __syncthreads();                                 // every wave is done reading the slab buffers
-    if (more) {                                      // the store epilogue uses no LDS: fetch the next tile under it
-      id = plan.take();
-      store_fetch(g, plan, a, id, M, K, smem);
-    }
-    LLAMARL_FENCE();
-
-    const StoreTile<G> cur = store_tile_of<G>(plan, a, cur_id, M, K);
-    counted = cur.nsplit > 1 || (cur.rowsA == BM && cur.rowsB == BN);    // no store of a lane is left out
-    int tid = threadIdx.x;                           // opaque per tile: see k_fwd_partials (a spilled per-lane constant
-    asm volatile("" : "+v"(tid));                    // reloaded here would wait for the slab requests above)
-    const LanePos<S> lp(tid);
-    // Store epilogue, one 16-row block at a time (fences keep the unrolled blocks from piling up address registers).
-    // Addresses are a uniform 64-bit tile base plus a 32-bit per-lane byte offset (a 256-row panel is < 2 GiB).
-    // The offset passes through an empty asm once per tile: otherwise the 32 row offsets of a lane, which do not
-    // depend on the tile, are hoisted out of the persistent loop and live in scratch memory.
-    const int row_l = lp.row(0, 0);                                // lane's first row; (ib, r) adds 16 ib + r
-    if (cur.nsplit > 1) {
-      // a split tile of the last round (block-uniform): the whole BM x BN fp32 block goes to the workspace,
-      // rows and columns past the matrix edge included (they hold zeros or values nobody reads)
-      char* blk = reinterpret_cast<char*>(a.part + ((int64_t)cur.split * plan.rem + cur.tail_index) * (BM * BN));
-      uint32_t lane_off = (uint32_t)row_l * (BN * 4) + (uint32_t)(KMAJOR ? lp.col(0) : lp.col_quad()) * 4u;
-      asm volatile("" : "+v"(lane_off));
-#pragma unroll
-      for (int i = 0; i < MB; ++i) {
-        LLAMARL_FENCE();
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          char* q = blk + (lane_off + (uint32_t)(i * 16 + r) * (BN * 4));
-          if constexpr (!KMAJOR) {
-            *reinterpret_cast<float4*>(q) = make_float4(acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]);
-          } else {
-#pragma unroll
-            for (int j = 0; j < NB; ++j) reinterpret_cast<float*>(q)[j * 16] = acc[i][j][r];
-          }
-        }
-      }
-    } else {
-      constexpr int esz = (MODE >= 3) ? 2 : 4;
-      char* Cb = reinterpret_cast<char*>(a.C);
-      const bool scatter = a.c_rows != nullptr;
-      const uint32_t ldc_b = (uint32_t)a.ldc * esz;
-      char* tile_base = Cb + (cur.row0 * a.ldc + cur.col0) * esz;
-      if constexpr (!KMAJOR) {
-        // K-contiguous operands are fetched quad-interleaved: a lane's four column blocks are neighbouring columns
-        // c .. c+3, stored as one unit; 16 lanes cover 64 consecutive columns of a row -- whole 128-byte lines for
-        // bf16 with no cross-lane traffic (stores that split a line over lanes of different rows measured ~0.5 ms
-        // per GB slower).  The number of columns is a multiple of 4 (checked on the host): a quad is never cut.
-        const int c = lp.col_quad();
-        const bool in_cols = c < cur.rowsB;
-        uint32_t lane_off = (uint32_t)row_l * ldc_b + (uint32_t)c * esz;
-        asm volatile("" : "+v"(lane_off));
-#pragma unroll
-        for (int i = 0; i < MB; ++i) {
-          LLAMARL_FENCE();
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int rel = i * 16 + r;
-            const int rib = row_l + rel;
-            if (rib < cur.rowsA && in_cols) {
-              char* q = scatter ? Cb + ((int64_t)a.c_rows[cur.row0 + rib] * a.ldc + cur.col0 + c) * esz
-                                : tile_base + (lane_off + (uint32_t)rel * ldc_b);
-              store_final4<MODE>(q, acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]);
-            }
-          }
-        }
-      } else {
-        // k-major operands keep the plain column order: one element per lane and column block
-        uint32_t lane_off = (uint32_t)row_l * ldc_b + (uint32_t)lp.col(0) * esz;
-        asm volatile("" : "+v"(lane_off));
-#pragma unroll
-        for (int i = 0; i < MB; ++i) {
-          LLAMARL_FENCE();
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int rel = i * 16 + r;
-            const int rib = row_l + rel;
-            if (rib < cur.rowsA) {
-              char* rowq = scatter ? Cb + ((int64_t)a.c_rows[cur.row0 + rib] * a.ldc + cur.col0 + lp.col(0)) * esz
-                                   : tile_base + (lane_off + (uint32_t)rel * ldc_b);
-#pragma unroll
-              for (int j = 0; j < NB; ++j)
-                if (lp.col(j) < cur.rowsB) store_final1<MODE>(rowq + j * 16 * esz, acc[i][j][r]);
-            }
-          }
-        }
-      }
-    }
-    if (!more) break;
-  }
+  if constexpr (G::HALVES)
+    with_blocks(g, [&](auto blocks) { store_tiles<G, MODE, decltype(blocks)::value>(a, ld, g, plan, M, K, smem); });
+  else
+    store_tiles<G, MODE, G::Shape::NB>(a, ld, g, plan, M, K, smem);
 }
 
 // Finishes the split tiles of a store contraction's last round: C tile = sum over splits (ascending) of the fp32
@@ -1118,8 +1376,8 @@ __global__ __launch_bounds__(256) void k_reduce_tail(StoreArgs a) {
     const int row = (u - j * U::PER_TILE) * U::ROWS + (int)(threadIdx.x / U::THREADS_PER_ROW);
     int tm, tn;
     plan.coords(whole + j, tm, tn);
-    const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * BN;
-    const int rowsA = (int)min((int64_t)BM, M - row0), rowsB = (int)min((int64_t)BN, a.Nn - col0);
+    const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * a.width;
+    const int rowsA = (int)min((int64_t)BM, M - row0), rowsB = (int)min((int64_t)a.width, a.Nn - col0);
     if (row >= rowsA || c >= rowsB) continue;
     const float* p = a.part + (int64_t)j * (BM * BN) + row * BN + c;
     float4 v[STORE_MAX_SPLITS];
@@ -1133,7 +1391,8 @@ __global__ __launch_bounds__(256) void k_reduce_tail(StoreArgs a) {
       if (q < splits) {
         s.x += v[q].x; s.y += v[q].y; s.z += v[q].z; s.w += v[q].w;
       }
-    store_final4<MODE>(Cb + (orow * a.ldc + col0 + c) * esz, s.x, s.y, s.z, s.w);
+    const float x[4] = {s.x, s.y, s.z, s.w};
+    store_final<MODE>(Cb + (orow * a.ldc + col0 + c) * esz, x);
   }
 }
 

@@ -42,15 +42,27 @@ inline int tile_edge(Tile t) { return t == TILE_256 ? 256 : t == TILE_128 ? 128 
 inline int64_t tile_count(int64_t rows, int64_t cols, int64_t edge) {
   return ((rows + edge - 1) / edge) * ((cols + edge - 1) / edge);
 }
-// Logits kernels (forward, recompute): N x V outputs.
-//   bf16, dz at (N, V, d) on 256- / 128- / 64-tiles: (512, 2048, 512) 22 / 16 / 12 us, (512, 8192, 1024) 30 / 18 / 22,
-//   (1041, 5003, 520) 26 / 18 / 26, (1024, 8192, 1024) 30 / 24 / 39, (1024, 16032, 2048) 58 / 70 / 115.
+// Logits kernels (forward, recompute): N x V outputs.  bf16 takes tiles of 256 vocabulary rows where 256 x 256 ones come to
+// LOGITS_MIN_TILES, and below that where they cost less in rounds of the grid than 128 x 128 ones, whose slab takes 1.02 us
+// with two workgroups a CU and 0.72 us with one (186 and 131 of logits_width's units); the latter win where K is short.
+//   forward at (N, V, d), 256 rows / 128 x 128: (882, 10487, 7808) 122 / 222 us, (1700, 5412, 1888) 35 / 58,
+//   (1024, 8192, 1024) 20.7 / 19.4, (1041, 5003, 520) 16.4 / 14.4, (256, 16000, 2048) 28 / 26.
+//   bf16, dz at (N, V, d) on 128- / 64-tiles: (512, 2048, 512) 16 / 12 us, (512, 8192, 1024) 18 / 22, (1041, 5003, 520) 18 / 26.
 //   fp32, dz on 128- / 64-tiles: (512, 2048, 512) 44 / 26 us, (512, 4096, 512) 45 / 34, (1024, 4096, 512) 48 / 57,
 //   (2048, 8192, 512) 127 / 206.
 constexpr int LOGITS_MIN_TILES = 192, LOGITS_MIN_TILES_BF16_128 = 128;   // of the larger edge; fewer: the next smaller one
-Tile logits_tile(int64_t N, int64_t V, llamarl_dtype dt) {
-  if (dt == LLAMARL_BF16 && tile_count(N, V, 256) >= LOGITS_MIN_TILES) return TILE_256;
-  return tile_count(N, V, 128) >= (dt == LLAMARL_BF16 ? LOGITS_MIN_TILES_BF16_128 : LOGITS_MIN_TILES) ? TILE_128 : TILE_64;
+Tile logits_tile(int64_t N, int64_t V, int64_t d, llamarl_dtype dt) {
+  const int64_t t128 = tile_count(N, V, 128);
+  if (dt == LLAMARL_BF16) {
+    const int64_t tiles_v = (V + 255) / 256;
+    if (tile_count(N, V, 256) >= LOGITS_MIN_TILES) return TILE_256;
+    if (tiles_v * ((N + 127) / 128) >= LOGITS_MIN_TILES_BF16_128) {
+      const int64_t nk = (d + 63) / 64, full = t128 / 512, left = t128 % 512;
+      const int64_t cost = full * (nk * 186 + 550) + (left == 0 ? 0 : nk * (left > 256 ? 186 : 131) + 550);
+      if (logits_width(FWD_COSTS, (int)tiles_v, (int)N, d, 256).cost < cost) return TILE_256;
+    }
+  }
+  return t128 >= (dt == LLAMARL_BF16 ? LOGITS_MIN_TILES_BF16_128 : LOGITS_MIN_TILES) ? TILE_128 : TILE_64;
 }
 // Store contractions: M x Nn outputs over K, split along K where tiles are few; counted in parts of 16 slabs, which
 // still pay for their partial blocks.
@@ -75,15 +87,14 @@ typedef TileGemmSmall<F32, Shape64, 4, 2> F32Loop64;
 
 // ---- workspace layouts (every block 256-byte aligned) ----------------------------------------------------
 struct FwdWs {
-  int tiles_v, tiles_t;
+  int tiles_v;
   int64_t n_pad;
   size_t off_m, off_s, off_zt, off_rows, off_tgt, off_nact, total;
 };
-FwdWs fwd_ws(int64_t N, int64_t V, llamarl_dtype dt) {
+FwdWs fwd_ws(int64_t N, int64_t d, int64_t V, llamarl_dtype dt) {
   FwdWs w;
-  const int tile = tile_edge(logits_tile(N, V, dt));
+  const int tile = tile_edge(logits_tile(N, V, d, dt));
   w.tiles_v = (int)((V + tile - 1) / tile);
-  w.tiles_t = (int)((N + tile - 1) / tile);
   w.n_pad = round_up(N, 256);
   // Smaller tiles leave more partials per token, so the planes of a call can be larger than those of a call with more
   // tokens (or vocabulary rows) on larger tiles.  A workspace sized for the larger call has to serve the smaller one as
@@ -197,7 +208,7 @@ llamarl_status check_head_shape(int64_t N, int64_t d, int64_t V, llamarl_dtype d
     return fail(LLAMARL_ERR_UNSUPPORTED, "a 256-row panel of %lld elements per row exceeds 2 GiB", (long long)widest);
   if (N * d * (int64_t)esize(dt) >= (int64_t)1 << 31)
     return fail(LLAMARL_ERR_UNSUPPORTED, "H must be smaller than 2 GiB (its rows are gathered with 32-bit offsets)");
-  if (tile_count(N, V, tile_edge(logits_tile(N, V, dt))) >= (int64_t)1 << 31 || V >= (int64_t)1 << 31)
+  if (tile_count(N, V, tile_edge(logits_tile(N, V, d, dt))) >= (int64_t)1 << 31 || V >= (int64_t)1 << 31)
     return fail(LLAMARL_ERR_UNSUPPORTED, "too many tiles");
   return LLAMARL_OK;
 }
@@ -260,6 +271,15 @@ llamarl_status launch_store_mode(const StoreArgs& a, int64_t work_items, int til
   return LLAMARL_OK;
 }
 
+// Width of the tiles of the k-major store contraction (dH): the narrowest that takes no more columns of tiles than 256.  (The
+// empty columns of a wide tile multiply zeros and cost a power-limited chip less than their share.  dW keeps 256: at
+// 6720 rows a narrow last column made it slower.)
+//   (6720, 40000, d), 256 / narrow: d = 264 223 / 213 us, 520 319 / 307, 1032 587 / 562, 1288 618 / 601
+int store_width(int64_t Nn) {
+  const int64_t cols = (Nn + 255) / 256;
+  return (int)std::max<int64_t>(128, round_up((Nn + cols - 1) / cols, 32));
+}
+
 // C [M,Nn] (+)= A B^T on the persistent grid; ws_part / ws_plan: workspace of the last round's split tiles
 template <typename G>
 llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t M, int64_t Nn,
@@ -278,7 +298,13 @@ llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int6
   a.A = A; a.a_scale = a_scale; a.lda = lda; a.B = B; a.ldb = ldb; a.M = M; a.Nn = Nn; a.K = K;
   constexpr int BM = G::Shape::BM, BN = G::Shape::BN;
   const int tiles_m = (int)((M + BM - 1) / BM);      // worst case: every row active
-  a.tiles_n = (int)((Nn + BN - 1) / BN);
+  a.width = BN;
+  a.nb1 = 0;
+  if constexpr (G::HALVES) {
+    a.width = store_width(Nn);
+    a.nb1 = (a.width - G::Shape::WAVE_N) / 16;
+  }
+  a.tiles_n = (int)((Nn + a.width - 1) / a.width);
   a.group_m = (G::KMAJOR && a.tiles_n <= 16) ? PATCH_ROWS_KMAJOR : PATCH_ROWS_STORE;
   a.C = C; a.ldc = ldc; a.c_is_f32 = c_is_f32; a.accumulate = accumulate;
   const int tiles = tiles_m * a.tiles_n;
@@ -300,7 +326,9 @@ int compact_blocks(int64_t N) { return (int)((N + COMPACT_BLOCK_ROWS - 1) / COMP
 template <typename G>
 llamarl_status launch_fwd_partials(const FwdArgs& a, hipStream_t st) {
   HIP_TRY(set_lds_if_large(k_fwd_partials<G>, fwd_lds_bytes<G>));
-  k_fwd_partials<G><<<dim3((unsigned)persistent_grid((int64_t)a.tiles_v * a.tiles_t, G::GROUPS_PER_CU)),
+  constexpr int narrowest = HAS_NARROW<G> ? 128 : G::Shape::BN;      // the kernel picks a width
+  const int64_t tiles_t = (a.N + narrowest - 1) / narrowest;
+  k_fwd_partials<G><<<dim3((unsigned)persistent_grid((int64_t)a.tiles_v * tiles_t, G::GROUPS_PER_CU)),
                       dim3(G::Shape::THREADS), fwd_lds_bytes<G>, st>>>(a);
   HIP_TRY(hipGetLastError());
   return LLAMARL_OK;
@@ -308,9 +336,10 @@ llamarl_status launch_fwd_partials(const FwdArgs& a, hipStream_t st) {
 template <typename G>
 llamarl_status launch_bwd_dz(DzArgs a, int64_t rows, hipStream_t st) {
   a.tiles_v = (int)((a.V + G::Shape::BM - 1) / G::Shape::BM);
-  a.tiles_t = (int)((rows + G::Shape::BN - 1) / G::Shape::BN);
+  constexpr int narrowest = HAS_NARROW<G> ? 128 : G::Shape::BN;      // the kernel picks a width
+  const int64_t tiles_t = (rows + narrowest - 1) / narrowest;
   HIP_TRY(set_lds_if_large(k_bwd_dz<G>, dz_lds_bytes<G>));
-  k_bwd_dz<G><<<dim3((unsigned)persistent_grid((int64_t)a.tiles_v * a.tiles_t, G::GROUPS_PER_CU)),
+  k_bwd_dz<G><<<dim3((unsigned)persistent_grid((int64_t)a.tiles_v * tiles_t, G::GROUPS_PER_CU)),
                 dim3(G::Shape::THREADS), dz_lds_bytes<G>, st>>>(a);
   HIP_TRY(hipGetLastError());
   return LLAMARL_OK;
@@ -323,24 +352,24 @@ llamarl_status run_logprobs(const void* H, const void* W, const int32_t* targets
                             int64_t d, int64_t V, int64_t v_off, int64_t V_total, int partial, float* out0,
                             float* out1, float* out2, char* ws, hipStream_t st) {
   constexpr llamarl_dtype dt = sizeof(typename TT::store_t) == 2 ? LLAMARL_BF16 : LLAMARL_F32;
-  const FwdWs w = fwd_ws(N, V, dt);
+  const FwdWs w = fwd_ws(N, d, V, dt);
   FwdArgs a;
   a.H = H; a.W = W; a.N = N; a.d = d; a.V = V; a.v_off = v_off;
-  a.tiles_v = w.tiles_v; a.tiles_t = w.tiles_t; a.n_pad = w.n_pad;
+  a.tiles_v = w.tiles_v; a.n_pad = w.n_pad;
   a.part_m = reinterpret_cast<float*>(ws + w.off_m);
   a.part_s = reinterpret_cast<float*>(ws + w.off_s);
   a.zt = reinterpret_cast<float*>(ws + w.off_zt);
   int32_t* rows = reinterpret_cast<int32_t*>(ws + w.off_rows);
   int32_t* n_act = reinterpret_cast<int32_t*>(ws + w.off_nact);
   int32_t* row_targets = reinterpret_cast<int32_t*>(ws + w.off_tgt);
-  a.rows = rows; a.row_targets = row_targets; a.n_act = n_act;
+  a.rows = rows; a.list_stride = row_targets - rows; a.n_act = n_act;
   // active-token list (mask and target range); inactive rows get their outputs here
   k_compact_rows<<<dim3((unsigned)compact_blocks(N)), dim3(COMPACT_THREADS), 0, st>>>(
       compact_args({partial ? 2 : 0, mask, targets, nullptr, V_total, N, 0, rows, n_act, row_targets, nullptr, nullptr,
                     nullptr, out0, out1, out2, 0.f, nullptr, nullptr}));
   HIP_TRY(hipGetLastError());
   llamarl_status s;
-  const Tile tile = logits_tile(N, V, dt);
+  const Tile tile = logits_tile(N, V, d, dt);
   if constexpr (dt == LLAMARL_BF16)
     s = (tile == TILE_256   ? launch_fwd_partials<Logits256>
          : tile == TILE_128 ? launch_fwd_partials<Bf16Loop128>
@@ -431,8 +460,8 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     a.dz_scale = dz_scale;
     a.v_off = v_off;
     a.dz = dz; a.ldz = w.ldz; a.dzt = dzt; a.rows = rows; a.n_act = n_act;
-    a.row_targets = all_targets + (int64_t)c * w.R; a.row_lse = all_lse + (int64_t)c * w.R; a.row_coef = all_coef + (int64_t)c * w.R;
-    const Tile logits = logits_tile(Rc, V, dt);
+    a.list_stride = w.n_list;
+    const Tile logits = logits_tile(Rc, V, d, dt);
     if constexpr (kBf16)
       s = (logits == TILE_256   ? launch_bwd_dz<Logits256>
            : logits == TILE_128 ? launch_bwd_dz<Bf16Loop128>
@@ -500,7 +529,7 @@ size_t llamarl_workspace_bytes(int64_t N, int64_t d, int64_t V, llamarl_dtype dt
   switch (pass) {
     case LLAMARL_PASS_LOGPROBS:
       if (V <= 0) return 0;
-      return fwd_ws(N, V, dt).total;
+      return fwd_ws(N, d, V, dt).total;
     case LLAMARL_PASS_LOSS_FWD:
       return loss_ws(N, N).total;     // sized for the worst case B = N
     case LLAMARL_PASS_LOSS_BWD:
@@ -522,7 +551,7 @@ static llamarl_status logprobs_entry(const void* H, const void* W, const int32_t
     return fail(LLAMARL_ERR_INVALID_ARG, "vocabulary slice [%lld, %lld) does not lie inside [0, %lld)", (long long)v_off,
                 (long long)(v_off + V), (long long)V_total);
   if (!aligned16(H) || !aligned16(W)) return fail(LLAMARL_ERR_INVALID_ARG, "H and W must be 16-byte aligned");
-  const size_t need = fwd_ws(N, V, dt).total;
+  const size_t need = fwd_ws(N, d, V, dt).total;
   if (!ws || ws_bytes < need)
     return fail(LLAMARL_ERR_WORKSPACE, "workspace of %zu bytes given, %zu needed", ws ? ws_bytes : (size_t)0, need);
   if (!aligned16(ws)) return fail(LLAMARL_ERR_INVALID_ARG, "workspace must be 16-byte aligned");
@@ -757,8 +786,8 @@ llamarl_status llamarl_mfma_ceiling(int iters, float* sink, double* flops, void*
   const int grid = persistent_grid((int64_t)1 << 30);      // one workgroup per CU
   k_mfma_ceiling<<<dim3((unsigned)grid), dim3(NTHREADS), 0, reinterpret_cast<hipStream_t>(stream)>>>(iters, sink);
   HIP_TRY(hipGetLastError());
-  // 16x16x32 MFMA = 2 * 16 * 16 * 32 flop; MB x NB of them per k-step and wavefront
-  *flops = (double)grid * (NTHREADS / 64) * (double)iters * CEILING_KSTEPS_PER_ITER * (MB * NB) * (2.0 * 16 * 16 * 32);
+  // 16x16x32 MFMA = 2 * 16 * 16 * 32 flop; CEILING_MB x CEILING_NB of them per k-step and wavefront
+  *flops = (double)grid * (NTHREADS / 64) * (double)iters * CEILING_KSTEPS_PER_ITER * (CEILING_MB * CEILING_NB) * (2.0 * 16 * 16 * 32);
   return LLAMARL_OK;
 }
 
@@ -776,7 +805,7 @@ llamarl_status llamarl_mfma_ceiling_traffic(int traffic, int iters, const void* 
                                                       k_mfma_ceiling_slab_loads, k_mfma_ceiling_reads_and_loads};
   const llamarl_status s = launch_ceiling_traffic(kernels[traffic], grid, iters, sink, panels, st);
   if (s != LLAMARL_OK) return s;
-  *flops = (double)grid * (NTHREADS / 64) * (double)iters * CEILING_KSTEPS_PER_ITER * (MB * NB) * (2.0 * 16 * 16 * 32);
+  *flops = (double)grid * (NTHREADS / 64) * (double)iters * CEILING_KSTEPS_PER_ITER * (CEILING_MB * CEILING_NB) * (2.0 * 16 * 16 * 32);
   return LLAMARL_OK;
 }
 

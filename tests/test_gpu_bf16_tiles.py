@@ -44,7 +44,26 @@ def test_tile_edges(lib, N, V, d, masked):
 @pytest.mark.parametrize("d", [64, 136, 264])                   # 1, 3 and 5 slabs
 def test_narrow_last_token_column(lib, N, d):
     # 192 or more tiles of 256 x 256 at every N: the last column holds 1 .. 256 tokens, half of the wavefronts idle up to 128
-    V = 49200
+    _check_head(lib, N, 49200, d)
+
+
+# 128 or 160 columns of tokens: one column, two, several, the last one full, of one token, of more than the left half;
+# 1, 2, 3, 4 and 9 slabs of the three that are resident
+@pytest.mark.parametrize("N,V", [(31, 49200), (128, 49200), (129, 49200), (159, 49200), (160, 49200), (300, 49200), (319, 49200),
+                                 (320, 49200), (600, 33000), (900, 10487), (1700, 5412)])
+@pytest.mark.parametrize("d", [8, 128, 192, 256, 520])
+def test_narrow_token_tiles(lib, N, V, d):
+    _check_head(lib, N, V, d)
+
+
+# dH on tiles of 160, 192, 224 and 256 columns, its rows past the last whole tile in one half and in both
+@pytest.mark.parametrize("N,V,d", [(6700, 8200, 264), (4000, 8200, 520), (2100, 8200, 1032), (2200, 8200, 1288),
+                                   (2305, 8200, 1160), (4100, 8200, 1024)])
+def test_narrow_gradient_tiles(lib, N, V, d):
+    _check_head(lib, N, V, d)
+
+
+def _check_head(lib, N, V, d):
     H, W, t, coef = _inputs(N, V, d, N + d)
     H, W = H.bfloat16(), W.bfloat16()
     t[0] = V - 1
