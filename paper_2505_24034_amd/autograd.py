@@ -4,11 +4,9 @@ in include/llamarl.h) and the statistics; `loss.backward()` fills `H.grad` and `
 `llamarl_offpolicy_loss_bwd`.  No arithmetic happens here: the forward chains `llamarl_token_logprobs` and
 `llamarl_offpolicy_loss_fwd`, keeps `lse` and `coef`, and the backward hands them to the library.
 
-The upstream gradient of the loss is read by the kernels where autograd left it, on the device.  `backward` also
-copies it to the host and refuses one that is not finite, but enqueues the kernels first: waiting for the copy before
+The upstream gradient of the loss is read by the kernels where autograd left it, on the device.  `backward` (through
+csrc/native.cpp) also copies it to the host and refuses one that is not finite, but enqueues the kernels first: waiting for the copy before
 launching them left the GPU idle for the whole launch sequence (a third of a small model's step)."""
-import math
-
 import torch
 
 from . import binding as L
@@ -31,14 +29,7 @@ class _AipoLoss(torch.autograd.Function):
     def backward(ctx, g_loss, _g_stats, _g_logp):
         H, W, targets, lse, coef = ctx.saved_tensors
         if g_loss.is_cuda and g_loss.dtype == torch.float32 and g_loss.dim() == 0 and not g_loss.is_neg():
-            on_host = torch.empty((), dtype=torch.float32, pin_memory=True)
-            on_host.copy_(g_loss, non_blocking=True)
-            copied = torch.cuda.Event()
-            copied.record()
-            dH, dW = L.offpolicy_loss_bwd_device_scale(H, W, targets, lse, coef, g_loss, dW_dtype=ctx.dW_dtype)
-            copied.synchronize()
-            if not math.isfinite(on_host.item()):
-                raise L.LlamarlError(L.ERR_INVALID_ARG, "grad_loss must be finite")
+            dH, dW = L._bwd_device_scale_checked(H, W, targets, lse, coef, g_loss, ctx.dW_dtype)
         else:
             dH, dW = L.offpolicy_loss_bwd(H, W, targets, lse, coef, grad_loss=float(g_loss), dW_dtype=ctx.dW_dtype)
         if dW.dtype != W.dtype:

@@ -1,11 +1,15 @@
-"""ctypes binding of libllamarl.so: argument marshalling only.
+"""Binding of libllamarl.so: argument marshalling only.
 
 Function names and argument order follow include/llamarl.h.  torch supplies
-device memory (`.data_ptr()`) and the HIP stream handle; every step of the path
-runs in the library's kernels.  There is no fallback: if the library is not
+device memory and the HIP stream handle; every step of the path
+runs in the library's kernels.  The calls of a training step are marshalled by
+csrc/native.cpp (checks, outputs, workspace, the C call: per call 16 -> 7 us for
+token_logprobs); the size queries, the static-scratch loss and the measurement
+aids go through ctypes.  There is no fallback: if the libraries are not
 built, or a call returns a non-zero status, a LlamarlError is raised.
 """
 import ctypes
+import importlib
 import os
 
 import torch
@@ -96,6 +100,37 @@ def load():
     return lib
 
 
+_native = None
+
+
+def _load_native():
+    """csrc/native.cpp, built next to the library"""
+    global _native
+    load()
+    try:
+        module = importlib.import_module("._native", __package__)
+    except ImportError as e:
+        raise LlamarlError(-1, "_native.so does not load (%s): build it with `python -m paper_2505_24034_amd.build`" % e)
+    module.set_error(LlamarlError)
+    _native = module
+    return module
+
+
+def _handle(stream):
+    return None if stream is None else stream.cuda_stream
+
+
+def _storage(dtype):
+    """dtype code of an output; -1: the inputs' own"""
+    if dtype is None:
+        return -1
+    if dtype == torch.bfloat16:
+        return BF16
+    if dtype == torch.float32:
+        return F32
+    raise LlamarlError(ERR_INVALID_ARG, "unsupported tensor dtype %s" % dtype)
+
+
 def _check(status):
     if status != OK:
         raise LlamarlError(status, load().llamarl_last_error().decode())
@@ -136,50 +171,15 @@ def _workspace(nbytes, device, ws):
 
 def token_logprobs(H, W, targets, mask=None, ws=None, stream=None):
     """llamarl_token_logprobs: returns (logp [N], lse [N]) float32 device tensors."""
-    lib = load()
-    dt = _dtype_code(H)
-    _need(H, H.dtype, "H"); _need(W, H.dtype, "W"); _need(targets, torch.int32, "targets")
-    N, d = H.shape
-    V = W.shape[0]
-    if W.shape[1] != d or targets.numel() != N:
-        raise LlamarlError(ERR_INVALID_ARG, "shape mismatch between H, W, targets")
-    if mask is not None:
-        _need(mask, torch.uint8, "mask")
-        if mask.numel() != N:
-            raise LlamarlError(ERR_INVALID_ARG, "mask must have N entries")
-    logp = torch.empty(N, dtype=torch.float32, device=H.device)
-    lse = torch.empty(N, dtype=torch.float32, device=H.device)
-    ws = _workspace(workspace_bytes(N, d, V, dt, PASS_LOGPROBS), H.device, ws)
-    _check(lib.llamarl_token_logprobs(_ptr(H), _ptr(W), _ptr(targets), _ptr(mask), N, d, V, dt, _ptr(logp), _ptr(lse),
-                                      _ptr(ws), ws.numel(), _stream(stream)))
-    return logp, lse
+    return (_native or _load_native()).token_logprobs(H, W, targets, mask, ws, _handle(stream))
 
 
 def offpolicy_loss_fwd(logp, mu_logp, adv, mask, B, T, rho=2.0, norm_mode=NORM_TOKEN_MEAN, clip_mode=CLIP_AIPO,
                        eps_lo=0.2, eps_hi=0.2, targets=None, V=0, ws=None, stream=None):
     """llamarl_offpolicy_loss_fwd: returns (loss [1], coef [B*T], stats [5]) float32 device tensors."""
-    lib = load()
-    N = B * T
-    _need(logp, torch.float32, "logp"); _need(mu_logp, torch.float32, "mu_logp"); _need(adv, torch.float32, "adv")
-    if logp.numel() != N or mu_logp.numel() != N or adv.numel() not in (B, N):
-        raise LlamarlError(ERR_INVALID_ARG, "shape mismatch between logp, mu_logp, adv and B*T")
-    per_token = 1 if (adv.numel() == N and N != B) else 0
-    if mask is not None:
-        _need(mask, torch.uint8, "mask")
-        if mask.numel() != N:
-            raise LlamarlError(ERR_INVALID_ARG, "mask must have B*T entries")
-    if targets is not None:
-        _need(targets, torch.int32, "targets")
-    dev = logp.device
-    loss = torch.empty(1, dtype=torch.float32, device=dev)
-    coef = torch.empty(N, dtype=torch.float32, device=dev)
-    stats = torch.empty(5, dtype=torch.float32, device=dev)
-    p = LossParams(float(rho), int(clip_mode), float(eps_lo), float(eps_hi), int(norm_mode))
-    ws = _workspace(workspace_bytes(N, 0, 0, 0, PASS_LOSS_FWD), dev, ws)
-    _check(lib.llamarl_offpolicy_loss_fwd(_ptr(logp), _ptr(mu_logp), _ptr(adv), per_token, _ptr(mask), _ptr(targets),
-                                          int(V), B, T, ctypes.byref(p), _ptr(loss), _ptr(coef), _ptr(stats),
-                                          _ptr(ws), ws.numel(), _stream(stream)))
-    return loss, coef, stats
+    return (_native or _load_native()).offpolicy_loss_fwd(logp, mu_logp, adv, mask, B, T, rho, int(norm_mode),
+                                                          int(clip_mode), eps_lo, eps_hi, targets, int(V), ws,
+                                                          _handle(stream))
 
 
 def offpolicy_loss_fwd_static(logp, mu_logp, adv, mask, B, T, loss, coef, stats, rho=2.0, norm_mode=NORM_TOKEN_MEAN,
@@ -217,6 +217,11 @@ def offpolicy_loss_bwd(H, W, targets, lse, coef, grad_loss=1.0, dW_dtype=None, d
     """llamarl_offpolicy_loss_bwd: returns (dH [N,d] in H's dtype, dW [V,d] in dW_dtype).
     phase_events: six raw hipEvent_t handles (ints) -> llamarl_offpolicy_loss_bwd_phases is called instead.
     max_rows_per_pass: -> llamarl_offpolicy_loss_bwd_chunked (workspace for that many active rows at a time)."""
+    if phase_events is None:
+        return (_native or _load_native()).offpolicy_loss_bwd(H, W, targets, lse, coef, grad_loss,
+                                                              -1 if dW is not None else _storage(dW_dtype), dW,
+                                                              accumulate_dW, dH, ws, _handle(stream),
+                                                              None if max_rows_per_pass is None else int(max_rows_per_pass))
     lib = load()
     dt = _dtype_code(H)
     _need(H, H.dtype, "H"); _need(W, H.dtype, "W"); _need(targets, torch.int32, "targets")
@@ -234,74 +239,36 @@ def offpolicy_loss_bwd(H, W, targets, lse, coef, grad_loss=1.0, dW_dtype=None, d
     if dH is None:
         dH = torch.empty(N, d, dtype=H.dtype, device=H.device)
     _need(dW, dW_dtype, "dW"); _need(dH, H.dtype, "dH")
-    if max_rows_per_pass is not None:
-        ws = _workspace(bwd_workspace_bytes(N, d, V, dt, int(max_rows_per_pass)), H.device, ws)
-        _check(lib.llamarl_offpolicy_loss_bwd_chunked(
-            _ptr(H), _ptr(W), _ptr(targets), _ptr(lse), _ptr(coef), float(grad_loss), N, d, V, dt, _ptr(dH), _ptr(dW),
-            _dtype_code(dW), int(bool(accumulate_dW)), int(max_rows_per_pass), _ptr(ws), ws.numel(), _stream(stream)))
-        return dH, dW
     ws = _workspace(workspace_bytes(N, d, V, dt, PASS_LOSS_BWD), H.device, ws)
-    args = (_ptr(H), _ptr(W), _ptr(targets), _ptr(lse), _ptr(coef), float(grad_loss), N, d, V, dt, _ptr(dH), _ptr(dW),
-            _dtype_code(dW), int(bool(accumulate_dW)), _ptr(ws), ws.numel(), _stream(stream))
-    if phase_events is None:
-        _check(lib.llamarl_offpolicy_loss_bwd(*args))
-    else:
-        ev = (ctypes.c_void_p * 6)(*[ctypes.c_void_p(int(e)) for e in phase_events])
-        _check(lib.llamarl_offpolicy_loss_bwd_phases(*args, ev))
+    ev = (ctypes.c_void_p * 6)(*[ctypes.c_void_p(int(e)) for e in phase_events])
+    _check(lib.llamarl_offpolicy_loss_bwd_phases(
+        _ptr(H), _ptr(W), _ptr(targets), _ptr(lse), _ptr(coef), float(grad_loss), N, d, V, dt, _ptr(dH), _ptr(dW),
+        _dtype_code(dW), int(bool(accumulate_dW)), _ptr(ws), ws.numel(), _stream(stream), ev))
     return dH, dW
 
 
 def offpolicy_loss_bwd_device_scale(H, W, targets, lse, coef, grad_loss, dW_dtype=None, stream=None):
     """llamarl_offpolicy_loss_bwd_device_scale: offpolicy_loss_bwd with grad_loss a one-element float32 device tensor,
     read on the device and not checked for being finite."""
-    lib = load()
-    dt = _dtype_code(H)
-    _need(H, H.dtype, "H"); _need(W, H.dtype, "W"); _need(targets, torch.int32, "targets")
-    _need(lse, torch.float32, "lse"); _need(coef, torch.float32, "coef"); _need(grad_loss, torch.float32, "grad_loss")
-    if grad_loss.numel() != 1:
-        raise LlamarlError(ERR_INVALID_ARG, "grad_loss must have one entry")
-    N, d = H.shape
-    V = W.shape[0]
-    dH = torch.empty(N, d, dtype=H.dtype, device=H.device)
-    dW = torch.empty(V, d, dtype=dW_dtype or H.dtype, device=H.device)
-    ws = _workspace(workspace_bytes(N, d, V, dt, PASS_LOSS_BWD), H.device, None)
-    _check(lib.llamarl_offpolicy_loss_bwd_device_scale(
-        _ptr(H), _ptr(W), _ptr(targets), _ptr(lse), _ptr(coef), _ptr(grad_loss), N, d, V, dt, _ptr(dH), _ptr(dW),
-        _dtype_code(dW), 0, _ptr(ws), ws.numel(), _stream(stream)))
-    return dH, dW
+    return (_native or _load_native()).offpolicy_loss_bwd_device_scale(H, W, targets, lse, coef, grad_loss, _storage(dW_dtype),
+                                                                       _handle(stream), False)
+
+
+def _bwd_device_scale_checked(H, W, targets, lse, coef, grad_loss, dW_dtype):
+    """offpolicy_loss_bwd_device_scale on the current stream; grad_loss is copied to the host on the way and refused,
+    after the kernels are enqueued, if it is not finite."""
+    return (_native or _load_native()).offpolicy_loss_bwd_device_scale(H, W, targets, lse, coef, grad_loss, _storage(dW_dtype),
+                                                                       None, True)
 
 
 def group_advantages(rewards, n, normalise_std=False, eps=1e-6, stream=None):
     """llamarl_group_advantages: rewards [P*n] (prompt-major) -> advantages [P*n]."""
-    lib = load()
-    _need(rewards, torch.float32, "rewards")
-    if n <= 0 or rewards.numel() % n != 0:
-        raise LlamarlError(ERR_INVALID_ARG, "rewards must hold P*n entries")
-    P = rewards.numel() // n
-    adv = torch.empty_like(rewards)
-    _check(lib.llamarl_group_advantages(_ptr(rewards), P, n, int(bool(normalise_std)), float(eps), _ptr(adv),
-                                        _stream(stream)))
-    return adv
+    return (_native or _load_native()).group_advantages(rewards, n, normalise_std, eps, _handle(stream))
 
 
 def kl_shaped_rewards(rewards, logp, base_logp, mask, lambda_kl, stream=None):
     """llamarl_kl_shaped_rewards: rewards [B], logp / base_logp / mask [B,T] -> (shaped [B], kl [B])."""
-    lib = load()
-    _need(rewards, torch.float32, "rewards")
-    _need(logp, torch.float32, "logp")
-    _need(base_logp, torch.float32, "base_logp")
-    if mask is not None:
-        _need(mask, torch.uint8, "mask")
-    B = rewards.numel()
-    if B <= 0 or logp.numel() % B != 0 or base_logp.numel() != logp.numel() or \
-            (mask is not None and mask.numel() != logp.numel()):
-        raise LlamarlError(ERR_INVALID_ARG, "logp, base_logp and mask must hold B*T entries")
-    T = logp.numel() // B
-    shaped = torch.empty_like(rewards)
-    kl = torch.empty_like(rewards)
-    _check(lib.llamarl_kl_shaped_rewards(_ptr(rewards), _ptr(logp), _ptr(base_logp), _ptr(mask), B, T,
-                                         float(lambda_kl), _ptr(shaped), _ptr(kl), _stream(stream)))
-    return shaped, kl
+    return (_native or _load_native()).kl_shaped_rewards(rewards, logp, base_logp, mask, lambda_kl, _handle(stream))
 
 
 def mfma_ceiling(iters, sink, stream=None):
@@ -325,50 +292,16 @@ def mfma_ceiling_traffic(traffic, iters, panels, sink, stream=None):
 
 def token_logprobs_partial(H, W_slice, targets, v0, V_total, mask=None, ws=None, stream=None):
     """llamarl_token_logprobs_partial: one vocabulary shard's (m [N], s [N], zt [N])."""
-    lib = load()
-    dt = _dtype_code(H)
-    _need(H, H.dtype, "H"); _need(W_slice, H.dtype, "W_slice"); _need(targets, torch.int32, "targets")
-    N, d = H.shape
-    Vs = W_slice.shape[0]
-    if W_slice.shape[1] != d or targets.numel() != N:
-        raise LlamarlError(ERR_INVALID_ARG, "shape mismatch between H, W_slice, targets")
-    if mask is not None:
-        _need(mask, torch.uint8, "mask")
-    m, s, zt = (torch.empty(N, dtype=torch.float32, device=H.device) for _ in range(3))
-    ws = _workspace(workspace_bytes(N, d, Vs, dt, PASS_LOGPROBS), H.device, ws)
-    _check(lib.llamarl_token_logprobs_partial(_ptr(H), _ptr(W_slice), _ptr(targets), _ptr(mask), N, d, Vs, int(v0),
-                                              int(V_total), dt, _ptr(m), _ptr(s), _ptr(zt), _ptr(ws), ws.numel(),
-                                              _stream(stream)))
-    return m, s, zt
+    return (_native or _load_native()).token_logprobs_partial(H, W_slice, targets, int(v0), int(V_total), mask, ws,
+                                                              _handle(stream))
 
 
 def merge_partials(m, s, zt, stream=None):
     """llamarl_merge_partials: m, s, zt [shards, N] -> (logp [N], lse [N])."""
-    lib = load()
-    for t, name in ((m, "m"), (s, "s"), (zt, "zt")):
-        _need(t, torch.float32, name)
-    if m.dim() != 2 or m.shape != s.shape or m.shape != zt.shape:
-        raise LlamarlError(ERR_INVALID_ARG, "m, s, zt must be [shards, N]")
-    shards, N = m.shape
-    logp = torch.empty(N, dtype=torch.float32, device=m.device)
-    lse = torch.empty(N, dtype=torch.float32, device=m.device)
-    _check(lib.llamarl_merge_partials(_ptr(m), _ptr(s), _ptr(zt), shards, N, _ptr(logp), _ptr(lse), _stream(stream)))
-    return logp, lse
+    return (_native or _load_native()).merge_partials(m, s, zt, _handle(stream))
 
 
 def offpolicy_loss_bwd_slice(H, W_slice, targets, v0, lse, coef, grad_loss=1.0, dW_dtype=None, ws=None, stream=None):
     """llamarl_offpolicy_loss_bwd_slice: returns (dH_partial [N,d], dW_slice [V_slice,d])."""
-    lib = load()
-    dt = _dtype_code(H)
-    _need(H, H.dtype, "H"); _need(W_slice, H.dtype, "W_slice"); _need(targets, torch.int32, "targets")
-    _need(lse, torch.float32, "lse"); _need(coef, torch.float32, "coef")
-    N, d = H.shape
-    Vs = W_slice.shape[0]
-    dW_dtype = dW_dtype or H.dtype
-    dH = torch.empty(N, d, dtype=H.dtype, device=H.device)
-    dW = torch.empty(Vs, d, dtype=dW_dtype, device=H.device)
-    ws = _workspace(workspace_bytes(N, d, Vs, dt, PASS_LOSS_BWD), H.device, ws)
-    _check(lib.llamarl_offpolicy_loss_bwd_slice(_ptr(H), _ptr(W_slice), _ptr(targets), _ptr(lse), _ptr(coef),
-                                                float(grad_loss), N, d, Vs, int(v0), dt, _ptr(dH), _ptr(dW),
-                                                _dtype_code(dW), 0, _ptr(ws), ws.numel(), _stream(stream)))
-    return dH, dW
+    return (_native or _load_native()).offpolicy_loss_bwd_slice(H, W_slice, targets, int(v0), lse, coef, grad_loss,
+                                                                _storage(dW_dtype), ws, _handle(stream))

@@ -1,4 +1,5 @@
-"""Builds the HIP library in-tree: paper_2505_24034_amd/libllamarl.so (gfx950 only)."""
+"""Builds the HIP library in-tree, paper_2505_24034_amd/libllamarl.so (gfx950 only), and the binding's argument
+marshalling, _native.so (host code against torch's headers)."""
 import os
 import subprocess
 import sys
@@ -16,8 +17,11 @@ FLAGS = [
 ]
 
 
-def build_library(verbose=True, extra_flags=()):
-    cmd = [HIPCC] + FLAGS + list(extra_flags) + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB_PATH]
+NATIVE_PATH = os.path.join(HERE, "_native.so")
+CXX = os.environ.get("CXX", "g++")
+
+
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
@@ -25,8 +29,32 @@ def build_library(verbose=True, extra_flags=()):
     if verbose and out.strip():
         print(out, flush=True)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError("%s failed:\n%s" % (os.path.basename(cmd[0]), out))
+
+
+def build_library(verbose=True, extra_flags=()):
+    _run([HIPCC] + FLAGS + list(extra_flags) + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB_PATH], verbose)
+    build_native(verbose)
     return LIB_PATH
+
+
+def build_native(verbose=True):
+    """csrc/native.cpp; needs libllamarl.so"""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(HIPCC)))
+    include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+               os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    cmd = [CXX, "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+    for d in include:
+        cmd += ["-isystem", d]
+    cmd += [os.path.join(CSRC, "native.cpp"), "-o", NATIVE_PATH, "-L" + os.path.join(root, "lib"), "-ltorch", "-ltorch_cpu",
+            "-ltorch_python", "-lc10", "-lc10_hip", "-ltorch_hip", "-L" + HERE, "-l:libllamarl.so", "-Wl,-rpath,$ORIGIN"]
+    _run(cmd, verbose)
+    return NATIVE_PATH
 
 
 if __name__ == "__main__":
