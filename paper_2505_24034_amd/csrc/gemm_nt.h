@@ -390,6 +390,11 @@ __device__ __forceinline__ void k_step(typename TT::frag_t (&a)[MB], const typen
   }
 }
 
+// Whether the last slab's second half holds anything: past K both operands are zeros, and their k-step is left out (d of
+// 520: 8.5 of 9 slabs, logits of 3000 x 40000 142 -> 138 us; 1032: 403 -> 398; whole slabs as before).
+template <int BK>
+__device__ __forceinline__ bool half_slab_left(int K) { return (unsigned)(K - 1) % BK >= BK / 2; }
+
 // The main loop, split in two so that a persistent workgroup can start fetching its NEXT tile before it runs the
 // epilogue of the current one:
 //   prefetch(): set up both operand streams of a tile and issue its first two K slabs.  Only legal once every
@@ -535,7 +540,7 @@ struct TileGemm {
       k_step<TT, true, true, false, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0], nxt + b_addr[0], nullptr);
       k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
     }
-    {
+    if (half_slab_left<BK>(K)) {
       const char* cur = smem + ((nk - 1) & 1) * STAGE_BYTES;
       LLAMARL_FENCE();
       k_step<TT, false, false, false, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nullptr, nullptr, nullptr);
@@ -711,9 +716,11 @@ struct TileGemmNarrow {
       narrow_k_step<TT, Fetch, nb, false, true, false, 0, false, LB>(b, a0, a1, acc, nxt + b_addr[0], nxt + b_addr[1],
                                                                   nxt + a_addr[1], nullptr);
     }
-    const char* cur = stage(smem, st);
-    LLAMARL_FENCE();
-    narrow_k_step<TT, Fetch, nb, false, false, false, 0, false, LB>(b, a1, a0, acc, cur + b_addr[1], nullptr, nullptr, nullptr);
+    if (half_slab_left<BK>(K)) {
+      const char* cur = stage(smem, st);
+      LLAMARL_FENCE();
+      narrow_k_step<TT, Fetch, nb, false, false, false, 0, false, LB>(b, a1, a0, acc, cur + b_addr[1], nullptr, nullptr, nullptr);
+    }
   }
 
 };

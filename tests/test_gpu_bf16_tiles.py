@@ -56,6 +56,13 @@ def test_narrow_token_tiles(lib, N, V, d):
     _check_head(lib, N, V, d)
 
 
+# the last slab up to its half, just past it and full, alone and after another: narrow tiles, 256 and 64 columns
+@pytest.mark.parametrize("d", [32, 40, 64, 96, 104, 160, 168])
+@pytest.mark.parametrize("N,V", [(40, 33000), (400, 33000), (1000, 49200)])
+def test_last_slab(lib, N, V, d):
+    _check_head(lib, N, V, d)
+
+
 # dH on tiles of 160, 192, 224 and 256 columns, its rows past the last whole tile in one half and in both
 @pytest.mark.parametrize("N,V,d", [(6700, 8200, 264), (4000, 8200, 520), (2100, 8200, 1032), (2200, 8200, 1288),
                                    (2305, 8200, 1160), (4100, 8200, 1024)])
