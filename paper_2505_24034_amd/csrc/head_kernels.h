@@ -1008,6 +1008,7 @@ constexpr int STORE_PART_COST = G::Shape::BM == 256 ? 18 : G::Shape::BM == 128 ?
 struct StorePlan {
   int tiles_m, tiles_n, group_m;
   int whole, rem, splits, n_items;
+  int full, last;      // items of whole rounds; this workgroup's item of the last one
   int next, stride;
   // part_cost: what writing one part's fp32 block and reading it back costs, in 1/256 of a slab of the whole grid
   __device__ __forceinline__ void init(int tiles_m_, int tiles_n_, int group_m_, int nk, int max_splits, int part_cost) {
@@ -1022,28 +1023,29 @@ struct StorePlan {
     // and at most STORE_TAIL_ROUNDS rounds of parts; the smallest such factor on ties.  Counting rounds alone cut the
     // dW of (N, V, d) = (7000, 33001, 1032) into 931 parts (0.5 GB of blocks): 515 us
     // instead of 487; (3000, 60000, 1504) 545 instead of 485, (4000, 128256, 2560) 2022 instead of 1944.
-    int best = 1;
-    int best_cost = nk * 256;                          // nk < 2^16 (a 256-row panel is < 2 GiB): 32 bits are enough
-    for (int sp = 2; sp <= max_splits && rem > 0; ++sp) {
-      const int rounds = (rem * sp + G - 1) / G;
-      if (nk / sp < 4 || rounds > STORE_TAIL_ROUNDS) break;
-      const int cost = rounds * nk * 256 / sp + rem * sp * part_cost + STORE_REDUCE_COST;
-      if (cost < best_cost) {
-        best = sp;
-        best_cost = cost;
-      }
-    }
-    splits = best;
+    // One factor a lane, cost and factor in one word: 31 factors one after the other, two divisions each, took 6 us.
+    const int sp = (threadIdx.x & 31) + 1;             // STORE_MAX_SPLITS lanes
+    const int rounds = (rem * sp + G - 1) / G;
+    // nk < 2^16 (a 256-row panel is < 2 GiB): costs are below 2^26
+    const unsigned cost = sp == 1 ? nk * 256 : rounds * nk * 256 / sp + rem * sp * part_cost + STORE_REDUCE_COST;
+    unsigned best = sp == 1 || (sp <= max_splits && nk / sp >= 4 && rounds <= STORE_TAIL_ROUNDS) ? cost * 32 + (sp - 1) : ~0u;
+#pragma unroll
+    for (int m = 16; m > 0; m >>= 1) best = min(best, (unsigned)__shfl_xor((int)best, m));
+    splits = rem > 0 ? __builtin_amdgcn_readfirstlane((int)(best & 31)) + 1 : 1;
     n_items = whole + rem * splits;
-    // 32 consecutive items per XCD and round (see TileSchedule): workgroup b sits on XCD b % 8
+    // 32 consecutive items per XCD and round (see TileSchedule): workgroup b sits on XCD b % 8.  The items of a last round
+    // that does not fill the grid are dealt to all XCDs alike.
     const int b = blockIdx.x;
-    next = (G & 7) == 0 ? (b & 7) * (G >> 3) + (b >> 3) : b;
+    full = n_items / G * G;
+    const int left = n_items - full, per = (left + 7) >> 3, mine = (b & 7) * per + (b >> 3);
+    last = (G & 7) != 0 ? full + b : (b >> 3) < per && mine < left ? full + mine : n_items;
+    next = full == 0 ? last : (G & 7) == 0 ? (b & 7) * (G >> 3) + (b >> 3) : b;
     stride = G;
   }
   __device__ __forceinline__ bool has_item() const { return next < n_items; }
   __device__ __forceinline__ int take() {
     const int it = next;
-    next += stride;
+    next = it >= full ? n_items : it + stride < full ? it + stride : last;
     return it;
   }
   // item -> tile id, K split and number of splits; tail items are split-major, so the 32 items an XCD holds in
@@ -1356,7 +1358,24 @@ struct TailUnit {
   static constexpr int PER_TILE = S::BM / ROWS;
 };
 constexpr int TAIL_MAX_BLOCKS = 2048;
-constexpr int STORE_MAX_SPLITS = 8;                  // most parts a tail tile is cut into
+// Most parts a tail tile is cut into.  Eight left most CUs idle where few tokens meet a long vocabulary: dH of
+// (300, 128256, 1032), 27 tiles of 128, 275 -> 141 us; (1024, 128256, 520) 272 -> 163.
+constexpr int STORE_MAX_SPLITS = 32;
+static_assert(STORE_MAX_SPLITS <= 32, "StorePlan::init weighs 32 factors");
+// The parts in ascending order, MOST loads of a thread in flight.  More than eight parts are few tiles, bound by latency: 32
+// of them eight at a time took 13 us.  All 32 at once, though, leave too few wavefronts for the many tiles of eight parts.
+template <int MOST>
+__device__ __forceinline__ void add_parts(float4& s, const float* p, int64_t plane, int splits) {
+  float4 v[MOST];
+#pragma unroll
+  for (int q = 0; q < MOST; ++q)
+    if (q < splits) v[q] = *reinterpret_cast<const float4*>(p + q * plane);
+#pragma unroll
+  for (int q = 0; q < MOST; ++q)
+    if (q < splits) {
+      s.x += v[q].x; s.y += v[q].y; s.z += v[q].z; s.w += v[q].w;
+    }
+}
 template <typename S, int MODE>
 __global__ __launch_bounds__(256) void k_reduce_tail(StoreArgs a) {
   const int whole = a.plan_out[0], rem = a.plan_out[1], splits = a.plan_out[2], tiles_m = a.plan_out[3];
@@ -1380,17 +1399,13 @@ __global__ __launch_bounds__(256) void k_reduce_tail(StoreArgs a) {
     const int rowsA = (int)min((int64_t)BM, M - row0), rowsB = (int)min((int64_t)a.width, a.Nn - col0);
     if (row >= rowsA || c >= rowsB) continue;
     const float* p = a.part + (int64_t)j * (BM * BN) + row * BN + c;
-    float4 v[STORE_MAX_SPLITS];
-#pragma unroll
-    for (int q = 0; q < STORE_MAX_SPLITS; ++q)
-      if (q < splits) v[q] = *reinterpret_cast<const float4*>(p + q * plane);
     const int64_t orow = a.c_rows ? (int64_t)a.c_rows[row0 + row] : row0 + row;
-    float4 s = v[0];
-#pragma unroll
-    for (int q = 1; q < STORE_MAX_SPLITS; ++q)
-      if (q < splits) {
-        s.x += v[q].x; s.y += v[q].y; s.z += v[q].z; s.w += v[q].w;
-      }
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (splits <= 8) {
+      add_parts<8>(s, p, plane, splits);
+    } else {
+      for (int q = 0; q < splits; q += 16) add_parts<16>(s, p + q * plane, plane, splits - q);
+    }
     const float x[4] = {s.x, s.y, s.z, s.w};
     store_final<MODE>(Cb + (orow * a.ldc + col0 + c) * esz, x);
   }

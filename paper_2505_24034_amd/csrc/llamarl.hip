@@ -65,7 +65,13 @@ Tile logits_tile(int64_t N, int64_t V, int64_t d, llamarl_dtype dt) {
   return t128 >= (dt == LLAMARL_BF16 ? LOGITS_MIN_TILES_BF16_128 : LOGITS_MIN_TILES) ? TILE_128 : TILE_64;
 }
 // Store contractions: M x Nn outputs over K, split along K where tiles are few; counted in parts of 16 slabs, which
-// still pay for their partial blocks.
+// still pay for their partial blocks.  Up to eight parts a tile the tiles of a count decide; beyond, where K is long and
+// the output small, 256-tiles of more than 128 rows if they fill the chip, 128-tiles by the output they hold (the rest of
+// an edge tile is padding).  bf16 dH on 256- / 128- / 64-tiles with up to 32 parts (before, with eight parts, on the tile of
+// the rule then):
+//   (64, 128256, 1024) 86 / 60 / 54 (146), (300, 128256, 520) 105 / 96 / 130 (172), (300, 128256, 1032) 141 / 145 / 231 (275),
+//   (150, 128256, 2048) 124 / 170 / 247 (302), (1024, 128256, 520) 163 / 203 / 373 (272), (64, 128256, 4096) 203 / 193 / 225 (309),
+//   (600, 60000, 1032) 100 / 102 / 195 (124); fp32 on 128- / 64-tiles (300, 16400, 260) 62 / 47 (92).
 //   bf16, dH at (N, V, d) on 256- / 128- / 64-tiles: (512, 2048, 512) 23 / 17.5 / 17 us, (1041, 5003, 520) 33 / 26 / 29,
 //   (1024, 8192, 1024) 42 / 36 / 43, (64, 128256, 4096) 337 / 236 / 229, (1024, 16032, 2048) 77 / 79 / 125;
 //   dW: (512, 2048, 512) 23 / 19 / 16, (512, 8192, 1024) 38 / 17 / 25, (1024, 16032, 2048) 67 / 73 / 131.
@@ -74,8 +80,13 @@ Tile logits_tile(int64_t N, int64_t V, int64_t d, llamarl_dtype dt) {
 Tile store_tile(int64_t M, int64_t Nn, int64_t K, llamarl_dtype dt) {
   const int64_t slab_k = dt == LLAMARL_BF16 ? 64 : 32;
   const int64_t parts = std::min<int64_t>(STORE_MAX_SPLITS, std::max<int64_t>(1, K / (16 * slab_k)));
-  if (dt == LLAMARL_BF16 && tile_count(M, Nn, 256) * parts >= 256) return TILE_256;
-  return tile_count(M, Nn, 128) * parts >= (dt == LLAMARL_BF16 ? 128 : 256) ? TILE_128 : TILE_64;
+  const int64_t few = std::min<int64_t>(parts, 8);
+  if (dt == LLAMARL_BF16) {
+    const int64_t t256 = tile_count(M, Nn, 256);
+    if (t256 * few >= 256 || (M > 128 && t256 * parts >= 256)) return TILE_256;
+  }
+  if (tile_count(M, Nn, 128) * few >= (dt == LLAMARL_BF16 ? 128 : 256)) return TILE_128;
+  return M * Nn / (128 * 128) * parts >= 256 ? TILE_128 : TILE_64;
 }
 
 typedef TileGemmSmall<BF16, Shape128, 2, 2> Bf16Loop128;
@@ -179,7 +190,7 @@ BwdWs bwd_ws(int64_t N, int64_t d, int64_t V, llamarl_dtype dt, int64_t max_rows
   w.off_plan = w.off_nact + (size_t)round_up((int64_t)(1 + w.n_pass) * (int64_t)sizeof(int32_t), 256);
   w.off_part = w.off_plan + 256;
   // fp32 partial blocks of the split tiles at the end of a store contraction (see StorePlan): at most
-  // STORE_TAIL_ROUNDS per workgroup of the grid, and never more than eight per tile
+  // STORE_TAIL_ROUNDS per workgroup of the grid, and never more than STORE_MAX_SPLITS per tile
   auto part_bytes = [&](int64_t M, int64_t edge) {
     const int64_t grid = (int64_t)MAX_GRID * (edge == 256 ? 1 : 2);
     return std::min(STORE_TAIL_ROUNDS * grid, tile_count(M, d, edge) * STORE_MAX_SPLITS) * edge * edge * 4;
@@ -308,7 +319,9 @@ llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int6
   a.group_m = (G::KMAJOR && a.tiles_n <= 16) ? PATCH_ROWS_KMAJOR : PATCH_ROWS_STORE;
   a.C = C; a.ldc = ldc; a.c_is_f32 = c_is_f32; a.accumulate = accumulate;
   const int tiles = tiles_m * a.tiles_n;
-  const int64_t items = (int64_t)tiles * STORE_MAX_SPLITS;   // a small contraction still gets a workgroup per split
+  constexpr int64_t PART_K = 4 * 8 * G::Type::EPC;           // a part has four slabs or more
+  // a small contraction still gets a workgroup per split
+  const int64_t items = (int64_t)tiles * std::min<int64_t>(STORE_MAX_SPLITS, std::max<int64_t>(1, (K + PART_K - 1) / PART_K));
   if (c_is_f32) return accumulate ? launch_store_mode<G, 2>(a, items, tiles, st) : launch_store_mode<G, 1>(a, items, tiles, st);
   if constexpr (sizeof(typename G::Type::store_t) == 2) {
     return accumulate ? launch_store_mode<G, 4>(a, items, tiles, st) : launch_store_mode<G, 3>(a, items, tiles, st);

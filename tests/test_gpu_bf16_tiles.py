@@ -70,6 +70,13 @@ def test_narrow_gradient_tiles(lib, N, V, d):
     _check_head(lib, N, V, d)
 
 
+# dH in up to 32 parts a tile: 64-, 128- and 256-tiles, a last round that fills every XCD and one that does not
+@pytest.mark.parametrize("N,V,d", [(1, 70000, 64), (64, 40000, 512), (129, 33000, 520), (300, 70000, 264), (300, 70000, 1032),
+                                   (520, 60000, 776), (140, 20000, 2048)])
+def test_many_parts(lib, N, V, d):
+    _check_head(lib, N, V, d)
+
+
 def _check_head(lib, N, V, d):
     H, W, t, coef = _inputs(N, V, d, N + d)
     H, W = H.bfloat16(), W.bfloat16()

@@ -64,6 +64,11 @@ def test_tile_edges(lib, N, V, d):
     assert _worst(dH, rdH) <= tol and _worst(dW, rdW) <= tol
 
 
+@pytest.mark.parametrize("N,V,d", [(200, 33000, 260), (300, 40000, 512)])      # dH in up to 32 parts: 64- and 128-tiles
+def test_many_parts(lib, N, V, d):
+    test_tile_edges(lib, N, V, d)
+
+
 @pytest.mark.parametrize("N,V,d", [(130, 300, 40), (400, 9000, 40)])      # 64- and 128-tiles
 def test_values_that_cannot_be_split(lib, N, V, d):
     # a constant-one column makes W[:, 0] a bias; -inf there bans a token, and 3.4e38 (infinity in bf16) times
