@@ -1347,7 +1347,7 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
 // Finishes the split tiles of a store contraction's last round: C tile = sum over splits (ascending) of the fp32
 // partial blocks, stored in the contraction's MODE (dtype, accumulate, row scatter); the plan is the one k_gemm_store
 // wrote.  Bound by memory latency: a work unit is a few rows of one tail tile (one float4 per thread and split), all
-// of a thread's loads are in flight before the first is added, and the units of all tail tiles are dealt to a bounded
+// of a thread's loads, up to sixteen, are in flight before the first is added, and the units of all tail tiles are dealt to a bounded
 // grid -- bounded because the number of tail tiles is only known on the device and a launch that finds none must
 // stay cheap.  Against one block per 32-row stripe, whose threads walked eight rows and their splits one dependent
 // load after the other: 18.0 -> 5.4 us for one tile in eight parts, 19.5 -> 5.4 us for 15, 52.8 -> 32 us for the dW
@@ -1359,7 +1359,7 @@ struct TailUnit {
 };
 constexpr int TAIL_MAX_BLOCKS = 2048;
 // Most parts a tail tile is cut into.  Eight left most CUs idle where few tokens meet a long vocabulary: dH of
-// (300, 128256, 1032), 27 tiles of 128, 275 -> 141 us; (1024, 128256, 520) 272 -> 163.
+// (300, 128256, 1032), 27 tiles of 128, 250 -> 133 us; (1024, 128256, 520) 243 -> 153.
 constexpr int STORE_MAX_SPLITS = 32;
 static_assert(STORE_MAX_SPLITS <= 32, "StorePlan::init weighs 32 factors");
 // The parts in ascending order, MOST loads of a thread in flight.  More than eight parts are few tiles, bound by latency: 32

@@ -67,11 +67,13 @@ Tile logits_tile(int64_t N, int64_t V, int64_t d, llamarl_dtype dt) {
 // Store contractions: M x Nn outputs over K, split along K where tiles are few; counted in parts of 16 slabs, which
 // still pay for their partial blocks.  Up to eight parts a tile the tiles of a count decide; beyond, where K is long and
 // the output small, 256-tiles of more than 128 rows if they fill the chip, 128-tiles by the output they hold (the rest of
-// an edge tile is padding).  bf16 dH on 256- / 128- / 64-tiles with up to 32 parts (before, with eight parts, on the tile of
-// the rule then):
-//   (64, 128256, 1024) 86 / 60 / 54 (146), (300, 128256, 520) 105 / 96 / 130 (172), (300, 128256, 1032) 141 / 145 / 231 (275),
-//   (150, 128256, 2048) 124 / 170 / 247 (302), (1024, 128256, 520) 163 / 203 / 373 (272), (64, 128256, 4096) 203 / 193 / 225 (309),
-//   (600, 60000, 1032) 100 / 102 / 195 (124); fp32 on 128- / 64-tiles (300, 16400, 260) 62 / 47 (92).
+// an edge tile is padding).  bf16 dH on 256- / 128- / 64-tiles with up to 32 parts, and now against eight parts and the rule
+// of then:
+//   (64, 128256, 1024) 86 / 60 / 54, 80 -> 51; (300, 128256, 520) 105 / 96 / 130, 110 -> 90; (64, 128256, 4096) 203 / 193 / 225,
+//   231 -> 186; (300, 128256, 1032) 141 / 145 / 231, 250 -> 133; (150, 128256, 2048) 124 / 170 / 247, 225 -> 117;
+//   (1024, 128256, 520) 163 / 203 / 373, 243 -> 153; (600, 60000, 1032) 100 / 102 / 195, 112 -> 90;
+//   fp32 on 128- / 64-tiles (300, 16400, 260) 62 / 47, 65 -> 41; (300, 40000, 1024) 289 -> 190.
+// With up to eight parts:
 //   bf16, dH at (N, V, d) on 256- / 128- / 64-tiles: (512, 2048, 512) 23 / 17.5 / 17 us, (1041, 5003, 520) 33 / 26 / 29,
 //   (1024, 8192, 1024) 42 / 36 / 43, (64, 128256, 4096) 337 / 236 / 229, (1024, 16032, 2048) 77 / 79 / 125;
 //   dW: (512, 2048, 512) 23 / 19 / 16, (512, 8192, 1024) 38 / 17 / 25, (1024, 16032, 2048) 67 / 73 / 131.
