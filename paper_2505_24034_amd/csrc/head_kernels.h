@@ -822,7 +822,7 @@ __device__ __forceinline__ void dz_tiles(const DzArgs& a, G& g, TileSchedule<PAT
     auto issue_part = [&](int part) {
       if (part > 0 && part < G::FIRST_PARTS && !last) issue_first<G, nb>(g, smem, part);
     };
-    float nc[nb > 0 ? nb : 1];                               // - upstream * coef; 0 past the active rows, whose logits are 0
+    float nc[nb > 0 ? nb : 1];                               // - upstream * coef; 0 past the active rows
     bool dead = false, any = false;
     const int first = (int)a.v_off + (int)v0 + lp.wm * S::WAVE_M;       // the wavefront's first row (a global index)
 #pragma unroll
@@ -831,11 +831,13 @@ __device__ __forceinline__ void dz_tiles(const DzArgs& a, G& g, TileSchedule<PAT
       float c = in ? upstream * tcoef[j] : 0.f;
       if constexpr (sizeof(typename G::Type::store_t) == 4) c *= scale;
       nc[j] = -c;
-      dead |= in && c == 0.f;
+      dead |= c == 0.f;
       any |= (uint32_t)(ttgt[j] - first) < (uint32_t)S::WAVE_M;
     }
     if (__any(dead)) {                                       // wave-uniform
-      // a row whose upstream * coef is 0 is exactly 0, whatever its logits are (they may be infinite or NaN)
+      // a row whose upstream * coef is 0 is exactly 0, whatever its logits are (they may be infinite or NaN), and so is a
+      // position past the active rows: dW contracts over the last 64 of them, and the zeros fetched for H there meet a -inf
+      // of W in a NaN
       asm volatile("");                                      // a branch, not 128 selects of every tile
 #pragma unroll
       for (int j = 0; j < nb; ++j)
