@@ -232,14 +232,18 @@ def offpolicy_loss_bwd(H, W, targets, lse, coef, grad_loss=1.0, dW_dtype=None, d
         dW_dtype = dW.dtype
     if dW_dtype is None:
         dW_dtype = H.dtype
-    if dW is None:
-        if accumulate_dW:
-            raise LlamarlError(ERR_INVALID_ARG, "accumulate_dW needs an existing dW tensor")
-        dW = torch.empty(V, d, dtype=dW_dtype, device=H.device)
-    if dH is None:
-        dH = torch.empty(N, d, dtype=H.dtype, device=H.device)
+    if dW is None and accumulate_dW:
+        raise LlamarlError(ERR_INVALID_ARG, "accumulate_dW needs an existing dW tensor")
+    current = torch.cuda.current_stream(H.device)
+    with torch.cuda.stream(stream):         # what the call allocates comes from its stream's pool: see CallStream in native.cpp
+        if dW is None:
+            dW = torch.empty(V, d, dtype=dW_dtype, device=H.device)
+            dW.record_stream(current)
+        if dH is None:
+            dH = torch.empty(N, d, dtype=H.dtype, device=H.device)
+            dH.record_stream(current)
+        ws = _workspace(workspace_bytes(N, d, V, dt, PASS_LOSS_BWD), H.device, ws)
     _need(dW, dW_dtype, "dW"); _need(dH, H.dtype, "dH")
-    ws = _workspace(workspace_bytes(N, d, V, dt, PASS_LOSS_BWD), H.device, ws)
     ev = (ctypes.c_void_p * 6)(*[ctypes.c_void_p(int(e)) for e in phase_events])
     _check(lib.llamarl_offpolicy_loss_bwd_phases(
         _ptr(H), _ptr(W), _ptr(targets), _ptr(lse), _ptr(coef), float(grad_loss), N, d, V, dt, _ptr(dH), _ptr(dW),

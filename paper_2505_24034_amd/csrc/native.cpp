@@ -11,11 +11,13 @@
 
 #include <ATen/ATen.h>
 #include <ATen/hip/HIPEvent.h>
+#include <c10/core/impl/VirtualGuardImpl.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cmath>
+#include <optional>
 
 #include "../../include/llamarl.h"
 
@@ -70,12 +72,34 @@ at::Tensor workspace(PyObject* o, size_t bytes, const at::Tensor& like) {
   if (o != Py_None) return tensor(o, "ws");
   return empty(like, {(int64_t)std::max<size_t>(bytes, 16)}, at::kByte);
 }
-void* stream_of(PyObject* o) {      // None: the current stream
-  if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
-  void* p = PyLong_AsVoidPtr(o);
-  if (p == nullptr && PyErr_Occurred()) throw Raised{};
-  return p;
-}
+// The stream of a call: the current one (None) or the caller's, which is the current one while the call allocates.  A workspace
+// out of another stream's pool would be free again, and given to that stream's next allocation, while the kernels still run.
+struct CallStream {
+  std::optional<c10::Stream> before;      // the current stream, where it is another
+  void* handle;
+  CallStream(PyObject* o, const at::Tensor& like) {
+    if (o == Py_None) {
+      handle = c10::hip::getCurrentHIPStream().stream();
+      return;
+    }
+    handle = PyLong_AsVoidPtr(o);
+    if (handle == nullptr && PyErr_Occurred()) throw Raised{};
+    const c10::DeviceIndex device = like.device().index();
+    if (handle == c10::hip::getCurrentHIPStream(device).stream()) return;
+    const c10::hip::HIPStream s = c10::hip::getStreamFromExternal(static_cast<hipStream_t>(handle), device);
+    before = c10::impl::VirtualGuardImpl(c10::DeviceType::CUDA).exchangeStream(
+        c10::Stream(c10::Stream::UNSAFE, like.device(), s.id()));
+  }
+  CallStream(const CallStream&) = delete;
+  ~CallStream() {
+    if (before) c10::impl::VirtualGuardImpl(c10::DeviceType::CUDA).exchangeStream(*before);
+  }
+  // an output may be read on the caller's current stream, and freed while it is
+  void returns(std::initializer_list<at::Tensor> ts) const {
+    if (before)
+      for (const at::Tensor& t : ts) t.record_stream(*before);
+  }
+};
 int64_t integer(PyObject* o) {
   const int64_t v = PyLong_AsLongLong(o);
   if (v == -1 && PyErr_Occurred()) throw Raised{};
@@ -149,13 +173,14 @@ PyObject* token_logprobs(PyObject* const* a) {
   x.same_width("W");
   const at::Tensor mask = optional(a[3], at::kByte, "mask");
   if (mask.defined() && mask.numel() != x.N) invalid("mask must have N entries");
+  const CallStream st(a[5], x.H);
   const at::Tensor logp = empty(x.H, {x.N}), lse = empty(x.H, {x.N});
   const at::Tensor ws = workspace(a[4], llamarl_workspace_bytes(x.N, x.d, x.V, x.dt, LLAMARL_PASS_LOGPROBS), x.H);
-  void* st = stream_of(a[5]);
   check(unlocked([&] {
     return llamarl_token_logprobs(ptr(x.H), ptr(x.W), ptr<int32_t>(x.targets), ptr<uint8_t>(mask), x.N, x.d, x.V, x.dt,
-                                  ptr<float>(logp), ptr<float>(lse), ptr(ws), (size_t)ws.numel(), st);
+                                  ptr<float>(logp), ptr<float>(lse), ptr(ws), (size_t)ws.numel(), st.handle);
   }));
+  st.returns({logp, lse});
   return tuple({logp, lse});
 }
 
@@ -165,14 +190,15 @@ PyObject* token_logprobs_partial(PyObject* const* a) {
   x.same_width("W_slice");
   const int64_t v0 = integer(a[3]), V_total = integer(a[4]);
   const at::Tensor mask = optional(a[5], at::kByte, "mask");
+  const CallStream st(a[7], x.H);
   const at::Tensor m = empty(x.H, {x.N}), s = empty(x.H, {x.N}), zt = empty(x.H, {x.N});
   const at::Tensor ws = workspace(a[6], llamarl_workspace_bytes(x.N, x.d, x.V, x.dt, LLAMARL_PASS_LOGPROBS), x.H);
-  void* st = stream_of(a[7]);
   check(unlocked([&] {
     return llamarl_token_logprobs_partial(ptr(x.H), ptr(x.W), ptr<int32_t>(x.targets), ptr<uint8_t>(mask), x.N, x.d, x.V, v0,
                                           V_total, x.dt, ptr<float>(m), ptr<float>(s), ptr<float>(zt), ptr(ws),
-                                          (size_t)ws.numel(), st);
+                                          (size_t)ws.numel(), st.handle);
   }));
+  st.returns({m, s, zt});
   return tuple({m, s, zt});
 }
 
@@ -181,12 +207,13 @@ PyObject* merge_partials(PyObject* const* a) {
   const at::Tensor &m = needed(a[0], at::kFloat, "m"), &s = needed(a[1], at::kFloat, "s"), &zt = needed(a[2], at::kFloat, "zt");
   if (m.dim() != 2 || m.sizes() != s.sizes() || m.sizes() != zt.sizes()) invalid("m, s, zt must be [shards, N]");
   const int64_t shards = m.size(0), N = m.size(1);
+  const CallStream st(a[3], m);
   const at::Tensor logp = empty(m, {N}), lse = empty(m, {N});
-  void* st = stream_of(a[3]);
   check(unlocked([&] {
     return llamarl_merge_partials(ptr<float>(m), ptr<float>(s), ptr<float>(zt), (int)shards, N, ptr<float>(logp), ptr<float>(lse),
-                                  st);
+                                  st.handle);
   }));
+  st.returns({logp, lse});
   return tuple({logp, lse});
 }
 
@@ -208,14 +235,15 @@ PyObject* offpolicy_loss_fwd(PyObject* const* a) {
   p.eps_lo = (float)real(a[9]);
   p.eps_hi = (float)real(a[10]);
   const int64_t V = integer(a[12]);
+  const CallStream st(a[14], logp);
   const at::Tensor loss = empty(logp, {1}), coef = empty(logp, {N}), stats = empty(logp, {5});
   const at::Tensor ws = workspace(a[13], llamarl_workspace_bytes(N, 0, 0, LLAMARL_F32, LLAMARL_PASS_LOSS_FWD), logp);
-  void* st = stream_of(a[14]);
   check(unlocked([&] {
     return llamarl_offpolicy_loss_fwd(ptr<float>(logp), ptr<float>(mu), ptr<float>(adv), per_token, ptr<uint8_t>(mask),
                                       ptr<int32_t>(targets), V, B, T, &p, ptr<float>(loss), ptr<float>(coef),
-                                      ptr<float>(stats), ptr(ws), (size_t)ws.numel(), st);
+                                      ptr<float>(stats), ptr(ws), (size_t)ws.numel(), st.handle);
   }));
+  st.returns({loss, coef, stats});
   return tuple({loss, coef, stats});
 }
 
@@ -230,6 +258,7 @@ PyObject* offpolicy_loss_bwd(PyObject* const* a) {
   const float grad_loss = (float)real(a[5]);
   const int accumulate = PyObject_IsTrue(a[8]);
   if (accumulate < 0) throw Raised{};
+  const CallStream st(a[11], x.H);
   at::Tensor dW, dH;
   if (a[7] != Py_None) dW = tensor(a[7], "dW");
   else if (accumulate) invalid("accumulate_dW needs an existing dW tensor");
@@ -243,15 +272,16 @@ PyObject* offpolicy_loss_bwd(PyObject* const* a) {
   const at::Tensor ws = workspace(a[10],
                                   chunked ? llamarl_bwd_workspace_bytes(x.N, x.d, x.V, x.dt, rows)
                                           : llamarl_workspace_bytes(x.N, x.d, x.V, x.dt, LLAMARL_PASS_LOSS_BWD), x.H);
-  void* st = stream_of(a[11]);
   check(unlocked([&] {
     return chunked ? llamarl_offpolicy_loss_bwd_chunked(ptr(x.H), ptr(x.W), ptr<int32_t>(x.targets), ptr<float>(lse),
                                                         ptr<float>(coef), grad_loss, x.N, x.d, x.V, x.dt, ptr(dH), ptr(dW), dW_dt,
-                                                        accumulate, rows, ptr(ws), (size_t)ws.numel(), st)
+                                                        accumulate, rows, ptr(ws), (size_t)ws.numel(), st.handle)
                    : llamarl_offpolicy_loss_bwd(ptr(x.H), ptr(x.W), ptr<int32_t>(x.targets), ptr<float>(lse), ptr<float>(coef),
                                                 grad_loss, x.N, x.d, x.V, x.dt, ptr(dH), ptr(dW), dW_dt, accumulate, ptr(ws),
-                                                (size_t)ws.numel(), st);
+                                                (size_t)ws.numel(), st.handle);
   }));
+  if (a[9] == Py_None) st.returns({dH});
+  if (a[7] == Py_None) st.returns({dW});
   return tuple({dH, dW});
 }
 
@@ -261,14 +291,15 @@ PyObject* offpolicy_loss_bwd_slice(PyObject* const* a) {
   const int64_t v0 = integer(a[3]);
   const at::Tensor &lse = needed(a[4], at::kFloat, "lse"), &coef = needed(a[5], at::kFloat, "coef");
   const float grad_loss = (float)real(a[6]);
+  const CallStream st(a[9], x.H);
   const at::Tensor dH = empty(x.H, {x.N, x.d}, x.H.scalar_type()), dW = empty(x.H, {x.V, x.d}, storage(integer(a[7]), x.H));
   const at::Tensor ws = workspace(a[8], llamarl_workspace_bytes(x.N, x.d, x.V, x.dt, LLAMARL_PASS_LOSS_BWD), x.H);
-  void* st = stream_of(a[9]);
   check(unlocked([&] {
     return llamarl_offpolicy_loss_bwd_slice(ptr(x.H), ptr(x.W), ptr<int32_t>(x.targets), ptr<float>(lse), ptr<float>(coef),
                                             grad_loss, x.N, x.d, x.V, v0, x.dt, ptr(dH), ptr(dW), dtype_code(dW), 0, ptr(ws),
-                                            (size_t)ws.numel(), st);
+                                            (size_t)ws.numel(), st.handle);
   }));
+  st.returns({dH, dW});
   return tuple({dH, dW});
 }
 
@@ -282,6 +313,7 @@ PyObject* offpolicy_loss_bwd_device_scale(PyObject* const* a) {
   if (g.numel() != 1) invalid("grad_loss must have one entry");
   const int checked = PyObject_IsTrue(a[8]);
   if (checked < 0) throw Raised{};
+  const CallStream st(a[7], x.H);
   at::Tensor on_host;
   at::cuda::CUDAEvent copied;
   if (checked) {
@@ -291,11 +323,10 @@ PyObject* offpolicy_loss_bwd_device_scale(PyObject* const* a) {
   }
   const at::Tensor dH = empty(x.H, {x.N, x.d}, x.H.scalar_type()), dW = empty(x.H, {x.V, x.d}, storage(integer(a[6]), x.H));
   const at::Tensor ws = workspace(Py_None, llamarl_workspace_bytes(x.N, x.d, x.V, x.dt, LLAMARL_PASS_LOSS_BWD), x.H);
-  void* st = stream_of(a[7]);
   check(unlocked([&] {
     return llamarl_offpolicy_loss_bwd_device_scale(ptr(x.H), ptr(x.W), ptr<int32_t>(x.targets), ptr<float>(lse), ptr<float>(coef),
                                                    ptr<float>(g), x.N, x.d, x.V, x.dt, ptr(dH), ptr(dW), dtype_code(dW), 0,
-                                                   ptr(ws), (size_t)ws.numel(), st);
+                                                   ptr(ws), (size_t)ws.numel(), st.handle);
   }));
   if (checked) {
     {
@@ -304,6 +335,7 @@ PyObject* offpolicy_loss_bwd_device_scale(PyObject* const* a) {
     }
     if (!std::isfinite(*on_host.data_ptr<float>())) invalid("grad_loss must be finite");
   }
+  st.returns({dH, dW});
   return tuple({dH, dW});
 }
 
@@ -315,9 +347,10 @@ PyObject* group_advantages(PyObject* const* a) {
   const int std = PyObject_IsTrue(a[2]);
   if (std < 0) throw Raised{};
   const float eps = (float)real(a[3]);
+  const CallStream st(a[4], r);
   const at::Tensor adv = empty(r, r.sizes());
-  void* st = stream_of(a[4]);
-  check(unlocked([&] { return llamarl_group_advantages(ptr<float>(r), r.numel() / n, n, std, eps, ptr<float>(adv), st); }));
+  check(unlocked([&] { return llamarl_group_advantages(ptr<float>(r), r.numel() / n, n, std, eps, ptr<float>(adv), st.handle); }));
+  st.returns({adv});
   return THPVariable_Wrap(adv);
 }
 
@@ -330,12 +363,13 @@ PyObject* kl_shaped_rewards(PyObject* const* a) {
   if (B <= 0 || logp.numel() % B != 0 || base.numel() != logp.numel() || (mask.defined() && mask.numel() != logp.numel()))
     invalid("logp, base_logp and mask must hold B*T entries");
   const float lambda = (float)real(a[4]);
+  const CallStream st(a[5], r);
   const at::Tensor shaped = empty(r, r.sizes()), kl = empty(r, r.sizes());
-  void* st = stream_of(a[5]);
   check(unlocked([&] {
     return llamarl_kl_shaped_rewards(ptr<float>(r), ptr<float>(logp), ptr<float>(base), ptr<uint8_t>(mask), B, logp.numel() / B,
-                                     lambda, ptr<float>(shaped), ptr<float>(kl), st);
+                                     lambda, ptr<float>(shaped), ptr<float>(kl), st.handle);
   }));
+  st.returns({shaped, kl});
   return tuple({shaped, kl});
 }
 

@@ -52,3 +52,58 @@ def test_callers_buffers_and_streams(lib):
     assert torch.equal(out[1], dH) and torch.equal(out[0], dW)
     for a in (on_current, given):
         assert torch.equal(a[0], logp) and torch.equal(a[1], lse)
+
+
+def _segment_stream(ptr):
+    """stream whose pool the memory at an address belongs to"""
+    for seg in torch.cuda.memory_snapshot():
+        if seg["address"] <= ptr < seg["address"] + seg["total_size"]:
+            return seg["stream"]
+
+
+def test_what_a_call_on_a_given_stream_allocates_is_that_streams(lib):
+    # From the current stream's pool, the workspace would be given to that stream's next allocation while the kernels of the
+    # call still use it.
+    N, d, V = 8192, 64, 60000               # workspaces of 10 MB and more, which the allocator gives a segment of their own
+    H, W, y = _head(N, V, d)
+    s = torch.cuda.Stream()
+    many = torch.zeros(1 << 21, device="cuda")
+    coef = torch.linspace(-1, 1, N, device="cuda")
+    lse = torch.zeros(N, device="cuda")
+    ones = torch.ones(2, N, device="cuda")
+    torch.cuda.synchronize()
+    here = torch.cuda.current_stream().cuda_stream
+    assert s.cuda_stream != here
+    g = torch.ones((), device="cuda")
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(6)]
+    for e in events:
+        e.record()
+    calls = [lambda: lib.token_logprobs(H, W, y, stream=s), lambda: lib.token_logprobs_partial(H, W, y, 0, V, stream=s),
+             lambda: lib.merge_partials(ones, ones, ones, stream=s),
+             lambda: lib.offpolicy_loss_fwd(many, many, many, None, 512, 4096, stream=s),
+             lambda: lib.offpolicy_loss_bwd(H, W, y, lse, coef, stream=s),
+             lambda: lib.offpolicy_loss_bwd(H, W, y, lse, coef, stream=s, max_rows_per_pass=256),
+             lambda: lib.offpolicy_loss_bwd(H, W, y, lse, coef, stream=s, phase_events=[e.cuda_event for e in events]),
+             lambda: lib.offpolicy_loss_bwd_slice(H, W, y, 0, lse, coef, stream=s),
+             lambda: lib.offpolicy_loss_bwd_device_scale(H, W, y, lse, coef, g, stream=s),
+             lambda: (lib.group_advantages(coef, 8, stream=s),), lambda: lib.kl_shaped_rewards(coef, lse, lse, None, 0.1, stream=s)]
+    for call in calls:
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        before = torch.cuda.memory_stats()["reserved_bytes.all.current"]
+        mine = sum(seg["total_size"] for seg in torch.cuda.memory_snapshot() if seg["stream"] == here)
+        out = call()
+        assert all(_segment_stream(t.data_ptr()) == s.cuda_stream for t in out)
+        # nothing, the workspace neither, came out of the current stream's pool
+        assert mine == sum(seg["total_size"] for seg in torch.cuda.memory_snapshot() if seg["stream"] == here)
+        assert torch.cuda.memory_stats()["reserved_bytes.all.current"] > before
+        assert torch.cuda.current_stream().cuda_stream == here
+        torch.cuda.synchronize()
+        del out
+    # the caller's own buffers stay where they are, and the stream is the current one again after an error
+    dW = torch.empty_like(W)
+    assert lib.offpolicy_loss_bwd(H, W, y, lse, coef, dW=dW, stream=s)[1].data_ptr() == dW.data_ptr()
+    with pytest.raises(lib.LlamarlError):
+        lib.token_logprobs(H, W, y, ws=torch.empty(64, dtype=torch.uint8, device="cuda"), stream=s)
+    assert torch.cuda.current_stream().cuda_stream == here
+    torch.cuda.synchronize()
