@@ -159,6 +159,11 @@ def _need(t, dtype, name):
         raise LlamarlError(ERR_INVALID_ARG, "%s must be a contiguous device tensor of %s" % (name, dtype))
 
 
+def _at_least(t, n, name):
+    if t is not None and t.numel() < n:
+        raise LlamarlError(ERR_INVALID_ARG, "%s must have %d entries" % (name, n))
+
+
 def workspace_bytes(N, d, V, dt, which):
     return int(load().llamarl_workspace_bytes(N, d, V, dt, which))
 
@@ -166,6 +171,8 @@ def workspace_bytes(N, d, V, dt, which):
 def _workspace(nbytes, device, ws):
     if ws is None:
         ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=device)
+    elif not (ws.is_cuda or ws.is_pinned()) or not torch.ops.aten.is_non_overlapping_and_dense(ws):
+        raise LlamarlError(ERR_INVALID_ARG, "ws must be a dense device tensor")
     return ws
 
 
@@ -201,6 +208,7 @@ def offpolicy_loss_fwd_static(logp, mu_logp, adv, mask, B, T, loss, coef, stats,
         _need(mask, torch.uint8, "mask")
     if targets is not None:
         _need(targets, torch.int32, "targets")
+    _at_least(mask, N, "mask"); _at_least(targets, N, "targets")
     p = LossParams(float(rho), int(clip_mode), float(eps_lo), float(eps_hi), int(norm_mode))
     _check(lib.llamarl_offpolicy_loss_fwd_static(_ptr(logp), _ptr(mu_logp), _ptr(adv), per_token, _ptr(mask),
                                                  _ptr(targets), int(V), B, T, ctypes.byref(p), _ptr(loss),
@@ -228,6 +236,9 @@ def offpolicy_loss_bwd(H, W, targets, lse, coef, grad_loss=1.0, dW_dtype=None, d
     _need(lse, torch.float32, "lse"); _need(coef, torch.float32, "coef")
     N, d = H.shape
     V = W.shape[0]
+    if W.numel() != V * d:
+        raise LlamarlError(ERR_INVALID_ARG, "shape mismatch between H and W")
+    _at_least(targets, N, "targets"); _at_least(lse, N, "lse"); _at_least(coef, N, "coef")
     if dW is not None:
         dW_dtype = dW.dtype
     if dW_dtype is None:
@@ -244,6 +255,7 @@ def offpolicy_loss_bwd(H, W, targets, lse, coef, grad_loss=1.0, dW_dtype=None, d
             dH.record_stream(current)
         ws = _workspace(workspace_bytes(N, d, V, dt, PASS_LOSS_BWD), H.device, ws)
     _need(dW, dW_dtype, "dW"); _need(dH, H.dtype, "dH")
+    _at_least(dW, V * d, "dW"); _at_least(dH, N * d, "dH")
     ev = (ctypes.c_void_p * 6)(*[ctypes.c_void_p(int(e)) for e in phase_events])
     _check(lib.llamarl_offpolicy_loss_bwd_phases(
         _ptr(H), _ptr(W), _ptr(targets), _ptr(lse), _ptr(coef), float(grad_loss), N, d, V, dt, _ptr(dH), _ptr(dW),

@@ -67,9 +67,17 @@ const at::Tensor& needed(PyObject* o, at::ScalarType dtype, const char* name) {
 at::Tensor empty(const at::Tensor& like, at::IntArrayRef sizes, at::ScalarType dtype = at::kFloat) {
   return at::empty(sizes, like.options().dtype(dtype).requires_grad(false));
 }
+// The kernels take sizes from H and W alone: an array that is too small for them would be read or written past its end.
+void at_least(const at::Tensor& t, int64_t n, const char* name) {
+  if (t.defined() && t.numel() < n) invalid(std::string(name) + " must have " + std::to_string(n) + " entries");
+}
 // the caller's workspace, or one for this call
 at::Tensor workspace(PyObject* o, size_t bytes, const at::Tensor& like) {
-  if (o != Py_None) return tensor(o, "ws");
+  if (o != Py_None) {
+    const at::Tensor& t = tensor(o, "ws");
+    if (!(t.is_cuda() || t.is_pinned()) || !t.is_non_overlapping_and_dense()) invalid("ws must be a dense device tensor");
+    return t;
+  }
   return empty(like, {(int64_t)std::max<size_t>(bytes, 16)}, at::kByte);
 }
 // The stream of a call: the current one (None) or the caller's, which is the current one while the call allocates.  A workspace
@@ -165,6 +173,13 @@ struct Head {          // H [N,d], W [V,d], targets [N]
     if (W.dim() < 2 || W.size(1) != d || targets.numel() != N)
       invalid(std::string("shape mismatch between H, ") + w_name + ", targets");
   }
+  // as the backward takes them
+  void holds(const char* w_name, const at::Tensor& lse, const at::Tensor& coef) const {
+    if (W.numel() != V * d) invalid(std::string("shape mismatch between H and ") + w_name);
+    at_least(targets, N, "targets");
+    at_least(lse, N, "lse");
+    at_least(coef, N, "coef");
+  }
 };
 
 // H, W, targets, mask, ws, stream
@@ -190,6 +205,7 @@ PyObject* token_logprobs_partial(PyObject* const* a) {
   x.same_width("W_slice");
   const int64_t v0 = integer(a[3]), V_total = integer(a[4]);
   const at::Tensor mask = optional(a[5], at::kByte, "mask");
+  at_least(mask, x.N, "mask");
   const CallStream st(a[7], x.H);
   const at::Tensor m = empty(x.H, {x.N}), s = empty(x.H, {x.N}), zt = empty(x.H, {x.N});
   const at::Tensor ws = workspace(a[6], llamarl_workspace_bytes(x.N, x.d, x.V, x.dt, LLAMARL_PASS_LOGPROBS), x.H);
@@ -228,6 +244,7 @@ PyObject* offpolicy_loss_fwd(PyObject* const* a) {
   const at::Tensor mask = optional(a[3], at::kByte, "mask");
   if (mask.defined() && mask.numel() != N) invalid("mask must have B*T entries");
   const at::Tensor targets = optional(a[11], at::kInt, "targets");
+  at_least(targets, N, "targets");
   llamarl_loss_params p;
   p.rho = (float)real(a[6]);
   p.norm_mode = (int)integer(a[7]);
@@ -255,6 +272,7 @@ at::ScalarType storage(int64_t code, const at::Tensor& like) {      // binding's
 PyObject* offpolicy_loss_bwd(PyObject* const* a) {
   const Head x(a[0], a[1], a[2], "W");
   const at::Tensor &lse = needed(a[3], at::kFloat, "lse"), &coef = needed(a[4], at::kFloat, "coef");
+  x.holds("W", lse, coef);
   const float grad_loss = (float)real(a[5]);
   const int accumulate = PyObject_IsTrue(a[8]);
   if (accumulate < 0) throw Raised{};
@@ -267,6 +285,8 @@ PyObject* offpolicy_loss_bwd(PyObject* const* a) {
   const llamarl_dtype dW_dt = dtype_code(dW);
   need(dW, dW.scalar_type(), "dW");
   need(dH, x.H.scalar_type(), "dH");
+  at_least(dW, x.V * x.d, "dW");
+  at_least(dH, x.N * x.d, "dH");
   const bool chunked = a[12] != Py_None;
   const int64_t rows = chunked ? integer(a[12]) : 0;
   const at::Tensor ws = workspace(a[10],
@@ -290,6 +310,7 @@ PyObject* offpolicy_loss_bwd_slice(PyObject* const* a) {
   const Head x(a[0], a[1], a[2], "W_slice");
   const int64_t v0 = integer(a[3]);
   const at::Tensor &lse = needed(a[4], at::kFloat, "lse"), &coef = needed(a[5], at::kFloat, "coef");
+  x.holds("W_slice", lse, coef);
   const float grad_loss = (float)real(a[6]);
   const CallStream st(a[9], x.H);
   const at::Tensor dH = empty(x.H, {x.N, x.d}, x.H.scalar_type()), dW = empty(x.H, {x.V, x.d}, storage(integer(a[7]), x.H));
@@ -311,6 +332,7 @@ PyObject* offpolicy_loss_bwd_device_scale(PyObject* const* a) {
   const at::Tensor &lse = needed(a[3], at::kFloat, "lse"), &coef = needed(a[4], at::kFloat, "coef"),
                    &g = needed(a[5], at::kFloat, "grad_loss");
   if (g.numel() != 1) invalid("grad_loss must have one entry");
+  x.holds("W", lse, coef);
   const int checked = PyObject_IsTrue(a[8]);
   if (checked < 0) throw Raised{};
   const CallStream st(a[7], x.H);

@@ -107,3 +107,42 @@ def test_what_a_call_on_a_given_stream_allocates_is_that_streams(lib):
         lib.token_logprobs(H, W, y, ws=torch.empty(64, dtype=torch.uint8, device="cuda"), stream=s)
     assert torch.cuda.current_stream().cuda_stream == here
     torch.cuda.synchronize()
+
+
+def test_arrays_too_small_for_the_head_are_refused(lib):
+    # the kernels take their sizes from H and W: each of these would be read or written past its end
+    H, W, y = _head()
+    N, d, V = 70, 64, 900
+    f = torch.zeros(N, device="cuda")
+    m = torch.ones(N, dtype=torch.uint8, device="cuda")
+    g = torch.ones((), device="cuda")
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(6)]
+    for e in events:
+        e.record()
+    phases = dict(phase_events=[e.cuda_event for e in events])
+    ws = torch.empty(lib.workspace_bytes(N, d, V, lib.BF16, lib.PASS_LOSS_BWD), dtype=torch.uint8, device="cuda")
+    refused = []
+    for args in [(H, W[:, :32].contiguous(), y, f, f), (H, W, y[:-1], f, f), (H, W, y, f[:-1], f), (H, W, y, f, f[:-1])]:
+        refused += [lambda a=args: lib.offpolicy_loss_bwd(*a), lambda a=args: lib.offpolicy_loss_bwd(*a, **phases),
+                    lambda a=args: lib.offpolicy_loss_bwd(*a, max_rows_per_pass=256),
+                    lambda a=args: lib.offpolicy_loss_bwd_slice(*a[:3], 0, *a[3:]),
+                    lambda a=args: lib.offpolicy_loss_bwd_device_scale(*a, g)]
+    for kw in [dict(dW=W[:-1].clone()), dict(dH=H[:-1].clone()), dict(ws=ws.cpu()), dict(ws=ws[::2]), dict(ws=ws[:1].expand(ws.numel()))]:
+        refused += [lambda k=kw: lib.offpolicy_loss_bwd(H, W, y, f, f, **k), lambda k=kw: lib.offpolicy_loss_bwd(H, W, y, f, f, **k, **phases)]
+    for bad in (ws.cpu(), ws[::2]):
+        refused += [lambda b=bad: lib.token_logprobs(H, W, y, ws=b), lambda b=bad: lib.token_logprobs_partial(H, W, y, 0, V, ws=b),
+                    lambda b=bad: lib.offpolicy_loss_fwd(f, f, f, None, 1, N, ws=b)]
+    refused += [lambda: lib.token_logprobs_partial(H, W, y, 0, V, m[:-1]), lambda: lib.token_logprobs_partial(H, W, y[:-1], 0, V),
+                lambda: lib.offpolicy_loss_fwd(f, f, f, m, 1, N, targets=y[:-1], V=V)]
+    out = f[:1].clone(), f.clone(), torch.zeros(5, device="cuda")
+    refused += [lambda: lib.offpolicy_loss_fwd_static(f, f, f, m[:-1], 1, N, *out),
+                lambda: lib.offpolicy_loss_fwd_static(f, f, f, m, 1, N, *out, targets=y[:-1], V=V)]
+    for i, call in enumerate(refused):
+        with pytest.raises(lib.LlamarlError) as e:
+            call()
+        assert e.value.status == lib.ERR_INVALID_ARG, i
+    # larger ones are taken
+    long = torch.zeros(N + 9, device="cuda")
+    lib.offpolicy_loss_bwd(H, W, torch.cat([y, y[:9]]), long, long, dW=torch.empty(V + 3, d, dtype=W.dtype, device="cuda"),
+                           dH=torch.empty(N + 1, d, dtype=H.dtype, device="cuda"), ws=ws.view(-1, 4).t())
+    torch.cuda.synchronize()
