@@ -411,6 +411,7 @@ struct TileGemm {
   typedef typename TT::frag_t frag_t;
   static constexpr bool KMAJOR = false;
   static constexpr bool HAS_IDLE = true, HALVES = false;
+  static constexpr bool REQUESTS_PAST_K = false;      // slabs past K may be in flight after run(): to be waited for
   static constexpr int BK = 8 * TT::EPC;
   static constexpr int LDS_BYTES = MAINLOOP_LDS_BYTES;
   static constexpr int GROUPS_PER_CU = 1;      // workgroups of a persistent grid per CU
@@ -617,6 +618,7 @@ struct TileGemmNarrow {
   typedef SlabFetch<LoaderA, LoaderB> Fetch;
   static constexpr bool KMAJOR = false;
   static constexpr bool HAS_IDLE = true, HALVES = true;
+  static constexpr bool REQUESTS_PAST_K = true;
   static constexpr int BK = 8 * TT::EPC;
   static constexpr int LDS_BYTES = NARROW_LDS_BYTES;
   static constexpr int FIRST_PARTS = 2;        // see TileGemm::issue_first

@@ -70,6 +70,7 @@ struct TileGemmSmall {
   typedef SlabLoader<TT, S::BN, S::WAVES, S::WAVE_N> LoaderB;
   static constexpr bool KMAJOR = false;
   static constexpr bool HAS_IDLE = false, HALVES = false;
+  static constexpr bool REQUESTS_PAST_K = true;
   static constexpr int BK = 8 * TT::EPC;
   static constexpr int LDS_BYTES = NSTAGE * S::STAGE_BYTES + 16;     // + a flag (fp32: redo this tile)
   static constexpr int GROUPS_PER_CU = GROUPS_PER_CU_;

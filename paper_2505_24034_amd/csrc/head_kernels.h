@@ -330,7 +330,7 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a, G& g, TileSchedule<P
     int ytok[nb > 0 ? nb : 1];
 #pragma unroll
     for (int j = 0; j < nb; ++j) ytok[j] = Words::template word<int>(words, 1, lp.col(j));
-    if constexpr (G::HALVES) wait_vmcnt0();             // slabs past K must not land in what is written next
+    if constexpr (G::REQUESTS_PAST_K) wait_vmcnt0();    // they must not land in what is fetched or written next
     __syncthreads();                                 // every wave is done reading the slab buffers and the token words
     LLAMARL_FENCE();
     if (!last) {                                     // start the next tile's first slabs; the epilogue hides them
@@ -804,7 +804,7 @@ __device__ __forceinline__ void dz_tiles(const DzArgs& a, G& g, TileSchedule<PAT
       tlse[j] = Words::template word<float>(words, 2, tok);
       tcoef[j] = Words::template word<float>(words, 3, tok);
     }
-    if constexpr (G::HALVES) wait_vmcnt0();             // slabs past K must not land in what is written next
+    if constexpr (G::REQUESTS_PAST_K) wait_vmcnt0();    // they must not land in what is fetched or written next
     __syncthreads();                                 // every wave is done reading the slab buffers and the token words
     LLAMARL_FENCE();
     if (!last) {                                     // the epilogue uses no LDS: fetch the next tile under it

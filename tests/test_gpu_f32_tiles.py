@@ -95,6 +95,12 @@ def test_values_that_cannot_be_split(lib, N, V, d):
     assert float((lse2[ok].double() - rlse[ok]).abs().max()) <= 2e-5
 
 
+def test_every_tile_contracted_twice(lib):
+    # 1105 tiles of 128, two or three a workgroup, and in each a value that cannot be split: the slabs that the second pass of a
+    # tile requests past K have to have landed before the next tile's first
+    test_values_that_cannot_be_split(lib, 2100, 8200, 40)
+
+
 def _no_smaller_than(x, low):
     """x with every magnitude below `low` replaced by one in [low, 2 low) of as many bits"""
     small = x.abs() < low
