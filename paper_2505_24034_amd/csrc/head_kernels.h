@@ -37,10 +37,8 @@ __host__ __device__ __forceinline__ int64_t packed_pitch(int64_t n_rows) {
   const int64_t p = (n_rows + 63) / 64;
   return ((p & 1) ? p : p + 1) * 64;
 }
-// Patch rows (TileSchedule::init).  Measured at the Llama-3-8B shape with patches dealt round-robin over the XCDs:
-// logits kernels 4 and 8 tie (2: +1 %); dW 8 (4: +1.6 %, 2: +5 %); dH: see PATCH_ROWS_KMAJOR.
 constexpr int STORE_LOAD_SLOT = 9;      // first slab-load slot of the K-contiguous store contraction (see k_step)
-constexpr int PATCH_ROWS_LOGITS = 4;
+// Patch rows of dW (see PATCH_ROWS_LOGITS): 8 (4: +1.6 %, 2: +5 %); dH: see PATCH_ROWS_KMAJOR.
 constexpr int PATCH_ROWS_STORE = 8;
 // dH on k-major operands, whole tiles of K = V, when the output is at most 16 tiles wide (d <= 4096): 16 x 2
 // patches (8 x 4: +0.8 %, 4 x 8: +1.7 %).  Wider outputs (d = 8192, 16384) keep 8 x 4 (16 x 2: +2 - 3 % there).
@@ -448,14 +446,14 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
     if (half < 8) {
       LogitsNarrow g;
       g.nb1 = half;
-      sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width());
+      sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
       if (!sch.has_tile()) return;
       with_blocks(g, [&](auto blocks) { fwd_tiles<LogitsNarrow, decltype(blocks)::value>(a, g, sch, n_act, smem); });
       return;
     }
   }
   G g;
-  sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width());             // token tiles that hold active rows only
+  sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);             // token tiles that hold active rows only
   if (!sch.has_tile()) return;                       // block-uniform
   fwd_tiles<G, G::Shape::NB>(a, g, sch, n_act, smem);
 }
@@ -953,14 +951,14 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzAr
     if (half < 8) {
       LogitsNarrow g;
       g.nb1 = half;
-      sch.init(a.tiles_v, (n_read + g.width() - 1) / g.width());
+      sch.init(a.tiles_v, (n_read + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
       if (!sch.has_tile()) return;
       with_blocks(g, [&](auto blocks) { dz_tiles<LogitsNarrow, decltype(blocks)::value>(a, g, sch, n_act, smem); });
       return;
     }
   }
   G g;
-  sch.init(a.tiles_v, (n_read + g.width() - 1) / g.width());
+  sch.init(a.tiles_v, (n_read + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
   if (!sch.has_tile()) return;                       // block-uniform: no active token at all
   dz_tiles<G, G::Shape::NB>(a, g, sch, n_act, smem);
 }

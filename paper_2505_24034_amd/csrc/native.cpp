@@ -20,6 +20,7 @@
 #include <optional>
 
 #include "../../include/llamarl.h"
+#include "tile_rules.h"
 
 namespace {
 
@@ -395,6 +396,33 @@ PyObject* kl_shaped_rewards(PyObject* const* a) {
   return tuple({shaped, kl});
 }
 
+// The rules by which the library cuts and deals out its work (tile_rules.h), for tests.
+// tiles_m, tiles_n, workgroups: the tiles (row * tiles_n + column) each workgroup of a logits kernel takes, in order
+PyObject* tile_walk(PyObject* const* a) {
+  const int tiles_m = (int)integer(a[0]), tiles_n = (int)integer(a[1]), workgroups = (int)integer(a[2]);
+  PyObject* out = PyList_New(0);
+  if (out == nullptr) throw Raised{};
+  for (int b = 0; b < workgroups; ++b) {
+    PyObject* walk = PyList_New(0);
+    llamarl::TileSchedule<llamarl::PATCH_ROWS_LOGITS> sch;
+    sch.init(tiles_m, tiles_n, b, workgroups);
+    while (walk != nullptr && sch.has_tile()) {
+      int tm, tn;
+      sch.take(tm, tn);
+      PyObject* id = PyLong_FromLongLong((int64_t)tm * tiles_n + tn);
+      if (id == nullptr || PyList_Append(walk, id) != 0) Py_CLEAR(walk);
+      Py_XDECREF(id);
+    }
+    const bool failed = walk == nullptr || PyList_Append(out, walk) != 0;
+    Py_XDECREF(walk);
+    if (failed) {
+      Py_DECREF(out);
+      throw Raised{};
+    }
+  }
+  return out;
+}
+
 template <PyObject* (*F)(PyObject* const*), int NARGS>
 PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
   HANDLE_TH_ERRORS
@@ -421,7 +449,7 @@ PyObject* set_error(PyObject*, PyObject* cls) {
 PyMethodDef g_methods[] = {
     ENTRY(token_logprobs, 6), ENTRY(token_logprobs_partial, 8), ENTRY(merge_partials, 4), ENTRY(offpolicy_loss_fwd, 15),
     ENTRY(offpolicy_loss_bwd, 13), ENTRY(offpolicy_loss_bwd_slice, 10), ENTRY(offpolicy_loss_bwd_device_scale, 9),
-    ENTRY(group_advantages, 5), ENTRY(kl_shaped_rewards, 6), {"set_error", set_error, METH_O, nullptr},
+    ENTRY(group_advantages, 5), ENTRY(kl_shaped_rewards, 6), ENTRY(tile_walk, 3), {"set_error", set_error, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};
 

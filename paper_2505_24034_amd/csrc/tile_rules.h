@@ -1,0 +1,85 @@
+// tile_rules.h -- which tiles a contraction is cut into and who takes which: plain arithmetic, the same in the kernels, in the
+// host code that launches them and in native.cpp, through which the tests ask for it without a GPU.
+#pragma once
+#include <stdint.h>
+
+#ifdef __HIP__
+#define LLAMARL_RULE __host__ __device__ __forceinline__
+#else
+#define LLAMARL_RULE inline
+#endif
+
+namespace llamarl {
+
+// Patch rows of the logits kernels (TileSchedule::init), measured at the Llama-3-8B shape with patches dealt round-robin over
+// the XCDs: 4 and 8 tie (2: +1 %).
+constexpr int PATCH_ROWS_LOGITS = 4;
+
+// Persistent tile schedule.  The grid has one workgroup per CU (every tile is taken once by a grid of any size; tests/
+// test_tile_rules.py walks them on the CPU); the hardware deals workgroups
+// round-robin to the 8 XCDs, each with a private L2.  Tile ids are ordered so that 32 consecutive ones form a patch
+// (group_m x 32/group_m tiles) that shares A and B panels; the workgroups of one XCD take one patch at a time, so
+// those panels are shared in its L2, and the eight patches in flight on the chip are consecutive in id order, so
+// they share panels through the Infinity Cache (against giving every XCD a contiguous eighth of the ids: -3.5 %
+// step time, -6.5 % for the dH contraction whose two operands both stream from HBM).  tiles_m x tiles_n is the
+// number of tiles that exist once the device-side active-row count is known.
+template <int GROUP_M>     // rows of a patch
+struct TileSchedule {
+  int tiles_m, tiles_n;
+  int next_id, end_id, stride;
+  bool turn;               // see take
+  int group, in_group;     // of next_id: its group of GROUP_M rows of tiles, and its place there
+  int group_step, in_group_step, round;
+  // The 32 workgroups of an XCD work on 32 consecutive ids = GROUP_M x (32 / GROUP_M)
+  // tiles, which load GROUP_M A panels and 32 / GROUP_M B panels: a B panel is shared by GROUP_M tiles, an A panel
+  // by 32 / GROUP_M.  Give the larger share to the operand that has to come from HBM.
+  LLAMARL_RULE void init(int tiles_m_, int tiles_n_, int bid, int nblk) {
+    tiles_m = tiles_m_;
+    tiles_n = tiles_n_;
+    const int ntiles = tiles_m * tiles_n;
+    const int xcd = bid & 7, local = bid >> 3;
+    turn = (nblk & 7) == 0 && nblk % (GROUP_M * tiles_n) == 0;
+    if ((nblk & 7) == 0 || nblk < 8) {
+      // Patches dealt round-robin over the XCDs: in round k XCD x works on patch 8 k + x, so the eight patches in
+      // flight are neighbours in id order and share operand panels through the Infinity Cache.
+      const int per = nblk >> 3;                            // workgroups per XCD = tiles per patch
+      next_id = nblk < 8 ? bid : xcd * per + local;         // few: not every XCD has a workgroup
+      stride = nblk;
+      end_id = ntiles;
+    } else {
+      const int base = ntiles >> 3, rem = ntiles & 7;
+      const int start = xcd * base + (xcd < rem ? xcd : rem);
+      end_id = start + base + (xcd < rem ? 1 : 0);
+      next_id = start + local;
+      stride = (nblk >> 3) + ((nblk & 7) > xcd ? 1 : 0);    // workgroups of this grid that sit on my XCD
+    }
+    const int per_group = GROUP_M * tiles_n;
+    group = next_id / per_group;
+    in_group = next_id - group * per_group;
+    group_step = stride / per_group;
+    in_group_step = stride - group_step * per_group;
+    round = 0;
+  }
+  LLAMARL_RULE bool has_tile() const { return next_id < end_id; }
+  // coordinates of the next tile; advance.  No division while the group is whole: this stands in every tile's epilogue.
+  LLAMARL_RULE void take(int& tm, int& tn) {
+    const int first_m = group * GROUP_M, left = tiles_m - first_m, gsize = left < GROUP_M ? left : GROUP_M;
+    tn = gsize == GROUP_M ? in_group / GROUP_M : in_group / gsize;
+    tm = first_m + in_group - tn * gsize;
+    // Where a round of the grid is a whole number of groups, a workgroup would get the same column in every round:
+    // turn the columns by one a round (a whole group is in one round, so each of its tiles is still taken once), so that nobody is left with all the narrow last columns (two columns, 300
+    // tokens: half of the workgroups had four full tiles, the other half four of 44 tokens).
+    if (turn) tn = (tn + round) % tiles_n;
+    ++round;
+    next_id += stride;
+    group += group_step;
+    in_group += in_group_step;
+    const int per_group = GROUP_M * tiles_n;
+    if (in_group >= per_group) {
+      in_group -= per_group;
+      ++group;
+    }
+  }
+};
+
+}  // namespace llamarl
