@@ -93,7 +93,6 @@ struct FwdArgs {
   float* part_s;          // [tiles_v][n_pad] sum of exp(logit - max)
   float* zt;              // [n_pad] target logit, written by the one tile that holds vocab row y_t
   const int32_t* rows;    // [n_act] active token rows, ascending: position p of the compacted list is token rows[p]
-  int64_t list_stride;    // rows + list_stride: their targets
   const int32_t* n_act;   // device scalar
 };  // partials and zt are indexed by compacted position, not by token
 
@@ -153,9 +152,10 @@ struct LogitsTile {
     asm volatile("" : "+s"(tv), "+s"(tt));           // divided out here, under an epilogue, not where they are used
   }
 };
-// What a tile of the logits kernels needs per token is in list order in memory (compact_rows) and goes through LDS: the
-// words of the tile's BN list positions from t0 on, of each of LISTS lists, fetched with the tile's first slabs and there
-// when its main loop starts: no global load stands between two tiles.  Loaded at the boundary, through the row list, they
+// What a tile of the logits kernels needs per token goes through LDS, a word a list position: list 0 the token rows of the
+// NEXT tile's columns, further lists this tile's words out of arrays by token (targets; lse, coef), fetched with the tile's first
+// slabs -- their rows came with the tile before -- and there when its main loop starts: no global load stands between two
+// tiles.  Loaded at the boundary, through the row list, they
 // were two dependent trips to memory; with accumulators that are not cleared, requests spread over the epilogue and no
 // wait but the loop's own, a tile of 10188 tokens x 128256 entries takes 1.1 - 2 us less (forward / dz: d = 256 900 / 1015
 // -> 817 / 909 us, 696 1945 / 1970 -> 1785 / 1830, 1024 2240 / 2388 -> 2128 / 2277, 4096 -0.7 / -0.4 %).
@@ -163,19 +163,24 @@ struct LogitsTile {
 template <typename S, int LISTS>
 struct TokenWords {
   static constexpr int PIECES = S::BN / 64, BYTES = LISTS * S::BN * 4;     // a wavefront fetches 64 words at a time
-  // rows: list 0 (the row list), the others `stride` entries after one another; next, cur: first positions of the next
-  // tile, whose rows are fetched, and of this one
-  __device__ __forceinline__ static void fetch(const int32_t* rows, int64_t stride, int next, int cur, int n_act, char* lds) {
-    const int wave = wave_id(), lane = threadIdx.x & 63;
+  static_assert(S::WAVES % PIECES == 0, "all pieces of a wavefront are of the same 64 positions");
+  __device__ __forceinline__ static int position() { return wave_id() % PIECES * 64 + (int)(threadIdx.x & 63); }
+  // rows: the row list; next: first position of the next tile; row: the token row of this lane's position of this tile;
+  // by_token: the arrays of lists 1 .., N words each
+  __device__ __forceinline__ static void fetch(const int32_t* rows, int next, int n_act, int row,
+                                               const void* const (&by_token)[LISTS - 1], int64_t N, char* lds) {
+    const int wave = wave_id();
 #pragma unroll
     for (int i = 0; i < (LISTS * PIECES + S::WAVES - 1) / S::WAVES; ++i) {
       const int piece = i * S::WAVES + wave, l = piece / PIECES;
       if (LISTS * PIECES % S::WAVES != 0 && piece >= LISTS * PIECES) break;      // wave-uniform
-      const uint64_t base = reinterpret_cast<uint64_t>(rows + l * stride);
-      const int first = (l == 0 ? next : cur) + piece % PIECES * 64;
+      uint64_t base = reinterpret_cast<uint64_t>(rows);
+#pragma unroll
+      for (int q = 1; q < LISTS; ++q) base = l == q ? reinterpret_cast<uint64_t>(by_token[q - 1]) : base;
       const i32x4_t rs = {__builtin_amdgcn_readfirstlane((int)(uint32_t)base),
-                          __builtin_amdgcn_readfirstlane((int)((uint32_t)(base >> 32) & 0xffffu)), n_act * 4, 0x00020000};
-      lds_dma4(lds_address(lds) + (uint32_t)piece * 256u, (uint32_t)min(first + lane, n_act - 1) * 4u, rs);
+                          __builtin_amdgcn_readfirstlane((int)((uint32_t)(base >> 32) & 0xffffu)),
+                          __builtin_amdgcn_readfirstlane((l == 0 ? n_act : (int)N) * 4), 0x00020000};
+      lds_dma4(lds_address(lds) + (uint32_t)piece * 256u, (uint32_t)(l == 0 ? min(next + position(), n_act - 1) : row) * 4u, rs);
     }
   }
   template <typename V>
@@ -302,13 +307,15 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a, G& g, TileSchedule<P
   cur.take(sch);
   int grow[decltype(g.lb)::ITERS];
   gather_rows_of_first<false>(g, a, cur, n_act, grow);
+  const int first_row = a.rows[min(cur.tt * width + Words::position(), n_act - 1)];
   logits_setup<false>(g, a, cur, n_act, grow);
 #pragma unroll
   for (int q = 0; q < G::FIRST_PARTS; ++q) issue_first<G, nb>(g, smem, q);
   bool more = sch.has_tile();
   next = cur;
   if (more) next.take(sch);
-  Words::fetch(a.rows, a.list_stride, next.tt * width, cur.tt * width, n_act, words);
+  const void* const by_token[] = {a.targets};
+  Words::fetch(a.rows, next.tt * width, n_act, first_row, by_token, a.N, words);
   bool counted = false;
   while (true) {
     f32x4_t acc[MB][nb > 0 ? nb : 1];
@@ -325,6 +332,7 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a, G& g, TileSchedule<P
     const int rowsT = min(width, n_act - tt * width);
     const bool last = !more;
     gather_rows<false>(g, words, grow);
+    const int word_row = Words::template word<int>(words, 0, Words::position());
     int ytok[nb > 0 ? nb : 1];
 #pragma unroll
     for (int j = 0; j < nb; ++j) ytok[j] = Words::template word<int>(words, 1, lp.col(j));
@@ -337,7 +345,7 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a, G& g, TileSchedule<P
       issue_first<G, nb>(g, smem, 0);
       more = sch.has_tile();
       if (more) next.take(sch);
-      Words::fetch(a.rows, a.list_stride, next.tt * width, cur.tt * width, n_act, words);
+      Words::fetch(a.rows, next.tt * width, n_act, word_row, by_token, a.N, words);
     }
     // From here to the next main loop nothing may wait on vmcnt: the counter is in order, so a wait for any load
     // (or spill reload) issued before the slab requests turns into a wait for the requests themselves, and the
@@ -608,10 +616,6 @@ struct CompactArgs {
   int aligned;               // targets / coef 16-byte, mask 4-byte aligned
   int32_t* rows;
   int32_t* n_act;
-  int32_t* row_targets;      // targets of the listed rows
-  const float* lse;          // mode 1: lse and coef of the listed rows as well
-  float* row_lse;
-  float* row_coef;
   float* out0;
   float* out1;
   float* out2;
@@ -670,17 +674,6 @@ __device__ __forceinline__ void compact_rows(const CompactArgs& a, int block, in
   const int64_t first = (int64_t)block * COMPACT_BLOCK_ROWS, t0 = first + 4 * tid;
   float top = 0.f;
   const uint32_t act = t0 < a.N ? active_rows4(a, t0, top) : 0u;
-  int y4[4];                                        // on their way while the rows in front are counted
-  float c4[4], l4[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (act >> i & 1u) {
-      y4[i] = a.targets[t0 + i];
-      if (a.mode == 1) {
-        c4[i] = a.coef[t0 + i];
-        l4[i] = a.lse[t0 + i];
-      }
-    }
   int front = 0;
 #pragma unroll 4
   for (int64_t t = 4 * tid; t < first; t += COMPACT_BLOCK_ROWS) front += __popc(active_rows4(a, t, top));
@@ -722,15 +715,7 @@ __device__ __forceinline__ void compact_rows(const CompactArgs& a, int block, in
   int at = base + upto - own;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
-    if (act >> i & 1u) {
-      a.rows[at] = (int32_t)(t0 + i);
-      a.row_targets[at] = y4[i];
-      if (a.mode == 1) {
-        a.row_coef[at] = c4[i];
-        a.row_lse[at] = l4[i];
-      }
-      ++at;
-    }
+    if (act >> i & 1u) a.rows[at++] = (int32_t)(t0 + i);
   if (tid == 0 && last) {
     *a.n_act = total;
     if (a.dz_scale != nullptr) {
@@ -744,6 +729,9 @@ __global__ __launch_bounds__(COMPACT_THREADS) void k_compact_rows(CompactArgs a)
 struct DzArgs {
   const void* H;
   const void* W;
+  const int32_t* targets;
+  const float* lse;
+  const float* coef;
   float g;
   const float* g_device;  // non-null: the upstream scalar is *g_device instead of g
   const float* dz_scale;  // fp32: dz is stored times this (dz_scale_for)
@@ -754,7 +742,6 @@ struct DzArgs {
   int64_t ldz;
   void* dzt;    // [V][packed_pitch(n_act)] vocab-major; columns past the active rows written as zero
   const int32_t* rows;    // active token rows (coef != 0), ascending; dz / dzt are indexed by list position
-  int64_t list_stride;    // rows + 1, 2, 3 list_stride: their targets, lse and coef
   const int32_t* n_act;
 };
 template <typename G, int nb>
@@ -774,13 +761,15 @@ __device__ __forceinline__ void dz_tiles(const DzArgs& a, G& g, TileSchedule<PAT
   cur.take(sch);
   int grow[decltype(g.lb)::ITERS];
   gather_rows_of_first<true>(g, a, cur, n_act, grow);
+  const int first_row = a.rows[min(cur.tt * width + Words::position(), n_act - 1)];
   logits_setup<true>(g, a, cur, n_act, grow);
 #pragma unroll
   for (int q = 0; q < G::FIRST_PARTS; ++q) issue_first<G, nb>(g, smem, q);
   bool more = sch.has_tile();
   next = cur;
   if (more) next.take(sch);
-  Words::fetch(a.rows, a.list_stride, next.tt * width, cur.tt * width, n_act, words);
+  const void* const by_token[] = {a.targets, a.lse, a.coef};
+  Words::fetch(a.rows, next.tt * width, n_act, first_row, by_token, a.N, words);
   while (true) {
     f32x4_t acc[MB][nb > 0 ? nb : 1];
     run_tile<G, nb>(g, smem, acc, S::wave_col(wave_id()) * S::WAVE_N >= n_act - cur.tt * width);
@@ -793,6 +782,7 @@ __device__ __forceinline__ void dz_tiles(const DzArgs& a, G& g, TileSchedule<PAT
     const int rowsT = min(width, n_act - tt * width), tok0 = lp.col_near(nb);
     const bool last = !more;
     gather_rows<true>(g, words, grow);
+    const int word_row = Words::template word<int>(words, 0, Words::position());
     float tcoef[nb > 0 ? nb : 1], tlse[nb > 0 ? nb : 1];
     int ttgt[nb > 0 ? nb : 1];
 #pragma unroll
@@ -811,7 +801,7 @@ __device__ __forceinline__ void dz_tiles(const DzArgs& a, G& g, TileSchedule<PAT
       issue_first<G, nb>(g, smem, 0);
       more = sch.has_tile();
       if (more) next.take(sch);
-      Words::fetch(a.rows, a.list_stride, next.tt * width, cur.tt * width, n_act, words);
+      Words::fetch(a.rows, next.tt * width, n_act, word_row, by_token, a.N, words);
     }
     LLAMARL_FENCE();                                 // nothing may wait on vmcnt from here on: see k_fwd_partials
 
@@ -983,6 +973,7 @@ struct StoreArgs {
   int group_m;              // rows of a 32-tile patch (see TileSchedule)
   int width, nb1;           // columns of a tile; column blocks of its right half (TileGemm)
   int max_splits;           // the tiles of the last, partial round may be split this many ways along K (1: never)
+  int max_parts;            // blocks that `part` has room for
   float* part;              // [splits][tail tiles][tile] fp32 partial products of split tiles
   int32_t* plan_out;        // [4] {whole, rem, splits, tiles_m}: what k_reduce_tail has to finish
 };
@@ -1011,7 +1002,7 @@ struct StorePlan {
   int full, last;      // items of whole rounds; this workgroup's item of the last one
   int next, stride;
   // part_cost: what writing one part's fp32 block and reading it back costs, in 1/256 of a slab of the whole grid
-  __device__ __forceinline__ void init(int tiles_m_, int tiles_n_, int group_m_, int nk, int max_splits, int part_cost) {
+  __device__ __forceinline__ void init(int tiles_m_, int tiles_n_, int group_m_, int nk, int max_splits, int max_parts, int part_cost) {
     tiles_m = tiles_m_;
     tiles_n = tiles_n_;
     group_m = group_m_;
@@ -1020,7 +1011,7 @@ struct StorePlan {
     rem = T - whole;
     // split factor of the tail: the one that makes the tail shortest -- ceil(rem s / G) rounds of nk / s slabs each, the
     // traffic of the rem s partial blocks and the reduction's launch -- among those that keep four K slabs per part
-    // and at most STORE_TAIL_ROUNDS rounds of parts; the smallest such factor on ties.  Counting rounds alone cut the
+    // and at most STORE_TAIL_ROUNDS rounds of parts, for which the workspace has room; the smallest such factor on ties.  Counting rounds alone cut the
     // dW of (N, V, d) = (7000, 33001, 1032) into 931 parts (0.5 GB of blocks): 515 us
     // instead of 487; (3000, 60000, 1504) 545 instead of 485, (4000, 128256, 2560) 2022 instead of 1944.
     // One factor a lane, cost and factor in one word: 31 factors one after the other, two divisions each, took 6 us.
@@ -1028,7 +1019,8 @@ struct StorePlan {
     const int rounds = (rem * sp + G - 1) / G;
     // nk < 2^16 (a 256-row panel is < 2 GiB): costs are below 2^26
     const unsigned cost = sp == 1 ? nk * 256 : rounds * nk * 256 / sp + rem * sp * part_cost + STORE_REDUCE_COST;
-    unsigned best = sp == 1 || (sp <= max_splits && nk / sp >= 4 && rounds <= STORE_TAIL_ROUNDS) ? cost * 32 + (sp - 1) : ~0u;
+    unsigned best = sp == 1 || (sp <= max_splits && nk / sp >= 4 && rounds <= STORE_TAIL_ROUNDS &&
+                                      rem * sp <= max_parts) ? cost * 32 + (sp - 1) : ~0u;
 #pragma unroll
     for (int m = 16; m > 0; m >>= 1) best = min(best, (unsigned)__shfl_xor((int)best, m));
     splits = rem > 0 ? __builtin_amdgcn_readfirstlane((int)(best & 31)) + 1 : 1;
@@ -1329,7 +1321,7 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
   const StoreStrides ld{a.packed_a ? pitch : a.lda, a.packed_b ? pitch : a.ldb};
   const int tiles_m = (int)((M + BM - 1) / BM);
   StorePlan plan;
-  plan.init(tiles_m, a.tiles_n, a.group_m, (int)((K + BK - 1) / BK), a.max_splits, STORE_PART_COST<G>);
+  plan.init(tiles_m, a.tiles_n, a.group_m, (int)((K + BK - 1) / BK), a.max_splits, a.max_parts, STORE_PART_COST<G>);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.plan_out[0] = plan.whole; a.plan_out[1] = plan.rem; a.plan_out[2] = plan.splits; a.plan_out[3] = tiles_m;
   }

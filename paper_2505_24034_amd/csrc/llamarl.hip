@@ -102,7 +102,7 @@ typedef TileGemmSmall<F32, Shape64, 4, 2> F32Loop64;
 struct FwdWs {
   int tiles_v;
   int64_t n_pad;
-  size_t off_m, off_s, off_zt, off_rows, off_tgt, off_nact, total;
+  size_t off_m, off_s, off_zt, off_rows, off_nact, total;
 };
 FwdWs fwd_ws(int64_t N, int64_t d, int64_t V, llamarl_dtype dt) {
   FwdWs w;
@@ -121,8 +121,7 @@ FwdWs fwd_ws(int64_t N, int64_t d, int64_t V, llamarl_dtype dt) {
   w.off_s = round_up((int64_t)plane, 256);
   w.off_zt = w.off_s + round_up((int64_t)plane, 256);
   w.off_rows = w.off_zt + (size_t)round_up(w.n_pad * (int64_t)sizeof(float), 256);
-  w.off_tgt = w.off_rows + (size_t)round_up(w.n_pad * (int64_t)sizeof(int32_t), 256);
-  w.off_nact = w.off_tgt + (size_t)round_up(w.n_pad * (int64_t)sizeof(int32_t), 256);
+  w.off_nact = w.off_rows + (size_t)round_up(w.n_pad * (int64_t)sizeof(int32_t), 256);
   w.total = w.off_nact + 256;
   return w;
 }
@@ -165,8 +164,7 @@ struct BwdWs {
                       // partials are sized for R rows; more active rows than that are taken in further passes
   int n_pass;         // passes the host enqueues = ceil(N / R); passes past the active rows find nothing to do
   int64_t ldz, ldzt;  // padded leading dimensions (elements): V rounded up to 64; packed_pitch(R)
-  size_t off_dz, off_dzt, off_wt, off_ht, off_rows, off_words, off_nact, off_plan, off_part, total;
-  int64_t n_list;     // entries of the row list and of each of the three lists of per-row words
+  size_t off_dz, off_dzt, off_wt, off_ht, off_rows, off_nact, off_plan, off_part, part, total;
 };
 // Most workgroups a persistent grid has (one per CU of an MI355X); also the most split items the last round of a
 // store contraction can hold, each leaving one BM x BN fp32 block in the workspace.
@@ -186,22 +184,25 @@ BwdWs bwd_ws(int64_t N, int64_t d, int64_t V, llamarl_dtype dt, int64_t max_rows
   w.off_wt = w.off_dzt + (size_t)round_up(V * w.ldzt * (int64_t)es, 256);
   w.off_ht = w.off_wt + (both ? (size_t)round_up(d * w.ldz * (int64_t)es, 256) : 0);
   w.off_rows = w.off_ht + (size_t)round_up(d * w.ldzt * (int64_t)es, 256);
-  w.n_list = round_up(N, 64);
-  w.off_words = w.off_rows + (size_t)(w.n_list * (int64_t)sizeof(int32_t));
-  w.off_nact = w.off_words + (size_t)(3 * w.n_list * (int64_t)sizeof(int32_t));
+  w.off_nact = w.off_rows + (size_t)round_up(round_up(N, 64) * (int64_t)sizeof(int32_t), 256);
   w.off_plan = w.off_nact + (size_t)round_up((int64_t)(1 + w.n_pass) * (int64_t)sizeof(int32_t), 256);
   w.off_part = w.off_plan + 256;
-  // fp32 partial blocks of the split tiles at the end of a store contraction (see StorePlan): at most
-  // STORE_TAIL_ROUNDS per workgroup of the grid, and never more than STORE_MAX_SPLITS per tile
+  // fp32 partial blocks of the split tiles at the end of a store contraction (see StorePlan): STORE_TAIL_ROUNDS per workgroup of
+  // the grid at most, and room for RESERVED_SPLITS per tile.  A tile is cut into more parts where the room, which is the
+  // larger of the two contractions', allows it (StoreArgs::max_parts): few tokens against a long vocabulary, where dW's many
+  // tiles have reserved it.  Reserving 32 a tile would make it four times as large for small heads, whose K is too short
+  // for them.
+  constexpr int RESERVED_SPLITS = 8;
   auto part_bytes = [&](int64_t M, int64_t edge) {
     const int64_t grid = (int64_t)MAX_GRID * (edge == 256 ? 1 : 2);
-    return std::min(STORE_TAIL_ROUNDS * grid, tile_count(M, d, edge) * STORE_MAX_SPLITS) * edge * edge * 4;
+    return std::min(STORE_TAIL_ROUNDS * grid, tile_count(M, d, edge) * RESERVED_SPLITS) * edge * edge * 4;
   };
   // passes of different lengths may run on different tiles: room for any
   int64_t part = 0;
   for (const int64_t M : {w.R, V})
     for (const int64_t edge : {256, 128, 64})
       if (edge != 256 || dt == LLAMARL_BF16) part = std::max(part, part_bytes(M, edge));
+  w.part = (size_t)part;
   w.total = w.off_part + (size_t)part;
   return w;
 }
@@ -297,7 +298,7 @@ int store_width(int64_t Nn) {
 template <typename G>
 llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t M, int64_t Nn,
                                  int64_t K, void* C, int64_t ldc, int c_is_f32, int accumulate, const int32_t* m_count,
-                                 const int32_t* k_count, const int32_t* c_rows, float* ws_part, int32_t* ws_plan,
+                                 const int32_t* k_count, const int32_t* c_rows, float* ws_part, size_t part_bytes, int32_t* ws_plan,
                                  const int32_t* pitch_count, int packed_a, int packed_b, const float* a_scale, hipStream_t st) {
   // the store epilogue of the K-contiguous loop writes four neighbouring columns per lane as one unit, and so
   // does the tail reduction
@@ -305,7 +306,9 @@ llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int6
     return fail(LLAMARL_ERR_UNSUPPORTED, "output columns and row stride must be multiples of 4");
   StoreArgs a;
   a.m_count = m_count; a.k_count = k_count; a.c_rows = c_rows;
-  a.max_splits = STORE_MAX_SPLITS; a.part = ws_part; a.plan_out = ws_plan;
+  a.max_splits = STORE_MAX_SPLITS; a.part = ws_part;
+  a.max_parts = (int)(part_bytes / (G::Shape::BM * G::Shape::BN * 4));
+  a.plan_out = ws_plan;
 
   a.pitch_count = pitch_count; a.packed_a = packed_a; a.packed_b = packed_b;
   a.A = A; a.a_scale = a_scale; a.lda = lda; a.B = B; a.ldb = ldb; a.M = M; a.Nn = Nn; a.K = K;
@@ -333,7 +336,7 @@ llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int6
 }
 
 CompactArgs compact_args(CompactArgs a) {
-  a.aligned = (a.mode == 1 || aligned16(a.targets)) && aligned16(a.coef) && (reinterpret_cast<uintptr_t>(a.mask) & 3u) == 0;
+  a.aligned = aligned16(a.targets) && aligned16(a.coef) && (reinterpret_cast<uintptr_t>(a.mask) & 3u) == 0;
   return a;
 }
 int compact_blocks(int64_t N) { return (int)((N + COMPACT_BLOCK_ROWS - 1) / COMPACT_BLOCK_ROWS); }
@@ -369,19 +372,18 @@ llamarl_status run_logprobs(const void* H, const void* W, const int32_t* targets
   constexpr llamarl_dtype dt = sizeof(typename TT::store_t) == 2 ? LLAMARL_BF16 : LLAMARL_F32;
   const FwdWs w = fwd_ws(N, d, V, dt);
   FwdArgs a;
-  a.H = H; a.W = W; a.N = N; a.d = d; a.V = V; a.v_off = v_off;
+  a.H = H; a.W = W; a.targets = targets; a.N = N; a.d = d; a.V = V; a.v_off = v_off;
   a.tiles_v = w.tiles_v; a.n_pad = w.n_pad;
   a.part_m = reinterpret_cast<float*>(ws + w.off_m);
   a.part_s = reinterpret_cast<float*>(ws + w.off_s);
   a.zt = reinterpret_cast<float*>(ws + w.off_zt);
   int32_t* rows = reinterpret_cast<int32_t*>(ws + w.off_rows);
   int32_t* n_act = reinterpret_cast<int32_t*>(ws + w.off_nact);
-  int32_t* row_targets = reinterpret_cast<int32_t*>(ws + w.off_tgt);
-  a.rows = rows; a.list_stride = row_targets - rows; a.n_act = n_act;
+  a.rows = rows; a.n_act = n_act;
   // active-token list (mask and target range); inactive rows get their outputs here
   k_compact_rows<<<dim3((unsigned)compact_blocks(N)), dim3(COMPACT_THREADS), 0, st>>>(
-      compact_args({partial ? 2 : 0, mask, targets, nullptr, V_total, N, 0, rows, n_act, row_targets, nullptr, nullptr,
-                    nullptr, out0, out1, out2, 0.f, nullptr, nullptr}));
+      compact_args({partial ? 2 : 0, mask, targets, nullptr, V_total, N, 0, rows, n_act, out0, out1, out2, 0.f, nullptr,
+                    nullptr}));
   HIP_TRY(hipGetLastError());
   llamarl_status s;
   const Tile tile = logits_tile(N, V, d, dt);
@@ -438,11 +440,8 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
   SetupArgs<stt> u;
   int32_t* plan = reinterpret_cast<int32_t*>(ws + w.off_plan);
   float* dz_scale = kBf16 ? nullptr : reinterpret_cast<float*>(plan + 16);     // plan: StoreArgs::plan_out, 4 entries
-  int32_t* all_targets = reinterpret_cast<int32_t*>(ws + w.off_words);
-  float* all_lse = reinterpret_cast<float*>(all_targets + w.n_list);
-  float* all_coef = all_lse + w.n_list;
-  u.compact = compact_args({1, nullptr, targets, coef, V, N, 0, all_rows, n_act_all, all_targets, lse, all_lse, all_coef,
-                            nullptr, nullptr, nullptr, g, g_device, dz_scale});
+  u.compact = compact_args({1, nullptr, nullptr, coef, V, N, 0, all_rows, n_act_all, nullptr, nullptr, nullptr, g, g_device,
+                            dz_scale});
   u.compact_blocks = compact_blocks(N);
   u.zero_blocks = (int)((N + SETUP_ROWS - 1) / SETUP_ROWS);
   u.dH = reinterpret_cast<stt*>(dH); u.d = d;
@@ -471,11 +470,10 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
 
     // recompute logits tile by tile, turn them into dz (rows / columns = list positions of the pass)
     DzArgs a;
-    a.H = H; a.W = W; a.g = g; a.g_device = g_device; a.N = N; a.d = d; a.V = V;
+    a.H = H; a.W = W; a.targets = targets; a.lse = lse; a.coef = coef; a.g = g; a.g_device = g_device; a.N = N; a.d = d; a.V = V;
     a.dz_scale = dz_scale;
     a.v_off = v_off;
     a.dz = dz; a.ldz = w.ldz; a.dzt = dzt; a.rows = rows; a.n_act = n_act;
-    a.list_stride = w.n_list;
     const Tile logits = logits_tile(Rc, V, d, dt);
     if constexpr (kBf16)
       s = (logits == TILE_256   ? launch_bwd_dz<Logits256>
@@ -495,11 +493,11 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
       const auto launch = dh_tile == TILE_256   ? launch_store_gemm<TileGemmTN>
                           : dh_tile == TILE_128 ? launch_store_gemm<Bf16LoopTN128>
                                                 : launch_store_gemm<Bf16LoopTN64>;
-      s = launch(dzt, w.ldzt, W, d, Rc, d, V, dH, d, 0, 0, n_act, nullptr, rows, part, plan, n_act, 1, 0, nullptr, st);
+      s = launch(dzt, w.ldzt, W, d, Rc, d, V, dH, d, 0, 0, n_act, nullptr, rows, part, w.part, plan, n_act, 1, 0, nullptr, st);
     } else {
       const auto launch = dh_tile == TILE_128 ? launch_store_gemm<F32Loop128> : launch_store_gemm<F32Loop64>;
-      s = launch(dz, w.ldz, wt, w.ldz, Rc, d, w.ldz, dH, d, 1, 0, n_act, nullptr, rows, part, plan, nullptr, 0, 0, dz_scale,
-                 st);
+      s = launch(dz, w.ldz, wt, w.ldz, Rc, d, w.ldz, dH, d, 1, 0, n_act, nullptr, rows, part, w.part, plan, nullptr, 0, 0,
+                 dz_scale, st);
     }
     if (s != LLAMARL_OK) return s;
     if (c == 0) PHASE_EVENT(3);
@@ -515,7 +513,7 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
         return dw_tile == TILE_128 ? launch_store_gemm<F32Loop128> : launch_store_gemm<F32Loop64>;
     }();
     s = launch_dw(dzt, w.ldzt, ht, w.ldzt, V, d, w.ldzt, dW, d, dW_dt == LLAMARL_F32, c == 0 ? accumulate_dW : 1, nullptr,
-                  n_act, nullptr, part, plan, n_act, 1, 1, dz_scale, st);
+                  n_act, nullptr, part, w.part, plan, n_act, 1, 1, dz_scale, st);
     if (s != LLAMARL_OK) return s;
     if (c == 0) PHASE_EVENT(5);
   }

@@ -201,3 +201,27 @@ def test_new_entry_points_reject_bad_arguments(clib):
         binding.ERR_INVALID_ARG
     assert clib.llamarl_mfma_ceiling_traffic(3, 10, fake(1), (1 << 22) - 1, fake(0), ctypes.byref(flops), None) == \
         binding.ERR_INVALID_ARG and b"panels" in clib.llamarl_last_error()
+
+
+@pytest.mark.parametrize("N,d,V,dt", [(256, 256, 1024, binding.F32), (1041, 520, 5003, binding.BF16), (300, 64, 4000, binding.BF16),
+                                      (300, 4096, 128256, binding.BF16), (4800, 516, 20011, binding.F32),
+                                      (16384, 4096, 128256, binding.BF16), (1, 8, 1, binding.BF16)])
+def test_workspaces_hold_panels_lists_and_partial_blocks_and_nothing_else(clib, N, d, V, dt):
+    """callers keep workspaces: what a call needs beside dz and the operand panels is a row list, and for the tiles that are cut
+    along K the larger contraction's eight blocks a tile, four a workgroup of the grid at most"""
+    up = lambda x, m: -(-x // m) * m
+    es = 2 if dt == binding.BF16 else 4
+    odd = lambda n: (lambda p: p if p & 1 else p + 1)(-(-n // 64)) * 64
+    ldz = up(V, 64)
+    panels = up(V * odd(N) * es, 256) + up(d * odd(N) * es, 256)
+    if dt == binding.F32:
+        panels += up(N * ldz * es, 256) + up(d * ldz * es, 256)
+    blocks = 0
+    for M in (N, V):
+        for edge in (256, 128, 64)[dt == binding.F32:]:
+            tiles = -(-M // edge) * -(-d // edge)
+            blocks = max(blocks, min(4 * 256 * (1 if edge == 256 else 2), 8 * tiles) * edge * edge * 4)
+    assert binding.workspace_bytes(N, d, V, dt, binding.PASS_LOSS_BWD) == panels + up(up(N, 64) * 4, 256) + 256 + 256 + blocks
+    n_pad = up(N, 256)
+    planes = max(-(-V // (256 if dt == binding.BF16 else 128)) * n_pad, min(-(-V // 64) * n_pad, 2 * 256 * 191)) * 4
+    assert binding.workspace_bytes(N, d, V, dt, binding.PASS_LOGPROBS) == 2 * up(planes, 256) + 2 * n_pad * 4 + 256
