@@ -72,8 +72,6 @@ constexpr int NTHREADS = Shape256::THREADS;
 constexpr int SLAB_A_BYTES = Shape256::SLAB_A_BYTES;              // 32 KB
 constexpr int STAGE_BYTES = Shape256::STAGE_BYTES;                // 64 KB
 constexpr int MAINLOOP_LDS_BYTES = 2 * STAGE_BYTES;               // 128 KB
-// Tiles of at most NARROW_BN columns: three resident slabs instead of two.
-constexpr int NARROW_BN = 160;
 constexpr int NARROW_STAGE_BYTES = (Shape256::BM + NARROW_BN) * SLAB_ROW_BYTES;      // 52 KB
 constexpr int NARROW_LDS_BYTES = 3 * NARROW_STAGE_BYTES;          // 156 KB
 

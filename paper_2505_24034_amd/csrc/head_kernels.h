@@ -234,42 +234,6 @@ __device__ __forceinline__ void with_blocks(const G& g, F&& f) {
     else f(std::integral_constant<int, 0>());
   }
 }
-// Which tiles a logits kernel of 256 vocabulary rows takes: 256 columns wide, or 128 or 160 (TileGemmNarrow), by what the
-// rounds of the grid cost.  Costs in 1/256 of the time of a slab of the 256 x 256 forward (1.4 us), for 128, 160 and 256
-// columns, measured over (6720, 128256, 512 .. 2048):
-//   slab, tile      a slab of d; what a tile costs besides (dz stores its tile, in partial lines where it is narrow)
-//   unaligned       rows of d that are no multiple of 128 bytes: a slab row touches two lines, and the requests bound a slab
-//   stream          W comes from HBM: 1 or 2 columns of narrow tiles, 1 or 2 - 4 of wide ones (two resident slabs)
-// Forward at (N, V, d), 256 / 160 / 128 columns: (300, 128256, 4096) 367 / 295 / 347 us, (225, ..) 264 / 266 / 268,
-// (450, ..) 427 / 415 / 455, (600, ..) 551 / 505 / 573, (360, 114156, 8168) 877 / 918 / 997.
-struct WidthCosts {
-  int slab[3], tile[3];
-};
-constexpr WidthCosts FWD_COSTS = {{167, 184, 256}, {328, 474, 765}};
-constexpr WidthCosts DZ_COSTS = {{177, 201, 261}, {440, 640, 1000}};
-constexpr int UNALIGNED_SLAB[3] = {220, 239, 294}, STREAM_NARROW[2] = {320, 200}, STREAM_WIDE[2] = {350, 300};
-struct LogitsWidth {
-  int half_blocks;        // column blocks of the right half of narrow tiles; 8: 256 columns
-  int64_t cost;
-};
-__host__ __device__ __forceinline__ LogitsWidth logits_width(const WidthCosts& c, int tiles_v, int n_act, int64_t d, int grid) {
-  LogitsWidth best = {8, 0};
-  const int nk = (int)((d + 63) / 64);
-#pragma unroll
-  for (int h = 2; h >= 0; --h) {
-    const int width = h == 2 ? 256 : 128 + 32 * h, cols = (int)((uint32_t)(n_act + width - 1) / (uint32_t)width);
-    const int64_t tiles = (int64_t)tiles_v * cols;
-    int slab = c.slab[h];
-    if (d % 64 != 0 && slab < UNALIGNED_SLAB[h]) slab = UNALIGNED_SLAB[h];
-    const int stream = width <= NARROW_BN ? (cols <= 2 ? STREAM_NARROW[cols == 2] : 0) : cols <= 4 ? STREAM_WIDE[cols >= 2] : 0;
-    if (slab < stream) slab = stream;
-    if (tiles + grid >= (1ll << 31)) continue;               // 32-bit division; so many rounds are 256 wide
-    const int64_t cost = (int64_t)((uint32_t)(tiles + grid - 1) / (uint32_t)grid) * (nk * slab + c.tile[h]);
-    if (h == 2 || (best.cost != 0 && cost < best.cost)) best = {h == 2 ? 8 : 2 * h, cost};
-  }
-  return best;
-}
-
 // LDS of the logits kernels: slabs, the token words and, in the forward, per-token (max, sum) of the wave rows.  Narrow
 // tiles have those inside their third slab, which is empty during an epilogue.
 template <typename G>
@@ -450,7 +414,7 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
   const int n_act = *a.n_act;
   TileSchedule<PATCH_ROWS_LOGITS> sch;
   if constexpr (HAS_NARROW<G>) {
-    const int half = logits_width(FWD_COSTS, a.tiles_v, n_act, a.d, gridDim.x).half_blocks;
+    const int half = fwd_width(a.tiles_v, n_act, a.d, gridDim.x).half_blocks;
     if (half < 8) {
       LogitsNarrow g;
       g.nb1 = half;
@@ -935,20 +899,19 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzAr
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int n_act = *a.n_act;
   TileSchedule<PATCH_ROWS_LOGITS> sch;
-  const int n_read = (n_act + 63) / 64 * 64;         // the contractions over dz^T read its columns that far
   if constexpr (HAS_NARROW<G>) {
-    const int half = logits_width(DZ_COSTS, a.tiles_v, n_act, a.d, gridDim.x).half_blocks;
+    const int half = dz_width(a.tiles_v, n_act, a.d, gridDim.x).half_blocks;
     if (half < 8) {
       LogitsNarrow g;
       g.nb1 = half;
-      sch.init(a.tiles_v, (n_read + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
+      sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
       if (!sch.has_tile()) return;
       with_blocks(g, [&](auto blocks) { dz_tiles<LogitsNarrow, decltype(blocks)::value>(a, g, sch, n_act, smem); });
       return;
     }
   }
   G g;
-  sch.init(a.tiles_v, (n_read + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
+  sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
   if (!sch.has_tile()) return;                       // block-uniform: no active token at all
   dz_tiles<G, G::Shape::NB>(a, g, sch, n_act, smem);
 }
@@ -966,7 +929,7 @@ struct StoreArgs {
   int c_is_f32;
   int accumulate;
   const int32_t* m_count;   // non-null: M = *m_count (device scalar)
-  const int32_t* k_count;   // non-null: K = *k_count rounded up to 64 (the operands are zero-padded that far)
+  const int32_t* k_count;   // non-null: K = dz_columns(*k_count) (the operands are zero-padded that far)
   const int32_t* c_rows;    // non-null: output row r goes to row c_rows[r] of C
   const int32_t* pitch_count;  // non-null: operands flagged below have the row pitch packed_pitch(*pitch_count)
   int packed_a, packed_b;   // A / B is such a panel (lda / ldb are then ignored)
@@ -1309,7 +1272,7 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int BK = 8 * G::Type::EPC, BM = G::Shape::BM;
   const int64_t M = a.m_count ? (int64_t)*a.m_count : a.M;
-  const int64_t K = a.k_count ? ((int64_t)*a.k_count + 63) / 64 * 64 : a.K;
+  const int64_t K = a.k_count ? dz_columns(*a.k_count, sizeof(typename G::Type::store_t) == 2) : a.K;
   // a later pass of a chunked backward that found no active rows: nothing to add to what the output holds
   if ((MODE == 2 || MODE == 4) && a.k_count != nullptr && K == 0) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1457,7 +1420,7 @@ __device__ __forceinline__ void transpose_tile(const ST* in, int64_t R, int64_t 
 }
 
 // H^T panel of a pass's active tokens: R = *r_count, the row pitch of `out` is packed_pitch(R), and only the first R
-// rounded up to 64 columns of `out` are written (the contraction that reads it stops there).
+// rounded up to 64 columns of `out` are written (the contraction that reads it stops there or before).
 template <typename ST>
 __global__ __launch_bounds__(256) void k_transpose(const ST* in, int64_t C, int64_t ld_in, ST* out, const int32_t* rows,
                                                     const int32_t* r_count) {

@@ -59,7 +59,7 @@ Tile logits_tile(int64_t N, int64_t V, int64_t d, llamarl_dtype dt) {
     if (tiles_v * ((N + 127) / 128) >= LOGITS_MIN_TILES_BF16_128) {
       const int64_t nk = (d + 63) / 64, full = t128 / 512, left = t128 % 512;
       const int64_t cost = full * (nk * 186 + 550) + (left == 0 ? 0 : nk * (left > 256 ? 186 : 131) + 550);
-      if (logits_width(FWD_COSTS, (int)tiles_v, (int)N, d, 256).cost < cost) return TILE_256;
+      if (fwd_width((int)tiles_v, (int)N, d, 256).cost < cost) return TILE_256;
     }
   }
   return t128 >= (dt == LLAMARL_BF16 ? LOGITS_MIN_TILES_BF16_128 : LOGITS_MIN_TILES) ? TILE_128 : TILE_64;
@@ -502,7 +502,7 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     if (s != LLAMARL_OK) return s;
     if (c == 0) PHASE_EVENT(3);
     if (c == 0) PHASE_EVENT(4);
-    // dW [V,d] (+)= dz^T [V,n_act] . H^T[d,n_act]^T      (K = n_act, zero-padded to a multiple of 64); passes after
+    // dW [V,d] (+)= dz^T [V,n_act] . H^T[d,n_act]^T      (K = dz_columns(n_act), zero-padded); passes after
     // the first add to what the earlier ones stored
     auto launch_dw = [&] {
       if constexpr (kBf16)

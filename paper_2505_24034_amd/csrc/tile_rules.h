@@ -82,4 +82,54 @@ struct TileSchedule {
   }
 };
 
+// Tiles of at most NARROW_BN columns: three resident slabs instead of two.
+constexpr int NARROW_BN = 160;
+// Which tiles a logits kernel of 256 vocabulary rows takes: 256 columns wide, or 128 or 160 (TileGemmNarrow), by what the
+// rounds of the grid cost.  Costs in 1/256 of the time of a slab of the 256 x 256 forward (1.4 us), for 128, 160 and 256
+// columns, measured over (6720, 128256, 512 .. 2048):
+//   slab, tile      a slab of d; what a tile costs besides (dz stores its tile, in partial lines where it is narrow)
+//   unaligned       rows of d that are no multiple of 128 bytes: a slab row touches two lines, and the requests bound a slab
+//   stream          W comes from HBM: 1 or 2 columns of narrow tiles, 1 or 2 - 4 of wide ones (two resident slabs)
+// Forward at (N, V, d), 256 / 160 / 128 columns: (300, 128256, 4096) 367 / 295 / 347 us, (225, ..) 264 / 266 / 268,
+// (450, ..) 427 / 415 / 455, (600, ..) 551 / 505 / 573, (360, 114156, 8168) 877 / 918 / 997.
+struct WidthCosts {
+  int slab[3], tile[3];
+};
+constexpr WidthCosts FWD_COSTS = {{167, 184, 256}, {328, 474, 765}};
+constexpr WidthCosts DZ_COSTS = {{177, 201, 261}, {440, 640, 1000}};
+constexpr int UNALIGNED_SLAB[3] = {220, 239, 294}, STREAM_NARROW[2] = {320, 200}, STREAM_WIDE[2] = {350, 300};
+struct LogitsWidth {
+  int half_blocks;        // column blocks of the right half of narrow tiles; 8: 256 columns
+  int64_t cost;
+};
+LLAMARL_RULE LogitsWidth logits_width(const WidthCosts& c, int tiles_v, int n_act, int64_t d, int grid) {
+  LogitsWidth best = {8, 0};
+  const int nk = (int)((d + 63) / 64);
+#pragma unroll
+  for (int h = 2; h >= 0; --h) {
+    const int width = h == 2 ? 256 : 128 + 32 * h, cols = (int)((uint32_t)(n_act + width - 1) / (uint32_t)width);
+    const int64_t tiles = (int64_t)tiles_v * cols;
+    int slab = c.slab[h];
+    if (d % 64 != 0 && slab < UNALIGNED_SLAB[h]) slab = UNALIGNED_SLAB[h];
+    const int stream = width <= NARROW_BN ? (cols <= 2 ? STREAM_NARROW[cols == 2] : 0) : cols <= 4 ? STREAM_WIDE[cols >= 2] : 0;
+    if (slab < stream) slab = stream;
+    if (tiles + grid >= (1ll << 31)) continue;               // 32-bit division; so many rounds are 256 wide
+    const int64_t cost = (int64_t)((uint32_t)(tiles + grid - 1) / (uint32_t)grid) * (nk * slab + c.tile[h]);
+    if (h == 2 || (best.cost != 0 && cost < best.cost)) best = {h == 2 ? 8 : 2 * h, cost};
+  }
+  return best;
+}
+LLAMARL_RULE LogitsWidth fwd_width(int tiles_v, int n_act, int64_t d, int grid) {
+  return logits_width(FWD_COSTS, tiles_v, n_act, d, grid);
+}
+LLAMARL_RULE LogitsWidth dz_width(int tiles_v, int n_act, int64_t d, int grid) {
+  return logits_width(DZ_COSTS, tiles_v, n_act, d, grid);
+}
+// Columns of dz^T, zeros past the active rows, that the dW contraction reads: the next 32 in bf16, half of its last slab.  Every
+// width is a multiple of that, so the columns of tiles that hold tokens write all of it.  Up to the next 64, tiles 160 wide
+// needed one more of zeros for 129 .. 160 rows, which the costs did not see.
+// dz at (150, 128256, d) before / now: d = 512 47 / 40 us, 1024 88 / 84, 4096 296 / 271 (on 256 columns 46, 89 and 301);
+// (470, 33000, 1024) 55.5 / 45, (780, 128256, 512) 140 / 134.
+LLAMARL_RULE int dz_columns(int n_act, bool bf16) { return bf16 ? (n_act + 31) / 32 * 32 : (n_act + 63) / 64 * 64; }
+
 }  // namespace llamarl

@@ -19,3 +19,12 @@ def test_every_tile_is_taken_once(rules, workgroups):
             rounds = -(-tiles_m * tiles_n // workgroups)
             if workgroups >= 8 and workgroups % 8 == 0:
                 assert max(map(len, walks)) == rounds
+
+
+def test_the_columns_that_hold_tokens_write_all_of_dz(rules):
+    # a column of tiles past them would walk all of W for zeros, at a cost the width rule does not count
+    for bf16, widths in ((1, (64, 128, 160, 256)), (0, (64, 128))):
+        for n in range(1, 3000):
+            read = rules.dz_columns(n, bf16)
+            assert n <= read < n + 64
+            assert all(-(-read // w) == -(-n // w) for w in widths), (n, bf16)
