@@ -1313,9 +1313,6 @@ struct TailUnit {
   static constexpr int PER_TILE = S::BM / ROWS;
 };
 constexpr int TAIL_MAX_BLOCKS = 2048;
-// Most parts a tail tile is cut into.  Eight left most CUs idle where few tokens meet a long vocabulary: dH of
-// (300, 128256, 1032), 27 tiles of 128, 250 -> 133 us; (1024, 128256, 520) 243 -> 153.
-constexpr int STORE_MAX_SPLITS = 32;
 static_assert(STORE_MAX_SPLITS <= 32, "StorePlan::init weighs 32 factors");
 // The parts in ascending order, MOST loads of a thread in flight.  More than eight parts are few tiles, bound by latency: 32
 // of them eight at a time took 13 us.  All 32 at once, though, leave too few wavefronts for the many tiles of eight parts.

@@ -33,64 +33,7 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t esize(llamarl_dtype dt) { return dt == LLAMARL_BF16 ? 2 : 4; }
 
-// ---- which main loop a contraction runs on ---------------------------------------------------------------
-// The choice depends on host-side sizes only (workspace sizes follow from it).  A large contraction runs fastest on the
-// largest tiles (bf16: 256 x 256, 1.2 - 1.3 times as fast as 128 x 128 when both fill the chip), a small one on the
-// tiles that give most CUs something to do.
-enum Tile { TILE_256, TILE_128, TILE_64 };
-inline int tile_edge(Tile t) { return t == TILE_256 ? 256 : t == TILE_128 ? 128 : 64; }
-inline int64_t tile_count(int64_t rows, int64_t cols, int64_t edge) {
-  return ((rows + edge - 1) / edge) * ((cols + edge - 1) / edge);
-}
-// Logits kernels (forward, recompute): N x V outputs.  bf16 takes tiles of 256 vocabulary rows where 256 x 256 ones come to
-// LOGITS_MIN_TILES, and below that where they cost less in rounds of the grid than 128 x 128 ones, whose slab takes 1.02 us
-// with two workgroups a CU and 0.72 us with one (186 and 131 of logits_width's units); the latter win where K is short.
-//   forward at (N, V, d), 256 rows / 128 x 128: (882, 10487, 7808) 122 / 222 us, (1700, 5412, 1888) 35 / 58,
-//   (1024, 8192, 1024) 20.7 / 19.4, (1041, 5003, 520) 16.4 / 14.4, (256, 16000, 2048) 28 / 26.
-//   bf16, dz at (N, V, d) on 128- / 64-tiles: (512, 2048, 512) 16 / 12 us, (512, 8192, 1024) 18 / 22, (1041, 5003, 520) 18 / 26.
-//   fp32, dz on 128- / 64-tiles: (512, 2048, 512) 44 / 26 us, (512, 4096, 512) 45 / 34, (1024, 4096, 512) 48 / 57,
-//   (2048, 8192, 512) 127 / 206.
-constexpr int LOGITS_MIN_TILES = 192, LOGITS_MIN_TILES_BF16_128 = 128;   // of the larger edge; fewer: the next smaller one
-Tile logits_tile(int64_t N, int64_t V, int64_t d, llamarl_dtype dt) {
-  const int64_t t128 = tile_count(N, V, 128);
-  if (dt == LLAMARL_BF16) {
-    const int64_t tiles_v = (V + 255) / 256;
-    if (tile_count(N, V, 256) >= LOGITS_MIN_TILES) return TILE_256;
-    if (tiles_v * ((N + 127) / 128) >= LOGITS_MIN_TILES_BF16_128) {
-      const int64_t nk = (d + 63) / 64, full = t128 / 512, left = t128 % 512;
-      const int64_t cost = full * (nk * 186 + 550) + (left == 0 ? 0 : nk * (left > 256 ? 186 : 131) + 550);
-      if (fwd_width((int)tiles_v, (int)N, d, 256).cost < cost) return TILE_256;
-    }
-  }
-  return t128 >= (dt == LLAMARL_BF16 ? LOGITS_MIN_TILES_BF16_128 : LOGITS_MIN_TILES) ? TILE_128 : TILE_64;
-}
-// Store contractions: M x Nn outputs over K, split along K where tiles are few; counted in parts of 16 slabs, which
-// still pay for their partial blocks.  Up to eight parts a tile the tiles of a count decide; beyond, where K is long and
-// the output small, 256-tiles of more than 128 rows if they fill the chip, 128-tiles by the output they hold (the rest of
-// an edge tile is padding).  bf16 dH on 256- / 128- / 64-tiles with up to 32 parts, and now against eight parts and the rule
-// of then:
-//   (64, 128256, 1024) 86 / 60 / 54, 80 -> 51; (300, 128256, 520) 105 / 96 / 130, 110 -> 90; (64, 128256, 4096) 203 / 193 / 225,
-//   231 -> 186; (300, 128256, 1032) 141 / 145 / 231, 250 -> 133; (150, 128256, 2048) 124 / 170 / 247, 225 -> 117;
-//   (1024, 128256, 520) 163 / 203 / 373, 243 -> 153; (600, 60000, 1032) 100 / 102 / 195, 112 -> 90;
-//   fp32 on 128- / 64-tiles (300, 16400, 260) 62 / 47, 65 -> 41; (300, 40000, 1024) 289 -> 190.
-// With up to eight parts:
-//   bf16, dH at (N, V, d) on 256- / 128- / 64-tiles: (512, 2048, 512) 23 / 17.5 / 17 us, (1041, 5003, 520) 33 / 26 / 29,
-//   (1024, 8192, 1024) 42 / 36 / 43, (64, 128256, 4096) 337 / 236 / 229, (1024, 16032, 2048) 77 / 79 / 125;
-//   dW: (512, 2048, 512) 23 / 19 / 16, (512, 8192, 1024) 38 / 17 / 25, (1024, 16032, 2048) 67 / 73 / 131.
-//   fp32 on 128- / 64-tiles, dH: (512, 4096, 512) 45 / 35, (1024, 4096, 512) 49 / 57, (300, 16400, 260) 137 / 69;
-//   dW: (512, 4096, 512) 35 / 31, (1024, 4096, 512) 48 / 52, (300, 16400, 260) 43 / 54.
-Tile store_tile(int64_t M, int64_t Nn, int64_t K, llamarl_dtype dt) {
-  const int64_t slab_k = dt == LLAMARL_BF16 ? 64 : 32;
-  const int64_t parts = std::min<int64_t>(STORE_MAX_SPLITS, std::max<int64_t>(1, K / (16 * slab_k)));
-  const int64_t few = std::min<int64_t>(parts, 8);
-  if (dt == LLAMARL_BF16) {
-    const int64_t t256 = tile_count(M, Nn, 256);
-    if (t256 * few >= 256 || (M > 128 && t256 * parts >= 256)) return TILE_256;
-  }
-  if (tile_count(M, Nn, 128) * few >= (dt == LLAMARL_BF16 ? 128 : 256)) return TILE_128;
-  return M * Nn / (128 * 128) * parts >= 256 ? TILE_128 : TILE_64;
-}
-
+// ---- main loops of the tiles that tile_rules.h picks --------------------------------------------------------
 typedef TileGemmSmall<BF16, Shape128, 2, 2> Bf16Loop128;
 typedef TileGemmSmall<BF16, Shape64, 4, 2> Bf16Loop64;
 typedef TileGemmTNSmall<Shape128, 2, 2> Bf16LoopTN128;
@@ -106,7 +49,7 @@ struct FwdWs {
 };
 FwdWs fwd_ws(int64_t N, int64_t d, int64_t V, llamarl_dtype dt) {
   FwdWs w;
-  const int tile = tile_edge(logits_tile(N, V, d, dt));
+  const int tile = tile_edge(logits_tile(N, V, d, dt == LLAMARL_BF16));
   w.tiles_v = (int)((V + tile - 1) / tile);
   w.n_pad = round_up(N, 256);
   // Smaller tiles leave more partials per token, so the planes of a call can be larger than those of a call with more
@@ -222,7 +165,7 @@ llamarl_status check_head_shape(int64_t N, int64_t d, int64_t V, llamarl_dtype d
     return fail(LLAMARL_ERR_UNSUPPORTED, "a 256-row panel of %lld elements per row exceeds 2 GiB", (long long)widest);
   if (N * d * (int64_t)esize(dt) >= (int64_t)1 << 31)
     return fail(LLAMARL_ERR_UNSUPPORTED, "H must be smaller than 2 GiB (its rows are gathered with 32-bit offsets)");
-  if (tile_count(N, V, tile_edge(logits_tile(N, V, d, dt))) >= (int64_t)1 << 31 || V >= (int64_t)1 << 31)
+  if (tile_count(N, V, tile_edge(logits_tile(N, V, d, dt == LLAMARL_BF16))) >= (int64_t)1 << 31 || V >= (int64_t)1 << 31)
     return fail(LLAMARL_ERR_UNSUPPORTED, "too many tiles");
   return LLAMARL_OK;
 }
@@ -283,15 +226,6 @@ llamarl_status launch_store_mode(const StoreArgs& a, int64_t work_items, int til
     }
   }
   return LLAMARL_OK;
-}
-
-// Width of the tiles of the k-major store contraction (dH): the narrowest that takes no more columns of tiles than 256.  (The
-// empty columns of a wide tile multiply zeros and cost a power-limited chip less than their share.  dW keeps 256: at
-// 6720 rows a narrow last column made it slower.)
-//   (6720, 40000, d), 256 / narrow: d = 264 223 / 213 us, 520 319 / 307, 1032 587 / 562, 1288 618 / 601
-int store_width(int64_t Nn) {
-  const int64_t cols = (Nn + 255) / 256;
-  return (int)std::max<int64_t>(128, round_up((Nn + cols - 1) / cols, 32));
 }
 
 // C [M,Nn] (+)= A B^T on the persistent grid; ws_part / ws_plan: workspace of the last round's split tiles
@@ -386,7 +320,7 @@ llamarl_status run_logprobs(const void* H, const void* W, const int32_t* targets
                     nullptr}));
   HIP_TRY(hipGetLastError());
   llamarl_status s;
-  const Tile tile = logits_tile(N, V, d, dt);
+  const Tile tile = logits_tile(N, V, d, dt == LLAMARL_BF16);
   if constexpr (dt == LLAMARL_BF16)
     s = (tile == TILE_256   ? launch_fwd_partials<Logits256>
          : tile == TILE_128 ? launch_fwd_partials<Bf16Loop128>
@@ -474,7 +408,7 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     a.dz_scale = dz_scale;
     a.v_off = v_off;
     a.dz = dz; a.ldz = w.ldz; a.dzt = dzt; a.rows = rows; a.n_act = n_act;
-    const Tile logits = logits_tile(Rc, V, d, dt);
+    const Tile logits = dz_tile(Rc, V, d, kBf16);
     if constexpr (kBf16)
       s = (logits == TILE_256   ? launch_bwd_dz<Logits256>
            : logits == TILE_128 ? launch_bwd_dz<Bf16Loop128>
@@ -488,7 +422,7 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     //   bf16: k-major operands dz^T [V][n_act] and W [V][d], K = V exactly
     //   fp32: K-contiguous operands dz [n_act][ldz] and W^T [d][ldz], K zero-padded to ldz
     float* part = reinterpret_cast<float*>(ws + w.off_part);
-    const Tile dh_tile = store_tile(Rc, d, V, dt), dw_tile = store_tile(V, d, Rc, dt);
+    const Tile dh_tile = store_tile(Rc, d, V, kBf16), dw_tile = store_tile(V, d, Rc, kBf16);
     if constexpr (kBf16) {
       const auto launch = dh_tile == TILE_256   ? launch_store_gemm<TileGemmTN>
                           : dh_tile == TILE_128 ? launch_store_gemm<Bf16LoopTN128>

@@ -132,4 +132,85 @@ LLAMARL_RULE LogitsWidth dz_width(int tiles_v, int n_act, int64_t d, int grid) {
 // (470, 33000, 1024) 55.5 / 45, (780, 128256, 512) 140 / 134.
 LLAMARL_RULE int dz_columns(int n_act, bool bf16) { return bf16 ? (n_act + 31) / 32 * 32 : (n_act + 63) / 64 * 64; }
 
+// ---- which main loop a contraction runs on ---------------------------------------------------------------
+// The choice depends on host-side sizes only (workspace sizes follow from it).  A large contraction runs fastest on the
+// largest tiles (bf16: 256 x 256, 1.2 - 1.3 times as fast as 128 x 128 when both fill the chip), a small one on the
+// tiles that give most CUs something to do.
+enum Tile { TILE_256, TILE_128, TILE_64 };
+LLAMARL_RULE int tile_edge(Tile t) { return t == TILE_256 ? 256 : t == TILE_128 ? 128 : 64; }
+LLAMARL_RULE int64_t tile_count(int64_t rows, int64_t cols, int64_t edge) {
+  return ((rows + edge - 1) / edge) * ((cols + edge - 1) / edge);
+}
+// Logits kernels (forward, recompute): N x V outputs.  bf16 takes tiles of 256 vocabulary rows where 256 x 256 ones come to
+// LOGITS_MIN_TILES, and below that where they cost less in rounds of the grid than 128 x 128 ones: a round of those takes the
+// slabs of two workgroups a CU, or of one where less than half of it is left, and a tile's remainder; `launch` is what the
+// first round takes less (their epilogues cover each other).  128 x 128 ones win where K is short, in dz up to longer K: narrow
+// tiles leave it partial lines to write.  Forward call / dz at (N, V, d), 256 rows : 128 x 128, us:
+//   (882, 10487, 7808) 127 : 204 / 129 : 226    (1700, 5412, 1888) 43 : 67 / 40 : 64       (1024, 8192, 1024) 27.2 : 28.3 / 24.6 : 24.0
+//   (1024, 8192, 256) 16.3 : 15.6 / 15.4 : 13.0 (2048, 4096, 264) 18.0 : 17.6 / 17.1 : 14.6 (512, 12000, 2048) 35.6 : 38.0 / 32.3 : 34.0
+//   (256, 33000, 1024) 38.5 : 35.3 / 37.6 : 31.5 (600, 7000, 512) 18.6 : 18.0 / 18.0 : 15.5 (512, 24000, 1024) 36.8 : 43.2 / 33.8 : 38.6
+//   bf16, dz at (N, V, d) on 128- / 64-tiles: (512, 2048, 512) 16 / 12 us, (512, 8192, 1024) 18 / 22, (1041, 5003, 520) 18 / 26.
+//   fp32, dz on 128- / 64-tiles: (512, 2048, 512) 44 / 26 us, (512, 4096, 512) 45 / 34, (1024, 4096, 512) 48 / 57,
+//   (2048, 8192, 512) 127 / 206.
+constexpr int LOGITS_MIN_TILES = 192, LOGITS_MIN_TILES_BF16_128 = 128;   // of the larger edge; fewer: the next smaller one
+struct SmallCosts {       // of 128 x 128 tiles, in logits_width's units
+  int slab_two, slab_one, tile, launch;
+};
+constexpr SmallCosts FWD_SMALL = {186, 131, 550, 400}, DZ_SMALL = {202, 142, 400, 500};
+LLAMARL_RULE Tile logits_tile_by(const SmallCosts& c, const WidthCosts& wide, int64_t N, int64_t V, int64_t d, bool bf16) {
+  const int64_t t128 = tile_count(N, V, 128);
+  if (bf16) {
+    const int64_t tiles_v = (V + 255) / 256;
+    if (tile_count(N, V, 256) >= LOGITS_MIN_TILES) return TILE_256;
+    if (tiles_v * ((N + 127) / 128) >= LOGITS_MIN_TILES_BF16_128) {
+      const int64_t nk = (d + 63) / 64, full = t128 / 512, left = t128 % 512;
+      const int64_t last = left == 0 ? 0 : nk * (left > 256 ? c.slab_two : c.slab_one) + c.tile;
+      if (logits_width(wide, (int)tiles_v, (int)N, d, 256).cost < full * (nk * c.slab_two + c.tile) + last - c.launch) return TILE_256;
+    }
+  }
+  return t128 >= (bf16 ? LOGITS_MIN_TILES_BF16_128 : LOGITS_MIN_TILES) ? TILE_128 : TILE_64;
+}
+LLAMARL_RULE Tile logits_tile(int64_t N, int64_t V, int64_t d, bool bf16) { return logits_tile_by(FWD_SMALL, FWD_COSTS, N, V, d, bf16); }
+LLAMARL_RULE Tile dz_tile(int64_t N, int64_t V, int64_t d, bool bf16) { return logits_tile_by(DZ_SMALL, DZ_COSTS, N, V, d, bf16); }
+
+// Most parts a tail tile is cut into.  Eight left most CUs idle where few tokens meet a long vocabulary: dH of
+// (300, 128256, 1032), 27 tiles of 128, 250 -> 133 us; (1024, 128256, 520) 243 -> 153.
+constexpr int STORE_MAX_SPLITS = 32;
+// Store contractions: M x Nn outputs over K, split along K where tiles are few; counted in parts of 16 slabs, which
+// still pay for their partial blocks.  Up to eight parts a tile the tiles of a count decide; beyond, where K is long and
+// the output small, 256-tiles of more than 128 rows if they fill the chip, 128-tiles by the output they hold (the rest of
+// an edge tile is padding).  bf16 dH on 256- / 128- / 64-tiles with up to 32 parts, and now against eight parts and the rule
+// of then:
+//   (64, 128256, 1024) 86 / 60 / 54, 80 -> 51; (300, 128256, 520) 105 / 96 / 130, 110 -> 90; (64, 128256, 4096) 203 / 193 / 225,
+//   231 -> 186; (300, 128256, 1032) 141 / 145 / 231, 250 -> 133; (150, 128256, 2048) 124 / 170 / 247, 225 -> 117;
+//   (1024, 128256, 520) 163 / 203 / 373, 243 -> 153; (600, 60000, 1032) 100 / 102 / 195, 112 -> 90;
+//   fp32 on 128- / 64-tiles (300, 16400, 260) 62 / 47, 65 -> 41; (300, 40000, 1024) 289 -> 190.
+// With up to eight parts:
+//   bf16, dH at (N, V, d) on 256- / 128- / 64-tiles: (512, 2048, 512) 23 / 17.5 / 17 us, (1041, 5003, 520) 33 / 26 / 29,
+//   (1024, 8192, 1024) 42 / 36 / 43, (64, 128256, 4096) 337 / 236 / 229, (1024, 16032, 2048) 77 / 79 / 125;
+//   dW: (512, 2048, 512) 23 / 19 / 16, (512, 8192, 1024) 38 / 17 / 25, (1024, 16032, 2048) 67 / 73 / 131.
+//   fp32 on 128- / 64-tiles, dH: (512, 4096, 512) 45 / 35, (1024, 4096, 512) 49 / 57, (300, 16400, 260) 137 / 69;
+//   dW: (512, 4096, 512) 35 / 31, (1024, 4096, 512) 48 / 52, (300, 16400, 260) 43 / 54.
+LLAMARL_RULE Tile store_tile(int64_t M, int64_t Nn, int64_t K, bool bf16) {
+  const int64_t slab_k = bf16 ? 64 : 32;
+  const int64_t most = K / (16 * slab_k), parts = most < 1 ? 1 : most < STORE_MAX_SPLITS ? most : STORE_MAX_SPLITS;
+  const int64_t few = parts < 8 ? parts : 8;
+  if (bf16) {
+    const int64_t t256 = tile_count(M, Nn, 256);
+    if (t256 * few >= 256 || (M > 128 && t256 * parts >= 256)) return TILE_256;
+  }
+  if (tile_count(M, Nn, 128) * few >= (bf16 ? 128 : 256)) return TILE_128;
+  return M * Nn / (128 * 128) * parts >= 256 ? TILE_128 : TILE_64;
+}
+
+// Width of the tiles of the k-major store contraction (dH): the narrowest that takes no more columns of tiles than 256.  (The
+// empty columns of a wide tile multiply zeros and cost a power-limited chip less than their share.  dW keeps 256: at
+// 6720 rows a narrow last column made it slower.)
+//   (6720, 40000, d), 256 / narrow: d = 264 223 / 213 us, 520 319 / 307, 1032 587 / 562, 1288 618 / 601
+LLAMARL_RULE int store_width(int64_t Nn) {
+  const int64_t cols = (Nn + 255) / 256;
+  const int width = (int)(((Nn + cols - 1) / cols + 31) / 32 * 32);
+  return width < 128 ? 128 : width;
+}
+
 }  // namespace llamarl
