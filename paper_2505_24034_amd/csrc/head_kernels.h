@@ -271,8 +271,9 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a, G& g, TileSchedule<P
   cur.take(sch);
   int grow[decltype(g.lb)::ITERS];
   gather_rows_of_first<false>(g, a, cur, n_act, grow);
-  const int first_row = a.rows[min(cur.tt * width + Words::position(), n_act - 1)];
+  int first_row = a.rows[min(cur.tt * width + Words::position(), n_act - 1)];
   logits_setup<false>(g, a, cur, n_act, grow);
+  asm volatile("" : "+v"(first_row));             // waited for here, with the others, not behind the slab requests
 #pragma unroll
   for (int q = 0; q < G::FIRST_PARTS; ++q) issue_first<G, nb>(g, smem, q);
   bool more = sch.has_tile();
@@ -725,8 +726,9 @@ __device__ __forceinline__ void dz_tiles(const DzArgs& a, G& g, TileSchedule<PAT
   cur.take(sch);
   int grow[decltype(g.lb)::ITERS];
   gather_rows_of_first<true>(g, a, cur, n_act, grow);
-  const int first_row = a.rows[min(cur.tt * width + Words::position(), n_act - 1)];
+  int first_row = a.rows[min(cur.tt * width + Words::position(), n_act - 1)];
   logits_setup<true>(g, a, cur, n_act, grow);
+  asm volatile("" : "+v"(first_row));             // waited for here, with the others, not behind the slab requests
 #pragma unroll
   for (int q = 0; q < G::FIRST_PARTS; ++q) issue_first<G, nb>(g, smem, q);
   bool more = sch.has_tile();
