@@ -1,6 +1,7 @@
 """Builds the HIP library in-tree, paper_2505_24034_amd/libllamarl.so (gfx950 only), and the binding's argument
 marshalling, _native.so (host code against torch's headers)."""
 import os
+import shutil
 import subprocess
 import sys
 
@@ -15,8 +16,6 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-command-line-argument", "-Wno-inline-asm",
 ]
-
-
 NATIVE_PATH = os.path.join(HERE, "_native.so")
 CXX = os.environ.get("CXX", "g++")
 
@@ -38,15 +37,19 @@ def build_library(verbose=True, extra_flags=()):
     return LIB_PATH
 
 
+def rocm_root():
+    """the ROCm installation of the compiler in use, which may be given by name alone"""
+    return os.path.dirname(os.path.dirname(os.path.realpath(shutil.which(HIPCC) or HIPCC)))
+
+
 def build_native(verbose=True):
     """csrc/native.cpp; needs libllamarl.so"""
     import sysconfig
 
     import torch
     root = os.path.dirname(torch.__file__)
-    rocm = os.path.dirname(os.path.dirname(os.path.realpath(HIPCC)))
     include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
-               os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+               os.path.join(rocm_root(), "include"), sysconfig.get_paths()["include"]]
     cmd = [CXX, "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
     for d in include:

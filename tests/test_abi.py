@@ -225,3 +225,10 @@ def test_workspaces_hold_panels_lists_and_partial_blocks_and_nothing_else(clib, 
     n_pad = up(N, 256)
     planes = max(-(-V // (256 if dt == binding.BF16 else 128)) * n_pad, min(-(-V // 64) * n_pad, 2 * 256 * 191)) * 4
     assert binding.workspace_bytes(N, d, V, dt, binding.PASS_LOGPROBS) == 2 * up(planes, 256) + 2 * n_pad * 4 + 256
+
+
+def test_compiler_given_by_name_finds_its_headers(monkeypatch):
+    from paper_2505_24034_amd import build
+    monkeypatch.setattr(build, "HIPCC", "hipcc")
+    monkeypatch.setenv("PATH", "/opt/rocm/bin" + os.pathsep + os.environ["PATH"])
+    assert os.path.exists(os.path.join(build.rocm_root(), "include", "hip", "hip_runtime.h"))
