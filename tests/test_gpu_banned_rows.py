@@ -4,22 +4,22 @@ zero rows, against which such a row's logit is 0 * -inf: they must not reach the
 import pytest
 import torch
 
+from tile_util import loops
 from test_gpu_f32_tiles import _inputs, _rel, _worst
 
 pytestmark = pytest.mark.gpu
 
 
 # active counts that leave 1 .. 63 positions of the last 64 empty
-@pytest.mark.parametrize("dtype,N,V,d", [
-    ("bf16", 1, 300, 64), ("bf16", 100, 3000, 64),                                     # 64-tiles
-    ("bf16", 383, 8065, 64), ("bf16", 500, 5003, 520),                                 # 128-tiles
-    ("bf16", 31, 49200, 64), ("bf16", 150, 49200, 72), ("bf16", 300, 49200, 520),      # 128 and 160 columns
-    ("bf16", 1001, 49200, 136), ("bf16", 1275, 49200, 264),                            # 256 columns
-    ("f32", 130, 300, 40), ("f32", 1, 700, 64),                                        # 64-tiles
-    ("f32", 400, 9000, 40), ("f32", 1217, 8200, 260),                                  # 128-tiles
+@pytest.mark.parametrize("dtype,N,V,d,loop", [
+    ("bf16", 1, 300, 64, "64"), ("bf16", 100, 3000, 64, "64"), ("bf16", 383, 8065, 64, "128"), ("bf16", 500, 5003, 520, "128"),
+    ("bf16", 31, 49200, 64, "256x128"), ("bf16", 150, 49200, 72, "256x160"), ("bf16", 300, 49200, 520, "256x160"),
+    ("bf16", 1001, 49200, 136, "256x256"), ("bf16", 1275, 49200, 264, "256x256"),
+    ("f32", 130, 300, 40, "64"), ("f32", 1, 700, 64, "64"), ("f32", 400, 9000, 40, "128"), ("f32", 1217, 8200, 260, "128"),
 ])
 @pytest.mark.parametrize("masked", [False, True])
-def test_banned_row_has_no_gradient(lib, dtype, N, V, d, masked):
+def test_banned_row_has_no_gradient(lib, dtype, N, V, d, loop, masked):
+    assert loops(N, V, d, bf16=dtype == "bf16")[1] == loop
     H, W, t, coef = _inputs(N, V, d, N + d)
     if dtype == "bf16":
         H, W = H.bfloat16(), W.bfloat16()
