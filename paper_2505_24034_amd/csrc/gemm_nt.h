@@ -335,7 +335,8 @@ __device__ __forceinline__ bool half_slab_left(int K) { return (unsigned)(K - 1)
 //   run():      the K loop.  Waves leave it at different times: __syncthreads() before reusing LDS.
 // smem must hold MAINLOOP_LDS_BYTES.
 //
-// NEAR: a lane's column blocks hold neighbouring output columns (tile_row_of); the epilogue must then take its columns from LanePos::col_quad().
+// NEAR: a lane's column blocks hold neighbouring output columns (tile_row_of); the epilogue must then take its columns from
+// LanePos::col_near().
 // YOUNGER, FIRST_ONLY: see run().
 template <typename TT, int LOAD_SLOT, int YOUNGER, bool FIRST_ONLY>
 struct TileGemm {
@@ -494,7 +495,7 @@ struct KSlots {
   constexpr int column(int j) const { return j == 0 ? barrier() : j == 1 && nb >= 6 ? 9 : 4 * (j + 1); }
   constexpr int row(int i) const { return nb >= 6 ? 10 + 4 * i : nb == 4 ? 5 + 3 * i : 4 + i; }     // ... of row block i
   // load n = 0 .. 7 of the slab after next; first: for eight blocks, see k_step
-  constexpr int load(int n, int first) const { return nb == 8 ? first + 2 * n : nb == 6 ? 9 + 2 * n : nb == 4 ? 8 + n : 4 + n / 2; }
+  constexpr int load(int n, int first) const { return nb == 8 ? first + 2 * n : nb == 4 ? 8 + n : 4 + n / 2; }
 };
 
 // One k-step, as k_step with the operands' roles exchanged: the column fragments b have one register set each, the four row

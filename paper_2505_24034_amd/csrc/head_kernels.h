@@ -262,7 +262,7 @@ __device__ __forceinline__ void fwd_tiles(const FwdArgs& a, G& g, TileSchedule<P
   constexpr int BM = S::BM, BN = S::BN, MB = S::MB;
   const int width = g.width();
   float* s_m = reinterpret_cast<float*>(smem + fwd_sums_at<G>);   // [waves along the vocabulary][tokens of the tile]
-  float* s_s = s_m + S::WAVES_M * BN;                           // outside the slab buffers: see prefetch below
+  float* s_s = s_m + S::WAVES_M * BN;                           // not in the stages of the next tile's first slabs
 
   typedef TokenWords<S, 2> Words;
   char* words = smem + fwd_words_at<G>;
@@ -835,8 +835,7 @@ __device__ __forceinline__ void dz_tiles(const DzArgs& a, G& g, TileSchedule<PAT
       const uint32_t ld_b = (uint32_t)ldzt * 2u;
       uint32_t lane_off = (uint32_t)lane_row0 * ld_b + (uint32_t)tok0 * 2u;
       asm volatile("" : "+v"(lane_off));
-      // ldzt is a multiple of 64: it cuts no group of 2, 4 or 8 neighbours, but may cut one of 6, which goes pair by pair
-      const int left = dzt_cols - tok0;
+      const bool in_cols = tok0 < dzt_cols;          // ldzt is a multiple of 64: it cuts no group of 2, 4 or 8 neighbours
       typedef uint32_t words_t __attribute__((ext_vector_type(nb / 2), aligned(4)));
 #pragma unroll
       for (int i = 0; i < MB; ++i) {
@@ -844,24 +843,17 @@ __device__ __forceinline__ void dz_tiles(const DzArgs& a, G& g, TileSchedule<PAT
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int rel = i * 16 + r;
-          if (lane_row0 + rel < rowsV) {
+          if (lane_row0 + rel < rowsV && in_cols) {
             words_t v;
 #pragma unroll
             for (int j = 0; j < nb / 2; ++j) {
               if constexpr (nb == 2) v = pack_bf16(acc[i][0][r], acc[i][1][r]);
               else v[j] = pack_bf16(acc[i][2 * j][r], acc[i][2 * j + 1][r]);
             }
-            char* q = tile_base + (lane_off + (uint32_t)rel * ld_b);
             // non-temporal: dz^T is gigabytes that the gradient contractions stream later; written normally it
             // pushes the H and W panels this kernel re-reads out of the Infinity Cache (-5 % kernel time at
             // 21 k active rows, where the active H rows alone are 174 MB; neutral at 8.6 k)
-            if (left >= nb) {
-              __builtin_nontemporal_store(v, reinterpret_cast<words_t*>(q));
-            } else if constexpr (nb == 6) {
-#pragma unroll
-              for (int j = 0; j < 3; ++j)
-                if (left >= 2 * j + 2) reinterpret_cast<uint32_t*>(q)[j] = v[j];
-            }
+            __builtin_nontemporal_store(v, reinterpret_cast<words_t*>(tile_base + (lane_off + (uint32_t)rel * ld_b)));
           }
         }
       }
@@ -936,7 +928,7 @@ struct StoreArgs {
   const int32_t* pitch_count;  // non-null: operands flagged below have the row pitch packed_pitch(*pitch_count)
   int packed_a, packed_b;   // A / B is such a panel (lda / ldb are then ignored)
   int group_m;              // rows of a 32-tile patch (see TileSchedule)
-  int width, nb1;           // columns of a tile; column blocks of its right half (TileGemm)
+  int width, nb1;           // columns of a tile; column blocks of its right half (TileGemmTN)
   int max_splits;           // the tiles of the last, partial round may be split this many ways along K (1: never)
   int max_parts;            // blocks that `part` has room for
   float* part;              // [splits][tail tiles][tile] fp32 partial products of split tiles
@@ -1019,7 +1011,7 @@ struct StorePlan {
       nsplit = splits;
     }
   }
-  __device__ __forceinline__ void coords(int id, int& tm, int& tn) const {   // as TileSchedule::coords
+  __device__ __forceinline__ void coords(int id, int& tm, int& tn) const {   // as TileSchedule::take, without the turn
     const int per_group = group_m * tiles_n;
     const int g = id / per_group;
     const int first_m = g * group_m;
@@ -1076,46 +1068,21 @@ __device__ __forceinline__ void store_fetch(G& g, const StorePlan& plan, const S
                               (const st*)a.B + t.col0 * ld.b + t.k_lo, ld.b, t.rowsB, t.k_len, smem);
 }
 
-// C neighbouring output elements (C even) in their final form.  MODE: 1 fp32, 2 fp32 accumulate, 3 bf16, 4 bf16 accumulate.
-template <int MODE, int C>
-__device__ __forceinline__ void store_final(char* q, const float (&x)[C]) {
+// Four neighbouring output elements in their final form.  MODE: 1 fp32, 2 fp32 accumulate, 3 bf16, 4 bf16 accumulate.
+template <int MODE>
+__device__ __forceinline__ void store_final(char* q, const float (&x)[4]) {
   if constexpr (MODE <= 2) {
-    if constexpr (C > 4) {
-      const float lo[4] = {x[0], x[1], x[2], x[3]};
-      float hi[C - 4];
-#pragma unroll
-      for (int j = 0; j < C - 4; ++j) hi[j] = x[4 + j];
-      store_final<MODE, 4>(q, lo);
-      store_final<MODE, C - 4>(q + 16, hi);
-    } else {
-      typedef float floats_t __attribute__((ext_vector_type(C), aligned(8)));
-      floats_t v;
-#pragma unroll
-      for (int j = 0; j < C; ++j) v[j] = x[j];
-      if (MODE == 2) v += *reinterpret_cast<const floats_t*>(q);
-      *reinterpret_cast<floats_t*>(q) = v;
-    }
+    f32x4_t v = {x[0], x[1], x[2], x[3]};
+    if (MODE == 2) v += *reinterpret_cast<const f32x4_t*>(q);
+    *reinterpret_cast<f32x4_t*>(q) = v;
   } else {
-    uint32_t w[C / 2];
-    if constexpr (MODE == 4) __builtin_memcpy(w, __builtin_assume_aligned(q, 4), C * 2);
+    float y[4] = {x[0], x[1], x[2], x[3]};
+    if constexpr (MODE == 4) {
+      const u32x2_t w = *reinterpret_cast<const u32x2_t*>(q);
 #pragma unroll
-    for (int j = 0; j < C / 2; ++j) {
-      float lo = x[2 * j], hi = x[2 * j + 1];
-      if constexpr (MODE == 4) {
-        lo += bf16_bits_to_float((uint16_t)(w[j] & 0xffffu));
-        hi += bf16_bits_to_float((uint16_t)(w[j] >> 16));
-      }
-      w[j] = pack_bf16(lo, hi);
+      for (int j = 0; j < 4; ++j) y[j] += bf16_bits_to_float((uint16_t)(w[j >> 1] >> (16 * (j & 1))));
     }
-    if constexpr (C == 2) {
-      *reinterpret_cast<uint32_t*>(q) = w[0];
-    } else {
-      typedef uint32_t words_t __attribute__((ext_vector_type(C / 2), aligned(4)));
-      words_t v;
-#pragma unroll
-      for (int j = 0; j < C / 2; ++j) v[j] = w[j];
-      *reinterpret_cast<words_t*>(q) = v;
-    }
+    *reinterpret_cast<u32x2_t*>(q) = u32x2_t{pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
   }
 }
 template <int MODE>
@@ -1210,11 +1177,12 @@ __device__ __forceinline__ void store_tiles(const StoreArgs a, const StoreStride
         const uint32_t ldc_b = (uint32_t)a.ldc * esz;
         char* tile_base = Cb + (t.row0 * a.ldc + t.col0) * esz;
         if constexpr (!KMAJOR) {
-          // A lane's column blocks are neighbouring columns c, c + 1, .., stored as one unit: 16 bytes of bf16 from eight
-          // blocks; 16 lanes cover 256 consecutive bytes of a row -- whole 128-byte lines with no cross-lane traffic (stores
-          // that split a line over lanes of different rows measured ~0.5 ms per GB slower).  The number of columns is a
-          // multiple of 4, of 8 for bf16 (checked on the host): only a group of six can be cut, and goes pair by pair.
-          const int c = lp.col_near(nb), left = t.rowsB - c;
+          // A lane's four column blocks are neighbouring columns c .. c + 3, stored as one unit, 8 bytes of bf16; 16 lanes
+          // cover 128 consecutive bytes of a row -- whole lines with no cross-lane traffic (stores that split a line over
+          // lanes of different rows measured ~0.5 ms per GB slower).  The number of columns is a multiple of 4 (checked on the
+          // host), so no unit is cut.
+          static_assert(nb == 4, "a unit of four columns");
+          const int c = lp.col_near(nb);
           uint32_t lane_off = (uint32_t)row_l * ldc_b + (uint32_t)c * esz;
           asm volatile("" : "+v"(lane_off));
 #pragma unroll
@@ -1224,21 +1192,13 @@ __device__ __forceinline__ void store_tiles(const StoreArgs a, const StoreStride
             for (int r = 0; r < 4; ++r) {
               const int rel = i * 16 + r;
               const int rib = row_l + rel;
-              if (rib < t.rowsA && left > 0) {
+              if (rib < t.rowsA && c < t.rowsB) {
                 char* q = scatter ? Cb + ((int64_t)a.c_rows[t.row0 + rib] * a.ldc + t.col0 + c) * esz
                                   : tile_base + (lane_off + (uint32_t)rel * ldc_b);
                 float x[nb];
 #pragma unroll
                 for (int j = 0; j < nb; ++j) x[j] = acc[i][j][r];
-                if (nb != 6 || left >= nb) {
-                  store_final<MODE>(q, x);
-                } else {
-#pragma unroll
-                  for (int j = 0; j < nb; j += 2) {
-                    const float pair[2] = {x[j], x[j + 1]};
-                    if (left >= j + 2) store_final<MODE>(q + j * esz, pair);
-                  }
-                }
+                store_final<MODE>(q, x);
               }
             }
           }
