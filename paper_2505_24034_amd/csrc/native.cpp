@@ -104,9 +104,9 @@ struct CallStream {
     if (before) c10::impl::VirtualGuardImpl(c10::DeviceType::CUDA).exchangeStream(*before);
   }
   // an output may be read on the caller's current stream, and freed while it is
-  void returns(std::initializer_list<at::Tensor> ts) const {
-    if (before)
-      for (const at::Tensor& t : ts) t.record_stream(*before);
+  template <typename... Ts>
+  void returns(const Ts&... ts) const {
+    if (before) (ts.record_stream(*before), ...);
   }
 };
 int64_t integer(PyObject* o) {
@@ -196,7 +196,7 @@ PyObject* token_logprobs(PyObject* const* a) {
     return llamarl_token_logprobs(ptr(x.H), ptr(x.W), ptr<int32_t>(x.targets), ptr<uint8_t>(mask), x.N, x.d, x.V, x.dt,
                                   ptr<float>(logp), ptr<float>(lse), ptr(ws), (size_t)ws.numel(), st.handle);
   }));
-  st.returns({logp, lse});
+  st.returns(logp, lse);
   return tuple({logp, lse});
 }
 
@@ -215,7 +215,7 @@ PyObject* token_logprobs_partial(PyObject* const* a) {
                                           V_total, x.dt, ptr<float>(m), ptr<float>(s), ptr<float>(zt), ptr(ws),
                                           (size_t)ws.numel(), st.handle);
   }));
-  st.returns({m, s, zt});
+  st.returns(m, s, zt);
   return tuple({m, s, zt});
 }
 
@@ -230,7 +230,7 @@ PyObject* merge_partials(PyObject* const* a) {
     return llamarl_merge_partials(ptr<float>(m), ptr<float>(s), ptr<float>(zt), (int)shards, N, ptr<float>(logp), ptr<float>(lse),
                                   st.handle);
   }));
-  st.returns({logp, lse});
+  st.returns(logp, lse);
   return tuple({logp, lse});
 }
 
@@ -261,7 +261,7 @@ PyObject* offpolicy_loss_fwd(PyObject* const* a) {
                                       ptr<int32_t>(targets), V, B, T, &p, ptr<float>(loss), ptr<float>(coef),
                                       ptr<float>(stats), ptr(ws), (size_t)ws.numel(), st.handle);
   }));
-  st.returns({loss, coef, stats});
+  st.returns(loss, coef, stats);
   return tuple({loss, coef, stats});
 }
 
@@ -301,8 +301,8 @@ PyObject* offpolicy_loss_bwd(PyObject* const* a) {
                                                 grad_loss, x.N, x.d, x.V, x.dt, ptr(dH), ptr(dW), dW_dt, accumulate, ptr(ws),
                                                 (size_t)ws.numel(), st.handle);
   }));
-  if (a[9] == Py_None) st.returns({dH});
-  if (a[7] == Py_None) st.returns({dW});
+  if (a[9] == Py_None) st.returns(dH);
+  if (a[7] == Py_None) st.returns(dW);
   return tuple({dH, dW});
 }
 
@@ -321,7 +321,7 @@ PyObject* offpolicy_loss_bwd_slice(PyObject* const* a) {
                                             grad_loss, x.N, x.d, x.V, v0, x.dt, ptr(dH), ptr(dW), dtype_code(dW), 0, ptr(ws),
                                             (size_t)ws.numel(), st.handle);
   }));
-  st.returns({dH, dW});
+  st.returns(dH, dW);
   return tuple({dH, dW});
 }
 
@@ -358,7 +358,7 @@ PyObject* offpolicy_loss_bwd_device_scale(PyObject* const* a) {
     }
     if (!std::isfinite(*on_host.data_ptr<float>())) invalid("grad_loss must be finite");
   }
-  st.returns({dH, dW});
+  st.returns(dH, dW);
   return tuple({dH, dW});
 }
 
@@ -373,7 +373,7 @@ PyObject* group_advantages(PyObject* const* a) {
   const CallStream st(a[4], r);
   const at::Tensor adv = empty(r, r.sizes());
   check(unlocked([&] { return llamarl_group_advantages(ptr<float>(r), r.numel() / n, n, std, eps, ptr<float>(adv), st.handle); }));
-  st.returns({adv});
+  st.returns(adv);
   return THPVariable_Wrap(adv);
 }
 
@@ -392,7 +392,7 @@ PyObject* kl_shaped_rewards(PyObject* const* a) {
     return llamarl_kl_shaped_rewards(ptr<float>(r), ptr<float>(logp), ptr<float>(base), ptr<uint8_t>(mask), B, logp.numel() / B,
                                      lambda, ptr<float>(shaped), ptr<float>(kl), st.handle);
   }));
-  st.returns({shaped, kl});
+  st.returns(shaped, kl);
   return tuple({shaped, kl});
 }
 
