@@ -5,8 +5,8 @@ in include/llamarl.h) and the statistics; `loss.backward()` fills `H.grad` and `
 `llamarl_offpolicy_loss_fwd`, keeps `lse` and `coef`, and the backward hands them to the library.
 
 The upstream gradient of the loss is read by the kernels where autograd left it, on the device.  `backward` (through
-csrc/native.cpp) also copies it to the host and refuses one that is not finite, but enqueues the kernels first: waiting for the copy before
-launching them left the GPU idle for the whole launch sequence (a third of a small model's step)."""
+csrc/native.cpp) also copies it to the host and refuses one that is not finite, but enqueues the kernels first: waiting
+for the copy before launching them left the GPU idle for the whole launch sequence (a third of a small model's step)."""
 import torch
 
 from . import binding as L

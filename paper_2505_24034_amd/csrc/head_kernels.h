@@ -16,7 +16,7 @@
 // lane's own registers and finish with two cross-lane steps (lane groups l/16 hold different rows).
 //
 // Every kernel is a template over its main loop G (TileGemm, TileGemmSmall, TileGemmTN), which brings element type,
-// tile shape and LDS size; llamarl.hip picks the loop.
+// tile shape and LDS size; the rules of tile_rules.h pick the loop.
 #pragma once
 #include "gemm_nt.h"
 #include "gemm_small.h"
@@ -155,9 +155,8 @@ struct LogitsTile {
 // What a tile of the logits kernels needs per token goes through LDS, a word a list position: list 0 the token rows of the
 // NEXT tile's columns, further lists this tile's words out of arrays by token (targets; lse, coef), fetched with the tile's first
 // slabs -- their rows came with the tile before -- and there when its main loop starts: no global load stands between two
-// tiles.  Loaded at the boundary, through the row list, they
-// were two dependent trips to memory; with accumulators that are not cleared, requests spread over the epilogue and no
-// wait but the loop's own, a tile of 10188 tokens x 128256 entries takes 1.1 - 2 us less (forward / dz: d = 256 900 / 1015
+// tiles.  Loaded at the boundary, through the row list, they were two dependent trips to memory; with accumulators that are
+// not cleared, requests spread over the epilogue and no wait but the loop's own, a tile of 10188 tokens x 128256 entries takes 1.1 - 2 us less (forward / dz: d = 256 900 / 1015
 // -> 817 / 909 us, 696 1945 / 1970 -> 1785 / 1830, 1024 2240 / 2388 -> 2128 / 2277, 4096 -0.7 / -0.4 %).
 // Positions past the list repeat its last word.
 template <typename S, int LISTS>
@@ -426,7 +425,8 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
     }
   }
   G g;
-  sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);             // token tiles that hold active rows only
+  // token tiles that hold active rows only
+  sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
   if (!sch.has_tile()) return;                       // block-uniform
   fwd_tiles<G, G::Shape::NB>(a, g, sch, n_act, smem);
 }
@@ -968,9 +968,8 @@ struct StorePlan {
     rem = T - whole;
     // split factor of the tail: the one that makes the tail shortest -- ceil(rem s / G) rounds of nk / s slabs each, the
     // traffic of the rem s partial blocks and the reduction's launch -- among those that keep four K slabs per part
-    // and at most STORE_TAIL_ROUNDS rounds of parts, for which the workspace has room; the smallest such factor on ties.  Counting rounds alone cut the
-    // dW of (N, V, d) = (7000, 33001, 1032) into 931 parts (0.5 GB of blocks): 515 us
-    // instead of 487; (3000, 60000, 1504) 545 instead of 485, (4000, 128256, 2560) 2022 instead of 1944.
+    // and at most STORE_TAIL_ROUNDS rounds of parts, for which the workspace has room; the smallest such factor on ties.
+    // Counting rounds alone cut the dW of (N, V, d) = (7000, 33001, 1032) into 931 parts (0.5 GB of blocks): 515 us instead of 487; (3000, 60000, 1504) 545 instead of 485, (4000, 128256, 2560) 2022 instead of 1944.
     // One factor a lane, cost and factor in one word: 31 factors one after the other, two divisions each, took 6 us.
     const int sp = (threadIdx.x & 31) + 1;             // STORE_MAX_SPLITS lanes
     const int rounds = (rem * sp + G - 1) / G;

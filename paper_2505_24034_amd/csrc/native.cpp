@@ -2,8 +2,9 @@
 //
 // A call of the binding on a small batch is host-bound: attribute look-ups, a Python object per output and ctypes' conversion
 // of sixteen arguments were most of it.  Host time of a call, in Python with ctypes / here: the loss at 16384 tokens 14.6 /
-// 8.9 us, rewards and advantages (two calls) 13.2 / 8.7, aipo_loss 35 / 23, a whole step 192 / 147.  Each entry takes positional arguments (binding.py fills in defaults) and talks to the C ABI of include/llamarl.h.  Every call
-// allocates what it returns; nothing is kept between calls.
+// 8.9 us, rewards and advantages (two calls) 13.2 / 8.7, aipo_loss 35 / 23, a whole step 192 / 147.  Each entry takes
+// positional arguments (binding.py fills in defaults) and talks to the C ABI of include/llamarl.h.  Every call allocates what
+// it returns; nothing is kept between calls.
 //
 // Errors: a check or a status that is not LLAMARL_OK raises binding.LlamarlError(status, message); C++ exceptions become the
 // Python exceptions torch itself raises for them.

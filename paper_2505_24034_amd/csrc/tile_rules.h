@@ -15,9 +15,8 @@ namespace llamarl {
 // the XCDs: 4 and 8 tie (2: +1 %).
 constexpr int PATCH_ROWS_LOGITS = 4;
 
-// Persistent tile schedule.  The grid has one workgroup per CU (every tile is taken once by a grid of any size; tests/
-// test_tile_rules.py walks them on the CPU); the hardware deals workgroups
-// round-robin to the 8 XCDs, each with a private L2.  Tile ids are ordered so that 32 consecutive ones form a patch
+// Persistent tile schedule.  The grid has one workgroup per CU (every tile is taken once by a grid of any size;
+// tests/test_tile_rules.py walks them on the CPU); the hardware deals workgroups round-robin to the 8 XCDs, each with a private L2.  Tile ids are ordered so that 32 consecutive ones form a patch
 // (group_m x 32/group_m tiles) that shares A and B panels; the workgroups of one XCD take one patch at a time, so
 // those panels are shared in its L2, and the eight patches in flight on the chip are consecutive in id order, so
 // they share panels through the Infinity Cache (against giving every XCD a contiguous eighth of the ids: -3.5 %
@@ -67,8 +66,8 @@ struct TileSchedule {
     tn = gsize == GROUP_M ? in_group / GROUP_M : in_group / gsize;
     tm = first_m + in_group - tn * gsize;
     // Where a round of the grid is a whole number of groups, a workgroup would get the same column in every round:
-    // turn the columns by one a round (a whole group is in one round, so each of its tiles is still taken once), so that nobody is left with all the narrow last columns (two columns, 300
-    // tokens: half of the workgroups had four full tiles, the other half four of 44 tokens).
+    // turn the columns by one a round (a whole group is in one round, so each of its tiles is still taken once), so that
+    // nobody is left with all the narrow last columns (two columns, 300 tokens: half of the workgroups had four full tiles, the other half four of 44 tokens).
     if (turn) tn = (tn + round) % tiles_n;
     ++round;
     next_id += stride;

@@ -107,6 +107,21 @@ def test_narrow_gradient_tiles(lib, N, V, d):
     _check_head(lib, N, V, d)
 
 
+# dz^T is written as far as dW reads it, the next 32 active rows: with NaN in what nothing writes, the gradients are the same
+@pytest.mark.parametrize("N,V,d,expected", [(129, 49200, 72, "256x160 64 128"), (160, 49200, 520, "256x160 64 256"),
+                                            (450, 33000, 1032, "256x160 256 256"), (97, 49200, 264, "256x128 64 256"),
+                                            (65, 900, 64, "64 64 64"), (400, 8065, 64, "128 64 64")])
+def test_dz_past_what_is_written(lib, N, V, d, expected):
+    assert " ".join(loops(N, V, d)[1:]) == expected
+    H, W, t, coef = _inputs(N, V, d, N + d)
+    H, W = H.bfloat16(), W.bfloat16()
+    _, lse = lib.token_logprobs(H, W, t)
+    plain = lib.offpolicy_loss_bwd(H, W, t, lse, coef)
+    ws = torch.full((lib.workspace_bytes(N, d, V, lib.BF16, lib.PASS_LOSS_BWD),), 255, dtype=torch.uint8, device="cuda")
+    poisoned = lib.offpolicy_loss_bwd(H, W, t, lse, coef, ws=ws)
+    assert all(torch.equal(a, b) for a, b in zip(plain, poisoned))
+
+
 # dH in up to 32 parts a tile: 64-, 128- and 256-tiles, a last round that fills every XCD and one that does not
 @pytest.mark.parametrize("N,V,d,edge", [(1, 70000, 64, "64"), (64, 40000, 512, "64"), (129, 33000, 520, "64"), (300, 70000, 264, "64"),
                                         (300, 70000, 1032, "256"), (520, 60000, 776, "256"), (140, 20000, 2048, "128")])
