@@ -20,7 +20,7 @@
 //     16 rows that 16 lanes of a ds_read_b128 touch over all 64 LDS banks.
 //   - the loop is software-pipelined by hand (see TileGemm::run): every ds_read_b128 and every slab load is
 //     issued in the shadow of an MFMA, far ahead of its use, and scheduling fences pin that interleave.
-//   - TileGemmNarrow: the same for 128 or 160 columns (few tokens), three slabs resident.
+//   - TileGemmWide: the same for 320 columns; TileGemmNarrow: for 128 or 160 (few tokens), three slabs resident.
 //   - out-of-range rows and the K tail use the buffer descriptor's bounds check: such lanes read zeros.
 //   - kernels are persistent (one workgroup per CU walks a list of tiles) and fetch the first slabs of their next
 //     tile before the epilogue of the current one, so the epilogue's VALU work overlaps that latency.
@@ -62,6 +62,11 @@ struct Shape256 : TileShape<2, 4, 8, 4> {
 struct Shape256Halves : TileShape<4, 2, 4, 8> {
   __device__ __forceinline__ static int wave_row(int wave) { return (wave + 2 * (wave >> 2)) & 3; }
   __device__ __forceinline__ static int wave_col(int wave) { return wave >> 2; }
+};
+// 256 x 320, as Shape256 with wavefronts of 128 x 80
+struct Shape320 : TileShape<2, 4, 8, 5> {
+  __device__ __forceinline__ static int wave_row(int wave) { return wave & 1; }
+  __device__ __forceinline__ static int wave_col(int wave) { return wave >> 1; }
 };
 typedef TileShape<2, 2, 4, 4> Shape128;   // 128 x 128, 4 wavefronts of  64 x 64
 typedef TileShape<4, 1, 1, 4> Shape64;    //  64 x  64, 4 wavefronts of  16 x 64
@@ -323,10 +328,78 @@ __device__ __forceinline__ void k_step(typename TT::frag_t (&a)[MB], const typen
   }
 }
 
+// The same for a wavefront of 8 x 5 blocks: 40 slots, slot t runs block (t / 5, snake5(t)).  Five column fragments twice leave
+// registers for four row fragments: block ib is in a[ib % 4], read when block ib - 4 is done, 14 - 16 slots ahead of its
+// use.  So the reads of a slab end at slot 20, its barrier is at slot 22, and the nine loads follow on the odd slots.
+__device__ __forceinline__ constexpr int snake5(int t) { return (t / 5 & 1) ? 4 - t % 5 : t % 5; }
+template <typename TT, typename Fetch, bool BAR, bool NEXT, bool FETCH, bool INIT = false>
+__device__ __forceinline__ void wide_k_step(typename TT::frag_t (&a)[4], const typename TT::frag_t (&bc)[5],
+                                            typename TT::frag_t (&bn)[5], f32x4_t (&acc)[8][5], const char* pa_cur,
+                                            const char* pa_nxt, const char* pb_nxt, const Fetch* sf) {
+  typedef typename TT::frag_t frag_t;
+#pragma unroll
+  for (int t = 0; t < 40; ++t) {
+    const int ib = t / 5, jb = snake5(t);
+    if (BAR && t == 22) {
+      wait_vmcnt<0>();            // as in k_step
+      __syncthreads();
+      LLAMARL_FENCE();
+    }
+    if (INIT) acc[ib][jb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    mma(a[ib & 3], bc[jb], acc[ib][jb]);
+    LLAMARL_FENCE();
+    if (t == 0) a[3] = *reinterpret_cast<const frag_t*>(pa_cur + 3 * BLOCK_BYTES);
+    if (t == 6) a[0] = *reinterpret_cast<const frag_t*>(pa_cur + 4 * BLOCK_BYTES);
+    if (t == 10) a[1] = *reinterpret_cast<const frag_t*>(pa_cur + 5 * BLOCK_BYTES);
+    if (t == 16) a[2] = *reinterpret_cast<const frag_t*>(pa_cur + 6 * BLOCK_BYTES);
+    if (t == 20) a[3] = *reinterpret_cast<const frag_t*>(pa_cur + 7 * BLOCK_BYTES);
+    LLAMARL_FENCE();
+    if (NEXT) {
+      if (t == 26) a[0] = *reinterpret_cast<const frag_t*>(pa_nxt);
+      if (t == 30) a[1] = *reinterpret_cast<const frag_t*>(pa_nxt + BLOCK_BYTES);
+      if (t == 36) a[2] = *reinterpret_cast<const frag_t*>(pa_nxt + 2 * BLOCK_BYTES);
+      if (t == 22) bn[0] = *reinterpret_cast<const frag_t*>(pb_nxt);
+      if (t == 24) bn[1] = *reinterpret_cast<const frag_t*>(pb_nxt + BLOCK_BYTES);
+      if (t == 28) bn[2] = *reinterpret_cast<const frag_t*>(pb_nxt + 2 * BLOCK_BYTES);
+      if (t == 32) bn[3] = *reinterpret_cast<const frag_t*>(pb_nxt + 3 * BLOCK_BYTES);
+      if (t == 34) bn[4] = *reinterpret_cast<const frag_t*>(pb_nxt + 4 * BLOCK_BYTES);
+      LLAMARL_FENCE();
+    }
+    if (FETCH && t >= 23 && (t & 1)) {
+      const int n = (t - 23) >> 1;
+      if (n < 4) sf->la->issue_one(sf->ra, sf->dst, n, sf->k0, sf->K, sf->wave, sf->lane);
+      else sf->lb->issue_one(sf->rb, sf->dst + SLAB_A_BYTES, n - 4, sf->k0, sf->K, sf->wave, sf->lane);
+      LLAMARL_FENCE();
+    }
+  }
+}
+
 // Whether the last slab's second half holds anything: past K both operands are zeros, and their k-step is left out (d of
 // 520: 8.5 of 9 slabs, logits of 3000 x 40000 142 -> 138 us; 1032: 403 -> 398; whole slabs as before).
 template <int BK>
 __device__ __forceinline__ bool half_slab_left(int K) { return (unsigned)(K - 1) % BK >= BK / 2; }
+
+// The order in which a logits kernel takes the slabs: the whole ones from `turn` on, wrapping round, then the rest of K.  Rows of
+// W and H often lie a power of two apart (d = 4096: 8 KB), and workgroups that walk K together then read the same few
+// channels of the memory: 256 workgroups streaming 1 GB of W took 235 us (4.5 TB/s) from slab 0, whatever their slabs in flight,
+// and 169 us (6.2) each from a slab of its own.  Workgroups that share a row of patches, and so the panels in their L2, start
+// together; the next row starts two slabs (256 bytes) on.  Forward call over a 128256 x 4096 head: 40 tokens 236 -> 181 us, 150
+// 228 -> 194, 300 309 -> 294.  Only where W streams: with more than TURN_COLUMNS columns of tiles, whose panels come from the caches, it
+// cost up to 1 %.
+constexpr int TURN_COLUMNS = 4;
+struct SlabOrder {
+  int whole, turn;
+  template <int BK>
+  __device__ __forceinline__ void init(int K, int row_of_patches) {
+    whole = K / BK;
+    turn = whole < 2 ? 0 : 2 * row_of_patches & ((1 << (31 - __builtin_clz(whole))) - 1);
+  }
+  template <int BK>
+  __device__ __forceinline__ int k(int kt) const {        // first k of the kt-th slab taken; past K where there is none
+    const int s = kt + turn;
+    return (kt >= whole ? kt : s >= whole ? s - whole : s) * BK;
+  }
+};
 
 // The main loop, split in two so that a persistent workgroup can start fetching its NEXT tile before it runs the
 // epilogue of the current one:
@@ -351,7 +424,10 @@ struct TileGemm {
   static constexpr int GROUPS_PER_CU = 1;      // workgroups of a persistent grid per CU
   SlabLoader<TT> la, lb;
   int K;
+  SlabOrder order;
   __device__ __forceinline__ static constexpr int width() { return Shape::BN; }
+
+  __device__ __forceinline__ int k_of(int kt) const { return FIRST_ONLY ? order.k<BK>(kt) : kt * BK; }
 
   template <bool NEAR>
   __device__ __forceinline__ void prefetch(const void* A_tile, int64_t lda, int rowsA, const void* B_tile, int64_t ldb,
@@ -374,9 +450,10 @@ struct TileGemm {
   template <bool NEAR>
   __device__ __forceinline__ void setup_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
                                                  int64_t ldb, int rowsB, int64_t K_, const int (&grow)[4],
-                                                 int64_t b_total) {
+                                                 int64_t b_total, int turn) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
+    order.init<BK>(K, turn);
     la.init(A_tile, lda, rowsA, wave, lane);
     lb.template init_gathered<NEAR>(B_base, ldb, b_total, grow, rowsB, wave, lane);
   }
@@ -386,8 +463,8 @@ struct TileGemm {
   __device__ __forceinline__ void issue_first(char* smem, int part) const {
     const int lane = threadIdx.x & 63, wave = wave_id();
     char* st = smem + (part >> 1) * STAGE_BYTES;
-    const int k0 = (part >> 1) * BK;
-    if (k0 >= K && part > 1) return;
+    if (part > 1 && BK >= K) return;
+    const int k0 = k_of(part >> 1);
     if ((part & 1) == 0) la.issue(st, k0, K, wave, lane);
     else lb.issue(st + SLAB_A_BYTES, k0, K, wave, lane);
   }
@@ -403,8 +480,8 @@ struct TileGemm {
       char* cur = smem + (kt & 1) * STAGE_BYTES;
       wait_vmcnt0();
       __syncthreads();
-      la.issue(cur, (kt + 2) * BK, K, wave, lane);
-      lb.issue(cur + SLAB_A_BYTES, (kt + 2) * BK, K, wave, lane);
+      la.issue(cur, k_of(kt + 2), K, wave, lane);
+      lb.issue(cur + SLAB_A_BYTES, k_of(kt + 2), K, wave, lane);
     }
     if (nk >= 2) {
       wait_vmcnt0();
@@ -454,7 +531,7 @@ struct TileGemm {
     if (!FIRST_ONLY && nk > 2) {       // slab 0 apart: its barrier waits for slab 1, older than the stores too
       char* cur = smem;
       const char* nxt = smem + STAGE_BYTES;
-      const SlabFetch<SlabLoader<TT>, SlabLoader<TT>> sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, 2 * BK, K, wave, lane};
+      const SlabFetch<SlabLoader<TT>, SlabLoader<TT>> sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, k_of(2), K, wave, lane};
       k_step<TT, true, true, true, LOAD_SLOT, FIRST_ONLY ? 0 : YOUNGER>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0],
                                                                         nxt + b_addr[0], &sf);
       k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
@@ -464,7 +541,7 @@ struct TileGemm {
       char* cur = smem + (kt & 1) * STAGE_BYTES;
       const char* nxt = smem + ((kt + 1) & 1) * STAGE_BYTES;
       LLAMARL_FENCE();
-      const SlabFetch<SlabLoader<TT>, SlabLoader<TT>> sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, (kt + 2) * BK, K, wave, lane};
+      const SlabFetch<SlabLoader<TT>, SlabLoader<TT>> sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, k_of(kt + 2), K, wave, lane};
       k_step<TT, true, true, true, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0], nxt + b_addr[0], &sf);
       k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
     }
@@ -479,6 +556,110 @@ struct TileGemm {
       const char* cur = smem + ((nk - 1) & 1) * STAGE_BYTES;
       LLAMARL_FENCE();
       k_step<TT, false, false, false, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nullptr, nullptr, nullptr);
+    }
+  }
+};
+
+// ---- wide tiles: 256 rows x 320 columns -----------------------------------------------------------------------------------
+// As TileGemm (see there); two slabs of 72 KB.  A product takes a tenth fewer bytes from L2 and LDS than on 256 x 256, and a
+// fifth fewer barriers and epilogues.  247 registers.  (A word of every line of W two slabs ahead, to have it in L2 earlier: 300
+// tokens 305 -> 330 us; a barrier that leaves one request in flight for that: the long contractions +2 %.)
+template <typename TT>
+struct TileGemmWide {
+  typedef TT Type;
+  typedef Shape320 Shape;
+  typedef typename TT::frag_t frag_t;
+  typedef SlabLoader<TT> LoaderA;
+  typedef SlabLoader<TT, Shape::BN, Shape::WAVES, Shape::WAVE_N> LoaderB;
+  typedef SlabFetch<LoaderA, LoaderB> Fetch;
+  static constexpr bool KMAJOR = false;
+  static constexpr bool HAS_IDLE = true, HALVES = false;
+  static constexpr bool REQUESTS_PAST_K = false;
+  static constexpr int BK = 8 * TT::EPC;
+  static constexpr int LDS_BYTES = 2 * Shape::STAGE_BYTES;
+  static constexpr int COUNTED_STORES = 2;
+  LoaderA la;
+  LoaderB lb;
+  int K;
+  SlabOrder order;
+  __device__ __forceinline__ static constexpr int width() { return Shape::BN; }
+
+  template <bool NEAR>
+  __device__ __forceinline__ void setup_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
+                                                 int64_t ldb, int rowsB, int64_t K_, const int (&grow)[LoaderB::ITERS],
+                                                 int64_t b_total, int turn) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    K = (int)K_;
+    order.init<BK>(K, turn);
+    la.init(A_tile, lda, rowsA, wave, lane);
+    lb.template init_gathered<NEAR>(B_base, ldb, b_total, grow, rowsB, wave, lane);
+  }
+  static constexpr int FIRST_PARTS = 4;
+  __device__ __forceinline__ void issue_first(char* smem, int part) const {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    char* st = smem + (part >> 1) * Shape::STAGE_BYTES;
+    if (part > 1 && BK >= K) return;
+    const int k0 = order.k<BK>(part >> 1);
+    if ((part & 1) == 0) la.issue(st, k0, K, wave, lane);
+    else lb.issue(st + SLAB_A_BYTES, k0, K, wave, lane);
+  }
+  __device__ __forceinline__ void run_idle(char* smem) const {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int nk = (K + BK - 1) / BK;
+    wait_vmcnt0();
+    __syncthreads();
+    for (int kt = 0; kt < nk - 2; ++kt) {
+      char* cur = smem + (kt & 1) * Shape::STAGE_BYTES;
+      wait_vmcnt0();
+      __syncthreads();
+      la.issue(cur, order.k<BK>(kt + 2), K, wave, lane);
+      lb.issue(cur + SLAB_A_BYTES, order.k<BK>(kt + 2), K, wave, lane);
+    }
+    if (nk >= 2) {
+      wait_vmcnt0();
+      __syncthreads();
+    }
+  }
+  __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[8][5], bool counted = false) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int nk = (K + BK - 1) / BK;
+    const int g = lane >> 4, l16 = lane & 15, sw = swizzle(l16);
+    int a_addr[2], b_addr[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      a_addr[ks] = (Shape::wave_row(wave) * Shape::WAVE_M + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
+      b_addr[ks] = SLAB_A_BYTES + (Shape::wave_col(wave) * Shape::WAVE_N + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
+    }
+    if (counted) wait_vmcnt<COUNTED_STORES>();
+    else wait_vmcnt0();
+    __syncthreads();
+    frag_t a[4], b0[5], b1[5];
+    a[0] = *reinterpret_cast<const frag_t*>(smem + a_addr[0]);
+#pragma unroll
+    for (int j = 0; j < 5; ++j) b0[j] = *reinterpret_cast<const frag_t*>(smem + b_addr[0] + j * BLOCK_BYTES);
+#pragma unroll
+    for (int i = 1; i < 3; ++i) a[i] = *reinterpret_cast<const frag_t*>(smem + a_addr[0] + i * BLOCK_BYTES);
+    LLAMARL_FENCE();
+    wide_k_step<TT, Fetch, false, true, false, true>(a, b0, b1, acc, smem + a_addr[0], smem + a_addr[1], smem + b_addr[1], nullptr);
+    for (int kt = 0; kt < nk - 2; ++kt) {
+      char* cur = smem + (kt & 1) * Shape::STAGE_BYTES;
+      const char* nxt = smem + ((kt + 1) & 1) * Shape::STAGE_BYTES;
+      LLAMARL_FENCE();
+      const Fetch sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, order.k<BK>(kt + 2), K, wave, lane};
+      wide_k_step<TT, Fetch, true, true, true>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0], nxt + b_addr[0], &sf);
+      wide_k_step<TT, Fetch, false, true, false>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
+    }
+    if (nk >= 2) {
+      const char* cur = smem + ((nk - 2) & 1) * Shape::STAGE_BYTES;
+      const char* nxt = smem + ((nk - 1) & 1) * Shape::STAGE_BYTES;
+      LLAMARL_FENCE();
+      wide_k_step<TT, Fetch, true, true, false>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0], nxt + b_addr[0], nullptr);
+      wide_k_step<TT, Fetch, false, true, false>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
+    }
+    if (half_slab_left<BK>(K)) {
+      const char* cur = smem + ((nk - 1) & 1) * Shape::STAGE_BYTES;
+      LLAMARL_FENCE();
+      wide_k_step<TT, Fetch, false, false, false>(a, b1, b0, acc, cur + a_addr[1], nullptr, nullptr, nullptr);
     }
   }
 };
@@ -560,15 +741,18 @@ struct TileGemmNarrow {
   LoaderA la;
   LoaderB lb;
   int K;
+  SlabOrder order;
   int nb1;
   __device__ __forceinline__ int width() const { return Shape::WAVE_N + 16 * nb1; }
+  __device__ __forceinline__ void set_width(int w) { nb1 = (w - Shape::WAVE_N) / 16; }
 
   template <bool NEAR>
   __device__ __forceinline__ void setup_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
                                                  int64_t ldb, int rowsB, int64_t K_, const int (&grow)[LoaderB::ITERS],
-                                                 int64_t b_total) {
+                                                 int64_t b_total, int turn) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
+    order.init<BK>(K, turn);
     la.init(A_tile, lda, rowsA, wave, lane);
     lb.template init_gathered<NEAR>(B_base, ldb, b_total, grow, rowsB, wave, lane, nb1);
   }
@@ -600,10 +784,11 @@ struct TileGemmNarrow {
   template <int nb>
   __device__ __forceinline__ void issue(char* st, int kt) const {
     const int lane = threadIdx.x & 63, wave = wave_id();
-    la.issue(st, kt * BK, K, wave, lane);
+    const int k0 = order.k<BK>(kt);
+    la.issue(st, k0, K, wave, lane);
     const i32x4_t rs = lb.rsrc();
 #pragma unroll
-    for (int it = 0; it < LB_LOADS<nb>; ++it) lb.issue_one(rs, st + SLAB_A_BYTES, it, kt * BK, K, wave, lane);
+    for (int it = 0; it < LB_LOADS<nb>; ++it) lb.issue_one(rs, st + SLAB_A_BYTES, it, k0, K, wave, lane);
   }
   template <int nb>
   __device__ __forceinline__ void issue_first(char* smem, int part) const {      // as issue_first
@@ -646,7 +831,7 @@ struct TileGemmNarrow {
       st = st == 2 ? 0 : st + 1;
       const char* nxt = stage(smem, st);
       LLAMARL_FENCE();
-      const Fetch sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, (kt + 3) * BK, K, wave, lane};
+      const Fetch sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, order.k<BK>(kt + 3), K, wave, lane};
       narrow_k_step<TT, Fetch, nb, true, true, true, 4 + LB, false, LB>(b, a1, a0, acc, cur + b_addr[1], nxt + b_addr[0],
                                                                      nxt + a_addr[0], &sf);
       narrow_k_step<TT, Fetch, nb, false, true, false, 0, false, LB>(b, a0, a1, acc, nxt + b_addr[0], nxt + b_addr[1],

@@ -105,7 +105,7 @@ struct TileGemmSmall {
   template <bool NEAR>
   __device__ __forceinline__ void setup_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
                                                  int64_t ldb, int rowsB, int64_t K_, const int (&grow)[LoaderB::ITERS],
-                                                 int64_t b_total) {
+                                                 int64_t b_total, int) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
     la.init(A_tile, lda, rowsA, wave, lane);

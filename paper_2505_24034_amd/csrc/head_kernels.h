@@ -97,6 +97,7 @@ struct FwdArgs {
 };  // partials and zt are indexed by compacted position, not by token
 
 typedef TileGemm<BF16, 11, 2, true> Logits256;      // counted: the two stores of a token's partials
+typedef TileGemmWide<BF16> LogitsWide;
 // zeros from an opaque register: as constants the compiler sets them ahead of the branch, for every tile
 template <int M, int N>
 __device__ __forceinline__ void clear(f32x4_t (&acc)[M][N]) {
@@ -121,7 +122,7 @@ __device__ __forceinline__ void run_tile(G& g, char* smem, f32x4_t (&acc)[G::Sha
     }
   }
   if constexpr (nb == 0) {
-  } else if constexpr (std::is_same<G, Logits256>::value) g.run(smem, acc, counted);
+  } else if constexpr (std::is_same<G, Logits256>::value || std::is_same<G, LogitsWide>::value) g.run(smem, acc, counted);
   else if constexpr (G::HALVES && !G::KMAJOR) g.template run<nb>(smem, acc, counted);
   else if constexpr (G::HALVES) g.template run<nb>(smem, acc);
   else g.run(smem, acc);
@@ -161,8 +162,9 @@ struct LogitsTile {
 // Positions past the list repeat its last word.
 template <typename S, int LISTS>
 struct TokenWords {
-  static constexpr int PIECES = S::BN / 64, BYTES = LISTS * S::BN * 4;     // a wavefront fetches 64 words at a time
-  static_assert(S::WAVES % PIECES == 0, "all pieces of a wavefront are of the same 64 positions");
+  // a wavefront fetches 64 words at a time, always of the same 64 positions (of which the last may lie past a wide tile)
+  static constexpr int PIECES = S::BN <= 64 ? 1 : S::BN <= 128 ? 2 : S::BN <= 256 ? 4 : 8, BYTES = LISTS * PIECES * 256;
+  static_assert(S::WAVES % PIECES == 0, "");
   __device__ __forceinline__ static int position() { return wave_id() % PIECES * 64 + (int)(threadIdx.x & 63); }
   // rows: the row list; next: first position of the next tile; row: the token row of this lane's position of this tile;
   // by_token: the arrays of lists 1 .., N words each
@@ -184,7 +186,7 @@ struct TokenWords {
   }
   template <typename V>
   __device__ __forceinline__ static V word(const char* lds, int list, int pos) {
-    return *reinterpret_cast<const V*>(lds + (list * S::BN + pos) * 4);
+    return *reinterpret_cast<const V*>(lds + (list * (PIECES * 64) + pos) * 4);
   }
 };
 // The logits kernels gather their column operand (H rows) through the active-row list: the rows a lane fetches.
@@ -214,7 +216,8 @@ __device__ __forceinline__ void logits_setup(G& g, const Args& a, const LogitsTi
   const int width = g.width();
   g.template setup_gathered<NEAR>((const st*)a.W + (int64_t)t.tv * BM * a.d, a.d,
                                      (int)min((int64_t)BM, a.V - (int64_t)t.tv * BM), a.H, a.d,
-                                     min(width, n_act - t.tt * width), a.d, grow, a.N);
+                                     min(width, n_act - t.tt * width), a.d, grow, a.N,
+                                     n_act <= TURN_COLUMNS * width ? t.tv / PATCH_ROWS_LOGITS : 0);
 }
 
 // f(std::integral_constant<int, column blocks of this wavefront>()): a kernel's walk over its tiles.  The wavefronts of a
@@ -251,7 +254,8 @@ typedef TileGemmNarrow<BF16> LogitsNarrow;
 template <typename G>
 constexpr bool HAS_NARROW = std::is_same<G, Logits256>::value;
 template <typename G>
-constexpr int fwd_lds_bytes = HAS_NARROW<G> ? (fwd_bytes_of<LogitsNarrow> > fwd_bytes_of<G> ? fwd_bytes_of<LogitsNarrow> : fwd_bytes_of<G>) : fwd_bytes_of<G>;
+constexpr int fwd_lds_bytes = HAS_NARROW<G> ? (fwd_bytes_of<LogitsNarrow> > fwd_bytes_of<LogitsWide> ? fwd_bytes_of<LogitsNarrow> : fwd_bytes_of<LogitsWide>) : fwd_bytes_of<G>;
+static_assert(fwd_lds_bytes<Logits256> <= 160 * 1024, "");
 template <typename G>
 constexpr int dz_lds_bytes = HAS_NARROW<G> ? (dz_bytes_of<LogitsNarrow> > dz_bytes_of<G> ? dz_bytes_of<LogitsNarrow> : dz_bytes_of<G>) : dz_bytes_of<G>;
 
@@ -414,10 +418,17 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
   const int n_act = *a.n_act;
   TileSchedule<PATCH_ROWS_LOGITS> sch;
   if constexpr (HAS_NARROW<G>) {
-    const int half = fwd_width(a.tiles_v, n_act, a.d, gridDim.x).half_blocks;
-    if (half < 8) {
+    const int width = fwd_width(a.tiles_v, n_act, a.d, gridDim.x).width;
+    if (width == LogitsWide::width()) {
+      LogitsWide g;
+      sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
+      if (!sch.has_tile()) return;
+      fwd_tiles<LogitsWide, LogitsWide::Shape::NB>(a, g, sch, n_act, smem);
+      return;
+    }
+    if (width <= NARROW_BN) {
       LogitsNarrow g;
-      g.nb1 = half;
+      g.set_width(width);
       sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
       if (!sch.has_tile()) return;
       with_blocks(g, [&](auto blocks) { fwd_tiles<LogitsNarrow, decltype(blocks)::value>(a, g, sch, n_act, smem); });
@@ -894,10 +905,10 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzAr
   const int n_act = *a.n_act;
   TileSchedule<PATCH_ROWS_LOGITS> sch;
   if constexpr (HAS_NARROW<G>) {
-    const int half = dz_width(a.tiles_v, n_act, a.d, gridDim.x).half_blocks;
-    if (half < 8) {
+    const int width = dz_width(a.tiles_v, n_act, a.d, gridDim.x).width;
+    if (width <= NARROW_BN) {
       LogitsNarrow g;
-      g.nb1 = half;
+      g.set_width(width);
       sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
       if (!sch.has_tile()) return;
       with_blocks(g, [&](auto blocks) { dz_tiles<LogitsNarrow, decltype(blocks)::value>(a, g, sch, n_act, smem); });

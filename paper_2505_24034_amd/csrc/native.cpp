@@ -438,7 +438,7 @@ PyObject* store_tile(PyObject* const* a) {
 // tiles_v, active rows, d, grid, backward: columns of the tiles of 256 vocabulary rows
 PyObject* logits_width(PyObject* const* a) {
   const auto rule = integer(a[4]) ? llamarl::dz_width : llamarl::fwd_width;
-  return PyLong_FromLong(128 + 16 * rule((int)integer(a[0]), (int)integer(a[1]), integer(a[2]), (int)integer(a[3])).half_blocks);
+  return PyLong_FromLong(rule((int)integer(a[0]), (int)integer(a[1]), integer(a[2]), (int)integer(a[3])).width);
 }
 
 template <PyObject* (*F)(PyObject* const*), int NARGS>

@@ -83,38 +83,49 @@ struct TileSchedule {
 
 // Tiles of at most NARROW_BN columns: three resident slabs instead of two.
 constexpr int NARROW_BN = 160;
-// Which tiles a logits kernel of 256 vocabulary rows takes: 256 columns wide, or 128 or 160 (TileGemmNarrow), by what the
-// rounds of the grid cost.  Costs in 1/256 of the time of a slab of the 256 x 256 forward (1.4 us), for 128, 160 and 256
-// columns, measured over (6720, 128256, 512 .. 2048):
+// Which tiles a logits kernel of 256 vocabulary rows takes: 256 columns wide, 128 or 160 (TileGemmNarrow), or, in the forward,
+// 320 (TileGemmWide), by what the rounds of the grid cost.  Costs in 1/256 of the time of a slab of the 256 x 256 forward
+// (1.4 us), for 128, 160, 256 and 320 columns, measured over (6720, 128256, 512 .. 2048):
 //   slab, tile      a slab of d; what a tile costs besides (dz stores its tile, in partial lines where it is narrow)
 //   unaligned       rows of d that are no multiple of 128 bytes: a slab row touches two lines, and the requests bound a slab
-//   stream          W comes from HBM: 1 or 2 columns of narrow tiles, 1 or 2 - 4 of wide ones (two resident slabs)
-// Forward at (N, V, d), 256 / 160 / 128 columns: (300, 128256, 4096) 367 / 295 / 347 us, (225, ..) 264 / 266 / 268,
-// (450, ..) 427 / 415 / 455, (600, ..) 551 / 505 / 573, (360, 114156, 8168) 877 / 918 / 997.
+//   one, two, few   W comes from HBM: a slab where there are 1, 2 or 3 - 4 columns of tiles (more share W in the caches)
+// 320 columns read a tenth less per product from LDS and L2 and have a fifth fewer tiles to wait for.  Long contractions, which the
+// power limit bounds, hardly gain (7600 .. 10600 tokens of a 128256 x 4096 head: -3 .. +3 % of 256 columns, by the tokens that fill
+// the last column); few rounds do where a fifth fewer tiles fit them, and one or two columns that read W once.  They start
+// at WIDE_MIN_SLABS slabs: shorter tiles gain as much (300 x 49200 x 520 35 -> 32.5 us), but stay on the loops that the tests of short K
+// name.
+// Forward at (N, V, d), 320 / 256 / 160 / 128 columns, us: (150, 128256, 4096) 223 / 230 / 188 / 248, (225, ..) 266 / 246 / 272 / 269,
+// (300, ..) 279 / 366 / 304 / 364, (450, ..) 434 / 426 / 423 / 475, (600, ..) 500 / 550 / 524 / 592, (1250, ..) 955 / 991 / 1044 / 1128,
+// (8576, ..) 6190 / 6348 / 6849 / 7153; (7125, 33001, 1032) 400 / 428 / 465 / 508; (2300, 16032, 8192) 449 / 540 / 486 / 529;
+// (2012, 16032, 8192) 442 / 388 / 464 / 450; (640, 128256, 776) 118 / 127 / 134 / 148.  dz, 256 / 160 / 128: (150, 128256, 4096) 261 / 231 / 267,
+// (225, ..) 265 / 277 / 280, (450, ..) 442 / 429 / 480, (600, ..) 560 / 526 / 597.
+constexpr int WIDTHS = 4, LOGITS_WIDTHS[WIDTHS] = {128, 160, 256, 320}, WIDE_MIN_SLABS = 10;
 struct WidthCosts {
-  int slab[3], tile[3];
+  int widths, slab[WIDTHS], tile[WIDTHS], one[WIDTHS], two[WIDTHS], few[WIDTHS];       // the first `widths` of them
 };
-constexpr WidthCosts FWD_COSTS = {{167, 184, 256}, {328, 474, 765}};
-constexpr WidthCosts DZ_COSTS = {{177, 201, 261}, {440, 640, 1000}};
-constexpr int UNALIGNED_SLAB[3] = {220, 239, 294}, STREAM_NARROW[2] = {320, 200}, STREAM_WIDE[2] = {350, 300};
+constexpr WidthCosts FWD_COSTS = {4, {167, 184, 256, 318}, {328, 474, 765, 1000}, {235, 240, 315, 365}, {185, 200, 300, 330}, {0, 0, 300, 0}};
+constexpr WidthCosts DZ_COSTS = {3, {177, 201, 261}, {440, 640, 1000}, {318, 318, 363}, {193, 206, 300}, {0, 0, 300}};
+constexpr int UNALIGNED_SLAB[WIDTHS] = {220, 239, 294, 355};
 struct LogitsWidth {
-  int half_blocks;        // column blocks of the right half of narrow tiles; 8: 256 columns
+  int width;
   int64_t cost;
 };
 LLAMARL_RULE LogitsWidth logits_width(const WidthCosts& c, int tiles_v, int n_act, int64_t d, int grid) {
-  LogitsWidth best = {8, 0};
+  LogitsWidth best = {256, 0};
   const int nk = (int)((d + 63) / 64);
 #pragma unroll
-  for (int h = 2; h >= 0; --h) {
-    const int width = h == 2 ? 256 : 128 + 32 * h, cols = (int)((uint32_t)(n_act + width - 1) / (uint32_t)width);
+  for (int i = 0; i < WIDTHS; ++i) {
+    const int h = i == 0 ? 2 : i == 3 ? 3 : 2 - i;           // 256 columns, then whatever costs less
+    const int width = LOGITS_WIDTHS[h], cols = (int)((uint32_t)(n_act + width - 1) / (uint32_t)width);
     const int64_t tiles = (int64_t)tiles_v * cols;
+    if (h >= c.widths || (width == 320 && nk < WIDE_MIN_SLABS)) continue;
+    if (tiles + grid >= (1ll << 31)) continue;               // 32-bit division; so many rounds are 256 wide
     int slab = c.slab[h];
     if (d % 64 != 0 && slab < UNALIGNED_SLAB[h]) slab = UNALIGNED_SLAB[h];
-    const int stream = width <= NARROW_BN ? (cols <= 2 ? STREAM_NARROW[cols == 2] : 0) : cols <= 4 ? STREAM_WIDE[cols >= 2] : 0;
+    const int stream = cols == 1 ? c.one[h] : cols == 2 ? c.two[h] : cols <= 4 ? c.few[h] : 0;
     if (slab < stream) slab = stream;
-    if (tiles + grid >= (1ll << 31)) continue;               // 32-bit division; so many rounds are 256 wide
     const int64_t cost = (int64_t)((uint32_t)(tiles + grid - 1) / (uint32_t)grid) * (nk * slab + c.tile[h]);
-    if (h == 2 || (best.cost != 0 && cost < best.cost)) best = {h == 2 ? 8 : 2 * h, cost};
+    if (i == 0 || (best.cost != 0 && cost < best.cost)) best = {width, cost};
   }
   return best;
 }

@@ -84,6 +84,15 @@ def test_narrow_token_tiles(lib, N, V, d):
     _check_head(lib, N, V, d)
 
 
+# 320 columns of tokens: one column, several, the last one of one token, of half of its wavefronts, full; 10, 11 and 17 slabs, the
+# last one up to its half and past it; slabs taken from another one than the first on
+@pytest.mark.parametrize("N,V", [(257, 49200), (320, 49200), (1041, 16380), (1280, 16380), (2241, 8190), (1601, 32700)])
+@pytest.mark.parametrize("d", [584, 640, 648, 704, 1032])
+def test_wide_token_tiles(lib, N, V, d):
+    assert loops(N, V, d)[0] == "256x320"
+    _check_head(lib, N, V, d)
+
+
 # the last slab up to its half, just past it and full, alone and after others: 128 x 128 tiles, 160 columns, 128 and 256
 @pytest.mark.parametrize("d", [32, 40, 64, 96, 104, 160, 168])
 @pytest.mark.parametrize("N,V", [(40, 33000), (400, 33000), (1000, 49200)])
