@@ -1,4 +1,5 @@
-// gemm_small.h -- K-contiguous contraction loop on 128 x 128 and 64 x 64 tiles, C[m,n] = sum_k A[m,k] * B[n,k].
+// gemm_small.h -- K-contiguous contraction loops on 128 x 128 and 64 x 64 tiles, C[m,n] = sum_k A[m,k] * B[n,k]: TileGemmSmall
+// (bf16) and TileGemmSplit (fp32).
 //
 // fp32 operands go through the bf16 matrix pipes: every value is written as a sum of three bf16 numbers,
 // x = h + m + l (h = bf16(x), m = bf16(x - h), l = bf16(x - h - m): 3 x 8 significant bits, so nothing of a normal fp32
@@ -16,15 +17,18 @@
 // A tile whose operands lost a bit or that has a non-finite sum is contracted again with fp32 MFMAs, whose results it
 // keeps.
 //
-// gfx950 mapping: four wavefronts, 128-byte slab rows with the XOR swizzle of gemm_nt.h, slabs fetched straight into
-// LDS.  The tiles are small enough for two or more workgroups per CU, whose main loops, splits and epilogues cover
-// each other's waits: the loop needs no hand-written slot table.  Bound by the VALU work of the splits (48 operations
-// per fragment, 8 fragments per 128 MFMAs of a wavefront) beside the MFMAs.  Measured against a 256 x 256 loop of
-// 16x16x4 fp32 MFMAs, per contraction of (N, V, d): (4096, 20011, 516) 690 - 930 -> 630 - 705 us, (1024, 32000, 2048)
-// 940 - 1020 -> 830 - 885 us (without ml and lm 545 - 585 and 705 - 750, with them but without `lost` 620 - 680 and
-// 820 - 865); (256, 1024, 256) on 64 x 64 tiles 45 - 97 -> 15 - 18 us.  Relative error against 64 bits over 60 shapes
-// (32 .. 8192 tokens, 300 .. 40000 entries, d 64 .. 2048): logp 7.1e-8 -> 3.1e-8, dH 4.3e-7 -> 1.9e-7, dW 2.2e-7 ->
-// 1.2e-7, and smaller than before at every one of them.
+// gfx950 mapping: four wavefronts a tile, two or three workgroups per CU, whose main loops and epilogues cover each other's waits:
+// no hand-written slot table.  bf16: 128-byte slab rows with the XOR swizzle of gemm_nt.h, slabs fetched straight into LDS.
+// fp32: an operation on the VALU takes 2.4 cycles from the matrix pipe of its SIMD even where another wavefront owns that, and a
+// split is 48 of them for 8 x 64 values; so a workgroup splits each value once, in registers on its way to LDS (192 operations a
+// slab and wavefront beside 128 MFMAs), where each of the two wavefronts that multiply it did it for itself (384).  The next row
+// block's parts are read under this one's MFMAs.  Forward call / dz / dH / dW, every wavefront splitting / now, us: (N, V, d) = (3600,
+// 20011, 516) 539 / 591 / 635 / 653 -> 467 / 548 / 551 / 569, (1024, 32000, 2048) - / 927 / 863 / 888 -> - / 813 / 792 / 814, (1000, 3000, 516)
+// 46 / 49 / 53 / 52 -> 45 / 47 / 43 / 45, (300, 16400, 260) - / 43 / 48 / 42 -> - / 37 / 43 / 38; the same bits.  (Parts read where they are
+// used: 512 for 467; the split of the next slab between the last row block's MFMAs: 496, its loads then have less time;
+// v_dot2_f32_bf16 for x - h: not exact; either workgroup of a CU preferred by s_setprio or started later: no change.)
+// Relative error against 64 bits over 60 shapes (32 .. 8192 tokens, 300 .. 40000 entries, d 64 .. 2048), fp32 MFMAs / split: logp 7.1e-8
+// / 3.1e-8, dH 4.3e-7 / 1.9e-7, dW 2.2e-7 / 1.2e-7, and smaller at every one of them.
 #pragma once
 #include "gemm_nt.h"
 
@@ -59,8 +63,8 @@ __device__ __forceinline__ Split3 split3(const f32x4_t& x0, const f32x4_t& x1, u
   return Split3{__builtin_bit_cast(bf16x8_t, h), __builtin_bit_cast(bf16x8_t, m), __builtin_bit_cast(bf16x8_t, l)};
 }
 
-// Same interface as TileGemm (prefetch / setup_gathered, issue_first / run).  NSTAGE slabs are resident, NSTAGE - 1 of them in
-// flight; smem must hold LDS_BYTES.
+// bf16.  Same interface as TileGemm (prefetch / setup_gathered, issue_first / run).  NSTAGE slabs are resident, NSTAGE - 1 of
+// them in flight; smem must hold LDS_BYTES.
 template <typename TT, typename S, int NSTAGE, int GROUPS_PER_CU_>
 struct TileGemmSmall {
   typedef TT Type;
@@ -72,14 +76,13 @@ struct TileGemmSmall {
   static constexpr bool HAS_IDLE = false, HALVES = false;
   static constexpr bool REQUESTS_PAST_K = true;
   static constexpr int BK = 8 * TT::EPC;
-  static constexpr int LDS_BYTES = NSTAGE * S::STAGE_BYTES + 16;     // + a flag (fp32: redo this tile)
+  static constexpr int LDS_BYTES = NSTAGE * S::STAGE_BYTES;
   static constexpr int GROUPS_PER_CU = GROUPS_PER_CU_;
   static constexpr int LOADS = LoaderA::ITERS + LoaderB::ITERS;      // of one thread per slab
   LoaderA la;
   LoaderB lb;
   int K;
   __device__ __forceinline__ static constexpr int width() { return S::BN; }
-  float unscale;     // run<true> only
 
   // A slab past K fetches nothing (every lane out of the descriptor's range: zeros land in LDS), so the number of
   // loads in flight is the same in every iteration and the waits can count them.
@@ -121,50 +124,192 @@ struct TileGemmSmall {
       for (int j = 0; j < S::NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
 
-  // the MFMAs of one slab; a_addr / b_addr: this lane's chunk of block 0 in either half of a slab row.
-  // low: sums of the seven small terms of split products; lost: see split3.  SPLIT = false: the operands' own MFMAs, A
-  // times a_factor
-  template <bool SPLIT>
+  // the MFMAs of one slab; a_addr / b_addr: this lane's chunk of block 0 in either half of a slab row
   __device__ __forceinline__ static void slab(const char* st, const int (&a_addr)[2], const int (&b_addr)[2],
-                                              f32x4_t (&acc)[S::MB][S::NB], f32x4_t (&low)[S::MB][S::NB], uint32_t& lost,
-                                              float a_factor) {
-    if constexpr (sizeof(typename TT::store_t) == 2) {
+                                              f32x4_t (&acc)[S::MB][S::NB]) {
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        frag_t b[S::NB], a[S::MB];
+    for (int ks = 0; ks < 2; ++ks) {
+      frag_t b[S::NB], a[S::MB];
 #pragma unroll
-        for (int j = 0; j < S::NB; ++j) b[j] = *reinterpret_cast<const frag_t*>(st + b_addr[ks] + j * BLOCK_BYTES);
+      for (int j = 0; j < S::NB; ++j) b[j] = *reinterpret_cast<const frag_t*>(st + b_addr[ks] + j * BLOCK_BYTES);
 #pragma unroll
-        for (int i = 0; i < S::MB; ++i) a[i] = *reinterpret_cast<const frag_t*>(st + a_addr[ks] + i * BLOCK_BYTES);
+      for (int i = 0; i < S::MB; ++i) a[i] = *reinterpret_cast<const frag_t*>(st + a_addr[ks] + i * BLOCK_BYTES);
 #pragma unroll
-        for (int i = 0; i < S::MB; ++i)
+      for (int i = 0; i < S::MB; ++i)
 #pragma unroll
-          for (int j = 0; j < S::NB; ++j) mma(a[i], b[j], acc[i][j]);
+        for (int j = 0; j < S::NB; ++j) mma(a[i], b[j], acc[i][j]);
+    }
+  }
+
+  __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[S::MB][S::NB]) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int wm = S::wave_row(wave), wn = S::wave_col(wave);
+    const int g = lane >> 4, l16 = lane & 15, sw = swizzle(l16);
+    int a_addr[2], b_addr[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      a_addr[ks] = (wm * S::WAVE_M + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
+      b_addr[ks] = S::SLAB_A_BYTES + (wn * S::WAVE_N + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
+    }
+    clear(acc);
+    const int nk = (K + BK - 1) / BK;
+    wait_vmcnt0();                     // the first slabs (and stores of a previous epilogue, which may sit between)
+    __syncthreads();
+    int st = 0;                        // stage of slab kt
+    for (int kt = 0; kt < nk; ++kt) {
+      if (kt > 0) {
+        wait_vmcnt<LOADS * (NSTAGE - 2)>();      // this thread's share of slab kt has landed
+        __syncthreads();                         // everyone's has, and everyone is done with slab kt - 1
       }
-    } else if constexpr (!SPLIT) {
+      // slab kt - 1's stage is free now
+      issue(smem + (st == 0 ? NSTAGE - 1 : st - 1) * S::STAGE_BYTES, kt + NSTAGE - 1);
+      slab(smem + st * S::STAGE_BYTES, a_addr, b_addr, acc);
+      st = st == NSTAGE - 1 ? 0 : st + 1;
+    }
+  }
+};
+
+// fp32 on 128 x 128 and 64 x 64 tiles, see the header.  A slab (32 k) goes through registers: a wavefront loads 16-row blocks of
+// one operand (half of the wavefronts A, half B), splits them and writes the three parts to LDS as the fragments the MFMAs
+// read, 16 bytes a lane.
+template <typename S, int GROUPS_PER_CU_>
+struct TileGemmSplit {
+  typedef F32 Type;
+  typedef S Shape;
+  static constexpr bool KMAJOR = false;
+  static constexpr bool HAS_IDLE = false, HALVES = false;
+  static constexpr bool REQUESTS_PAST_K = false;
+  static constexpr int BK = 32;
+  static constexpr int BLOCKS_A = S::BM / 16, BLOCKS = (S::BM + S::BN) / 16, PER = BLOCKS / S::WAVES;      // of a wavefront
+  static_assert(BLOCKS % S::WAVES == 0 && BLOCKS_A % PER == 0, "a wavefront's blocks are of one operand");
+  static constexpr int FRAG_BYTES = 1024, SPLIT_BYTES = 3 * FRAG_BYTES;
+  static constexpr int LDS_BYTES = BLOCKS * SPLIT_BYTES + 16;        // + a flag (redo this tile)
+  static constexpr int GROUPS_PER_CU = GROUPS_PER_CU_;
+  struct Rows {                                                      // which tile rows a lane fetches, see SlabLoader
+    static constexpr int ITERS = PER;
+    template <bool NEAR>
+    __device__ __forceinline__ static int lane_tile_row(int it, int wave, int lane, int nb) {
+      return tile_row_of<NEAR, S::WAVE_N>(max((wave * PER + it - BLOCKS_A) * 16 + (lane & 15), 0), nb);
+    }
+  } lb;
+  uint64_t base;          // of this wavefront's operand
+  uint32_t bytes;
+  uint32_t voff[PER];     // byte offset of (row, chunk lane / 16)
+  int K;
+  float unscale;          // run<true> only
+  __device__ __forceinline__ static constexpr int width() { return S::BN; }
+  __device__ __forceinline__ static bool holds_a(int wave) { return wave * PER < BLOCKS_A; }
+
+  __device__ __forceinline__ void set_rows(const void* p, uint32_t size, int it, int row, bool valid, uint32_t row_bytes, int lane) {
+    base = reinterpret_cast<uint64_t>(p);
+    bytes = size;
+    voff[it] = valid ? (uint32_t)row * row_bytes + (uint32_t)(lane >> 4) * 16u : OOB_OFFSET;
+  }
+  __device__ __forceinline__ void set_a(const void* A_tile, int64_t lda, int rowsA, int wave, int lane) {
+    const uint32_t row_bytes = (uint32_t)(lda * 4);
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int i = 0; i < S::MB; ++i) {
-          frag_t a = *reinterpret_cast<const frag_t*>(st + a_addr[ks] + i * BLOCK_BYTES);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) a[r] *= a_factor;
-#pragma unroll
-          for (int j = 0; j < S::NB; ++j)
-            mma(a, *reinterpret_cast<const frag_t*>(st + b_addr[ks] + j * BLOCK_BYTES), acc[i][j]);
-        }
+    for (int it = 0; it < PER; ++it) {
+      const int row = (wave * PER + it) * 16 + (lane & 15);
+      set_rows(A_tile, row_bytes * (uint32_t)rowsA, it, row, row < rowsA, row_bytes, lane);
+    }
+  }
+  template <bool NEAR>
+  __device__ __forceinline__ void prefetch(const void* A_tile, int64_t lda, int rowsA, const void* B_tile, int64_t ldb,
+                                           int rowsB, int64_t K_, char*) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    K = (int)K_;
+    if (holds_a(wave)) {                             // wave-uniform
+      set_a(A_tile, lda, rowsA, wave, lane);
     } else {
-      // The 32 k of a slab are one k-step of the 16x16x32 MFMA.  Which k sits at which position of the fragment does
-      // not matter as long as both operands agree: a lane takes the chunks of the two conflict-free reads.
+      const uint32_t row_bytes = (uint32_t)(ldb * 4);
+#pragma unroll
+      for (int it = 0; it < PER; ++it) {
+        const int row = Rows::template lane_tile_row<NEAR>(it, wave, lane, S::NB);
+        set_rows(B_tile, row_bytes * (uint32_t)rowsB, it, row, row < rowsB, row_bytes, lane);
+      }
+    }
+  }
+  template <bool NEAR>
+  __device__ __forceinline__ void setup_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
+                                                 int64_t ldb, int rowsB, int64_t K_, const int (&grow)[PER],
+                                                 int64_t b_total, int) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    K = (int)K_;
+    if (holds_a(wave)) {
+      set_a(A_tile, lda, rowsA, wave, lane);
+    } else {
+      const uint32_t row_bytes = (uint32_t)(ldb * 4);
+#pragma unroll
+      for (int it = 0; it < PER; ++it)
+        set_rows(B_base, row_bytes * (uint32_t)b_total, it, grow[it],
+                 Rows::template lane_tile_row<NEAR>(it, wave, lane, S::NB) < rowsB, row_bytes, lane);
+    }
+  }
+  static constexpr int FIRST_PARTS = 0;              // the other workgroups of the CU cover a tile's first slab
+  __device__ __forceinline__ void issue_first(char*, int) const {}
+
+  // A lane's 2 x 4 elements of its row in each block: chunks lane / 16 and lane / 16 + 4 of the slab.  Which k sits at which
+  // position of a fragment does not matter as long as both operands agree.
+  __device__ __forceinline__ void load(int k0, f32x4_t (&x)[PER][2]) const {
+    const uint64_t b = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base >> 32)) << 32) |
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base);
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(b), 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+    const int left = K - k0 - 4 * (int)((threadIdx.x & 63) >> 4);      // of this lane's first chunk on
+#pragma unroll
+    for (int it = 0; it < PER; ++it)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        x[it][c] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                                   rs, left > 16 * c ? voff[it] + 64u * c : OOB_OFFSET, k0 * 4, 0));
+  }
+  // LDS traffic of this wavefront is over, and everyone's.  (Not __syncthreads(): the loads of the next slab stay in flight.)
+  __device__ __forceinline__ static void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+  __device__ __forceinline__ static void clear(f32x4_t (&acc)[S::MB][S::NB]) {
+#pragma unroll
+    for (int i = 0; i < S::MB; ++i)
+#pragma unroll
+      for (int j = 0; j < S::NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ __forceinline__ static bf16x8_t frag(const char* block, int part, int lane) {
+    return *reinterpret_cast<const bf16x8_t*>(block + part * FRAG_BYTES + lane * 16);
+  }
+
+  // low: sums of the seven small terms of split products
+  __device__ __forceinline__ void split_slabs(char* smem, f32x4_t (&acc)[S::MB][S::NB], f32x4_t (&low)[S::MB][S::NB],
+                                              uint32_t& lost) const {
+    const int lane = threadIdx.x & 63, wave = wave_id(), nk = (K + BK - 1) / BK;
+    const char* pa = smem + S::wave_row(wave) * S::MB * SPLIT_BYTES;
+    const char* pb = smem + (BLOCKS_A + S::wave_col(wave) * S::NB) * SPLIT_BYTES;
+    char* mine = smem + wave * PER * SPLIT_BYTES + lane * 16;
+    f32x4_t x[PER][2];
+    load(0, x);
+    for (int kt = 0; kt < nk; ++kt) {
+      Split3 sp[PER];
+#pragma unroll
+      for (int it = 0; it < PER; ++it) sp[it] = split3(x[it][0], x[it][1], lost);
+      lds_barrier();                                 // everyone is done with the previous slab's parts
+#pragma unroll
+      for (int it = 0; it < PER; ++it) {
+        *reinterpret_cast<bf16x8_t*>(mine + it * SPLIT_BYTES) = sp[it].h;
+        *reinterpret_cast<bf16x8_t*>(mine + it * SPLIT_BYTES + FRAG_BYTES) = sp[it].m;
+        *reinterpret_cast<bf16x8_t*>(mine + it * SPLIT_BYTES + 2 * FRAG_BYTES) = sp[it].l;
+      }
+      if (kt + 1 < nk) load((kt + 1) * BK, x);
+      lds_barrier();
+      auto parts = [&](const char* q) { return Split3{frag(q, 0, lane), frag(q, 1, lane), frag(q, 2, lane)}; };
       Split3 b[S::NB];
 #pragma unroll
-      for (int j = 0; j < S::NB; ++j)
-        b[j] = split3(*reinterpret_cast<const frag_t*>(st + b_addr[0] + j * BLOCK_BYTES),
-                      *reinterpret_cast<const frag_t*>(st + b_addr[1] + j * BLOCK_BYTES), lost);
+      for (int j = 0; j < S::NB; ++j) b[j] = parts(pb + j * SPLIT_BYTES);
+      // The next row block is read under this one's MFMAs; left to itself the compiler reads it where it is used.
+      Split3 next = parts(pa);
 #pragma unroll
       for (int i = 0; i < S::MB; ++i) {
-        const Split3 a = split3(*reinterpret_cast<const frag_t*>(st + a_addr[0] + i * BLOCK_BYTES),
-                                *reinterpret_cast<const frag_t*>(st + a_addr[1] + i * BLOCK_BYTES), lost);
+        const Split3 a = next;
+        LLAMARL_FENCE();
+        if (i + 1 < S::MB) next = parts(pa + (i + 1) * SPLIT_BYTES);
+        LLAMARL_FENCE();
         // j innermost: consecutive MFMAs do not wait for each other's accumulator
 #pragma unroll
         for (int j = 0; j < S::NB; ++j) mma(a.m, b[j].l, low[i][j]);
@@ -182,73 +327,64 @@ struct TileGemmSmall {
         for (int j = 0; j < S::NB; ++j) mma(a.h, b[j].m, low[i][j]);
 #pragma unroll
         for (int j = 0; j < S::NB; ++j) mma(a.h, b[j].h, acc[i][j]);
+        LLAMARL_FENCE();
       }
     }
   }
-
-  // the K loop; the first slabs are on their way
-  template <bool SPLIT>
-  __device__ __forceinline__ void slabs(char* smem, const int (&a_addr)[2], const int (&b_addr)[2],
-                                        f32x4_t (&acc)[S::MB][S::NB], f32x4_t (&low)[S::MB][S::NB], uint32_t& lost,
-                                        float a_factor) const {
-    const int nk = (K + BK - 1) / BK;
-    wait_vmcnt0();                     // the first slabs (and stores of a previous epilogue, which may sit between)
-    __syncthreads();
-    int st = 0;                        // stage of slab kt
+  // the operands' own MFMAs, A times a_factor; a block takes two fragments of LDS
+  __device__ __forceinline__ void native_slabs(char* smem, f32x4_t (&acc)[S::MB][S::NB], float a_factor) const {
+    const int lane = threadIdx.x & 63, wave = wave_id(), nk = (K + BK - 1) / BK;
+    const float factor = holds_a(wave) ? a_factor : 1.f;
+    auto at = [&](int block, int c) { return reinterpret_cast<f32x4_t*>(smem + (block * 2 + c) * FRAG_BYTES + lane * 16); };
     for (int kt = 0; kt < nk; ++kt) {
-      if (kt > 0) {
-        wait_vmcnt<LOADS * (NSTAGE - 2)>();      // this thread's share of slab kt has landed
-        __syncthreads();                         // everyone's has, and everyone is done with slab kt - 1
-      }
-      // slab kt - 1's stage is free now
-      issue(smem + (st == 0 ? NSTAGE - 1 : st - 1) * S::STAGE_BYTES, kt + NSTAGE - 1);
-      slab<SPLIT>(smem + st * S::STAGE_BYTES, a_addr, b_addr, acc, low, lost, a_factor);
-      st = st == NSTAGE - 1 ? 0 : st + 1;
+      f32x4_t x[PER][2];
+      load(kt * BK, x);
+      lds_barrier();
+#pragma unroll
+      for (int it = 0; it < PER; ++it)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) *at(wave * PER + it, c) = x[it][c] * factor;
+      lds_barrier();
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int i = 0; i < S::MB; ++i) {
+          const f32x4_t a = *at(S::wave_row(wave) * S::MB + i, c);
+#pragma unroll
+          for (int j = 0; j < S::NB; ++j) mma(a, *at(BLOCKS_A + S::wave_col(wave) * S::NB + j, c), acc[i][j]);
+        }
     }
   }
 
-  // A_SCALED (fp32): A holds its values divided by `unscale`, a power of two; the sums come out unscaled.  The native pass
+  // A_SCALED: A holds its values divided by `unscale`, a power of two; the sums come out unscaled.  The native pass
   // unscales the operand itself: what it is there for may be a sum that only overflows scaled.
   template <bool A_SCALED = false>
   __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[S::MB][S::NB]) {
-    constexpr bool SPLIT = sizeof(typename TT::store_t) == 4;
     const float factor = A_SCALED ? unscale : 1.f;
-    const int lane = threadIdx.x & 63, wave = wave_id();
-    const int wm = S::wave_row(wave), wn = S::wave_col(wave);
-    const int g = lane >> 4, l16 = lane & 15, sw = swizzle(l16);
-    int a_addr[2], b_addr[2];
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      a_addr[ks] = (wm * S::WAVE_M + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
-      b_addr[ks] = S::SLAB_A_BYTES + (wn * S::WAVE_N + l16) * SLAB_ROW_BYTES + (((4 * ks + g) ^ sw) * 16);
-    }
-    int* redo = reinterpret_cast<int*>(smem + NSTAGE * S::STAGE_BYTES);
-    if (SPLIT && threadIdx.x == 0) *redo = 0;
+    int* redo = reinterpret_cast<int*>(smem + BLOCKS * SPLIT_BYTES);
+    if (threadIdx.x == 0) *redo = 0;
+    wait_vmcnt0();                                   // token words (TokenWords) are there after the first barrier
     f32x4_t low[S::MB][S::NB];
     uint32_t lost = 0;
     clear(acc);
     clear(low);
-    slabs<SPLIT>(smem, a_addr, b_addr, acc, low, lost, 1.f);
-    if constexpr (SPLIT) {
-      bool bad = (lost & 0xffffu) != 0;
+    split_slabs(smem, acc, low, lost);
+    bool bad = (lost & 0xffffu) != 0;
 #pragma unroll
-      for (int i = 0; i < S::MB; ++i)
+    for (int i = 0; i < S::MB; ++i)
 #pragma unroll
-        for (int j = 0; j < S::NB; ++j)
+      for (int j = 0; j < S::NB; ++j)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            acc[i][j][r] += low[i][j][r];
-            bad |= !(fabsf(acc[i][j][r]) < INFINITY);
-            if constexpr (A_SCALED) acc[i][j][r] *= factor;
-          }
-      if (bad) *redo = 1;
-      wait_vmcnt0();                   // slabs past K that are still in flight would overwrite the ones fetched below
-      __syncthreads();
-      if (*redo) {                     // workgroup-uniform
-        clear(acc);
-        first_slabs(smem);
-        slabs<false>(smem, a_addr, b_addr, acc, low, lost, factor);
-      }
+        for (int r = 0; r < 4; ++r) {
+          acc[i][j][r] += low[i][j][r];
+          bad |= !(fabsf(acc[i][j][r]) < INFINITY);
+          if constexpr (A_SCALED) acc[i][j][r] *= factor;
+        }
+    if (bad) *redo = 1;
+    __syncthreads();
+    if (*redo) {                                     // workgroup-uniform
+      clear(acc);
+      native_slabs(smem, acc, factor);
     }
   }
 };

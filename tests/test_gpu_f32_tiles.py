@@ -69,6 +69,13 @@ def test_many_parts(lib, N, V, d):
     test_tile_edges(lib, N, V, d)
 
 
+# the last slab of 32 up to one 16-byte chunk, half of it (a lane's first chunk) and past that, alone and after another
+@pytest.mark.parametrize("N,V", [(65, 129), (400, 8200)])                      # 64- and 128-tiles
+@pytest.mark.parametrize("d", [4, 16, 20, 44, 48])
+def test_last_slab(lib, N, V, d):
+    test_tile_edges(lib, N, V, d)
+
+
 @pytest.mark.parametrize("N,V,d", [(130, 300, 40), (400, 9000, 40)])      # 64- and 128-tiles
 def test_values_that_cannot_be_split(lib, N, V, d):
     # a constant-one column makes W[:, 0] a bias; -inf there bans a token, and 3.4e38 (infinity in bf16) times
