@@ -944,6 +944,8 @@ struct StoreArgs {
   int max_parts;            // blocks that `part` has room for
   float* part;              // [splits][tail tiles][tile] fp32 partial products of split tiles
   int32_t* plan_out;        // [4] {whole, rem, splits, tiles_m}: what k_reduce_tail has to finish
+  int grid;                 // workgroups of this contraction
+  int tail_blocks;          // ... and of its reduction (0: no tile is ever split)
 };
 
 struct StoreStrides {       // row strides of A and B
@@ -969,12 +971,14 @@ struct StorePlan {
   int whole, rem, splits, n_items;
   int full, last;      // items of whole rounds; this workgroup's item of the last one
   int next, stride;
-  // part_cost: what writing one part's fp32 block and reading it back costs, in 1/256 of a slab of the whole grid
-  __device__ __forceinline__ void init(int tiles_m_, int tiles_n_, int group_m_, int nk, int max_splits, int max_parts, int part_cost) {
+  // b: this workgroup of G; part_cost: what writing one part's fp32 block and reading it back costs, in 1/256 of a slab of the
+  // whole grid
+  __device__ __forceinline__ void init(int tiles_m_, int tiles_n_, int group_m_, int nk, int max_splits, int max_parts, int part_cost,
+                                       int b, int G) {
     tiles_m = tiles_m_;
     tiles_n = tiles_n_;
     group_m = group_m_;
-    const int T = tiles_m * tiles_n, G = gridDim.x;
+    const int T = tiles_m * tiles_n;
     whole = T / G * G;
     rem = T - whole;
     // split factor of the tail: the one that makes the tail shortest -- ceil(rem s / G) rounds of nk / s slabs each, the
@@ -994,7 +998,6 @@ struct StorePlan {
     n_items = whole + rem * splits;
     // 32 consecutive items per XCD and round (see TileSchedule): workgroup b sits on XCD b % 8.  The items of a last round
     // that does not fill the grid are dealt to all XCDs alike.
-    const int b = blockIdx.x;
     full = n_items / G * G;
     const int left = n_items - full, per = (left + 7) >> 3, mine = (b & 7) * per + (b >> 3);
     last = (G & 7) != 0 ? full + b : (b >> 3) < per && mine < left ? full + mine : n_items;
@@ -1239,15 +1242,15 @@ __device__ __forceinline__ void store_tiles(const StoreArgs a, const StoreStride
   }
 }
 
+// workgroup `block` of a contraction's a.grid
 template <typename G, int MODE>
-__global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(const StoreArgs a) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
+__device__ __forceinline__ void gemm_store(const StoreArgs& a, int block, char* smem) {
   constexpr int BK = 8 * G::Type::EPC, BM = G::Shape::BM;
   const int64_t M = a.m_count ? (int64_t)*a.m_count : a.M;
   const int64_t K = a.k_count ? dz_columns(*a.k_count, sizeof(typename G::Type::store_t) == 2) : a.K;
   // a later pass of a chunked backward that found no active rows: nothing to add to what the output holds
   if ((MODE == 2 || MODE == 4) && a.k_count != nullptr && K == 0) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (block == 0 && threadIdx.x == 0) {
       a.plan_out[0] = 0; a.plan_out[1] = 0; a.plan_out[2] = 1; a.plan_out[3] = 0;
     }
     return;
@@ -1256,8 +1259,9 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
   const StoreStrides ld{a.packed_a ? pitch : a.lda, a.packed_b ? pitch : a.ldb};
   const int tiles_m = (int)((M + BM - 1) / BM);
   StorePlan plan;
-  plan.init(tiles_m, a.tiles_n, a.group_m, (int)((K + BK - 1) / BK), a.max_splits, a.max_parts, STORE_PART_COST<G>);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  plan.init(tiles_m, a.tiles_n, a.group_m, (int)((K + BK - 1) / BK), a.max_splits, a.max_parts, STORE_PART_COST<G>,
+            block, a.grid);
+  if (block == 0 && threadIdx.x == 0) {
     a.plan_out[0] = plan.whole; a.plan_out[1] = plan.rem; a.plan_out[2] = plan.splits; a.plan_out[3] = tiles_m;
   }
   if (!plan.has_item()) return;                      // block-uniform
@@ -1269,6 +1273,20 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(
     with_blocks(g, [&](auto blocks) { store_tiles<G, MODE, decltype(blocks)::value>(a, ld, g, plan, M, K, smem); });
   else
     store_tiles<G, MODE, G::Shape::NB>(a, ld, g, plan, M, K, smem);
+}
+template <typename G, int MODE>
+__global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_gemm_store(const StoreArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  gemm_store<G, MODE>(a, blockIdx.x, smem);
+}
+// dH and dW in one launch, where both run on small tiles: neither needs the other's result, and what bounds a small one is the
+// launch, the first loads and the stores, which the other's products cover (figures at plan_store).
+template <typename GH, int MODE_H, typename GW, int MODE_W>
+__global__ __launch_bounds__(GH::Shape::THREADS, MIN_WAVES<GH> < MIN_WAVES<GW> ? MIN_WAVES<GH> : MIN_WAVES<GW>)
+void k_gemm_store_pair(const StoreArgs h, const StoreArgs w) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  if ((int)blockIdx.x < h.grid) gemm_store<GH, MODE_H>(h, blockIdx.x, smem);
+  else gemm_store<GW, MODE_W>(w, (int)blockIdx.x - h.grid, smem);
 }
 
 // Finishes the split tiles of a store contraction's last round: C tile = sum over splits (ascending) of the fp32
@@ -1301,7 +1319,7 @@ __device__ __forceinline__ void add_parts(float4& s, const float* p, int64_t pla
     }
 }
 template <typename S, int MODE>
-__global__ __launch_bounds__(256) void k_reduce_tail(StoreArgs a) {
+__device__ __forceinline__ void reduce_tail(const StoreArgs& a, int block) {
   const int whole = a.plan_out[0], rem = a.plan_out[1], splits = a.plan_out[2], tiles_m = a.plan_out[3];
   if (splits <= 1) return;                           // block-uniform
   const int64_t M = a.m_count ? (int64_t)*a.m_count : a.M;
@@ -1314,7 +1332,7 @@ __global__ __launch_bounds__(256) void k_reduce_tail(StoreArgs a) {
   char* Cb = reinterpret_cast<char*>(a.C);
   const int c = (int)(threadIdx.x % U::THREADS_PER_ROW) * 4;
   const int64_t plane = (int64_t)rem * (BM * BN);
-  for (int u = blockIdx.x; u < rem * U::PER_TILE; u += gridDim.x) {
+  for (int u = block; u < rem * U::PER_TILE; u += a.tail_blocks) {
     const int j = u / U::PER_TILE;
     const int row = (u - j * U::PER_TILE) * U::ROWS + (int)(threadIdx.x / U::THREADS_PER_ROW);
     int tm, tn;
@@ -1333,6 +1351,13 @@ __global__ __launch_bounds__(256) void k_reduce_tail(StoreArgs a) {
     const float x[4] = {s.x, s.y, s.z, s.w};
     store_final<MODE>(Cb + (orow * a.ldc + col0 + c) * esz, x);
   }
+}
+template <typename S, int MODE>
+__global__ __launch_bounds__(256) void k_reduce_tail(StoreArgs a) { reduce_tail<S, MODE>(a, blockIdx.x); }
+template <typename SH, int MODE_H, typename SW, int MODE_W>      // of k_gemm_store_pair
+__global__ __launch_bounds__(256) void k_reduce_tail_pair(StoreArgs h, StoreArgs w) {
+  if ((int)blockIdx.x < h.tail_blocks) reduce_tail<SH, MODE_H>(h, blockIdx.x);
+  else reduce_tail<SW, MODE_W>(w, (int)blockIdx.x - h.tail_blocks);
 }
 
 // out[c][p] = in[src(p)][c] for p < R, c < C; out[c][p] = 0 for R <= p < ld_out, one 64 x 64 tile (origin r0, c0) by a

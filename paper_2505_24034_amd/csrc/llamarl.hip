@@ -208,65 +208,99 @@ hipError_t set_lds_if_large(K kernel, int bytes) {
   return bytes > 65536 ? set_lds(kernel, bytes) : hipSuccess;
 }
 
-template <typename G, int MODE>
-llamarl_status launch_store_mode(const StoreArgs& a, int64_t work_items, int tiles_worst, hipStream_t st) {
-  HIP_TRY(set_lds_if_large(k_gemm_store<G, MODE>, G::LDS_BYTES));
-  const int grid = persistent_grid(work_items, G::GROUPS_PER_CU);
-  k_gemm_store<G, MODE><<<dim3((unsigned)grid), dim3(G::Shape::THREADS), G::LDS_BYTES, st>>>(a);
-  HIP_TRY(hipGetLastError());
-  // the split tiles of the last round, if the device-side sizes left any: fewer than `grid` of them.  A contraction
-  // whose longest K leaves no two parts of four slabs is never split (StorePlan::init).
-  constexpr int BK = 8 * G::Type::EPC;
-  if (a.max_splits > 1 && (a.K + BK - 1) / BK >= 8) {
-    const int tail = std::min(grid - 1, tiles_worst);
-    if (tail > 0) {
-      const int units = tail * TailUnit<typename G::Shape>::PER_TILE;
-      k_reduce_tail<typename G::Shape, MODE><<<dim3((unsigned)std::min(units, TAIL_MAX_BLOCKS)), dim3(256), 0, st>>>(a);
-      HIP_TRY(hipGetLastError());
-    }
-  }
-  return LLAMARL_OK;
-}
-
-// C [M,Nn] (+)= A B^T on the persistent grid; ws_part / ws_plan: workspace of the last round's split tiles
+// C [M,Nn] (+)= A B^T, see StoreArgs; a: the caller's part of the arguments (operands, counts, output, workspace).
 template <typename G>
-llamarl_status launch_store_gemm(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t M, int64_t Nn,
-                                 int64_t K, void* C, int64_t ldc, int c_is_f32, int accumulate, const int32_t* m_count,
-                                 const int32_t* k_count, const int32_t* c_rows, float* ws_part, size_t part_bytes, int32_t* ws_plan,
-                                 const int32_t* pitch_count, int packed_a, int packed_b, const float* a_scale, hipStream_t st) {
+llamarl_status plan_store(StoreArgs& a, size_t part_bytes, bool paired) {
+  constexpr int BM = G::Shape::BM, BN = G::Shape::BN, BK = 8 * G::Type::EPC;
   // the store epilogue of the K-contiguous loop writes four neighbouring columns per lane as one unit, and so
   // does the tail reduction
-  if (Nn % 4 != 0 || ldc % 4 != 0)
+  if (a.Nn % 4 != 0 || a.ldc % 4 != 0)
     return fail(LLAMARL_ERR_UNSUPPORTED, "output columns and row stride must be multiples of 4");
-  StoreArgs a;
-  a.m_count = m_count; a.k_count = k_count; a.c_rows = c_rows;
-  a.max_splits = STORE_MAX_SPLITS; a.part = ws_part;
-  a.max_parts = (int)(part_bytes / (G::Shape::BM * G::Shape::BN * 4));
-  a.plan_out = ws_plan;
-
-  a.pitch_count = pitch_count; a.packed_a = packed_a; a.packed_b = packed_b;
-  a.A = A; a.a_scale = a_scale; a.lda = lda; a.B = B; a.ldb = ldb; a.M = M; a.Nn = Nn; a.K = K;
-  constexpr int BM = G::Shape::BM, BN = G::Shape::BN;
-  const int tiles_m = (int)((M + BM - 1) / BM);      // worst case: every row active
+  a.max_splits = STORE_MAX_SPLITS;
+  a.max_parts = (int)(part_bytes / (BM * BN * 4));
+  const int tiles_m = (int)((a.M + BM - 1) / BM);      // worst case: every row active
   a.width = BN;
   a.nb1 = 0;
   if constexpr (G::HALVES) {
-    a.width = store_width(Nn);
+    a.width = store_width(a.Nn);
     a.nb1 = (a.width - G::Shape::WAVE_N) / 16;
   }
-  a.tiles_n = (int)((Nn + a.width - 1) / a.width);
+  a.tiles_n = (int)((a.Nn + a.width - 1) / a.width);
   a.group_m = (G::KMAJOR && a.tiles_n <= 16) ? PATCH_ROWS_KMAJOR : PATCH_ROWS_STORE;
-  a.C = C; a.ldc = ldc; a.c_is_f32 = c_is_f32; a.accumulate = accumulate;
   const int tiles = tiles_m * a.tiles_n;
-  constexpr int64_t PART_K = 4 * 8 * G::Type::EPC;           // a part has four slabs or more
+  constexpr int64_t PART_K = 4 * BK;                         // a part has four slabs or more
   // a small contraction still gets a workgroup per split
-  const int64_t items = (int64_t)tiles * std::min<int64_t>(STORE_MAX_SPLITS, std::max<int64_t>(1, (K + PART_K - 1) / PART_K));
-  if (c_is_f32) return accumulate ? launch_store_mode<G, 2>(a, items, tiles, st) : launch_store_mode<G, 1>(a, items, tiles, st);
+  const int64_t items = (int64_t)tiles * std::min<int64_t>(STORE_MAX_SPLITS, std::max<int64_t>(1, (a.K + PART_K - 1) / PART_K));
+  const int full = persistent_grid((int64_t)1 << 30, G::GROUPS_PER_CU);
+  // Of a pair each contraction takes half of the workgroups (both have the same products to form) and cuts its tiles into fewer
+  // parts, except where a tile is few slabs: its first loads and its stores want workgroups.  Backward at (N, V, d), three
+  // quarters of the rows active, one contraction after the other / together, each cut for the whole grid / as here, us:
+  //   fp32 (256, 1024, 256) 42.2 / 33.0 / 33.0, (1024, 4096, 512) 129 / 119 / 111, (300, 16400, 260) 117 / 120 / 114 (130 on halves),
+  //   (4800, 20011, 516) 1622 / 1622 / 1593; bf16 (1041, 5003, 520) 58.8 / 52.8 / 46.4, (512, 8192, 1024) 58.9 / 52.0 / 50.1,
+  //   (2048, 4096, 264) 64.6 / 48.3 / 44.6, (4096, 3000, 512) 74.7 / 68.2 / 63.2, (300, 16400, 264) 43.8 / 40.0 / 38.9.
+  a.grid = (int)std::min<int64_t>(items, paired && a.K >= 12 * BK ? full / 2 : full);
+  // the split tiles of the last round, if the device-side sizes left any: fewer than `grid` of them.  A contraction
+  // whose longest K leaves no two parts of four slabs is never split (StorePlan::init).
+  a.tail_blocks = (a.K + BK - 1) / BK < 8 ? 0 : std::min(std::min(a.grid - 1, tiles) * TailUnit<typename G::Shape>::PER_TILE, TAIL_MAX_BLOCKS);
+  return LLAMARL_OK;
+}
+
+template <typename G, int MODE>
+llamarl_status launch_store_mode(const StoreArgs& a, hipStream_t st) {
+  HIP_TRY(set_lds_if_large(k_gemm_store<G, MODE>, G::LDS_BYTES));
+  k_gemm_store<G, MODE><<<dim3((unsigned)a.grid), dim3(G::Shape::THREADS), G::LDS_BYTES, st>>>(a);
+  HIP_TRY(hipGetLastError());
+  if (a.tail_blocks > 0) {
+    k_reduce_tail<typename G::Shape, MODE><<<dim3((unsigned)a.tail_blocks), dim3(256), 0, st>>>(a);
+    HIP_TRY(hipGetLastError());
+  }
+  return LLAMARL_OK;
+}
+// f(std::integral_constant<int, MODE>()), see store_final
+template <typename G, typename F>
+llamarl_status with_mode(const StoreArgs& a, F&& f) {
+  if (a.c_is_f32) return a.accumulate ? f(std::integral_constant<int, 2>()) : f(std::integral_constant<int, 1>());
   if constexpr (sizeof(typename G::Type::store_t) == 2) {
-    return accumulate ? launch_store_mode<G, 4>(a, items, tiles, st) : launch_store_mode<G, 3>(a, items, tiles, st);
+    return a.accumulate ? f(std::integral_constant<int, 4>()) : f(std::integral_constant<int, 3>());
   } else {
     return fail(LLAMARL_ERR_INVALID_ARG, "a 16-bit output needs a 16-bit input type");
   }
+}
+template <typename G>
+llamarl_status launch_store(StoreArgs a, size_t part_bytes, hipStream_t st) {
+  const llamarl_status s = plan_store<G>(a, part_bytes, false);
+  if (s != LLAMARL_OK) return s;
+  return with_mode<G>(a, [&](auto mode) { return launch_store_mode<G, decltype(mode)::value>(a, st); });
+}
+
+// dH (h, which never accumulates) and dW (w) in one launch, and their split tiles in another; parts: the workspace's blocks,
+// of which each contraction takes what its parts can need, dH at least half.
+template <typename GH, typename GW>
+llamarl_status launch_store_pair(StoreArgs h, StoreArgs w, float* parts, size_t part_bytes, hipStream_t st) {
+  constexpr size_t BLOCK_H = GH::Shape::BM * GH::Shape::BN * 4, BLOCK_W = GW::Shape::BM * GW::Shape::BN * 4;
+  constexpr int BK = 8 * GW::Type::EPC;
+  const int64_t most_w = tile_count(w.M, w.Nn, GW::Shape::BM) * std::min<int64_t>(STORE_MAX_SPLITS, (w.K + BK - 1) / BK / 4);
+  const size_t for_w = std::min(part_bytes / 2, (size_t)most_w * BLOCK_W);
+  const size_t for_h = (part_bytes - for_w) / BLOCK_H * BLOCK_H;
+  h.part = parts;
+  w.part = parts + for_h / 4;
+  llamarl_status s = plan_store<GH>(h, for_h, true);
+  if (s == LLAMARL_OK) s = plan_store<GW>(w, part_bytes - for_h, true);
+  if (s != LLAMARL_OK) return s;
+  return with_mode<GW>(w, [&](auto mode) -> llamarl_status {
+    constexpr int MODE_H = sizeof(typename GH::Type::store_t) == 2 ? 3 : 1, MODE_W = decltype(mode)::value;
+    constexpr int LDS = GH::LDS_BYTES > GW::LDS_BYTES ? GH::LDS_BYTES : GW::LDS_BYTES;
+    const auto kernel = k_gemm_store_pair<GH, MODE_H, GW, MODE_W>;
+    HIP_TRY(set_lds_if_large(kernel, LDS));
+    kernel<<<dim3((unsigned)(h.grid + w.grid)), dim3(GH::Shape::THREADS), LDS, st>>>(h, w);
+    HIP_TRY(hipGetLastError());
+    const int tails = h.tail_blocks + w.tail_blocks;
+    if (tails > 0) {
+      k_reduce_tail_pair<typename GH::Shape, MODE_H, typename GW::Shape, MODE_W><<<dim3((unsigned)tails), dim3(256), 0, st>>>(h, w);
+      HIP_TRY(hipGetLastError());
+    }
+    return LLAMARL_OK;
+  });
 }
 
 CompactArgs compact_args(CompactArgs a) {
@@ -373,7 +407,7 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
   // K-contiguous dH contraction
   SetupArgs<stt> u;
   int32_t* plan = reinterpret_cast<int32_t*>(ws + w.off_plan);
-  float* dz_scale = kBf16 ? nullptr : reinterpret_cast<float*>(plan + 16);     // plan: StoreArgs::plan_out, 4 entries
+  float* dz_scale = kBf16 ? nullptr : reinterpret_cast<float*>(plan + 16);     // plan: StoreArgs::plan_out, 4 entries of dH, 4 of dW
   u.compact = compact_args({1, nullptr, nullptr, coef, V, N, 0, all_rows, n_act_all, nullptr, nullptr, nullptr, g, g_device,
                             dz_scale});
   u.compact_blocks = compact_blocks(N);
@@ -423,31 +457,48 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     //   fp32: K-contiguous operands dz [n_act][ldz] and W^T [d][ldz], K zero-padded to ldz
     float* part = reinterpret_cast<float*>(ws + w.off_part);
     const Tile dh_tile = store_tile(Rc, d, V, kBf16), dw_tile = store_tile(V, d, Rc, kBf16);
+    StoreArgs h = {};
+    h.M = Rc; h.Nn = d; h.C = dH; h.ldc = d; h.c_is_f32 = !kBf16; h.m_count = n_act; h.c_rows = rows; h.part = part; h.plan_out = plan;
+    h.a_scale = dz_scale;
     if constexpr (kBf16) {
-      const auto launch = dh_tile == TILE_256   ? launch_store_gemm<TileGemmTN>
-                          : dh_tile == TILE_128 ? launch_store_gemm<Bf16LoopTN128>
-                                                : launch_store_gemm<Bf16LoopTN64>;
-      s = launch(dzt, w.ldzt, W, d, Rc, d, V, dH, d, 0, 0, n_act, nullptr, rows, part, w.part, plan, n_act, 1, 0, nullptr, st);
+      h.A = dzt; h.packed_a = 1; h.pitch_count = n_act; h.B = W; h.ldb = d; h.K = V;
     } else {
-      const auto launch = dh_tile == TILE_128 ? launch_store_gemm<F32Loop128> : launch_store_gemm<F32Loop64>;
-      s = launch(dz, w.ldz, wt, w.ldz, Rc, d, w.ldz, dH, d, 1, 0, n_act, nullptr, rows, part, w.part, plan, nullptr, 0, 0,
-                 dz_scale, st);
+      h.A = dz; h.lda = w.ldz; h.B = wt; h.ldb = w.ldz; h.K = w.ldz;
     }
+    // dW [V,d] (+)= dz^T [V,n_act] . H^T[d,n_act]^T      (K = dz_columns(n_act), zero-padded); passes after
+    // the first add to what the earlier ones stored
+    StoreArgs o = {};
+    o.A = dzt; o.B = ht; o.packed_a = o.packed_b = 1; o.pitch_count = o.k_count = n_act; o.M = V; o.Nn = d; o.K = w.ldzt;
+    o.C = dW; o.ldc = d; o.c_is_f32 = dW_dt == LLAMARL_F32; o.accumulate = c == 0 ? accumulate_dW : 1; o.part = part;
+    o.plan_out = plan + 4; o.a_scale = dz_scale;
+    if (!ev && dh_tile != TILE_256 && dw_tile != TILE_256) {
+      const bool h128 = dh_tile == TILE_128, w128 = dw_tile == TILE_128;
+      if constexpr (kBf16)
+        s = (h128 ? (w128 ? launch_store_pair<Bf16LoopTN128, Bf16Loop128> : launch_store_pair<Bf16LoopTN128, Bf16Loop64>)
+                  : (w128 ? launch_store_pair<Bf16LoopTN64, Bf16Loop128> : launch_store_pair<Bf16LoopTN64, Bf16Loop64>))(
+            h, o, part, w.part, st);
+      else
+        s = (h128 ? (w128 ? launch_store_pair<F32Loop128, F32Loop128> : launch_store_pair<F32Loop128, F32Loop64>)
+                  : (w128 ? launch_store_pair<F32Loop64, F32Loop128> : launch_store_pair<F32Loop64, F32Loop64>))(
+            h, o, part, w.part, st);
+      if (s != LLAMARL_OK) return s;
+      continue;
+    }
+    if constexpr (kBf16)
+      s = (dh_tile == TILE_256   ? launch_store<TileGemmTN>
+           : dh_tile == TILE_128 ? launch_store<Bf16LoopTN128>
+                                 : launch_store<Bf16LoopTN64>)(h, w.part, st);
+    else
+      s = (dh_tile == TILE_128 ? launch_store<F32Loop128> : launch_store<F32Loop64>)(h, w.part, st);
     if (s != LLAMARL_OK) return s;
     if (c == 0) PHASE_EVENT(3);
     if (c == 0) PHASE_EVENT(4);
-    // dW [V,d] (+)= dz^T [V,n_act] . H^T[d,n_act]^T      (K = dz_columns(n_act), zero-padded); passes after
-    // the first add to what the earlier ones stored
-    auto launch_dw = [&] {
-      if constexpr (kBf16)
-        return dw_tile == TILE_256   ? launch_store_gemm<Store256>
-               : dw_tile == TILE_128 ? launch_store_gemm<Bf16Loop128>
-                                     : launch_store_gemm<Bf16Loop64>;
-      else
-        return dw_tile == TILE_128 ? launch_store_gemm<F32Loop128> : launch_store_gemm<F32Loop64>;
-    }();
-    s = launch_dw(dzt, w.ldzt, ht, w.ldzt, V, d, w.ldzt, dW, d, dW_dt == LLAMARL_F32, c == 0 ? accumulate_dW : 1, nullptr,
-                  n_act, nullptr, part, w.part, plan, n_act, 1, 1, dz_scale, st);
+    if constexpr (kBf16)
+      s = (dw_tile == TILE_256   ? launch_store<Store256>
+           : dw_tile == TILE_128 ? launch_store<Bf16Loop128>
+                                 : launch_store<Bf16Loop64>)(o, w.part, st);
+    else
+      s = (dw_tile == TILE_128 ? launch_store<F32Loop128> : launch_store<F32Loop64>)(o, w.part, st);
     if (s != LLAMARL_OK) return s;
     if (c == 0) PHASE_EVENT(5);
   }

@@ -1,0 +1,57 @@
+"""dH and dW in one launch (both on tiles of 128 or 64): each pairing of tile edges and output forms, ragged sizes, split and
+whole tiles on either side, in one pass and in row passes; entry by entry against float64."""
+import pytest
+import torch
+
+from tile_util import loops
+
+pytestmark = pytest.mark.gpu
+
+
+# (N, V, d, active share), (dH, dW) edges
+SIZES = [
+    ("bf16", 37, 130, 72, 1.0, ("64", "64")), ("bf16", 1, 70, 8, 1.0, ("64", "64")), ("bf16", 500, 1000, 264, 0.6, ("64", "64")),
+    ("bf16", 300, 9001, 264, 0.8, ("64", "128")), ("bf16", 300, 9001, 1032, 0.8, ("128", "128")),
+    ("bf16", 1041, 5003, 520, 0.7, ("128", "128")), ("bf16", 2050, 130, 1032, 0.5, ("128", "64")),
+    ("f32", 37, 130, 72, 1.0, ("64", "64")), ("f32", 1, 70, 4, 1.0, ("64", "64")), ("f32", 1000, 3000, 516, 0.7, ("64", "64")),
+    ("f32", 300, 16400, 260, 0.8, ("64", "128")), ("f32", 500, 5003, 1032, 0.7, ("128", "128")),
+    ("f32", 700, 3000, 1032, 0.9, ("128", "64")),
+]
+
+
+@pytest.mark.parametrize("dt,N,V,d,share,edges", SIZES)
+@pytest.mark.parametrize("form", ["plain", "accumulate", "fp32", "fp32 accumulate", "passes", "no rows"])
+def test_pair(lib, dt, N, V, d, share, edges, form):
+    bf16 = dt == "bf16"
+    assert loops(N, V, d, bf16)[2:] == edges
+    store = torch.bfloat16 if bf16 else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(N + V + d)
+    H = torch.randn(N, d, generator=g, device="cuda").to(store)
+    W = (torch.randn(V, d, generator=g, device="cuda") * d ** -0.5).to(store)
+    y = torch.randint(0, V, (N,), generator=g, device="cuda")
+    coef = torch.randn(N, generator=g, device="cuda") / N
+    coef[torch.rand(N, generator=g, device="cuda") >= (0.0 if form == "no rows" else share)] = 0.0
+    z = H.double() @ W.double().T
+    lse = torch.logsumexp(z, dim=1)
+    dz = -torch.exp(z - lse[:, None])
+    dz[torch.arange(N, device="cuda"), y] += 1.0
+    dz *= coef.double()[:, None]
+    rdH, rdW = dz @ W.double(), dz.T @ H.double()
+    old = torch.randn(V, d, generator=g, device="cuda") * rdW.std().float()
+    kw = {}
+    if "fp32" in form or form == "passes":
+        kw["dW_dtype"] = torch.float32
+    if "accumulate" in form:
+        kw.update(dW=old.to(torch.float32 if "fp32" in form else store), accumulate_dW=True)
+        rdW = rdW + kw["dW"].double()
+    if form == "passes":
+        kw["max_rows_per_pass"] = 256
+    dH, dW = lib.offpolicy_loss_bwd(H, W, y.int(), lse.float(), coef, **kw)
+    # An entry is a sum of K products.  bf16: each dz is rounded once, by up to 2^-8 of it (8 significant bits); the stored result once more.  In both types
+    # exp(z - lse) carries the logits' and lse's own rounding, |z| <= 8: 8 sqrt(d) 2^-24 and 10 2^-24, below 2^-15, and the
+    # sum's order sqrt(K) 2^-24.  (dz * 1 + tiny: coef * (1 - p) of the target cancels only where p is near 1.)
+    each, result = (2.0 ** -8 + 2.0 ** -14, 2.0 ** -8) if bf16 else (2.0 ** -14, 2.0 ** -22)
+    for name, got, ref, bound in (("dH", dH, rdH, dz.abs() @ W.double().abs()), ("dW", dW, rdW, dz.abs().T @ H.double().abs())):
+        rounds = 2.0 ** -22 if got.dtype == torch.float32 else result
+        assert bool(((got.double() - ref).abs() <= each * bound + rounds * ref.abs()).all()), name
+    assert not bool(dH[coef == 0].any())
