@@ -642,13 +642,16 @@ __device__ __forceinline__ float dz_scale_for(float c) {
   return (c == 0.f || e >= 60) ? 1.f : __uint_as_float((uint32_t)(min(60 - e, 126) + 127) << 23);
 }
 
-__device__ __forceinline__ void compact_rows(const CompactArgs& a, int block, int nblocks) {
+// put(position, row) for the active rows of block's range; returns the active rows up to its end.  want_top (of the last block,
+// block-uniform): top = the largest |coef| of the batch.
+template <typename Put>
+__device__ __forceinline__ int place_rows(const CompactArgs& a, int block, bool want_top, float& top, Put put) {
   constexpr int WAVES = COMPACT_THREADS / 64;
   __shared__ int s_front[WAVES], s_own[WAVES];
   __shared__ float s_top[WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t first = (int64_t)block * COMPACT_BLOCK_ROWS, t0 = first + 4 * tid;
-  float top = 0.f;
+  top = 0.f;
   const uint32_t act = t0 < a.N ? active_rows4(a, t0, top) : 0u;
   int front = 0;
 #pragma unroll 4
@@ -673,8 +676,7 @@ __device__ __forceinline__ void compact_rows(const CompactArgs& a, int block, in
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) front += __shfl_xor(front, o);
-  const bool last = block == nblocks - 1;           // has seen every row
-  if (last && a.dz_scale != nullptr) {
+  if (want_top) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
     if (lane == 0) s_top[wave] = top;
@@ -691,13 +693,18 @@ __device__ __forceinline__ void compact_rows(const CompactArgs& a, int block, in
   int at = base + upto - own;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
-    if (act >> i & 1u) a.rows[at++] = (int32_t)(t0 + i);
-  if (tid == 0 && last) {
+    if (act >> i & 1u) put(at++, (int32_t)(t0 + i));
+  if (want_top)
+    for (int w = 0; w < WAVES; ++w) top = fmaxf(top, s_top[w]);
+  return total;
+}
+__device__ __forceinline__ void compact_rows(const CompactArgs& a, int block, int nblocks) {
+  const bool last = block == nblocks - 1;           // has seen every row
+  float top;
+  const int total = place_rows(a, block, last && a.dz_scale != nullptr, top, [&](int at, int32_t row) { a.rows[at] = row; });
+  if (threadIdx.x == 0 && last) {
     *a.n_act = total;
-    if (a.dz_scale != nullptr) {
-      for (int w = 0; w < WAVES; ++w) top = fmaxf(top, s_top[w]);
-      *a.dz_scale = dz_scale_for(fabsf((a.g_device != nullptr ? *a.g_device : a.g) * top));
-    }
+    if (a.dz_scale != nullptr) *a.dz_scale = dz_scale_for(fabsf((a.g_device != nullptr ? *a.g_device : a.g) * top));
   }
 }
 __global__ __launch_bounds__(COMPACT_THREADS) void k_compact_rows(CompactArgs a) { compact_rows(a, blockIdx.x, gridDim.x); }
@@ -1361,55 +1368,37 @@ __global__ __launch_bounds__(256) void k_reduce_tail_pair(StoreArgs h, StoreArgs
 }
 
 // out[c][p] = in[src(p)][c] for p < R, c < C; out[c][p] = 0 for R <= p < ld_out, one 64 x 64 tile (origin r0, c0) by a
-// workgroup of THREADS.  src(p) = p, or rows[p] where a list is given.
-template <typename ST, int THREADS>
-__device__ __forceinline__ void transpose_tile(const ST* in, int64_t R, int64_t C, int64_t ld_in, ST* out, int64_t ld_out,
-                                               const int32_t* rows, int64_t r0, int64_t c0) {
+// workgroup of THREADS: 16-byte loads and stores along both matrices' rows (of 16-byte multiples, aligned: the host has checked
+// H, W and the workspace, and d), the transposition through LDS in between.  The LDS row is padded by one chunk: the columns a
+// wavefront gathers for its stores then start in different banks.
+template <typename ST, int THREADS, typename Src>
+__device__ __forceinline__ void transpose_tile(const ST* in, int64_t R, int64_t C, int64_t ld_in, ST* out, int64_t ld_out, Src src,
+                                               int64_t r0, int64_t c0) {
   constexpr int EPV = 16 / sizeof(ST);                          // elements of a 16-byte chunk
   constexpr int CHUNKS = 64 / EPV, LINES = THREADS / CHUNKS;    // chunks along a tile row; rows taken at a time
-  // whole 16-byte chunks along both matrices' rows (block-uniform test): 16-byte loads and stores, the transposition
-  // through LDS in between.  The LDS row is padded by one chunk: the columns a wavefront gathers for its stores then
-  // start in different banks.
-  if (C % EPV == 0 && ld_in % EPV == 0 && ld_out % EPV == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
-      (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
-    __shared__ __attribute__((aligned(16))) ST t[64][64 + EPV];
-    const int q = threadIdx.x % CHUNKS, line = threadIdx.x / CHUNKS;
+  __shared__ __attribute__((aligned(16))) ST t[64][64 + EPV];
+  const int q = threadIdx.x % CHUNKS, line = threadIdx.x / CHUNKS;
 #pragma unroll
-    for (int h = 0; h < 64; h += LINES) {
-      const int rr = line + h;
-      const int64_t r = r0 + rr, c = c0 + q * EPV;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (rr < 64 && r < R && c < C) v = *reinterpret_cast<const uint4*>(in + (rows ? (int64_t)rows[r] : r) * ld_in + c);
-      if (rr < 64) *reinterpret_cast<uint4*>(&t[rr][q * EPV]) = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int h = 0; h < 64; h += LINES) {
-      const int cc = line + h;
-      const int64_t c = c0 + cc, r = r0 + q * EPV;
-      if (cc < 64 && c < C && r < ld_out) {
-        ST w[EPV];
-#pragma unroll
-        for (int j = 0; j < EPV; ++j) w[j] = t[q * EPV + j][cc];
-        uint4 v;
-        __builtin_memcpy(&v, w, 16);
-        *reinterpret_cast<uint4*>(out + c * ld_out + r) = v;
-      }
-    }
-    return;
-  }
-  __shared__ ST tile[64][65];
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int rr = ty; rr < 64; rr += THREADS / 64) {
-    const int64_t r = r0 + rr, c = c0 + tx;
-    ST v = 0;
-    if (r < R && c < C) v = in[(rows ? (int64_t)rows[r] : r) * ld_in + c];
-    tile[rr][tx] = v;
+  for (int h = 0; h < 64; h += LINES) {
+    const int rr = line + h;
+    const int64_t r = r0 + rr, c = c0 + q * EPV;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (rr < 64 && r < R && c < C) v = *reinterpret_cast<const uint4*>(in + src(r) * ld_in + c);
+    if (rr < 64) *reinterpret_cast<uint4*>(&t[rr][q * EPV]) = v;
   }
   __syncthreads();
-  for (int cc = ty; cc < 64; cc += THREADS / 64) {
-    const int64_t c = c0 + cc, r = r0 + tx;
-    if (c < C && r < ld_out) out[c * ld_out + r] = tile[tx][cc];
+#pragma unroll
+  for (int h = 0; h < 64; h += LINES) {
+    const int cc = line + h;
+    const int64_t c = c0 + cc, r = r0 + q * EPV;
+    if (cc < 64 && c < C && r < ld_out) {
+      ST w[EPV];
+#pragma unroll
+      for (int j = 0; j < EPV; ++j) w[j] = t[q * EPV + j][cc];
+      uint4 v;
+      __builtin_memcpy(&v, w, 16);
+      *reinterpret_cast<uint4*>(out + c * ld_out + r) = v;
+    }
   }
 }
 
@@ -1420,16 +1409,20 @@ __global__ __launch_bounds__(256) void k_transpose(const ST* in, int64_t C, int6
                                                     const int32_t* r_count) {
   const int64_t R = *r_count, r0 = (int64_t)blockIdx.x * 64;
   if (r0 >= R) return;                                          // block-uniform
-  transpose_tile<ST, 256>(in, R, C, ld_in, out, packed_pitch(R), rows, r0, (int64_t)blockIdx.y * 64);
+  transpose_tile<ST, 256>(in, R, C, ld_in, out, packed_pitch(R), [&](int64_t r) { return (int64_t)rows[r]; }, r0, (int64_t)blockIdx.y * 64);
 }
 
 // What the backward prepares before it knows the active rows, in one launch: the active-row list (first blocks), zeros
 // in the dH rows of inactive tokens (coef == 0: the dH contraction only writes the active ones; a wavefront takes a
-// row) and, fp32 only, W^T [d][ldz] (64 x 64 tiles).  Three launches of a few microseconds each otherwise.
+// row), fp32 only, W^T [d][ldz] (64 x 64 tiles), and, for up to SETUP_HT_ROWS rows, the H^T panel
+// that is k_transpose's otherwise: its blocks place the rows again for themselves.  Launches of a few microseconds each otherwise.
 template <typename ST>
 struct SetupArgs {
   CompactArgs compact;
-  int compact_blocks, zero_blocks;
+  int compact_blocks, ht_blocks, zero_blocks;
+  const ST* H;
+  ST* ht;
+  int ht_tiles_r;            // tiles of H^T along the list; a block takes every ht_blocks / ht_tiles_r-th along d
   ST* dH;
   int64_t d;
   const ST* W;               // fp32 only
@@ -1439,6 +1432,7 @@ struct SetupArgs {
   int wt_blocks;
 };
 constexpr int SETUP_MAX_WT_BLOCKS = 1 << 20;           // a launch has fewer than 2^32 threads: 2^22 blocks
+constexpr int SETUP_HT_ROWS = 2048, SETUP_HT_BLOCKS = 512;             // two a CU; more tiles take turns
 constexpr int SETUP_ROWS = COMPACT_THREADS / 64;       // dH rows of a block
 template <typename ST>
 __global__ __launch_bounds__(COMPACT_THREADS) void k_bwd_setup(SetupArgs<ST> a) {
@@ -1448,6 +1442,22 @@ __global__ __launch_bounds__(COMPACT_THREADS) void k_bwd_setup(SetupArgs<ST> a) 
     return;
   }
   block -= a.compact_blocks;
+  if (block < a.ht_blocks) {
+    __shared__ int32_t s_rows[64];
+    const int tc = block / a.ht_tiles_r, r0 = (block - tc * a.ht_tiles_r) * 64;
+    float top;
+    const int R = place_rows(a.compact, 0, false, top, [&](int at, int32_t row) {
+      if ((uint32_t)(at - r0) < 64u) s_rows[at - r0] = row;
+    });
+    if (r0 >= R) return;                               // block-uniform
+    for (int64_t c0 = (int64_t)tc * 64; c0 < a.d; c0 += (int64_t)(a.ht_blocks / a.ht_tiles_r) * 64) {
+      __syncthreads();                                 // the rows are there; everyone is done with the previous tile's LDS
+      transpose_tile<ST, COMPACT_THREADS>(a.H, R, a.d, a.d, a.ht, packed_pitch(R), [&](int64_t r) { return (int64_t)s_rows[r - r0]; },
+                                          r0, c0);
+    }
+    return;
+  }
+  block -= a.ht_blocks;
   if (block < a.zero_blocks) {
     const int64_t t = (int64_t)block * SETUP_ROWS + (threadIdx.x >> 6);
     if (t >= a.compact.N || a.compact.coef[t] != 0.f) return;
@@ -1461,7 +1471,7 @@ __global__ __launch_bounds__(COMPACT_THREADS) void k_bwd_setup(SetupArgs<ST> a) 
     for (int64_t tile = block; tile < a.wt_tiles; tile += a.wt_blocks) {
       const int64_t tc = tile / a.wt_tiles_r, tr = tile - tc * a.wt_tiles_r;
       if (tile != block) __syncthreads();              // everyone is done with the previous tile's LDS
-      transpose_tile<ST, COMPACT_THREADS>(a.W, a.V, a.d, a.d, a.wt, a.ldz, nullptr, tr * 64, tc * 64);
+      transpose_tile<ST, COMPACT_THREADS>(a.W, a.V, a.d, a.d, a.wt, a.ldz, [](int64_t r) { return r; }, tr * 64, tc * 64);
     }
   }
 }

@@ -412,12 +412,19 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
                             dz_scale});
   u.compact_blocks = compact_blocks(N);
   u.zero_blocks = (int)((N + SETUP_ROWS - 1) / SETUP_ROWS);
+  u.H = reinterpret_cast<const stt*>(H); u.ht = ht;
+  u.ht_tiles_r = (int)(w.ldzt / 64);
+  // Backward at (N, V, d), k_transpose / here, us: bf16 (128, 1000, 128) 18.2 / 16.8, (1041, 5003, 520) 46.2 / 44.2, (2048, 4096, 264)
+  // 44.9 / 42.7, (4096, 3000, 512) 63.4 / 64.6 (every block reads all of coef); fp32 (512, 2048, 512) 63.0 / 59.7
+  static_assert(SETUP_HT_ROWS <= COMPACT_BLOCK_ROWS, "a block places all rows");
+  const bool ht_in_setup = N <= SETUP_HT_ROWS && w.n_pass == 1;
+  u.ht_blocks = ht_in_setup ? u.ht_tiles_r * (int)std::min<int64_t>((d + 63) / 64, std::max(SETUP_HT_BLOCKS / u.ht_tiles_r, 1)) : 0;
   u.dH = reinterpret_cast<stt*>(dH); u.d = d;
   u.W = reinterpret_cast<const stt*>(W); u.V = V; u.ldz = w.ldz; u.wt = wt;
   u.wt_tiles_r = w.ldz / 64;
   u.wt_tiles = kBf16 ? 0 : u.wt_tiles_r * ((d + 63) / 64);
   u.wt_blocks = (int)std::min<int64_t>(u.wt_tiles, SETUP_MAX_WT_BLOCKS);
-  const int64_t setup_blocks = (int64_t)u.compact_blocks + u.zero_blocks + u.wt_blocks;
+  const int64_t setup_blocks = (int64_t)u.compact_blocks + u.ht_blocks + u.zero_blocks + u.wt_blocks;
   k_bwd_setup<stt><<<dim3((unsigned)setup_blocks), dim3(COMPACT_THREADS), 0, st>>>(u);
   HIP_TRY(hipGetLastError());
   if (w.n_pass > 1) {
@@ -431,9 +438,11 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     const int32_t* n_act = w.n_pass > 1 ? pass_cnt + c : n_act_all;
     const int64_t Rc = std::min(w.R, N - (int64_t)c * w.R);       // rows the pass can hold at most
     // operand panel H^T [d][pitch] of the pass's tokens (dW contraction)
-    k_transpose<stt><<<dim3((unsigned)(w.ldzt / 64), (unsigned)((d + 63) / 64)), dim3(256), 0, st>>>(
-        reinterpret_cast<const stt*>(H), d, d, ht, rows, n_act);
-    HIP_TRY(hipGetLastError());
+    if (!ht_in_setup) {
+      k_transpose<stt><<<dim3((unsigned)(w.ldzt / 64), (unsigned)((d + 63) / 64)), dim3(256), 0, st>>>(
+          reinterpret_cast<const stt*>(H), d, d, ht, rows, n_act);
+      HIP_TRY(hipGetLastError());
+    }
     if (c == 0) PHASE_EVENT(1);
 
     // recompute logits tile by tile, turn them into dz (rows / columns = list positions of the pass)

@@ -13,6 +13,7 @@ SIZES = [
     ("bf16", 37, 130, 72, 1.0, ("64", "64")), ("bf16", 1, 70, 8, 1.0, ("64", "64")), ("bf16", 500, 1000, 264, 0.6, ("64", "64")),
     ("bf16", 300, 9001, 264, 0.8, ("64", "128")), ("bf16", 300, 9001, 1032, 0.8, ("128", "128")),
     ("bf16", 1041, 5003, 520, 0.7, ("128", "128")), ("bf16", 2050, 130, 1032, 0.5, ("128", "64")),
+    ("bf16", 2048, 130, 1032, 0.9, ("128", "64")), ("bf16", 2049, 130, 1032, 0.9, ("128", "64")),       # H^T by either kernel
     ("f32", 37, 130, 72, 1.0, ("64", "64")), ("f32", 1, 70, 4, 1.0, ("64", "64")), ("f32", 1000, 3000, 516, 0.7, ("64", "64")),
     ("f32", 300, 16400, 260, 0.8, ("64", "128")), ("f32", 500, 5003, 1032, 0.7, ("128", "128")),
     ("f32", 700, 3000, 1032, 0.9, ("128", "64")),
