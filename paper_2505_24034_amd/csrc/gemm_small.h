@@ -172,7 +172,11 @@ struct TileGemmSmall {
 // fp32 on 128 x 128 and 64 x 64 tiles, see the header.  A slab (32 k) goes through registers: a wavefront loads 16-row blocks of
 // one operand (half of the wavefronts A, half B), splits them and writes the three parts to LDS as the fragments the MFMAs
 // read, 16 bytes a lane.
-template <typename S, int GROUPS_PER_CU_>
+// STAGES: 2 where LDS has room for the parts of two slabs in every workgroup (64 x 64 tiles, few of them: a chain of slabs with
+// nothing to cover it).  The next slab is split and written behind this one's fragment reads, and a slab has one barrier instead of
+// two: (N, V, d), fp32, us, backward (100, 5000, 1024) 88.6 / 80.3, (256, 1024, 256) 30.9 / 28.9, (512, 2048, 512) 59.5 / 55.1; log-probs 38.4 /
+// 35.5, 17.8 / 17.1, 25.1 / 23.6.  (Loads two or three slabs ahead gained nothing on that; on 128 x 128 tiles they spill: 467 -> 990 us.)
+template <typename S, int GROUPS_PER_CU_, int STAGES>
 struct TileGemmSplit {
   typedef F32 Type;
   typedef S Shape;
@@ -183,7 +187,7 @@ struct TileGemmSplit {
   static constexpr int BLOCKS_A = S::BM / 16, BLOCKS = (S::BM + S::BN) / 16, PER = BLOCKS / S::WAVES;      // of a wavefront
   static_assert(BLOCKS % S::WAVES == 0 && BLOCKS_A % PER == 0, "a wavefront's blocks are of one operand");
   static constexpr int FRAG_BYTES = 1024, SPLIT_BYTES = 3 * FRAG_BYTES;
-  static constexpr int LDS_BYTES = BLOCKS * SPLIT_BYTES + 16;        // + a flag (redo this tile)
+  static constexpr int STAGE_BYTES = BLOCKS * SPLIT_BYTES, LDS_BYTES = STAGES * STAGE_BYTES + 16;      // + a flag (redo this tile)
   static constexpr int GROUPS_PER_CU = GROUPS_PER_CU_;
   struct Rows {                                                      // which tile rows a lane fetches, see SlabLoader
     static constexpr int ITERS = PER;
@@ -280,54 +284,89 @@ struct TileGemmSplit {
   __device__ __forceinline__ void split_slabs(char* smem, f32x4_t (&acc)[S::MB][S::NB], f32x4_t (&low)[S::MB][S::NB],
                                               uint32_t& lost) const {
     const int lane = threadIdx.x & 63, wave = wave_id(), nk = (K + BK - 1) / BK;
-    const char* pa = smem + S::wave_row(wave) * S::MB * SPLIT_BYTES;
-    const char* pb = smem + (BLOCKS_A + S::wave_col(wave) * S::NB) * SPLIT_BYTES;
-    char* mine = smem + wave * PER * SPLIT_BYTES + lane * 16;
+    const int pa = S::wave_row(wave) * S::MB * SPLIT_BYTES, pb = (BLOCKS_A + S::wave_col(wave) * S::NB) * SPLIT_BYTES;
+    const int mine = wave * PER * SPLIT_BYTES + lane * 16;
     f32x4_t x[PER][2];
-    load(0, x);
-    for (int kt = 0; kt < nk; ++kt) {
-      Split3 sp[PER];
+    Split3 sp[PER];
+    auto split = [&] {
 #pragma unroll
       for (int it = 0; it < PER; ++it) sp[it] = split3(x[it][0], x[it][1], lost);
-      lds_barrier();                                 // everyone is done with the previous slab's parts
+    };
+    auto write = [&](char* st) {
 #pragma unroll
       for (int it = 0; it < PER; ++it) {
-        *reinterpret_cast<bf16x8_t*>(mine + it * SPLIT_BYTES) = sp[it].h;
-        *reinterpret_cast<bf16x8_t*>(mine + it * SPLIT_BYTES + FRAG_BYTES) = sp[it].m;
-        *reinterpret_cast<bf16x8_t*>(mine + it * SPLIT_BYTES + 2 * FRAG_BYTES) = sp[it].l;
+        *reinterpret_cast<bf16x8_t*>(st + mine + it * SPLIT_BYTES) = sp[it].h;
+        *reinterpret_cast<bf16x8_t*>(st + mine + it * SPLIT_BYTES + FRAG_BYTES) = sp[it].m;
+        *reinterpret_cast<bf16x8_t*>(st + mine + it * SPLIT_BYTES + 2 * FRAG_BYTES) = sp[it].l;
       }
-      if (kt + 1 < nk) load((kt + 1) * BK, x);
+    };
+    auto parts = [&](const char* q) { return Split3{frag(q, 0, lane), frag(q, 1, lane), frag(q, 2, lane)}; };
+    // j innermost: consecutive MFMAs do not wait for each other's accumulator
+    auto products = [&](const Split3& a, const Split3 (&b)[S::NB], int i) {
+#pragma unroll
+      for (int j = 0; j < S::NB; ++j) mma(a.m, b[j].l, low[i][j]);
+#pragma unroll
+      for (int j = 0; j < S::NB; ++j) mma(a.l, b[j].m, low[i][j]);
+#pragma unroll
+      for (int j = 0; j < S::NB; ++j) mma(a.l, b[j].h, low[i][j]);
+#pragma unroll
+      for (int j = 0; j < S::NB; ++j) mma(a.h, b[j].l, low[i][j]);
+#pragma unroll
+      for (int j = 0; j < S::NB; ++j) mma(a.m, b[j].m, low[i][j]);
+#pragma unroll
+      for (int j = 0; j < S::NB; ++j) mma(a.m, b[j].h, low[i][j]);
+#pragma unroll
+      for (int j = 0; j < S::NB; ++j) mma(a.h, b[j].m, low[i][j]);
+#pragma unroll
+      for (int j = 0; j < S::NB; ++j) mma(a.h, b[j].h, acc[i][j]);
+    };
+    load(0, x);
+    if constexpr (STAGES == 2) {
+      static_assert(S::MB == 1, "all parts of a slab are read before its products");
+      split();
+      write(smem);
+      if (nk > 1) load(BK, x);
       lds_barrier();
-      auto parts = [&](const char* q) { return Split3{frag(q, 0, lane), frag(q, 1, lane), frag(q, 2, lane)}; };
-      Split3 b[S::NB];
+      char *cur = smem, *other = smem + STAGE_BYTES;
+      for (int kt = 0; kt < nk; ++kt) {
+        Split3 b[S::NB];
 #pragma unroll
-      for (int j = 0; j < S::NB; ++j) b[j] = parts(pb + j * SPLIT_BYTES);
-      // The next row block is read under this one's MFMAs; left to itself the compiler reads it where it is used.
-      Split3 next = parts(pa);
-#pragma unroll
-      for (int i = 0; i < S::MB; ++i) {
-        const Split3 a = next;
+        for (int j = 0; j < S::NB; ++j) b[j] = parts(cur + pb + j * SPLIT_BYTES);
+        const Split3 a = parts(cur + pa);
         LLAMARL_FENCE();
-        if (i + 1 < S::MB) next = parts(pa + (i + 1) * SPLIT_BYTES);
+        if (kt + 1 < nk) {                             // everyone was done with that stage at the last barrier
+          split();
+          write(other);
+          if (kt + 2 < nk) load((kt + 2) * BK, x);
+        }
         LLAMARL_FENCE();
-        // j innermost: consecutive MFMAs do not wait for each other's accumulator
-#pragma unroll
-        for (int j = 0; j < S::NB; ++j) mma(a.m, b[j].l, low[i][j]);
-#pragma unroll
-        for (int j = 0; j < S::NB; ++j) mma(a.l, b[j].m, low[i][j]);
-#pragma unroll
-        for (int j = 0; j < S::NB; ++j) mma(a.l, b[j].h, low[i][j]);
-#pragma unroll
-        for (int j = 0; j < S::NB; ++j) mma(a.h, b[j].l, low[i][j]);
-#pragma unroll
-        for (int j = 0; j < S::NB; ++j) mma(a.m, b[j].m, low[i][j]);
-#pragma unroll
-        for (int j = 0; j < S::NB; ++j) mma(a.m, b[j].h, low[i][j]);
-#pragma unroll
-        for (int j = 0; j < S::NB; ++j) mma(a.h, b[j].m, low[i][j]);
-#pragma unroll
-        for (int j = 0; j < S::NB; ++j) mma(a.h, b[j].h, acc[i][j]);
-        LLAMARL_FENCE();
+        products(a, b, 0);
+        lds_barrier();
+        char* t = cur;
+        cur = other;
+        other = t;
+      }
+    } else {
+      for (int kt = 0; kt < nk; ++kt) {
+        split();
+        lds_barrier();                                 // everyone is done with the previous slab's parts
+        write(smem);
+        if (kt + 1 < nk) load((kt + 1) * BK, x);
+        lds_barrier();
+        Split3 b[S::NB];
+  #pragma unroll
+        for (int j = 0; j < S::NB; ++j) b[j] = parts(smem + pb + j * SPLIT_BYTES);
+        // The next row block is read under this one's MFMAs; left to itself the compiler reads it where it is used.
+        Split3 next = parts(smem + pa);
+  #pragma unroll
+        for (int i = 0; i < S::MB; ++i) {
+          const Split3 a = next;
+          LLAMARL_FENCE();
+          if (i + 1 < S::MB) next = parts(smem + pa + (i + 1) * SPLIT_BYTES);
+          LLAMARL_FENCE();
+          products(a, b, i);
+          LLAMARL_FENCE();
+        }
       }
     }
   }
@@ -361,7 +400,7 @@ struct TileGemmSplit {
   template <bool A_SCALED = false>
   __device__ __forceinline__ void run(char* smem, f32x4_t (&acc)[S::MB][S::NB]) {
     const float factor = A_SCALED ? unscale : 1.f;
-    int* redo = reinterpret_cast<int*>(smem + BLOCKS * SPLIT_BYTES);
+    int* redo = reinterpret_cast<int*>(smem + STAGES * STAGE_BYTES);
     if (threadIdx.x == 0) *redo = 0;
     wait_vmcnt0();                                   // token words (TokenWords) are there after the first barrier
     f32x4_t low[S::MB][S::NB];

@@ -38,8 +38,8 @@ typedef TileGemmSmall<BF16, Shape128, 2, 2> Bf16Loop128;
 typedef TileGemmSmall<BF16, Shape64, 4, 2> Bf16Loop64;
 typedef TileGemmTNSmall<Shape128, 2, 2> Bf16LoopTN128;
 typedef TileGemmTNSmall<Shape64, 4, 2> Bf16LoopTN64;
-typedef TileGemmSplit<Shape128, 2> F32Loop128;
-typedef TileGemmSplit<Shape64, 3> F32Loop64;
+typedef TileGemmSplit<Shape128, 2, 1> F32Loop128;
+typedef TileGemmSplit<Shape64, 3, 2> F32Loop64;
 
 // ---- workspace layouts (every block 256-byte aligned) ----------------------------------------------------
 struct FwdWs {
