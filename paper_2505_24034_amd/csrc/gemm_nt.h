@@ -384,8 +384,11 @@ __device__ __forceinline__ bool half_slab_left(int K) { return (unsigned)(K - 1)
 // channels of the memory: 256 workgroups streaming 1 GB of W took 235 us (4.5 TB/s) from slab 0, whatever their slabs in flight,
 // and 169 us (6.2) each from a slab of its own.  Workgroups that share a row of patches, and so the panels in their L2, start
 // together; the next row starts two slabs (256 bytes) on.  Forward call over a 128256 x 4096 head: 40 tokens 236 -> 181 us, 150
-// 228 -> 194, 300 309 -> 294.  Only where W streams: with more than TURN_COLUMNS columns of tiles, whose panels come from the caches, it
-// cost up to 1 %.
+// 228 -> 194, 300 309 -> 294.  Only where W streams: with more than TURN_COLUMNS columns of tiles the panels come from the caches.  There
+// 256 and 320 columns have a loop without it (TURN): two more scalar registers through the main loop and eight more scalar
+// operations a slab cost dz of 33001 x 1032 0.3 - 1.6 % (6400 tokens 455 / 461 us, 9500 663 / 671; 128256 x 4096, 8576 tokens: 6434 / 6482)
+// and 320 columns up to 1 % (8576 tokens 6234 / 6284) although nothing turned.  At 225, 500 and 900 tokens of a 128256 x 4096 head
+// turning takes dz from 324 to 271, 470 to 447 and 801 to 789 us.
 constexpr int TURN_COLUMNS = 4;
 struct SlabOrder {
   int whole, turn;
@@ -410,8 +413,8 @@ struct SlabOrder {
 //
 // NEAR: a lane's column blocks hold neighbouring output columns (tile_row_of); the epilogue must then take its columns from
 // LanePos::col_near().
-// YOUNGER, FIRST_ONLY: see run().
-template <typename TT, int LOAD_SLOT, int YOUNGER, bool FIRST_ONLY>
+// YOUNGER, FIRST_ONLY: see run().  TURN: slabs in the order of SlabOrder.
+template <typename TT, int LOAD_SLOT, int YOUNGER, bool FIRST_ONLY, bool TURN = false>
 struct TileGemm {
   typedef TT Type;
   typedef Shape256 Shape;
@@ -427,7 +430,7 @@ struct TileGemm {
   SlabOrder order;
   __device__ __forceinline__ static constexpr int width() { return Shape::BN; }
 
-  __device__ __forceinline__ int k_of(int kt) const { return FIRST_ONLY ? order.k<BK>(kt) : kt * BK; }
+  __device__ __forceinline__ int k_of(int kt) const { return TURN ? order.k<BK>(kt) : kt * BK; }
 
   template <bool NEAR>
   __device__ __forceinline__ void prefetch(const void* A_tile, int64_t lda, int rowsA, const void* B_tile, int64_t ldb,
@@ -453,7 +456,7 @@ struct TileGemm {
                                                  int64_t b_total, int turn) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
-    order.init<BK>(K, turn);
+    if (TURN) order.init<BK>(K, turn);
     la.init(A_tile, lda, rowsA, wave, lane);
     lb.template init_gathered<NEAR>(B_base, ldb, b_total, grow, rowsB, wave, lane);
   }
@@ -564,7 +567,7 @@ struct TileGemm {
 // As TileGemm (see there); two slabs of 72 KB.  A product takes a tenth fewer bytes from L2 and LDS than on 256 x 256, and a
 // fifth fewer barriers and epilogues.  247 registers.  (A word of every line of W two slabs ahead, to have it in L2 earlier: 300
 // tokens 305 -> 330 us; a barrier that leaves one request in flight for that: the long contractions +2 %.)
-template <typename TT>
+template <typename TT, bool TURN>
 struct TileGemmWide {
   typedef TT Type;
   typedef Shape320 Shape;
@@ -584,13 +587,15 @@ struct TileGemmWide {
   SlabOrder order;
   __device__ __forceinline__ static constexpr int width() { return Shape::BN; }
 
+  __device__ __forceinline__ int k_of(int kt) const { return TURN ? order.k<BK>(kt) : kt * BK; }
+
   template <bool NEAR>
   __device__ __forceinline__ void setup_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
                                                  int64_t ldb, int rowsB, int64_t K_, const int (&grow)[LoaderB::ITERS],
                                                  int64_t b_total, int turn) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
-    order.init<BK>(K, turn);
+    if (TURN) order.init<BK>(K, turn);
     la.init(A_tile, lda, rowsA, wave, lane);
     lb.template init_gathered<NEAR>(B_base, ldb, b_total, grow, rowsB, wave, lane);
   }
@@ -599,7 +604,7 @@ struct TileGemmWide {
     const int lane = threadIdx.x & 63, wave = wave_id();
     char* st = smem + (part >> 1) * Shape::STAGE_BYTES;
     if (part > 1 && BK >= K) return;
-    const int k0 = order.k<BK>(part >> 1);
+    const int k0 = k_of(part >> 1);
     if ((part & 1) == 0) la.issue(st, k0, K, wave, lane);
     else lb.issue(st + SLAB_A_BYTES, k0, K, wave, lane);
   }
@@ -612,8 +617,8 @@ struct TileGemmWide {
       char* cur = smem + (kt & 1) * Shape::STAGE_BYTES;
       wait_vmcnt0();
       __syncthreads();
-      la.issue(cur, order.k<BK>(kt + 2), K, wave, lane);
-      lb.issue(cur + SLAB_A_BYTES, order.k<BK>(kt + 2), K, wave, lane);
+      la.issue(cur, k_of(kt + 2), K, wave, lane);
+      lb.issue(cur + SLAB_A_BYTES, k_of(kt + 2), K, wave, lane);
     }
     if (nk >= 2) {
       wait_vmcnt0();
@@ -645,7 +650,7 @@ struct TileGemmWide {
       char* cur = smem + (kt & 1) * Shape::STAGE_BYTES;
       const char* nxt = smem + ((kt + 1) & 1) * Shape::STAGE_BYTES;
       LLAMARL_FENCE();
-      const Fetch sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, order.k<BK>(kt + 2), K, wave, lane};
+      const Fetch sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, k_of(kt + 2), K, wave, lane};
       wide_k_step<TT, Fetch, true, true, true>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0], nxt + b_addr[0], &sf);
       wide_k_step<TT, Fetch, false, true, false>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
     }

@@ -97,7 +97,9 @@ struct FwdArgs {
 };  // partials and zt are indexed by compacted position, not by token
 
 typedef TileGemm<BF16, 11, 2, true> Logits256;      // counted: the two stores of a token's partials
-typedef TileGemmWide<BF16> LogitsWide;
+typedef TileGemm<BF16, 11, 2, true, true> Logits256Turned;
+typedef TileGemmWide<BF16, false> LogitsWide;
+typedef TileGemmWide<BF16, true> LogitsWideTurned;
 // zeros from an opaque register: as constants the compiler sets them ahead of the branch, for every tile
 template <int M, int N>
 __device__ __forceinline__ void clear(f32x4_t (&acc)[M][N]) {
@@ -122,7 +124,8 @@ __device__ __forceinline__ void run_tile(G& g, char* smem, f32x4_t (&acc)[G::Sha
     }
   }
   if constexpr (nb == 0) {
-  } else if constexpr (std::is_same<G, Logits256>::value || std::is_same<G, LogitsWide>::value) g.run(smem, acc, counted);
+  } else if constexpr (std::is_same<G, Logits256>::value || std::is_same<G, Logits256Turned>::value ||
+                       std::is_same<G, LogitsWide>::value || std::is_same<G, LogitsWideTurned>::value) g.run(smem, acc, counted);
   else if constexpr (G::HALVES && !G::KMAJOR) g.template run<nb>(smem, acc, counted);
   else if constexpr (G::HALVES) g.template run<nb>(smem, acc);
   else g.run(smem, acc);
@@ -416,30 +419,25 @@ template <typename G>
 __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partials(FwdArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int n_act = *a.n_act;
-  TileSchedule<PATCH_ROWS_LOGITS> sch;
+  auto walk = [&](auto g) __attribute__((always_inline)) {
+    TileSchedule<PATCH_ROWS_LOGITS> sch;
+    // token tiles that hold active rows only
+    sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
+    if (!sch.has_tile()) return;                     // block-uniform
+    with_blocks(g, [&](auto blocks) { fwd_tiles<decltype(g), decltype(blocks)::value>(a, g, sch, n_act, smem); });
+  };
   if constexpr (HAS_NARROW<G>) {
     const int width = fwd_width(a.tiles_v, n_act, a.d, gridDim.x).width;
-    if (width == LogitsWide::width()) {
-      LogitsWide g;
-      sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
-      if (!sch.has_tile()) return;
-      fwd_tiles<LogitsWide, LogitsWide::Shape::NB>(a, g, sch, n_act, smem);
-      return;
-    }
+    const bool turn = n_act <= TURN_COLUMNS * width;
+    if (width == LogitsWide::width()) return turn ? walk(LogitsWideTurned()) : walk(LogitsWide());
     if (width <= NARROW_BN) {
       LogitsNarrow g;
       g.set_width(width);
-      sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
-      if (!sch.has_tile()) return;
-      with_blocks(g, [&](auto blocks) { fwd_tiles<LogitsNarrow, decltype(blocks)::value>(a, g, sch, n_act, smem); });
-      return;
+      return walk(g);
     }
+    if (turn) return walk(Logits256Turned());
   }
-  G g;
-  // token tiles that hold active rows only
-  sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
-  if (!sch.has_tile()) return;                       // block-uniform
-  fwd_tiles<G, G::Shape::NB>(a, g, sch, n_act, smem);
+  walk(G());
 }
 
 // lse[t] = log sum over vocab tiles; logp[t] = z[t,y_t] - lse[t], for the active tokens (the compaction pass
@@ -910,22 +908,23 @@ template <typename G>
 __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_bwd_dz(DzArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int n_act = *a.n_act;
-  TileSchedule<PATCH_ROWS_LOGITS> sch;
+  auto walk = [&](auto g) __attribute__((always_inline)) {
+    TileSchedule<PATCH_ROWS_LOGITS> sch;
+    // token tiles that hold active rows only
+    sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
+    if (!sch.has_tile()) return;                     // block-uniform
+    with_blocks(g, [&](auto blocks) { dz_tiles<decltype(g), decltype(blocks)::value>(a, g, sch, n_act, smem); });
+  };
   if constexpr (HAS_NARROW<G>) {
     const int width = dz_width(a.tiles_v, n_act, a.d, gridDim.x).width;
     if (width <= NARROW_BN) {
       LogitsNarrow g;
       g.set_width(width);
-      sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
-      if (!sch.has_tile()) return;
-      with_blocks(g, [&](auto blocks) { dz_tiles<LogitsNarrow, decltype(blocks)::value>(a, g, sch, n_act, smem); });
-      return;
+      return walk(g);
     }
+    if (n_act <= TURN_COLUMNS * width) return walk(Logits256Turned());
   }
-  G g;
-  sch.init(a.tiles_v, (n_act + g.width() - 1) / g.width(), blockIdx.x, gridDim.x);
-  if (!sch.has_tile()) return;                       // block-uniform: no active token at all
-  dz_tiles<G, G::Shape::NB>(a, g, sch, n_act, smem);
+  walk(G());
 }
 
 struct StoreArgs {

@@ -1,0 +1,72 @@
+"""What the compiler made of the kernels, read from the built library's own code object: properties that the sources' main loops
+rely on and that no result shows."""
+import collections
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+import yaml
+
+from paper_2505_24034_amd import build
+
+LLVM = os.path.join(build.rocm_root(), "llvm", "bin")
+
+
+def _run(tool, *args):
+    return subprocess.run([os.path.join(LLVM, tool), *args], stdout=subprocess.PIPE, text=True, check=True).stdout
+
+
+@pytest.fixture(scope="module")
+def code_object(tmp_path_factory):
+    """the gfx950 part of libllamarl.so: a bundle of (offset, size, length of the target's name, the name)"""
+    data = open(build.LIB_PATH, "rb").read()
+    start = data.index(b"__CLANG_OFFLOAD_BUNDLE__")
+    at = start + 32
+    for _ in range(struct.unpack_from("<Q", data, start + 24)[0]):
+        offset, size, n = struct.unpack_from("<QQQ", data, at)
+        if data[at + 24:at + 24 + n].endswith(b"gfx950"):
+            path = tmp_path_factory.mktemp("code") / "gfx950.elf"
+            path.write_bytes(data[start + offset:start + offset + size])
+            return str(path)
+        at += 24 + n
+    raise AssertionError("no gfx950 code in " + build.LIB_PATH)
+
+
+@pytest.fixture(scope="module")
+def kernels(code_object):
+    """mangled name -> the compiler's record"""
+    notes = _run("llvm-readelf", "--notes", code_object)
+    records = yaml.safe_load(notes[notes.index("amdhsa.kernels:"):].split("\n...")[0])
+    return {k[".name"]: k for k in records["amdhsa.kernels"]}
+
+
+@pytest.fixture(scope="module")
+def loops(code_object):
+    """mangled name -> counts of the instructions of each block that branches back to its own start"""
+    out, kernel, block, counts = collections.defaultdict(list), None, None, None
+    for line in _run("llvm-objdump", "-d", "--no-show-raw-insn", "--symbolize-operands", code_object).splitlines():
+        if m := re.match(r"[0-9a-f]+ <(_Z\w+)>:", line):
+            kernel, block, counts = m.group(1), None, collections.Counter()
+        elif m := re.match(r"[0-9a-f]+ <(L\d+)>:", line):
+            block, counts = m.group(1), collections.Counter()
+        elif m := re.match(r"\s+([a-z]\w+) ?(\S*)", line):
+            op = m.group(1)
+            counts["mfma" if "mfma" in op else op.split("_")[0]] += 1
+            if op.startswith("s_cbranch"):
+                if m.group(2) == block:
+                    out[kernel].append(counts)
+                block = None                          # what follows does not belong to the loop
+    return out
+
+
+@pytest.mark.parametrize("kernel,mfmas,scalar", [("k_fwd_partials", 64, 50), ("k_bwd_dz", 64, 50), ("k_fwd_partials", 80, 59)])
+def test_long_contractions_have_a_loop_without_an_order_of_slabs(loops, kernel, mfmas, scalar):
+    # MFMAs of a wavefront a slab: 64 on 256 columns (and in the narrow loop's left half), 80 on 320.  49 and 58 scalar instructions:
+    # three for each of the eight or nine requests, the waits and the barrier, addresses, the count and the branch.  The order
+    # of slabs adds four or more.
+    found = [c["s"] for name, blocks in loops.items() if re.match(r"_ZN7llamarl\d+%sINS_8TileGemmI" % kernel, name)
+             for c in blocks if c["mfma"] == mfmas]
+    assert found
+    assert min(found) <= scalar, found

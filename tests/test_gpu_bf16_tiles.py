@@ -93,6 +93,14 @@ def test_wide_token_tiles(lib, N, V, d):
     _check_head(lib, N, V, d)
 
 
+# 256 columns, slabs taken from another one than the first on up to 1024 tokens, in order beyond: one column of tiles, two, the last
+# of each loop and the first of the other; whole slabs and a rest
+@pytest.mark.parametrize("N,d", [(200, 264), (256, 576), (500, 576), (500, 520), (1024, 264), (1024, 520), (1025, 264), (1025, 520)])
+def test_turned_slabs(lib, N, d):
+    assert loops(N, 49200, d)[:2] == ("256x256", "256x256")
+    _check_head(lib, N, 49200, d)
+
+
 # the last slab up to its half, just past it and full, alone and after others: 128 x 128 tiles, 160 columns, 128 and 256
 @pytest.mark.parametrize("d", [32, 40, 64, 96, 104, 160, 168])
 @pytest.mark.parametrize("N,V", [(40, 33000), (400, 33000), (1000, 49200)])
