@@ -254,7 +254,8 @@ llamarl_status llamarl_offpolicy_loss_bwd_slice(const void* H, const void* W_sli
  * (phase_events[0..5], HOST array of hipEvent_t passed as void*) on `stream`: [0] before the first kernel,
  * [1] after the set-up kernels (active-row list, zeroed dH rows, operand panels), [2] after the recompute + dz
  * kernel, [3] after the dH contraction (the reduction of its last round's split tiles included), [4] = [3],
- * [5] after the dW contraction.  Same results, same
+ * [5] after the dW contraction.  A head whose gradients are both contracted on tiles smaller than 256 x 256 (every fp32 one) has
+ * them in one launch: there [3] and [4] stand before it, and [4] to [5] is both contractions.  Same results, same
  * kernels, same error behaviour (plus INVALID_ARG for a null event).  The backward's four stages are all in this
  * one call, so per-kernel rooflines of the backward can only be timed from inside it.
  */

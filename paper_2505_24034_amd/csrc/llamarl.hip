@@ -480,8 +480,10 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     o.A = dzt; o.B = ht; o.packed_a = o.packed_b = 1; o.pitch_count = o.k_count = n_act; o.M = V; o.Nn = d; o.K = w.ldzt;
     o.C = dW; o.ldc = d; o.c_is_f32 = dW_dt == LLAMARL_F32; o.accumulate = c == 0 ? accumulate_dW : 1; o.part = part;
     o.plan_out = plan + 4; o.a_scale = dz_scale;
-    if (!ev && dh_tile != TILE_256 && dw_tile != TILE_256) {
+    if (dh_tile != TILE_256 && dw_tile != TILE_256) {
       const bool h128 = dh_tile == TILE_128, w128 = dw_tile == TILE_128;
+      if (c == 0) PHASE_EVENT(3);
+      if (c == 0) PHASE_EVENT(4);
       if constexpr (kBf16)
         s = (h128 ? (w128 ? launch_store_pair<Bf16LoopTN128, Bf16Loop128> : launch_store_pair<Bf16LoopTN128, Bf16Loop64>)
                   : (w128 ? launch_store_pair<Bf16LoopTN64, Bf16Loop128> : launch_store_pair<Bf16LoopTN64, Bf16Loop64>))(
@@ -491,24 +493,18 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
                   : (w128 ? launch_store_pair<F32Loop64, F32Loop128> : launch_store_pair<F32Loop64, F32Loop64>))(
             h, o, part, w.part, st);
       if (s != LLAMARL_OK) return s;
-      continue;
-    }
-    if constexpr (kBf16)
+    } else if constexpr (kBf16) {                      // fp32 has no other tiles
       s = (dh_tile == TILE_256   ? launch_store<TileGemmTN>
            : dh_tile == TILE_128 ? launch_store<Bf16LoopTN128>
                                  : launch_store<Bf16LoopTN64>)(h, w.part, st);
-    else
-      s = (dh_tile == TILE_128 ? launch_store<F32Loop128> : launch_store<F32Loop64>)(h, w.part, st);
-    if (s != LLAMARL_OK) return s;
-    if (c == 0) PHASE_EVENT(3);
-    if (c == 0) PHASE_EVENT(4);
-    if constexpr (kBf16)
+      if (s != LLAMARL_OK) return s;
+      if (c == 0) PHASE_EVENT(3);
+      if (c == 0) PHASE_EVENT(4);
       s = (dw_tile == TILE_256   ? launch_store<Store256>
            : dw_tile == TILE_128 ? launch_store<Bf16Loop128>
                                  : launch_store<Bf16Loop64>)(o, w.part, st);
-    else
-      s = (dw_tile == TILE_128 ? launch_store<F32Loop128> : launch_store<F32Loop64>)(o, w.part, st);
-    if (s != LLAMARL_OK) return s;
+      if (s != LLAMARL_OK) return s;
+    }
     if (c == 0) PHASE_EVENT(5);
   }
 #undef PHASE_EVENT

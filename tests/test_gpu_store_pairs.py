@@ -56,3 +56,24 @@ def test_pair(lib, dt, N, V, d, share, edges, form):
         rounds = 2.0 ** -22 if got.dtype == torch.float32 else result
         assert bool(((got.double() - ref).abs() <= each * bound + rounds * ref.abs()).all()), name
     assert not bool(dH[coef == 0].any())
+
+
+@pytest.mark.parametrize("dt,N,V,d,share,edges", [c for c in SIZES if c[1] >= 300])
+def test_the_call_that_records_events_runs_the_same_kernels(lib, dt, N, V, d, share, edges):
+    g = torch.Generator(device="cuda").manual_seed(N + V + d)
+    store = torch.bfloat16 if dt == "bf16" else torch.float32
+    H = torch.randn(N, d, generator=g, device="cuda").to(store)
+    W = (torch.randn(V, d, generator=g, device="cuda") * d ** -0.5).to(store)
+    y = torch.randint(0, V, (N,), generator=g, device="cuda").int()
+    coef = torch.randn(N, generator=g, device="cuda") / N
+    coef[torch.rand(N, generator=g, device="cuda") >= share] = 0.0
+    lse = lib.token_logprobs(H, W, y)[1]
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(6)]
+    for e in events:
+        e.record()
+    plain = lib.offpolicy_loss_bwd(H, W, y, lse, coef)
+    timed = lib.offpolicy_loss_bwd(H, W, y, lse, coef, phase_events=[e.cuda_event for e in events])
+    assert all(torch.equal(a, b) for a, b in zip(plain, timed))       # other parts of K would be another order of the sums
+    torch.cuda.synchronize()
+    between = [a.elapsed_time(b) for a, b in zip(events, events[1:])]
+    assert min(between) >= 0 and between[4] > between[2]
