@@ -175,7 +175,8 @@ llamarl_status llamarl_offpolicy_loss_fwd_static(const float* logp, const float*
  *   grad_loss      in  upstream scalar dL/dloss (host value, usually 1)
  *   dH             out [N,d] of type dt
  *   dW             out [V,d] of type dW_dt (LLAMARL_F32 or dt); if
- *                      accumulate_dW != 0 the result is added to what dW holds
+ *                      accumulate_dW != 0 the result is added to what dW holds;
+ *                      may be W itself: it is written when nothing reads W any more
  *   ws             scratch, >= llamarl_workspace_bytes(N,d,V,dt,LLAMARL_PASS_LOSS_BWD)
  */
 llamarl_status llamarl_offpolicy_loss_bwd(const void* H, const void* W, const int32_t* targets, const float* lse,
@@ -203,6 +204,7 @@ llamarl_status llamarl_offpolicy_loss_bwd_device_scale(const void* H, const void
  * nothing to do and cost microseconds.  A caller who knows that at most R rows are active bounds the workspace at
  * no cost; a smaller R trades it for one read-modify-write of dW per extra pass -- and, for a bf16 dW, one more
  * rounding to bf16 per pass (use dW_dt = LLAMARL_F32 when that matters).  max_rows_per_pass = 0 means N.
+ * dW must not be W where more than one pass has work: a later pass recomputes its logits from W.
  * A dH row comes out of one pass only; it equals the one-pass result up to the order of its fp32 sums (where the
  * contraction's K range is cut depends on how many tiles the pass has), and is reproducible run to run like
  * everything else.
@@ -255,7 +257,7 @@ llamarl_status llamarl_offpolicy_loss_bwd_slice(const void* H, const void* W_sli
  * [1] after the set-up kernels (active-row list, zeroed dH rows, operand panels), [2] after the recompute + dz
  * kernel, [3] after the dH contraction (the reduction of its last round's split tiles included), [4] = [3],
  * [5] after the dW contraction.  A head whose gradients are both contracted on tiles smaller than 256 x 256 (every fp32 one) has
- * them in one launch: there [3] and [4] stand before it, and [4] to [5] is both contractions.  Same results, same
+ * them in one launch (unless dW is W in bf16): there [3] and [4] stand before it, and [4] to [5] is both contractions.  Same results, same
  * kernels, same error behaviour (plus INVALID_ARG for a null event).  The backward's four stages are all in this
  * one call, so per-kernel rooflines of the backward can only be timed from inside it.
  */

@@ -273,6 +273,11 @@ llamarl_status launch_store(StoreArgs a, size_t part_bytes, hipStream_t st) {
   return with_mode<G>(a, [&](auto mode) { return launch_store_mode<G, decltype(mode)::value>(a, st); });
 }
 
+bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + (uint64_t)b_bytes && y < x + (uint64_t)a_bytes;
+}
+
 // dH (h, which never accumulates) and dW (w) in one launch, and their split tiles in another; parts: the workspace's blocks,
 // of which each contraction takes what its parts can need, dH at least half.
 template <typename GH, typename GW>
@@ -480,7 +485,9 @@ llamarl_status run_bwd(const void* H, const void* W, const int32_t* targets, con
     o.A = dzt; o.B = ht; o.packed_a = o.packed_b = 1; o.pitch_count = o.k_count = n_act; o.M = V; o.Nn = d; o.K = w.ldzt;
     o.C = dW; o.ldc = d; o.c_is_f32 = dW_dt == LLAMARL_F32; o.accumulate = c == 0 ? accumulate_dW : 1; o.part = part;
     o.plan_out = plan + 4; o.a_scale = dz_scale;
-    if (dh_tile != TILE_256 && dw_tile != TILE_256) {
+    // bf16's dH reads W: a dW that is W itself (weights updated in place) is written when that is over
+    const bool dw_over_w = kBf16 && overlap(W, V * d * 2, dW, V * d * (o.c_is_f32 ? 4 : 2));
+    if (dh_tile != TILE_256 && dw_tile != TILE_256 && !dw_over_w) {
       const bool h128 = dh_tile == TILE_128, w128 = dw_tile == TILE_128;
       if (c == 0) PHASE_EVENT(3);
       if (c == 0) PHASE_EVENT(4);

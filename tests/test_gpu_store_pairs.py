@@ -77,3 +77,26 @@ def test_the_call_that_records_events_runs_the_same_kernels(lib, dt, N, V, d, sh
     torch.cuda.synchronize()
     between = [a.elapsed_time(b) for a, b in zip(events, events[1:])]
     assert min(between) >= 0 and between[4] > between[2]
+
+
+# bf16's dH reads W, so this is no pair: dW is written when dH is done
+@pytest.mark.parametrize("dt,N,V,d,share,edges", [c for c in SIZES if c[1] >= 300])
+def test_weights_updated_in_place(lib, dt, N, V, d, share, edges):
+    g = torch.Generator(device="cuda").manual_seed(N + V + d)
+    store = torch.bfloat16 if dt == "bf16" else torch.float32
+    H = torch.randn(N, d, generator=g, device="cuda").to(store)
+    W = (torch.randn(V, d, generator=g, device="cuda") * d ** -0.5).to(store)
+    y = torch.randint(0, V, (N,), generator=g, device="cuda").int()
+    coef = torch.randn(N, generator=g, device="cuda") / N
+    coef[torch.rand(N, generator=g, device="cuda") >= share] = 0.0
+    lse = lib.token_logprobs(H, W, y)[1]
+    dH, dW = lib.offpolicy_loss_bwd(H, W, y, lse, coef, dW_dtype=torch.float32)
+    updated = W.clone()
+    got, _ = lib.offpolicy_loss_bwd(H, updated, y, lse, coef, dW=updated, accumulate_dW=True)
+    # Both dH are sums of the same products, their K cut into other parts: fp32 sums of up to 2^14 terms in another order, below
+    # 2^-17 of their largest.  That can put them on either side of the middle between two bf16 numbers, which are up to 2^-7 of
+    # the smaller one apart (eight significant bits); one rounding of a sum is half of that.
+    apart = 2.0 ** -7 if dt == "bf16" else 0.0
+    assert bool(((got.double() - dH.double()).abs() <= apart * dH.double().abs() + 2.0 ** -17 * dH.double().abs().max()).all())
+    want = W.double() + dW.double()
+    assert bool(((updated.double() - want).abs() <= (apart / 2 + 2.0 ** -23) * want.abs() + 2.0 ** -17 * dW.double().abs().max()).all())
