@@ -220,7 +220,9 @@ struct TileGemmSplit {
   template <bool NEAR>
   __device__ __forceinline__ void prefetch(const void* A_tile, int64_t lda, int rowsA, const void* B_tile, int64_t ldb,
                                            int rowsB, int64_t K_, char*) {
-    const int lane = threadIdx.x & 63, wave = wave_id();
+    int tid = threadIdx.x;                           // opaque per tile: what depends on the lane alone is not kept for the next
+    asm volatile("" : "+v"(tid));                    // one, which took two or three registers more than there are (scratch)
+    const int lane = tid & 63, wave = wave_id();
     K = (int)K_;
     if (holds_a(wave)) {                             // wave-uniform
       set_a(A_tile, lda, rowsA, wave, lane);

@@ -70,3 +70,10 @@ def test_long_contractions_have_a_loop_without_an_order_of_slabs(loops, kernel, 
              for c in blocks if c["mfma"] == mfmas]
     assert found
     assert min(found) <= scalar, found
+
+
+def test_no_kernel_keeps_vector_registers_in_memory(kernels):
+    # reloads wait for what was requested before them, a tile's first slabs for instance
+    spilled = {n: (k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for n, k in kernels.items()
+               if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
+    assert not spilled
