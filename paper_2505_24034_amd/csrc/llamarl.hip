@@ -208,9 +208,10 @@ hipError_t set_lds_if_large(K kernel, int bytes) {
   return bytes > 65536 ? set_lds(kernel, bytes) : hipSuccess;
 }
 
-// C [M,Nn] (+)= A B^T, see StoreArgs; a: the caller's part of the arguments (operands, counts, output, workspace).
+// C [M,Nn] (+)= A B^T, see StoreArgs; a: the caller's part of the arguments (operands, counts, output, workspace); workgroups: at
+// most so many of them.
 template <typename G>
-llamarl_status plan_store(StoreArgs& a, size_t part_bytes, bool paired) {
+llamarl_status plan_store(StoreArgs& a, size_t part_bytes, int workgroups) {
   constexpr int BM = G::Shape::BM, BN = G::Shape::BN, BK = 8 * G::Type::EPC;
   // the store epilogue of the K-contiguous loop writes four neighbouring columns per lane as one unit, and so
   // does the tail reduction
@@ -231,14 +232,7 @@ llamarl_status plan_store(StoreArgs& a, size_t part_bytes, bool paired) {
   constexpr int64_t PART_K = 4 * BK;                         // a part has four slabs or more
   // a small contraction still gets a workgroup per split
   const int64_t items = (int64_t)tiles * std::min<int64_t>(STORE_MAX_SPLITS, std::max<int64_t>(1, (a.K + PART_K - 1) / PART_K));
-  const int full = persistent_grid((int64_t)1 << 30, G::GROUPS_PER_CU);
-  // Of a pair each contraction takes half of the workgroups (both have the same products to form) and cuts its tiles into fewer
-  // parts, except where a tile is few slabs: its first loads and its stores want workgroups.  Backward at (N, V, d), three
-  // quarters of the rows active, one contraction after the other / together, each cut for the whole grid / as here, us:
-  //   fp32 (256, 1024, 256) 42.2 / 33.0 / 33.0, (1024, 4096, 512) 129 / 119 / 111, (300, 16400, 260) 117 / 120 / 114 (130 on halves),
-  //   (4800, 20011, 516) 1622 / 1622 / 1593; bf16 (1041, 5003, 520) 58.8 / 52.8 / 46.4, (512, 8192, 1024) 58.9 / 52.0 / 50.1,
-  //   (2048, 4096, 264) 64.6 / 48.3 / 44.6, (4096, 3000, 512) 74.7 / 68.2 / 63.2, (300, 16400, 264) 43.8 / 40.0 / 38.9.
-  a.grid = (int)std::min<int64_t>(items, paired && a.K >= 12 * BK ? full / 2 : full);
+  a.grid = (int)std::min<int64_t>(items, workgroups);
   // the split tiles of the last round, if the device-side sizes left any: fewer than `grid` of them.  A contraction
   // whose longest K leaves no two parts of four slabs is never split (StorePlan::init).
   a.tail_blocks = (a.K + BK - 1) / BK < 8 ? 0 : std::min(std::min(a.grid - 1, tiles) * TailUnit<typename G::Shape>::PER_TILE, TAIL_MAX_BLOCKS);
@@ -268,7 +262,7 @@ llamarl_status with_mode(const StoreArgs& a, F&& f) {
 }
 template <typename G>
 llamarl_status launch_store(StoreArgs a, size_t part_bytes, hipStream_t st) {
-  const llamarl_status s = plan_store<G>(a, part_bytes, false);
+  const llamarl_status s = plan_store<G>(a, part_bytes, persistent_grid((int64_t)1 << 30, G::GROUPS_PER_CU));
   if (s != LLAMARL_OK) return s;
   return with_mode<G>(a, [&](auto mode) { return launch_store_mode<G, decltype(mode)::value>(a, st); });
 }
@@ -283,14 +277,16 @@ bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
 template <typename GH, typename GW>
 llamarl_status launch_store_pair(StoreArgs h, StoreArgs w, float* parts, size_t part_bytes, hipStream_t st) {
   constexpr size_t BLOCK_H = GH::Shape::BM * GH::Shape::BN * 4, BLOCK_W = GW::Shape::BM * GW::Shape::BN * 4;
-  constexpr int BK = 8 * GW::Type::EPC;
+  constexpr int BK = 8 * GW::Type::EPC;                // both have operands of one type
   const int64_t most_w = tile_count(w.M, w.Nn, GW::Shape::BM) * std::min<int64_t>(STORE_MAX_SPLITS, (w.K + BK - 1) / BK / 4);
   const size_t for_w = std::min(part_bytes / 2, (size_t)most_w * BLOCK_W);
   const size_t for_h = (part_bytes - for_w) / BLOCK_H * BLOCK_H;
   h.part = parts;
   w.part = parts + for_h / 4;
-  llamarl_status s = plan_store<GH>(h, for_h, true);
-  if (s == LLAMARL_OK) s = plan_store<GW>(w, part_bytes - for_h, true);
+  const bool h_long = h.K >= PAIR_LONG_SLABS * BK, w_long = w.K >= PAIR_LONG_SLABS * BK;
+  const int cus = persistent_grid((int64_t)1 << 30);
+  llamarl_status s = plan_store<GH>(h, for_h, pair_workgroups(cus, GH::GROUPS_PER_CU, GW::GROUPS_PER_CU, h_long, w_long));
+  if (s == LLAMARL_OK) s = plan_store<GW>(w, part_bytes - for_h, pair_workgroups(cus, GW::GROUPS_PER_CU, GH::GROUPS_PER_CU, w_long, h_long));
   if (s != LLAMARL_OK) return s;
   return with_mode<GW>(w, [&](auto mode) -> llamarl_status {
     constexpr int MODE_H = sizeof(typename GH::Type::store_t) == 2 ? 3 : 1, MODE_W = decltype(mode)::value;

@@ -435,6 +435,10 @@ PyObject* logits_tile(PyObject* const* a) {
 PyObject* store_tile(PyObject* const* a) {
   return PyLong_FromLong(llamarl::tile_edge(llamarl::store_tile(integer(a[0]), integer(a[1]), integer(a[2]), integer(a[3]) != 0)));
 }
+// CUs, workgroups of the one and of the other a CU holds, whether the one and the other are long
+PyObject* pair_workgroups(PyObject* const* a) {
+  return PyLong_FromLong(llamarl::pair_workgroups((int)integer(a[0]), (int)integer(a[1]), (int)integer(a[2]), integer(a[3]) != 0, integer(a[4]) != 0));
+}
 // tiles_v, active rows, d, grid, backward: columns of the tiles of 256 vocabulary rows
 PyObject* logits_width(PyObject* const* a) {
   const auto rule = integer(a[4]) ? llamarl::dz_width : llamarl::fwd_width;
@@ -467,7 +471,7 @@ PyObject* set_error(PyObject*, PyObject* cls) {
 PyMethodDef g_methods[] = {
     ENTRY(token_logprobs, 6), ENTRY(token_logprobs_partial, 8), ENTRY(merge_partials, 4), ENTRY(offpolicy_loss_fwd, 15),
     ENTRY(offpolicy_loss_bwd, 13), ENTRY(offpolicy_loss_bwd_slice, 10), ENTRY(offpolicy_loss_bwd_device_scale, 9),
-    ENTRY(group_advantages, 5), ENTRY(kl_shaped_rewards, 6), ENTRY(tile_walk, 3), ENTRY(logits_width, 5), ENTRY(dz_columns, 2), ENTRY(logits_tile, 5), ENTRY(store_tile, 4), {"set_error", set_error, METH_O, nullptr},
+    ENTRY(group_advantages, 5), ENTRY(kl_shaped_rewards, 6), ENTRY(tile_walk, 3), ENTRY(logits_width, 5), ENTRY(dz_columns, 2), ENTRY(logits_tile, 5), ENTRY(store_tile, 4), ENTRY(pair_workgroups, 5), {"set_error", set_error, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};
 

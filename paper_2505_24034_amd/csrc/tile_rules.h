@@ -223,4 +223,24 @@ LLAMARL_RULE int store_width(int64_t Nn) {
   return width < 128 ? 128 : width;
 }
 
+// Workgroups of a contraction in a launch of two (dH and dW on small tiles): `own` and `other` are what a CU holds of either by
+// itself, long: K has PAIR_LONG_SLABS slabs or more (with every row active).  Each takes half of the workgroups (both have the same
+// products to form) and cuts its tiles into fewer parts, except where a tile is few slabs: its first loads and its stores want
+// workgroups.  Backward at (N, V, d), three quarters of the rows active, one contraction after the other / together, each cut for
+// the whole grid / as here, us:
+//   fp32 (256, 1024, 256) 42.2 / 33.0 / 33.0, (1024, 4096, 512) 129 / 119 / 111, (300, 16400, 260) 117 / 120 / 114 (130 on halves),
+//   (4800, 20011, 516) 1622 / 1622 / 1593; bf16 (1041, 5003, 520) 58.8 / 52.8 / 46.4, (512, 8192, 1024) 58.9 / 52.0 / 50.1,
+//   (2048, 4096, 264) 64.6 / 48.3 / 44.6, (4096, 3000, 512) 74.7 / 68.2 / 63.2, (300, 16400, 264) 43.8 / 40.0 / 38.9.
+// The grid is the host's, who does not know how many rows are active; with few of them halves and whole grids are the same within
+// -2 .. +10 %: a tenth active, bf16 (2048, 4096, 264) 38.9 / 30.3 / 31.1, a fifth, fp32 (2048, 8192, 512) 155 / 137 / 125.
+// The kernel's registers are those of the larger body, so two long ones share what a CU holds of that (fp32, three workgroups with
+// 64 x 64 tiles and two with 128 x 128): halves of what each could have alone put a third more workgroups into the plan than run at
+// once.  fp32, halves of its own / as here: (1359, 21070, 68) 255 / 225, (351, 24111, 332) 253 / 213, (2030, 869, 1592) 204 / 180,
+// (346, 3658, 1432) 168 / 146, (700, 3000, 1032) 171 / 167, but (3593, 5092, 76) 159 / 166.  Where one is short the plan is too
+// coarse for either to win everywhere: (66, 11647, 1124) 141 / 134, (79, 18054, 452) 96 / 99, (2452, 219, 1780) 119 / 132.
+constexpr int PAIR_LONG_SLABS = 12;
+LLAMARL_RULE int pair_workgroups(int cus, int own, int other, bool own_long, bool other_long) {
+  return !own_long ? cus * own : cus * (other_long && other < own ? other : own) / 2;
+}
+
 }  // namespace llamarl

@@ -9,7 +9,7 @@ import subprocess
 import pytest
 import yaml
 
-from paper_2505_24034_amd import build
+from paper_2505_24034_amd import binding, build
 
 LLVM = os.path.join(build.rocm_root(), "llvm", "bin")
 
@@ -77,3 +77,18 @@ def test_no_kernel_keeps_vector_registers_in_memory(kernels):
     spilled = {n: (k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for n, k in kernels.items()
                if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
     assert not spilled
+
+
+def test_two_long_contractions_in_a_launch_run_at_once(kernels):
+    rules, seen = binding._load_native(), 0
+    for name, k in kernels.items():
+        if "k_gemm_store_pairINS_13TileGemmSplit" not in name:
+            continue
+        # TileGemmSplit<TileShape<four numbers>, what a CU holds of it by itself, ..> of dH and dW, the second abbreviated if equal
+        own = [int(n) for n in re.findall(r"ILi\dELi\dELi\dELi\dEEELi(\d)E", name)]
+        h, w = own if len(own) == 2 else 2 * own
+        held = 512 // (-(-k[".vgpr_count"] // 8) * 8)          # a workgroup is a wavefront on each SIMD, of 512 registers
+        for cus in (256, 255, 8, 1):
+            assert rules.pair_workgroups(cus, h, w, 1, 1) + rules.pair_workgroups(cus, w, h, 1, 1) <= cus * held, name
+        seen += 1
+    assert seen == 8
