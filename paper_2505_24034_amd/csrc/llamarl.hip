@@ -250,14 +250,17 @@ llamarl_status launch_store_mode(const StoreArgs& a, hipStream_t st) {
   }
   return LLAMARL_OK;
 }
-// f(std::integral_constant<int, MODE>()), see store_final
+// f(std::integral_constant<int, MODE>()), see store_final.  k-major operands are bf16's dH, which is bf16 and never accumulates.
 template <typename G, typename F>
 llamarl_status with_mode(const StoreArgs& a, F&& f) {
-  if (a.c_is_f32) return a.accumulate ? f(std::integral_constant<int, 2>()) : f(std::integral_constant<int, 1>());
-  if constexpr (sizeof(typename G::Type::store_t) == 2) {
-    return a.accumulate ? f(std::integral_constant<int, 4>()) : f(std::integral_constant<int, 3>());
+  if constexpr (G::KMAJOR) {
+    return f(std::integral_constant<int, 3>());
   } else {
-    return fail(LLAMARL_ERR_INVALID_ARG, "a 16-bit output needs a 16-bit input type");
+    if (a.c_is_f32) return a.accumulate ? f(std::integral_constant<int, 2>()) : f(std::integral_constant<int, 1>());
+    if constexpr (sizeof(typename G::Type::store_t) == 2)
+      return a.accumulate ? f(std::integral_constant<int, 4>()) : f(std::integral_constant<int, 3>());
+    else
+      return fail(LLAMARL_ERR_INVALID_ARG, "a 16-bit output needs a 16-bit input type");
   }
 }
 template <typename G>

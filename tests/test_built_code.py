@@ -92,3 +92,10 @@ def test_two_long_contractions_in_a_launch_run_at_once(kernels):
             assert rules.pair_workgroups(cus, h, w, 1, 1) + rules.pair_workgroups(cus, w, h, 1, 1) <= cus * held, name
         seen += 1
     assert seen == 8
+
+
+def test_bf16_dH_is_built_in_its_one_output_form(kernels):
+    # k_gemm_store<TileGemmTN.., MODE>: a bf16 dH is stored in bf16 and never added to what is there (MODE 3)
+    modes = {re.match(r"_ZN7llamarl12k_gemm_storeINS_\d+TileGemmTN(?:Small.*EEE|E)Li(\d)E", n).group(1)
+             for n in kernels if "k_gemm_storeINS_10TileGemmTNE" in n or "k_gemm_storeINS_15TileGemmTNSmall" in n}
+    assert modes == {"3"}
