@@ -384,11 +384,8 @@ __device__ __forceinline__ bool half_slab_left(int K) { return (unsigned)(K - 1)
 // channels of the memory: 256 workgroups streaming 1 GB of W took 235 us (4.5 TB/s) from slab 0, whatever their slabs in flight,
 // and 169 us (6.2) each from a slab of its own.  Workgroups that share a row of patches, and so the panels in their L2, start
 // together; the next row starts two slabs (256 bytes) on.  Forward call over a 128256 x 4096 head: 40 tokens 236 -> 181 us, 150
-// 228 -> 194, 300 309 -> 294.  Only where W streams: with more than TURN_COLUMNS columns of tiles the panels come from the caches.  There
-// 256 and 320 columns have a loop without it (TURN): two more scalar registers through the main loop and eight more scalar
-// operations a slab cost dz of 33001 x 1032 0.3 - 1.6 % (6400 tokens 455 / 461 us, 9500 663 / 671; 128256 x 4096, 8576 tokens: 6434 / 6482)
-// and 320 columns up to 1 % (8576 tokens 6234 / 6284) although nothing turned.  At 225, 500 and 900 tokens of a 128256 x 4096 head
-// turning takes dz from 324 to 271, 470 to 447 and 801 to 789 us.
+// 228 -> 194, 300 309 -> 294; dz at 225, 500 and 900 tokens 324 -> 271, 470 -> 447, 801 -> 789.  Only where W streams: with more
+// than TURN_COLUMNS columns of tiles the panels come from the caches.
 constexpr int TURN_COLUMNS = 4;
 struct SlabOrder {
   int whole, turn;
@@ -398,10 +395,37 @@ struct SlabOrder {
     turn = whole < 2 ? 0 : 2 * row_of_patches & ((1 << (31 - __builtin_clz(whole))) - 1);
   }
   template <int BK>
-  __device__ __forceinline__ int k(int kt) const {        // first k of the kt-th slab taken; past K where there is none
+  __device__ __forceinline__ int k(int kt, int) const {   // first k of the kt-th slab taken; past K where there is none
     const int s = kt + turn;
     return (kt >= whole ? kt : s >= whole ? s - whole : s) * BK;
   }
+  __device__ __forceinline__ bool rest_is_last() const { return true; }
+};
+// Two scalar registers through the main loop and eight scalar operations a slab, which long contractions on 256 columns notice though
+// nothing turns: dz of 33001 x 1032 0.3 - 1.6 % (6400 tokens 455 / 461 us, 9500 663 / 671; 128256 x 4096, 8576 tokens: 6434 / 6482), the
+// forward up to 0.6 %.  dz has a loop in order beside the turned one.  The forward, whose short calls notice a kernel with one loop more (two
+// more: (1700, 5412, 192) 16.3 -> 16.6 us, (128, 98304, 64) 20.1 -> 20.5), wraps round all slabs there, the rest of K among them: one register
+// and three operations.  (kt ^ turn, as cheap, breaks up the runs of slabs that share a line where rows are no multiple of 128 bytes:
+// (256, 49200, 520) 30.0 / 30.9 us, in order 31.4.)
+struct SlabRing {
+  int first;                                              // k of the slab taken first
+  template <int BK>
+  __device__ __forceinline__ void init(int K, int row_of_patches) {
+    first = (2 * row_of_patches & ((1 << (31 - __builtin_clz((K + BK - 1) / BK))) - 1)) * BK;
+  }
+  template <int BK>
+  __device__ __forceinline__ int k(int kt, int K) const {
+    const uint32_t s = (uint32_t)(kt * BK + first);
+    return (int)min(s, s - (uint32_t)((K + BK - 1) & -BK));         // past the end: wrapped; before it the difference is huge
+  }
+  __device__ __forceinline__ bool rest_is_last() const { return first == 0; }
+};
+struct InOrder {
+  template <int BK>
+  __device__ __forceinline__ void init(int, int) {}
+  template <int BK>
+  __device__ __forceinline__ int k(int kt, int) const { return kt * BK; }
+  __device__ __forceinline__ bool rest_is_last() const { return true; }
 };
 
 // The main loop, split in two so that a persistent workgroup can start fetching its NEXT tile before it runs the
@@ -413,8 +437,8 @@ struct SlabOrder {
 //
 // NEAR: a lane's column blocks hold neighbouring output columns (tile_row_of); the epilogue must then take its columns from
 // LanePos::col_near().
-// YOUNGER, FIRST_ONLY: see run().  TURN: slabs in the order of SlabOrder.
-template <typename TT, int LOAD_SLOT, int YOUNGER, bool FIRST_ONLY, bool TURN = false>
+// YOUNGER, FIRST_ONLY: see run().
+template <typename TT, int LOAD_SLOT, int YOUNGER, bool FIRST_ONLY, typename Order = InOrder>
 struct TileGemm {
   typedef TT Type;
   typedef Shape256 Shape;
@@ -427,10 +451,8 @@ struct TileGemm {
   static constexpr int GROUPS_PER_CU = 1;      // workgroups of a persistent grid per CU
   SlabLoader<TT> la, lb;
   int K;
-  SlabOrder order;
+  Order order;
   __device__ __forceinline__ static constexpr int width() { return Shape::BN; }
-
-  __device__ __forceinline__ int k_of(int kt) const { return TURN ? order.k<BK>(kt) : kt * BK; }
 
   template <bool NEAR>
   __device__ __forceinline__ void prefetch(const void* A_tile, int64_t lda, int rowsA, const void* B_tile, int64_t ldb,
@@ -456,7 +478,7 @@ struct TileGemm {
                                                  int64_t b_total, int turn) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
-    if (TURN) order.init<BK>(K, turn);
+    order.template init<BK>(K, turn);
     la.init(A_tile, lda, rowsA, wave, lane);
     lb.template init_gathered<NEAR>(B_base, ldb, b_total, grow, rowsB, wave, lane);
   }
@@ -467,7 +489,7 @@ struct TileGemm {
     const int lane = threadIdx.x & 63, wave = wave_id();
     char* st = smem + (part >> 1) * STAGE_BYTES;
     if (part > 1 && BK >= K) return;
-    const int k0 = k_of(part >> 1);
+    const int k0 = order.template k<BK>(part >> 1, K);
     if ((part & 1) == 0) la.issue(st, k0, K, wave, lane);
     else lb.issue(st + SLAB_A_BYTES, k0, K, wave, lane);
   }
@@ -483,8 +505,8 @@ struct TileGemm {
       char* cur = smem + (kt & 1) * STAGE_BYTES;
       wait_vmcnt0();
       __syncthreads();
-      la.issue(cur, k_of(kt + 2), K, wave, lane);
-      lb.issue(cur + SLAB_A_BYTES, k_of(kt + 2), K, wave, lane);
+      la.issue(cur, order.template k<BK>(kt + 2, K), K, wave, lane);
+      lb.issue(cur + SLAB_A_BYTES, order.template k<BK>(kt + 2, K), K, wave, lane);
     }
     if (nk >= 2) {
       wait_vmcnt0();
@@ -534,7 +556,7 @@ struct TileGemm {
     if (!FIRST_ONLY && nk > 2) {       // slab 0 apart: its barrier waits for slab 1, older than the stores too
       char* cur = smem;
       const char* nxt = smem + STAGE_BYTES;
-      const SlabFetch<SlabLoader<TT>, SlabLoader<TT>> sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, k_of(2), K, wave, lane};
+      const SlabFetch<SlabLoader<TT>, SlabLoader<TT>> sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, order.template k<BK>(2, K), K, wave, lane};
       k_step<TT, true, true, true, LOAD_SLOT, FIRST_ONLY ? 0 : YOUNGER>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0],
                                                                         nxt + b_addr[0], &sf);
       k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
@@ -544,7 +566,7 @@ struct TileGemm {
       char* cur = smem + (kt & 1) * STAGE_BYTES;
       const char* nxt = smem + ((kt + 1) & 1) * STAGE_BYTES;
       LLAMARL_FENCE();
-      const SlabFetch<SlabLoader<TT>, SlabLoader<TT>> sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, k_of(kt + 2), K, wave, lane};
+      const SlabFetch<SlabLoader<TT>, SlabLoader<TT>> sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, order.template k<BK>(kt + 2, K), K, wave, lane};
       k_step<TT, true, true, true, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0], nxt + b_addr[0], &sf);
       k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
     }
@@ -555,7 +577,7 @@ struct TileGemm {
       k_step<TT, true, true, false, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0], nxt + b_addr[0], nullptr);
       k_step<TT, false, true, false, LOAD_SLOT>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
     }
-    if (half_slab_left<BK>(K)) {
+    if (half_slab_left<BK>(K) || !order.rest_is_last()) {
       const char* cur = smem + ((nk - 1) & 1) * STAGE_BYTES;
       LLAMARL_FENCE();
       k_step<TT, false, false, false, LOAD_SLOT>(a, b1, b0, acc, cur + a_addr[1], nullptr, nullptr, nullptr);
@@ -567,7 +589,7 @@ struct TileGemm {
 // As TileGemm (see there); two slabs of 72 KB.  A product takes a tenth fewer bytes from L2 and LDS than on 256 x 256, and a
 // fifth fewer barriers and epilogues.  247 registers.  (A word of every line of W two slabs ahead, to have it in L2 earlier: 300
 // tokens 305 -> 330 us; a barrier that leaves one request in flight for that: the long contractions +2 %.)
-template <typename TT, bool TURN>
+template <typename TT>
 struct TileGemmWide {
   typedef TT Type;
   typedef Shape320 Shape;
@@ -587,15 +609,13 @@ struct TileGemmWide {
   SlabOrder order;
   __device__ __forceinline__ static constexpr int width() { return Shape::BN; }
 
-  __device__ __forceinline__ int k_of(int kt) const { return TURN ? order.k<BK>(kt) : kt * BK; }
-
   template <bool NEAR>
   __device__ __forceinline__ void setup_gathered(const void* A_tile, int64_t lda, int rowsA, const void* B_base,
                                                  int64_t ldb, int rowsB, int64_t K_, const int (&grow)[LoaderB::ITERS],
                                                  int64_t b_total, int turn) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     K = (int)K_;
-    if (TURN) order.init<BK>(K, turn);
+    order.init<BK>(K, turn);
     la.init(A_tile, lda, rowsA, wave, lane);
     lb.template init_gathered<NEAR>(B_base, ldb, b_total, grow, rowsB, wave, lane);
   }
@@ -604,7 +624,7 @@ struct TileGemmWide {
     const int lane = threadIdx.x & 63, wave = wave_id();
     char* st = smem + (part >> 1) * Shape::STAGE_BYTES;
     if (part > 1 && BK >= K) return;
-    const int k0 = k_of(part >> 1);
+    const int k0 = order.k<BK>(part >> 1, K);
     if ((part & 1) == 0) la.issue(st, k0, K, wave, lane);
     else lb.issue(st + SLAB_A_BYTES, k0, K, wave, lane);
   }
@@ -617,8 +637,8 @@ struct TileGemmWide {
       char* cur = smem + (kt & 1) * Shape::STAGE_BYTES;
       wait_vmcnt0();
       __syncthreads();
-      la.issue(cur, k_of(kt + 2), K, wave, lane);
-      lb.issue(cur + SLAB_A_BYTES, k_of(kt + 2), K, wave, lane);
+      la.issue(cur, order.k<BK>(kt + 2, K), K, wave, lane);
+      lb.issue(cur + SLAB_A_BYTES, order.k<BK>(kt + 2, K), K, wave, lane);
     }
     if (nk >= 2) {
       wait_vmcnt0();
@@ -650,7 +670,7 @@ struct TileGemmWide {
       char* cur = smem + (kt & 1) * Shape::STAGE_BYTES;
       const char* nxt = smem + ((kt + 1) & 1) * Shape::STAGE_BYTES;
       LLAMARL_FENCE();
-      const Fetch sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, k_of(kt + 2), K, wave, lane};
+      const Fetch sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, order.k<BK>(kt + 2, K), K, wave, lane};
       wide_k_step<TT, Fetch, true, true, true>(a, b1, b0, acc, cur + a_addr[1], nxt + a_addr[0], nxt + b_addr[0], &sf);
       wide_k_step<TT, Fetch, false, true, false>(a, b0, b1, acc, nxt + a_addr[0], nxt + a_addr[1], nxt + b_addr[1], nullptr);
     }
@@ -789,7 +809,7 @@ struct TileGemmNarrow {
   template <int nb>
   __device__ __forceinline__ void issue(char* st, int kt) const {
     const int lane = threadIdx.x & 63, wave = wave_id();
-    const int k0 = order.k<BK>(kt);
+    const int k0 = order.k<BK>(kt, K);
     la.issue(st, k0, K, wave, lane);
     const i32x4_t rs = lb.rsrc();
 #pragma unroll
@@ -836,7 +856,7 @@ struct TileGemmNarrow {
       st = st == 2 ? 0 : st + 1;
       const char* nxt = stage(smem, st);
       LLAMARL_FENCE();
-      const Fetch sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, order.k<BK>(kt + 3), K, wave, lane};
+      const Fetch sf{&la, &lb, la.rsrc(), lb.rsrc(), cur, order.k<BK>(kt + 3, K), K, wave, lane};
       narrow_k_step<TT, Fetch, nb, true, true, true, 4 + LB, false, LB>(b, a1, a0, acc, cur + b_addr[1], nxt + b_addr[0],
                                                                      nxt + a_addr[0], &sf);
       narrow_k_step<TT, Fetch, nb, false, true, false, 0, false, LB>(b, a0, a1, acc, nxt + b_addr[0], nxt + b_addr[1],

@@ -97,9 +97,9 @@ struct FwdArgs {
 };  // partials and zt are indexed by compacted position, not by token
 
 typedef TileGemm<BF16, 11, 2, true> Logits256;      // counted: the two stores of a token's partials
-typedef TileGemm<BF16, 11, 2, true, true> Logits256Turned;
-typedef TileGemmWide<BF16, false> LogitsWide;
-typedef TileGemmWide<BF16, true> LogitsWideTurned;
+typedef TileGemm<BF16, 11, 2, true, SlabOrder> Logits256Turned;
+typedef TileGemm<BF16, 11, 2, true, SlabRing> Logits256Ring;
+typedef TileGemmWide<BF16> LogitsWide;
 // zeros from an opaque register: as constants the compiler sets them ahead of the branch, for every tile
 template <int M, int N>
 __device__ __forceinline__ void clear(f32x4_t (&acc)[M][N]) {
@@ -125,7 +125,7 @@ __device__ __forceinline__ void run_tile(G& g, char* smem, f32x4_t (&acc)[G::Sha
   }
   if constexpr (nb == 0) {
   } else if constexpr (std::is_same<G, Logits256>::value || std::is_same<G, Logits256Turned>::value ||
-                       std::is_same<G, LogitsWide>::value || std::is_same<G, LogitsWideTurned>::value) g.run(smem, acc, counted);
+                       std::is_same<G, Logits256Ring>::value || std::is_same<G, LogitsWide>::value) g.run(smem, acc, counted);
   else if constexpr (G::HALVES && !G::KMAJOR) g.template run<nb>(smem, acc, counted);
   else if constexpr (G::HALVES) g.template run<nb>(smem, acc);
   else g.run(smem, acc);
@@ -428,16 +428,16 @@ __global__ __launch_bounds__(G::Shape::THREADS, MIN_WAVES<G>) void k_fwd_partial
   };
   if constexpr (HAS_NARROW<G>) {
     const int width = fwd_width(a.tiles_v, n_act, a.d, gridDim.x).width;
-    const bool turn = n_act <= TURN_COLUMNS * width;
-    if (width == LogitsWide::width()) return turn ? walk(LogitsWideTurned()) : walk(LogitsWide());
+    if (width == LogitsWide::width()) return walk(LogitsWide());
     if (width <= NARROW_BN) {
       LogitsNarrow g;
       g.set_width(width);
       return walk(g);
     }
-    if (turn) return walk(Logits256Turned());
+    walk(Logits256Ring());
+  } else {
+    walk(G());
   }
-  walk(G());
 }
 
 // lse[t] = log sum over vocab tiles; logp[t] = z[t,y_t] - lse[t], for the active tokens (the compaction pass
