@@ -91,15 +91,16 @@ constexpr int NARROW_BN = 160;
 //   one, two, few   W comes from HBM: a slab where there are 1, 2 or 3 - 4 columns of tiles (more share W in the caches)
 // 320 columns read a tenth less per product from LDS and L2 and have a fifth fewer tiles to wait for.  Long contractions, which the
 // power limit bounds, hardly gain (7600 .. 10600 tokens of a 128256 x 4096 head: -3 .. +3 % of 256 columns, by the tokens that fill
-// the last column); few rounds do where a fifth fewer tiles fit them, and one or two columns that read W once.  They start
-// at WIDE_MIN_SLABS slabs: shorter tiles gain as much (300 x 49200 x 520 35 -> 32.5 us), but stay on the loops that the tests of short K
-// name.
+// the last column); few rounds do where a fifth fewer tiles fit them, and one or two columns that read W once.  As much at
+// short K, 320 columns against the best of the others: (300, 49200, 72) 21.0 / 19.3 us, (320, 128256, 128) 32.5 / 29.2, (3200, 50304, 128) 101 / 73,
+// (600, 128256, 256) 62.4 / 55.6, (8000, 33001, 264) 170 / 167, (300, 49200, 520) 36.4 / 34.1, (2300, 16032, 576) 56.2 / 50.7; worse
+// at one of 86 such sizes by more than 3 %: (1600, 32000, 520) 70.7 / 73.7.
 // Forward at (N, V, d), 320 / 256 / 160 / 128 columns, us: (150, 128256, 4096) 223 / 230 / 188 / 248, (225, ..) 266 / 246 / 272 / 269,
 // (300, ..) 279 / 366 / 304 / 364, (450, ..) 434 / 426 / 423 / 475, (600, ..) 500 / 550 / 524 / 592, (1250, ..) 955 / 991 / 1044 / 1128,
 // (8576, ..) 6190 / 6348 / 6849 / 7153; (7125, 33001, 1032) 400 / 428 / 465 / 508; (2300, 16032, 8192) 449 / 540 / 486 / 529;
 // (2012, 16032, 8192) 442 / 388 / 464 / 450; (640, 128256, 776) 118 / 127 / 134 / 148.  dz, 256 / 160 / 128: (150, 128256, 4096) 261 / 231 / 267,
 // (225, ..) 265 / 277 / 280, (450, ..) 442 / 429 / 480, (600, ..) 560 / 526 / 597.
-constexpr int WIDTHS = 4, LOGITS_WIDTHS[WIDTHS] = {128, 160, 256, 320}, WIDE_MIN_SLABS = 10;
+constexpr int WIDTHS = 4, LOGITS_WIDTHS[WIDTHS] = {128, 160, 256, 320};
 struct WidthCosts {
   int widths, slab[WIDTHS], tile[WIDTHS], one[WIDTHS], two[WIDTHS], few[WIDTHS];       // the first `widths` of them
 };
@@ -111,21 +112,32 @@ struct LogitsWidth {
   int64_t cost;
 };
 LLAMARL_RULE LogitsWidth logits_width(const WidthCosts& c, int tiles_v, int n_act, int64_t d, int grid) {
-  LogitsWidth best = {256, 0};
   const int nk = (int)((d + 63) / 64);
+  // Every workgroup does this before anything else.  All widths together, without branches: the divisions by the grid share one
+  // reciprocal; one after the other they were 0.1 us of a forward call.
+  int cols[WIDTHS];
+  uint32_t rounds[WIDTHS];
+  bool fits[WIDTHS];
+#pragma unroll
+  for (int h = 0; h < WIDTHS; ++h) {
+    cols[h] = (int)((uint32_t)(n_act + LOGITS_WIDTHS[h] - 1) / (uint32_t)LOGITS_WIDTHS[h]);
+    const int64_t tiles = (int64_t)tiles_v * cols[h];
+    fits[h] = tiles + grid < (1ll << 31);                    // 32-bit division; so many rounds are 256 wide
+    rounds[h] = ((uint32_t)tiles + (uint32_t)grid - 1u) / (uint32_t)grid;
+  }
+  LogitsWidth best = {256, 0};
 #pragma unroll
   for (int i = 0; i < WIDTHS; ++i) {
     const int h = i == 0 ? 2 : i == 3 ? 3 : 2 - i;           // 256 columns, then whatever costs less
-    const int width = LOGITS_WIDTHS[h], cols = (int)((uint32_t)(n_act + width - 1) / (uint32_t)width);
-    const int64_t tiles = (int64_t)tiles_v * cols;
-    if (h >= c.widths || (width == 320 && nk < WIDE_MIN_SLABS)) continue;
-    if (tiles + grid >= (1ll << 31)) continue;               // 32-bit division; so many rounds are 256 wide
+    if (h >= c.widths) continue;
     int slab = c.slab[h];
-    if (d % 64 != 0 && slab < UNALIGNED_SLAB[h]) slab = UNALIGNED_SLAB[h];
-    const int stream = cols == 1 ? c.one[h] : cols == 2 ? c.two[h] : cols <= 4 ? c.few[h] : 0;
-    if (slab < stream) slab = stream;
-    const int64_t cost = (int64_t)((uint32_t)(tiles + grid - 1) / (uint32_t)grid) * (nk * slab + c.tile[h]);
-    if (i == 0 || (best.cost != 0 && cost < best.cost)) best = {width, cost};
+    slab = d % 64 != 0 && slab < UNALIGNED_SLAB[h] ? UNALIGNED_SLAB[h] : slab;
+    const int stream = cols[h] == 1 ? c.one[h] : cols[h] == 2 ? c.two[h] : cols[h] <= 4 ? c.few[h] : 0;
+    slab = slab < stream ? stream : slab;
+    const int64_t cost = (int64_t)rounds[h] * (nk * slab + c.tile[h]);
+    const bool take = fits[h] & ((i == 0) | ((best.cost != 0) & (cost < best.cost)));
+    best.width = take ? LOGITS_WIDTHS[h] : best.width;
+    best.cost = take ? cost : best.cost;
   }
   return best;
 }

@@ -75,8 +75,8 @@ def test_wide_last_token_column(lib, N, d):
 
 # 128 or 160 columns of tokens (dz of the last two sizes at short K: 128 x 128 tiles): one column, two, several, the last one
 # full, of one token, of more than the left half; 1, 2, 3, 4 and 9 slabs of the three that are resident
-@pytest.mark.parametrize("N,V", [(31, 49200), (128, 49200), (129, 49200), (159, 49200), (160, 49200), (300, 49200), (319, 49200),
-                                 (320, 49200), (600, 33000), (900, 10487), (1700, 5412)])
+@pytest.mark.parametrize("N,V", [(31, 49200), (128, 49200), (129, 49200), (159, 49200), (160, 49200), (300, 70000), (319, 70000),
+                                 (320, 70000), (600, 33000), (900, 10487), (1700, 5412)])
 @pytest.mark.parametrize("d", [8, 128, 192, 256, 520])
 def test_narrow_token_tiles(lib, N, V, d):
     assert loops(N, V, d)[0] in ("256x128", "256x160")
@@ -89,6 +89,14 @@ def test_narrow_token_tiles(lib, N, V, d):
 @pytest.mark.parametrize("N,V", [(257, 49200), (320, 49200), (1041, 16380), (1280, 16380), (2241, 8190), (1601, 32700)])
 @pytest.mark.parametrize("d", [584, 640, 648, 704, 1032])
 def test_wide_token_tiles(lib, N, V, d):
+    assert loops(N, V, d)[0] == "256x320"
+    _check_head(lib, N, V, d)
+
+
+# ... at 1, 2, 3, 5 and 9 slabs, the last one up to its half, past it and full
+@pytest.mark.parametrize("N,V", [(257, 49200), (300, 49200), (320, 49200), (1041, 16380), (2241, 8190), (2300, 16032)])
+@pytest.mark.parametrize("d", [8, 40, 72, 104, 168, 192, 264, 520, 576])
+def test_wide_token_tiles_of_few_slabs(lib, N, V, d):
     assert loops(N, V, d)[0] == "256x320"
     _check_head(lib, N, V, d)
 
