@@ -6,9 +6,10 @@
 //   k_bwd_dz         recomputed logits tile -> dz = g * coef * (onehot - softmax), written in both orientations
 //   k_gemm_store     plain contraction with a store epilogue: dW = dz^T H (K-contiguous operands) and
 //                    dH = dz W (k-major operands: dz^T as written, W as the caller holds it; bf16)
+//   k_gemm_store_pair   both of them, where neither is on 256-tiles;  k_reduce_tail, k_reduce_tail_pair: sums of split tiles
 //   k_transpose      [R,C] -> [C,R] with zero padding and row gather (H^T panel of the active tokens)
 //   k_compact_rows   ascending list of active token rows (the backward's is part of k_bwd_setup)
-//   k_bwd_setup      the backward's list, zeroed inactive dH rows, fp32: W^T;  k_reduce_tail: sums of split tiles
+//   k_bwd_setup      the backward's list, zeroed inactive dH rows, fp32: W^T, and H^T of up to SETUP_HT_ROWS rows
 //
 // In the two logits kernels the MFMA "row" operand is W (vocab) and the "column" operand is H (tokens): an
 // accumulator lane then holds ONE token per column block (column = lane % 16) and 4 vocab entries per 16x16

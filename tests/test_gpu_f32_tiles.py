@@ -103,8 +103,8 @@ def test_values_that_cannot_be_split(lib, N, V, d):
 
 
 def test_every_tile_contracted_twice(lib):
-    # 1105 tiles of 128, two or three a workgroup, and in each a value that cannot be split: the slabs that the second pass of a
-    # tile requests past K have to have landed before the next tile's first
+    # 1105 tiles of 128, two or three a workgroup, and in each a value that cannot be split: what a tile's second pass leaves in LDS,
+    # and the flag that asks for it, must not reach the next tile
     test_values_that_cannot_be_split(lib, 2100, 8200, 40)
 
 

@@ -21,10 +21,28 @@ SIZES = [
 
 
 @pytest.mark.parametrize("dt,N,V,d,share,edges", SIZES)
-@pytest.mark.parametrize("form", ["plain", "accumulate", "fp32", "fp32 accumulate", "passes", "no rows"])
+@pytest.mark.parametrize("form", ["plain", "accumulate", "fp32", "fp32 accumulate", "no rows"])
 def test_pair(lib, dt, N, V, d, share, edges, form):
+    assert loops(N, V, d, dt == "bf16")[2:] == edges
+    _check_pair(lib, dt, N, V, d, share, form)
+
+
+# ... in passes of R rows, which pick their tiles by R: the first full, the second partly filled and added to the first's dW, the
+# third empty
+@pytest.mark.parametrize("dt,N,V,d,R,edges", [
+    ("bf16", 552, 130, 264, 256, ("64", "64")), ("bf16", 552, 9001, 264, 256, ("64", "128")),
+    ("bf16", 2088, 1000, 2056, 1024, ("128", "128")), ("bf16", 2088, 130, 2056, 1024, ("128", "64")),
+    ("f32", 552, 1000, 264, 256, ("64", "64")), ("f32", 552, 9001, 520, 256, ("64", "128")),
+    ("f32", 552, 9001, 1032, 256, ("128", "128")), ("f32", 1576, 3000, 1032, 768, ("128", "64")),
+])
+@pytest.mark.parametrize("form", ["fp32", "fp32 accumulate"])
+def test_pair_in_passes(lib, dt, N, V, d, R, edges, form):
+    assert loops(R, V, d, dt == "bf16")[2:] == edges
+    _check_pair(lib, dt, N, V, d, 0.7, form, R)
+
+
+def _check_pair(lib, dt, N, V, d, share, form, rows_per_pass=None):
     bf16 = dt == "bf16"
-    assert loops(N, V, d, bf16)[2:] == edges
     store = torch.bfloat16 if bf16 else torch.float32
     g = torch.Generator(device="cuda").manual_seed(N + V + d)
     H = torch.randn(N, d, generator=g, device="cuda").to(store)
@@ -40,13 +58,14 @@ def test_pair(lib, dt, N, V, d, share, edges, form):
     rdH, rdW = dz @ W.double(), dz.T @ H.double()
     old = torch.randn(V, d, generator=g, device="cuda") * rdW.std().float()
     kw = {}
-    if "fp32" in form or form == "passes":
+    if "fp32" in form:
         kw["dW_dtype"] = torch.float32
     if "accumulate" in form:
         kw.update(dW=old.to(torch.float32 if "fp32" in form else store), accumulate_dW=True)
         rdW = rdW + kw["dW"].double()
-    if form == "passes":
-        kw["max_rows_per_pass"] = 256
+    if rows_per_pass:
+        assert rows_per_pass < int((coef != 0).sum()) <= 2 * rows_per_pass
+        kw["max_rows_per_pass"] = rows_per_pass
     dH, dW = lib.offpolicy_loss_bwd(H, W, y.int(), lse.float(), coef, **kw)
     # An entry is a sum of K products.  bf16: each dz is rounded once, by up to 2^-8 of it (8 significant bits); the stored result once more.  In both types
     # exp(z - lse) carries the logits' and lse's own rounding, |z| <= 8: 8 sqrt(d) 2^-24 and 10 2^-24, below 2^-15, and the

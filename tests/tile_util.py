@@ -4,8 +4,8 @@ from paper_2505_24034_amd import binding
 
 
 def loops(N, V, d, bf16=True, active=None):
-    """(forward, dz, dH, dW): "64", "128" or "256", the tiles' edge; "256x128", "256x160" or "256x256" for the logits kernels of
-    256 vocabulary rows.  active: rows with gradient (all)"""
+    """(forward, dz, dH, dW): "64", "128" or "256", the tiles' edge; "256x128", "256x160", "256x256" or, forward only,
+    "256x320" for the logits kernels of 256 vocabulary rows.  active: rows with gradient (all)"""
     r = binding._load_native()
     tiles_v = -(-V // 256)
 
